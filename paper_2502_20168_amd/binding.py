@@ -4,6 +4,10 @@ Every function has the name of the C entry point it calls (include/ssm.h).  Tens
 tensors that live on the GPU; torch is used for device memory and for the current stream and for
 nothing else -- all arithmetic of the layer runs in the HIP kernels of the library.  There is no
 CPU fallback: if the library has not been built, loading raises.
+
+The calls of a training or serving loop go through _ssmbind (csrc/pybind.cpp), which checks the arguments, allocates
+the outputs and makes the C call natively.  It answers None for arguments that it does not take; the general
+path here, through ctypes, then checks them one by one and raises the error that names the argument.
 """
 from __future__ import annotations
 
@@ -35,7 +39,10 @@ EXPORTS = ("ssm_strerror", "ssm_version", "ssm_workspace_bytes", "ssm_discretize
            "ssm_half_glu_bwd", "ssm_block_workspace_bytes", "ssm_block_fwd", "ssm_block_bwd", "ssm_set_spin_limit",
            "ssm_scan_states_noalloc", "ssm_scan_states_noalloc_status", "ssm_plan_describe")
 
+BIND_PATH = os.path.join(HERE, "_ssmbind.so")
+
 _lib = None
+_native = None
 _vp, _i64, _sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_size_t
 
 
@@ -113,6 +120,29 @@ def lib():
         L.ssm_block_bwd.argtypes = [_vp] * 9 + [_i64] * 4 + [_vp] * 4 + [_vp] * 8 + [_vp, _sz, _vp]
         _lib = L
     return _lib
+
+
+def _bind():
+    """The native half of the binding (loaded behind the library, which it is linked to)."""
+    global _native
+    if _native is None:
+        lib()
+        if not os.path.exists(BIND_PATH):
+            raise ImportError("_ssmbind.so is not built: run `python paper_2502_20168_amd/build.py` first")
+        from . import _ssmbind
+        _native = _ssmbind
+    return _native
+
+
+def _handle(stream):
+    return None if stream is None else stream.cuda_stream
+
+
+def _done(r, where):
+    """Result of a native call that was made: its outputs, or the library's error."""
+    if type(r) is int:
+        raise SsmError(r, where)
+    return r
 
 
 def strerror(code: int) -> str:
@@ -207,6 +237,11 @@ def ssm_scan_fwd(Lambda, B, C, D, log_delta, u, is_first=None, x0=None, *, want_
                  want_x_last=True, workspace=None, stream=None, out=None,
                  profile=False) -> Dict[str, object]:
     """Forward pass.  Returns dict(y, x or None, x_last or None[, stage_ms])."""
+    if not profile:
+        r = (_native or _bind()).scan_fwd(Lambda, B, C, D, log_delta, u, is_first, x0, want_x, want_x_last, workspace, _handle(stream),
+                                          out)
+        if r is not None:
+            return _done(r, "ssm_scan_fwd")
     torch = _torch()
     Bt, L, H, P = _check_inputs(Lambda, B, C, D, log_delta, u, is_first, x0)
     out = out or {}
@@ -233,6 +268,10 @@ def ssm_scan_fwd(Lambda, B, C, D, log_delta, u, is_first=None, x0=None, *, want_
 def ssm_scan_bwd(Lambda, B, C, D, log_delta, u, is_first, x0, x, dy, *, want_dx0=True,
                  workspace=None, stream=None, out=None, profile=False) -> Dict[str, object]:
     """Gradient pass.  Returns dict(du, dLambda, dB, dC, dD, dlog_delta, dx0 or None[, stage_ms])."""
+    if not profile:
+        r = (_native or _bind()).scan_bwd(Lambda, B, C, D, log_delta, u, is_first, x0, x, dy, want_dx0, workspace, _handle(stream), out)
+        if r is not None:
+            return _done(r, "ssm_scan_bwd")
     torch = _torch()
     Bt, L, H, P = _check_inputs(Lambda, B, C, D, log_delta, u, is_first, x0)
     _chk(x, torch.complex64, (Bt, L, P), "x")
@@ -267,6 +306,9 @@ def ssm_scan_bwd(Lambda, B, C, D, log_delta, u, is_first, x0, x, dy, *, want_dx0
 
 def ssm_scan_states(A_bar, v, is_first=None, x0=None, *, want_x_last=True, workspace=None, stream=None):
     """In-place resettable scan of v [Bt,L,P] (becomes x).  Returns (v, x_last or None)."""
+    r = (_native or _bind()).scan_states(A_bar, v, is_first, x0, want_x_last, workspace, _handle(stream))
+    if r is not None:
+        return v, _done(r, "ssm_scan_states")[0]
     torch = _torch()
     Bt, L, P = v.shape
     _chk(A_bar, torch.complex64, (P,), "A_bar")
@@ -306,6 +348,9 @@ def ssm_scan_states_noalloc_status(stream=None) -> int:
 def ssm_scan_states_reverse(A_bar, gx, x, is_first=None, x0=None, *, want_dx0=True, workspace=None,
                             stream=None):
     """In-place reverse scan of gx [Bt,L,P] (becomes chi).  Returns (gx, dA_bar, dx0 or None)."""
+    r = (_native or _bind()).scan_states_reverse(A_bar, gx, x, is_first, x0, want_dx0, workspace, _handle(stream))
+    if r is not None:
+        return (gx,) + _done(r, "ssm_scan_states_reverse")
     torch = _torch()
     Bt, L, P = gx.shape
     _chk(A_bar, torch.complex64, (P,), "A_bar")
@@ -329,6 +374,9 @@ def ssm_step_plan_bytes(H: int, P: int) -> int:
 
 def ssm_step_prepare(Lambda, B, C, log_delta, stream=None):
     """Discretise and pack the parameters once per roll-out.  Returns the plan (a cuda byte tensor)."""
+    r = (_native or _bind()).step_prepare(Lambda, B, C, log_delta, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_step_prepare")
     torch = _torch()
     P, H = B.shape
     _chk(Lambda, torch.complex64, (P,), "Lambda")
@@ -345,6 +393,9 @@ def ssm_step_prepare(Lambda, B, C, log_delta, stream=None):
 
 def ssm_step(plan, D, u, x_prev=None, is_first=None, *, P=None, x=None, y=None, stream=None):
     """One transition.  u [Bt,H], x_prev [Bt,P] or None, is_first [Bt] u8 or None.  Returns (x, y)."""
+    r = (_native or _bind()).step(plan, D, u, x_prev, is_first, P, x, y, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_step")
     torch = _torch()
     Bt, H = u.shape
     if P is None:
@@ -364,6 +415,9 @@ def ssm_step(plan, D, u, x_prev=None, is_first=None, *, P=None, x=None, y=None, 
 
 def ssm_step_bwd(plan, D, dy, dx=None, is_first=None, *, P, want_dx_prev=True, stream=None):
     """Adjoint of one transition.  dy [Bt,H], dx [Bt,P] or None.  Returns (gx, du, dx_prev)."""
+    r = (_native or _bind()).step_bwd(plan, D, dy, dx, is_first, P, want_dx_prev, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_step_bwd")
     torch = _torch()
     Bt, H = dy.shape
     _chk(D, torch.float32, (H,), "D")
@@ -382,6 +436,9 @@ def ssm_step_bwd(plan, D, dy, dx=None, is_first=None, *, P, want_dx_prev=True, s
 
 def ssm_lambda_return(reward, cont, value, gamma: float, lam: float, *, ret=None, stream=None):
     """Time-major [T, N] float32 tensors.  Returns ret [T, N]."""
+    r = (_native or _bind()).lambda_return(reward, cont, value, gamma, lam, ret, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_lambda_return")
     torch = _torch()
     T, N = reward.shape
     for name, t in (("reward", reward), ("cont", cont), ("value", value), ("ret", ret)):
@@ -395,6 +452,9 @@ def ssm_lambda_return(reward, cont, value, gamma: float, lam: float, *, ret=None
 
 def ssm_lambda_return_bwd(cont, value, ret, dret, gamma: float, lam: float, *, stream=None):
     """Returns (dreward, dcont, dvalue), each [T, N]."""
+    r = (_native or _bind()).lambda_return_bwd(cont, value, ret, dret, gamma, lam, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_lambda_return_bwd")
     torch = _torch()
     T, N = cont.shape
     for name, t in (("cont", cont), ("value", value), ("ret", ret), ("dret", dret)):
@@ -426,6 +486,9 @@ def _glu_workspace(T, H, want_bwd, device):
 
 def ssm_half_glu_fwd(u, W, *, want_gate=True, workspace=None, y=None, gate=None, stream=None):
     """u [T, H], W [H, H] float32.  Returns (y, gate); gate is None unless asked for."""
+    r = (_native or _bind()).half_glu_fwd(u, W, want_gate, workspace, y, gate, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_half_glu_fwd")
     torch = _torch()
     T, H = u.shape
     _chk(u, torch.float32, (T, H), "u")
@@ -444,6 +507,9 @@ def ssm_half_glu_fwd(u, W, *, want_gate=True, workspace=None, y=None, gate=None,
 
 def ssm_half_glu_bwd(u, W, gate, dy, *, workspace=None, du=None, dW=None, stream=None):
     """Returns (du [T, H], dW [H, H])."""
+    r = (_native or _bind()).half_glu_bwd(u, W, gate, dy, workspace, du, dW, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_half_glu_bwd")
     torch = _torch()
     T, H = u.shape
     for name, t in (("u", u), ("gate", gate), ("dy", dy), ("du", du)):
@@ -475,6 +541,9 @@ def _block_workspace(Bt, L, H, P, want_bwd, device):
 def ssm_block_fwd(Lambda, B, C, D, log_delta, W, u, is_first=None, x0=None, *, want_gate=True, workspace=None,
                   stream=None):
     """SSM layer followed by the half-GLU gate.  Returns dict(y, out, gate, x, x_last)."""
+    r = (_native or _bind()).block_fwd(Lambda, B, C, D, log_delta, u, is_first, x0, W, want_gate, workspace, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_block_fwd")
     torch = _torch()
     Bt, L, H = u.shape
     P = Lambda.shape[0]
@@ -502,6 +571,9 @@ def ssm_block_fwd(Lambda, B, C, D, log_delta, W, u, is_first=None, x0=None, *, w
 
 def ssm_block_bwd(Lambda, B, C, D, log_delta, W, u, is_first, x0, x, y, gate, dout, *, workspace=None, stream=None):
     """Gradient pass of ssm_block_fwd.  Returns dict(du, dLambda, dB, dC, dD, dlog_delta, dx0, dW)."""
+    r = (_native or _bind()).block_bwd(Lambda, B, C, D, log_delta, u, is_first, x0, W, x, y, gate, dout, workspace, _handle(stream))
+    if r is not None:
+        return _done(r, "ssm_block_bwd")
     torch = _torch()
     Bt, L, H = u.shape
     P = Lambda.shape[0]

@@ -1,15 +1,20 @@
 """Builds libssmscan.so (HIP, gfx950 only) in-tree with hipcc: one object per source, compiled in
-parallel, then one link."""
+parallel, then one link.  Beside it _ssmbind.so, the native half of the Python binding (host code only, against
+torch's C++ headers), which is linked to the library."""
 from __future__ import annotations
 
 import concurrent.futures
+import importlib.util
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssmscan.so")
+BIND = os.path.join(HERE, "_ssmbind.so")
+BIND_SOURCE = os.path.join(CSRC, "pybind.cpp")
 SOURCES = ["ssm_api.hip", "gemm.hip", "gemm_inst2.hip", "gemm_inst3.hip", "gemm_pair.hip", "scan.hip", "params.hip",
            "block.hip", "noalloc.hip"]
 HEADERS = [os.path.join(CSRC, h) for h in ("ssm_internal.h", "gemm_common.h", "gemm_kernel.h", "lookback.h")] + \
@@ -25,11 +30,12 @@ def _newest_header() -> float:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(BIND):
         return True
     t = os.path.getmtime(LIB)
     deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS
-    return any(os.path.getmtime(d) > t for d in deps)
+    return any(os.path.getmtime(d) > t for d in deps) or any(os.path.getmtime(d) > os.path.getmtime(BIND)
+                                                             for d in [BIND_SOURCE] + HEADERS)
 
 
 def _compile(hipcc: str, src: str, obj: str, verbose: bool) -> None:
@@ -37,6 +43,17 @@ def _compile(hipcc: str, src: str, obj: str, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+
+
+def _bind_command(out: str):
+    """The host compiler's command for the native half of the binding (torch is located, not imported)."""
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    inc, lib = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-w",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", BIND_SOURCE, "-o", out,
+            "-L" + HERE, "-lssmscan", "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python",
+            "-Wl,-rpath,$ORIGIN"]
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -65,6 +82,13 @@ def build(force: bool = True, verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
+    if force or not os.path.exists(BIND) or os.path.getmtime(BIND) < max(os.path.getmtime(BIND_SOURCE), hdr_t):
+        tmp = BIND + ".tmp%d" % os.getpid()
+        cmd = _bind_command(tmp)
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+        os.replace(tmp, BIND)
     return LIB
 
 
