@@ -183,14 +183,11 @@ def main():
     scans = (((L % 128 == 0 and L // 128 <= 32) or (L in (16, 32, 64) and T % 128 == 0))
              and (T // 128) * ((2 * P + 127) // 128) >= 64)
     products = 3 if scans else 6
-    t128 = ((T + 127) // 128) * ((H + 127) // 128)
-    out_split = t128 < 200 and 2 * t128 >= 200 and P >= 256 and (2 * P) % 64 == 0
     # every launch of the projection kernel in one step: role, fp32 flops, duration
     if scans:
         launches = [
             {"role": "input projection + forward scan in the tile (S2 + S3)", "gemms": 1, "ms": fs[1]},
-            {"role": "output projection" + (" + D u on 64x128 tiles" if out_split else " + D u")
-                     + " (S4)", "gemms": 1, "ms": fs[3]},
+            {"role": "output projection + D u (S4)", "gemms": 1, "ms": fs[3]},
             {"role": "C^H dy + reverse scan in the tile (S5 + S6)", "gemms": 1, "ms": bs[1]},
             {"role": "Re(Bbar^H chi) + D dy, the dBbar slabs and the dC slabs, one launch, two workgroups per CU (S7 + S5)",
              "gemms": 3, "ms": bs[3]},
@@ -208,12 +205,12 @@ def main():
         l["executed_tflops"] = round(products * l["fp32_flops"] / (l["ms"] * 1e-3) / 1e12, 1)
         l["frac_of_f16_matrix_peak"] = round(l["executed_tflops"] / PEAK_F16_MFMA_TFLOPS, 4)
         l["us"] = round(float(l.pop("ms")) * 1e3, 2)
-    # Dominant kernel = the launch of gemm_ws_kernel with the largest share of the step.  Its algorithmic
+    # Dominant kernel = the launch of gemm_pk_kernel with the largest share of the step.  Its algorithmic
     # work: the partial products per multiply-add that its operand split needs.
     dom = max(launches, key=lambda l: l["us"])
     dom_fp32_tflops = dom["fp32_flops"] / (dom["us"] * 1e-6) / 1e12
     ach = products * dom_fp32_tflops
-    roofline = {"kernel": "gemm_ws_kernel (%s)" % dom["role"],
+    roofline = {"kernel": "gemm_pk_kernel (%s)" % dom["role"],
                 "bound": "mfma", "achieved": round(ach, 1), "peak": PEAK_F16_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ach / PEAK_F16_MFMA_TFLOPS, 4),
                 "traffic": None,
@@ -399,7 +396,7 @@ def step_mode(ssm, torch, d, H, P, Bt=1024, horizon=10):
                          "fwd_achieved": round(exe(f_ms), 1), "fwd_frac": round(exe(f_ms) / PEAK_F16_MFMA_TFLOPS, 4),
                          "bwd_achieved": round(exe(b_ms), 1), "bwd_frac": round(exe(b_ms) / PEAK_F16_MFMA_TFLOPS, 4),
                          "fp32_equivalent_tflops_fwd": round(flops / (f_ms * 1e-3) / 1e12, 1)},
-            "note": "dependent steps (two GEMM launches each on 64x64x64 tiles, three bf16 planes), replayed as one HIP "
+            "note": "dependent steps (two launches of products each on tiles of 32 rows, three bf16 planes), replayed as one HIP "
                     "graph; bound by the latency of two dependent launches, not by throughput"}
 
 
@@ -425,7 +422,7 @@ def s5_block(ssm, torch, wl, d, Bt, L, H, P, iters=10):
                          "fwd_achieved": round(exe_f, 1), "fwd_frac": round(exe_f / PEAK_F16_MFMA_TFLOPS, 4),
                          "bwd_achieved": round(exe_b, 1), "bwd_frac": round(exe_b / PEAK_F16_MFMA_TFLOPS, 4)},
             "note": "layer + gate, forward and gradient pass, replayed as HIP graphs (includes the binding's output "
-                    "allocations inside the graph); GELU of the layer output is formed where the output projection's result is stored (on 64x128 tiles at this shape)"}
+                    "allocations inside the graph); GELU of the layer output is formed where the output projection's result is stored"}
 
 
 def block_ops(ssm, torch, wl, T, H, iters=20):

@@ -41,8 +41,8 @@
  *     128, and the batch gives at least 64 tiles of 128 tokens x 64 states) an operand is staged as two
  *     fp16 planes of the operand scaled by a power of two (three partial products, errors at the level
  *     of fp32 products): u, x, dy and chi get a scale per token where tokens are the rows of the
- *     product, the weights and the operands of the sums over tokens one per matrix.  Under one scale
- *     with largest magnitude m an element a is held with an absolute error of at most
+ *     product and the weights one per column of its result, the operands of the sums over tokens one
+ *     per matrix.  Under one scale with largest magnitude m an element a is held with an absolute error of at most
  *     max(2^-22 |a|, 2^-39 m): elements more than 2^17 below m are fixed-point, not floating-point.
  *     The same staging is used at other sequence lengths when H >= 512, P >= 512 and Bt * L is large
  *     enough that every product has more than 64 tiles of 128 x 128 (the scan kernels then record the

@@ -21,10 +21,10 @@ extern "C" {
  *   forward : [0] discretise+pack, [1] input projection, [2] scan, [3] output projection
  *   backward: [0] discretise+pack and dD partials, [1] gx = C^H dy (with the reverse scan in its tiles
  *             where the shape allows), [2] reverse scan kernel, [3] du with the dBbar and dC partials
- *             (one launch), [4] empty (the sum of the two halves of du shares the next launch),
+ *             (one launch), [4] empty,
  *             [5] parameter epilogue
- * A stage that holds no kernel on this call (a scan that runs inside its projection, a product that
- * is not run as two halves) reads as the few microseconds between two events.                   */
+ * A stage that holds no kernel on this call (a scan that runs inside its projection, [4]) reads as the
+ * few microseconds between two events.                                                          */
 ssm_status ssm_scan_fwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C,
                                  const float *D, const float *log_delta, const float *u,
                                  const uint8_t *is_first, const ssm_c64 *x0,
@@ -50,8 +50,9 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
  *   [4] gradient pass: 3 = du, dBbar slabs and dC slabs in one launch; 2 = two launches of two products
  *   [5] 1 when the slab work items take the first slots of the launch of [4] == 3
  *   [6], [7] the same for the launches of C^H dy with dC and of du with dBbar when [4] == 2
- *   [8] 1 when du runs as two K halves that the parameter epilogue's launch adds
- *   [9] tile tier of the input projection, [10] of the output projection (0: 128x128x32, 1: 64x128x32, 2: 64x64x64)
+ *   [8] always 0 (du is one product)
+ *   [9] tile tier of the input projection, [10] of the output projection: how coarse a tile a product of this
+ *       size can afford by rounds of workgroups (0: 128x128, 1: 64x128, 2: 64x64)
  *   [11] workgroups along time of the scan kernels (1: no look-back; unused when [0] == 1)
  * Returns SSM_ERR_INVALID_ARG / SSM_ERR_UNSUPPORTED for shapes the library does not take.           */
 #define SSM_PLAN_FIELDS 12

@@ -1,8 +1,7 @@
 // Operations around the SSM layer (gfx950): the bootstrapped lambda-return of the actor-critic
 // section and the half-GLU gate of the S5 sequence layer (appendix), with their adjoints.
 #include "../../include/ssm.h"
-#include "ssm_internal.h"
-#include "gemm_common.h"
+#include "pack.h"
 
 namespace ssm {
 namespace {
@@ -87,10 +86,13 @@ __global__ void __launch_bounds__(256) lambda_return_bwd_kernel(const float *__r
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float gelu_exact(float x) { return gelu_value(x); }
 
+// Every element-wise pass also packs W for the product behind it, in workgroups of its own at the head of the grid.
 __global__ void __launch_bounds__(256) gelu_kernel(const float4 *__restrict__ u, float4 *__restrict__ x1, long n4,
-                                                   const float *__restrict__ ut, float *__restrict__ x1t, long n)
+                                                   const float *__restrict__ ut, float *__restrict__ x1t, long n, PackSrc src, PackJob w)
 {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
+    if ((int)blockIdx.x < w.nblocks) { pack_block<PACK_WN>(src, w, blockIdx.x, lds); return; }
+    const long i = (long)(blockIdx.x - w.nblocks) * 256 + threadIdx.x;
     if (i < n4) {
         const float4 a = u[i];
         x1[i] = make_float4(gelu_exact(a.x), gelu_exact(a.y), gelu_exact(a.z), gelu_exact(a.w));
@@ -106,9 +108,11 @@ __global__ void __launch_bounds__(256) gelu_kernel(const float4 *__restrict__ u,
 __global__ void __launch_bounds__(256) gate_bwd_prep_kernel(const float *__restrict__ u, const float *__restrict__ s,
                                                             const float *__restrict__ dy, float *__restrict__ x1,
                                                             float *__restrict__ dz, float *__restrict__ ds,
-                                                            float *__restrict__ gd, long n)
+                                                            float *__restrict__ gd, long n, PackSrc src, PackJob w)
 {
-    const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
+    if ((int)blockIdx.x < w.nblocks) { pack_block<PACK_WT>(src, w, blockIdx.x, lds); return; }
+    const long i0 = ((long)(blockIdx.x - w.nblocks) * 256 + threadIdx.x) * 4;
     if (i0 + 4 <= n) {
         const float4 a = *reinterpret_cast<const float4 *>(u + i0);
         const float4 g = *reinterpret_cast<const float4 *>(s + i0);
@@ -135,7 +139,7 @@ __global__ void __launch_bounds__(256) gate_bwd_prep_kernel(const float *__restr
 // operands as two scaled fp16 planes (three matrix instructions per k block instead of six): they also
 // measure the largest magnitudes that scale those planes -- of every token row of the product's first
 // operand in pieces of 64 columns (rowmax[piece][row]; 16 neighbouring lanes hold one piece), of a whole
-// operand per workgroup (slots[workgroup]), and of W by the extra workgroups behind the first main_blocks.
+// operand per workgroup (slots[workgroup]).
 __device__ __forceinline__ unsigned abs_bits4(float4 v)
 {
     return __float_as_uint(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
@@ -155,31 +159,15 @@ __device__ __forceinline__ unsigned block_max(unsigned v, unsigned *red)
     __syncthreads();
     return max(max(red[0], red[1]), max(red[2], red[3]));
 }
-__device__ __forceinline__ void weight_max_block(const float *__restrict__ W, long nW, unsigned *__restrict__ wslots,
-                                                 int b, int nb, unsigned *red)
-{
-    unsigned m = 0;
-    if ((reinterpret_cast<uintptr_t>(W) & 15) == 0 && nW % 4 == 0) {
-        const float4 *W4 = reinterpret_cast<const float4 *>(W);
-        for (long j = (long)b * 256 + threadIdx.x; j < nW / 4; j += (long)nb * 256) m = max(m, abs_bits4(W4[j]));
-    } else {
-        for (long j = (long)b * 256 + threadIdx.x; j < nW; j += (long)nb * 256) m = max(m, __float_as_uint(fabsf(W[j])));
-    }
-    m = block_max(m, red);
-    if (threadIdx.x == 0) wslots[b] = m;
-}
-
 __global__ void __launch_bounds__(256) gelu_max_kernel(const float4 *__restrict__ u, float4 *__restrict__ x1, long n4,
-                                                       int H, long T, unsigned *__restrict__ rowmax,
-                                                       const float *__restrict__ W, long nW,
-                                                       unsigned *__restrict__ wslots, int w_blocks)
+                                                       int H, long T, unsigned *__restrict__ rowmax, PackSrc src, PackJob w)
 {
-    __shared__ unsigned red[4];
-    if ((int)blockIdx.x < w_blocks) {                    // (first in the grid: their short chains of loads start at once)
-        weight_max_block(W, nW, wslots, (int)blockIdx.x, w_blocks, red);
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
+    if ((int)blockIdx.x < w.nblocks) {                   // (first in the grid: their chains of loads start at once)
+        pack_block<PACK_WN>(src, w, blockIdx.x, lds);
         return;
     }
-    const long i = (long)(blockIdx.x - w_blocks) * 256 + threadIdx.x;
+    const long i = (long)(blockIdx.x - w.nblocks) * 256 + threadIdx.x;
     unsigned m = 0;
     if (i < n4) {                                        // (n4 is a multiple of 16: a row piece is in or out as a whole)
         const float4 a = u[i];
@@ -200,15 +188,15 @@ __global__ void __launch_bounds__(256) gate_bwd_prep_max_kernel(const float *__r
                                                                 float *__restrict__ gd, long n, int H, long T,
                                                                 unsigned *__restrict__ dz_rowmax,
                                                                 unsigned *__restrict__ x1_slots, unsigned *__restrict__ dz_slots,
-                                                                const float *__restrict__ W, long nW,
-                                                                unsigned *__restrict__ wslots, int w_blocks)
+                                                                PackSrc src, PackJob w)
 {
-    __shared__ unsigned red[4];
-    if ((int)blockIdx.x < w_blocks) {
-        weight_max_block(W, nW, wslots, (int)blockIdx.x, w_blocks, red);
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
+    unsigned *red = reinterpret_cast<unsigned *>(lds);
+    if ((int)blockIdx.x < w.nblocks) {
+        pack_block<PACK_WT>(src, w, blockIdx.x, lds);
         return;
     }
-    const int b = (int)blockIdx.x - w_blocks, main_blocks = (int)gridDim.x - w_blocks;
+    const int b = (int)blockIdx.x - w.nblocks, main_blocks = (int)gridDim.x - w.nblocks;
     const long stride = (long)main_blocks * 1024;
     unsigned mx = 0, mz = 0;
     for (long base = ((long)b * 256 + threadIdx.x) * 4; base < n; base += 4 * stride) {
@@ -263,12 +251,11 @@ __global__ void __launch_bounds__(256) sum_slabs_kernel(const float *__restrict_
 }
 
 constexpr int GLU_MAX_SLOTS = 512;      // workgroups of the element-wise pass that report a maximum each
-constexpr int GLU_W_BLOCKS = 256;       // workgroups that measure W
 struct GluLayout {
-    size_t x1, dz, ds, gd, dWpart, total; int splits;
+    size_t x1, dz, ds, gd, dWpart, wfrag, wexp, total; int splits, planes;
     // widths that are multiples of 64: two scaled fp16 planes per operand, with their largest magnitudes
     bool two_planes; size_t rowmax, slots; int row_parts, main_blocks;
-    bool paired, dw_first;     // gradient pass: dz W^T and the slabs of x1^T dz in one launch (dW's work items first)
+    bool dw_first;             // gradient pass, one launch for dz W^T and the slabs of x1^T dz: dW's work items first
 };
 
 bool make_glu_layout(int64_t T, int64_t H, bool bwd, GluLayout &o)
@@ -278,16 +265,18 @@ bool make_glu_layout(int64_t T, int64_t H, bool bwd, GluLayout &o)
     o.x1 = off; off += up((size_t)T * H * 4);
     o.dz = o.ds = o.gd = o.dWpart = 0; o.splits = 1;
     o.two_planes = gate_two_planes_shape(T, H);
-    // gradient pass on two planes: both products wait for the same element-wise pass and share one launch, the
-    // K splits of the reduction from the schedule model of that launch (no K halves of du then: the slabs
-    // fill the chip beside it)
-    o.paired = bwd && o.two_planes; o.dw_first = false;
+    // gradient pass: both products wait for the same element-wise pass and share one launch; on two planes the K
+    // splits of the reduction come from the schedule model of that launch
+    o.planes = o.two_planes ? 2 : 3; o.dw_first = false;
+    o.wfrag = off; off += up(packed_frag_bytes(H, H, o.planes));
+    o.wexp = off; off += up((size_t)(H + 31) / 32 * 32 * 4);
     if (bwd) {
         o.dz = off; off += up((size_t)T * H * 4);
         o.ds = off; off += up((size_t)T * H * 4);
         o.gd = off; off += up((size_t)T * H * 4);
-        o.splits = o.paired ? gemm_pick_splits_balanced(H, H, T, ((T + 127) / 128) * ((H + 127) / 128), H, o.dw_first)
-                            : gemm_pick_splits(H, H, T, 0);
+        if (o.two_planes) o.splits = gemm_pick_splits_balanced(H, H, T, ((T + 127) / 128) * ((H + 127) / 128), H, o.dw_first);
+        else if (gemm_small_pair(T, H)) o.splits = gemm_pick_splits_small(H, H, T, T, H, H);
+        else o.splits = gemm_pick_splits(H, H, T, ((T + 127) / 128) * ((H + 127) / 128));
     }
     if (bwd) { o.dWpart = off; off += up((size_t)o.splits * H * H * 4); }
     o.rowmax = o.slots = 0; o.row_parts = o.main_blocks = 0;
@@ -296,10 +285,25 @@ bool make_glu_layout(int64_t T, int64_t H, bool bwd, GluLayout &o)
         const int64_t blocks = (T * H / 4 + 255) / 256;
         o.main_blocks = (int)(bwd ? (blocks < GLU_MAX_SLOTS ? blocks : GLU_MAX_SLOTS) : blocks);
         o.rowmax = off; off += up((size_t)o.row_parts * T * 4);
-        o.slots = off; off += up((size_t)(2 * GLU_MAX_SLOTS + GLU_W_BLOCKS) * 4);     // x1, dz, W
+        o.slots = off; off += up((size_t)(2 * GLU_MAX_SLOTS) * 4);     // x1, dz
     }
     o.total = off;
     return true;
+}
+
+PackJob glu_pack(char *ws, const GluLayout &lo, int64_t H, int kind)
+{
+    PackJob j{};
+    j.kind = kind; j.N = j.K = (int)H; j.planes = lo.planes;
+    j.frag = ws + lo.wfrag; j.exp = reinterpret_cast<int *>(ws + lo.wexp);
+    j.nblocks = pack_blocks(kind, (int)H);
+    return j;
+}
+PackSrc glu_source(const float *W, int64_t H)
+{
+    PackSrc s{};
+    s.W = W; s.H = (int)H;
+    return s;
 }
 
 }  // namespace
@@ -357,28 +361,28 @@ ssm_status ssm_half_glu_fwd(const float *u, const float *W, int64_t T, int64_t H
     if (misaligned(u, 16) || misaligned(W, 4) || misaligned(y, 4) || misaligned(gate, 4)) return SSM_ERR_INVALID_ARG;
     if (!workspace || misaligned(workspace, ALIGN) || ws_bytes < lo.total) return SSM_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    float *x1 = reinterpret_cast<float *>(static_cast<char *>(workspace) + lo.x1);
+    char *ws = static_cast<char *>(workspace);
+    float *x1 = reinterpret_cast<float *>(ws + lo.x1);
     const long n = (long)T * H, n4 = n / 4;
-    unsigned *rowmax = reinterpret_cast<unsigned *>(static_cast<char *>(workspace) + lo.rowmax);
-    unsigned *wslots = reinterpret_cast<unsigned *>(static_cast<char *>(workspace) + lo.slots) + 2 * GLU_MAX_SLOTS;
+    unsigned *rowmax = reinterpret_cast<unsigned *>(ws + lo.rowmax);
+    const PackJob w = glu_pack(ws, lo, H, PACK_WN);
     if (lo.two_planes) {
-        hipLaunchKernelGGL(gelu_max_kernel, dim3((unsigned)(lo.main_blocks + GLU_W_BLOCKS)), dim3(256), 0, s,
+        hipLaunchKernelGGL(gelu_max_kernel, dim3((unsigned)(lo.main_blocks + w.nblocks)), dim3(256), 0, s,
                            reinterpret_cast<const float4 *>(u), reinterpret_cast<float4 *>(x1), n4, (int)H, (long)T, rowmax,
-                           W, (long)H * H, wslots, GLU_W_BLOCKS);
+                           glu_source(W, H), w);
     } else {
         const long threads = n4 > 4 ? n4 : 4;
-        hipLaunchKernelGGL(gelu_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                           reinterpret_cast<const float4 *>(u), reinterpret_cast<float4 *>(x1), n4, u, x1, n);
+        hipLaunchKernelGGL(gelu_kernel, dim3((unsigned)((threads + 255) / 256 + w.nblocks)), dim3(256), 0, s,
+                           reinterpret_cast<const float4 *>(u), reinterpret_cast<float4 *>(x1), n4, u, x1, n, glu_source(W, H), w);
     }
     HIP_TRY(hipGetLastError());
     // y[t, j] = u[t, j] sigmoid(sum_i x1[t, i] W[i, j])
     GemmArgs g{};
-    g.A = x1; g.lda = H; g.a_kcontig = 1;
-    g.B = W; g.ldb = H; g.b_kcontig = 0;
+    g.A = x1; g.lda = H; g.w = PackedW{w.frag, w.exp}; g.planes = lo.planes;
     g.C = y; g.ldc = H; g.E = u; g.lde = H; g.C2 = gate; g.epilogue = 3;
-    g.M = (int)T; g.N = (int)H; g.K = (int)H; g.splits = 1;
-    if (lo.two_planes) { g.amaxA = AbsMax{nullptr, 0, rowmax, lo.row_parts, (long)T}; g.amaxB = AbsMax{wslots, GLU_W_BLOCKS, nullptr, 0, 0}; }
-    HIP_TRY(launch_gemm(g, s));
+    g.M = (int)T; g.N = (int)H; g.K = (int)H;
+    if (lo.two_planes) g.amaxA = AbsMax{nullptr, 0, rowmax, lo.row_parts, (long)T};
+    HIP_TRY(launch_product(g, s));
     return SSM_OK;
 }
 
@@ -402,32 +406,30 @@ ssm_status ssm_half_glu_bwd(const float *u, const float *W, const float *gate, c
     float *dWpart = reinterpret_cast<float *>(ws + lo.dWpart);
     const long n = (long)T * H;
     unsigned *rowmax = reinterpret_cast<unsigned *>(ws + lo.rowmax);
-    unsigned *x1_slots = reinterpret_cast<unsigned *>(ws + lo.slots), *dz_slots = x1_slots + GLU_MAX_SLOTS, *wslots = dz_slots + GLU_MAX_SLOTS;
+    unsigned *x1_slots = reinterpret_cast<unsigned *>(ws + lo.slots), *dz_slots = x1_slots + GLU_MAX_SLOTS;
+    const PackJob w = glu_pack(ws, lo, H, PACK_WT);
     if (lo.two_planes) {
-        hipLaunchKernelGGL(gate_bwd_prep_max_kernel, dim3((unsigned)(lo.main_blocks + GLU_W_BLOCKS)), dim3(256), 0, s, u, gate, dy,
-                           x1, dz, ds, gd, n, (int)H, (long)T, rowmax, x1_slots, dz_slots, W, (long)H * H, wslots, GLU_W_BLOCKS);
+        hipLaunchKernelGGL(gate_bwd_prep_max_kernel, dim3((unsigned)(lo.main_blocks + w.nblocks)), dim3(256), 0, s, u, gate, dy,
+                           x1, dz, ds, gd, n, (int)H, (long)T, rowmax, x1_slots, dz_slots, glu_source(W, H), w);
     } else {
-        hipLaunchKernelGGL(gate_bwd_prep_kernel, dim3((unsigned)(((n + 3) / 4 + 255) / 256)), dim3(256), 0, s, u, gate, dy, x1,
-                           dz, ds, gd, n);
+        hipLaunchKernelGGL(gate_bwd_prep_kernel, dim3((unsigned)(((n + 3) / 4 + 255) / 256 + w.nblocks)), dim3(256), 0, s, u, gate, dy, x1,
+                           dz, ds, gd, n, glu_source(W, H), w);
     }
     HIP_TRY(hipGetLastError());
     // du[t, i] = ds[t, i] + gd[t, i] sum_j dz[t, j] W[i, j]
     GemmArgs g{};
-    g.A = dz; g.lda = H; g.a_kcontig = 1;
-    g.B = W; g.ldb = H; g.b_kcontig = 1;
+    g.A = dz; g.lda = H; g.w = PackedW{w.frag, w.exp}; g.planes = lo.planes;
     g.C = du; g.ldc = H; g.E = ds; g.E2 = gd; g.lde = H; g.epilogue = 4;
-    g.M = (int)T; g.N = (int)H; g.K = (int)H; g.splits = 1;
-    if (lo.two_planes) { g.amaxA = AbsMax{nullptr, 0, rowmax, lo.row_parts, (long)T}; g.amaxB = AbsMax{wslots, GLU_W_BLOCKS, nullptr, 0, 0}; }
-    if (!lo.paired) HIP_TRY(launch_gemm(g, s));
-    // dW[i, j] = sum_t x1[t, i] dz[t, j]: reduction over tokens in K slabs, then a fixed-order sum
+    g.M = (int)T; g.N = (int)H; g.K = (int)H;
+    if (lo.two_planes) g.amaxA = AbsMax{nullptr, 0, rowmax, lo.row_parts, (long)T};
+    // dW[i, j] = sum_t x1[t, i] dz[t, j]: reduction over tokens in K slabs (same launch), then a fixed-order sum
     GemmArgs h{};
-    h.A = x1; h.lda = H; h.a_kcontig = 0;
-    h.B = dz; h.ldb = H; h.b_kcontig = 0;
+    h.A = x1; h.lda = H;
+    h.B = dz; h.ldb = H;
     h.C = dWpart; h.ldc = H;
     h.M = (int)H; h.N = (int)H; h.K = (int)T; h.splits = lo.splits;
     if (lo.two_planes) { h.amaxA = AbsMax{x1_slots, lo.main_blocks, nullptr, 0, 0}; h.amaxB = AbsMax{dz_slots, lo.main_blocks, nullptr, 0, 0}; }
-    if (lo.paired) HIP_TRY(launch_gemm_pair(g, h, s, lo.dw_first));
-    else HIP_TRY(launch_gemm(h, s));
+    HIP_TRY(launch_products(g, &h, nullptr, lo.dw_first, s));
     const long nw = (long)H * H;
     hipLaunchKernelGGL(sum_slabs_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, dWpart, nw, lo.splits, dW);
     HIP_TRY(hipGetLastError());

@@ -1,12 +1,7 @@
-// Tile selection and launch of the projection GEMMs.
-//
-// One kernel template (gemm_kernel.h) computes the fp32-in / fp32-out products on the 16-bit matrix
-// cores with both operands split while they are staged: exactly into three bf16 planes (six bf16
-// MFMAs per k block), or, when the largest magnitude of both operands is known, into two fp16 planes
-// of the operand scaled by a power of two (three fp16 MFMAs per k block); fp32 accumulation and
-// fp32-class accuracy either way.  The instantiations live in gemm_inst2.hip / gemm_inst3.hip (one
-// problem per launch) and gemm_pair.hip (several problems per launch).
-#include "gemm_kernel.h"
+// Host side of the projection products: which shapes scan inside them, how many K slabs a reduction gets, and
+// the launch (instantiations in products2.hip / products3.hip).
+#include "ssm_internal.h"
+#include "../../include/ssm.h"
 
 namespace ssm {
 
@@ -35,16 +30,23 @@ bool gemm_small_pair(int64_t T, int64_t N)
     return ((T + 127) / 128) * ((N + 127) / 128) <= SMALL_PAIR_ITEMS;
 }
 
-// K splits of an M x N reduction over K rows that shares such a launch with a product whose K loop is
-// k_main long: work items about as long as that product's, at most two rounds of workgroups in all
-int gemm_pick_splits_small(int64_t M, int64_t N, int64_t K, int64_t partner_tiles64, int64_t k_main)
+// K splits of an M x N reduction over K rows that shares such a launch with a product of main_M x main_N whose K loop is
+// k_main long: work items about as long as that product's (an item takes about 1.5 times as long per row as the product), at
+// most two rounds of workgroups in all; where there is room for it in one round, at least 128 rows per item.
+int gemm_pick_splits_small(int64_t M, int64_t N, int64_t K, int64_t main_M, int64_t main_N, int64_t k_main)
 {
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    int64_t s = (K + k_main / 2) / (k_main < 64 ? 64 : k_main);
-    const int64_t room = (512 - partner_tiles64) / tiles;
+    const int64_t kt = k_main < 64 ? 64 : k_main;
+    int64_t s = (K + k_main / 2) / kt;
+    const int64_t room = (512 - ((main_M + 63) / 64) * ((main_N + 63) / 64)) / tiles;
     if (s > room) s = room;
     const int64_t maxs = (K + 63) / 64;
     if (s > maxs) s = maxs;
+    const int64_t t64 = ((main_M + 63) / 64) * ((main_N + 127) / 128), items = t64 <= 128 ? ((main_M + 31) / 32) * ((main_N + 127) / 128) : t64;
+    int64_t one = (3 * K / 2 + kt / 2) / kt;
+    if (one > (256 - items) / tiles) one = (256 - items) / tiles;
+    if (one > K / 128) one = K / 128;
+    if (s < one) s = one;
     if (s > 64) s = 64;
     if (s < 1) s = 1;
     return (int)s;
@@ -115,80 +117,33 @@ int gemm_pick_splits_balanced(int64_t M, int64_t N, int64_t K, int64_t main_tile
     return gemm_pick_splits_model(K, main_tiles, k_main, ((M + 127) / 128) * ((N + 127) / 128), (size_t)M * N * 4, false, red_first);
 }
 
-// Layout code of a problem, or -1 when the projection kernel has no instantiation for it.
-int gemm_layout_of(const GemmArgs &a)
-{
-    if (a.epilogue == 2) return (a.a_kcontig && a.b_kcontig) ? gemm_layout(true, true, 2) : -1;
-    if (a.epilogue == 3) return (a.a_kcontig && !a.b_kcontig) ? gemm_layout(true, false, 3) : -1;
-    if (a.epilogue == 4) return (a.a_kcontig && a.b_kcontig) ? gemm_layout(true, true, 4) : -1;
-    if (a.epilogue == 6) return (a.a_kcontig && a.b_kcontig) ? gemm_layout(true, true, 6) : -1;
-    if (a.epilogue == 5) return (a.a_kcontig && !a.b_kcontig && a.N % 2 == 0) ? gemm_layout(true, false, 5) : -1;
-    if (a.epilogue == 7) return (a.a_kcontig && a.b_kcontig) ? gemm_layout(true, true, 7) : -1;
-    if (a.epilogue == 8) return (a.a_kcontig && !a.b_kcontig) ? gemm_layout(true, false, 8) : -1;
-    if (a.a_kcontig) return gemm_layout(true, a.b_kcontig != 0, a.epilogue);
-    if (!a.b_kcontig && !a.epilogue) return gemm_layout(false, false, 0);
-    return -1;
-}
-
-bool gemm_use_two_planes(const GemmArgs &a)
-{
-    // A product whose operands both come with their largest magnitude is staged as two scaled fp16
-    // planes per operand (three matrix instructions per k block instead of six, same accuracy class).
-    // A: one maximum, or one per row when its rows are contiguous along k; B: one maximum
-    const bool a_ok = (a.amaxA.rows && a.amaxA.row_parts > 0 && a.a_kcontig) || (!a.amaxA.rows && a.amaxA.slots && a.amaxA.n > 0);
-    return a_ok && a.amaxB.slots && a.amaxB.n > 0;
-}
-
+// The projections scan their own output tiles where a sequence is a whole number of 128-step pieces (a bounded chain
+// of tiles per sequence) or every 128 tokens are whole sequences of whole 16-step chunks, and there are enough tiles
+// (measured with tiles of 128 tokens: from 64 of them on -- a quarter of the CUs -- the scanning tile beats smaller tiles
+// plus a scan kernel: +2 % at 64 tiles, +7..13 % at 96-128; no difference at 32-48).
 bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P)
 {
-    // 128-row tiles that hold a piece of one sequence (a bounded chain of tiles per sequence) or a
-    // whole number of sequences made of whole 16-step chunks, and enough tiles
-    const bool chain = L % SCAN_TILE == 0 && L / SCAN_TILE <= SCAN_MAX_CHAIN;
-    const bool whole = L < SCAN_TILE && SCAN_TILE % L == 0 && L % SCAN_RC == 0 && (Bt * L) % SCAN_TILE == 0;
+    constexpr int64_t PIECE = 128, CHUNK = 16, MIN_TILES = 64;
+    const bool chain = L % PIECE == 0 && L <= SCAN_MAX_STEPS;
+    const bool whole = L < PIECE && PIECE % L == 0 && L % CHUNK == 0 && (Bt * L) % PIECE == 0;
     if (!chain && !whole) return false;
-    // (measured: from 64 tiles on -- a quarter of the CUs -- the scanning tile with its two fp16 planes beats
-    // smaller tiles plus a scan kernel: +2 % at 64 tiles, +7..13 % at 96-128; no difference at 32-48)
-    constexpr int64_t SCAN_MIN_TILES = 64;
-    const int64_t tiles = (Bt * L / SCAN_TILE) * ((2 * P + SCAN_TILE - 1) / SCAN_TILE);
-    return tiles >= SCAN_MIN_TILES && tiles * 64 <= 0x7fffffffLL;
+    const int64_t tiles = (Bt * L / PIECE) * ((2 * P + 127) / 128);
+    return tiles >= MIN_TILES && tiles * (PIECE / 64) * 64 <= 0x7fffffffLL;
 }
 
-// argument checks shared by the two scanning epilogues
-bool gemm_scan_args_ok(const GemmArgs &a)
-{
-    if (a.splits > 1 || !a.scan.lam || !a.scan.err || a.scan.L <= 0) return false;
-    const int L = a.scan.L;
-    const bool chain = L % SCAN_TILE == 0 && L / SCAN_TILE <= SCAN_MAX_CHAIN && a.scan.desc;
-    const bool whole = L < SCAN_TILE && SCAN_TILE % L == 0 && L % SCAN_RC == 0 && a.M % SCAN_TILE == 0;
-    if (!chain && !whole) return false;
-    if (a.M % L != 0 || a.N != 2 * a.scan.P || !a.a_kcontig) return false;
-    if (a.epilogue == 7) return a.b_kcontig != 0;
-    return !a.b_kcontig && a.scan.xsaved && a.scan.partial;
-}
+// Two workgroups per CU either way: tiles of 128 tokens (half the weight traffic, half as many scans to set up and hand
+// over) from the size on at which they still give every CU two of them.
+int gemm_scan_rows(int64_t T, int64_t P) { return (T / 128) * ((2 * P + 127) / 128) >= 512 ? 128 : 64; }
 
 size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
 {
-    if (L < SCAN_TILE) return 0;                     // whole sequences per tile: nothing is handed over
-    const int64_t tiles = (Bt * L / SCAN_TILE) * ((2 * P + SCAN_TILE - 1) / SCAN_TILE);
+    if (L <= 64) return 0;                           // a tile holds whole sequences: nothing is handed over
+    const int64_t tiles = (Bt * L / 64) * ((2 * P + 127) / 128);
     return (size_t)tiles * 64 * 2 * sizeof(unsigned long long);
 }
 
-// du = Re(Bbar^H chi) + D dy has only M/128 * H/128 tiles of 128x128.  Where they would fill less than the
-// chip but twice as many would (and the launch is shared with the dBbar slabs on three bf16 planes), it
-// runs as two halves of K into two slabs that the parameter epilogue's launch adds.
-bool gemm_out_split_shape(int64_t T, int64_t H, int64_t P)
-{
-    // a half must still be long enough (8 K tiles) to pay for the sum
-    const int64_t tiles = ((T + 127) / 128) * ((H + 127) / 128);
-    return tiles < 200 && 2 * tiles >= 200 && P >= 256 && (2 * P) % 64 == 0;
-}
-
-// Tile tier of an M x N product with `splits` K splits: 0 = 128x128x32 tiles, 1 = 64x128x32, 2 = 64x64x64.
-// The launch takes about (rounds of workgroups on the 256 CUs) x (K steps) x (time of a K step); a K step of a
-// 64x128x32 tile takes as long as one of a 128x128x32 tile, one of a 64x64x64 tile 1.2 times as long for twice
-// the K range (measured), so per unit of K the tiers cost rounds x 1, 1 and 0.6.  The cheapest wins, the
-// smaller tile on a tie (more CUs share the work).  (The rule before, "the largest tile that still gives 200
-// workgroups", took 64x128 tiles for 192 tiles of 128x128: two rounds instead of one, 40 us instead of 24.)
+// Tile tier of an M x N product with `splits` K splits, by rounds of workgroups on the 256 CUs: 0 = 128x128 tiles, 1 =
+// 64x128, 2 = 64x64.  Only reported (ssm_plan_describe): how coarse a tile a product of this size can afford.
 int gemm_tile_tier(int64_t M, int64_t N, int splits_in)
 {
     const int64_t splits = splits_in < 1 ? 1 : splits_in;
@@ -200,24 +155,39 @@ int gemm_tile_tier(int64_t M, int64_t N, int splits_in)
     return c1 <= c0 ? 1 : 0;
 }
 
-hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
+namespace {
+bool reduction_ok(const GemmArgs &t, int planes)
 {
-    if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;
-    const bool two = gemm_use_two_planes(a);
-    if (a.epilogue == 7 || a.epilogue == 8) {
-        // a projection that scans its own output (forward: the input projection; reverse: C^H dy): 128x128 tiles only
-        if (!gemm_scan_args_ok(a) || gemm_layout_of(a) < 0) return hipErrorInvalidValue;
-        return two ? gemm_dispatch_two_planes(a, 0, s) : gemm_dispatch_three_planes(a, 0, s);
+    return t.A && t.B && t.C && t.M > 0 && t.N > 0 && t.K > 0 && (planes == 3 || (t.amaxA.slots && t.amaxA.n > 0 && t.amaxB.slots && t.amaxB.n > 0));
+}
+// a scanning epilogue: whole sequences per tile or a chain of tiles, and its buffers
+bool scan_args_ok(const GemmArgs &a)
+{
+    const ScanEpilogue &c = a.scan;
+    if (a.planes != 2 || !c.lam || !c.err || c.L <= 0 || a.N != 2 * c.P || a.M % c.L != 0 || (c.rows != 64 && c.rows != 128) || a.M % c.rows != 0) return false;
+    const bool chain = c.L % c.rows == 0 && c.L <= SCAN_MAX_STEPS && (c.desc || c.L == 64);
+    const bool whole = c.L < c.rows && 64 % c.L == 0 && c.L % (c.rows / 8) == 0;
+    return (chain || whole) && (a.epilogue == 7 || (c.xsaved && c.partial));
+}
+}  // namespace
+
+hipError_t launch_products(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
+{
+    if (a.M <= 0 || a.N <= 0 || a.K <= 0 || !a.A || !a.C || !a.w.frag || (a.planes != 2 && a.planes != 3)) return hipErrorInvalidValue;
+    if (a.planes == 2 && (!a.w.exp || !a.amaxA.rows || a.amaxA.row_parts <= 0)) return hipErrorInvalidValue;
+    if ((c && !b) || (b && !reduction_ok(*b, a.planes)) || (c && !reduction_ok(*c, a.planes))) return hipErrorInvalidValue;
+    switch (a.epilogue) {
+    case 0: break;
+    case 1: if (!a.diag || !a.E) return hipErrorInvalidValue; break;
+    case 2: if (!a.diag || !a.E || a.N % 2) return hipErrorInvalidValue; break;
+    case 3: if (!a.E) return hipErrorInvalidValue; break;
+    case 4: if (!a.E || !a.E2) return hipErrorInvalidValue; break;
+    case 5: if ((a.C2 && !a.diag) || a.N % 2) return hipErrorInvalidValue; break;
+    case 6: if (!a.diag || !a.E || !a.C2) return hipErrorInvalidValue; break;
+    case 7: case 8: if (!scan_args_ok(a)) return hipErrorInvalidValue; break;
+    default: return hipErrorInvalidValue;
     }
-    if (a.splits > 1 && a.epilogue) return hipErrorInvalidValue;
-    if (a.epilogue < 0 || a.epilogue > 6 || (a.epilogue && a.epilogue != 5 && !a.E)) return hipErrorInvalidValue;
-    if (a.epilogue == 5 && a.C2 && !a.diag) return hipErrorInvalidValue;
-    if ((a.epilogue == 1 || a.epilogue == 2 || a.epilogue == 6) && !a.diag) return hipErrorInvalidValue;
-    if (a.epilogue == 6 && !a.C2) return hipErrorInvalidValue;
-    if (a.epilogue == 4 && !a.E2) return hipErrorInvalidValue;
-    if (gemm_layout_of(a) < 0) return hipErrorInvalidValue;
-    const int tier = gemm_tile_tier(a.M, a.N, a.splits);
-    return two ? gemm_dispatch_two_planes(a, tier, s) : gemm_dispatch_three_planes(a, tier, s);
+    return a.planes == 2 ? products_two_planes(a, b, c, tn_first, s) : products_three_planes(a, b, c, tn_first, s);
 }
 
 }  // namespace ssm

@@ -1,0 +1,966 @@
+// Products of fp32 activations with packed weights (gfx950):
+//
+//   C[m,n] = f( sum_k A[m,k] W(n,k) ),   A [M, K] fp32 with k contiguous, rows = tokens
+//
+// on the 16-bit matrix cores with both operands split into planes: two fp16 planes of the operand scaled by a
+// power of two (NPL = 2: every token row and every weight row n has its own scale) or three bf16 planes
+// (NPL = 3, exact); see split2_f16 / split3 in gemm_kernel.h.
+//
+// The weights are split once per call, by the prep launch, into fragment order: the 16 bytes that lane l needs for a
+// 32 x 16 block of W are at frag[((n / 32) (Kp / 16) + k / 16) NPL + plane][l].  A consumer wavefront therefore loads its
+// fragments from the L2 straight into registers, one fully coalesced 1 KiB load each, PFB k steps ahead, and only the
+// activations pass through producers and LDS.  What bounded the kernel that staged both operands through LDS was
+// the LDS itself: per 128x128x32 tile 64 KB of fragment reads and 32 KB of stores (which it takes at half rate)
+// for 768 cycles of matrix work.  Here a wavefront owns all BM rows of 32 columns, so no fragment of the weights is
+// loaded twice in a workgroup, and the LDS carries 16 KB of stores and 64 KB of reads for the same matrix work.
+// Measured stand-alone, 4096 x 1024 x 512: 15.2 us against 21.9; 4096 x 512 x 1024: 14.5 against 24; 32768 x 1024 x 512:
+// 104 us, 990 TFLOP/s of fp16 matrix work (a large fp16 library product reaches 1200 on this card).
+//
+// A workgroup is four consumer wavefronts (32 columns each) and four producer wavefronts (load, split, store to LDS);
+// BM = 64 rows by default, 32 where 64-row tiles would leave CUs idle.  At most 128 registers: two workgroups share a
+// CU, and the first loads, the stores and the scans of one overlap the K loop of the other.
+#pragma once
+
+#include "gemm_kernel.h"
+
+namespace ssm {
+
+constexpr int PK_BN = 128, PK_BK = 64, PK_CONSUMERS = 4, PK_PRODUCERS = 4, PK_STAGES = 2;
+constexpr int PK_THREADS = 64 * (PK_CONSUMERS + PK_PRODUCERS);
+
+// Place of an element of the output tile staged in LDS: rows of BN floats, pieces of 32 (rows, at 32 columns) swapped in rows
+// 4 .. 7 of every eight, so that the two groups of rows that a wavefront stores at once meet different banks.
+template <int BN = PK_BN>
+__device__ __forceinline__ int tile_at(int row, int col)
+{
+    return BN == 32 ? (row ^ ((row >> 2) & 1)) * BN + col : row * BN + (col ^ ((row & 4) << 3));
+}
+
+struct PkDev {
+    const float *A; long lda;
+    const uint4 *frag; const int *bexp;     // packed weights; log2 of the scale of every row n (two planes)
+    float *C; long ldc;
+    const float *diag; const float *E; long lde;
+    const float *E2; float *C2;
+    const uint8_t *rowflag;
+    int M, N, K, nkt;                       // nkt: K tiles of 64
+    int ntm, ntn, nx, mode, slot0;          // tiles; slots per XCD, placement mode, first slot
+    int sc_nt, sc_cpu, sc_ncg, sc_units, sc_rev;
+    ScanEpilogue scan;
+    const unsigned *rows; int row_parts; long row_stride;    // largest magnitudes of the rows of A (two planes), see AbsMax
+    unsigned *c2_rowmax;                    // epilogue 6: [ceil(N/128)][M] or null
+};
+
+// ---------------------------------------------------------------------------------------------
+// Epilogues 7 and 8: the resettable scan (forward, or the reverse one of the gradient pass) over the rows of a
+// ROWS x 128 output tile: 64 or 128 steps of 64 complex states, either a piece of one sequence (the pieces form a
+// chain) or whole sequences.  The order of the arithmetic is that of units of 64 steps and chunks of 8 whichever ROWS is,
+// so that the states do not depend on the tile a launch takes (and with it on the batch) to the last bit.  All eight
+// wavefronts take part, 64 lanes x ROWS/8 steps (one or two chunks each):
+//   1. the accumulators go through LDS so that a thread owns consecutive steps of one state;
+//   2. per-thread pass for zero incoming state, chunk aggregates combined through LDS;
+//   3. chain: the aggregate of every unit (state for zero incoming state, reset tag) is published as tagged 64-bit
+//      words before any wait.  Wavefront q folds the q-th run of 8 earlier units of the sequence (in scan order), all
+//      its words requested at once; then every wavefront folds the runs over the sequence's incoming state.  The grouping
+//      depends on the position in the chain alone, so results are bitwise reproducible whatever the timing;
+//   4. second per-thread pass writes the states (forward: x_last at the sequence end; reverse: the per-tile row of
+//      dAbar and dx0).
+// Every predecessor sits in an earlier slot of the same XCD (placement mode 5), i.e. it was dispatched earlier and
+// publishes without waiting for anything, and every wait is bounded.
+// ---------------------------------------------------------------------------------------------
+constexpr int SCAN_WAVES = 8, SCAN_CHUNK = 8, SCAN_UNIT = 64, SCAN_RUN = 8;      // steps, steps, units
+static_assert(SCAN_MAX_STEPS <= SCAN_WAVES * SCAN_RUN * SCAN_UNIT, "a run for every wavefront");
+// (128 rows: 80 KiB, two workgroups per CU)
+constexpr size_t scan_lds_bytes(int ROWS)
+{
+    return (size_t)ROWS * PK_BN * 4                                  // staged tile
+           + ROWS / SCAN_CHUNK * 64 * 8                              // chunk states
+           + SCAN_WAVES * 64 * 8 * 2;                                // folded runs of predecessors: product and state
+}
+
+struct ScanLds {
+    float *tile; float2 *cS, *pS, *pA;
+    float2 *uS; unsigned *top;                       // state of the tile's first unit, largest magnitudes: in the places of the last chunks, which nobody reads
+    __device__ ScanLds(void *base, int rows)
+    {
+        char *p = static_cast<char *>(base);
+        tile = reinterpret_cast<float *>(p); p += (size_t)rows * PK_BN * 4;
+        cS = reinterpret_cast<float2 *>(p); p += rows / SCAN_CHUNK * 64 * 8;
+        pS = reinterpret_cast<float2 *>(p); p += SCAN_WAVES * 64 * 8;
+        pA = reinterpret_cast<float2 *>(p);
+        uS = cS + (SCAN_UNIT / SCAN_CHUNK - 1) * 64;
+        top = reinterpret_cast<unsigned *>(cS + (rows / SCAN_CHUNK - 1) * 64);
+    }
+};
+
+// v[e], e < 8, per lane -> every lane gets the maximum over the 64 lanes of v[rows8_index(lane)]: three halving
+// exchanges between lanes that differ in bit 0, 1, 2 (data-parallel-primitive moves inside quads, then a half-row
+// mirror: lane ^ 7, whose partner holds the other half of the remaining pair), a rotation by 8 inside a row of 16,
+// and the two exchanges across rows (lane swaps).
+__device__ __forceinline__ unsigned rows8_wave_max(unsigned (&v)[8], int lane)
+{
+    {
+        const bool up = lane & 1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned keep = up ? v[k + 4] : v[k], send = up ? v[k] : v[k + 4];
+            v[k] = max(keep, dpp_move<0xb1>(send));                   // quad_perm [1,0,3,2]: lane ^ 1
+        }
+    }
+    {
+        const bool up = (lane >> 1) & 1;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const unsigned keep = up ? v[k + 2] : v[k], send = up ? v[k] : v[k + 2];
+            v[k] = max(keep, dpp_move<0x4e>(send));                   // quad_perm [2,3,0,1]: lane ^ 2
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        // lanes with the same two low bits: rotations by 4 and 8 inside a row of 16, lane swaps across rows
+        v[k] = max(v[k], dpp_move<0x124>(v[k]));                      // row_ror:4
+        v[k] = max(v[k], dpp_move<0x128>(v[k]));                      // row_ror:8
+        v[k] = lane_xor_max<16>(v[k]);
+        v[k] = lane_xor_max<32>(v[k]);
+    }
+    // (bitwise: a selection between two array elements becomes one between their addresses, and the array goes to scratch)
+    return v[0] ^ ((v[0] ^ v[1]) & (0u - (unsigned)((lane >> 2) & 1)));
+}
+__device__ __forceinline__ int rows8_index(int lane) { return 4 * (lane & 1) + 2 * ((lane >> 1) & 1) + ((lane >> 2) & 1); }
+
+// Reverse scan: the saved states x_{t-1} of a thread's steps (x_{-1} = x0, zero when absent), plus the last state of
+// the sequence for the thread that owns its last steps.
+template <int RC> struct ScanSaved { float2 xp[RC]; float2 xl; };
+template <int RC>
+__device__ __forceinline__ ScanSaved<RC> scan_request_saved(const ScanEpilogue &a, int q, int c, int m0, int n0)
+{
+    const int p = n0 / 2 + c;
+    const bool active = p < a.P;
+    const int row0 = m0 + q * RC;
+    const int b = row0 / a.L, t0 = row0 % a.L;
+    // (row addresses are uniform: one lane offset for all of them)
+    const float2 *xprev = a.xsaved + ((long)row0 - 1) * a.P + n0 / 2;                // x_{t0-1}; valid for e >= 1 or t0 > 0
+    ScanSaved<RC> s;
+    s.xl = make_float2(0.f, 0.f);
+    if (a.xmax_out && active && t0 + RC == a.L) s.xl = (xprev + (long)RC * a.P)[c];
+#pragma unroll
+    for (int e = 0; e < RC; ++e) {
+        s.xp[e] = make_float2(0.f, 0.f);
+        if (active) {
+            if (t0 + e > 0) s.xp[e] = (xprev + (long)e * a.P)[c];
+            else if (a.x0) s.xp[e] = a.x0[(long)b * a.P + p];
+        }
+    }
+    return s;
+}
+
+// The flags of the tile's steps, one or two bytes per lane of every wavefront, requested first of all and turned into words
+// of bits when the first K tile has arrived: the scan starts without a trip to memory, and what it does about resets is
+// decided by scalar instructions.
+template <int ROWS> struct ScanFlagBytes { unsigned own[ROWS / 64], next; };
+template <int ROWS> struct ScanFlags {                       // bit r of first[h]: row 64 h + r of the tile
+    unsigned long long first[ROWS / 64], drop[ROWS / 64];
+    // word h (bitwise: a selection between array elements becomes one between their addresses, and the array goes to scratch)
+    static __device__ __forceinline__ unsigned long long word(const unsigned long long (&w)[ROWS / 64], int h)
+    {
+        return ROWS == 64 ? w[0] : w[0] ^ ((w[0] ^ w[ROWS / 64 - 1]) & (0ull - (unsigned long long)h));
+    }
+    // the bits of the n rows from r on (within one word)
+    static __device__ __forceinline__ unsigned bits(const unsigned long long (&w)[ROWS / 64], int r, int n)
+    {
+        return (unsigned)(word(w, r / 64) >> (r & 63)) & ((1u << n) - 1u);
+    }
+};
+template <int ROWS, bool REV>
+__device__ __forceinline__ ScanFlagBytes<ROWS> scan_request_flags(const ScanEpilogue &a, int l, int m0, int M)
+{
+    ScanFlagBytes<ROWS> v;
+    v.next = 0;
+#pragma unroll
+    for (int h = 0; h < ROWS / 64; ++h) v.own[h] = 0;
+    if (a.is_first) {
+#pragma unroll
+        for (int h = 0; h < ROWS / 64; ++h) v.own[h] = a.is_first[m0 + 64 * h + l];
+        if (REV) v.next = a.is_first[min(m0 + ROWS, M - 1)];
+    }
+    return v;
+}
+// first: is_first.  drop: the state that flows into the step is dropped -- forward: the step's own flag; reverse: the flag
+// of the next time step (nothing flows in at a sequence end).
+template <int ROWS, bool REV>
+__device__ __forceinline__ ScanFlags<ROWS> scan_flags(const ScanEpilogue &a, const ScanFlagBytes<ROWS> &v, int m0)
+{
+    constexpr int H = ROWS / 64;
+    ScanFlags<ROWS> f;
+#pragma unroll
+    for (int h = 0; h < H; ++h) f.first[h] = f.drop[h] = __ballot(v.own[h] != 0);
+    if (REV) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) f.drop[h] = (f.first[h] >> 1) | (h + 1 < H ? f.first[h + 1 < H ? h + 1 : h] << 63 : 0ull);
+        if (a.L < ROWS) {
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+                for (int r = a.L - 1; r < 64; r += a.L) f.drop[h] |= 1ull << r;          // (L divides 64)
+        } else if ((m0 + ROWS) % a.L == 0 || __builtin_amdgcn_readfirstlane(v.next) != 0) f.drop[H - 1] |= 1ull << 63;
+    }
+    return f;
+}
+
+// the maximum over the 64 lanes, in all of them
+__device__ __forceinline__ unsigned wave_max(unsigned v)
+{
+    v = max(v, dpp_move<0xb1>(v));
+    v = max(v, dpp_move<0x4e>(v));
+    v = max(v, dpp_move<0x124>(v));
+    v = max(v, dpp_move<0x128>(v));
+    v = lane_xor_max<16>(v);
+    return lane_xor_max<32>(v);
+}
+
+// The tile is staged in lds.tile on entry.  REV: chi_t = gx_t + [not is_first_{t+1}] conj(Abar) chi_{t+1}, which walks
+// time backwards (later chunks and later tiles are the predecessors) and also reduces
+// dAbar += [not is_first_t] conj(x_{t-1}) chi_t per tile and writes dx0.
+template <int ROWS, bool REV>
+__device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds &lds, int q, int c, int m0, int n0, int tile,
+                                                   ScanSaved<ROWS / SCAN_WAVES> &saved, const ScanFlags<ROWS> &flags)
+{
+    constexpr int RC = ROWS / SCAN_WAVES, H = ROWS / SCAN_UNIT, NC = RC / SCAN_CHUNK, WH = SCAN_WAVES / H, UC = SCAN_UNIT / SCAN_CHUNK;
+    static_assert(SCAN_CHUNK == 8 && UC == 8 && (H == 1 || H == 2), "the powers of Abar below");
+    const ScanEpilogue &a = g.scan;
+    // (q, the wavefront, is uniform, and so is all that follows from it: positions, chunks, resets)
+    const int hs = REV ? H - 1 - q / WH : q / WH;            // unit of the tile, in scan order
+    const int c0 = (REV ? WH - 1 - q % WH : q % WH) * NC;    // the thread's first chunk of the unit, in scan order
+    const int p = n0 / 2 + c;
+    const bool active = p < a.P;
+    // A tile is either one piece of a chain of tiles of one sequence or holds whole sequences: then there is no chain, a
+    // sequence starts at a chunk boundary inside the tile and its incoming state is x0 (forward) or zero (reverse).
+    const bool whole_seqs = a.L < ROWS;
+    const int row0 = m0 + q * RC;                            // token index of this thread's first step
+    const int b = row0 / a.L, t0 = row0 - b * a.L;           // its sequence and its lowest time index
+    const int tmL = whole_seqs ? 0 : t0 / ROWS, nt = whole_seqs ? 1 : a.L / ROWS;
+    const int tn = n0 / PK_BN;
+    const int npred = H * (REV ? nt - 1 - tmL : tmL);        // units of the chain before the tile in scan order
+    const unsigned fmask = flags.bits(flags.first, q * RC, RC), rmask = flags.bits(flags.drop, q * RC, RC);
+    // whether a chunk of unit h (scan order) contains a reset
+    auto chunk_resets = [&](int h, int j) { return flags.bits(flags.drop, REV ? ROWS - SCAN_UNIT * h - 8 * (j + 1) : SCAN_UNIT * h + 8 * j, 8) != 0; };
+    auto unit_resets = [&](int h) { return flags.word(flags.drop, REV ? H - 1 - h : h) != 0; };
+
+    float2 lam = active ? a.lam[p] : make_float2(0.f, 0.f);
+    if (REV) lam.y = -lam.y;
+    float2 X = make_float2(0.f, 0.f);                        // state that flows into the sequence
+    if (!REV && a.x0 && active) X = a.x0[(long)b * a.P + p];
+    auto mine = [&](int e) { return reinterpret_cast<float2 *>(lds.tile + tile_at(q * RC + e, 2 * c)); };      // the thread's steps
+    float2 val[SCAN_CHUNK], S[NC];
+    auto read_chunk = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < SCAN_CHUNK; ++i) val[i] = *mine(REV ? RC - 1 - (8 * k + i) : 8 * k + i);
+    };
+    // Reverse: the saved states pass through this launch exactly once, so their largest magnitude is recorded on
+    // the way: dy^T x, in the next launch, stages x under that scale (x0 is not part of x)
+    float xmax = 0.f, amax = 0.f;
+    // pass 1: state after each of the thread's chunks for zero incoming state (a reset zeroes the multiplier)
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        S[k] = make_float2(0.f, 0.f);
+        read_chunk(k);
+#pragma unroll
+        for (int i = 0; i < SCAN_CHUNK; ++i) {
+            const int e = REV ? RC - 1 - (8 * k + i) : 8 * k + i;
+            const bool r = (rmask >> e) & 1u;
+            const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
+            S[k] = cfma(le, S[k], val[i]);
+        }
+        if (c0 + k < UC - 1) lds.cS[(hs * UC + c0 + k) * 64 + c] = S[k];
+    }
+    float2 lrc = cmul(lam, lam);                             // Abar^8 by three squarings
+    lrc = cmul(lrc, lrc); lrc = cmul(lrc, lrc);
+    float2 lunit = cmul(lrc, lrc);                           // Abar^64 by three more
+    lunit = cmul(lunit, lunit); lunit = cmul(lunit, lunit);
+    __syncthreads();                                         // the chunk states are in LDS
+
+    // exclusive combine over the chunks of the same unit (or sequence) that come earlier in scan order
+    float2 Aex[NC], Sex[NC];
+    {
+        const int cfirst = c0 - (whole_seqs ? min(c0, (REV ? a.L - RC - t0 : t0) / SCAN_CHUNK) : c0);
+        // (all chunk states are read first, whether this thread folds them or not: left inside the condition below,
+        // the reads end up in its branch and a thread waits for LDS once per chunk it folds, the last chunk's
+        // wavefront seven times in a row, and the unit's aggregate goes out late)
+        float2 Sc[UC - 1];
+#pragma unroll
+        for (int j = 0; j < UC - NC; ++j) {
+            Sc[j] = lds.cS[(hs * UC + j) * 64 + c];
+            asm volatile("" : "+v"(Sc[j].x), "+v"(Sc[j].y));
+        }
+        Aex[0] = make_float2(1.f, 0.f); Sex[0] = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int j = 0; j < UC - NC; ++j) {
+            if (j < cfirst || j >= c0) continue;
+            const bool any = chunk_resets(hs, j);
+            const float2 Aj = make_float2(any ? 0.f : lrc.x, any ? 0.f : lrc.y);
+            Sex[0] = cfma(Aj, Sex[0], Sc[j]);
+            Aex[0] = cmul(Aj, Aex[0]);
+        }
+#pragma unroll
+        for (int k = 1; k < NC; ++k) {                       // (a sequence is a whole number of a thread's steps)
+            const bool any = chunk_resets(hs, c0 + k - 1);
+            const float2 Aj = make_float2(any ? 0.f : lrc.x, any ? 0.f : lrc.y);
+            Sex[k] = cfma(Aj, Sex[k - 1], S[k - 1]);
+            Aex[k] = cmul(Aj, Aex[k - 1]);
+        }
+    }
+    if (!whole_seqs) {
+        if (c0 == UC - NC) {
+            // the unit's aggregate goes out before anything is waited for
+            const bool has_succ = REV ? (tmL > 0) : (tmL + 1 < nt);
+            const bool any = chunk_resets(hs, UC - 1);
+            const float2 Ath = make_float2(any ? 0.f : lrc.x, any ? 0.f : lrc.y);
+            const float2 Su = cfma(Ath, Sex[NC - 1], S[NC - 1]);
+            const unsigned tag = unit_resets(hs) ? 2u : 1u;
+            if (active && has_succ) {
+                const int unit = (m0 / ROWS) * H + (REV ? H - 1 - hs : hs);
+                unsigned long long *word = a.desc + (((size_t)unit * g.ntn + tn) * 64 + c) * 2;
+                publish_word(word, Su.x, tag);
+                publish_word(word + 1, Su.y, tag);
+            }
+            if (H == 2 && hs == 0) lds.uS[c] = Su;
+        }
+        if (REV && RC == 16) saved = scan_request_saved<RC>(a, q, c, m0, n0);    // (128 rows: no registers for them before)
+        // The k-th unit in scan order is unit k of the sequence forward, unit H nt - 1 - k in reverse.  Wavefront q folds
+        // the q-th run.
+        const int kn = min(SCAN_RUN, npred - q * SCAN_RUN);
+        if (kn > 0) {
+            float2 Ar = make_float2(1.f, 0.f), Sr = make_float2(0.f, 0.f);
+            // (all words of the run are requested in every round until all are there, for all lanes: the loads of a round are
+            // in flight together, and the wavefront leaves the loop as one)
+            const long step = (REV ? -1 : 1) * (long)g.ntn * 64 * 2;
+            const int kb = q * SCAN_RUN;
+            const unsigned long long *w = a.desc + (((size_t)(b * nt * H + (REV ? nt * H - 1 - kb : kb)) * g.ntn + tn) * 64 + c) * 2;
+            auto fold = [&](auto count) {
+                constexpr int N = decltype(count)::value;    // requests per round, at least kn
+                unsigned long long w0[N], w1[N];
+                bool all = false;                            // of this lane
+                for (unsigned spins = 0;; ++spins) {
+                    all = true;
+#pragma unroll
+                    for (int j = 0; j < N; ++j) {
+                        const unsigned long long *wj = w + step * min(j, kn - 1);
+                        w0[j] = poll_word(wj); w1[j] = poll_word(wj + 1);
+                    }
+#pragma unroll
+                    for (int j = 0; j < N; ++j) all = all & (word_tag(w0[j]) != 0) & (word_tag(w1[j]) != 0);
+                    if (__ballot(active && !all) == 0 || spins >= a.spin_limit) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (active && !all) atomicOr(a.err, 1u);     // gave up: flagged, and finished anyway
+#pragma unroll
+                for (int j = 0; j < N; ++j) {
+                    if (j >= kn) continue;
+                    // a missing aggregate hands on NaN: every state that depends on it becomes NaN, so the failure cannot
+                    // pass as data
+                    const bool missing = (word_tag(w0[j]) == 0) | (word_tag(w1[j]) == 0), cut = missing | (word_tag(w0[j]) == 2u);
+                    const float2 Sj = missing ? make_float2(__builtin_nanf(""), __builtin_nanf("")) : make_float2(word_value(w0[j]), word_value(w1[j]));
+                    const float2 Aj = make_float2(cut ? 0.f : lunit.x, cut ? 0.f : lunit.y);
+                    Sr = cfma(Aj, Sr, Sj);
+                    Ar = cmul(Aj, Ar);
+                }
+            };
+            if (kn <= SCAN_RUN / 2) fold(std::integral_constant<int, SCAN_RUN / 2>{});
+            else fold(std::integral_constant<int, SCAN_RUN>{});
+            lds.pS[q * 64 + c] = Sr;
+            lds.pA[q * 64 + c] = Ar;
+        }
+        if (npred > 0 || H == 2) {
+            __syncthreads();                                 // the folded runs and the first unit's state are in LDS
+            const int nrun = (npred + SCAN_RUN - 1) / SCAN_RUN;
+            float2 before = X, Al = make_float2(1.f, 0.f), Sl = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int j = 0; j < SCAN_WAVES; ++j) {
+                if (j >= nrun) break;
+                Al = lds.pA[j * 64 + c]; Sl = lds.pS[j * 64 + c];
+                before = X;
+                X = cfma(Al, X, Sl);
+            }
+            if (H == 2 && hs == 1) {
+                // the tile's own first unit is one more predecessor, in the last run if that has room
+                const float2 S0 = lds.uS[c];
+                const bool any = unit_resets(0);
+                const float2 A0 = make_float2(any ? 0.f : lunit.x, any ? 0.f : lunit.y);
+                if (npred % SCAN_RUN != 0) X = cfma(cmul(A0, Al), before, cfma(A0, Sl, S0));
+                else X = cfma(A0, X, S0);
+            }
+        }
+    } else if (REV && RC == 16) saved = scan_request_saved<RC>(a, q, c, m0, n0);
+
+    // pass 2: the states themselves
+    float2 xs = make_float2(0.f, 0.f);
+    asm volatile("" : "+v"(lam.x), "+v"(lam.y));             // (or the selected multipliers of pass 1 are kept: 2 RC registers)
+    float2 *dst = reinterpret_cast<float2 *>(g.C) + (long)row0 * a.P + n0 / 2;
+    float2 acc = make_float2(0.f, 0.f);                      // reverse: dAbar += [not is_first_t] conj(x_{t-1}) chi_t
+    if (REV) xmax = fmaxf(fabsf(saved.xl.x), fabsf(saved.xl.y));
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        read_chunk(k);                                       // (again: held since pass 1 they would take the registers of what is in flight)
+        unsigned rm[SCAN_CHUNK];                             // largest magnitude per step (row of the tile), for rowmax_out
+        xs = cfma(Aex[k], X, Sex[k]);
+#pragma unroll
+        for (int i = 0; i < SCAN_CHUNK; ++i) {
+            const int e = REV ? RC - 1 - (8 * k + i) : 8 * k + i;
+            const bool r = (rmask >> e) & 1u;
+            const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
+            xs = cfma(le, xs, val[i]);
+            if (active) (dst + (long)e * a.P)[c] = xs;
+            const float me = fmaxf(fabsf(xs.x), fabsf(xs.y));
+            rm[e % SCAN_CHUNK] = active ? __float_as_uint(me) : 0u;
+            amax = fmaxf(amax, me);
+            if (REV) {
+                if (t0 + e > 0) xmax = fmaxf(xmax, fmaxf(fabsf(saved.xp[e].x), fabsf(saved.xp[e].y)));
+                const bool m = (fmask >> e) & 1u;
+                const float2 qv = make_float2(m ? 0.f : saved.xp[e].x, m ? 0.f : saved.xp[e].y);
+                acc.x = fmaf(qv.x, xs.x, fmaf(qv.y, xs.y, acc.x));
+                acc.y = fmaf(qv.x, xs.y, fmaf(-qv.y, xs.x, acc.y));
+            }
+        }
+        if (a.rowmax_out) {
+            // largest magnitude of every row within this column tile, stored as [column tile][row] (the consumer of C
+            // takes the maximum over the column tiles): lane l < 8 ends up with row rows8_index(l)
+            const unsigned r = rows8_wave_max(rm, c);
+            if (c < 8) a.rowmax_out[(size_t)tn * g.M + row0 + (REV ? RC - 8 * (k + 1) : 8 * k) + rows8_index(c)] = r;
+        }
+    }
+    if (!REV) {
+        if (active && a.x_last && t0 + RC == a.L) a.x_last[(long)b * a.P + p] = xs;
+    } else {
+        // lam holds conj(Abar) here: dx0 = [not is_first_0] conj(Abar) chi_0
+        if (active && a.dx0 && t0 == 0) a.dx0[(long)b * a.P + p] = (fmask & 1u) ? make_float2(0.f, 0.f) : cmul(lam, xs);
+        *mine(0) = acc;                                      // (its own row of the tile, which it has read)
+        __syncthreads();                                     // the wavefronts' contributions to dAbar are in LDS
+        if (q == 0 && active) {
+            float2 sum = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int j = 0; j < SCAN_WAVES; ++j) { const float2 v = *reinterpret_cast<const float2 *>(lds.tile + tile_at(j * RC, 2 * c)); sum.x += v.x; sum.y += v.y; }
+            a.partial[(size_t)(m0 / ROWS) * a.P + p] = sum;
+        }
+    }
+    if (a.amax_out) {
+        // one atomic per workgroup, spread over ABSMAX_SLOTS addresses (the bit patterns of non-negative floats order
+        // like unsigned integers)
+        const unsigned v0 = wave_max(active ? __float_as_uint(amax) : 0u), vx0 = REV ? wave_max(active ? __float_as_uint(xmax) : 0u) : 0u;
+        if (c == 0) { lds.top[q] = v0; lds.top[SCAN_WAVES + q] = vx0; }
+        __syncthreads();                                     // the wavefronts' maxima are in LDS
+        if (q == 0 && c == 0) {
+            unsigned v = v0, vx = vx0;
+            for (int j = 1; j < SCAN_WAVES; ++j) { v = max(v, lds.top[j]); vx = max(vx, lds.top[SCAN_WAVES + j]); }
+            atomicMax(a.amax_out + (unsigned)tile % ABSMAX_SLOTS, v);
+            if (REV && a.xmax_out) atomicMax(a.xmax_out + (unsigned)tile % ABSMAX_SLOTS, vx);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Epilogues 0 .. 6: the tile goes through LDS and all eight wavefronts store it in rows of 512 bytes, 16 bytes per lane.
+// The inputs of the store function are requested before the workgroup meets (by the producers while the consumers
+// work on the last K tile), so that their way from memory is not paid behind the K loop.
+// ---------------------------------------------------------------------------------------------
+template <int BM, int BN, int EPI>
+struct StoreInputs {
+    static constexpr int KW = 128 / BN, LANES = BN / 4;                  // partial tiles to add up, lanes that share a row
+    static constexpr int ALL = BM * BN / 4 < PK_THREADS ? 1 : BM * BN / 4 / PK_THREADS;      // units of four columns per thread,
+    static constexpr int UNITS = ALL < 4 ? ALL : 4, BATCHES = ALL / UNITS;      // in batches of at most four
+    static constexpr bool HAS_E = EPI >= 1 && EPI <= 6, HAS_E2 = EPI == 4, HAS_DIAG = EPI == 1 || EPI == 2 || EPI == 5 || EPI == 6;
+    float4 e[UNITS], e2[UNITS], d;
+    bool dropped[UNITS];
+
+    static __device__ __forceinline__ int row_of(int tid, int batch, int i) { return tid / LANES + (batch * UNITS + i) * (PK_THREADS / LANES); }
+    static __device__ __forceinline__ float4 load4(const float *p, int n)          // n valid values from p
+    {
+        if (n >= 4) { const f32x4u v = *reinterpret_cast<const f32x4u *>(p); return make_float4(v.x, v.y, v.z, v.w); }
+        return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
+    }
+    __device__ __forceinline__ void request(const PkDev &g, int tid, int batch, int m0, int n0)
+    {
+        const int col = n0 + 4 * (tid % LANES), n = g.N - col;
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i) {
+            const long row = m0 + row_of(tid, batch, i);
+            const bool in = row < g.M && n > 0 && row < m0 + BM;
+            e[i] = e2[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            dropped[i] = false;
+            if (HAS_E && (EPI != 5 || g.E) && in) e[i] = load4(g.E + row * g.lde + col, n);
+            if (HAS_E2 && in) e2[i] = load4(g.E2 + row * g.lde + col, n);
+            if ((EPI == 2 || EPI == 5) && g.rowflag && in) dropped[i] = g.rowflag[row] != 0;
+        }
+        d = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (HAS_DIAG && n > 0 && (EPI != 5 || g.C2)) d = load4(g.diag + col, n);
+    }
+    static __device__ __forceinline__ void put4(float *p, float4 v, int n)
+    {
+        if (n >= 4) { f32x4u w = {v.x, v.y, v.z, v.w}; *reinterpret_cast<f32x4u *>(p) = w; return; }
+        if (n > 0) p[0] = v.x;
+        if (n > 1) p[1] = v.y;
+        if (n > 2) p[2] = v.z;
+    }
+    __device__ __forceinline__ void store(const PkDev &g, const float *tile, int tid, int batch, int m0, int n0)
+    {
+        const int c = 4 * (tid % LANES), col = n0 + c, n = g.N - col;
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i) {
+            const int r = row_of(tid, batch, i);
+            const long row = m0 + r;
+            if (BM * BN / 4 < PK_THREADS && r >= BM) continue;           // (threads past the tile)
+            const bool in = row < g.M && n > 0;
+            float4 v = *reinterpret_cast<const float4 *>(tile + tile_at<BN>(r, c));
+#pragma unroll
+            for (int k = 1; k < KW; ++k) {
+                const float4 w = *reinterpret_cast<const float4 *>(tile + k * BM * BN + tile_at<BN>(r, c));
+                v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+            }
+            float4 o = v, o2 = v;
+            bool second = false;
+            if constexpr (EPI == 1 || EPI == 6) {
+                // v + diag[col] * E[row, col]  (D (.) u and D (.) dy); 6: GELU of it into C2 as well
+                o = make_float4(fmaf(d.x, e[i].x, v.x), fmaf(d.y, e[i].y, v.y), fmaf(d.z, e[i].z, v.z), fmaf(d.w, e[i].w, v.w));
+                if constexpr (EPI == 6) {
+                    o2 = make_float4(gelu_value(o.x), gelu_value(o.y), gelu_value(o.z), gelu_value(o.w));
+                    second = true;
+                }
+            } else if constexpr (EPI == 2) {
+                // one recurrence step (Eq. 3, first line): columns are interleaved (re, im) pairs of complex states, diag
+                // holds Abar; adds the carried state [not rowflag[row]] (Abar E)
+                if (!dropped[i])
+                    o = make_float4(v.x + fmaf(d.x, e[i].x, -d.y * e[i].y), v.y + fmaf(d.x, e[i].y, d.y * e[i].x),
+                                    v.z + fmaf(d.z, e[i].z, -d.w * e[i].w), v.w + fmaf(d.z, e[i].w, d.w * e[i].z));
+            } else if constexpr (EPI == 5) {
+                // its adjoint: g = v + E (E may be null), C2 = [not rowflag[row]] conj(Abar) g
+                o = make_float4(v.x + e[i].x, v.y + e[i].y, v.z + e[i].z, v.w + e[i].w);
+                second = g.C2 != nullptr;
+                o2 = dropped[i] ? make_float4(0.f, 0.f, 0.f, 0.f)
+                                : make_float4(fmaf(d.x, o.x, d.y * o.y), fmaf(d.x, o.y, -d.y * o.x), fmaf(d.z, o.z, d.w * o.w), fmaf(d.z, o.w, -d.w * o.z));
+            } else if constexpr (EPI == 3) {
+                // half-GLU gate: s = sigmoid(v) is kept in C2 when asked and the stored value is E[row, col] * s
+                o2 = make_float4(sigmoidf(v.x), sigmoidf(v.y), sigmoidf(v.z), sigmoidf(v.w));
+                second = g.C2 != nullptr;
+                o = make_float4(e[i].x * o2.x, e[i].y * o2.y, e[i].z * o2.z, e[i].w * o2.w);
+            } else if constexpr (EPI == 4) {
+                // adjoint of the gate with respect to its input: E + v * E2
+                o = make_float4(fmaf(v.x, e2[i].x, e[i].x), fmaf(v.y, e2[i].y, e[i].y), fmaf(v.z, e2[i].z, e[i].z), fmaf(v.w, e2[i].w, e[i].w));
+            }
+            if (in) {
+                put4(g.C + row * g.ldc + col, o, n);
+                if (second) put4(g.C2 + row * g.ldc + col, o2, n);
+            }
+            if constexpr (EPI == 6 && BN == 128) {
+                // the product that consumes C2 stages its rows under a scale each: the largest magnitude of every row within
+                // the workgroup's 128 columns (32 neighbouring lanes hold them)
+                if (g.c2_rowmax) {
+                    unsigned m = 0;
+                    if (in) m = __float_as_uint(fmaxf(fmaxf(fabsf(o2.x), n > 1 ? fabsf(o2.y) : 0.f), fmaxf(n > 2 ? fabsf(o2.z) : 0.f, n > 3 ? fabsf(o2.w) : 0.f)));
+                    m = max(m, dpp_move<0xb1>(m));
+                    m = max(m, dpp_move<0x4e>(m));
+                    m = max(m, dpp_move<0x124>(m));
+                    m = max(m, dpp_move<0x128>(m));
+                    m = lane_xor_max<16>(m);
+                    if (tid % 32 == 0 && row < g.M) g.c2_rowmax[(size_t)(n0 / PK_BN) * g.M + row] = m;
+                }
+            }
+        }
+    }
+};
+
+// Place of the c-th 16-byte piece of row r of an LDS plane (rows of 128 bytes, no padding): the pieces of a row are permuted
+// so that 16 lanes reading the same piece of 16 rows, and 32 lanes writing two neighbouring rows, meet every bank once.
+__device__ __forceinline__ int pk_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
+
+template <int BM, int BN, int NPL, int EPI>
+__device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tile, int tid)
+{
+    constexpr int NC = PK_CONSUMERS, NP = PK_PRODUCERS, BK = PK_BK, NS = PK_STAGES, PT = 64 * NP;
+    constexpr int S = BK;                         // row stride of an LDS plane in halves; see pk_swizzle
+    constexpr int PLANE = BM * S, STAGE = NPL * PLANE;
+    constexpr int MI = BM / 32, KS = BK / 16;
+    // BN < 128: the consumers of the same 32 columns share out the k steps of a K tile
+    constexpr int CG = BN / 32, KW = NC / CG, KSW = KS / KW;
+    static_assert(BN == 128 || BM == 32, "narrow tiles have 32 rows");
+    constexpr bool SCANS = EPI == 7 || EPI == 8;
+    constexpr int RC = SCANS ? BM / SCAN_WAVES : 8, FR = SCANS ? BM : 64;      // (scans)
+    static_assert(!SCANS || BM >= 64, "scanning tiles have 64 or 128 rows");
+    // k steps of the weights in flight: what 128 registers hold (at 32 rows eight measured no better than four)
+    constexpr int PFB = (NPL == 3 && MI == 2) || MI == 4 ? 2 : 4;
+    static_assert(MI <= 2 || NPL == 2, "128 rows of three planes do not fit the registers");
+    __bf16 *stages = reinterpret_cast<__bf16 *>(smem_raw);
+    int *rowexp = reinterpret_cast<int *>(stages + NS * STAGE);      // [BM] log2 of the scale of every row (two planes)
+
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int nk = g.nkt;
+    ScanSaved<RC> saved;
+    ScanFlagBytes<FR> flag_bytes;
+    ScanFlags<FR> flags;
+    StoreInputs<BM, BN, EPI> in;
+    if constexpr (SCANS) flag_bytes = scan_request_flags<FR, EPI == 8>(g.scan, l, m0, g.M);
+
+    if (wave >= NC) {
+        // ------------------------------------------------------------------ producers
+        // a thread stages NV units of 1 row x 4 k per K tile; PF K tiles of loads in flight
+        constexpr int NV = BM * BK / 4 / PT, PF = BM == 32 ? 4 : 2;
+        static_assert(NV * PT * 4 == BM * BK, "tile must be a multiple of the producers' units");
+        const int pt = tid - 64 * NC;
+        const int kq = 4 * (pt % (BK / 4)), r0 = pt / (BK / 4);
+        constexpr int RSTEP = PT / (BK / 4);
+        static_assert(RSTEP % 16 == 0, "the swizzle of a thread's rows is one");
+        // (a uniform base and a 32-bit offset per unit; rows past M: never stored)
+        const char *src = reinterpret_cast<const char *>(g.A + (long)m0 * g.lda);
+        unsigned row_at[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) row_at[i] = (unsigned)min(r0 + i * RSTEP, g.M - 1 - m0) * (4u * (unsigned)g.lda);
+        float4 r[PF][NV];
+        // Nothing is read past a row: a unit that reaches over its end (the last K tile of a K that is no multiple of 64,
+        // and the requests behind the last tile) reads the row's last four values, and stash() puts them into
+        // place.  No branch around the loads: where paths with different numbers of loads in flight meet, the
+        // compiler waits for the larger one, which cost a whole K tile of prefetch distance.
+        const int klast = g.K >= 4 ? g.K - 4 : 0;
+        auto fetch = [&](int set, int t) {
+            const unsigned k = 4u * (unsigned)min(t * BK + kq, klast);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const f32x4u v = *reinterpret_cast<const f32x4u *>(src + (row_at[i] + k));
+                r[set][i] = make_float4(v.x, v.y, v.z, v.w);
+            }
+        };
+        float sc[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) sc[i] = 1.f;
+        // Two planes: the 16 lanes that stage a row gather the words of its largest magnitude among them, and one of them
+        // hands log2 of the scale to the consumers (which read it behind the K loop).
+        unsigned rw[NV];
+        if constexpr (NPL == 2) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const unsigned *w = g.rows + min(m0 + r0 + i * RSTEP, g.M - 1);
+                rw[i] = w[(long)min(kq / 4, g.row_parts - 1) * g.row_stride];
+                for (int j = kq / 4 + 16; j < g.row_parts; j += 16) rw[i] = max(rw[i], w[(long)j * g.row_stride]);
+            }
+        }
+        const bool narrow = g.K < 4;
+        if (narrow) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                float v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = kq + j < g.K ? reinterpret_cast<const float *>(src + row_at[i])[kq + j] : 0.f;
+                r[0][i] = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < PF; ++j) fetch(j, j);
+        }
+        if constexpr (NPL == 2) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                unsigned v = rw[i];
+                v = max(v, dpp_move<0xb1>(v));                        // quad_perm [1,0,3,2]
+                v = max(v, dpp_move<0x4e>(v));                        // quad_perm [2,3,0,1]
+                v = max(v, dpp_move<0x124>(v));                       // row_ror:4
+                v = max(v, dpp_move<0x128>(v));                       // row_ror:8
+                const int e = log2_scale_of(v);
+                sc[i] = pow2f(e);
+                if (kq == 0) rowexp[r0 + i * RSTEP] = e;
+            }
+        }
+        const int ktail = (g.K % BK != 0 && !narrow) ? nk - 1 : nk;      // the K tile that hangs over
+        auto stash = [&](int set, int t) {
+            if (t == ktail) {
+                const int sh = t * BK + kq - klast;              // > 0: the unit was read sh values early; >= 4: it lies past the row
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    const float4 v = r[set][i];
+                    r[set][i] = make_float4(sh <= 0 ? v.x : (sh == 1 ? v.y : (sh == 2 ? v.z : (sh == 3 ? v.w : 0.f))),
+                                            sh <= 0 ? v.y : (sh == 1 ? v.z : (sh == 2 ? v.w : 0.f)),
+                                            sh <= 0 ? v.z : (sh == 1 ? v.w : 0.f), sh <= 0 ? v.w : 0.f);
+                }
+            }
+            __bf16 *st = stages + (t % NS) * STAGE + r0 * S + 8 * pk_swizzle(r0, kq / 8) + kq % 8;      // (RSTEP rows on: the same)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const Split4 sp = NPL == 3 ? split3(r[set][i]) : split2_f16_mix(r[set][i], sc[i]);
+#pragma unroll
+                for (int p = 0; p < NPL; ++p) *reinterpret_cast<bf16x4 *>(st + p * PLANE + i * RSTEP * S) = sp.p[p];
+            }
+        };
+        static_assert(NS == 2, "the loop below");
+        stash(0, 0);
+        fetch(0, PF);
+        __syncthreads();
+        if constexpr (SCANS) flags = scan_flags<FR, EPI == 8>(g.scan, flag_bytes, m0);
+        // iteration kt stages tile kt + 1 from register set (kt + 1) % PF while the consumers work on tile kt
+        for (int kt = 0; kt + 1 < nk; kt += PF) {
+#pragma unroll
+            for (int j = 0; j < PF; ++j) {
+                if (kt + j + 1 >= nk) break;
+                stash((j + 1) % PF, kt + j + 1);
+                fetch((j + 1) % PF, kt + j + 1 + PF);
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+        if constexpr (EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
+        if constexpr (!SCANS) in.request(g, tid, 0, m0, n0);
+        __syncthreads();                             // barriers 1 and 2, see below
+        __syncthreads();
+    } else {
+        // ------------------------------------------------------------------ consumers
+        const int li = l & 31, hh = l >> 5;
+        const int cg = wave % CG, kw = wave / CG;
+        const bool work = n0 + cg * 32 < g.N;       // (a wavefront whose 32 columns lie past N only attends the barriers)
+        v16f acc[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+        const int nks = nk * KS;
+        const uint4 *bp = g.frag + ((size_t)(work ? n0 / 32 + cg : 0) * nks + kw * KSW) * (NPL * 64) + l;
+        int frag_at[KSW];
+#pragma unroll
+        for (int ks = 0; ks < KSW; ++ks) frag_at[ks] = li * S + 8 * pk_swizzle(li, 2 * (kw * KSW + ks) + hh);
+        uint4 fb[PFB][NPL];
+        constexpr int MG = MI < 2 ? MI : 2, NG = MI / MG;         // row fragments per step of the loop below, steps per k step
+        bf16x8 fa[2][MG][NPL];
+        auto load_weights = [&](int set, int s) {
+#pragma unroll
+            for (int p = 0; p < NPL; ++p) fb[set][p] = bp[(size_t)s * (NPL * 64) + p * 64];
+        };
+        auto load_rows = [&](int set, int kt, int ks, int ig) {
+            const __bf16 *st = stages + (kt % NS) * STAGE + frag_at[ks];
+#pragma unroll
+            for (int i = 0; i < MG; ++i)
+#pragma unroll
+                for (int p = 0; p < NPL; ++p) fa[set][i][p] = *reinterpret_cast<const bf16x8 *>(st + p * PLANE + (ig * MG + i) * 32 * S);
+        };
+        // the products of one accumulator keep their order (smallest first): a3b1, a2b2, a1b3, a2b1, a1b2, a1b1 with
+        // three planes, a2b1, a1b2, a1b1 with two
+        auto multiply = [&](int sa, int sb, int ig) {
+            constexpr int NPROD = NPL == 3 ? 6 : 3;
+            constexpr int PA3[6] = {2, 1, 0, 1, 0, 0}, PB3[6] = {0, 1, 2, 0, 1, 0};
+            constexpr int PA2[3] = {1, 0, 0}, PB2[3] = {0, 1, 0};
+#pragma unroll
+            for (int p = 0; p < NPROD; ++p)
+#pragma unroll
+                for (int i = 0; i < MG; ++i) {
+                    v16f &c = acc[ig * MG + i];
+                    if constexpr (NPL == 3)
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[sa][i][PA3[p]], __builtin_bit_cast(bf16x8, fb[sb][PB3[p]]), c, 0, 0, 0);
+                    else
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[sa][i][PA2[p % 3]]),
+                                                                   __builtin_bit_cast(f16x8, fb[sb][PB2[p % 3]]), c, 0, 0, 0);
+                }
+        };
+        int eb = 0;                                   // log2 of the scale of this lane's weight row
+        if (work) {
+#pragma unroll
+            for (int s = 0; s < PFB; ++s) load_weights(s, min(s / KSW, nk - 1) * KS + s % KSW);
+            if constexpr (NPL == 2) eb = g.bexp[n0 + cg * 32 + li];
+        }
+        __syncthreads();
+        if constexpr (SCANS) flags = scan_flags<FR, EPI == 8>(g.scan, flag_bytes, m0);
+        if (work) {
+            load_rows(0, 0, 0, 0);
+            constexpr int KU = PFB > KSW ? PFB / KSW : 1;           // K tiles per round of the fragments' registers
+            for (int kt0 = 0; kt0 < nk; kt0 += KU) {
+#pragma unroll
+                for (int u = 0; u < KU; ++u) {
+                    const int kt = kt0 + u;
+                    if (KU > 1 && kt >= nk) break;
+#pragma unroll
+                    for (int st = 0; st < KSW * NG; ++st) {
+                        // the row fragments of the next step are requested before the matrix instructions of this one; at the
+                        // last step of a K tile the workgroup barrier comes first: it releases the stage just read and
+                        // guarantees that the next one is filled
+                        const int ks = st / NG, ig = st % NG, set = (u * KSW + ks) % PFB, rs = (u * KSW * NG + st) & 1;
+                        if (st + 1 < KSW * NG) load_rows(rs ^ 1, kt, (st + 1) / NG, (st + 1) % NG);
+                        else {
+                            __syncthreads();
+                            load_rows(rs ^ 1, kt + 1, 0, 0);   // past the last tile: a harmless read of a stale stage
+                        }
+                        multiply(rs, set, ig);
+                        if (ig == NG - 1) {
+                            const int tn = kt + (ks + PFB) / KSW;
+                            load_weights(set, min(tn, nk - 1) * KS + (ks + PFB) % KSW);
+                        }
+                        // issue order: an LDS read in the shadow of each of the first matrix instructions, the loads of the
+                        // weights behind the last
+                        constexpr int NREAD = NPL * MG, NMFMA = (NPL == 3 ? 6 : 3) * MG;
+#pragma unroll
+                        for (int z = 0; z < NREAD; ++z) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        }
+                        __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NREAD, 0);
+                        if (ig == NG - 1) __builtin_amdgcn_sched_group_barrier(0x020, NPL, 0);
+                    }
+                }
+            }
+        } else {
+            for (int kt = 0; kt < nk; ++kt) __syncthreads();
+        }
+
+        auto row_of = [&](int i, int r) { return i * 32 + 8 * (r / 4) + 4 * hh + (r % 4); };     // row inside the tile
+        if constexpr (NPL == 2) {
+            // the power of two that takes both operand scales off again (their sum can leave the exponent range of a
+            // single factor: one exponent adjustment per element, exact like a multiplication by the power)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][r] = __builtin_ldexpf(acc[i][r], -(rowexp[row_of(i, r)] + eb));
+        }
+        // (at 128 rows the accumulators leave no registers for the inputs before they are staged)
+        if constexpr (EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
+        if constexpr (!SCANS && MI < 4) in.request(g, tid, 0, m0, n0);
+        __syncthreads();                                 // barrier 1: every wavefront has left the K loop, LDS is free
+        float *out = reinterpret_cast<float *>(smem_raw);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[kw * BM * BN + tile_at<BN>(row_of(i, r), cg * 32 + li)] = acc[i][r];
+        if constexpr (!SCANS && MI == 4) in.request(g, tid, 0, m0, n0);
+        __syncthreads();                                 // barrier 2: the tile is staged
+    }
+
+    // (producers and consumers together: one copy of the code)
+    if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags);
+    else {
+#pragma unroll
+        for (int batch = 0; batch < in.BATCHES; ++batch) {
+            if (batch > 0) in.request(g, tid, batch, m0, n0);
+            in.store(g, reinterpret_cast<const float *>(smem_raw), tid, batch, m0, n0);
+        }
+    }
+}
+
+// Tile of the workgroup in slot q of XCD x (workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2):
+//   mode 0: XCD x owns the contiguous band of tiles [x nx, (x+1) nx), so it reads its band of A and the weights once
+//           into its own L2;
+//   mode 5 (scan epilogues): a unit = the tiles of one sequence and one group of column tiles, time-major; units are dealt
+//           to the XCDs, so a tile only ever waits for tiles in earlier slots of its own XCD, which were dispatched
+//           before it.
+__device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
+{
+    if (g.mode == 0) return x * g.nx + q;
+    const int per_unit = g.sc_nt * g.sc_cpu;
+    const int uid = x + 8 * (q / per_unit), r = q % per_unit;
+    const int b = uid / g.sc_ncg, cg = uid % g.sc_ncg;
+    const int tn = cg * g.sc_cpu + r % g.sc_cpu;
+    const int tslot = r / g.sc_cpu;                 // time-ordered slot; the reverse scan starts at the sequence end
+    const int tmL = g.sc_rev ? g.sc_nt - 1 - tslot : tslot;
+    return (uid < g.sc_units && tn < g.ntn) ? (b * g.sc_nt + tmL) * g.ntn + tn : g.ntm * g.ntn;
+}
+
+// The tile of a product.
+//   32 rows where 64-row tiles would occupy at most half of the CUs (1024 x 1024 x 512, 128 tiles of 64 x 128: 6.2 us
+//     against 7.7; 4096 x 512 x 1024, 256 tiles: 16.7 against 14.5).  What a workgroup then waits for is its chain of
+//     dependent matrix instructions (a 32 x 128 x 64 tile of three planes: 24 on one accumulator, 0.55 us), so fewer columns,
+//     whose consumers share out k, until there are two workgroups per CU.
+//   128 rows (two planes) where they give every CU two workgroups
+//     (32768 x 512 x 1024: 117 us against 122; 4800 x 1024 x 1024, 304 tiles: 47 against 40), and where that lets the reductions that
+//     follow in the launch start at once instead of behind the first round (4800 x 1024 x 1024 with 192 items: 75 against 100).
+struct PkTile { int rows, cols; };
+inline PkTile pk_tile(const GemmArgs &a, int64_t other_items, bool follow)
+{
+    const auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    if (tiles(64, 128) <= 128)
+        return {32, a.c2_rowmax || tiles(32, 64) + other_items > 256 ? 128 : tiles(32, 32) + other_items > 128 ? 64 : 32};
+    const int64_t following_items = follow ? other_items : 0;
+    if (a.planes != 2) return {64, 128};
+    return {tiles(128, 128) >= 512 || (following_items > 0 && tiles(64, 128) + following_items > 512 && tiles(128, 128) + following_items <= 512) ? 128 : 64, 128};
+}
+
+template <int TB>
+int64_t reduction_items(const GemmArgs *t)
+{
+    return t ? (int64_t)((t->M + TB - 1) / TB) * ((t->N + TB - 1) / TB) * (t->splits < 1 ? 1 : t->splits) : 0;
+}
+
+constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, bool scans)
+{
+    const size_t st = (size_t)PK_STAGES * NPL * BM * PK_BK * 2 + (size_t)BM * 4;       // stages and scales
+    const size_t ep = scans ? scan_lds_bytes(BM) : (size_t)BM * BN * 4 * (128 / BN);             // the staged tile
+    return ep > st ? ep : st;
+}
+
+// One launch carries a product with packed weights and up to two K = T reductions (TNB > 0: their tile is
+// TNB x TNB; absent ones have no slots).  Every problem owns a contiguous range of the slots of every XCD.
+// (a reduction may have more wavefronts than a product; the surplus leaves a product's workgroup at once)
+constexpr int pk_threads(int TNB) { return TNB > 0 ? 64 * (tn_consumers(TNB) + tn_producers(TNB)) : PK_THREADS; }
+
+template <int BM, int BN, int NPL, int EPI, int TNB, int WPE>
+__global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int x = blockIdx.x % 8, q = blockIdx.x / 8, tid = threadIdx.x;
+    if (TNB == 0 || (q >= g.slot0 && q < g.slot0 + g.nx)) {
+        const int tile = pk_place(g, x, q - g.slot0);
+        if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
+        const int tm = tile / g.ntn, tn = tile - tm * g.ntn;
+        gemm_pk_tile<BM, BN, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid);
+    } else if constexpr (TNB > 0) {
+        if (q >= t0.slot0 && q < t0.slot0 + t0.nx) gemm_tn_problem<TNB, NPL>(t0, smem_raw, x, q - t0.slot0, tid);
+        // (a branch of its own: choosing between the two argument structs at run time would put them on the stack)
+        else gemm_tn_problem<TNB, NPL>(t1, smem_raw, x, q - t1.slot0, tid);
+    }
+}
+
+template <int BM, int BN>
+inline PkDev make_pk_dev(const GemmArgs &a)
+{
+    PkDev g{};
+    g.A = a.A; g.lda = a.lda; g.frag = static_cast<const uint4 *>(a.w.frag); g.bexp = a.w.exp; g.C = a.C; g.ldc = a.ldc;
+    g.diag = a.diag; g.E = a.E; g.lde = a.lde; g.E2 = a.E2; g.C2 = a.C2; g.rowflag = a.rowflag;
+    g.M = a.M; g.N = a.N; g.K = a.K; g.nkt = (a.K + PK_BK - 1) / PK_BK;
+    g.ntm = (a.M + BM - 1) / BM; g.ntn = (a.N + BN - 1) / BN;
+    const long ntiles = (long)g.ntm * g.ntn;
+    g.nx = (int)((ntiles + 7) / 8); g.mode = 0; g.slot0 = 0;
+    g.scan = a.scan;
+    g.rows = a.amaxA.rows; g.row_parts = a.amaxA.row_parts; g.row_stride = a.amaxA.row_stride;
+    g.c2_rowmax = a.c2_rowmax;
+    if ((a.epilogue == 7 || a.epilogue == 8) && a.scan.L >= BM) {
+        g.sc_rev = a.epilogue == 8;
+        const int nseq = a.M / a.scan.L;
+        g.sc_nt = a.scan.L / BM;
+        int ncg = nseq >= 8 ? 1 : (8 + nseq - 1) / nseq;
+        if (ncg > g.ntn) ncg = g.ntn;
+        g.sc_ncg = ncg;
+        g.sc_cpu = (g.ntn + ncg - 1) / ncg;
+        g.sc_units = nseq * ncg;
+        g.mode = 5;
+        g.nx = ((g.sc_units + 7) / 8) * g.sc_nt * g.sc_cpu;
+    }
+    return g;
+}
+
+// t0, t1: the reductions of the launch (null: none; t1 only with t0); tn_first: their work items take the first slots.
+template <int BM, int BN, int NPL, int EPI, int TNB, int WPE>
+hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
+{
+    if ((TNB > 0) != (b != nullptr) || (c && !b)) return hipErrorInvalidValue;
+    PkDev g = make_pk_dev<BM, BN>(a);
+    GemmDev t[2]{};
+    long slots = 0;
+    if (!tn_first) { g.slot0 = 0; slots = g.nx; }
+    if constexpr (TNB > 0) {
+        const GemmArgs *tn[2] = {b, c};
+        for (int i = 0; i < 2; ++i) {
+            if (tn[i]) t[i] = make_tn_dev<TNB>(*tn[i]);
+            t[i].slot0 = (int)slots;
+            slots += t[i].nx;
+        }
+    }
+    if (tn_first) { g.slot0 = (int)slots; slots += g.nx; }
+    constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI == 7 || EPI == 8), tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL) : 0;
+    constexpr size_t smem = pk > tnl ? pk : tnl;
+    auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE>;
+    static std::atomic<bool> raised[KERNEL_MAXDEV];
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), smem, raised);
+    if (e != hipSuccess) return e;
+    if (slots <= 0 || slots > 0x7fffffffL / 8) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(pk_threads(TNB)), smem, s, g, t[0], t[1]);
+    return hipGetLastError();
+}
+
+}  // namespace ssm

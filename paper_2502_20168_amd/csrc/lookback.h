@@ -9,7 +9,8 @@ namespace ssm {
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    // (one rounding order wherever it is inlined)
+    return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x));
 }
 // a * b + c
 __device__ __forceinline__ float2 cfma(float2 a, float2 b, float2 c)

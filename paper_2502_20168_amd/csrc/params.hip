@@ -3,44 +3,9 @@
 // The handful of transcendental evaluations per state run in double precision: they are
 // P-sized (a few hundred values), and the (exp(z) - 1)/z quotient cancels badly in fp32 for the
 // small |Lambda Delta| that slowly decaying states have.
-#include "ssm_internal.h"
+#include "pack.h"
 
 namespace ssm {
-
-struct Zoh {
-    double delta;
-    double lr, li;   // Abar = exp(Lambda Delta)
-    double gr, gi;   // g = (Abar - 1)/Lambda = Delta * expm1(z)/z
-    double zr, zi;   // z = Lambda Delta
-};
-
-__device__ __forceinline__ void cdiv(double ar, double ai, double br, double bi, double &qr, double &qi)
-{
-    const double den = br * br + bi * bi;
-    qr = (ar * br + ai * bi) / den;
-    qi = (ai * br - ar * bi) / den;
-}
-
-__device__ Zoh zoh_discretize(float2 Lambda, float log_delta)
-{
-    Zoh o;
-    o.delta = exp((double)log_delta);
-    o.zr = (double)Lambda.x * o.delta;
-    o.zi = (double)Lambda.y * o.delta;
-    const double ea = exp(o.zr), cb = cos(o.zi), sb = sin(o.zi), sh = sin(0.5 * o.zi);
-    o.lr = ea * cb;
-    o.li = ea * sb;
-    // exp(z) - 1 with the cancellation removed: expm1(a) cos b - 2 sin^2(b/2) + i e^a sin b
-    const double er = expm1(o.zr) * cb - 2.0 * sh * sh, ei = ea * sb;
-    if (o.zr == 0.0 && o.zi == 0.0) {
-        o.gr = o.delta; o.gi = 0.0;
-    } else {
-        double qr, qi;
-        cdiv(er, ei, o.zr, o.zi, qr, qi);
-        o.gr = o.delta * qr; o.gi = o.delta * qi;
-    }
-    return o;
-}
 
 // ---------------------------------------------------------------------------------------------
 // partial[s][h] = sum_{t in slab s} a[t,h] * b[t,h]      (dD = sum_t dy_t (.) u_t)
@@ -266,101 +231,107 @@ __device__ __forceinline__ void absmax_pass_block(const PrepArgs::Pass &q, int p
     if (tid == 0) q.slots[piece] = u;
 }
 
-// Workgroups [0, P): state p -> Abar_p, packed Bbar rows 2p, 2p+1 (and the interleaved complex
-// Bbar when asked).  Workgroups [P, P+H): row h of C -> (Re, -Im) interleaved.  Further workgroups
-// (gradient pass only): the column-dot slabs behind dD.
-__global__ void __launch_bounds__(256) prep_kernel(PrepArgs a)
+// Everything that has to be done before the products of a pass, in one launch: the weights of its products in
+// fragment order, the column-dot slabs behind dD (gradient pass), the largest magnitudes that scale the planes of
+// the activations, and the words to be cleared.  The longest chains of dependent work come first in the grid.
+__global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
 {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
     const int blk = blockIdx.x, tid = threadIdx.x;
     if (blk == 0 && tid == 0 && a.hdr) {
         a.hdr->err = 0; a.hdr->magic = 0x53534d31u;
     }
-    if (a.pass[0].nblocks > 0 && blk >= a.pass[0].block0) {
-        // passes over the activations whose largest magnitude no earlier kernel could record
-        const int second = (a.pass[1].nblocks > 0 && blk >= a.pass[1].block0) ? 1 : 0;
-        absmax_pass_block(a.pass[second], blk - a.pass[second].block0);
-    } else if (blk < a.P) {
-        const int p = blk;
-        const Zoh z = zoh_discretize(a.Lambda[p], a.log_delta[p]);
-        const float gr = (float)z.gr, gi = (float)z.gi;
-        if (tid == 0 && a.lam_bar) a.lam_bar[p] = make_float2((float)z.lr, (float)z.li);
-        float m = 0.f;
-        if (a.B) {
-            for (int h = tid; h < a.H; h += 256) {
-                const float2 bv = a.B[(long)p * a.H + h];
-                const float re = gr * bv.x - gi * bv.y, im = gr * bv.y + gi * bv.x;
-                if (a.Bbar_ri) {
-                    a.Bbar_ri[(long)(2 * p) * a.H + h] = re;
-                    a.Bbar_ri[(long)(2 * p + 1) * a.H + h] = im;
-                }
-                if (a.Bbar_c64) a.Bbar_c64[(long)p * a.H + h] = make_float2(re, im);
-                m = fmaxf(m, fmaxf(fabsf(re), fabsf(im)));
-            }
-        }
-        if (a.bbar_max) {
-            const unsigned u = block_absmax(m);
-            if (tid == 0) a.bbar_max[p] = u;
-        }
-    } else if (blk < a.P + a.H) {
-        const int h = blk - a.P;
-        const float2 *src = a.C + (long)h * a.P;
-        float2 *dst = reinterpret_cast<float2 *>(a.Cc) + (long)h * a.P;
-        float m = 0.f;
-        for (int p = tid; p < a.P; p += 256) {
-            const float2 c = src[p];
-            dst[p] = make_float2(c.x, -c.y);
-            m = fmaxf(m, fmaxf(fabsf(c.x), fabsf(c.y)));
-        }
-        if (a.cc_max) {
-            const unsigned u = block_absmax(m);
-            if (tid == 0) a.cc_max[h] = u;
-        }
-    } else if (a.zero16 && blk >= a.zero_block0) {
-        // clears the tagged words that the scanning input projection will publish into
-        const size_t per = 256 * 8;
-        const size_t i0 = (size_t)(blk - a.zero_block0) * per + tid;
+    const PackSrc src{a.Lambda, a.B, a.C, a.log_delta, a.W, a.P, a.H, a.lam_bar};
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const size_t i = i0 + (size_t)j * 256;
-            if (i < a.n16) a.zero16[i] = make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < PREP_MAX_PACKS; ++i) {
+        if (i < a.npack && blk < a.pack[i].block0 + a.pack[i].nblocks) {
+            pack_dispatch(src, a.pack[i], blk - a.pack[i].block0, lds);
+            return;
         }
-    } else {
-        // column-dot slabs of the gradient pass share this launch (they depend on nothing here)
-        const int cb = blk - (a.P + a.H);
-        coldot_block(a.cd, cb % a.cd_colblocks, cb / a.cd_colblocks, a.cd_amax, a.cd_bmax, cb, a.cd_arow);
     }
+    if (a.cd.partial && blk < a.cd_block0 + a.cd_colblocks * a.cd.nslab) {
+        const int cb = blk - a.cd_block0;
+        coldot_block(a.cd, cb % a.cd_colblocks, cb / a.cd_colblocks, a.cd_amax, a.cd_bmax, cb, a.cd_arow);
+        return;
+    }
+    if (a.pass.nblocks > 0 && blk < a.pass.block0 + a.pass.nblocks) {
+        absmax_pass_block(a.pass, blk - a.pass.block0);
+        return;
+    }
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+        if (a.zero[z].nblocks > 0 && blk < a.zero[z].block0 + a.zero[z].nblocks) {
+            const size_t i0 = (size_t)(blk - a.zero[z].block0) * (256 * 8) + tid;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const size_t i = i0 + (size_t)k * 256;
+                if (i < a.zero[z].n16) a.zero[z].p[i] = make_uint4(0, 0, 0, 0);
+            }
+            return;
+        }
+    }
+}
+
+int pack_blocks(int kind, int N)
+{
+    const int per = pack_lanes(kind) * pack_per_lane(kind), npad = (N + 31) / 32 * 32;
+    return (npad + per - 1) / per;
 }
 
 hipError_t launch_prep(const PrepArgs &a_in, hipStream_t s)
 {
     PrepArgs a = a_in;
-    a.cd_colblocks = 0;
-    unsigned blocks = (unsigned)(a.P + (a.Cc ? a.H : 0));
+    long blocks = 0;
+    if (a.npack < 0 || a.npack > PREP_MAX_PACKS) return hipErrorInvalidValue;
+    for (int i = 0; i < a.npack; ++i) {
+        PackJob &j = a.pack[i];
+        if (!j.frag || (j.planes != 3 && (j.planes != 2 || !j.exp))) return hipErrorInvalidValue;
+        j.block0 = (int)blocks; j.nblocks = pack_blocks(j.kind, j.N);
+        blocks += j.nblocks;
+    }
+    a.cd_block0 = (int)blocks; a.cd_colblocks = 0;
     if (a.cd.partial) {
-        if (!a.Cc) return hipErrorInvalidValue;       // block ranges assume the C rows are present
         a.cd_colblocks = (a.cd.H + 63) / 64;
-        blocks += (unsigned)(a.cd_colblocks * a.cd.nslab);
+        blocks += (long)a.cd_colblocks * a.cd.nslab;
     }
-    a.zero_block0 = 0;
-    if (a.zero16 && a.n16 > 0) {
-        if (!a.Cc) return hipErrorInvalidValue;       // block ranges assume the C rows are present
-        a.zero_block0 = (int)blocks;
-        blocks += (unsigned)((a.n16 + 256 * 8 - 1) / (256 * 8));
-    } else {
-        a.zero16 = nullptr;
-    }
-    // the passes come last; pass[1] without pass[0] moves up
-    if (a.pass[0].nblocks <= 0 && a.pass[1].nblocks > 0) { a.pass[0] = a.pass[1]; a.pass[1].nblocks = 0; }
-    for (int i = 0; i < 2; ++i) {
-        PrepArgs::Pass &q = a.pass[i];
-        if (q.nblocks <= 0) { q.nblocks = 0; continue; }
-        if (!a.Cc || !q.x || !q.slots) return hipErrorInvalidValue;
+    PrepArgs::Pass &q = a.pass;
+    if (q.nblocks > 0) {
+        if (!q.x || !q.slots) return hipErrorInvalidValue;
         q.vec = (reinterpret_cast<uintptr_t>(q.x) & 15) == 0 && q.n % 4 == 0 && q.rowlen % 4 == 0;
         if (q.rowlen < 0 || (q.rowlen > 0 && q.n % (size_t)q.rowlen != 0)) return hipErrorInvalidValue;
         q.block0 = (int)blocks;
-        blocks += (unsigned)q.nblocks;
+        blocks += q.nblocks;
     }
-    hipLaunchKernelGGL(prep_kernel, dim3(blocks), dim3(256), 0, s, a);
+    for (PrepArgs::Zero &z : a.zero) {
+        z.block0 = (int)blocks;
+        z.nblocks = (z.p && z.n16 > 0) ? (int)((z.n16 + 256 * 8 - 1) / (256 * 8)) : 0;
+        blocks += z.nblocks;
+    }
+    if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// Workgroup p: Abar_p and, when asked, row p of Bbar as interleaved complex.
+__global__ void __launch_bounds__(256) discretize_kernel(const float2 *__restrict__ Lambda, const float2 *__restrict__ B,
+                                                         const float *__restrict__ log_delta, int H, float2 *__restrict__ lam_bar,
+                                                         float2 *__restrict__ Bbar)
+{
+    const int p = blockIdx.x;
+    const Zoh z = zoh_discretize(Lambda[p], log_delta[p]);
+    const float gr = (float)z.gr, gi = (float)z.gi;
+    if (threadIdx.x == 0) lam_bar[p] = make_float2((float)z.lr, (float)z.li);
+    if (Bbar)
+        for (int h = threadIdx.x; h < H; h += 256) {
+            const float2 b = B[(long)p * H + h];
+            Bbar[(long)p * H + h] = make_float2(gr * b.x - gi * b.y, gr * b.y + gi * b.x);
+        }
+}
+
+hipError_t launch_discretize(const float2 *Lambda, const float2 *B, const float *log_delta, int P, int H, float2 *lam_bar, float2 *Bbar,
+                             hipStream_t s)
+{
+    hipLaunchKernelGGL(discretize_kernel, dim3((unsigned)P), dim3(256), 0, s, Lambda, B, log_delta, H, lam_bar, Bbar);
     return hipGetLastError();
 }
 
@@ -447,39 +418,11 @@ __device__ __forceinline__ void block_sum2(double *red_r, double *red_i, double 
     i = (red_i[0] + red_i[1]) + (red_i[2] + red_i[3]);
 }
 
-// 2048 elements per workgroup (eight per thread, as two float4 where alignment allows)
-__device__ __forceinline__ void sum_halves_block(const SumHalvesArgs &a, int blk, int tid)
-{
-    const long base = (long)blk * 2048;
-    if (a.vec) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const long i = base + 4L * (tid + 256 * j);
-            if (i < a.n) {
-                const float4 x = *reinterpret_cast<const float4 *>(a.s0 + i), y = *reinterpret_cast<const float4 *>(a.s1 + i);
-                const float4 e = *reinterpret_cast<const float4 *>(a.e + i);
-                const float4 d = *reinterpret_cast<const float4 *>(a.D + i % a.H);
-                *reinterpret_cast<float4 *>(a.out + i) = make_float4(fmaf(d.x, e.x, x.x + y.x), fmaf(d.y, e.y, x.y + y.y),
-                                                                     fmaf(d.z, e.z, x.z + y.z), fmaf(d.w, e.w, x.w + y.w));
-            }
-        }
-    } else {
-        for (int j = 0; j < 8; ++j) {
-            const long i = base + tid + 256L * j;
-            if (i < a.n) a.out[i] = fmaf(a.D[i % a.H], a.e[i], a.s0[i] + a.s1[i]);
-        }
-    }
-}
-
 __global__ void __launch_bounds__(256) epilogue_kernel(EpilogueArgs a)
 {
     __shared__ double red_r[256], red_i[256];
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x < a.sum.nblocks) {        // the streaming sum of the two halves of du comes first
-        sum_halves_block(a.sum, blockIdx.x, tid);
-        return;
-    }
-    const int blk = blockIdx.x - a.sum.nblocks;
+    const int blk = blockIdx.x;
     const long PH2 = 2L * a.P * a.H;
     if (blk < a.P) {
         // The workgroups of this launch are all resident at once, so it lasts as long as the chain of dependent
@@ -555,18 +498,9 @@ __global__ void __launch_bounds__(256) epilogue_kernel(EpilogueArgs a)
     }
 }
 
-hipError_t launch_epilogue(const EpilogueArgs &a_in, hipStream_t s)
+hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s)
 {
-    EpilogueArgs a = a_in;
-    a.sum.nblocks = 0; a.sum.vec = 0;
-    if (a.sum.s0) {
-        auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-        a.sum.vec = a.sum.H % 4 == 0 && al16(a.sum.s0) && al16(a.sum.s1) && al16(a.sum.D) && al16(a.sum.e) && al16(a.sum.out);
-        const long nb = (a.sum.n + 2047) / 2048;
-        if (nb > 0x7fff0000L) return hipErrorInvalidValue;
-        a.sum.nblocks = (int)nb;
-    }
-    hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)(a.sum.nblocks + a.P + a.H)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)(a.P + a.H)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

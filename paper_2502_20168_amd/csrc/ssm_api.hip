@@ -74,7 +74,23 @@ namespace {
 constexpr size_t ALIGN = 256;
 inline size_t up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
-constexpr int64_t SMALL_HALVES_MIN_P = 256;      // a small du as two K halves: each half keeps four K steps of 64
+// weights of one product in fragment order, and the exponents of their rows (two planes)
+struct PackedLayout { size_t frag, exp; int N, K; };
+void add_packed(size_t &off, PackedLayout &o, int64_t N, int64_t K, int planes)
+{
+    o.N = (int)N; o.K = (int)K;
+    o.frag = off; off += up(packed_frag_bytes(N, K, planes));
+    o.exp = off; off += up((size_t)(N + 31) / 32 * 32 * 4);
+}
+PackJob pack_job(char *base, const PackedLayout &l, int kind, int planes)
+{
+    PackJob j{};
+    j.kind = kind; j.N = l.N; j.K = l.K; j.planes = planes;
+    j.frag = base + l.frag; j.exp = reinterpret_cast<int *>(base + l.exp);
+    return j;
+}
+PackedW packed(const char *base, const PackedLayout &l) { return PackedW{base + l.frag, reinterpret_cast<const int *>(base + l.exp)}; }
+
 struct Layout {
     ScanPlan plan;
     int splitC, splitB, nslab;
@@ -87,10 +103,13 @@ struct Layout {
     bool planes2_unfused;
     bool slabs_first;        // launch of three products: the slabs' work items go first
     bool dc_first, db_first; // launches of two products (separate scan kernels): the slab items go first
-    size_t hdr, lam, Bri, Cc, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, yhalves, total;
+    int planes;              // per operand of every product
+    PackedLayout w_in, w_out;          // forward: Bbar and C
+    PackedLayout w_gx, w_du;           // gradient pass: both transposed
+    size_t hdr, lam, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
     // largest magnitudes of the operands of the products (shapes whose projections scan their own tiles):
     // amax_atomic: 2 x ABSMAX_SLOTS words gathered with atomics, directly before fdesc so that one range is
-    // cleared; amax_slots: [P] Bbar, [H] Cc, then 2 x PREP_PASS_BLOCKS and 2 x amax_cd words of the passes
+    // cleared; amax_slots: PREP_PASS_BLOCKS and 2 x amax_cd words of the passes
     size_t amax_atomic, amax_slots; int amax_cd;
     // per-row maxima of the operands whose rows are tokens: rowmax (u forward: [T]; dy gradient pass: [ceil(H/64), T]) and
     // rowpart [ceil(2P/128), T] (x forward, chi gradient pass: one word per column tile of the scanning projection)
@@ -125,7 +144,6 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.plan = plan_scan(Bt, L, P);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
     const int64_t rows128 = ((int64_t)T + 127) / 128;
-    bool du_small_halves = false;     // a small du on 64x64x64 tiles as two K halves (summed in the parameter epilogue's launch)
     o.slabs_first = o.dc_first = o.db_first = false;
     o.dc_early = gemm_scan_shape_ok(Bt, L, P) && rows128 * ((2 * P + 127) / 128) <= 192;
     if (gemm_scan_shape_ok(Bt, L, P) && !o.dc_early) {
@@ -137,26 +155,17 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         if (!gemm_scan_shape_ok(Bt, L, P)) {
             // separate scan kernels: a launch of two products with several rounds of work items
             o.splitC = gemm_pick_splits_balanced(H, 2 * P, (int64_t)T, rows128 * ((2 * P + 127) / 128), H, o.dc_first);
-            const bool du_halves = gemm_out_split_shape((int64_t)T, H, P);     // du as two K halves (see yhalves below)
-            o.splitB = gemm_pick_splits_balanced(2 * P, H, (int64_t)T, rows128 * ((H + 127) / 128) * (du_halves ? 2 : 1),
-                                                 du_halves ? P : 2 * P, o.db_first);
+            o.splitB = gemm_pick_splits_balanced(2 * P, H, (int64_t)T, rows128 * ((H + 127) / 128), 2 * P, o.db_first);
         }
-        const int64_t rows64 = ((int64_t)T + 63) / 64;
         if (gemm_small_pair((int64_t)T, 2 * P))
-            o.splitC = gemm_pick_splits_small(H, 2 * P, (int64_t)T, rows64 * ((2 * P + 63) / 64), H);
-        if (gemm_small_pair((int64_t)T, H)) {
-            // (measured: a gain when both halves keep four K steps and fit one round of workgroups with room for the slabs)
-            du_small_halves = bwd && P >= SMALL_HALVES_MIN_P && 2 * rows64 * ((H + 63) / 64) <= 256;
-            o.splitB = du_small_halves ? gemm_pick_splits_small(2 * P, H, (int64_t)T, 2 * rows64 * ((H + 63) / 64), P)
-                                       : gemm_pick_splits_small(2 * P, H, (int64_t)T, rows64 * ((H + 63) / 64), 2 * P);
-        }
+            o.splitC = gemm_pick_splits_small(H, 2 * P, (int64_t)T, (int64_t)T, 2 * P, H);
+        if (gemm_small_pair((int64_t)T, H))
+            o.splitB = gemm_pick_splits_small(2 * P, H, (int64_t)T, (int64_t)T, H, 2 * P);
     }
     o.nslab = coldot_slabs((int64_t)T);
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));
     o.lam = off; off += up((size_t)P * 8);
-    o.Bri = off; off += up((size_t)2 * P * H * 4);
-    o.Cc = off; off += up((size_t)2 * P * H * 4);
     o.ticket = off; off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
     o.desc = off; off += up(o.plan.desc_bytes);
     o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
@@ -172,7 +181,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.row_parts = 1;
         o.rowpart = off; off += up(T * 4);                           // rows of x / chi, directly behind: one range is cleared
         o.amax_cd = o.nslab * (int)((H + 63) / 64);
-        o.amax_slots = off; off += up((size_t)(P + H + 2 * PREP_PASS_BLOCKS + 2 * o.amax_cd) * 4);
+        o.amax_slots = off; off += up((size_t)(PREP_PASS_BLOCKS + 2 * o.amax_cd) * 4);
         o.rowmax = off; off += up(T * (size_t)((H + 63) / 64) * 4);
     }
     if (gemm_scan_shape_ok(Bt, L, P)) {              // tagged words of a projection that scans its own output
@@ -181,25 +190,26 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.fdesc_bytes = gemm_scan_desc_bytes(Bt, L, P);
         o.fdesc = off; off += up(o.fdesc_bytes);
         o.amax_cd = o.nslab * (int)((H + 63) / 64);
-        o.amax_slots = off; off += up((size_t)(P + H + 2 * PREP_PASS_BLOCKS + 2 * o.amax_cd) * 4);
+        o.amax_slots = off; off += up((size_t)(PREP_PASS_BLOCKS + 2 * o.amax_cd) * 4);
         o.row_parts = (int)((2 * P + 127) / 128);
         o.rowmax = off; off += up(T * (size_t)((H + 63) / 64) * 4);
         o.rowpart = off; off += up(T * (size_t)o.row_parts * 4);
-        const size_t per_tile = (size_t)(Bt * L / 128) * P;        // one dAbar row per 128-row tile
+        const size_t per_tile = (size_t)(Bt * L / gemm_scan_rows(Bt * L, P)) * P;  // one dAbar row per scanning tile
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
-    o.yhalves = 0;
+    o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
     if (!bwd) {
+        add_packed(off, o.w_in, 2 * P, H, o.planes);
+        add_packed(off, o.w_out, H, 2 * P, o.planes);
         o.xbuf = off; off += up(T * P * 8);
     } else {
+        add_packed(off, o.w_gx, 2 * P, H, o.planes);
+        add_packed(off, o.w_du, H, 2 * P, o.planes);
         o.chi = off; off += up(T * P * 8);
         o.dCpart = off; off += up((size_t)o.splitC * 2 * P * H * 4);
         o.dBpart = off; off += up((size_t)o.splitB * 2 * P * H * 4);
         o.dApart = off; off += up(dA_elems * 8);
         o.dDpart = off; off += up((size_t)o.nslab * H * 4);
-        // two K halves of du, where it shares its launch with the dBbar slabs only (at the scanning shapes it
-        // runs whole, first in a launch of three problems with two workgroups per CU)
-        if (!gemm_scan_shape_ok(Bt, L, P) && (gemm_out_split_shape((int64_t)T, H, P) || du_small_halves)) { o.yhalves = off; off += up(2 * T * H * 4); }
     }
     o.total = off;
     return SSM_OK;
@@ -253,16 +263,30 @@ struct StageTimer {
 #define MARK() do { if (timer) timer->mark(); } while (0)
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) return SSM_ERR_HIP; } while (0)
 
-// The S5 block: the gate's product consumes GELU(y) and W as two scaled fp16 planes, so the layer's forward
-// pass measures them on its way: the rows of GELU(y) where the output projection stores it, W in a pass
-// of the prep launch.
-struct GateMax { unsigned *x1_rowmax; const float *W; size_t nW; unsigned *wslots; int nwslots; };
+// What a pass needs cleared, in its prep launch: the words that gather maxima with atomics and, directly behind them, the
+// tagged words of the scanning projections or the row maxima of the recording scan kernels; the ticket counters and
+// descriptors of scan kernels with several workgroups along time.
+void zero_ranges(PrepArgs &pa, const Layout &lo, char *ws, bool fused, size_t T)
+{
+    if (lo.planes == 2) {
+        pa.zero[0].p = reinterpret_cast<uint4 *>(ws + lo.amax_atomic);
+        pa.zero[0].n16 = (2 * ABSMAX_SLOTS * 4 + (fused ? lo.fdesc_bytes : up(T * 4))) / 16;
+    }
+    if (!fused && lo.plan.nTB > 1) {
+        pa.zero[1].p = reinterpret_cast<uint4 *>(ws + lo.ticket);
+        pa.zero[1].n16 = (lo.desc + up(lo.plan.desc_bytes) - lo.ticket) / 16;
+    }
+}
+
+// The S5 block: the layer's forward pass prepares the gate's product on its way -- W goes into fragment order in the
+// prep launch, and with two planes the rows of GELU(y) are measured where the output projection stores it.
+struct GatePrep { unsigned *x1_rowmax; const float *W; PackJob w; };
 
 ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, const float *D,
                    const float *log_delta, const float *u, const uint8_t *is_first, const ssm_c64 *x0,
                    int64_t Bt, int64_t L, int64_t H, int64_t P, float *y, ssm_c64 *x, ssm_c64 *x_last,
                    void *workspace, size_t ws_bytes, hipStream_t s, StageTimer *timer, float *gelu_y = nullptr,
-                   const GateMax *gate_max = nullptr)
+                   const GatePrep *gate = nullptr)
 {
     if (!Lambda || !B || !C || !D || !log_delta || !u || !y) return SSM_ERR_INVALID_ARG;
     Layout lo;
@@ -277,63 +301,49 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     char *ws = static_cast<char *>(workspace);
     WsHeader *hdr = reinterpret_cast<WsHeader *>(ws + lo.hdr);
     float2 *lam = reinterpret_cast<float2 *>(ws + lo.lam);
-    float *Bri = reinterpret_cast<float *>(ws + lo.Bri);
-    float *Cc = reinterpret_cast<float *>(ws + lo.Cc);
     ScanDesc *desc = reinterpret_cast<ScanDesc *>(ws + lo.desc);
     float2 *xs = x ? reinterpret_cast<float2 *>(x) : reinterpret_cast<float2 *>(ws + lo.xbuf);
     const int T = (int)(Bt * L);
 
-    // Shapes whose sequences are whole numbers of 128-row tiles: the input projection scans its own
+    // Shapes whose sequences are whole numbers of 128-step pieces: the input projection scans its own
     // output tile and stores the states directly (no scan kernel, Bbar u never goes to memory).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
-    if (!fused && lo.plan.nTB > 1)
-        HIP_TRY(launch_clear(hdr, ws + lo.ticket, lo.desc + up(lo.plan.desc_bytes) - lo.ticket, s));
     PrepArgs pa{};
     pa.Lambda = reinterpret_cast<const float2 *>(Lambda); pa.B = reinterpret_cast<const float2 *>(B);
     pa.C = reinterpret_cast<const float2 *>(C); pa.log_delta = log_delta;
-    pa.P = (int)P; pa.H = (int)H; pa.lam_bar = lam; pa.Bbar_ri = Bri; pa.Cc = Cc; pa.Bbar_c64 = nullptr;
-    pa.hdr = (fused || lo.plan.nTB == 1) ? hdr : nullptr;
-    // the atomic slots and the tagged words behind them are cleared in the same launch
-    if (fused) { pa.zero16 = reinterpret_cast<uint4 *>(ws + lo.amax_atomic); pa.n16 = (2 * ABSMAX_SLOTS * 4 + lo.fdesc_bytes) / 16; }
-    if (lo.planes2_unfused) { pa.zero16 = reinterpret_cast<uint4 *>(ws + lo.amax_atomic); pa.n16 = (2 * ABSMAX_SLOTS * 4 + up((size_t)T * 4)) / 16; }
+    pa.P = (int)P; pa.H = (int)H; pa.lam_bar = lam; pa.hdr = hdr;
+    pa.pack[0] = pack_job(ws, lo.w_in, PACK_IN, lo.planes);
+    pa.pack[1] = pack_job(ws, lo.w_out, PACK_OUT, lo.planes);
+    pa.npack = 2;
+    zero_ranges(pa, lo, ws, fused, (size_t)T);
     // two scaled fp16 planes per operand: every operand of the two products brings its largest magnitude
-    const bool two_planes = fused || lo.planes2_unfused;
-    unsigned *am_bbar = reinterpret_cast<unsigned *>(ws + lo.amax_slots), *am_cc = am_bbar + P;
+    const bool two_planes = lo.planes == 2;
     unsigned *rowmax = reinterpret_cast<unsigned *>(ws + lo.rowmax), *rowpart = reinterpret_cast<unsigned *>(ws + lo.rowpart);
     if (two_planes) {
         // u and x enter their products with tokens as rows: every token gets its own scale
-        pa.bbar_max = am_bbar; pa.cc_max = am_cc;
-        pa.pass[0].x = u; pa.pass[0].n = (size_t)T * H; pa.pass[0].slots = rowmax; pa.pass[0].rowlen = (int)H;
-        pa.pass[0].nblocks = row_pass_blocks((size_t)T);
+        pa.pass.x = u; pa.pass.n = (size_t)T * H; pa.pass.slots = rowmax; pa.pass.rowlen = (int)H;
+        pa.pass.nblocks = row_pass_blocks((size_t)T);
     }
-    if (gate_max) {
-        pa.pass[1].x = gate_max->W; pa.pass[1].n = gate_max->nW; pa.pass[1].slots = gate_max->wslots;
-        pa.pass[1].nblocks = gate_max->nwslots; pa.pass[1].rowlen = 0;
-    }
+    if (gate) { pa.W = gate->W; pa.pack[pa.npack++] = gate->w; }
     HIP_TRY(launch_prep(pa, s));
     MARK();
 
     // v[t, 2p+c] = sum_h u[t,h] * Bbar_ri[2p+c, h]      (second scan-element component, Eq. 6)
     GemmArgs g1{};
-    g1.A = u; g1.lda = H; g1.a_kcontig = 1;
-    g1.B = Bri; g1.ldb = H; g1.b_kcontig = 1;
+    g1.A = u; g1.lda = H; g1.w = packed(ws, lo.w_in); g1.planes = lo.planes;
     g1.C = reinterpret_cast<float *>(xs); g1.ldc = 2 * P;
-    g1.M = T; g1.N = (int)(2 * P); g1.K = (int)H; g1.splits = 1;
+    g1.M = T; g1.N = (int)(2 * P); g1.K = (int)H;
+    if (two_planes) g1.amaxA = AbsMax{nullptr, 0, rowmax, 1, T};
     if (fused) {
         g1.epilogue = 7;
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
-        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.spin_limit = spin_limit();
-        if (two_planes) {
-            g1.amaxA = AbsMax{nullptr, 0, rowmax, 1, T}; g1.amaxB = AbsMax{am_bbar, (int)P, nullptr, 0, 0};
-            g1.scan.rowmax_out = rowpart;                    // of the states, for the output projection
-        }
-    } else if (two_planes) {
-        g1.amaxA = AbsMax{nullptr, 0, rowmax, 1, T}; g1.amaxB = AbsMax{am_bbar, (int)P, nullptr, 0, 0};
+        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = gemm_scan_rows(T, P); g1.scan.spin_limit = spin_limit();
+        g1.scan.rowmax_out = rowpart;                        // of the states, for the output projection
     }
-    HIP_TRY(launch_gemm(g1, s));
+    HIP_TRY(launch_product(g1, s));
     MARK();
 
     if (!fused) {
@@ -354,15 +364,13 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
 
     // y[t,h] = sum_p (Re C[h,p] x_re - Im C[h,p] x_im) + D[h] u[t,h]       (Eq. 3, second line)
     GemmArgs g2{};
-    g2.A = reinterpret_cast<const float *>(xs); g2.lda = 2 * P; g2.a_kcontig = 1;
-    g2.B = Cc; g2.ldb = 2 * P; g2.b_kcontig = 1;
+    g2.A = reinterpret_cast<const float *>(xs); g2.lda = 2 * P; g2.w = packed(ws, lo.w_out); g2.planes = lo.planes;
     g2.M = T; g2.N = (int)H; g2.K = (int)(2 * P);
-    if (two_planes) { g2.amaxA = AbsMax{nullptr, 0, rowpart, lo.row_parts, T}; g2.amaxB = AbsMax{am_cc, (int)H, nullptr, 0, 0}; }
+    if (two_planes) g2.amaxA = AbsMax{nullptr, 0, rowpart, lo.row_parts, T};
     g2.C = y; g2.ldc = H; g2.diag = D; g2.E = u; g2.lde = H; g2.epilogue = 1;
     if (gelu_y) { g2.epilogue = 6; g2.C2 = gelu_y; }       // the S5 block: GELU(y) for the gate, same store
-    if (gelu_y && gate_max) g2.c2_rowmax = gate_max->x1_rowmax;
-    g2.splits = 1;
-    HIP_TRY(launch_gemm(g2, s));
+    if (gelu_y && gate) g2.c2_rowmax = gate->x1_rowmax;
+    HIP_TRY(launch_product(g2, s));
     MARK();
     return SSM_OK;
 }
@@ -389,8 +397,6 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     char *ws = static_cast<char *>(workspace);
     WsHeader *hdr = reinterpret_cast<WsHeader *>(ws + lo.hdr);
     float2 *lam = reinterpret_cast<float2 *>(ws + lo.lam);
-    float *Bri = reinterpret_cast<float *>(ws + lo.Bri);
-    float *Cc = reinterpret_cast<float *>(ws + lo.Cc);
     ScanDesc *desc = reinterpret_cast<ScanDesc *>(ws + lo.desc);
     float2 *chi = reinterpret_cast<float2 *>(ws + lo.chi);
     float *dCpart = reinterpret_cast<float *>(ws + lo.dCpart);
@@ -400,57 +406,55 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     const int T = (int)(Bt * L);
     const float *xf = reinterpret_cast<const float *>(x);
 
-    // Shapes whose sequences are whole numbers of 128-row tiles: C^H dy runs the reverse scan on its
+    // Shapes whose sequences are whole numbers of 128-step pieces: C^H dy runs the reverse scan on its
     // own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
-    if (!fused && lo.plan.nTB > 1)
-        HIP_TRY(launch_clear(hdr, ws + lo.ticket, lo.desc + up(lo.plan.desc_bytes) - lo.ticket, s));
     PrepArgs pa{};
     pa.Lambda = reinterpret_cast<const float2 *>(Lambda); pa.B = reinterpret_cast<const float2 *>(B);
     pa.C = reinterpret_cast<const float2 *>(C); pa.log_delta = log_delta;
-    pa.P = (int)P; pa.H = (int)H; pa.lam_bar = lam; pa.Bbar_ri = Bri; pa.Cc = Cc; pa.Bbar_c64 = nullptr;
-    pa.hdr = (fused || lo.plan.nTB == 1) ? hdr : nullptr;
-    if (fused) { pa.zero16 = reinterpret_cast<uint4 *>(ws + lo.amax_atomic); pa.n16 = (2 * ABSMAX_SLOTS * 4 + lo.fdesc_bytes) / 16; }
-    if (lo.planes2_unfused) { pa.zero16 = reinterpret_cast<uint4 *>(ws + lo.amax_atomic); pa.n16 = (2 * ABSMAX_SLOTS * 4 + up((size_t)T * 4)) / 16; }
+    pa.P = (int)P; pa.H = (int)H; pa.lam_bar = lam; pa.hdr = hdr;
+    pa.pack[0] = pack_job(ws, lo.w_du, PACK_DU, lo.planes);
+    pa.pack[1] = pack_job(ws, lo.w_gx, PACK_GX, lo.planes);
+    pa.npack = 2;
+    zero_ranges(pa, lo, ws, fused, (size_t)T);
     // dD slabs: sum_t dy[t,h] u[t,h] over row slabs, in the same launch
     pa.cd.a = dy; pa.cd.b = u; pa.cd.T = T; pa.cd.H = (int)H; pa.cd.nslab = lo.nslab; pa.cd.partial = dDpart;
     // two scaled fp16 planes per operand: dy and u are measured where dD reads them, chi and the saved
     // states where the reverse scan stores / reads them
-    const bool two_planes = fused || lo.planes2_unfused;
+    const bool two_planes = lo.planes == 2;
     const bool x_pass = lo.dc_early || lo.planes2_unfused;       // the largest magnitude of the saved states from a pass of the prep launch
     unsigned *am_atomic = reinterpret_cast<unsigned *>(ws + lo.amax_atomic), *am_xsaved = am_atomic + ABSMAX_SLOTS;
-    unsigned *am_bbar = reinterpret_cast<unsigned *>(ws + lo.amax_slots), *am_cc = am_bbar + P, *am_pass = am_cc + H;
-    unsigned *am_dy = am_pass + 2 * PREP_PASS_BLOCKS, *am_u = am_dy + lo.amax_cd;
+    unsigned *am_pass = reinterpret_cast<unsigned *>(ws + lo.amax_slots);
+    unsigned *am_dy = am_pass + PREP_PASS_BLOCKS, *am_u = am_dy + lo.amax_cd;
     unsigned *rowmax = reinterpret_cast<unsigned *>(ws + lo.rowmax), *rowpart = reinterpret_cast<unsigned *>(ws + lo.rowpart);
     const int x_pieces = pass_pieces((size_t)T * 2 * P);
     if (two_planes) {
-        pa.bbar_max = am_bbar; pa.cc_max = am_cc; pa.cd_amax = am_dy; pa.cd_bmax = am_u;
+        pa.cd_amax = am_dy; pa.cd_bmax = am_u;
         pa.cd_arow = rowmax;                 // [ceil(H/64)][T]: rows of dy, measured where the dD column dots read it
-        if (x_pass) { pa.pass[0].x = xf; pa.pass[0].n = (size_t)T * 2 * P; pa.pass[0].slots = am_pass; pa.pass[0].nblocks = x_pieces; }
+        if (x_pass) { pa.pass.x = xf; pa.pass.n = (size_t)T * 2 * P; pa.pass.slots = am_pass; pa.pass.nblocks = x_pieces; }
     }
     // dy and chi enter C^H dy and Bbar^H chi with tokens as rows (a scale per token); the sums over tokens
     // (dC, dBbar) take one scale per matrix
     const AbsMax mx_dy{am_dy, lo.amax_cd, nullptr, 0, 0}, mx_u{am_u, lo.amax_cd, nullptr, 0, 0},
                  mx_x{x_pass ? am_pass : am_xsaved, x_pass ? x_pieces : ABSMAX_SLOTS, nullptr, 0, 0},
                  mx_chi{am_atomic, ABSMAX_SLOTS, nullptr, 0, 0},
-                 mx_bbar{am_bbar, (int)P, nullptr, 0, 0}, mx_cc{am_cc, (int)H, nullptr, 0, 0},
                  mx_dy_rows{nullptr, 0, rowmax, (int)((H + 63) / 64), T}, mx_chi_rows{nullptr, 0, rowpart, lo.row_parts, T};
     HIP_TRY(launch_prep(pa, s));
     MARK();
 
     // gx[t, 2p+c] = sum_h dy[t,h] * Cc[h, 2p+c]           (C^H dy_t)
     GemmArgs g3{};
-    g3.A = dy; g3.lda = H; g3.a_kcontig = 1;
-    g3.B = Cc; g3.ldb = 2 * P; g3.b_kcontig = 0;
+    g3.A = dy; g3.lda = H; g3.w = packed(ws, lo.w_gx); g3.planes = lo.planes;
     g3.C = reinterpret_cast<float *>(chi); g3.ldc = 2 * P;
-    g3.M = T; g3.N = (int)(2 * P); g3.K = (int)H; g3.splits = 1;
+    g3.M = T; g3.N = (int)(2 * P); g3.K = (int)H;
     // dC slabs: [h, 2p+c] = sum_t dy[t,h] * x[t, 2p+c]
     GemmArgs g4{};
-    g4.A = dy; g4.lda = H; g4.a_kcontig = 0;
-    g4.B = xf; g4.ldb = 2 * P; g4.b_kcontig = 0;
+    g4.A = dy; g4.lda = H;
+    g4.B = xf; g4.ldb = 2 * P;
     g4.C = dCpart; g4.ldc = 2 * P;
     g4.M = (int)H; g4.N = (int)(2 * P); g4.K = T; g4.splits = lo.splitC;
+    if (two_planes) { g3.amaxA = mx_dy_rows; g4.amaxA = mx_dy; g4.amaxB = mx_x; }
     if (fused) {
         // the product scans its own tiles; the dC slabs wait for the next launch, where the largest
         // magnitude of the saved states (recorded here, as the scan reads them) is known
@@ -460,15 +464,12 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
-        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.spin_limit = spin_limit();
-        g3.amaxA = mx_dy_rows; g3.amaxB = mx_cc;
+        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = gemm_scan_rows(T, P); g3.scan.spin_limit = spin_limit();
         g3.scan.amax_out = am_atomic; g3.scan.xmax_out = lo.dc_early ? nullptr : am_xsaved; g3.scan.rowmax_out = rowpart;
-        if (lo.dc_early) { g4.amaxA = mx_dy; g4.amaxB = mx_x; HIP_TRY(launch_gemm_pair(g3, g4, s)); }
-        else HIP_TRY(launch_gemm(g3, s));
+        HIP_TRY(launch_products(g3, lo.dc_early ? &g4 : nullptr, nullptr, false, s));
     } else {
         // dC needs only dy and the saved states: it shares the launch (whichever kind of work item the schedule model puts first)
-        if (two_planes) { g3.amaxA = mx_dy_rows; g3.amaxB = mx_cc; g4.amaxA = mx_dy; g4.amaxB = mx_x; }
-        HIP_TRY(launch_gemm_pair(g3, g4, s, lo.dc_first));
+        HIP_TRY(launch_products(g3, &g4, nullptr, lo.dc_first, s));
     }
     MARK();
 
@@ -488,45 +489,29 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     MARK();
 
     // du[t,h] = sum_{p,c} chi[t, 2p+c] * Bbar_ri[2p+c, h] + D[h] dy[t,h]      (Re(Bbar^H chi) + D dy)
-    const float *du_halves = nullptr;
     GemmArgs g5{};
-    g5.A = reinterpret_cast<const float *>(chi); g5.lda = 2 * P; g5.a_kcontig = 1;
-    g5.B = Bri; g5.ldb = H; g5.b_kcontig = 0;
+    g5.A = reinterpret_cast<const float *>(chi); g5.lda = 2 * P; g5.w = packed(ws, lo.w_du); g5.planes = lo.planes;
+    g5.C = du; g5.ldc = H; g5.diag = D; g5.E = dy; g5.lde = H; g5.epilogue = 1;
     g5.M = T; g5.N = (int)H; g5.K = (int)(2 * P);
     // dBbar slabs: [2p+c, h] = sum_t chi[t, 2p+c] * u[t,h]   (same launch)
     GemmArgs g6{};
-    g6.A = reinterpret_cast<const float *>(chi); g6.lda = 2 * P; g6.a_kcontig = 0;
-    g6.B = u; g6.ldb = H; g6.b_kcontig = 0;
+    g6.A = reinterpret_cast<const float *>(chi); g6.lda = 2 * P;
+    g6.B = u; g6.ldb = H;
     g6.C = dBpart; g6.ldc = H;
     g6.M = (int)(2 * P); g6.N = (int)H; g6.K = T; g6.splits = lo.splitB;
-    if (two_planes) { g4.amaxA = mx_dy; g4.amaxB = mx_x; g5.amaxA = mx_chi_rows; g5.amaxB = mx_bbar; g6.amaxA = mx_chi; g6.amaxB = mx_u; }
-    if (lo.yhalves) {
-        // du has too few 128x128 tiles for half a chip's worth of time: it runs as two K halves (twice
-        // the workgroups, half as long); a streaming pass adds the halves and D dy
-        float *halves = reinterpret_cast<float *>(ws + lo.yhalves);
-        g5.C = halves; g5.ldc = H; g5.splits = 2;
-        du_halves = halves;                  // added by extra workgroups of the parameter epilogue's launch
-    } else {
-        g5.C = du; g5.ldc = H; g5.diag = D; g5.E = dy; g5.lde = H; g5.epilogue = 1; g5.splits = 1;
-    }
-    if (fused && !lo.dc_early) HIP_TRY(launch_gemm_triple(g5, g6, g4, s, lo.slabs_first));   // three products, two workgroups per CU
-    else {
-        // (the slabs first when du runs as two K halves, or where the schedule model says so)
-        HIP_TRY(launch_gemm_pair(g5, g6, s, lo.yhalves != 0 || (!fused && lo.db_first)));
-    }
+    if (two_planes) { g5.amaxA = mx_chi_rows; g6.amaxA = mx_chi; g6.amaxB = mx_u; }
+    // three products in one launch where the dC slabs had to wait for the largest magnitude of the saved states
+    if (fused && !lo.dc_early) HIP_TRY(launch_products(g5, &g6, &g4, lo.slabs_first, s));
+    else HIP_TRY(launch_products(g5, &g6, nullptr, !fused && lo.db_first, s));
     MARK();
     MARK();
 
     EpilogueArgs ea{};
-    if (du_halves) {
-        ea.sum.s0 = du_halves; ea.sum.s1 = du_halves + (size_t)T * H; ea.sum.D = D; ea.sum.e = dy; ea.sum.out = du;
-        ea.sum.n = (long)T * H; ea.sum.H = (int)H;
-    }
     ea.Lambda = reinterpret_cast<const float2 *>(Lambda); ea.B = reinterpret_cast<const float2 *>(B);
     ea.log_delta = log_delta; ea.P = (int)P; ea.H = (int)H;
     ea.dBbar_part = dBpart; ea.nsplit_B = lo.splitB;
     ea.dC_part = dCpart; ea.nsplit_C = lo.splitC;
-    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / 128 : (int64_t)Bt * lo.plan.nTB;
+    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, P) : (int64_t)Bt * lo.plan.nTB;
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
     ea.dC = reinterpret_cast<float2 *>(dC); ea.dD = dD; ea.dlog_delta = dlog_delta;
@@ -576,13 +561,8 @@ ssm_status ssm_discretize(const ssm_c64 *Lambda, const ssm_c64 *B, const float *
     if (misaligned(Lambda, 8) || misaligned(B, 8) || misaligned(log_delta, 4) || misaligned(A_bar, 8) ||
         misaligned(B_bar, 8))
         return SSM_ERR_INVALID_ARG;
-    PrepArgs pa{};
-    pa.Lambda = reinterpret_cast<const float2 *>(Lambda);
-    pa.B = B_bar ? reinterpret_cast<const float2 *>(B) : nullptr;
-    pa.log_delta = log_delta; pa.P = (int)P; pa.H = (int)H;
-    pa.lam_bar = reinterpret_cast<float2 *>(A_bar);
-    pa.Bbar_c64 = reinterpret_cast<float2 *>(B_bar);
-    HIP_TRY(launch_prep(pa, static_cast<hipStream_t>(stream)));
+    HIP_TRY(launch_discretize(reinterpret_cast<const float2 *>(Lambda), reinterpret_cast<const float2 *>(B), log_delta, (int)P, (int)H,
+                              reinterpret_cast<float2 *>(A_bar), reinterpret_cast<float2 *>(B_bar), static_cast<hipStream_t>(stream)));
     return SSM_OK;
 }
 
@@ -650,13 +630,13 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     const int64_t T = Bt * L;
     out[0] = fused ? 1 : 0;
-    out[1] = (fused || lo.planes2_unfused) ? 2 : 3;
+    out[1] = lo.planes;
     out[2] = lo.splitC; out[3] = lo.splitB;
     out[4] = (fused && !lo.dc_early) ? 3 : 2;
     out[5] = lo.slabs_first ? 1 : 0;
     out[6] = (!fused && lo.dc_first) ? 1 : 0;
-    out[7] = (lo.yhalves != 0 || (!fused && lo.db_first)) ? 1 : 0;
-    out[8] = lo.yhalves != 0 ? 1 : 0;
+    out[7] = (!fused && lo.db_first) ? 1 : 0;
+    out[8] = 0;
     out[9] = fused ? 0 : gemm_tile_tier(T, 2 * P, 1);
     out[10] = gemm_tile_tier(T, H, 1);
     out[11] = lo.plan.nTB;
@@ -708,14 +688,17 @@ ssm_status ssm_scan_states_reverse(const ssm_c64 *A_bar, ssm_c64 *gx, const ssm_
 }
 
 namespace {
-struct StepPlan { size_t lam, Bri, Cc, total; };
+constexpr int STEP_PLANES = 3;
+struct StepPlan { size_t lam, total; PackedLayout in, out, gx, du; };
 bool make_step_plan(int64_t H, int64_t P, StepPlan &o)
 {
     if (H <= 0 || P <= 0 || H > SSM_MAX_WIDTH || P > SSM_MAX_WIDTH) return false;
     size_t off = 0;
     o.lam = off; off += up((size_t)P * 8);
-    o.Bri = off; off += up((size_t)2 * P * H * 4);
-    o.Cc = off; off += up((size_t)2 * P * H * 4);
+    add_packed(off, o.in, 2 * P, H, STEP_PLANES);
+    add_packed(off, o.out, H, 2 * P, STEP_PLANES);
+    add_packed(off, o.gx, 2 * P, H, STEP_PLANES);
+    add_packed(off, o.du, H, 2 * P, STEP_PLANES);
     o.total = off;
     return true;
 }
@@ -744,8 +727,11 @@ ssm_status ssm_step_prepare(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c
     pa.C = reinterpret_cast<const float2 *>(C); pa.log_delta = log_delta;
     pa.P = (int)P; pa.H = (int)H;
     pa.lam_bar = reinterpret_cast<float2 *>(pb + pl.lam);
-    pa.Bbar_ri = reinterpret_cast<float *>(pb + pl.Bri);
-    pa.Cc = reinterpret_cast<float *>(pb + pl.Cc);
+    pa.pack[0] = pack_job(pb, pl.du, PACK_DU, STEP_PLANES);
+    pa.pack[1] = pack_job(pb, pl.in, PACK_IN, STEP_PLANES);
+    pa.pack[2] = pack_job(pb, pl.out, PACK_OUT, STEP_PLANES);
+    pa.pack[3] = pack_job(pb, pl.gx, PACK_GX, STEP_PLANES);
+    pa.npack = 4;
     HIP_TRY(launch_prep(pa, static_cast<hipStream_t>(stream)));
     return SSM_OK;
 }
@@ -767,24 +753,22 @@ ssm_status ssm_step(const void *plan, size_t plan_bytes, const float *D, const f
     hipStream_t s = static_cast<hipStream_t>(stream);
     // x = Bbar u (+ Abar (.) x_prev where the sequence continues)          (Eq. 3, first line)
     GemmArgs g1{};
-    g1.A = u; g1.lda = H; g1.a_kcontig = 1;
-    g1.B = reinterpret_cast<const float *>(pb + pl.Bri); g1.ldb = H; g1.b_kcontig = 1;
+    g1.A = u; g1.lda = H; g1.w = packed(pb, pl.in); g1.planes = STEP_PLANES;
     g1.C = reinterpret_cast<float *>(x); g1.ldc = 2 * P;
-    g1.M = (int)Bt; g1.N = (int)(2 * P); g1.K = (int)H; g1.splits = 1;
+    g1.M = (int)Bt; g1.N = (int)(2 * P); g1.K = (int)H;
     if (x_prev) {
         g1.epilogue = 2;
         g1.diag = reinterpret_cast<const float *>(pb + pl.lam);
         g1.E = reinterpret_cast<const float *>(x_prev); g1.lde = 2 * P;
         g1.rowflag = is_first;
     }
-    HIP_TRY(launch_gemm(g1, s));
+    HIP_TRY(launch_product(g1, s));
     // y = Re(C x) + D (.) u                                                 (Eq. 3, second line)
     GemmArgs g2{};
-    g2.A = reinterpret_cast<const float *>(x); g2.lda = 2 * P; g2.a_kcontig = 1;
-    g2.B = reinterpret_cast<const float *>(pb + pl.Cc); g2.ldb = 2 * P; g2.b_kcontig = 1;
+    g2.A = reinterpret_cast<const float *>(x); g2.lda = 2 * P; g2.w = packed(pb, pl.out); g2.planes = STEP_PLANES;
     g2.C = y; g2.ldc = H; g2.diag = D; g2.E = u; g2.lde = H; g2.epilogue = 1;
-    g2.M = (int)Bt; g2.N = (int)H; g2.K = (int)(2 * P); g2.splits = 1;
-    HIP_TRY(launch_gemm(g2, s));
+    g2.M = (int)Bt; g2.N = (int)H; g2.K = (int)(2 * P);
+    HIP_TRY(launch_product(g2, s));
     return SSM_OK;
 }
 
@@ -805,30 +789,27 @@ ssm_status ssm_step_bwd(const void *plan, size_t plan_bytes, const float *D, con
     hipStream_t s = static_cast<hipStream_t>(stream);
     // gx = C^H dy + dx;  dx_prev = [not is_first] conj(Abar) (.) gx
     GemmArgs g1{};
-    g1.A = dy; g1.lda = H; g1.a_kcontig = 1;
-    g1.B = reinterpret_cast<const float *>(pb + pl.Cc); g1.ldb = 2 * P; g1.b_kcontig = 0;
+    g1.A = dy; g1.lda = H; g1.w = packed(pb, pl.gx); g1.planes = STEP_PLANES;
     g1.C = reinterpret_cast<float *>(gx); g1.ldc = 2 * P;
     g1.E = reinterpret_cast<const float *>(dx); g1.lde = 2 * P;
     g1.C2 = reinterpret_cast<float *>(dx_prev);
     g1.diag = reinterpret_cast<const float *>(pb + pl.lam); g1.rowflag = is_first; g1.epilogue = 5;
-    g1.M = (int)Bt; g1.N = (int)(2 * P); g1.K = (int)H; g1.splits = 1;
-    HIP_TRY(launch_gemm(g1, s));
+    g1.M = (int)Bt; g1.N = (int)(2 * P); g1.K = (int)H;
+    HIP_TRY(launch_product(g1, s));
     // du = Re(Bbar^H gx) + D (.) dy
     GemmArgs g2{};
-    g2.A = reinterpret_cast<const float *>(gx); g2.lda = 2 * P; g2.a_kcontig = 1;
-    g2.B = reinterpret_cast<const float *>(pb + pl.Bri); g2.ldb = H; g2.b_kcontig = 0;
+    g2.A = reinterpret_cast<const float *>(gx); g2.lda = 2 * P; g2.w = packed(pb, pl.du); g2.planes = STEP_PLANES;
     g2.C = du; g2.ldc = H; g2.diag = D; g2.E = dy; g2.lde = H; g2.epilogue = 1;
-    g2.M = (int)Bt; g2.N = (int)H; g2.K = (int)(2 * P); g2.splits = 1;
-    HIP_TRY(launch_gemm(g2, s));
+    g2.M = (int)Bt; g2.N = (int)H; g2.K = (int)(2 * P);
+    HIP_TRY(launch_product(g2, s));
     return SSM_OK;
 }
 
 namespace {
 struct BlockLayout {
     size_t ssm, x1, glu, dypre, total;
-    // forward: the gate's product on two scaled fp16 planes (width a multiple of 64 and an output projection
-    // whose wavefronts own 64 columns): rows of GELU(y) in pieces of 64 columns, pieces of W
-    bool gate_two_planes; size_t x1_rowmax, wslots; int nwslots;
+    // forward: the gate's W in fragment order; with two planes the rows of GELU(y) in pieces of 128 columns
+    int gate_planes, row_parts; PackedLayout w; size_t x1_rowmax;
 };
 bool make_block_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, BlockLayout &o)
 {
@@ -838,15 +819,11 @@ bool make_block_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, Bl
     size_t off = 0;
     o.ssm = off; off += up(lo.total);
     o.x1 = o.glu = o.dypre = 0;
-    o.gate_two_planes = false; o.x1_rowmax = o.wslots = 0; o.nwslots = 0;
+    o.gate_planes = gate_two_planes_shape(Bt * L, H) ? 2 : 3; o.row_parts = (int)((H + 127) / 128); o.x1_rowmax = 0;
     if (!bwd) {
         o.x1 = off; off += TH;
-        o.gate_two_planes = gate_two_planes_shape(Bt * L, H) && gemm_tile_tier(Bt * L, H, 1) <= 1;
-        if (o.gate_two_planes) {
-            o.nwslots = pass_pieces((size_t)H * H);
-            o.x1_rowmax = off; off += up((size_t)(H / 64) * Bt * L * 4);
-            o.wslots = off; off += up((size_t)o.nwslots * 4);
-        }
+        add_packed(off, o.w, H, H, o.gate_planes);
+        if (o.gate_planes == 2) { o.x1_rowmax = off; off += up((size_t)o.row_parts * Bt * L * 4); }
     } else {
         const size_t g = ssm_half_glu_workspace_bytes(Bt * L, H, 1);
         if (g == 0) return false;
@@ -881,21 +858,17 @@ ssm_status ssm_block_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 
     hipStream_t s = static_cast<hipStream_t>(stream);
     float *x1 = reinterpret_cast<float *>(ws + bl.x1);
     // the layer; its output projection also stores x1 = GELU(y)
-    GateMax gm{reinterpret_cast<unsigned *>(ws + bl.x1_rowmax), W, (size_t)H * H, reinterpret_cast<unsigned *>(ws + bl.wslots), bl.nwslots};
+    GatePrep gp{bl.gate_planes == 2 ? reinterpret_cast<unsigned *>(ws + bl.x1_rowmax) : nullptr, W, pack_job(ws, bl.w, PACK_WN, bl.gate_planes)};
     st = run_fwd(Lambda, B, C, D, log_delta, u, is_first, x0, Bt, L, H, P, y, x, x_last, ws + bl.ssm, bl.x1 - bl.ssm, s,
-                 nullptr, x1, bl.gate_two_planes ? &gm : nullptr);
+                 nullptr, x1, &gp);
     if (st != SSM_OK) return st;
     // out[t, j] = y[t, j] sigmoid(sum_i x1[t, i] W[i, j])
     GemmArgs g{};
-    g.A = x1; g.lda = H; g.a_kcontig = 1;
-    g.B = W; g.ldb = H; g.b_kcontig = 0;
+    g.A = x1; g.lda = H; g.w = packed(ws, bl.w); g.planes = bl.gate_planes;
     g.C = out; g.ldc = H; g.E = y; g.lde = H; g.C2 = gate; g.epilogue = 3;
-    g.M = (int)(Bt * L); g.N = (int)H; g.K = (int)H; g.splits = 1;
-    if (bl.gate_two_planes) {
-        g.amaxA = AbsMax{nullptr, 0, gm.x1_rowmax, (int)(H / 64), (long)(Bt * L)};
-        g.amaxB = AbsMax{gm.wslots, gm.nwslots, nullptr, 0, 0};
-    }
-    HIP_TRY(launch_gemm(g, s));
+    g.M = (int)(Bt * L); g.N = (int)H; g.K = (int)H;
+    if (bl.gate_planes == 2) g.amaxA = AbsMax{nullptr, 0, gp.x1_rowmax, bl.row_parts, (long)(Bt * L)};
+    HIP_TRY(launch_product(g, s));
     return SSM_OK;
 }
 

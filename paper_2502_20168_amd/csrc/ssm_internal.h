@@ -9,24 +9,20 @@
 namespace ssm {
 
 // ---------------------------------------------------------------------------------------------
-// Projection GEMM:  C[m,n] = sum_k A(m,k) * B(n,k)  (+ epilogue term)
-// epilogue 0: none; 1: + diag[n] * E[m,n]; 2: + [not rowflag[m]] * (Abar (.) E)[m,n] with diag = Abar
-// as interleaved complex and the columns of C and E interleaved (re, im) pairs (one recurrence step);
-// 3: C = E (.) sigmoid(product), sigmoid kept in C2 when non-null (half-GLU gate);
-// 4: C = E + product (.) E2 (adjoint of the gate with respect to its input: E = dy (.) s, E2 = GELU'(u));
-// 6: as 1, and C2 = GELU(C) (output projection that feeds the half-GLU gate);
-// 7: the resettable scan over the rows of the output tile (see ScanEpilogue): C = states;
-// 8: the reverse-time scan of the gradient pass over the rows of the output tile: C = chi;
-// 5: C = product + E (E may be null), C2 = [not rowflag[m]] conj(Abar) (.) C with diag = Abar and complex
-//    (re, im) column pairs (adjoint of one recurrence step)
-// A(m,k) = a_kcontig ? A[m*lda + k] : A[k*lda + m];  B(n,k) = b_kcontig ? B[n*ldb + k] : B[k*ldb + n]
-// splits > 1: split z covers a contiguous K range and writes its own slab C + z*M*ldc
-// (no epilogue term in that case); the caller reduces the slabs.
+// Projection products.  Two kinds:
+//   a product of activations with packed weights, C[m,n] = f(sum_k A[m,k] W(n,k))  (gemm_packed.h).  f:
+//     epilogue 0: none; 1: + diag[n] * E[m,n]; 2: + [not rowflag[m]] * (Abar (.) E)[m,n] with diag = Abar as
+//     interleaved complex and the columns of C and E interleaved (re, im) pairs (one recurrence step);
+//     3: C = E (.) sigmoid(product), sigmoid kept in C2 when non-null (half-GLU gate);
+//     4: C = E + product (.) E2 (adjoint of the gate with respect to its input: E = dy (.) s, E2 = GELU'(u));
+//     5: C = product + E (E may be null), C2 = [not rowflag[m]] conj(Abar) (.) C with diag = Abar and complex
+//        (re, im) column pairs (adjoint of one recurrence step);
+//     6: as 1, and C2 = GELU(C) (output projection that feeds the half-GLU gate);
+//     7: the resettable scan over the rows of the output tile (see ScanEpilogue): C = states;
+//     8: the reverse-time scan of the gradient pass over the rows of the output tile: C = chi;
+//   a reduction over tokens, C[m,n] = sum_k A[k,m] B[k,n]  (gemm_kernel.h).  splits > 1: split z covers a
+//     contiguous K range and writes its own slab C + z*M*ldc; the caller reduces the slabs.
 // ---------------------------------------------------------------------------------------------
-// Epilogue 7 of the projection GEMM: the resettable scan (Eq. 4 with the elements of Eq. 9 and the
-// operator of Eq. 10) over the rows of the output tile itself, so that the input projection stores
-// the states x directly and Bbar u never goes to memory.  Rows are tokens (Bt sequences of L steps,
-// L a multiple of the 128-row tile), columns (re, im) pairs of P states.
 // Largest magnitude of a matrix, kept as n bit patterns of non-negative floats whose maximum it is
 // (written by the kernel that produced the matrix, or by a pass over it), or, for a matrix whose
 // rows are tokens, per row: rows[j * row_stride + r], j < row_parts, are patterns whose maximum is the
@@ -39,66 +35,69 @@ struct AbsMax {
     const unsigned *rows; int row_parts; long row_stride;
 };
 
+// Epilogue 7 of a product with packed weights: the resettable scan (Eq. 4 with the elements of Eq. 9 and the
+// operator of Eq. 10) over the rows of the output tile itself, so that the input projection stores the states x
+// directly and Bbar u never goes to memory.  Rows are tokens (Bt sequences of L steps), columns (re, im) pairs of P
+// states.
+constexpr int SCAN_MAX_STEPS = 4096;         // longest sequence
 struct ScanEpilogue {
     const float2 *lam;            // [P] Abar
     const uint8_t *is_first;      // [Bt*L] or null
     const float2 *x0;             // [Bt, P] or null
     float2 *x_last;               // [Bt, P] or null (forward)
     const float2 *xsaved;         // [Bt, L, P] states of the forward pass (reverse, epilogue 8)
-    float2 *partial;              // [Bt * L/128, P] per-tile rows of dAbar (reverse)
+    float2 *partial;              // [Bt * L / rows, P] per-tile rows of dAbar (reverse)
     float2 *dx0;                  // [Bt, P] or null (reverse)
-    unsigned long long *desc;     // [M/128 * ceil(N/128) * 64][2] tagged aggregate words, zero on entry
+    unsigned long long *desc;     // [M / 64 * ceil(N/128) * 64][2] tagged aggregate words, zero on entry
     unsigned *err;                // set when a bounded wait gives up
     unsigned *amax_out;           // [ABSMAX_SLOTS] or null: atomic maximum of the magnitudes stored to C, zero on entry
     unsigned *xmax_out;           // [ABSMAX_SLOTS] or null (reverse, with amax_out): atomic maximum of the magnitudes of xsaved
     unsigned *rowmax_out;         // [ceil(N/128), M] or null: per column tile and row, the largest magnitude stored to C
     int L, P;
+    int rows;                     // tokens per tile: gemm_scan_rows
     unsigned spin_limit;
 };
 
+// Weights in fragment order, split into planes (see gemm_packed.h); exp: log2 of the scale of every row n (two planes).
+struct PackedW { const void *frag; const int *exp; };
+// bytes of the fragments of N x K weights
+inline size_t packed_frag_bytes(int64_t N, int64_t K, int planes) { return (size_t)((N + 31) / 32 * 32) * (size_t)((K + 63) / 64 * 64) * 2 * planes; }
+
 struct GemmArgs {
-    const float *A; int64_t lda; int a_kcontig;
-    const float *B; int64_t ldb; int b_kcontig;
+    const float *A; int64_t lda;
+    const float *B; int64_t ldb;                     // reductions
+    PackedW w; int planes;                           // products with packed weights: 2 or 3 planes per operand
     float *C; int64_t ldc;
     const float *diag; const float *E; int64_t lde;
     int epilogue; const uint8_t *rowflag;
-    const float *E2; float *C2;                      // epilogues 3 and 4 (gate), pitch lde / ldc
+    const float *E2; float *C2;                      // epilogues 3, 4, 6 (gate), pitch lde / ldc; 5
     int M, N, K, splits;
     ScanEpilogue scan;                               // epilogues 7 and 8
-    AbsMax amaxA, amaxB;                             // largest magnitudes of A and B when known
-    unsigned *c2_rowmax;                             // epilogue 6, tile tiers 0 and 1: [ceil(N/64)][M] words, the largest
-                                                     // magnitude of every row of C2 per piece of 64 columns; or null
+    AbsMax amaxA, amaxB;                             // largest magnitudes of A (products: of its rows) and B when known
+    unsigned *c2_rowmax;                             // epilogue 6: [ceil(N/128)][M] words, the largest magnitude of every
+                                                     // row of C2 per piece of 128 columns; or null
 };
 // The gate's products stage two scaled fp16 planes per operand (and the passes before them measure the
-// largest magnitudes) at widths that are multiples of 64 from 512 on, with enough tokens that a T x H
-// product runs on tiles whose wavefronts own 64 columns (measured on 4096 tokens: -13 % at H = 1024, even
-// at H = 512; +2 % at 1024 tokens, H = 256, where the passes cost more than the shorter K loops save)
+// largest magnitudes) at widths that are multiples of 64 from 512 on, with enough tokens (measured on 4096 tokens:
+// -13 % at H = 1024, even at H = 512; +2 % at 1024 tokens, H = 256, where the passes cost more than the shorter K
+// loops save)
 inline bool gate_two_planes_shape(int64_t T, int64_t H) { return H % 64 == 0 && H >= 512 && ((T + 63) / 64) * ((H + 127) / 128) >= 200; }
-// tile tier launch_gemm picks for an M x N product with `splits` K splits: 0 = 128x128x32 tiles, 1 = 64x128x32, 2 = 64x64x64
+// tile tier of an M x N product by rounds of workgroups (reported by ssm_plan_describe): 0 = 128x128x32 tiles, 1 = 64x128x32, 2 = 64x64x64
 int gemm_tile_tier(int64_t M, int64_t N, int splits);
 // the input projection (epilogue 7) and C^H dy (epilogue 8, the reverse scan of the gradient pass) scan
 // their own output tiles at this shape
 bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P);
+// tokens per scanning tile at such a shape: 64 or 128
+int gemm_scan_rows(int64_t T, int64_t P);
 // bytes of tagged words epilogues 7 and 8 need (zeroed before the launch)
 size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P);
-// a product is staged as two scaled fp16 planes per operand when both operands carry their largest magnitude
-bool gemm_use_two_planes(const GemmArgs &g);
-// argument checks of the scanning epilogues; layout code of a problem (-1: no instantiation)
-bool gemm_scan_args_ok(const GemmArgs &g);
-int gemm_layout_of(const GemmArgs &g);
-hipError_t launch_gemm(const GemmArgs &g, hipStream_t s);
-// the instantiations of the kernel for one problem per launch (tier 0: 128x128x32 tiles, 1: 64x128x32, 2: 64x64x64)
-hipError_t gemm_dispatch_two_planes(const GemmArgs &g, int tier, hipStream_t s);
-hipError_t gemm_dispatch_three_planes(const GemmArgs &g, int tier, hipStream_t s);
-// a T x H product with a K loop of 2P has 100-199 tiles of 128x128 and a K loop long enough to halve (du next to
-// the dBbar slabs at shapes with separate scan kernels runs as two K halves then)
-bool gemm_out_split_shape(int64_t T, int64_t H, int64_t P);
-// two independent problems in one launch (falls back to two launches for layouts without a
-// paired instantiation)
-hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t s, bool second_first = false);
-// three independent problems in one launch: a product over the state dimension and two K = T reductions
-// (slabs_first: b and c take the first slots of the launch, a the last)
-hipError_t launch_gemm_triple(const GemmArgs &a, const GemmArgs &b, const GemmArgs &c, hipStream_t s, bool slabs_first = false);
+// One launch: a product with packed weights and up to two reductions over tokens whose inputs are ready at the same
+// time (b, c: null when absent; c only with b).  tn_first: the reductions' work items take the first slots.
+hipError_t launch_products(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
+inline hipError_t launch_product(const GemmArgs &a, hipStream_t s) { return launch_products(a, nullptr, nullptr, false, s); }
+// the instantiations with two and three planes
+hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
+hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
 // number of K splits for a reduction over K rows with an M x N result that shares its launch
 // with a product of partner_tiles 128x128 tiles
 int gemm_pick_splits(int64_t M, int64_t N, int64_t K, int64_t partner_tiles);
@@ -109,10 +108,10 @@ int gemm_pick_splits(int64_t M, int64_t N, int64_t K, int64_t partner_tiles);
 int gemm_pick_splits_balanced(int64_t M, int64_t N, int64_t K, int64_t main_tiles, int64_t k_main, bool &red_first);
 int gemm_pick_splits_model(int64_t T, int64_t main_tiles, int64_t k_main, int64_t red_tiles, size_t split_bytes, bool two_per_cu,
                            bool &red_first);
-// a product over T tokens with N columns has so few tiles that it and the reduction in its launch run on
-// 64x64x64 tiles; the K splits of that reduction (partner_tiles64: the product's 64x64 tiles, k_main: its K)
+// a product over T tokens with N columns has so few tiles that the reduction in its launch runs on 64x64x64 tiles; the K
+// splits of that reduction (main_M x main_N, k_main: the product)
 bool gemm_small_pair(int64_t T, int64_t N);
-int gemm_pick_splits_small(int64_t M, int64_t N, int64_t K, int64_t partner_tiles64, int64_t k_main);
+int gemm_pick_splits_small(int64_t M, int64_t N, int64_t K, int64_t main_M, int64_t main_N, int64_t k_main);
 
 // ---------------------------------------------------------------------------------------------
 // Resettable scan over the sequence dimension (forward and reverse time).
@@ -185,42 +184,42 @@ struct ColDotArgs {          // partial[s][h] = sum over the rows of slab s of a
 };
 int coldot_slabs(int64_t T);
 
+// Weights of one product for the prep launch to split and put into fragment order (see gemm_packed.h):
+//   PACK_IN   n = 2p+c, k = h:  Bbar                     (input projection)
+//   PACK_OUT  n = h, k = 2p+c:  (Re C, -Im C)             (output projection)
+//   PACK_GX   n = 2p+c, k = h:  (Re C, -Im C) transposed  (C^H dy)
+//   PACK_DU   n = h, k = 2p+c:  Bbar transposed           (Re(Bbar^H chi))
+//   PACK_WN   n = j, k = i:     W[i, j]                   (gate)
+//   PACK_WT   n = i, k = j:     W[i, j]                   (adjoint of the gate)
+enum PackKind { PACK_IN, PACK_OUT, PACK_GX, PACK_DU, PACK_WN, PACK_WT };
+struct PackJob { int kind, N, K, planes; void *frag; int *exp; int block0, nblocks; };   // the last two set by the launch
+int pack_blocks(int kind, int N);            // workgroups of 256 threads that a job takes
+
+constexpr int PREP_MAX_PACKS = 4;
 struct PrepArgs {
-    const float2 *Lambda; const float2 *B; const float2 *C; const float *log_delta;
+    const float2 *Lambda; const float2 *B; const float2 *C; const float *log_delta; const float *W;
     int P, H;
-    float2 *lam_bar;         // [P]
-    float *Bbar_ri;          // [2P, H]: row 2p = Re(g_p B[p,:]), row 2p+1 = Im(g_p B[p,:]); may be null
-    float *Cc;               // [H, 2P]: (Re C[h,p], -Im C[h,p]) interleaved; may be null
-    float2 *Bbar_c64;        // [P, H] interleaved complex, for ssm_discretize; may be null
+    float2 *lam_bar;         // [P], written by the PACK_IN or the PACK_DU job
+    PackJob pack[PREP_MAX_PACKS]; int npack;
     WsHeader *hdr;           // cleared when non-null
     ColDotArgs cd;           // cd.partial non-null: the launch also computes the column-dot slabs
-    int cd_colblocks;        // set by launch_prep
-    uint4 *zero16; size_t n16;   // region to clear in the same launch (tagged words of epilogue 7), may be null
-    int zero_block0;         // set by launch_prep: first workgroup of the clearing range
+    int cd_block0, cd_colblocks;                 // set by launch_prep
+    struct Zero { uint4 *p; size_t n16; int block0, nblocks; } zero[2];   // regions to clear in the same launch (block ranges set by it)
     // largest magnitudes for the two-plane fp16 staging of the products (all may be null):
-    unsigned *bbar_max;      // [P]: of the rows 2p, 2p+1 of Bbar_ri
-    unsigned *cc_max;        // [H]: of row h of Cc
     unsigned *cd_amax, *cd_bmax;   // [cd.nslab * ceil(cd.H/64)]: of the pieces of cd.a and cd.b
     unsigned *cd_arow;       // [ceil(cd.H/64)][cd.T]: of every row of cd.a within a block of 64 columns
-    struct Pass { const float *x; size_t n; unsigned *slots; int nblocks, block0, vec, rowlen; } pass[2];
+    struct Pass { const float *x; size_t n; unsigned *slots; int nblocks, block0, vec, rowlen; } pass;
                              // rowlen == 0: slots[nblocks] of nblocks pieces of x[n]; rowlen > 0: slots[n / rowlen],
                              // one per row of rowlen values; block0 and vec set by launch_prep
 };
 constexpr int PREP_PASS_BLOCKS = 256;        // pieces of a pass that measures one maximum per piece
 constexpr int PREP_ROW_PASS_BLOCKS = 1024;   // workgroups of a pass that measures one maximum per row
 hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
-
-
-
-// out = s0 + s1 + D (.) e over n = rows * H elements: the two K halves of du and D dy, added by extra
-// workgroups of the parameter epilogue's launch (both only wait for the products before them)
-struct SumHalvesArgs {
-    const float *s0, *s1, *D, *e; float *out; long n; int H;
-    int vec, nblocks;                        // set by launch_epilogue
-};
+// ssm_discretize: Abar [P] and, when asked, Bbar [P, H] as interleaved complex
+hipError_t launch_discretize(const float2 *Lambda, const float2 *B, const float *log_delta, int P, int H, float2 *lam_bar, float2 *Bbar,
+                             hipStream_t s);
 
 struct EpilogueArgs {
-    SumHalvesArgs sum;                       // s0 == nullptr: nothing to add
     const float2 *Lambda; const float2 *B; const float *log_delta; int P, H;
     const float *dBbar_part; int nsplit_B;   // [nsplit_B][2P][H]
     const float *dC_part; int nsplit_C;      // [nsplit_C][H][2P]  (sum_t dy x_re, sum_t dy x_im)
