@@ -22,6 +22,8 @@
 #include "ssm_internal.h"
 #include "lookback.h"
 
+#include <type_traits>
+
 namespace ssm {
 
 // Abar^(16 * cy) for cy a power of two, in double so that the power itself adds no error
@@ -42,10 +44,11 @@ __device__ __forceinline__ unsigned group16_max(unsigned (&v)[16], int lane)
 #pragma unroll
     for (int bit = 0; bit < 4; ++bit) {
         const int n = 8 >> bit;
-        const bool up = (lane >> bit) & 1;
+        // (bitwise: a selection between array elements becomes one between their addresses, and the array goes to scratch)
+        const unsigned up = 0u - ((unsigned)(lane >> bit) & 1u);
 #pragma unroll
         for (int k = 0; k < n; ++k) {
-            const unsigned keep = up ? v[k + n] : v[k], send = up ? v[k] : v[k + n];
+            const unsigned x = (v[k] ^ v[k + n]) & up, keep = v[k] ^ x, send = v[k + n] ^ x;
             v[k] = max(keep, (unsigned)__shfl_xor((int)send, 1 << bit));
         }
     }
@@ -95,41 +98,40 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     const long rowbase = (long)b * L;
     // every thread of the workgroup owns E steps of a valid state: no guards needed
     const bool full = ((tb + 1) * a.cy * E <= L) && ((px + 1) * a.pxb <= a.P);
-    const long stride = REV ? -(long)a.P : (long)a.P;            // elements between consecutive logical steps
-    const long first = (rowbase + (REV ? (L - 1 - s0) : s0)) * a.P + p;   // element of logical step s0
+    const int stride = REV ? -a.P : a.P;                         // elements between consecutive logical steps
+    const int pc = min(p, a.P - 1), sc = min(s0, L - 1);         // a valid state and step for every thread
+    const long first = (rowbase + (REV ? (L - 1 - sc) : sc)) * a.P + pc;      // element of logical step s0
+    const bool ends = len > 0 && s0 + len == L;                  // the thread owns the last logical step
 
     float2 lam = active ? a.lam[p] : make_float2(0.f, 0.f);
     if (REV) lam.y = -lam.y;
 
-    // logical step s <-> time t: forward t = s, reverse t = L-1-s
+    // logical step s <-> time t: forward t = s, reverse t = L-1-s.
+    // Steps past the end of the sequence re-read the last valid one.  They (and lanes past P) are computed on and never
+    // stored: nothing follows them, so no state depends on them.  (Guards around every load and step made the launches with
+    // a ragged end wait for one step after the other: 4800 x 512, L = 200: 20.7 us forward, 23.4 reverse.)
     float2 val[E];
     float2 xp[REV ? E : 1];
-    if (full) {
+    {
         const float2 *src = a.in + first;
+        const int lim = max(len - 1, 0) * stride;
 #pragma unroll
-        for (int e = 0; e < E; ++e) val[e] = src[e * stride];
+        for (int e = 0; e < E; ++e) val[e] = src[full ? e * stride : (REV ? max(e * stride, lim) : min(e * stride, lim))];
         if constexpr (REV) {
-            // state before each step: x[t-1]; only the very last logical step can have t = 0
-            const float2 *xs = a.xsaved + first - a.P;
+            // state before each step: x[t-1]; only the very last logical step has t = 0
+            const int row = L - 2 - sc;                          // t - 1 of step s0
+            const float2 *xs = a.xsaved + (rowbase + max(row, 0)) * a.P + pc;
+            const int xlim = max(min(len - 1, row), 0) * stride;
+            float2 xfirst = make_float2(0.f, 0.f);
+            if (a.x0 && ends && active) xfirst = a.x0[(long)b * a.P + p];
 #pragma unroll
-            for (int e = 0; e < E - 1; ++e) xp[e] = xs[e * stride];
-            if (s0 + E < L) xp[E - 1] = xs[(E - 1) * stride];
-            else xp[E - 1] = a.x0 ? a.x0[(long)b * a.P + p] : make_float2(0.f, 0.f);
-        }
-    } else {
+            for (int e = 0; e < E; ++e) xp[e] = xs[full && e < E - 1 ? e * stride : max(e * stride, xlim)];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            val[e] = make_float2(0.f, 0.f);
-            if constexpr (REV) xp[e] = make_float2(0.f, 0.f);
-            if (e < len && active) {
-                const int s = s0 + e;
-                const int t = REV ? (L - 1 - s) : s;
-                val[e] = a.in[(rowbase + t) * a.P + p];
-                if constexpr (REV) {
-                    if (t > 0) xp[e] = a.xsaved[(rowbase + t - 1) * a.P + p];
-                    else if (a.x0) xp[e] = a.x0[(long)b * a.P + p];
+            for (int e = 0; e < E; ++e)
+                if (!full || e == E - 1) {
+                    const bool t0 = s0 + e == L - 1;
+                    xp[e] = make_float2(t0 ? xfirst.x : xp[e].x, t0 ? xfirst.y : xp[e].y);
                 }
-            }
         }
     }
 
@@ -138,8 +140,9 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     if (a.is_first && len > 0) {
         const int tlo = REV ? (L - s0 - len) : s0;             // lowest time index of the chunk
         const uint8_t *fp = a.is_first + rowbase + tlo;
-        if (len == E && (reinterpret_cast<uintptr_t>(fp) & 15) == 0) {
-            const uint4 w = *reinterpret_cast<const uint4 *>(fp);
+        if (len == E) {
+            typedef unsigned u32x4u __attribute__((ext_vector_type(4), aligned(1)));
+            const u32x4u w = *reinterpret_cast<const u32x4u *>(fp);
             const unsigned ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -147,12 +150,11 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
                 fmask |= f << (REV ? (E - 1 - j) : j);
             }
         } else {
+            unsigned f[E];
 #pragma unroll
-            for (int e = 0; e < E; ++e)
-                if (e < len) {
-                    const int t = REV ? (L - 1 - (s0 + e)) : (s0 + e);
-                    fmask |= (unsigned)(a.is_first[rowbase + t] != 0) << e;
-                }
+            for (int e = 0; e < E; ++e) f[e] = fp[REV ? max(len - 1 - e, 0) : min(e, len - 1)];
+#pragma unroll
+            for (int e = 0; e < E; ++e) fmask |= (unsigned)(f[e] != 0 && e < len) << e;
         }
     }
     // rmask bit e: the incoming state of logical step s0+e is dropped.
@@ -165,36 +167,26 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
         if (a.is_first && len > 0 && s0 > 0) rmask |= (unsigned)(a.is_first[rowbase + (L - s0)] != 0);
     }
     // wavefront-uniform: no flag anywhere in the steps of this wavefront -> plain recurrence
-    const bool plain = full && (__builtin_amdgcn_ballot_w64((rmask | mmask) != 0) == 0);
+    const bool plain = (__builtin_amdgcn_ballot_w64((rmask | mmask) != 0) == 0);
 
     // ---- level 1, first pass: aggregate of the thread's steps for zero incoming state
     float2 A = make_float2(1.f, 0.f), S = make_float2(0.f, 0.f);
     static_assert(E == 16, "Abar^E below is four squarings");
-    if (full) {
-        if (plain) {
+    if (plain) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) S = cfma(lam, S, val[e]);
-        } else {
-            // branch-free: a reset zeroes the multiplier of that step
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const bool r = (rmask >> e) & 1u;
-                const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
-                S = cfma(le, S, val[e]);
-            }
-        }
-        float2 l2 = cmul(lam, lam);
-        l2 = cmul(l2, l2); l2 = cmul(l2, l2); l2 = cmul(l2, l2);
-        A = (rmask & 0xffffu) ? make_float2(0.f, 0.f) : l2;
+        for (int e = 0; e < E; ++e) S = cfma(lam, S, val[e]);
     } else {
+        // branch-free: a reset zeroes the multiplier of that step
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if (e < len) {
-                if ((rmask >> e) & 1u) { S = val[e]; A = make_float2(0.f, 0.f); }
-                else { S = cfma(lam, S, val[e]); A = cmul(A, lam); }
-            }
+            const bool r = (rmask >> e) & 1u;
+            const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
+            S = cfma(le, S, val[e]);
         }
     }
+    float2 l2 = cmul(lam, lam);
+    l2 = cmul(l2, l2); l2 = cmul(l2, l2); l2 = cmul(l2, l2);
+    A = (rmask & 0xffffu) ? make_float2(0.f, 0.f) : l2;
     sA[tid] = A;
     sS[tid] = S;
     __syncthreads();
@@ -282,70 +274,36 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     float2 xs = cfma(Aex, sX[lane], Sex);
     float2 acc = make_float2(0.f, 0.f);
     unsigned rm[MAXOUT ? E : 1];                     // MAXOUT: magnitude of the value stored at step e
-    if constexpr (MAXOUT) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) rm[e] = 0u;
-    }
-    if (full) {
-        float2 *dst = a.out + first;
-        if (plain) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                xs = cfma(lam, xs, val[e]);
-                dst[e * stride] = xs;
-                if constexpr (MAXOUT) rm[e] = __float_as_uint(fmaxf(fabsf(xs.x), fabsf(xs.y)));
-                if constexpr (REV) {
-                    // conj(x_{t-1}) * chi_t
-                    acc.x = fmaf(xp[e].x, xs.x, fmaf(xp[e].y, xs.y, acc.x));
-                    acc.y = fmaf(xp[e].x, xs.y, fmaf(-xp[e].y, xs.x, acc.y));
-                }
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const bool r = (rmask >> e) & 1u;
-                const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
-                xs = cfma(le, xs, val[e]);
-                dst[e * stride] = xs;
-                if constexpr (MAXOUT) rm[e] = __float_as_uint(fmaxf(fabsf(xs.x), fabsf(xs.y)));
-                if constexpr (REV) {
-                    const bool m = (mmask >> e) & 1u;
-                    const float2 q = make_float2(m ? 0.f : xp[e].x, m ? 0.f : xp[e].y);
-                    acc.x = fmaf(q.x, xs.x, fmaf(q.y, xs.y, acc.x));
-                    acc.y = fmaf(q.x, xs.y, fmaf(-q.y, xs.x, acc.y));
-                }
-            }
-        }
-        if constexpr (REV) {
-            if (s0 + E == L && a.dx0)
-                a.dx0[(long)b * a.P + p] = ((mmask >> (E - 1)) & 1u) ? make_float2(0.f, 0.f) : cmul(lam, xs);
-        } else {
-            if (s0 + E == L && a.x_last) a.x_last[(long)b * a.P + p] = xs;
-        }
-    } else {
+    float2 xend = make_float2(0.f, 0.f);             // state of the last logical step
+    float2 *dst = a.out + first;
+    auto second_pass = [&](auto all_steps, auto no_resets) {
+        constexpr bool FULL = decltype(all_steps)::value, PLAIN = decltype(no_resets)::value;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if (e < len) {
-                const int s = s0 + e;
-                const int t = REV ? (L - 1 - s) : s;
-                xs = ((rmask >> e) & 1u) ? val[e] : cfma(lam, xs, val[e]);
-                if (active) {
-                    a.out[(rowbase + t) * a.P + p] = xs;
-                    if constexpr (MAXOUT) rm[e] = __float_as_uint(fmaxf(fabsf(xs.x), fabsf(xs.y)));
-                    if constexpr (REV) {
-                        if (!((mmask >> e) & 1u)) {
-                            // conj(x_{t-1}) * chi_t
-                            acc.x += xp[e].x * xs.x + xp[e].y * xs.y;
-                            acc.y += xp[e].x * xs.y - xp[e].y * xs.x;
-                        }
-                        if (t == 0 && a.dx0)
-                            a.dx0[(long)b * a.P + p] =
-                                ((mmask >> e) & 1u) ? make_float2(0.f, 0.f) : cmul(lam, xs);
-                    } else {
-                        if (t == L - 1 && a.x_last) a.x_last[(long)b * a.P + p] = xs;
-                    }
-                }
+            const bool r = !PLAIN && ((rmask >> e) & 1u), valid = FULL || (e < len && active);
+            const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
+            xs = cfma(le, xs, val[e]);
+            if (valid) dst[e * stride] = xs;
+            if constexpr (MAXOUT) rm[e] = valid ? __float_as_uint(fmaxf(fabsf(xs.x), fabsf(xs.y))) : 0u;
+            if constexpr (REV) {
+                // conj(x_{t-1}) * chi_t
+                const bool m = !valid || (!PLAIN && ((mmask >> e) & 1u));
+                const float2 q = make_float2(m ? 0.f : xp[e].x, m ? 0.f : xp[e].y);
+                acc.x = fmaf(q.x, xs.x, fmaf(q.y, xs.y, acc.x));
+                acc.y = fmaf(q.x, xs.y, fmaf(-q.y, xs.x, acc.y));
             }
+            if (!FULL || e == E - 1) { const bool end = s0 + e == L - 1; xend = make_float2(end ? xs.x : xend.x, end ? xs.y : xend.y); }
+        }
+    };
+    // (uniform per wavefront)
+    if (full && plain) second_pass(std::true_type{}, std::true_type{});
+    else if (full) second_pass(std::true_type{}, std::false_type{});
+    else second_pass(std::false_type{}, std::false_type{});
+    if (ends && active) {
+        if constexpr (REV) {
+            if (a.dx0) a.dx0[(long)b * a.P + p] = ((mmask >> (len - 1)) & 1u) ? make_float2(0.f, 0.f) : cmul(lam, xend);
+        } else {
+            if (a.x_last) a.x_last[(long)b * a.P + p] = xend;
         }
     }
 
