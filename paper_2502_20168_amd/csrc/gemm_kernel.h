@@ -283,24 +283,29 @@ constexpr int TN_STAGES = 2;
 // Wavefronts: eight of either kind beside small products, whose workgroups have a CU to themselves and wait for the split
 // of every K tile and for chains of dependent matrix instructions (two consumers share out the k steps of a 32 x 32 block
 // and add up their results).
-constexpr int tn_producers(int TB) { return TB == 128 ? 4 : 8; }
-constexpr int tn_consumers(int TB) { return TB == 128 ? 4 : 8; }
-constexpr int tn_bk(int TB) { return TB == 128 ? 32 : 64; }
-constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * 2 * NPL * tn_bk(TB) * TB * 2 + (NPL == 2 ? 16 : 0); }     // stages, two scales
+constexpr int tn_producers(int TB) { return TB == 64 ? 8 : 4; }
+constexpr int tn_consumers(int TB) { return TB == 64 ? 8 : 4; }
+// Tiles by name: 128 = 128 x 128, 96 = 128 x 64 (three planes: half the registers and three quarters of the LDS of a square
+// tile, so that two workgroups share a CU here too), 64 = 64 x 64.
+constexpr int tn_rows(int TB) { return TB == 64 ? 64 : 128; }
+constexpr int tn_cols(int TB) { return TB == 128 ? 128 : 64; }
+constexpr int tn_bk(int TB) { return TB == 64 ? 64 : 32; }
+constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * NPL * tn_bk(TB) * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }     // stages, two scales
 
 template <int TB, int NPL, int EDGE>
 __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, int m0, int n0, int z, int kbeg, int kend, int tid)
 {
-    constexpr int BK = tn_bk(TB), NS = TN_STAGES, NC = tn_consumers(TB), KG = NC / 4, NP = tn_producers(TB), PT = 64 * NP;
+    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), BK = tn_bk(TB), NS = TN_STAGES, NC = tn_consumers(TB), KG = NC / 4, NP = tn_producers(TB), PT = 64 * NP;
     // K tiles of global loads in flight per producer (128 x 128 tiles: 3, 4 and 6 measured 1-5 % slower)
-    constexpr int PF = TB == 128 ? 2 : 4;
-    using L = SplitLoader<TB, BK, PT, NPL>;
+    constexpr int PF = TB == 64 ? 4 : 2;
+    using LA = SplitLoader<TM, BK, PT, NPL>;
+    using LB = SplitLoader<TN, BK, PT, NPL>;
     static_assert(NPL == 2 || NPL == 3, "three bf16 planes or two scaled fp16 planes per operand");
-    constexpr int STAGE_A = NPL * L::PLANE, STAGE = 2 * STAGE_A;
+    constexpr int STAGE_A = NPL * LA::PLANE, STAGE = STAGE_A + NPL * LB::PLANE;
     // two-plane staging: log2 of the scales of A and B, written by the producers before the first barrier and read by
     // the consumers after the K loop
     int *opexp = reinterpret_cast<int *>(stages + NS * STAGE);
-    constexpr int WM = TB / 2, WN = TB / 2, MI = WM / 32, NI = WN / 32;
+    constexpr int WM = TM / 2, WN = TN / 2, MI = WM / 32, NI = WN / 32;
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nk = (kend - kbeg + BK - 1) / BK;   // (the range is not empty)
@@ -309,7 +314,8 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
         // ------------------------------------------------------------------ producers
         // PF register sets: while tile t is split and stored, the loads of tiles t+1 .. t+PF are in flight
         const int ptid = tid - 64 * NC;
-        L la[PF], lb[PF];
+        LA la[PF];
+        LB lb[PF];
         auto fetch = [&](int set, int t) {
             la[set].template load<EDGE>(g.A, g.lda, m0, g.M, kbeg + t * BK, kend, ptid);
             lb[set].template load<EDGE>(g.B, g.ldb, n0, g.N, kbeg + t * BK, kend, ptid);
@@ -386,11 +392,11 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) fa[set][i][s] = L::fragment(st + s * L::PLANE, wm * WM + i * 32, (kg * KS + ks) * 16, l);
+            for (int s = 0; s < NPL; ++s) fa[set][i][s] = LA::fragment(st + s * LA::PLANE, wm * WM + i * 32, (kg * KS + ks) * 16, l);
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) fb[set][j][s] = L::fragment(st + STAGE_A + s * L::PLANE, wn * WN + j * 32, (kg * KS + ks) * 16, l);
+            for (int s = 0; s < NPL; ++s) fb[set][j][s] = LB::fragment(st + STAGE_A + s * LB::PLANE, wn * WN + j * 32, (kg * KS + ks) * 16, l);
     };
     // the products of one accumulator keep their order (smallest first); the MI*NI accumulators alternate so that
     // consecutive matrix instructions are independent
@@ -465,7 +471,7 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_ldexpf(acc[i][j][r], -st);
     }
     float *Cz = g.C + (long)z * g.M * g.ldc;
-    const bool full = (m0 + TB <= g.M) && (n0 + TB <= g.N);      // no store of this tile needs a bounds check
+    const bool full = (m0 + TM <= g.M) && (n0 + TN <= g.N);      // no store of this tile needs a bounds check
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -496,17 +502,18 @@ __device__ __forceinline__ void gemm_tn_problem(const GemmDev &g, unsigned char 
     int z, tile;
     tn_place(g, x, q, z, tile);
     if (q >= g.nx || z >= g.splits || tile >= g.ntm * g.ntn) return;
-    const int m0 = (tile / g.ntn) * TB, n0 = (tile % g.ntn) * TB;
+    constexpr int TM = tn_rows(TB), TN = tn_cols(TB);
+    const int m0 = (tile / g.ntn) * TM, n0 = (tile % g.ntn) * TN;
     const int kbeg = z * g.kper, kend = min(g.K, kbeg + g.kper);
     __bf16 *stages = reinterpret_cast<__bf16 *>(smem);
     if (kbeg >= kend) {
         // more splits than K tiles: a slab of zeros
         float *Cz = g.C + (long)z * g.M * g.ldc;
-        for (int i = tid; i < TB * TB; i += blockDim.x) {
-            const int row = m0 + i / TB, col = n0 + i % TB;
+        for (int i = tid; i < TM * TN; i += blockDim.x) {
+            const int row = m0 + i / TN, col = n0 + i % TN;
             if (row < g.M && col < g.N) Cz[(long)row * g.ldc + col] = 0.f;
         }
-    } else if (m0 + TB <= g.M && n0 + TB <= g.N) {
+    } else if (m0 + TM <= g.M && n0 + TN <= g.N) {
         gemm_tn_tile<TB, NPL, 0>(g, stages, m0, n0, z, kbeg, kend, tid);
     } else if (g.M >= 4 && g.N >= 4) {
         gemm_tn_tile<TB, NPL, 1>(g, stages, m0, n0, z, kbeg, kend, tid);
@@ -526,8 +533,8 @@ inline GemmDev make_tn_dev(const GemmArgs &a)
     int kper = (a.K + splits - 1) / splits;
     kper = (kper + BK - 1) / BK * BK;
     g.kper = kper;
-    g.ntm = (a.M + TB - 1) / TB;
-    g.ntn = (a.N + TB - 1) / TB;
+    g.ntm = (a.M + tn_rows(TB) - 1) / tn_rows(TB);
+    g.ntn = (a.N + tn_cols(TB) - 1) / tn_cols(TB);
     const long ntiles = (long)g.ntm * g.ntn;
     g.splits = splits;
     if (splits == 1) { g.mode = 0; g.mpar = 0; g.nx = (int)((ntiles + 7) / 8); }

@@ -22,7 +22,7 @@ hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const Gem
     }
 #define SSM_PAIR(epi) \
     case epi: \
-        if (!gemm_small_pair(a.M, a.N)) return SSM_PK(64, 128, epi, 128, 2); \
+        if (!gemm_small_pair(a.M, a.N)) return SSM_PK(64, 128, epi, 96, 4); \
         SSM_SMALL(epi, 64, 4); \
         return SSM_PK(64, 128, epi, 64, 4)
     switch (a.epilogue) {
