@@ -114,9 +114,14 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     float2 xp[REV ? E : 1];
     {
         const float2 *src = a.in + first;
-        const int lim = max(len - 1, 0) * stride;
+        if (full) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) val[e] = src[full ? e * stride : (REV ? max(e * stride, lim) : min(e * stride, lim))];
+            for (int e = 0; e < E; ++e) val[e] = src[e * stride];
+        } else {
+            const int lim = max(len - 1, 0) * stride;
+#pragma unroll
+            for (int e = 0; e < E; ++e) val[e] = src[REV ? max(e * stride, lim) : min(e * stride, lim)];
+        }
         if constexpr (REV) {
             // state before each step: x[t-1]; only the very last logical step has t = 0
             const int row = L - 2 - sc;                          // t - 1 of step s0
@@ -124,14 +129,20 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
             const int xlim = max(min(len - 1, row), 0) * stride;
             float2 xfirst = make_float2(0.f, 0.f);
             if (a.x0 && ends && active) xfirst = a.x0[(long)b * a.P + p];
+            if (full) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) xp[e] = xs[full && e < E - 1 ? e * stride : max(e * stride, xlim)];
+                for (int e = 0; e < E - 1; ++e) xp[e] = xs[e * stride];
+                xp[E - 1] = xs[max((E - 1) * stride, xlim)];
+                xp[E - 1] = make_float2(ends ? xfirst.x : xp[E - 1].x, ends ? xfirst.y : xp[E - 1].y);
+            } else {
 #pragma unroll
-            for (int e = 0; e < E; ++e)
-                if (!full || e == E - 1) {
+                for (int e = 0; e < E; ++e) xp[e] = xs[max(e * stride, xlim)];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
                     const bool t0 = s0 + e == L - 1;
                     xp[e] = make_float2(t0 ? xfirst.x : xp[e].x, t0 ? xfirst.y : xp[e].y);
                 }
+            }
         }
     }
 
@@ -230,6 +241,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
         const int j = sg0 + chunk;
         if (j < tb) {
             const ScanDesc *pred = mine - (size_t)(tb - j) * desc_stride;
+            const float2 power = pow_block(lam, a.cy);           // (before the wait, not behind it)
             unsigned tag = 0;
             if (!wait_pair(pred->agg, 1u, a.spin_limit, Sj, tag)) {
                 // gave up: flag it, hand on NaN (the states that depend on the missing aggregate become
@@ -238,7 +250,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
                 Sj = make_float2(__builtin_nanf(""), __builtin_nanf(""));
                 Aj = make_float2(0.f, 0.f);
             } else {
-                Aj = (tag == 2u) ? make_float2(0.f, 0.f) : pow_block(lam, a.cy);
+                Aj = make_float2(tag == 2u ? 0.f : power.x, tag == 2u ? 0.f : power.y);
             }
         }
         sA[tid] = Aj;
@@ -257,7 +269,21 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
         __syncthreads();
         if (lastchunk) {
             const int n = tb - sg0;
-            for (int c = 0; c < n; ++c) Xin = cfma(sA[c * a.pxb + lane], Xin, sS[c * a.pxb + lane]);
+            // (five aggregates are read at a time: one by one, every step of the chain waits for LDS)
+            for (int c0 = 0; c0 < n; c0 += 5) {
+                float2 Ac[5], Sc[5];
+#pragma unroll
+                for (int c = 0; c < 5; ++c) {
+                    const int i = min(c0 + c, n - 1) * a.pxb + lane;
+                    Ac[c] = sA[i]; Sc[c] = sS[i];
+                    asm volatile("" : "+v"(Ac[c].x), "+v"(Ac[c].y), "+v"(Sc[c].x), "+v"(Sc[c].y));
+                }
+#pragma unroll
+                for (int c = 0; c < 5; ++c) {
+                    const float2 nX = cfma(Ac[c], Xin, Sc[c]);
+                    Xin = make_float2(c0 + c < n ? nX.x : Xin.x, c0 + c < n ? nX.y : Xin.y);
+                }
+            }
         }
     }
     if (lastchunk) {
