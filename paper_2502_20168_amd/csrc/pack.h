@@ -232,8 +232,8 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
     };
     if (planes == 2) {
         for (int c0 = 0; c0 < nch; c0 += ROUND) {
-            discretize(c0 * 4 / PACK_ZOH_BATCH);
             fetch_round(c0);
+            discretize(c0 * 4 / PACK_ZOH_BATCH);
 #pragma unroll
             for (int t = 0; t < KEPT; ++t) {
                 float v[V][8];
@@ -244,8 +244,8 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
         reduce_max();
     }
     for (int c0 = 0; c0 < nch; c0 += ROUND) {
-        discretize(c0 * 4 / PACK_ZOH_BATCH);
         if (planes != 2 || !single) fetch_round(c0);
+        discretize(c0 * 4 / PACK_ZOH_BATCH);
 #pragma unroll
         for (int t = 0; t < KEPT; ++t) {
             const int c = c0 + t * ROWS + row;
