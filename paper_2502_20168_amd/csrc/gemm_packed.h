@@ -22,10 +22,11 @@
 #pragma once
 
 #include "gemm_kernel.h"
+#include "pk_units.h"
 
 namespace ssm {
 
-constexpr int PK_BN = 128, PK_BK = 64, PK_CONSUMERS = 4, PK_PRODUCERS = 4, PK_STAGES = 2;
+constexpr int PK_BN = 128, PK_CONSUMERS = 4, PK_PRODUCERS = 4, PK_STAGES = 2;
 constexpr int PK_THREADS = 64 * (PK_CONSUMERS + PK_PRODUCERS);
 
 // Place of an element of the output tile staged in LDS: rows of BN floats, pieces of 32 (rows, at 32 columns) swapped in rows
@@ -607,18 +608,17 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
         constexpr int RSTEP = PT / (BK / 4);
         static_assert(RSTEP % 16 == 0, "the swizzle of a thread's rows is one");
         // (a uniform base and a 32-bit offset per unit; rows past M: never stored)
-        const char *src = reinterpret_cast<const char *>(g.A + (long)m0 * g.lda);
+        const PkUnits units(g.K, g.lda);
+        const char *src = units.base(g.A + (long)m0 * g.lda, g.frag);
         unsigned row_at[NV];
 #pragma unroll
-        for (int i = 0; i < NV; ++i) row_at[i] = (unsigned)min(r0 + i * RSTEP, g.M - 1 - m0) * (4u * (unsigned)g.lda);
+        for (int i = 0; i < NV; ++i) row_at[i] = units.row(r0 + i * RSTEP, g.M - m0);
         float4 r[PF][NV];
-        // Nothing is read past a row: a unit that reaches over its end (the last K tile of a K that is no multiple of 64,
-        // and the requests behind the last tile) reads the row's last four values, and stash() puts them into
-        // place.  No branch around the loads: where paths with different numbers of loads in flight meet, the
-        // compiler waits for the larger one, which cost a whole K tile of prefetch distance.
-        const int klast = g.K >= 4 ? g.K - 4 : 0;
+        // Nothing is read past a row (see PkUnits); stash() puts the values of a unit that was read early into place.  No branch
+        // around the loads: where paths with different numbers of loads in flight meet, the compiler waits
+        // for the larger one, which cost a whole K tile of prefetch distance.
         auto fetch = [&](int set, int t) {
-            const unsigned k = 4u * (unsigned)min(t * BK + kq, klast);
+            const unsigned k = units.k(t, kq);
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 const f32x4u v = *reinterpret_cast<const f32x4u *>(src + (row_at[i] + k));
@@ -639,13 +639,14 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
                 for (int j = kq / 4 + 16; j < g.row_parts; j += 16) rw[i] = max(rw[i], w[(long)j * g.row_stride]);
             }
         }
-        const bool narrow = g.K < 4;
+        const bool narrow = units.narrow;
         if (narrow) {
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
+                const float *row = g.A + (long)(m0 + min(r0 + i * RSTEP, g.M - 1 - m0)) * g.lda;
                 float v[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = kq + j < g.K ? reinterpret_cast<const float *>(src + row_at[i])[kq + j] : 0.f;
+                for (int j = 0; j < 4; ++j) v[j] = kq + j < g.K ? row[kq + j] : 0.f;
                 r[0][i] = make_float4(v[0], v[1], v[2], v[3]);
             }
         } else {
@@ -668,7 +669,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
         const int ktail = (g.K % BK != 0 && !narrow) ? nk - 1 : nk;      // the K tile that hangs over
         auto stash = [&](int set, int t) {
             if (t == ktail) {
-                const int sh = t * BK + kq - klast;              // > 0: the unit was read sh values early; >= 4: it lies past the row
+                const int sh = t * BK + kq - units.klast;              // > 0: the unit was read sh values early; >= 4: it lies past the row
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
                     const float4 v = r[set][i];
