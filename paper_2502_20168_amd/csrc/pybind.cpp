@@ -124,12 +124,22 @@ PyObject *tuple(std::initializer_list<const at::Tensor *> items)
 }
 PyObject *item(PyObject *d, const char *key) { return d == Py_None ? nullptr : PyDict_GetItemString(d, key); }
 
+// The C call without the interpreter's lock.  Its arguments are values by then: taking a tensor's data pointer can throw (a
+// tensor without storage, for instance a batched one), and an exception must find the lock held.
+template <class... P, class... A>
+ssm_status call_without_gil(ssm_status (*entry)(P...), A... args)
+{
+    static_assert(sizeof...(P) == sizeof...(A) && (std::is_trivially_copyable_v<A> && ...), "pointers and numbers");
+    ssm_status rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = entry(args...);
+    Py_END_ALLOW_THREADS
+    return rc;
+}
+
 #define GENERAL_PATH_UNLESS(cond) do { if (!(cond)) Py_RETURN_NONE; } while (0)
-#define CALL(expr) \
-    ssm_status rc; \
-    Py_BEGIN_ALLOW_THREADS \
-    rc = (expr); \
-    Py_END_ALLOW_THREADS \
+#define CALL(...) \
+    const ssm_status rc = call_without_gil(__VA_ARGS__); \
     if (rc != SSM_OK) return PyLong_FromLong((long)rc)
 #define ENTRY(name) PyObject *name(PyObject *, PyObject *const *a, Py_ssize_t n)
 #define TRY_BEGIN try {
@@ -167,8 +177,8 @@ ENTRY(scan_fwd)
     at::Tensor x = output(item(a[12], "x"), yes(a[8]), {i.Bt, i.L, i.P}, C64, u, bad);
     at::Tensor xl = output(item(a[12], "x_last"), yes(a[9]), {i.Bt, i.P}, C64, u, bad);
     GENERAL_PATH_UNLESS(!bad);
-    CALL(ssm_scan_fwd(i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), i.u.f32(), i.is_first.u8(), i.x0.c64(),
-                      i.Bt, i.L, i.H, i.P, f32(y), c64(x), c64(xl), w.p, w.n, s));
+    CALL(ssm_scan_fwd, i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), i.u.f32(), i.is_first.u8(), i.x0.c64(),
+                      i.Bt, i.L, i.H, i.P, f32(y), c64(x), c64(xl), w.p, w.n, s);
     return dict({{"y", &y}, {"x", &x}, {"x_last", &xl}});
     TRY_END
 }
@@ -194,9 +204,9 @@ ENTRY(scan_bwd)
     at::Tensor dl = output(item(a[13], "dlog_delta"), true, {i.P}, F32, u, bad);
     at::Tensor dx0 = output(item(a[13], "dx0"), yes(a[10]), {i.Bt, i.P}, C64, u, bad);
     GENERAL_PATH_UNLESS(!bad);
-    CALL(ssm_scan_bwd(i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), i.u.f32(), i.is_first.u8(), i.x0.c64(),
+    CALL(ssm_scan_bwd, i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), i.u.f32(), i.is_first.u8(), i.x0.c64(),
                       i.Bt, i.L, i.H, i.P, x.c64(), dy.f32(), f32(du), c64(dL), c64(dB), c64(dC), f32(dD), f32(dl), c64(dx0),
-                      w.p, w.n, s));
+                      w.p, w.n, s);
     return dict({{"du", &du}, {"dLambda", &dL}, {"dB", &dB}, {"dC", &dC}, {"dD", &dD}, {"dlog_delta", &dl}, {"dx0", &dx0}});
     TRY_END
 }
@@ -216,8 +226,8 @@ ENTRY(block_fwd)
     at::Tensor y = empty({i.Bt, i.L, i.H}, F32, u), out = empty({i.Bt, i.L, i.H}, F32, u), gate;
     if (yes(a[9])) gate = empty({i.Bt, i.L, i.H}, F32, u);
     at::Tensor x = empty({i.Bt, i.L, i.P}, C64, u), xl = empty({i.Bt, i.P}, C64, u);
-    CALL(ssm_block_fwd(i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), W.f32(), i.u.f32(), i.is_first.u8(),
-                       i.x0.c64(), i.Bt, i.L, i.H, i.P, f32(y), f32(out), f32(gate), c64(x), c64(xl), w.p, w.n, s));
+    CALL(ssm_block_fwd, i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), W.f32(), i.u.f32(), i.is_first.u8(),
+                       i.x0.c64(), i.Bt, i.L, i.H, i.P, f32(y), f32(out), f32(gate), c64(x), c64(xl), w.p, w.n, s);
     return dict({{"y", &y}, {"out", &out}, {"gate", &gate}, {"x", &x}, {"x_last", &xl}});
     TRY_END
 }
@@ -238,9 +248,9 @@ ENTRY(block_bwd)
     at::Tensor du = empty({i.Bt, i.L, i.H}, F32, u), dL = empty({i.P}, C64, u), dB = empty({i.P, i.H}, C64, u),
                dC = empty({i.H, i.P}, C64, u), dD = empty({i.H}, F32, u), dl = empty({i.P}, F32, u), dx0 = empty({i.Bt, i.P}, C64, u),
                dW = empty({i.H, i.H}, F32, u);
-    CALL(ssm_block_bwd(i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), W.f32(), i.u.f32(), i.is_first.u8(),
+    CALL(ssm_block_bwd, i.Lambda.c64(), i.B.c64(), i.C.c64(), i.D.f32(), i.log_delta.f32(), W.f32(), i.u.f32(), i.is_first.u8(),
                        i.x0.c64(), i.Bt, i.L, i.H, i.P, x.c64(), y.f32(), gate.f32(), dout.f32(), f32(du), c64(dL), c64(dB), c64(dC),
-                       f32(dD), f32(dl), c64(dx0), f32(dW), w.p, w.n, s));
+                       f32(dD), f32(dl), c64(dx0), f32(dW), w.p, w.n, s);
     return dict({{"du", &du}, {"dLambda", &dL}, {"dB", &dB}, {"dC", &dC}, {"dD", &dD}, {"dlog_delta", &dl}, {"dx0", &dx0}, {"dW", &dW}});
     TRY_END
 }
@@ -258,7 +268,7 @@ ENTRY(step_prepare)
     const size_t bytes = ssm_step_plan_bytes(H, P);
     GENERAL_PATH_UNLESS(bytes > 0);
     at::Tensor plan = empty({(int64_t)bytes}, U8, *B.t);
-    CALL(ssm_step_prepare(Lambda.c64(), B.c64(), C.c64(), log_delta.f32(), H, P, plan.data_ptr(), bytes, s));
+    CALL(ssm_step_prepare, Lambda.c64(), B.c64(), C.c64(), log_delta.f32(), H, P, plan.data_ptr(), bytes, s);
     return wrap(plan);
     TRY_END
 }
@@ -283,7 +293,7 @@ ENTRY(step)
     }
     GENERAL_PATH_UNLESS(P > 0 && D.is(F32, {H}) && u.is(F32, {Bt, H}) && x_prev.is(C64, {Bt, P}, true) && first.is(U8, {Bt}, true));
     at::Tensor x = xo.t ? *xo.t : empty({Bt, P}, C64, *u.t), y = yo.t ? *yo.t : empty({Bt, H}, F32, *u.t);
-    CALL(ssm_step(plan.t->data_ptr(), (size_t)plan.t->numel(), D.f32(), u.f32(), x_prev.c64(), first.u8(), Bt, H, P, c64(x), f32(y), s));
+    CALL(ssm_step, plan.t->data_ptr(), (size_t)plan.t->numel(), D.f32(), u.f32(), x_prev.c64(), first.u8(), Bt, H, P, c64(x), f32(y), s);
     return tuple({&x, &y});
     TRY_END
 }
@@ -301,8 +311,8 @@ ENTRY(step_bwd)
     GENERAL_PATH_UNLESS(P > 0 && D.is(F32, {H}) && dy.is(F32, {Bt, H}) && dx.is(C64, {Bt, P}, true) && first.is(U8, {Bt}, true));
     at::Tensor gx = empty({Bt, P}, C64, *dy.t), du = empty({Bt, H}, F32, *dy.t), dp;
     if (yes(a[6])) dp = empty({Bt, P}, C64, *dy.t);
-    CALL(ssm_step_bwd(plan.t->data_ptr(), (size_t)plan.t->numel(), D.f32(), dy.f32(), dx.c64(), first.u8(), Bt, H, P, c64(gx), f32(du),
-                      c64(dp), s));
+    CALL(ssm_step_bwd, plan.t->data_ptr(), (size_t)plan.t->numel(), D.f32(), dy.f32(), dx.c64(), first.u8(), Bt, H, P, c64(gx), f32(du),
+                      c64(dp), s);
     return tuple({&gx, &du, &dp});
     TRY_END
 }
@@ -327,7 +337,7 @@ ENTRY(lambda_return)
     const int64_t T = r.size(0), N = r.size(1);
     GENERAL_PATH_UNLESS(r.is(F32, {T, N}) && c.is(F32, {T, N}) && v.is(F32, {T, N}) && o.is(F32, {T, N}, true));
     at::Tensor ret = o.t ? *o.t : empty({T, N}, F32, *r.t);
-    CALL(ssm_lambda_return(r.f32(), c.f32(), v.f32(), gamma, lam, T, N, f32(ret), s));
+    CALL(ssm_lambda_return, r.f32(), c.f32(), v.f32(), gamma, lam, T, N, f32(ret), s);
     return wrap(ret);
     TRY_END
 }
@@ -344,7 +354,7 @@ ENTRY(lambda_return_bwd)
     const int64_t T = c.size(0), N = c.size(1);
     GENERAL_PATH_UNLESS(c.is(F32, {T, N}) && v.is(F32, {T, N}) && r.is(F32, {T, N}) && d.is(F32, {T, N}));
     at::Tensor dr = empty({T, N}, F32, *c.t), dc = empty({T, N}, F32, *c.t), dv = empty({T, N}, F32, *c.t);
-    CALL(ssm_lambda_return_bwd(c.f32(), v.f32(), r.f32(), d.f32(), gamma, lam, T, N, f32(dr), f32(dc), f32(dv), s));
+    CALL(ssm_lambda_return_bwd, c.f32(), v.f32(), r.f32(), d.f32(), gamma, lam, T, N, f32(dr), f32(dc), f32(dv), s);
     return tuple({&dr, &dc, &dv});
     TRY_END
 }
@@ -363,7 +373,7 @@ ENTRY(scan_states)
     GENERAL_PATH_UNLESS(!w.bad);
     at::Tensor xl;
     if (yes(a[4])) xl = empty({Bt, P}, C64, *v.t);
-    CALL(ssm_scan_states(A.c64(), v.ptr<ssm_c64>(), first.u8(), x0.c64(), Bt, L, P, c64(xl), w.p, w.n, s));
+    CALL(ssm_scan_states, A.c64(), v.ptr<ssm_c64>(), first.u8(), x0.c64(), Bt, L, P, c64(xl), w.p, w.n, s);
     return tuple({&xl});
     TRY_END
 }
@@ -383,7 +393,7 @@ ENTRY(scan_states_reverse)
     GENERAL_PATH_UNLESS(!w.bad);
     at::Tensor dA = empty({P}, C64, *g.t), dx0;
     if (yes(a[5])) dx0 = empty({Bt, P}, C64, *g.t);
-    CALL(ssm_scan_states_reverse(A.c64(), g.ptr<ssm_c64>(), x.c64(), first.u8(), x0.c64(), Bt, L, P, c64(dA), c64(dx0), w.p, w.n, s));
+    CALL(ssm_scan_states_reverse, A.c64(), g.ptr<ssm_c64>(), x.c64(), first.u8(), x0.c64(), Bt, L, P, c64(dA), c64(dx0), w.p, w.n, s);
     return tuple({&dA, &dx0});
     TRY_END
 }
@@ -403,7 +413,7 @@ ENTRY(half_glu_fwd)
     at::Tensor y = yo.t ? *yo.t : empty({T, H}, F32, *u.t), gate;
     if (go.t) gate = *go.t;
     else if (yes(a[2])) gate = empty({T, H}, F32, *u.t);
-    CALL(ssm_half_glu_fwd(u.f32(), W.f32(), T, H, f32(y), f32(gate), w.p, w.n, s));
+    CALL(ssm_half_glu_fwd, u.f32(), W.f32(), T, H, f32(y), f32(gate), w.p, w.n, s);
     return tuple({&y, &gate});
     TRY_END
 }
@@ -422,7 +432,7 @@ ENTRY(half_glu_bwd)
     Workspace w(ws, ws.none ? ssm_half_glu_workspace_bytes(T, H, 1) : 0, *u.t);
     GENERAL_PATH_UNLESS(!w.bad);
     at::Tensor du = duo.t ? *duo.t : empty({T, H}, F32, *u.t), dW = dWo.t ? *dWo.t : empty({H, H}, F32, *u.t);
-    CALL(ssm_half_glu_bwd(u.f32(), W.f32(), g.f32(), dy.f32(), T, H, f32(du), f32(dW), w.p, w.n, s));
+    CALL(ssm_half_glu_bwd, u.f32(), W.f32(), g.f32(), dy.f32(), T, H, f32(du), f32(dW), w.p, w.n, s);
     return tuple({&du, &dW});
     TRY_END
 }

@@ -49,3 +49,47 @@ def test_native_and_general_path_agree_and_honour_given_outputs_streams_and_work
     with pytest.raises(ssm.SsmError) as e:
         ssm.ssm_scan_fwd(**a, workspace=ws[:256])
     assert e.value.code == ssm.SSM_ERR_WORKSPACE
+
+
+BATCHED = r"""
+import sys, types, warnings
+sys.path.insert(0, %r)
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2502_20168_amd import binding as ssm
+warnings.simplefilter("ignore")
+Bt, L, H, P, T = 2, 8, 4, 3, 5
+with FakeTensorMode(allow_non_fake_inputs=True):
+    c = lambda *s: torch.empty(s, dtype=torch.complex64, device="cuda")
+    f = lambda *s: torch.empty(s, device="cuda")
+    par = [c(P), c(P, H), c(H, P), f(H), f(P)]
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    k = {"workspace": ws, "stream": types.SimpleNamespace(cuda_stream=0)}
+    grads = {"du": f(Bt, L, H), "dLambda": c(P), "dB": c(P, H), "dC": c(H, P), "dD": f(H), "dlog_delta": f(P), "dx0": c(Bt, P)}
+    calls = {
+        "scan_fwd": (f(7, Bt, L, H), lambda u: ssm.ssm_scan_fwd(*par, u, out={"y": f(Bt, L, H), "x": c(Bt, L, P), "x_last": c(Bt, P)}, **k)),
+        "scan_bwd": (f(7, Bt, L, H), lambda dy: ssm.ssm_scan_bwd(*par, f(Bt, L, H), None, None, c(Bt, L, P), dy, out=grads, **k)),
+        "step": (f(7, Bt, H), lambda u: ssm.ssm_step(ws, par[3], u, P=P, x=c(Bt, P), y=f(Bt, H), stream=k["stream"])),
+        "lambda_return": (f(7, T, Bt), lambda r: ssm.ssm_lambda_return(r, f(T, Bt), f(T, Bt), 0.9, 0.9, ret=f(T, Bt), stream=k["stream"])),
+        "scan_states": (c(7, Bt, L, P), lambda v: ssm.ssm_scan_states(par[0], v, want_x_last=False, **k)),
+        "half_glu_fwd": (f(7, T, H), lambda u: ssm.ssm_half_glu_fwd(u, f(H, H), y=f(T, H), gate=f(T, H), **k)),
+        "half_glu_bwd": (f(7, T, H), lambda u: ssm.ssm_half_glu_bwd(u, f(H, H), f(T, H), f(T, H), du=f(T, H), dW=f(H, H), **k)),
+    }
+    for name, (batch, call) in calls.items():
+        print(name, flush=True)
+        try:
+            torch.func.vmap(call)(batch)
+        except RuntimeError as e:
+            assert "data pointer" in str(e), e
+        else:
+            raise AssertionError("not refused")
+print("all refused")
+"""
+
+
+def test_a_tensor_without_storage_raises_and_does_not_end_the_interpreter():
+    """The data pointer of a batched tensor (torch.func.vmap over a call) cannot be taken: the call raises torch's error."""
+    import os, subprocess, sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", BATCHED % root], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("all refused"), (r.returncode, r.stdout, r.stderr[-2000:])
