@@ -14,6 +14,7 @@
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/ssm.h"
@@ -97,7 +98,13 @@ bool stream_of(PyObject *o, const Arg *workspace, void *&s)
     if (PyErr_Occurred()) { PyErr_Clear(); return false; }
     return true;
 }
-bool yes(PyObject *o) { return o == Py_True || (o != Py_False && PyObject_IsTrue(o) > 0); }
+bool yes(PyObject *o)
+{
+    if (o == Py_True || o == Py_False) return o == Py_True;
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw python_error();                 // (its error is the caller's)
+    return v > 0;
+}
 
 PyObject *wrap(const at::Tensor &t)
 {
@@ -142,8 +149,9 @@ ssm_status call_without_gil(ssm_status (*entry)(P...), A... args)
     const ssm_status rc = call_without_gil(__VA_ARGS__); \
     if (rc != SSM_OK) return PyLong_FromLong((long)rc)
 #define ENTRY(name) PyObject *name(PyObject *, PyObject *const *a, Py_ssize_t n)
-#define TRY_BEGIN try {
-#define TRY_END } catch (const std::exception &e) { PyErr_SetString(PyExc_RuntimeError, e.what()); return nullptr; }
+// (torch's own translation: an allocation that fails raises torch.OutOfMemoryError here as on the general path)
+#define TRY_BEGIN HANDLE_TH_ERRORS
+#define TRY_END END_HANDLE_TH_ERRORS
 
 // The eight inputs that the layer's calls share, and the shape they agree on.
 struct LayerArgs {

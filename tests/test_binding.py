@@ -93,3 +93,35 @@ def test_a_tensor_without_storage_raises_and_does_not_end_the_interpreter():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", BATCHED % root], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("all refused"), (r.returncode, r.stdout, r.stderr[-2000:])
+
+
+class _NoTruthValue:
+    def __bool__(self):
+        raise ValueError("neither")
+
+
+def test_an_error_raised_by_an_option_is_the_callers():
+    import types
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    from paper_2502_20168_amd import binding as ssm
+    with FakeTensorMode(allow_non_fake_inputs=True):
+        a = {k: None if v is None else torch.empty(v.shape, dtype=v.dtype, device="cuda") for k, v in _small("cpu").items()}
+        out = {"y": torch.empty(a["u"].shape, device="cuda")}
+        with pytest.raises(ValueError, match="neither"):
+            ssm.ssm_scan_fwd(**a, want_x=_NoTruthValue(), out=out, workspace=out["y"], stream=types.SimpleNamespace(cuda_stream=0))
+
+
+@pytest.mark.gpu
+def test_an_allocation_that_fails_raises_torchs_error():
+    import torch
+    from paper_2502_20168_amd import binding as ssm
+    r = torch.zeros(64, 1 << 20, device="cuda")                  # 256 MiB
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            ssm.ssm_lambda_return(r, r, r, 0.9, 0.9)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
