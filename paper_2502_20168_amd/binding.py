@@ -39,8 +39,6 @@ EXPORTS = ("ssm_strerror", "ssm_version", "ssm_workspace_bytes", "ssm_discretize
            "ssm_half_glu_bwd", "ssm_block_workspace_bytes", "ssm_block_fwd", "ssm_block_bwd", "ssm_set_spin_limit",
            "ssm_scan_states_noalloc", "ssm_scan_states_noalloc_status", "ssm_plan_describe")
 
-BIND_PATH = os.path.join(HERE, "_ssmbind.so")
-
 _lib = None
 _native = None
 _vp, _i64, _sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_size_t
@@ -122,15 +120,28 @@ def lib():
     return _lib
 
 
+class _GeneralPathOnly:
+    """Stands in for a native half that cannot be loaded: like it, answers None for what it does not take."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _bind():
-    """The native half of the binding (loaded behind the library, which it is linked to)."""
+    """The native half of the binding (loaded behind the library, which it is linked to).  It is built against one build
+    of torch; where it is missing or does not load, every call takes the general path (the same kernels, a few
+    microseconds more on the host) and this says so once."""
     global _native
     if _native is None:
         lib()
-        if not os.path.exists(BIND_PATH):
-            raise ImportError("_ssmbind.so is not built: run `python paper_2502_20168_amd/build.py` first")
-        from . import _ssmbind
-        _native = _ssmbind
+        try:
+            from . import _ssmbind
+            _native = _ssmbind
+        except ImportError as e:
+            import warnings
+            warnings.warn("the native half of the binding does not load (%s): run `python paper_2502_20168_amd/build.py`; calls go "
+                          "through ctypes" % e, RuntimeWarning, stacklevel=3)
+            _native = _GeneralPathOnly()
     return _native
 
 

@@ -125,3 +125,16 @@ def test_an_allocation_that_fails_raises_torchs_error():
             ssm.ssm_lambda_return(r, r, r, 0.9, 0.9)
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+def test_without_its_native_half_the_binding_takes_the_general_path(monkeypatch):
+    import sys
+    import paper_2502_20168_amd as package
+    from paper_2502_20168_amd import binding as ssm
+    monkeypatch.setattr(ssm, "_native", None)
+    monkeypatch.delattr(package, "_ssmbind", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2502_20168_amd._ssmbind", None)      # (its import raises ImportError)
+    with pytest.warns(RuntimeWarning, match="native half"), pytest.raises(ValueError, match="Lambda must be a contiguous cuda tensor"):
+        ssm.ssm_scan_fwd(**_small("cpu"))
+    with pytest.raises(ValueError, match="Lambda must be"):      # said once; every call is served
+        ssm.ssm_step_prepare(*(_small("cpu")[k] for k in ("Lambda", "B", "C", "log_delta")))
