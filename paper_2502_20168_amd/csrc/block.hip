@@ -265,8 +265,7 @@ bool make_glu_layout(int64_t T, int64_t H, bool bwd, GluLayout &o)
     o.x1 = off; off += up((size_t)T * H * 4);
     o.dz = o.ds = o.gd = o.dWpart = 0; o.splits = 1;
     o.two_planes = gate_two_planes_shape(T, H);
-    // gradient pass: both products wait for the same element-wise pass and share one launch; on two planes the K
-    // splits of the reduction come from the schedule model of that launch
+    // gradient pass: both products wait for the same element-wise pass and share one launch
     o.planes = o.two_planes ? 2 : 3; o.dw_first = false;
     o.wfrag = off; off += up(packed_frag_bytes(H, H, o.planes));
     o.wexp = off; off += up((size_t)(H + 31) / 32 * 32 * 4);
@@ -274,9 +273,8 @@ bool make_glu_layout(int64_t T, int64_t H, bool bwd, GluLayout &o)
         o.dz = off; off += up((size_t)T * H * 4);
         o.ds = off; off += up((size_t)T * H * 4);
         o.gd = off; off += up((size_t)T * H * 4);
-        if (o.two_planes) o.splits = gemm_pick_splits_balanced(H, H, T, ((T + 127) / 128) * ((H + 127) / 128), H, o.dw_first);
-        else if (gemm_small_pair(T, H)) o.splits = gemm_pick_splits_small(H, H, T, T, H, H);
-        else o.splits = gemm_pick_splits(H, H, T, ((T + 127) / 128) * ((H + 127) / 128));
+        const SlabPlan dW = gemm_plan_slabs(H, H, T, 1, reduction_tile(o.planes, gemm_small_pair(T, H)), H);
+        o.splits = dW.slabs; o.dw_first = dW.first;
     }
     if (bwd) { o.dWpart = off; off += up((size_t)o.splits * H * H * 4); }
     o.rowmax = o.slots = 0; o.row_parts = o.main_blocks = 0;

@@ -5,21 +5,6 @@
 
 namespace ssm {
 
-int gemm_pick_splits(int64_t M, int64_t N, int64_t K, int64_t partner_tiles)
-{
-    // A long reduction with a small result shares its launch with a product of partner_tiles
-    // 128x128 tiles: enough K splits that the two together fill the last round of workgroups
-    // on the 256 CUs, keeping at least 256 rows of K per split.
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    const int64_t target = 256 - partner_tiles % 256;
-    int64_t s = (target + tiles / 2) / tiles;
-    const int64_t maxs = (K + 255) / 256;
-    if (s > maxs) s = maxs;
-    if (s > 64) s = 64;
-    if (s < 1) s = 1;
-    return (int)s;
-}
-
 // A product over T tokens with N columns that has few 128x128 tiles shares its launch with a K = T
 // reduction on 64x64x64 tiles: a quarter of the multiply-adds per workgroup, so that the chain of K
 // steps a small shape waits for is short.
@@ -30,91 +15,31 @@ bool gemm_small_pair(int64_t T, int64_t N)
     return ((T + 127) / 128) * ((N + 127) / 128) <= SMALL_PAIR_ITEMS;
 }
 
-// K splits of an M x N reduction over K rows that shares such a launch with a product of main_M x main_N whose K loop is
-// k_main long: work items about as long as that product's (an item takes about 1.5 times as long per row as the product), at
-// most two rounds of workgroups in all; where there is room for it in one round, at least 128 rows per item.
-int gemm_pick_splits_small(int64_t M, int64_t N, int64_t K, int64_t main_M, int64_t main_N, int64_t k_main)
+// Reductions of M x N over K rows (`count` of them, with the same number of tiles) that share a launch with a product.
+// What a launch of several rounds wants is one work item of the reductions per CU, a few less rather than more, and all of
+// them in the first slots: every CU then works on one item from beginning to end while the product's tiles pass through its
+// second place.  Beside a small product, whose workgroups have a CU to themselves (64 x 64 tiles, eight wavefronts of
+// either kind), half as many, and in front only where an item is the longer chain (more rows than the product's K loop).
+// The counts are those that divide 8 or that 8 divides, because then an XCD owns whole slabs or one band of one
+// (tn_place), and a few between; the one whose number of items is nearest in ratio; an item keeps at least 192 (64) rows.
+// Measured on 251 launches (every product's reductions at 1000 .. 32768 tokens, H and P from 64 to 1024) against 18 counts in either order:
+// the gradient pass is 0.7 % slower than with the best of them on geometric mean, 8 % at worst.  Some (us; this rule, best, same
+// count with the product first):
+//   one launch of three products   24x128, H 1024, P 512: 129 129 131     16x256, 512, 512: 93.4 93.4 95.2    4x4096, 256, 256: 101 101 102
+//   launches of two, two planes    16x1000, 512, 512: 308 308 330         24x200, 1024, 512: 188 187 201
+//   launches of two, three planes  20x300, 500, 250: 121 121 130          40x200, 768, 384: 259 259 298
+//   beside small products          20x100, 256, 256: 46.7 46.7 50.5       8x128, 256, 256: 39.1 39.1 39.2
+SlabPlan gemm_plan_slabs(int64_t M, int64_t N, int64_t K, int count, ReductionTile tile, int64_t k_main)
 {
-    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    const int64_t kt = k_main < 64 ? 64 : k_main;
-    int64_t s = (K + k_main / 2) / kt;
-    const int64_t room = (512 - ((main_M + 63) / 64) * ((main_N + 63) / 64)) / tiles;
-    if (s > room) s = room;
-    const int64_t maxs = (K + 63) / 64;
-    if (s > maxs) s = maxs;
-    const int64_t t64 = ((main_M + 63) / 64) * ((main_N + 127) / 128), items = t64 <= 128 ? ((main_M + 31) / 32) * ((main_N + 127) / 128) : t64;
-    int64_t one = (3 * K / 2 + kt / 2) / kt;
-    if (one > (256 - items) / tiles) one = (256 - items) / tiles;
-    if (one > K / 128) one = K / 128;
-    if (s < one) s = one;
-    if (s > 64) s = 64;
-    if (s < 1) s = 1;
-    return (int)s;
-}
-
-// List scheduling of nl work items of l K tiles and then ns items of s K tiles on the 256 CUs, as the
-// dispatcher hands out workgroups in slot order to CUs as they fall free (a CU's two workgroups share its
-// throughput, so a CU is one machine): the K tiles the busiest CU ends up with.  Loads are kept as (level, number of CUs) pairs; a batch of items goes to all CUs of
-// the lowest level at once.
-int64_t lpt_makespan(int64_t nl, int64_t l, int64_t ns, int64_t s)
-{
-    constexpr int64_t CUS = 256;
-    constexpr int MAXLV = 16;
-    int64_t lv[MAXLV], cnt[MAXLV];
-    int n = 0;
-    const int64_t q = nl / CUS, r = nl % CUS;
-    lv[n] = q * l; cnt[n] = CUS - r; ++n;                    // ascending levels
-    if (r) { lv[n] = (q + 1) * l; cnt[n] = r; ++n; }
-    while (ns > 0) {
-        const int64_t k = cnt[0] < ns ? cnt[0] : ns;
-        const int64_t target = lv[0] + s;
-        ns -= k;
-        cnt[0] -= k;
-        if (cnt[0] == 0) { for (int i = 1; i < n; ++i) { lv[i - 1] = lv[i]; cnt[i - 1] = cnt[i]; } --n; }
-        int pos = 0;
-        while (pos < n && lv[pos] < target) ++pos;
-        if (pos < n && lv[pos] == target) { cnt[pos] += k; continue; }
-        if (n == MAXLV) { lv[n - 1] = lv[n - 1] > target ? lv[n - 1] : target; cnt[n - 1] += k; continue; }   // (never with two item lengths)
-        for (int i = n; i > pos; --i) { lv[i] = lv[i - 1]; cnt[i] = cnt[i - 1]; }
-        lv[pos] = target; cnt[pos] = k; ++n;
-    }
-    return lv[n - 1];
-}
-
-// K splits of the K = T reductions (red_tiles tiles of 128x128 in all, split_bytes of slabs per split in
-// all) that share a launch of 128x128x32 tiles with a product of main_tiles tiles whose K loop is k_main
-// long: the count that minimises the busiest CU's K tiles plus what every further set of slabs costs (their
-// bytes are written by this launch and read by the parameter epilogue's: measured 1.4 us, about 1.4 K
-// tiles, per split of two reductions with 2 MiB slabs).  red_first: the reductions' work items belong in the
-// first slots of the launch.  One workgroup per CU: whichever order the schedule model finishes earlier,
-// the product first on a tie (measured on ten shapes with separate scan kernels: the model's choice was
-// the faster order on every one, by up to 5 % of the step).  Two workgroups per CU: the reductions first
-// when their items are at least twice as long as the product's (then a CU holds one of each kind for most
-// of the launch instead of ending on single long items; 1024 x 16 tokens, H = P = 512: 0.469 against 0.482 ms).
-int gemm_pick_splits_model(int64_t T, int64_t main_tiles, int64_t k_main, int64_t red_tiles, size_t split_bytes, bool two_per_cu,
-                           bool &red_first)
-{
-    static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64};
-    const int64_t a = (k_main + 31) / 32;
-    const double per_split = 0.2 + 0.6 * (double)split_bytes / (double)(2 << 20);
+    const bool small = tile == REDUCTION_64x64;
+    const int64_t tiles = reduction_items(M, N, count, tile), want = small ? 128 : 224, min_rows = small ? 64 : 192;
     int best = 1;
-    double best_cost = -1.0;
-    red_first = false;
-    for (int sp : cand) {
-        if (sp > 1 && sp > T / 256) break;
-        const int64_t b = (((T + sp - 1) / sp) + 31) / 32;
-        const int64_t m_main = lpt_makespan(main_tiles, a, red_tiles * sp, b), m_red = lpt_makespan(red_tiles * sp, b, main_tiles, a);
-        const int64_t m = m_red < m_main ? m_red : m_main;
-        const double cost = (double)m + per_split * sp;
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; red_first = two_per_cu ? b >= 2 * a : m_red < m_main; }
+    for (int s : {2, 3, 4, 5, 8, 12, 16, 24, 32, 40, 48, 56, 64}) {
+        if (K / s < min_rows) break;
+        // s is nearer than best: want / (tiles best) > (tiles s) / want
+        if (tiles * s <= want || want * want > tiles * best * tiles * s) best = s;
     }
-    return best;
-}
-
-// (one reduction of M x N over K rows beside a product of main_tiles tiles, one workgroup per CU)
-int gemm_pick_splits_balanced(int64_t M, int64_t N, int64_t K, int64_t main_tiles, int64_t k_main, bool &red_first)
-{
-    return gemm_pick_splits_model(K, main_tiles, k_main, ((M + 127) / 128) * ((N + 127) / 128), (size_t)M * N * 4, false, red_first);
+    return {best, !small || (K + best - 1) / best > k_main};
 }
 
 // The projections scan their own output tiles where a sequence is a whole number of 128-step pieces (a bounded chain

@@ -26,7 +26,6 @@ hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmA
     case 0: SSM_TALL(0, 128);                             // C^H dy with the dC slabs (separate scan kernels)
     case 1: SSM_TALL(1, 128);                             // du with the dBbar slabs, and the dC slabs
     case 4: SSM_TALL(4, 128);                             // adjoint of the gate with the dW slabs
-    case 8: return SSM_PK(64, 128, 8, 128);               // C^H dy that scans, with the dC slabs (few tiles)
     default: return hipErrorInvalidValue;
     }
 #undef SSM_ALONE

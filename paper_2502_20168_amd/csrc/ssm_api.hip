@@ -93,16 +93,14 @@ PackedW packed(const char *base, const PackedLayout &l) { return PackedW{base + 
 
 struct Layout {
     ScanPlan plan;
-    int splitC, splitB, nslab;
-    // scanning shapes with fewer scanning tiles than CUs: the dC slabs share the launch of C^H dy (they need
-    // the largest magnitude of the saved states from a pass of the prep launch); otherwise they wait for the
-    // launch of Re(Bbar^H chi), and the reverse scan records that magnitude on its way
-    bool dc_early;
+    int nslab;
+    // slabs of dC = dy^T x and dBbar = chi^T u.  Scanning shapes: both in the launch of Re(Bbar^H chi) (dC waits there for
+    // the largest magnitude of the saved states, which the reverse scan records on its way); otherwise dC shares the
+    // launch of C^H dy.
+    SlabPlan dC, dB;
     // separate scan kernels, products of more than 64 tiles: two scaled fp16 planes there too (the scan kernels
     // record the largest magnitude of every token row of x and chi with atomics, the prep launch measures the rest)
     bool planes2_unfused;
-    bool slabs_first;        // launch of three products: the slabs' work items go first
-    bool dc_first, db_first; // launches of two products (separate scan kernels): the slab items go first
     int planes;              // per operand of every product
     PackedLayout w_in, w_out;          // forward: Bbar and C
     PackedLayout w_gx, w_du;           // gradient pass: both transposed
@@ -115,16 +113,6 @@ struct Layout {
     // rowpart [ceil(2P/128), T] (x forward, chi gradient pass: one word per column tile of the scanning projection)
     size_t rowmax, rowpart; int row_parts;
 };
-
-// K splits of the two K = T reductions that share the launch of du (shapes whose projections scan their
-// own tiles, more scanning tiles than 192), two workgroups per CU; slabs_first: their work items take the
-// first slots of the launch.
-int pick_triple_splits(int64_t T, int64_t H, int64_t P, bool &slabs_first)
-{
-    const int64_t n_du = ((T + 127) / 128) * ((H + 127) / 128);
-    const int64_t slab_tiles = 2 * ((2 * P + 127) / 128) * ((H + 127) / 128);
-    return gemm_pick_splits_model(T, n_du, 2 * P, slab_tiles, (size_t)2 * 2 * P * H * 4, true, slabs_first);
-}
 
 ssm_status check_dims(int64_t Bt, int64_t L, int64_t H, int64_t P)
 {
@@ -143,25 +131,6 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     const size_t T = (size_t)Bt * L;
     o.plan = plan_scan(Bt, L, P);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
-    const int64_t rows128 = ((int64_t)T + 127) / 128;
-    o.slabs_first = o.dc_first = o.db_first = false;
-    o.dc_early = gemm_scan_shape_ok(Bt, L, P) && rows128 * ((2 * P + 127) / 128) <= 192;
-    if (gemm_scan_shape_ok(Bt, L, P) && !o.dc_early) {
-        // dy^T x and chi^T u share the launch of Re(Bbar^H chi)
-        o.splitC = o.splitB = pick_triple_splits((int64_t)T, H, P, o.slabs_first);
-    } else {
-        o.splitC = gemm_pick_splits(H, 2 * P, (int64_t)T, rows128 * ((2 * P + 127) / 128));   // shares C^H dy's launch
-        o.splitB = gemm_pick_splits(2 * P, H, (int64_t)T, rows128 * ((H + 127) / 128));       // shares Bbar^H chi's launch
-        if (!gemm_scan_shape_ok(Bt, L, P)) {
-            // separate scan kernels: a launch of two products with several rounds of work items
-            o.splitC = gemm_pick_splits_balanced(H, 2 * P, (int64_t)T, rows128 * ((2 * P + 127) / 128), H, o.dc_first);
-            o.splitB = gemm_pick_splits_balanced(2 * P, H, (int64_t)T, rows128 * ((H + 127) / 128), 2 * P, o.db_first);
-        }
-        if (gemm_small_pair((int64_t)T, 2 * P))
-            o.splitC = gemm_pick_splits_small(H, 2 * P, (int64_t)T, (int64_t)T, 2 * P, H);
-        if (gemm_small_pair((int64_t)T, H))
-            o.splitB = gemm_pick_splits_small(2 * P, H, (int64_t)T, (int64_t)T, H, 2 * P);
-    }
     o.nslab = coldot_slabs((int64_t)T);
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));
@@ -198,6 +167,12 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
     o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
+    if (gemm_scan_shape_ok(Bt, L, P)) {
+        o.dC = o.dB = gemm_plan_slabs(2 * P, H, (int64_t)T, 2, REDUCTION_128x128, 2 * P);
+    } else {
+        o.dC = gemm_plan_slabs(H, 2 * P, (int64_t)T, 1, reduction_tile(o.planes, gemm_small_pair((int64_t)T, 2 * P)), H);
+        o.dB = gemm_plan_slabs(2 * P, H, (int64_t)T, 1, reduction_tile(o.planes, gemm_small_pair((int64_t)T, H)), 2 * P);
+    }
     if (!bwd) {
         add_packed(off, o.w_in, 2 * P, H, o.planes);
         add_packed(off, o.w_out, H, 2 * P, o.planes);
@@ -206,8 +181,8 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         add_packed(off, o.w_gx, 2 * P, H, o.planes);
         add_packed(off, o.w_du, H, 2 * P, o.planes);
         o.chi = off; off += up(T * P * 8);
-        o.dCpart = off; off += up((size_t)o.splitC * 2 * P * H * 4);
-        o.dBpart = off; off += up((size_t)o.splitB * 2 * P * H * 4);
+        o.dCpart = off; off += up((size_t)o.dC.slabs * 2 * P * H * 4);
+        o.dBpart = off; off += up((size_t)o.dB.slabs * 2 * P * H * 4);
         o.dApart = off; off += up(dA_elems * 8);
         o.dDpart = off; off += up((size_t)o.nslab * H * 4);
     }
@@ -423,7 +398,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     // two scaled fp16 planes per operand: dy and u are measured where dD reads them, chi and the saved
     // states where the reverse scan stores / reads them
     const bool two_planes = lo.planes == 2;
-    const bool x_pass = lo.dc_early || lo.planes2_unfused;       // the largest magnitude of the saved states from a pass of the prep launch
+    const bool x_pass = lo.planes2_unfused;       // the largest magnitude of the saved states from a pass of the prep launch
     unsigned *am_atomic = reinterpret_cast<unsigned *>(ws + lo.amax_atomic), *am_xsaved = am_atomic + ABSMAX_SLOTS;
     unsigned *am_pass = reinterpret_cast<unsigned *>(ws + lo.amax_slots);
     unsigned *am_dy = am_pass + PREP_PASS_BLOCKS, *am_u = am_dy + lo.amax_cd;
@@ -453,7 +428,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     g4.A = dy; g4.lda = H;
     g4.B = xf; g4.ldb = 2 * P;
     g4.C = dCpart; g4.ldc = 2 * P;
-    g4.M = (int)H; g4.N = (int)(2 * P); g4.K = T; g4.splits = lo.splitC;
+    g4.M = (int)H; g4.N = (int)(2 * P); g4.K = T; g4.splits = lo.dC.slabs;
     if (two_planes) { g3.amaxA = mx_dy_rows; g4.amaxA = mx_dy; g4.amaxB = mx_x; }
     if (fused) {
         // the product scans its own tiles; the dC slabs wait for the next launch, where the largest
@@ -465,11 +440,11 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
         g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = gemm_scan_rows(T, P); g3.scan.spin_limit = spin_limit();
-        g3.scan.amax_out = am_atomic; g3.scan.xmax_out = lo.dc_early ? nullptr : am_xsaved; g3.scan.rowmax_out = rowpart;
-        HIP_TRY(launch_products(g3, lo.dc_early ? &g4 : nullptr, nullptr, false, s));
+        g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart;
+        HIP_TRY(launch_product(g3, s));
     } else {
-        // dC needs only dy and the saved states: it shares the launch (whichever kind of work item the schedule model puts first)
-        HIP_TRY(launch_products(g3, &g4, nullptr, lo.dc_first, s));
+        // dC needs only dy and the saved states: it shares the launch
+        HIP_TRY(launch_products(g3, &g4, nullptr, lo.dC.first, s));
     }
     MARK();
 
@@ -498,19 +473,18 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     g6.A = reinterpret_cast<const float *>(chi); g6.lda = 2 * P;
     g6.B = u; g6.ldb = H;
     g6.C = dBpart; g6.ldc = H;
-    g6.M = (int)(2 * P); g6.N = (int)H; g6.K = T; g6.splits = lo.splitB;
+    g6.M = (int)(2 * P); g6.N = (int)H; g6.K = T; g6.splits = lo.dB.slabs;
     if (two_planes) { g5.amaxA = mx_chi_rows; g6.amaxA = mx_chi; g6.amaxB = mx_u; }
     // three products in one launch where the dC slabs had to wait for the largest magnitude of the saved states
-    if (fused && !lo.dc_early) HIP_TRY(launch_products(g5, &g6, &g4, lo.slabs_first, s));
-    else HIP_TRY(launch_products(g5, &g6, nullptr, !fused && lo.db_first, s));
+    HIP_TRY(launch_products(g5, &g6, fused ? &g4 : nullptr, lo.dB.first, s));
     MARK();
     MARK();
 
     EpilogueArgs ea{};
     ea.Lambda = reinterpret_cast<const float2 *>(Lambda); ea.B = reinterpret_cast<const float2 *>(B);
     ea.log_delta = log_delta; ea.P = (int)P; ea.H = (int)H;
-    ea.dBbar_part = dBpart; ea.nsplit_B = lo.splitB;
-    ea.dC_part = dCpart; ea.nsplit_C = lo.splitC;
+    ea.dBbar_part = dBpart; ea.nsplit_B = lo.dB.slabs;
+    ea.dC_part = dCpart; ea.nsplit_C = lo.dC.slabs;
     ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, P) : (int64_t)Bt * lo.plan.nTB;
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
@@ -631,11 +605,10 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     const int64_t T = Bt * L;
     out[0] = fused ? 1 : 0;
     out[1] = lo.planes;
-    out[2] = lo.splitC; out[3] = lo.splitB;
-    out[4] = (fused && !lo.dc_early) ? 3 : 2;
-    out[5] = lo.slabs_first ? 1 : 0;
-    out[6] = (!fused && lo.dc_first) ? 1 : 0;
-    out[7] = (!fused && lo.db_first) ? 1 : 0;
+    out[2] = lo.dC.slabs; out[3] = lo.dB.slabs;
+    out[4] = fused ? 3 : 2;
+    out[5] = fused && lo.dB.first;
+    out[6] = !fused && lo.dC.first; out[7] = !fused && lo.dB.first;
     out[8] = 0;
     out[9] = fused ? 0 : gemm_tile_tier(T, 2 * P, 1);
     out[10] = gemm_tile_tier(T, H, 1);

@@ -98,20 +98,20 @@ inline hipError_t launch_product(const GemmArgs &a, hipStream_t s) { return laun
 // the instantiations with two and three planes
 hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
 hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
-// number of K splits for a reduction over K rows with an M x N result that shares its launch
-// with a product of partner_tiles 128x128 tiles
-int gemm_pick_splits(int64_t M, int64_t N, int64_t K, int64_t partner_tiles);
-// the same for launches of several rounds of work items (a schedule model of the launch; red_first: the
-// reduction's work items belong in the first slots); the model behind it: reductions over T rows with red_tiles
-// tiles of 128x128 in all (split_bytes of slabs per split in all) beside a product of main_tiles tiles with a
-// K loop of k_main, one or two workgroups per CU
-int gemm_pick_splits_balanced(int64_t M, int64_t N, int64_t K, int64_t main_tiles, int64_t k_main, bool &red_first);
-int gemm_pick_splits_model(int64_t T, int64_t main_tiles, int64_t k_main, int64_t red_tiles, size_t split_bytes, bool two_per_cu,
-                           bool &red_first);
-// a product over T tokens with N columns has so few tiles that the reduction in its launch runs on 64x64x64 tiles; the K
-// splits of that reduction (main_M x main_N, k_main: the product)
+// a product over T tokens with N columns has so few tiles that the reduction in its launch runs on 64x64 tiles
 bool gemm_small_pair(int64_t T, int64_t N);
-int gemm_pick_splits_small(int64_t M, int64_t N, int64_t K, int64_t main_M, int64_t main_N, int64_t k_main);
+// Tiles of the reductions of a launch: beside small products, beside other products on three planes, on two planes.
+enum ReductionTile { REDUCTION_64x64 = 64, REDUCTION_128x64 = 96, REDUCTION_128x128 = 128 };
+inline ReductionTile reduction_tile(int planes, bool small) { return planes == 2 ? REDUCTION_128x128 : small ? REDUCTION_64x64 : REDUCTION_128x64; }
+// K slabs of `count` reductions of M x N over K rows that share a launch with a product whose K loop is k_main long, and
+// whether their work items take the first slots
+struct SlabPlan { int slabs; bool first; };
+inline int64_t reduction_items(int64_t M, int64_t N, int slabs, ReductionTile tile)
+{
+    const int64_t tm = tile == REDUCTION_64x64 ? 64 : 128, tn = tile == REDUCTION_128x128 ? 128 : 64;
+    return ((M + tm - 1) / tm) * ((N + tn - 1) / tn) * slabs;
+}
+SlabPlan gemm_plan_slabs(int64_t M, int64_t N, int64_t K, int count, ReductionTile tile, int64_t k_main);
 
 // ---------------------------------------------------------------------------------------------
 // Resettable scan over the sequence dimension (forward and reverse time).

@@ -1,8 +1,8 @@
 """Host logic that decides what a call launches (no GPU needed): which shapes scan inside the projections,
 how many planes, tile tiers, K slabs of the reductions and which work items go first.  The decisions are
 read back through ssm_plan_describe (include/ssm_measure.h); the expectations are the rules the design
-states, evaluated here independently in Python for the scheduling model."""
-import heapq
+states, evaluated here independently in Python."""
+from fractions import Fraction
 
 import pytest
 
@@ -15,10 +15,10 @@ def test_benchmark_configurations_take_the_paths_the_design_states():
     assert [p["scans_in_projections"] for p in plans] == [0, 0, 1, 1, 1]
     assert [p["planes"] for p in plans] == [3, 3, 2, 2, 2]
     assert [p["products_per_gradient_launch"] for p in plans] == [2, 2, 3, 3, 3]
-    # the benchmark shape: eight slabs per reduction behind du, the output projection on 64x128 tiles
-    assert plans[2]["slabs_dC"] == 8 and plans[2]["slabs_dBbar"] == 8 and plans[2]["slabs_first"] == 0
+    # the benchmark shape: four slabs per reduction, in front of du
+    assert plans[2]["slabs_dC"] == 4 and plans[2]["slabs_dBbar"] == 4 and plans[2]["slabs_first"] == 1
     assert plans[2]["tier_out"] == 1 and plans[2]["tier_in"] == 0
-    # 1024 x 16 tokens: few long slab items, dispatched first
+    # 1024 x 16 tokens: the same
     assert plans[4]["slabs_dC"] == 4 and plans[4]["slabs_first"] == 1
     # the small configurations run everything on 64x64x64 tiles
     assert plans[0]["tier_in"] == 2 and plans[0]["tier_out"] == 2 and plans[1]["tier_in"] == 2
@@ -45,56 +45,46 @@ def test_192_tiles_of_128_take_one_round_of_large_tiles():
     assert ssm.ssm_plan_describe(30, 100, 512, 512)["tier_in"] == 0
 
 
-def _makespan(first, second):
-    """List scheduling of (count, length) items on 256 machines in the given order."""
-    h = [0] * 256
-    heapq.heapify(h)
-    for n, ln in (first, second):
-        for _ in range(n):
-            heapq.heappush(h, heapq.heappop(h) + ln)
-    return max(h)
+COUNTS = (1, 2, 3, 4, 5, 8, 12, 16, 24, 32, 40, 48, 56, 64)
 
 
-def _model(T, main_tiles, k_main, red_tiles, split_bytes):
-    a = -(-k_main // 32)
-    per = 0.2 + 0.6 * split_bytes / (2 << 20)
-    best = None
-    for sp in (1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64):
-        if sp > 1 and sp > T // 256:
-            break
-        b = -(-(-(-T // sp)) // 32)
-        m_main, m_red = _makespan((main_tiles, a), (red_tiles * sp, b)), _makespan((red_tiles * sp, b), (main_tiles, a))
-        cost = min(m_main, m_red) + per * sp
-        if best is None or cost < best[0]:
-            best = (cost, sp, m_red < m_main, b >= 2 * a)
-    return best
+def _slabs(T, tiles, small):
+    """The count whose number of work items is nearest, in ratio, to 224 (128 beside small products)."""
+    want, rows = (128, 64) if small else (224, 192)
+    allowed = [s for s in COUNTS if s == 1 or T // s >= rows]
+    return min(allowed, key=lambda s: (max(Fraction(tiles * s, want), Fraction(want, tiles * s)), s))
+
+
+def _ceil(x, y):
+    return -(-x // y)
 
 
 @pytest.mark.parametrize("Bt,L,H,P", [(16, 256, 512, 512), (4, 4096, 256, 256), (1024, 16, 512, 512), (32, 128, 1024, 512),
-                                      (256, 64, 256, 256), (8, 1024, 512, 512)])
-def test_slabs_of_the_three_product_launch_follow_the_schedule_model(Bt, L, H, P):
+                                      (256, 64, 256, 256), (8, 1024, 512, 512), (24, 128, 1024, 512), (32, 128, 512, 256), (4, 128, 1024, 1024),
+                                      (64, 128, 64, 70)])
+def test_slabs_of_the_three_product_launch(Bt, L, H, P):
     T = Bt * L
     p = ssm.ssm_plan_describe(Bt, L, H, P)
-    assert p["products_per_gradient_launch"] == 3
-    c = lambda x, y: -(-x // y)
-    _, sp, _, twice = _model(T, c(T, 128) * c(H, 128), 2 * P, 2 * c(2 * P, 128) * c(H, 128), 2 * 2 * P * H * 4)
-    assert p["slabs_dC"] == sp and p["slabs_dBbar"] == sp
-    assert p["slabs_first"] == int(twice)
+    assert p["products_per_gradient_launch"] == 3 and p["scans_in_projections"] == 1
+    s = _slabs(T, 2 * _ceil(2 * P, 128) * _ceil(H, 128), False)
+    assert p["slabs_dC"] == s and p["slabs_dBbar"] == s
+    assert p["slabs_first"] == 1
 
 
 @pytest.mark.parametrize("Bt,L,H,P", [(64, 100, 512, 512), (16, 1000, 256, 256), (24, 200, 1024, 512), (20, 300, 512, 256),
-                                      (10, 1000, 512, 512)])
-def test_slabs_and_order_of_the_two_product_launches_follow_the_schedule_model(Bt, L, H, P):
+                                      (10, 1000, 512, 512), (40, 200, 768, 384), (40, 100, 256, 256), (16, 64, 256, 256), (1, 256, 1024, 1024),
+                                      (8, 128, 64, 256), (5, 77, 96, 40), (1, 3, 2, 1)])
+def test_slabs_and_order_of_the_two_product_launches(Bt, L, H, P):
     T = Bt * L
     p = ssm.ssm_plan_describe(Bt, L, H, P)
     assert p["products_per_gradient_launch"] == 2 and p["scans_in_projections"] == 0
-    c = lambda x, y: -(-x // y)
-    red = c(H, 128) * c(2 * P, 128)
-    _, spC, firstC, _ = _model(T, c(T, 128) * c(2 * P, 128), H, red, H * 2 * P * 4)
-    assert p["slabs_dC"] == spC and p["dC_first"] == int(firstC)
-    halves = p["du_as_two_k_halves"]
-    _, spB, firstB, _ = _model(T, c(T, 128) * c(H, 128) * (2 if halves else 1), P if halves else 2 * P, red, H * 2 * P * 4)
-    assert p["slabs_dBbar"] == spB and p["dBbar_first"] == int(bool(halves) or firstB)
+    for M, N, K, slabs, first in ((H, 2 * P, H, "slabs_dC", "dC_first"), (2 * P, H, 2 * P, "slabs_dBbar", "dBbar_first")):
+        # beside a product of T x N with a K loop of K
+        small = _ceil(T, 128) * _ceil(N, 128) <= 64
+        tile = (128, 128) if p["planes"] == 2 else (64, 64) if small else (128, 64)
+        s = _slabs(T, _ceil(M, tile[0]) * _ceil(N, tile[1]), small)
+        assert p[slabs] == s
+        assert p[first] == int(not small or _ceil(T, s) > K)
 
 
 def test_every_plan_is_bounded_and_repeatable():
