@@ -7,7 +7,7 @@ namespace ssm {
 hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
 {
     const int64_t others = reduction_items<128>(b) + reduction_items<128>(c);
-    const PkTile t = a.epilogue >= 7 ? PkTile{a.scan.rows, 128} : pk_tile(a, others, !tn_first);
+    const PkTile t = a.epilogue >= 7 ? PkTile{a.scan.rows, 128} : pk_tile(a, others);
 #define SSM_PK(rows, cols, epi, tnb) launch_pk_variant<rows, cols, 2, epi, tnb, 4>(a, b, c, tn_first, s)
 #define SSM_TALL(epi, tnb) return t.rows <= 64 ? SSM_PK(64, 128, epi, tnb) : SSM_PK(128, 128, epi, tnb)
 #define SSM_ALONE(epi) \

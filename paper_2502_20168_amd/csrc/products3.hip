@@ -6,7 +6,7 @@ namespace ssm {
 
 hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
 {
-    const PkTile t = pk_tile(a, reduction_items<64>(b) + reduction_items<64>(c), !tn_first);
+    const PkTile t = pk_tile(a, reduction_items<64>(b) + reduction_items<64>(c));
 #define SSM_PK(rows, cols, epi, tnb, wpe) launch_pk_variant<rows, cols, 3, epi, tnb, wpe>(a, b, c, tn_first, s)
 #define SSM_SMALL(epi, tnb, wpe) \
     if (t.rows == 32) return t.cols == 32 ? SSM_PK(32, 32, epi, tnb, wpe) : t.cols == 64 ? SSM_PK(32, 64, epi, tnb, wpe) : SSM_PK(32, 128, epi, tnb, wpe)
