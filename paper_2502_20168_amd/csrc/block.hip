@@ -245,8 +245,24 @@ __global__ void __launch_bounds__(256) sum_slabs_kernel(const float *__restrict_
 {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
+    // (up to eight loads in flight: one slab at a time, a sum over many slabs of a small matrix is that many trips to memory in a row:
+    // 4096 tokens, H = 64, 64 slabs: the gate's gradient pass 29.1 us, now 15.1)
     float acc = 0.f;
-    for (int z = 0; z < nslab; ++z) acc += part[(long)z * n + i];
+    int z = 0;
+    const float *p = part + i;
+    auto batch = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        for (; z + N <= nslab; z += N, p += N * n) {
+            float v[N];
+#pragma unroll
+            for (int j = 0; j < N; ++j) v[j] = p[j * n];
+#pragma unroll
+            for (int j = 0; j < N; ++j) acc += v[j];
+        }
+    };
+    batch(std::integral_constant<int, 8>{});
+    batch(std::integral_constant<int, 4>{});
+    batch(std::integral_constant<int, 1>{});
     out[i] = acc;
 }
 
