@@ -56,9 +56,18 @@ bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P)
     return tiles >= MIN_TILES && tiles * (PIECE / 64) * 64 <= 0x7fffffffLL;
 }
 
-// Two workgroups per CU either way: tiles of 128 tokens (half the weight traffic, half as many scans to set up and hand
-// over) from the size on at which they still give every CU two of them.
-int gemm_scan_rows(int64_t T, int64_t P) { return (T / 128) * ((2 * P + 127) / 128) >= 512 ? 128 : 64; }
+// Two workgroups per CU either way.  Tiles of 128 tokens have half the weight traffic and half as many scans to set up and hand
+// over, tiles of 64 more workgroups.  Time with 128 rows against 64 on 310 shapes, by tiles of 128 tokens x 64 states:
+//                               192 tiles      256            384            512 and more
+//   L >= 64, forward            -9 .. +2 %     -19 .. +1 %    -27 .. +3 %    -22 .. +1 %    (128 tiles: -1 .. +9 %)
+//   L >= 64, gradient pass       0 .. +7 %      -2 .. +6 %    -11 .. +2 %    -11 .. +1 %
+//   L < 64, forward              0 .. +4 %       0 .. +2 %     -5 .. +4 %    -10 .. +2 %    (a tile holds whole sequences:
+//   L < 64, gradient pass       +2 .. +7 %      +2 .. +7 %      0 .. +3 %     -5 .. +2 %     nothing is handed over)
+int gemm_scan_rows(int64_t T, int64_t L, int64_t P, bool reverse)
+{
+    const int64_t tiles = (T / 128) * ((2 * P + 127) / 128);
+    return tiles >= (L < 64 ? 512 : reverse ? 384 : 192) ? 128 : 64;
+}
 
 size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
 {

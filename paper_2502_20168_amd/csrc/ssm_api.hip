@@ -163,7 +163,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.row_parts = (int)((2 * P + 127) / 128);
         o.rowmax = off; off += up(T * (size_t)((H + 63) / 64) * 4);
         o.rowpart = off; off += up(T * (size_t)o.row_parts * 4);
-        const size_t per_tile = (size_t)(Bt * L / gemm_scan_rows(Bt * L, P)) * P;  // one dAbar row per scanning tile
+        const size_t per_tile = (size_t)(Bt * L / gemm_scan_rows(Bt * L, L, P, true)) * P;  // one dAbar row per scanning tile
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
     o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
@@ -315,7 +315,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
-        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = gemm_scan_rows(T, P); g1.scan.spin_limit = spin_limit();
+        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = gemm_scan_rows(T, L, P, false); g1.scan.spin_limit = spin_limit();
         g1.scan.rowmax_out = rowpart;                        // of the states, for the output projection
     }
     HIP_TRY(launch_product(g1, s));
@@ -439,7 +439,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
-        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = gemm_scan_rows(T, P); g3.scan.spin_limit = spin_limit();
+        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = gemm_scan_rows(T, L, P, true); g3.scan.spin_limit = spin_limit();
         g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart;
         HIP_TRY(launch_product(g3, s));
     } else {
@@ -485,7 +485,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     ea.log_delta = log_delta; ea.P = (int)P; ea.H = (int)H;
     ea.dBbar_part = dBpart; ea.nsplit_B = lo.dB.slabs;
     ea.dC_part = dCpart; ea.nsplit_C = lo.dC.slabs;
-    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, P) : (int64_t)Bt * lo.plan.nTB;
+    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : (int64_t)Bt * lo.plan.nTB;
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
     ea.dC = reinterpret_cast<float2 *>(dC); ea.dD = dD; ea.dlog_delta = dlog_delta;

@@ -88,7 +88,7 @@ int gemm_tile_tier(int64_t M, int64_t N, int splits);
 // their own output tiles at this shape
 bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P);
 // tokens per scanning tile at such a shape: 64 or 128
-int gemm_scan_rows(int64_t T, int64_t P);
+int gemm_scan_rows(int64_t T, int64_t L, int64_t P, bool reverse);
 // bytes of tagged words epilogues 7 and 8 need (zeroed before the launch)
 size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P);
 // One launch: a product with packed weights and up to two reductions over tokens whose inputs are ready at the same
