@@ -50,9 +50,8 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
  *   [4] gradient pass: 3 = du, dBbar slabs and dC slabs in one launch; 2 = two launches of two products
  *   [5] 1 when the slab work items take the first slots of the launch of [4] == 3
  *   [6], [7] the same for the launches of C^H dy with dC and of du with dBbar when [4] == 2
- *   [8] always 0 (du is one product)
- *   [9] tile tier of the input projection, [10] of the output projection: how coarse a tile a product of this
- *       size can afford by rounds of workgroups (0: 128x128, 1: 64x128, 2: 64x64)
+ *   [8], [9], [10] tile of the launch of the input projection, of the output projection and of du, as
+ *       1024 x rows + columns
  *   [11] workgroups along time of the scan kernels (1: no look-back; unused when [0] == 1)
  * Returns SSM_ERR_INVALID_ARG / SSM_ERR_UNSUPPORTED for shapes the library does not take.           */
 #define SSM_PLAN_FIELDS 12

@@ -607,11 +607,11 @@ def ssm_block_bwd(Lambda, B, C, D, log_delta, W, u, is_first, x0, x, y, gate, do
 
 SSM_PLAN_FIELDS = 12
 PLAN_FIELD_NAMES = ("scans_in_projections", "planes", "slabs_dC", "slabs_dBbar", "products_per_gradient_launch",
-                    "slabs_first", "dC_first", "dBbar_first", "du_as_two_k_halves", "tier_in", "tier_out", "scan_time_blocks")
+                    "slabs_first", "dC_first", "dBbar_first", "tile_in", "tile_out", "tile_du", "scan_time_blocks")
 
 
 def ssm_plan_describe(Bt: int, L: int, H: int, P: int) -> Dict[str, int]:
-    """What ssm_scan_fwd / ssm_scan_bwd would launch for a shape (host logic only, needs no GPU)."""
+    """What ssm_scan_fwd / ssm_scan_bwd would launch for a shape (host logic only, needs no GPU); the tiles are 1024 x rows + columns."""
     out = (ctypes.c_int32 * SSM_PLAN_FIELDS)()
     fn = lib().ssm_plan_describe
     fn.restype = ctypes.c_int

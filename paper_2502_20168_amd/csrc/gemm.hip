@@ -1,5 +1,5 @@
-// Host side of the projection products: which shapes scan inside them, how many K slabs a reduction gets, and
-// the launch (instantiations in products2.hip / products3.hip).
+// Host side of the projection products: which shapes scan inside them, how many K slabs a reduction gets, the tile
+// of a product, and the launch (instantiations in products2.hip / products3.hip).
 #include "ssm_internal.h"
 #include "../../include/ssm.h"
 
@@ -76,17 +76,27 @@ size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
     return (size_t)tiles * 64 * 2 * sizeof(unsigned long long);
 }
 
-// Tile tier of an M x N product with `splits` K splits, by rounds of workgroups on the 256 CUs: 0 = 128x128 tiles, 1 =
-// 64x128, 2 = 64x64.  Only reported (ssm_plan_describe): how coarse a tile a product of this size can afford.
-int gemm_tile_tier(int64_t M, int64_t N, int splits_in)
+// The tile of a product.
+//   32 rows where 64-row tiles would occupy at most half of the CUs (1024 x 1024 x 512, 128 tiles of 64 x 128: 6.2 us
+//     against 7.7; 4096 x 512 x 1024, 256 tiles: 16.7 against 14.5).  What a workgroup then waits for is its chain of
+//     dependent matrix instructions (a 32 x 128 x 64 tile of three planes: 24 on one accumulator, 0.55 us), so fewer columns,
+//     whose consumers share out k, until there are two workgroups per CU.
+//   128 rows (two planes) where they give every CU two workgroups
+//     (32768 x 512 x 1024: 117 us against 122; 4800 x 1024 x 1024, 304 tiles: 47 against 40), and where the launch with its
+//     reductions then fits two workgroups per CU and with 64 rows does not by far (gradient pass of 4000 tokens, H = P = 512: 110 against
+//     116 us; the gate's, 4096 tokens, H = 1024: 92 against 97, but H = 768, 564 workgroups: 67 against 62).
+PkTile product_tile(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c)
 {
-    const int64_t splits = splits_in < 1 ? 1 : splits_in;
-    const int64_t r0 = (((M + 127) / 128) * ((N + 127) / 128) * splits + 255) / 256;
-    const int64_t r1 = (((M + 63) / 64) * ((N + 127) / 128) * splits + 255) / 256;
-    const int64_t r2 = (((M + 63) / 64) * ((N + 63) / 64) * splits + 255) / 256;
-    const int64_t c0 = 10 * r0, c1 = 10 * r1, c2 = 6 * r2;
-    if (c2 < c0 && c2 < c1) return 2;
-    return c1 <= c0 ? 1 : 0;
+    if (a.epilogue == 7 || a.epilogue == 8) return {a.scan.rows, 128};
+    const auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    int64_t items = 0;
+    for (const GemmArgs *t : {b, c})
+        if (t) items += reduction_items(t->M, t->N, t->splits < 1 ? 1 : t->splits, reduction_tile(a.planes, gemm_small_pair(a.M, a.N)));
+    // (two planes: no 32-row tiles beside reductions, and none where there are always more tiles but in the widest layers)
+    if (tiles(64, 128) <= 128 && (a.planes == 3 || (!b && (a.epilogue == 1 || a.epilogue == 6))))
+        return {32, a.c2_rowmax || tiles(32, 64) + items > 256 ? 128 : tiles(32, 32) + items > 128 ? 64 : 32};
+    if (a.planes != 2) return {64, 128};
+    return {tiles(128, 128) >= 512 || (items > 0 && tiles(64, 128) + items > 576 && tiles(128, 128) + items <= 512) ? 128 : 64, 128};
 }
 
 namespace {

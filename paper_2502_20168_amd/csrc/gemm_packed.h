@@ -853,31 +853,6 @@ __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
     return (uid < g.sc_units && tn < g.ntn) ? (b * g.sc_nt + tmL) * g.ntn + tn : g.ntm * g.ntn;
 }
 
-// The tile of a product.
-//   32 rows where 64-row tiles would occupy at most half of the CUs (1024 x 1024 x 512, 128 tiles of 64 x 128: 6.2 us
-//     against 7.7; 4096 x 512 x 1024, 256 tiles: 16.7 against 14.5).  What a workgroup then waits for is its chain of
-//     dependent matrix instructions (a 32 x 128 x 64 tile of three planes: 24 on one accumulator, 0.55 us), so fewer columns,
-//     whose consumers share out k, until there are two workgroups per CU.
-//   128 rows (two planes) where they give every CU two workgroups
-//     (32768 x 512 x 1024: 117 us against 122; 4800 x 1024 x 1024, 304 tiles: 47 against 40), and where the launch with its
-//     reductions then fits two workgroups per CU and with 64 rows does not by far (gradient pass of 4000 tokens, H = P = 512: 110 against
-//     116 us; the gate's, 4096 tokens, H = 1024: 92 against 97, but H = 768, 564 workgroups: 67 against 62).
-struct PkTile { int rows, cols; };
-inline PkTile pk_tile(const GemmArgs &a, int64_t other_items)
-{
-    const auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    if (tiles(64, 128) <= 128)
-        return {32, a.c2_rowmax || tiles(32, 64) + other_items > 256 ? 128 : tiles(32, 32) + other_items > 128 ? 64 : 32};
-    if (a.planes != 2) return {64, 128};
-    return {tiles(128, 128) >= 512 || (other_items > 0 && tiles(64, 128) + other_items > 576 && tiles(128, 128) + other_items <= 512) ? 128 : 64, 128};
-}
-
-template <int TB>
-int64_t reduction_items(const GemmArgs *t)
-{
-    return t ? (int64_t)((t->M + TB - 1) / TB) * ((t->N + TB - 1) / TB) * (t->splits < 1 ? 1 : t->splits) : 0;
-}
-
 constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, bool scans)
 {
     const size_t st = (size_t)PK_STAGES * NPL * BM * PK_BK * 2 + (size_t)BM * 4;       // stages and scales

@@ -6,8 +6,7 @@ namespace ssm {
 
 hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
 {
-    const int64_t others = reduction_items<128>(b) + reduction_items<128>(c);
-    const PkTile t = a.epilogue >= 7 ? PkTile{a.scan.rows, 128} : pk_tile(a, others);
+    const PkTile t = product_tile(a, b, c);
 #define SSM_PK(rows, cols, epi, tnb) launch_pk_variant<rows, cols, 2, epi, tnb, 4>(a, b, c, tn_first, s)
 #define SSM_TALL(epi, tnb) return t.rows <= 64 ? SSM_PK(64, 128, epi, tnb) : SSM_PK(128, 128, epi, tnb)
 #define SSM_ALONE(epi) \
@@ -16,7 +15,9 @@ hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmA
         SSM_TALL(epi, 0)
     if (!b) {
         switch (a.epilogue) {
-        SSM_ALONE(0); SSM_ALONE(1); SSM_ALONE(3); SSM_ALONE(6);
+        SSM_ALONE(1); SSM_ALONE(6);
+        case 0: SSM_TALL(0, 0);
+        case 3: SSM_TALL(3, 0);
         case 7: SSM_TALL(7, 0);
         case 8: SSM_TALL(8, 0);
         default: return hipErrorInvalidValue;

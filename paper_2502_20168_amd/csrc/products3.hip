@@ -6,7 +6,7 @@ namespace ssm {
 
 hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
 {
-    const PkTile t = pk_tile(a, reduction_items<64>(b) + reduction_items<64>(c));
+    const PkTile t = product_tile(a, b, c);
 #define SSM_PK(rows, cols, epi, tnb, wpe) launch_pk_variant<rows, cols, 3, epi, tnb, wpe>(a, b, c, tn_first, s)
 #define SSM_SMALL(epi, tnb, wpe) \
     if (t.rows == 32) return t.cols == 32 ? SSM_PK(32, 32, epi, tnb, wpe) : t.cols == 64 ? SSM_PK(32, 64, epi, tnb, wpe) : SSM_PK(32, 128, epi, tnb, wpe)
@@ -24,7 +24,7 @@ hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const Gem
     case epi: \
         if (!gemm_small_pair(a.M, a.N)) return SSM_PK(64, 128, epi, 96, 4); \
         SSM_SMALL(epi, 64, 4); \
-        return SSM_PK(64, 128, epi, 64, 4)
+        return hipErrorInvalidValue            /* (a small pair has at most 128 tiles of 64 x 128: 32 rows) */
     switch (a.epilogue) {
     SSM_PAIR(0); SSM_PAIR(1); SSM_PAIR(4);
     default: return hipErrorInvalidValue;

@@ -609,9 +609,17 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     out[4] = fused ? 3 : 2;
     out[5] = fused && lo.dB.first;
     out[6] = !fused && lo.dC.first; out[7] = !fused && lo.dB.first;
-    out[8] = 0;
-    out[9] = fused ? 0 : gemm_tile_tier(T, 2 * P, 1);
-    out[10] = gemm_tile_tier(T, H, 1);
+    // the tiles of the input and the output projection and of du
+    GemmArgs in{}, o{}, du{}, dC{}, dB{};
+    in.planes = o.planes = du.planes = lo.planes;
+    in.M = o.M = du.M = (int)T; in.N = (int)(2 * P); o.N = du.N = (int)H;
+    in.epilogue = fused ? 7 : 0; in.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : 0; o.epilogue = du.epilogue = 1;
+    dC.M = (int)H; dC.N = (int)(2 * P); dC.splits = lo.dC.slabs;
+    dB.M = (int)(2 * P); dB.N = (int)H; dB.splits = lo.dB.slabs;
+    const auto tile = [](PkTile t) { return t.rows * 1024 + t.cols; };
+    out[8] = tile(product_tile(in, nullptr, nullptr));
+    out[9] = tile(product_tile(o, nullptr, nullptr));
+    out[10] = tile(product_tile(du, &dB, fused ? &dC : nullptr));
     out[11] = lo.plan.nTB;
     return SSM_OK;
 }

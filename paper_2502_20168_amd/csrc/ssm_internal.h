@@ -82,8 +82,6 @@ struct GemmArgs {
 // -13 % at H = 1024, even at H = 512; +2 % at 1024 tokens, H = 256, where the passes cost more than the shorter K
 // loops save)
 inline bool gate_two_planes_shape(int64_t T, int64_t H) { return H % 64 == 0 && H >= 512 && ((T + 63) / 64) * ((H + 127) / 128) >= 200; }
-// tile tier of an M x N product by rounds of workgroups (reported by ssm_plan_describe): 0 = 128x128x32 tiles, 1 = 64x128x32, 2 = 64x64x64
-int gemm_tile_tier(int64_t M, int64_t N, int splits);
 // the input projection (epilogue 7) and C^H dy (epilogue 8, the reverse scan of the gradient pass) scan
 // their own output tiles at this shape
 bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P);
@@ -98,6 +96,10 @@ inline hipError_t launch_product(const GemmArgs &a, hipStream_t s) { return laun
 // the instantiations with two and three planes
 hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
 hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);
+// the tile of the product of a launch (arguments as for launch_products; of a, M, N, planes, epilogue, scan.rows and
+// c2_rowmax count, of the reductions M, N and splits)
+struct PkTile { int rows, cols; };
+PkTile product_tile(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c);
 // a product over T tokens with N columns has so few tiles that the reduction in its launch runs on 64x64 tiles
 bool gemm_small_pair(int64_t T, int64_t N);
 // Tiles of the reductions of a launch: beside small products, beside other products on three planes, on two planes.

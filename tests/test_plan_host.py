@@ -1,5 +1,5 @@
 """Host logic that decides what a call launches (no GPU needed): which shapes scan inside the projections,
-how many planes, tile tiers, K slabs of the reductions and which work items go first.  The decisions are
+how many planes, the tiles, K slabs of the reductions and which work items go first.  The decisions are
 read back through ssm_plan_describe (include/ssm_measure.h); the expectations are the rules the design
 states, evaluated here independently in Python."""
 from fractions import Fraction
@@ -10,6 +10,17 @@ from paper_2502_20168_amd import binding as ssm
 from paper_2502_20168_amd import workloads as wl
 
 
+TILES = ("tile_in", "tile_out", "tile_du")
+
+
+def _tile(plan, name):
+    return divmod(plan[name], 1024)
+
+
+def _ceil(x, y):
+    return -(-x // y)
+
+
 def test_benchmark_configurations_take_the_paths_the_design_states():
     plans = [ssm.ssm_plan_describe(w.Bt, w.L, w.H, w.P) for w in wl.CONFIGS]
     assert [p["scans_in_projections"] for p in plans] == [0, 0, 1, 1, 1]
@@ -17,32 +28,40 @@ def test_benchmark_configurations_take_the_paths_the_design_states():
     assert [p["products_per_gradient_launch"] for p in plans] == [2, 2, 3, 3, 3]
     # the benchmark shape: four slabs per reduction, in front of du
     assert plans[2]["slabs_dC"] == 4 and plans[2]["slabs_dBbar"] == 4 and plans[2]["slabs_first"] == 1
-    assert plans[2]["tier_out"] == 1 and plans[2]["tier_in"] == 0
+    assert [_tile(plans[2], k) for k in TILES] == [(128, 128), (64, 128), (64, 128)]
     # 1024 x 16 tokens: the same
     assert plans[4]["slabs_dC"] == 4 and plans[4]["slabs_first"] == 1
-    # the small configurations run everything on 64x64x64 tiles
-    assert plans[0]["tier_in"] == 2 and plans[0]["tier_out"] == 2 and plans[1]["tier_in"] == 2
+    # the small configurations run everything on tiles of 32 rows
+    assert all(_tile(p, k)[0] == 32 for p in plans[:2] for k in TILES)
 
 
-def _tier(M, N):
-    r = lambda bm, bn: -(-(-(-M // bm) * -(-N // bn)) // 256)
-    c0, c1, c2 = 10 * r(128, 128), 10 * r(64, 128), 6 * r(64, 64)
-    if c2 < c0 and c2 < c1:
-        return 2
-    return 1 if c1 <= c0 else 0
+def _expected_tile(T, N, planes, items=0):
+    """Rows and columns of the tile of a T x N product without a scan beside `items` work items of reductions."""
+    tiles = lambda rows, cols: _ceil(T, rows) * _ceil(N, cols)
+    if tiles(64, 128) <= 128 and (planes == 3 or items == 0):
+        return 32, 128 if tiles(32, 64) + items > 256 else 64 if tiles(32, 32) + items > 128 else 32
+    fits = items > 0 and tiles(64, 128) + items > 576 and tiles(128, 128) + items <= 512
+    return 128 if planes == 2 and (tiles(128, 128) >= 512 or fits) else 64, 128
 
 
 @pytest.mark.parametrize("Bt,L,H,P", [(30, 100, 512, 512), (64, 100, 512, 512), (18, 100, 1024, 512), (8, 100, 256, 256),
-                                      (16, 1000, 256, 256), (5, 77, 96, 40), (100, 100, 256, 128)])
-def test_tile_tier_is_rounds_of_workgroups_times_time_per_k_step(Bt, L, H, P):
+                                      (16, 1000, 256, 256), (5, 77, 96, 40), (100, 100, 256, 128), (40, 100, 512, 512), (1, 3, 2, 1),
+                                      (16, 256, 512, 512), (24, 128, 1024, 512), (64, 128, 64, 256), (128, 256, 512, 512), (256, 16, 96, 512)])
+def test_reported_tiles_are_those_of_the_launches(Bt, L, H, P):
+    T = Bt * L
     p = ssm.ssm_plan_describe(Bt, L, H, P)
-    assert p["scans_in_projections"] == 0
-    assert p["tier_in"] == _tier(Bt * L, 2 * P) and p["tier_out"] == _tier(Bt * L, H)
-
-
-def test_192_tiles_of_128_take_one_round_of_large_tiles():
-    # 3000 tokens x 1024 columns: 192 tiles of 128x128 (one round) against 376 of 64x128 (two rounds)
-    assert ssm.ssm_plan_describe(30, 100, 512, 512)["tier_in"] == 0
+    red = lambda M, N, s, t: _ceil(M, t[0]) * _ceil(N, t[1]) * s
+    small = _ceil(T, 128) * _ceil(H, 128) <= 64
+    t = (128, 128) if p["planes"] == 2 else (64, 64) if small else (128, 64)
+    items = red(2 * P, H, p["slabs_dBbar"], t)
+    if p["scans_in_projections"]:
+        items += red(H, 2 * P, p["slabs_dC"], t)
+        rows = 128 if T // 128 * _ceil(2 * P, 128) >= (192 if L >= 64 else 512) else 64
+        assert _tile(p, "tile_in") == (rows, 128)
+    elif p["planes"] == 3:
+        assert _tile(p, "tile_in") == _expected_tile(T, 2 * P, 3)
+    assert _tile(p, "tile_out") == _expected_tile(T, H, p["planes"])
+    assert _tile(p, "tile_du") == _expected_tile(T, H, p["planes"], items)
 
 
 COUNTS = (1, 2, 3, 4, 5, 8, 12, 16, 24, 32, 40, 48, 56, 64)
@@ -53,10 +72,6 @@ def _slabs(T, tiles, small):
     want, rows = (128, 64) if small else (224, 192)
     allowed = [s for s in COUNTS if s == 1 or T // s >= rows]
     return min(allowed, key=lambda s: (max(Fraction(tiles * s, want), Fraction(want, tiles * s)), s))
-
-
-def _ceil(x, y):
-    return -(-x // y)
 
 
 @pytest.mark.parametrize("Bt,L,H,P", [(16, 256, 512, 512), (4, 4096, 256, 256), (1024, 16, 512, 512), (32, 128, 1024, 512),
@@ -97,7 +112,7 @@ def test_every_plan_is_bounded_and_repeatable():
         assert a == b
         for k in ("slabs_dC", "slabs_dBbar"):
             assert 1 <= a[k] <= 64 and (a[k] == 1 or -(-Bt * L // a[k]) >= 64)       # a slab keeps at least one K step of 64
-        assert a["planes"] in (2, 3) and a["tier_in"] in (0, 1, 2) and a["tier_out"] in (0, 1, 2)
+        assert a["planes"] in (2, 3) and all(_tile(a, k) in ((32, 32), (32, 64), (32, 128), (64, 128), (128, 128)) for k in TILES)
         assert ssm.ssm_workspace_bytes(Bt, L, H, P, True) > 0 and ssm.ssm_workspace_bytes(Bt, L, H, P, False) > 0
 
 

@@ -40,6 +40,13 @@ def test_products(shape, resets):
     check_workload(wl.custom("products", Bt, L, H, P, p_reset=resets, force_first=bool(resets), with_x0=True, seed=11), backward=True)
 
 
+def test_few_tokens_of_the_widest_layers():
+    """Two planes without a scan in the tile, at fewer tokens than a tile has rows: only layers this wide get there."""
+    p = ssm.ssm_plan_describe(3, 11, 8200, 4100)
+    assert p["planes"] == 2 and p["scans_in_projections"] == 0 and p["tile_in"] == 1024 * 64 + 128
+    check_workload(wl.custom("wide", 3, 11, 8200, 4100, p_reset=0.05, with_x0=True, seed=13), backward=False)
+
+
 def test_states_do_not_depend_on_the_tile_of_the_launch():
     """6 x 640 tokens scan in 64-row tiles, 40 x 640 in 128-row ones: the same sequences have the same states to the last bit."""
     import torch
