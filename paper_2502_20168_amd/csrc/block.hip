@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(256) gelu_kernel(const float4 *__restrict__ u,
                                                    const float *__restrict__ ut, float *__restrict__ x1t, long n, PackSrc src, PackJob w)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
-    if ((int)blockIdx.x < w.nblocks) { pack_block<PACK_WN>(src, w, blockIdx.x, lds); return; }
+    if ((int)blockIdx.x < w.nblocks) { pack_block<PACK_WN, 3>(src, w, blockIdx.x, lds); return; }
     const long i = (long)(blockIdx.x - w.nblocks) * 256 + threadIdx.x;
     if (i < n4) {
         const float4 a = u[i];
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(256) gate_bwd_prep_kernel(const float *__restr
                                                             float *__restrict__ gd, long n, PackSrc src, PackJob w)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
-    if ((int)blockIdx.x < w.nblocks) { pack_block<PACK_WT>(src, w, blockIdx.x, lds); return; }
+    if ((int)blockIdx.x < w.nblocks) { pack_block<PACK_WT, 3>(src, w, blockIdx.x, lds); return; }
     const long i0 = ((long)(blockIdx.x - w.nblocks) * 256 + threadIdx.x) * 4;
     if (i0 + 4 <= n) {
         const float4 a = *reinterpret_cast<const float4 *>(u + i0);
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) gelu_max_kernel(const float4 *__restrict_
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
     if ((int)blockIdx.x < w.nblocks) {                   // (first in the grid: their chains of loads start at once)
-        pack_block<PACK_WN>(src, w, blockIdx.x, lds);
+        pack_block<PACK_WN, 2>(src, w, blockIdx.x, lds);
         return;
     }
     const long i = (long)(blockIdx.x - w.nblocks) * 256 + threadIdx.x;
@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(256) gate_bwd_prep_max_kernel(const float *__r
     __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
     unsigned *red = reinterpret_cast<unsigned *>(lds);
     if ((int)blockIdx.x < w.nblocks) {
-        pack_block<PACK_WT>(src, w, blockIdx.x, lds);
+        pack_block<PACK_WT, 2>(src, w, blockIdx.x, lds);
         return;
     }
     const int b = (int)blockIdx.x - w.nblocks, main_blocks = (int)gridDim.x - w.nblocks;
@@ -310,7 +310,7 @@ PackJob glu_pack(char *ws, const GluLayout &lo, int64_t H, int kind)
     PackJob j{};
     j.kind = kind; j.N = j.K = (int)H; j.planes = lo.planes;
     j.frag = ws + lo.wfrag; j.exp = reinterpret_cast<int *>(ws + lo.wexp);
-    j.nblocks = pack_blocks(kind, (int)H);
+    pack_place(j, 0);
     return j;
 }
 PackSrc glu_source(const float *W, int64_t H)

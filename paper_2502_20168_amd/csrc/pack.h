@@ -45,12 +45,23 @@ __device__ __forceinline__ Zoh zoh_discretize(float2 Lambda, float log_delta)
     return o;
 }
 
-// (Abar, g) rounded, for the packing jobs.  Not inlined: inside their loops its many constants and temporaries took
-// the registers of the values in flight, and the transposing job of Bbar spilled (13 us instead of 7).
-__device__ __attribute__((noinline)) float4 zoh_rounded(float2 Lambda, float log_delta)
+// (Abar, g) rounded, for the packing jobs.  Two planes: not inlined, because inside their loops its many constants and temporaries
+// took the registers of the values in flight, and the transposing job of Bbar spilled (13 us instead of 7).  Three planes: inlined, so
+// that the values are on their way meanwhile (a call waits for all loads first).
+template <int PLANES>
+__device__ __forceinline__ float4 zoh_rounded(float2 Lambda, float log_delta)
 {
     const Zoh z = zoh_discretize(Lambda, log_delta);
     return make_float4((float)z.lr, (float)z.li, (float)z.gr, (float)z.gi);
+}
+__device__ __attribute__((noinline)) float4 zoh_rounded_call(float2 Lambda, float log_delta) { return zoh_rounded<3>(Lambda, log_delta); }
+template <>
+__device__ __forceinline__ float4 zoh_rounded<2>(float2 Lambda, float log_delta) { return zoh_rounded_call(Lambda, log_delta); }
+
+struct ZohPair { float4 a, b; };
+__device__ __attribute__((noinline)) ZohPair zoh_rounded_pair(float2 La, float da, float2 Lb, float db)
+{
+    return ZohPair{zoh_rounded<3>(La, da), zoh_rounded<3>(Lb, db)};
 }
 
 // What the jobs read.
@@ -62,25 +73,34 @@ constexpr size_t PACK_LDS_BYTES = PACK_ZOH_BATCH * 8 + 4 * 16 * 4;
 // lanes that share a row of chunks, values of n per lane, chunks per thread that stay in registers
 constexpr int pack_lanes(int kind) { return kind == PACK_IN ? 4 : (kind == PACK_WN ? 16 : 8); }
 constexpr int pack_per_lane(int kind) { return (kind == PACK_IN || kind == PACK_GX) ? 2 : 1; }
-constexpr int pack_kept(int kind) { return pack_per_lane(kind) == 2 ? 2 : 4; }
+constexpr int pack_kept(int kind, int planes) { return planes == 3 ? 1 : pack_per_lane(kind) == 2 ? 2 : 4; }
 
-// A workgroup of 256 threads packs pack_lanes * pack_per_lane consecutive n over the whole (padded) K.  A thread owns
-// one n (or the pair re, im of one state) and every (256 / lanes)-th chunk of eight consecutive k: the 16 bytes per
-// plane that one lane of a fragment holds, so stores are whole 128-byte lines.  The job is bound by latency: all loads
-// of a thread are in flight together and stay in registers between the largest magnitude of every n (its scale, two
-// planes) and the split, so that it is one trip to memory (measured at H = P = 512, two trips of dependent chunks
-// instead: prep launches of 11.1 and 17.6 us).  A K longer than that is read twice, round by round.
-template <int KIND>
-__device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, int blk, unsigned char *lds)
+// A workgroup of 256 threads packs pack_lanes * pack_per_lane consecutive n.  A thread owns one n (or the pair re, im of
+// one state) and chunks of eight consecutive k: the 16 bytes per plane that one lane of a fragment holds, so stores are
+// whole 128-byte lines.  Up to H = P = 512 the jobs are bound by latency: an empty launch takes 2 us, the discretisation 1.2 us
+// and a thread's way through one chunk 0.5 us.
+//   Three planes: nothing has to be known about the rest of a row, so a thread has one chunk, and K is shared out over
+//     workgroups.  Prep launch of the gradient pass (before, with four chunks per thread, one workgroup per n and all of K; us):
+//     1024 x (H 128, P 64) 4.9 -> 4.0, 256 tokens x (256, 512) 9.6 -> 6.6, 512 x (512, 512) 10.0 -> 7.0, 256 x (1024, 1024) 14.2 -> 11.9
+//     (41 MB of weights and fragments there).
+//   Two planes: every (256 / lanes)-th chunk of the whole K.  All loads of a thread are in flight together and stay in
+//     registers between the largest magnitude of every n (its scale) and the split, so that it is one trip to memory
+//     (measured at H = P = 512, two trips of dependent chunks instead: prep launches of 11.1 and 17.6 us).
+//     A K longer than that is read twice, round by round.
+template <int KIND, int PLANES>
+__device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, int wg, unsigned char *lds)
 {
-    constexpr int G = pack_lanes(KIND), V = pack_per_lane(KIND), ROWS = 256 / G, KEPT = pack_kept(KIND), RAW = 8 * V;
+    constexpr int G = pack_lanes(KIND), V = pack_per_lane(KIND), ROWS = 256 / G, KEPT = pack_kept(KIND, PLANES), RAW = 8 * V;
+    constexpr bool SHARED_K = PLANES == 3;
+    const int blk = SHARED_K ? wg / j.kparts : wg;
+    const int first = SHARED_K ? (wg - blk * j.kparts) * ROWS : 0;                   // the workgroup's first chunk
     float2 *gz = reinterpret_cast<float2 *>(lds);                                    // [PACK_ZOH_BATCH] g of the states (PACK_DU)
     unsigned *red = reinterpret_cast<unsigned *>(lds + PACK_ZOH_BATCH * 8);          // [4][G * V]
     const int tid = threadIdx.x, nl = tid % G, row = tid / G, lane = tid & 63, wave = tid >> 6;
     const int unit = blk * G + nl;                                                   // state, or n
     const int n0 = unit * V;
     const int nch = (j.K + 63) / 64 * 8;                                             // chunks, padded to whole K tiles
-    const int npad = (j.N + 31) / 32 * 32, planes = j.planes;
+    const int npad = (j.N + 31) / 32 * 32;
     const int usrc = min(unit, j.N / V - 1);                                         // (clamped: the values past N are zeroed)
     const bool whole = j.K % 8 == 0;                                                 // no chunk is cut by the end of K
 
@@ -122,25 +142,51 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
     };
     float2 g = make_float2(0.f, 0.f);
     int batch = -1;
+    // (three planes: the state whose discretisation this thread computes, requested ahead of the values; PACK_DU: of its workgroup's chunks)
+    float2 own_lambda;
+    float own_delta;
+    if constexpr (SHARED_K && (KIND == PACK_IN || KIND == PACK_DU)) {
+        const int p = KIND == PACK_IN ? usrc : min(first * 4 + tid, s.P - 1);
+        own_lambda = s.Lambda[p]; own_delta = s.log_delta[p];
+    }
     // the discretisation behind the values: the thread's own state (PACK_IN), or a batch of states for the whole
     // workgroup (PACK_DU; all threads meet here, the batch index is uniform)
     auto discretize = [&](int b) {
         if constexpr (KIND == PACK_IN) {
             if (batch >= 0) return;
             batch = 0;
-            const float4 z = zoh_rounded(s.Lambda[usrc], s.log_delta[usrc]);
+            const float4 z = SHARED_K ? zoh_rounded<PLANES>(own_lambda, own_delta) : zoh_rounded<PLANES>(s.Lambda[usrc], s.log_delta[usrc]);
             g = make_float2(z.z, z.w);
-            if (row == 0 && s.lam_bar && unit < s.P) s.lam_bar[unit] = make_float2(z.x, z.y);
+            if (row == 0 && first == 0 && s.lam_bar && unit < s.P) s.lam_bar[unit] = make_float2(z.x, z.y);
+        } else if constexpr (KIND == PACK_DU && SHARED_K) {
+            static_assert(!SHARED_K || ROWS * 4 <= 256, "a state per thread");
+            const int p = first * 4 + tid;
+            if (tid < ROWS * 4) {
+                const float4 z = zoh_rounded<PLANES>(own_lambda, own_delta);
+                gz[tid] = make_float2(z.z, z.w);
+                if (blk == 0 && s.lam_bar && p < s.P) s.lam_bar[p] = make_float2(z.x, z.y);
+            }
+            __syncthreads();
         } else if constexpr (KIND == PACK_DU) {
             if (b == batch) return;
             batch = b;
             __syncthreads();
             const int nb = min(PACK_ZOH_BATCH, s.P - b * PACK_ZOH_BATCH);
-            for (int i = tid; i < nb; i += 256) {
-                const int p = b * PACK_ZOH_BATCH + i;
-                const float4 z = zoh_rounded(s.Lambda[p], s.log_delta[p]);
+            auto keep = [&](int i, float4 z) {
                 gz[i] = make_float2(z.z, z.w);
-                if (blk == 0 && s.lam_bar) s.lam_bar[p] = make_float2(z.x, z.y);
+                if (blk == 0 && s.lam_bar) s.lam_bar[b * PACK_ZOH_BATCH + i] = make_float2(z.x, z.y);
+            };
+            const float2 *Lam = s.Lambda + b * PACK_ZOH_BATCH;
+            const float *ld = s.log_delta + b * PACK_ZOH_BATCH;
+            if (nb <= 256) {
+                if (tid < nb) keep(tid, zoh_rounded<PLANES>(Lam[tid], ld[tid]));
+            } else {
+                for (int i = tid; i < nb; i += 512) {        // (two chains of double-precision arithmetic at a time)
+                    const int k = min(i + 256, nb - 1);
+                    const ZohPair z = zoh_rounded_pair(Lam[i], ld[i], Lam[k], ld[k]);
+                    keep(i, z.a);
+                    if (i + 256 < nb) keep(i + 256, z.b);
+                }
             }
             __syncthreads();
         }
@@ -152,7 +198,7 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
             // (read ahead of the selections below: the compiler would move each read into its branch, and wait 32 times)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                q[e] = gz[(4 * c) % PACK_ZOH_BATCH + e];
+                q[e] = gz[SHARED_K ? 4 * (c - first) + e : (4 * c) % PACK_ZOH_BATCH + e];
                 asm volatile("" : "+v"(q[e].x), "+v"(q[e].y));
             }
         }
@@ -209,28 +255,41 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
         for (int i = 0; i < V; ++i) {
             const int n = n0 + i;
             const float4 lo = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]), hi = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
-            uint4 *dst = static_cast<uint4 *>(j.frag) + ((size_t)(n / 32) * nks + c / 2) * (planes * 64) + n % 32 + 32 * (c & 1);
-            const Split4 a = planes == 3 ? split3(lo) : split2_f16(lo, scale[i]), b = planes == 3 ? split3(hi) : split2_f16(hi, scale[i]);
+            uint4 *dst = static_cast<uint4 *>(j.frag) + ((size_t)(n / 32) * nks + c / 2) * (PLANES * 64) + n % 32 + 32 * (c & 1);
+            const Split4 a = split_planes<PLANES>(lo, scale[i]), b = split_planes<PLANES>(hi, scale[i]);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                if (q < planes) {
-                    const uint2 x = __builtin_bit_cast(uint2, a.p[q]), y = __builtin_bit_cast(uint2, b.p[q]);
-                    dst[q * 64] = make_uint4(x.x, x.y, y.x, y.y);
-                }
+            for (int q = 0; q < PLANES; ++q) {
+                const uint2 x = __builtin_bit_cast(uint2, a.p[q]), y = __builtin_bit_cast(uint2, b.p[q]);
+                dst[q * 64] = make_uint4(x.x, x.y, y.x, y.y);
             }
         }
     };
 
-    // rounds of KEPT chunks per thread; with a single round the values stay in registers between the two passes
-    constexpr int ROUND = KEPT * ROWS;
-    static_assert(PACK_ZOH_BATCH % (4 * ROUND) == 0, "a round's states lie in one batch");
-    const bool single = nch <= ROUND;
     float raw[KEPT][RAW];
     auto fetch_round = [&](int c0) {
 #pragma unroll
         for (int t = 0; t < KEPT; ++t) fetch(min(c0 + t * ROWS + row, nch - 1), raw[t]);
     };
-    if (planes == 2) {
+    auto put_round = [&](int c0) {
+#pragma unroll
+        for (int t = 0; t < KEPT; ++t) {
+            const int c = c0 + t * ROWS + row;
+            if (c < nch) {
+                float v[V][8];
+                finish(c, raw[t], v);
+                put(c, v);
+            }
+        }
+    };
+    if constexpr (SHARED_K) {
+        fetch_round(first);
+        discretize(0);
+        put_round(first);
+    } else {
+        // rounds of KEPT chunks per thread; with a single round the values stay in registers between the two passes
+        constexpr int ROUND = KEPT * ROWS;
+        static_assert(PACK_ZOH_BATCH % (4 * ROUND) == 0, "a round's states lie in one batch");
+        const bool single = nch <= ROUND;
         for (int c0 = 0; c0 < nch; c0 += ROUND) {
             fetch_round(c0);
             discretize(c0 * 4 / PACK_ZOH_BATCH);
@@ -242,31 +301,24 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
             }
         }
         reduce_max();
-    }
-    for (int c0 = 0; c0 < nch; c0 += ROUND) {
-        if (planes != 2 || !single) fetch_round(c0);
-        discretize(c0 * 4 / PACK_ZOH_BATCH);
-#pragma unroll
-        for (int t = 0; t < KEPT; ++t) {
-            const int c = c0 + t * ROWS + row;
-            if (c < nch) {
-                float v[V][8];
-                finish(c, raw[t], v);
-                put(c, v);
-            }
+        for (int c0 = 0; c0 < nch; c0 += ROUND) {
+            if (!single) fetch_round(c0);
+            discretize(c0 * 4 / PACK_ZOH_BATCH);
+            put_round(c0);
         }
     }
 }
 
-__device__ __forceinline__ void pack_dispatch(const PackSrc &s, const PackJob &j, int blk, unsigned char *lds)
+template <int PLANES>
+__device__ __forceinline__ void pack_dispatch(const PackSrc &s, const PackJob &j, int wg, unsigned char *lds)
 {
     switch (j.kind) {
-    case PACK_IN: pack_block<PACK_IN>(s, j, blk, lds); break;
-    case PACK_OUT: pack_block<PACK_OUT>(s, j, blk, lds); break;
-    case PACK_GX: pack_block<PACK_GX>(s, j, blk, lds); break;
-    case PACK_DU: pack_block<PACK_DU>(s, j, blk, lds); break;
-    case PACK_WN: pack_block<PACK_WN>(s, j, blk, lds); break;
-    default: pack_block<PACK_WT>(s, j, blk, lds); break;
+    case PACK_IN: pack_block<PACK_IN, PLANES>(s, j, wg, lds); break;
+    case PACK_OUT: pack_block<PACK_OUT, PLANES>(s, j, wg, lds); break;
+    case PACK_GX: pack_block<PACK_GX, PLANES>(s, j, wg, lds); break;
+    case PACK_DU: pack_block<PACK_DU, PLANES>(s, j, wg, lds); break;
+    case PACK_WN: pack_block<PACK_WN, PLANES>(s, j, wg, lds); break;
+    default: pack_block<PACK_WT, PLANES>(s, j, wg, lds); break;
     }
 }
 

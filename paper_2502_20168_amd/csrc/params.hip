@@ -238,16 +238,20 @@ __global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
     const int blk = blockIdx.x, tid = threadIdx.x;
-    if (blk == 0 && tid == 0 && a.hdr) {
-        a.hdr->err = 0; a.hdr->magic = 0x53534d31u;
-    }
     const PackSrc src{a.Lambda, a.B, a.C, a.log_delta, a.W, a.P, a.H, a.lam_bar};
-#pragma unroll
-    for (int i = 0; i < PREP_MAX_PACKS; ++i) {
-        if (i < a.npack && blk < a.pack[i].block0 + a.pack[i].nblocks) {
-            pack_dispatch(src, a.pack[i], blk - a.pack[i].block0, lds);
-            return;
-        }
+    static_assert(PREP_MAX_PACKS == 4, "one load for all");
+    const int e0 = a.pack_end[0], e1 = a.pack_end[1], e2 = a.pack_end[2], e3 = a.pack_end[3];
+    WsHeader *hdr = a.hdr;
+    // (what decides the workgroup's job and what every job reads are requested together, and the job itself next: left to
+    // where they are used, the arguments come in five or six trips one behind the other, 1 us of the 3 that a small launch takes)
+    asm volatile("" ::"s"(src.Lambda), "s"(src.B), "s"(src.C), "s"(src.log_delta), "s"(src.W), "s"(src.P), "s"(src.H), "s"(src.lam_bar), "s"(e0),
+                 "s"(e1), "s"(e2), "s"(e3), "s"(hdr));
+    if (blk < e3) {
+        const PackJob job = a.pack[(blk >= e0) + (blk >= e1) + (blk >= e2)];
+        if (blk == 0 && tid == 0 && hdr) { hdr->err = 0; hdr->magic = 0x53534d31u; }
+        if (job.planes == 3) pack_dispatch<3>(src, job, blk - job.block0, lds);
+        else pack_dispatch<2>(src, job, blk - job.block0, lds);
+        return;
     }
     if (a.cd.partial && blk < a.cd_block0 + a.cd_colblocks * a.cd.nslab) {
         const int cb = blk - a.cd_block0;
@@ -272,23 +276,26 @@ __global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
     }
 }
 
-int pack_blocks(int kind, int N)
+void pack_place(PackJob &j, int block0)
 {
-    const int per = pack_lanes(kind) * pack_per_lane(kind), npad = (N + 31) / 32 * 32;
-    return (npad + per - 1) / per;
+    const int per = pack_lanes(j.kind) * pack_per_lane(j.kind), npad = (j.N + 31) / 32 * 32;
+    const int chunks = (j.K + 63) / 64 * 8, rows = 256 / pack_lanes(j.kind);
+    j.kparts = j.planes == 3 ? (chunks + rows - 1) / rows : 1;
+    j.block0 = block0; j.nblocks = (npad + per - 1) / per * j.kparts;
 }
 
 hipError_t launch_prep(const PrepArgs &a_in, hipStream_t s)
 {
     PrepArgs a = a_in;
     long blocks = 0;
-    if (a.npack < 0 || a.npack > PREP_MAX_PACKS) return hipErrorInvalidValue;
+    if (a.npack < 1 || a.npack > PREP_MAX_PACKS) return hipErrorInvalidValue;
     for (int i = 0; i < a.npack; ++i) {
         PackJob &j = a.pack[i];
         if (!j.frag || (j.planes != 3 && (j.planes != 2 || !j.exp))) return hipErrorInvalidValue;
-        j.block0 = (int)blocks; j.nblocks = pack_blocks(j.kind, j.N);
+        pack_place(j, (int)blocks);
         blocks += j.nblocks;
     }
+    for (int i = 0; i < PREP_MAX_PACKS; ++i) a.pack_end[i] = i < a.npack ? a.pack[i].block0 + a.pack[i].nblocks : (int)blocks;
     a.cd_block0 = (int)blocks; a.cd_colblocks = 0;
     if (a.cd.partial) {
         a.cd_colblocks = (a.cd.H + 63) / 64;

@@ -194,16 +194,17 @@ int coldot_slabs(int64_t T);
 //   PACK_WN   n = j, k = i:     W[i, j]                   (gate)
 //   PACK_WT   n = i, k = j:     W[i, j]                   (adjoint of the gate)
 enum PackKind { PACK_IN, PACK_OUT, PACK_GX, PACK_DU, PACK_WN, PACK_WT };
-struct PackJob { int kind, N, K, planes; void *frag; int *exp; int block0, nblocks; };   // the last two set by the launch
-int pack_blocks(int kind, int N);            // workgroups of 256 threads that a job takes
+struct PackJob { int kind, N, K, planes; void *frag; int *exp; int block0, nblocks, kparts; };   // the last three set by the launch
+void pack_place(PackJob &j, int block0);     // workgroups of 256 threads that a job takes, from block0 on; three planes: parts that K is shared out in
 
 constexpr int PREP_MAX_PACKS = 4;
 struct PrepArgs {
     const float2 *Lambda; const float2 *B; const float2 *C; const float *log_delta; const float *W;
     int P, H;
     float2 *lam_bar;         // [P], written by the PACK_IN or the PACK_DU job
-    PackJob pack[PREP_MAX_PACKS]; int npack;
     WsHeader *hdr;           // cleared when non-null
+    int pack_end[PREP_MAX_PACKS]; int npack;     // first workgroup behind every job (set by launch_prep); jobs: at least one
+    PackJob pack[PREP_MAX_PACKS];
     ColDotArgs cd;           // cd.partial non-null: the launch also computes the column-dot slabs
     int cd_block0, cd_colblocks;                 // set by launch_prep
     struct Zero { uint4 *p; size_t n16; int block0, nblocks; } zero[2];   // regions to clear in the same launch (block ranges set by it)
