@@ -81,6 +81,8 @@ size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
 //     against 7.7; 4096 x 512 x 1024, 256 tiles: 16.7 against 14.5).  What a workgroup then waits for is its chain of
 //     dependent matrix instructions (a 32 x 128 x 64 tile of three planes: 24 on one accumulator, 0.55 us), so fewer columns,
 //     whose consumers share out k, until there are two workgroups per CU.
+//   32 x 64 at any number of rows (three planes) where the result has at most 64 columns, half of a wider tile (16000 tokens, H = 64, P = 256: forward
+//     pass 43.6 us against 45.1; the gate's at 16384 tokens, H = 64: 11.7 against 12.4; at 96 columns, and with two planes, the wider tile is faster).
 //   128 rows (two planes) where they give every CU two workgroups
 //     (32768 x 512 x 1024: 117 us against 122; 4800 x 1024 x 1024, 304 tiles: 47 against 40), and where the launch with its
 //     reductions then fits two workgroups per CU and with 64 rows does not by far (gradient pass of 4000 tokens, H = P = 512: 110 against
@@ -92,6 +94,7 @@ PkTile product_tile(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c)
     int64_t items = 0;
     for (const GemmArgs *t : {b, c})
         if (t) items += reduction_items(t->M, t->N, t->splits < 1 ? 1 : t->splits, reduction_tile(a.planes, gemm_small_pair(a.M, a.N)));
+    if (a.planes == 3 && a.N <= 64 && tiles(64, 128) > 128 && !b && !a.c2_rowmax) return {32, 64};
     // (two planes: no 32-row tiles beside reductions, and none where there are always more tiles but in the widest layers)
     if (tiles(64, 128) <= 128 && (a.planes == 3 || (!b && (a.epilogue == 1 || a.epilogue == 6))))
         return {32, a.c2_rowmax || tiles(32, 64) + items > 256 ? 128 : tiles(32, 32) + items > 128 ? 64 : 32};

@@ -38,6 +38,8 @@ def test_benchmark_configurations_take_the_paths_the_design_states():
 def _expected_tile(T, N, planes, items=0):
     """Rows and columns of the tile of a T x N product without a scan beside `items` work items of reductions."""
     tiles = lambda rows, cols: _ceil(T, rows) * _ceil(N, cols)
+    if planes == 3 and N <= 64 and tiles(64, 128) > 128 and items == 0:
+        return 32, 64
     if tiles(64, 128) <= 128 and (planes == 3 or items == 0):
         return 32, 128 if tiles(32, 64) + items > 256 else 64 if tiles(32, 32) + items > 128 else 32
     fits = items > 0 and tiles(64, 128) + items > 576 and tiles(128, 128) + items <= 512
@@ -46,7 +48,7 @@ def _expected_tile(T, N, planes, items=0):
 
 @pytest.mark.parametrize("Bt,L,H,P", [(30, 100, 512, 512), (64, 100, 512, 512), (18, 100, 1024, 512), (8, 100, 256, 256),
                                       (16, 1000, 256, 256), (5, 77, 96, 40), (100, 100, 256, 128), (40, 100, 512, 512), (1, 3, 2, 1),
-                                      (16, 256, 512, 512), (24, 128, 1024, 512), (64, 128, 64, 256), (128, 256, 512, 512), (256, 16, 96, 512)])
+                                      (16, 256, 512, 512), (24, 128, 1024, 512), (64, 128, 64, 256), (128, 256, 512, 512), (256, 16, 96, 512), (300, 100, 40, 70)])
 def test_reported_tiles_are_those_of_the_launches(Bt, L, H, P):
     T = Bt * L
     p = ssm.ssm_plan_describe(Bt, L, H, P)

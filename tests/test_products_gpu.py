@@ -17,6 +17,7 @@ SHAPES = [
     (16, 64, 256, 256),    # k shared between consumers, reductions beside small products
     (1, 24, 20, 1030),     # more states than a packing job's batch and register rounds
     (1, 24, 1100, 12),     # the same for H
+    (90, 100, 40, 70),     # 32 x 64 tiles at many rows: at most 64 columns
     (20, 300, 500, 250),   # 64-row tiles of three planes, ragged
     (24, 200, 1024, 512),  # two planes, separate scans, 128-row tiles beside the reductions
     (8, 128, 96, 512),     # 64-row scanning tiles, chain of two
