@@ -152,14 +152,19 @@ __device__ __forceinline__ void absmax_rows_batch(const PrepArgs::Pass &q, size_
                 const int i = lane + 64 * h;
                 const bool ok = row0 + r < rows && i < q.rowlen / 4;
                 const float4 *x4 = reinterpret_cast<const float4 *>(q.x + (ok ? row0 + r : 0) * (size_t)q.rowlen);
-                const float4 t = x4[ok ? i : 0];
-                a[r][h] = ok ? t : make_float4(0.f, 0.f, 0.f, 0.f);
+                a[r][h] = x4[ok ? i : 0];
             }
+        // (held here, or the compiler moves every load into the branch of its selection below, where it is waited for before the next:
+        // 16384 rows of 512 values took 11.2 us in the prep launch, now 9.7)
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(a[r][h].x), "+v"(a[r][h].y), "+v"(a[r][h].z), "+v"(a[r][h].w));
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                m[r] = fmaxf(m[r], fmaxf(fmaxf(fabsf(a[r][h].x), fabsf(a[r][h].y)), fmaxf(fabsf(a[r][h].z), fabsf(a[r][h].w))));
+                if (lane + 64 * h < q.rowlen / 4) m[r] = fmaxf(m[r], fmaxf(fmaxf(fabsf(a[r][h].x), fabsf(a[r][h].y)), fmaxf(fabsf(a[r][h].z), fabsf(a[r][h].w))));
     } else {
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
