@@ -586,9 +586,8 @@ def ssm_block_bwd(Lambda, B, C, D, log_delta, W, u, is_first, x0, x, y, gate, do
     if r is not None:
         return _done(r, "ssm_block_bwd")
     torch = _torch()
-    Bt, L, H = u.shape
-    P = Lambda.shape[0]
-    for name, t in (("u", u), ("y", y), ("gate", gate), ("dout", dout)):
+    Bt, L, H, P = _check_inputs(Lambda, B, C, D, log_delta, u, is_first, x0)
+    for name, t in (("y", y), ("gate", gate), ("dout", dout)):
         _chk(t, torch.float32, (Bt, L, H), name)
     _chk(x, torch.complex64, (Bt, L, P), "x")
     _chk(W, torch.float32, (H, H), "W")

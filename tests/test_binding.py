@@ -17,15 +17,118 @@ def test_arguments_on_the_cpu_are_refused_by_name():
         ssm.ssm_scan_fwd(**_small("cpu"))
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("name,change", [("B", lambda t: t[:, :2]), ("D", lambda t: t.double()), ("u", lambda t: t.transpose(0, 1)),
-                                         ("log_delta", lambda t: t.cpu())])
-def test_a_wrong_argument_is_named(name, change):
+def _calls(device, run=True):
+    """One call of every entry point that has a native half: name -> (function, keyword arguments, names of the tensors it checks).
+    run: with the plan and the saved activations of a call on the GPU."""
+    import torch
     from paper_2502_20168_amd import binding as ssm
-    a = _small("cuda")
-    a[name] = change(a[name])
-    with pytest.raises((ValueError, ssm.SsmError)):
-        ssm.ssm_scan_fwd(**a)
+    torch.manual_seed(3)
+    a = _small(device)
+    u = a["u"]
+    Bt, L, H, P, T = u.shape[0], u.shape[1], u.shape[2], a["Lambda"].shape[0], 6
+    c = lambda *s: torch.randn(s, dtype=torch.complex64, device=device)
+    f = lambda *s: torch.randn(s, device=device)
+    flags = lambda *s: (torch.rand(s, device=device) < 0.3).to(torch.uint8)
+    a["is_first"], a["x0"] = flags(Bt, L), c(Bt, P)
+    A = 0.6 * c(P)
+    W = f(H, H)
+    layer = tuple(a)
+    fwd, step = {}, {"is_first": flags(Bt), "P": P, "plan": torch.empty(1 << 16, dtype=torch.uint8, device=device)}
+    if run:
+        fwd = ssm.ssm_block_fwd(**a, W=W)
+        step["plan"] = ssm.ssm_step_prepare(a["Lambda"], a["B"], a["C"], a["log_delta"])
+    saved = {"x": fwd.get("x", c(Bt, L, P)), "y": fwd.get("y", f(Bt, L, H)), "gate": fwd.get("gate", f(Bt, L, H))}
+    ret = {"reward": f(T, Bt), "cont": torch.rand(T, Bt, device=device), "value": f(T, Bt)}
+    return {
+        "scan_fwd": (ssm.ssm_scan_fwd, a, layer),
+        "scan_bwd": (ssm.ssm_scan_bwd, {**a, "x": saved["x"], "dy": f(Bt, L, H)}, layer + ("x", "dy")),
+        "block_fwd": (ssm.ssm_block_fwd, {**a, "W": W}, layer + ("W",)),
+        "block_bwd": (ssm.ssm_block_bwd, {**a, "W": W, **saved, "dout": f(Bt, L, H)}, layer + ("W", "x", "y", "gate", "dout")),
+        "step_prepare": (ssm.ssm_step_prepare, {k: a[k] for k in ("Lambda", "B", "C", "log_delta")}, ("Lambda", "B", "C", "log_delta")),
+        "step": (ssm.ssm_step, {**step, "D": a["D"], "u": f(Bt, H), "x_prev": c(Bt, P)}, ("D", "u", "x_prev", "is_first")),
+        "step_bwd": (ssm.ssm_step_bwd, {**step, "D": a["D"], "dy": f(Bt, H), "dx": c(Bt, P)}, ("D", "dy", "dx", "is_first")),
+        "lambda_return": (ssm.ssm_lambda_return, {**ret, "gamma": 0.9, "lam": 0.8}, tuple(ret)),
+        "lambda_return_bwd": (ssm.ssm_lambda_return_bwd, {"cont": ret["cont"], "value": ret["value"], "ret": f(T, Bt), "dret": f(T, Bt), "gamma": 0.9,
+                                                          "lam": 0.8}, ("cont", "value", "ret", "dret")),
+        "scan_states": (ssm.ssm_scan_states, {"A_bar": A, "v": c(Bt, L, P), "is_first": a["is_first"], "x0": a["x0"]},
+                        ("A_bar", "v", "is_first", "x0")),
+        "scan_states_reverse": (ssm.ssm_scan_states_reverse, {"A_bar": A, "gx": c(Bt, L, P), "x": c(Bt, L, P), "is_first": a["is_first"],
+                                                              "x0": a["x0"]}, ("A_bar", "gx", "x", "is_first", "x0")),
+        "half_glu_fwd": (ssm.ssm_half_glu_fwd, {"u": f(T, H), "W": W}, ("u", "W")),
+        "half_glu_bwd": (ssm.ssm_half_glu_bwd, {"u": f(T, H), "W": W, "gate": torch.rand(T, H, device=device), "dy": f(T, H)},
+                         ("u", "W", "gate", "dy")),
+    }
+
+
+CALLS = ("scan_fwd", "scan_bwd", "block_fwd", "block_bwd", "step_prepare", "step", "step_bwd", "lambda_return", "lambda_return_bwd",
+         "scan_states", "scan_states_reverse", "half_glu_fwd", "half_glu_bwd")
+
+
+def test_every_native_entry_point_is_among_the_calls():
+    from paper_2502_20168_amd import _ssmbind
+    assert sorted(CALLS) == sorted(n for n in dir(_ssmbind) if not n.startswith("_")) == sorted(_calls("cpu", run=False))
+
+
+def _flat(r):
+    import torch
+    return [r] if torch.is_tensor(r) or r is None else [t for k in (sorted(r) if isinstance(r, dict) else range(len(r))) for t in _flat(r[k])]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", CALLS)
+def test_native_and_general_path_return_the_same(call, monkeypatch):
+    import torch
+    from paper_2502_20168_amd import binding as ssm
+    fn, kw, _ = _calls("cuda")[call]
+    if call == "step_prepare":                                   # (the plan has bytes that nothing writes: compared by a step)
+        prepare, u = fn, torch.randn(5, kw["B"].shape[1], device="cuda")
+        fn = lambda **k: ssm.ssm_step(prepare(**k), torch.ones(u.shape[1], device="cuda"), u, P=k["Lambda"].shape[0])
+    copy = lambda: {k: v.clone() if torch.is_tensor(v) else v for k, v in kw.items()}        # (scans work in place)
+    made = []
+    native = ssm._bind()
+
+    class Watched:
+        def __getattr__(self, name):
+            return lambda *a: made.append(getattr(native, name)(*a)) or made[-1]
+
+    monkeypatch.setattr(ssm, "_native", Watched())
+    got = _flat(fn(**copy()))
+    assert made and all(m is not None and not isinstance(m, int) for m in made)              # the native half made the call
+    monkeypatch.setattr(ssm, "_native", ssm._GeneralPathOnly())
+    ref = _flat(fn(**copy()))
+    torch.cuda.synchronize()
+    assert len(got) == len(ref)
+    for g, r in zip(got, ref):
+        assert (g is None) == (r is None)
+        if g is not None:
+            assert g.dtype == r.dtype and g.shape == r.shape and torch.equal(torch.view_as_real(g) if g.is_complex() else g,
+                                                                             torch.view_as_real(r) if r.is_complex() else r)
+
+
+WRONG = {"shape": lambda t: t[..., :-1].contiguous(), "stride": lambda t: t.repeat_interleave(2, -1)[..., ::2], "device": lambda t: t.cpu(),
+         "type": lambda t: t.half() if t.is_floating_point() else t.real.contiguous() if t.is_complex() else t.int()}
+
+
+@pytest.mark.parametrize("wrong", sorted(WRONG))
+@pytest.mark.parametrize("call", CALLS)
+def test_a_wrong_argument_is_named(call, wrong):
+    """Every tensor of every call with a wrong shape, stride, device or type: the error names it, before anything is launched (fake
+    tensors on the GPU, so that a call that is not refused cannot reach one)."""
+    import inspect
+    import types
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode(allow_non_fake_inputs=True):
+        fn, kw, names = _calls("cuda", run=False)[call]
+        kw["stream"] = types.SimpleNamespace(cuda_stream=0)
+        if "workspace" in inspect.signature(fn).parameters:
+            kw["workspace"] = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+        sets_the_shape = {"u", "Lambda", "reward", "cont", "v", "gx", "dy", "B"}           # (its wrong shape makes the others wrong)
+        for name in names:
+            if wrong == "shape" and name in sets_the_shape:
+                continue
+            with pytest.raises(ValueError, match="^%s must be a contiguous cuda tensor" % name):
+                fn(**{**kw, name: WRONG[wrong](kw[name])})
 
 
 @pytest.mark.gpu
