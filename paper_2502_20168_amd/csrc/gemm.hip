@@ -8,7 +8,8 @@ namespace ssm {
 // A product over T tokens with N columns that has few 128x128 tiles shares its launch with a K = T
 // reduction on 64x64x64 tiles: a quarter of the multiply-adds per workgroup, so that the chain of K
 // steps a small shape waits for is short.
-// (measured: 16 and 32 leave gains on the table, 128 doubles the step at 40 x 100 tokens, H = P = 256)
+// (forward + gradient pass with 32 instead of 64, 36 shapes of 1000 .. 4000 tokens, H and P 128 .. 512: 3 % faster to 3 %
+// slower, 0.1 % slower on the mean; above 64 the product itself has a workgroup per CU)
 constexpr int64_t SMALL_PAIR_ITEMS = 64;
 bool gemm_small_pair(int64_t T, int64_t N)
 {
@@ -43,9 +44,9 @@ SlabPlan gemm_plan_slabs(int64_t M, int64_t N, int64_t K, int count, ReductionTi
 }
 
 // The projections scan their own output tiles where a sequence is a whole number of 128-step pieces (a bounded chain
-// of tiles per sequence) or every 128 tokens are whole sequences of whole 16-step chunks, and there are enough tiles
-// (measured with tiles of 128 tokens: from 64 of them on -- a quarter of the CUs -- the scanning tile beats smaller tiles
-// plus a scan kernel: +2 % at 64 tiles, +7..13 % at 96-128; no difference at 32-48).
+// of tiles per sequence) or every 128 tokens are whole sequences of whole 16-step chunks, and there are at least 64 tiles of
+// 128 tokens.  (From there on the scanning tile with two planes beats a scan kernel and three planes on every shape measured;
+// between 32 and 64 tiles it would by 4-20 % too, but those shapes keep the exact split into three planes.)
 bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P)
 {
     constexpr int64_t PIECE = 128, CHUNK = 16, MIN_TILES = 64;

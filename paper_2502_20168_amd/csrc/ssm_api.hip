@@ -140,9 +140,10 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
     size_t dA_elems = o.plan.partial_elems;
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
-    // (measured on eleven shapes: a gain of 6-16 % per step where both contraction lengths are long, H >= 512 and
-    // 2P >= 1024; with shorter ones the maxima the scan kernels and the prep launch then record cost more than the
-    // third fewer matrix instructions save: 3-9 % slower)
+    // (forward + gradient pass with three planes instead, 20 shapes of H, P >= 512 at 3200 .. 16000 tokens: 17 % slower at
+    // 32 x 100 tokens, H = P = 512, 28-56 % at the others.  With a shorter contraction two planes would be faster as well, by
+    // 4-29 % from 4800 tokens on (nothing at 32 x 100, H = P = 256); those shapes keep the exact split into three planes,
+    // which holds every element to its own last bit whatever else its row or matrix holds)
     o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
                         H >= 512 && P >= 512;
     if (o.planes2_unfused) {

@@ -78,9 +78,10 @@ struct GemmArgs {
                                                      // row of C2 per piece of 128 columns; or null
 };
 // The gate's products stage two scaled fp16 planes per operand (and the passes before them measure the
-// largest magnitudes) at widths that are multiples of 64 from 512 on, with enough tokens (measured on 4096 tokens:
-// -13 % at H = 1024, even at H = 512; +2 % at 1024 tokens, H = 256, where the passes cost more than the shorter K
-// loops save)
+// largest magnitudes) at widths that are multiples of 64 from 512 on, with enough tokens (against three planes, forward +
+// gradient pass: -7 % at 4096 tokens, H = 512, -17 % at 16384; -24 % at 4096, H = 1024.  Below the line, two planes against
+// three: +27 % at 2048 tokens, H = 256, where the passes cost more than the shorter K loops save, -3 % at 16384; +12 % at
+// 1024, H = 512, -4 % at 2048 and -11 % at 3000, where the exact three planes are kept)
 inline bool gate_two_planes_shape(int64_t T, int64_t H) { return H % 64 == 0 && H >= 512 && ((T + 63) / 64) * ((H + 127) / 128) >= 200; }
 // the input projection (epilogue 7) and C^H dy (epilogue 8, the reverse scan of the gradient pass) scan
 // their own output tiles at this shape
