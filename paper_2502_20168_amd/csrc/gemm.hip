@@ -16,6 +16,10 @@ bool gemm_small_pair(int64_t T, int64_t N)
     return ((T + 127) / 128) * ((N + 127) / 128) <= SMALL_PAIR_ITEMS;
 }
 
+// a launch of a two-plane product and `items` work items of reductions fits two workgroups per CU with tiles of 128 rows and
+// with 64 does not by far
+static bool takes_tall_tiles(int64_t tall, int64_t low, int64_t items) { return low + items > 576 && tall + items <= 512; }
+
 // Reductions of M x N over K rows (`count` of them, with the same number of tiles) that share a launch with a product.
 // What a launch of several rounds wants is one work item of the reductions per CU, a few less rather than more, and all of
 // them in the first slots: every CU then works on one item from beginning to end while the product's tiles pass through its
@@ -23,6 +27,10 @@ bool gemm_small_pair(int64_t T, int64_t N)
 // either kind), half as many, and in front only where an item is the longer chain (more rows than the product's K loop).
 // The counts are those that divide 8 or that 8 divides, because then an XCD owns whole slabs or one band of one
 // (tn_place), and a few between; the one whose number of items is nearest in ratio; an item keeps at least 192 (64) rows.
+// One reduction, two planes: fewer, down to 160 items, where the launch with tiles of 128 rows then fits (4800 tokens, H 1024, P 512:
+// 304 + 192 workgroups instead of 600 + 256, each of the two launches 68.5 us against 71; gradient pass, 62 shapes of 2400 ..
+// 11000 tokens: -5 .. +1.5 %, -1.1 % on the mean; the gate's 8448 tokens, H 512: 66.6 against 74.5.  With 144 items and fewer
+// +3 .. +30 %; two reductions beside one product -5 .. +9 %, +2 % on the mean).
 // Measured on 251 launches (every product's reductions at 1000 .. 32768 tokens, H and P from 64 to 1024) against 18 counts in either order:
 // the gradient pass is 0.7 % slower than with the best of them on geometric mean, 8 % at worst.  Some (us; this rule, best, same
 // count with the product first):
@@ -34,12 +42,16 @@ SlabPlan gemm_plan_slabs(int64_t M, int64_t N, int64_t K, int count, ReductionTi
 {
     const bool small = tile == REDUCTION_64x64;
     const int64_t tiles = reduction_items(M, N, count, tile), want = small ? 128 : 224, min_rows = small ? 64 : 192;
-    int best = 1;
+    // the product beside them: K tokens, as many columns as the reductions
+    const int64_t columns = (N + 127) / 128, tall = (K + 127) / 128 * columns, low = (K + 63) / 64 * columns;
+    int best = 1, fitting = 0;
     for (int s : {2, 3, 4, 5, 8, 12, 16, 24, 32, 40, 48, 56, 64}) {
         if (K / s < min_rows) break;
         // s is nearer than best: want / (tiles best) > (tiles s) / want
         if (tiles * s <= want || want * want > tiles * best * tiles * s) best = s;
+        if (tile == REDUCTION_128x128 && count == 1 && tiles * s >= 160 && takes_tall_tiles(tall, low, tiles * s)) fitting = s;
     }
+    if (fitting && fitting < best) best = fitting;
     return {best, !small || (K + best - 1) / best > k_main};
 }
 
@@ -100,7 +112,7 @@ PkTile product_tile(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c)
     if (tiles(64, 128) <= 128 && (a.planes == 3 || (!b && (a.epilogue == 1 || a.epilogue == 6))))
         return {32, a.c2_rowmax || tiles(32, 64) + items > 256 ? 128 : tiles(32, 32) + items > 128 ? 64 : 32};
     if (a.planes != 2) return {64, 128};
-    return {tiles(128, 128) >= 512 || (items > 0 && tiles(64, 128) + items > 576 && tiles(128, 128) + items <= 512) ? 128 : 64, 128};
+    return {tiles(128, 128) >= 512 || (items > 0 && takes_tall_tiles(tiles(128, 128), tiles(64, 128), items)) ? 128 : 64, 128};
 }
 
 namespace {

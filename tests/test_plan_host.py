@@ -69,11 +69,15 @@ def test_reported_tiles_are_those_of_the_launches(Bt, L, H, P):
 COUNTS = (1, 2, 3, 4, 5, 8, 12, 16, 24, 32, 40, 48, 56, 64)
 
 
-def _slabs(T, tiles, small):
-    """The count whose number of work items is nearest, in ratio, to 224 (128 beside small products)."""
+def _slabs(tiles, T, small=False, fit=None):
+    """The count whose number of work items is nearest, in ratio, to 224 (128 beside small products); one two-plane reduction
+    beside a product of `fit` columns: at most the largest that leaves 160 items and makes room for 128-row tiles."""
     want, rows = (128, 64) if small else (224, 192)
     allowed = [s for s in COUNTS if s == 1 or T // s >= rows]
-    return min(allowed, key=lambda s: (max(Fraction(tiles * s, want), Fraction(want, tiles * s)), s))
+    nearest = min(allowed, key=lambda s: (max(Fraction(tiles * s, want), Fraction(want, tiles * s)), s))
+    fits = [s for s in allowed if fit and s > 1 and tiles * s >= 160 and _ceil(T, 128) * _ceil(fit, 128) + tiles * s <= 512
+            and _ceil(T, 64) * _ceil(fit, 128) + tiles * s > 576]
+    return min([nearest] + fits[-1:])
 
 
 @pytest.mark.parametrize("Bt,L,H,P", [(16, 256, 512, 512), (4, 4096, 256, 256), (1024, 16, 512, 512), (32, 128, 1024, 512),
@@ -83,13 +87,14 @@ def test_slabs_of_the_three_product_launch(Bt, L, H, P):
     T = Bt * L
     p = ssm.ssm_plan_describe(Bt, L, H, P)
     assert p["products_per_gradient_launch"] == 3 and p["scans_in_projections"] == 1
-    s = _slabs(T, 2 * _ceil(2 * P, 128) * _ceil(H, 128), False)
+    s = _slabs(2 * _ceil(2 * P, 128) * _ceil(H, 128), T)
     assert p["slabs_dC"] == s and p["slabs_dBbar"] == s
     assert p["slabs_first"] == 1
 
 
 @pytest.mark.parametrize("Bt,L,H,P", [(64, 100, 512, 512), (16, 1000, 256, 256), (24, 200, 1024, 512), (20, 300, 512, 256),
                                       (10, 1000, 512, 512), (40, 200, 768, 384), (40, 100, 256, 256), (16, 64, 256, 256), (1, 256, 1024, 1024),
+                                      (48, 100, 512, 512), (100, 100, 512, 1024),
                                       (8, 128, 64, 256), (5, 77, 96, 40), (1, 3, 2, 1)])
 def test_slabs_and_order_of_the_two_product_launches(Bt, L, H, P):
     T = Bt * L
@@ -99,7 +104,7 @@ def test_slabs_and_order_of_the_two_product_launches(Bt, L, H, P):
         # beside a product of T x N with a K loop of K
         small = _ceil(T, 128) * _ceil(N, 128) <= 64
         tile = (128, 128) if p["planes"] == 2 else (64, 64) if small else (128, 64)
-        s = _slabs(T, _ceil(M, tile[0]) * _ceil(N, tile[1]), small)
+        s = _slabs(_ceil(M, tile[0]) * _ceil(N, tile[1]), T, small, N if p["planes"] == 2 else None)
         assert p[slabs] == s
         assert p[first] == int(not small or _ceil(T, s) > K)
 
