@@ -35,7 +35,7 @@ static bool takes_tall_tiles(int64_t tall, int64_t low, int64_t items) { return 
 // the gradient pass is 0.7 % slower than with the best of them on geometric mean, 8 % at worst.  Some (us; this rule, best, same
 // count with the product first):
 //   one launch of three products   24x128, H 1024, P 512: 129 129 131     16x256, 512, 512: 93.4 93.4 95.2    4x4096, 256, 256: 101 101 102
-//   launches of two, two planes    16x1000, 512, 512: 308 308 330         24x200, 1024, 512: 188 187 201
+//   launches of two, two planes    16x1000, 512, 512: 308 308 330
 //   launches of two, three planes  20x300, 500, 250: 121 121 130          40x200, 768, 384: 259 259 298
 //   beside small products          20x100, 256, 256: 46.7 46.7 50.5       8x128, 256, 256: 39.1 39.1 39.2
 SlabPlan gemm_plan_slabs(int64_t M, int64_t N, int64_t K, int count, ReductionTile tile, int64_t k_main)
