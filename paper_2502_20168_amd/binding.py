@@ -29,7 +29,7 @@ SSM_NOALLOC_SCRATCH_BYTES = 8 << 20
 SSM_FWD_STAGES = 4
 SSM_BWD_STAGES = 6
 FWD_STAGE_NAMES = ("discretize_pack", "project_in", "scan", "project_out")
-BWD_STAGE_NAMES = ("discretize_pack_dD", "gx", "reverse_scan", "du_dBbar_dC_partials", "sum_du_halves",
+BWD_STAGE_NAMES = ("discretize_pack_dD", "gx", "reverse_scan", "du_dBbar_dC_partials", "unused",
                    "param_epilogue")
 
 EXPORTS = ("ssm_strerror", "ssm_version", "ssm_workspace_bytes", "ssm_discretize", "ssm_scan_fwd",
