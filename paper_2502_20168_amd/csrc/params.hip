@@ -236,6 +236,48 @@ __device__ __forceinline__ void absmax_pass_block(const PrepArgs::Pass &q, int p
     if (tid == 0) q.slots[piece] = u;
 }
 
+__device__ void psi_prime(double zr, double zi, double er, double ei, double &pr, double &pi)
+{
+    // psi'(z) = (z e^z - e^z + 1)/z^2 = sum_k z^k (k+1)/(k+2)!
+    if (zr * zr + zi * zi < 0.25) {
+        double tr = 0.5, ti = 0.0;
+        pr = 0.5; pi = 0.0;
+        // (|z| < 1/2: the terms behind the seventeenth are below 1e-20 of the first; unrolled, so that their coefficients are constants)
+#pragma unroll
+        for (int k = 1; k < 18; ++k) {
+            const double c = (double)(k + 1) / ((double)k * (double)(k + 2));
+            const double nr = (tr * zr - ti * zi) * c, ni = (tr * zi + ti * zr) * c;
+            tr = nr; ti = ni;
+            pr += tr; pi += ti;
+        }
+    } else {
+        // (e^z - psi(z))/z with psi = expm1(z)/z; er, ei = e^z
+        const double sh = sin(0.5 * zi);
+        const double mr = expm1(zr) * cos(zi) - 2.0 * sh * sh, mi = ei;
+        double psr, psi_;
+        cdiv(mr, mi, zr, zi, psr, psi_);
+        cdiv(er - psr, ei - psi_, zr, zi, pr, pi);
+    }
+}
+
+__device__ __forceinline__ void adjoint_block(const PackSrc &s, StateAdjoint *out, int blk)
+{
+    const int p = blk * (int)blockDim.x + (int)threadIdx.x;
+    if (p >= s.P) return;
+    const float2 L = s.Lambda[p];
+    const Zoh z = zoh_discretize(L, s.log_delta[p]);
+    double pr, pi;
+    psi_prime(z.zr, z.zi, z.lr, z.li, pr, pi);
+    const double d = z.delta, Lr = L.x, Li = L.y;
+    StateAdjoint o;
+    o.ar = d * z.lr; o.ai = d * z.li;                        // Delta Abar
+    o.pr = d * d * pr; o.pi = d * d * pi;                    // Delta^2 psi'
+    o.mr = d * (Lr * z.lr - Li * z.li); o.mi = d * (Lr * z.li + Li * z.lr);
+    o.gr = (float)z.gr; o.gi = (float)z.gi;
+    o.pad[0] = o.pad[1] = 0.f;
+    out[p] = o;
+}
+
 // Everything that has to be done before the products of a pass, in one launch: the weights of its products in
 // fragment order, the column-dot slabs behind dD (gradient pass), the largest magnitudes that scale the planes of
 // the activations, and the words to be cleared.  The longest chains of dependent work come first in the grid.
@@ -251,9 +293,13 @@ __global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
     // where they are used, the arguments come in five or six trips one behind the other, 1 us of the 3 that a small launch takes)
     asm volatile("" ::"s"(src.Lambda), "s"(src.B), "s"(src.C), "s"(src.log_delta), "s"(src.W), "s"(src.P), "s"(src.H), "s"(src.lam_bar), "s"(e0),
                  "s"(e1), "s"(e2), "s"(e3), "s"(hdr));
+    if (a.adj && blk < a.adj_blocks) {
+        adjoint_block(src, a.adj, blk);
+        return;
+    }
     if (blk < e3) {
         const PackJob job = a.pack[(blk >= e0) + (blk >= e1) + (blk >= e2)];
-        if (blk == 0 && tid == 0 && hdr) { hdr->err = 0; hdr->magic = 0x53534d31u; }
+        if (blk == a.adj_blocks && tid == 0 && hdr) { hdr->err = 0; hdr->magic = 0x53534d31u; }
         if (job.planes == 3) pack_dispatch<3>(src, job, blk - job.block0, lds);
         else pack_dispatch<2>(src, job, blk - job.block0, lds);
         return;
@@ -294,6 +340,8 @@ hipError_t launch_prep(const PrepArgs &a_in, hipStream_t s)
     PrepArgs a = a_in;
     long blocks = 0;
     if (a.npack < 1 || a.npack > PREP_MAX_PACKS) return hipErrorInvalidValue;
+    a.adj_blocks = a.adj ? (a.P + 255) / 256 : 0;
+    blocks = a.adj_blocks;
     for (int i = 0; i < a.npack; ++i) {
         PackJob &j = a.pack[i];
         if (!j.frag || (j.planes != 3 && (j.planes != 2 || !j.exp))) return hipErrorInvalidValue;
@@ -364,154 +412,170 @@ int coldot_slabs(int64_t T)
 //       dlog_delta_p = Delta * Re(conj(Lambda Abar) dAbar + conj(Abar) dg)
 //   workgroups [P, P+H): row h of dC = sum of its slabs with the imaginary part negated
 //       (dC[h,p] = sum_t dy[t,h] conj(x[t,p])), and dD[h] = sum of the column-dot slabs.
+// The factors of dAbar and dg depend on the parameters alone: the prep launch of the pass computes them (adjoint_block),
+// a thread per state beside everything else it does.  Here, in every workgroup of a state, their double-precision
+// transcendentals were 2 to 3.4 us in front of sums of 1 to 3 us.
 // ---------------------------------------------------------------------------------------------
-__device__ void psi_prime(double zr, double zi, double er, double ei, double &pr, double &pi)
+// Four consecutive values of a row from p, n of which exist (an address that is only float-aligned).
+__device__ __forceinline__ float4 load4(const float *p, int n)
 {
-    // psi'(z) = (z e^z - e^z + 1)/z^2 = sum_k z^k (k+1)/(k+2)!
-    if (zr * zr + zi * zi < 0.25) {
-        double tr = 0.5, ti = 0.0;
-        pr = 0.5; pi = 0.0;
-        for (int k = 1; k < 32; ++k) {
-            const double c = (double)(k + 1) / ((double)k * (double)(k + 2));
-            const double nr = (tr * zr - ti * zi) * c, ni = (tr * zi + ti * zr) * c;
-            tr = nr; ti = ni;
-            pr += tr; pi += ti;
-        }
-    } else {
-        // (e^z - psi(z))/z with psi = expm1(z)/z; er, ei = e^z
-        const double sh = sin(0.5 * zi);
-        const double mr = expm1(zr) * cos(zi) - 2.0 * sh * sh, mi = ei;
-        double psr, psi_;
-        cdiv(mr, mi, zr, zi, psr, psi_);
-        cdiv(er - psr, ei - psi_, zr, zi, pr, pi);
+    if (n >= 4) { const f32x4u v = *reinterpret_cast<const f32x4u *>(p); return make_float4(v.x, v.y, v.z, v.w); }
+    return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
+}
+__device__ __forceinline__ void store4(float *p, float4 v, int n)
+{
+    if (n >= 4) { const f32x4u w = {v.x, v.y, v.z, v.w}; *reinterpret_cast<f32x4u *>(p) = w; return; }
+    if (n > 0) p[0] = v.x;
+    if (n > 1) p[1] = v.y;
+    if (n > 2) p[2] = v.z;
+}
+__device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+
+// s[r] = sum over the slabs i, i + step, ... < n of the four values at base + i stride + r pitch, r < R: in the order of the
+// slabs, four of them (4 R loads) in flight at a time.  A slab past the end re-reads the last one and is not added.
+template <int R>
+__device__ __forceinline__ void sum_slabs(const float *base, long stride, long pitch, int i, int step, int n, int valid, float4 (&s)[R])
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (; i < n; i += 4 * step) {
+        float4 v[4][R];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[j][r] = load4(base + (long)min(i + j * step, n - 1) * stride + r * pitch, valid);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (i + j * step < n) s[r] = add4(s[r], v[j][r]);
     }
 }
 
-// fixed-order sum of n slabs (stride apart) with up to eight loads in flight
-__device__ __forceinline__ float sum_slabs(const float *base, long stride, int n, int i = 0, float s = 0.f)
-{
-    // (i, s: continue behind the first i slabs, whose sum in the same order is s)
-    for (; i + 8 <= n; i += 8) {
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = base[(long)(i + j) * stride];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s += v[j];
-    }
-    for (; i + 4 <= n; i += 4) {
-        const float v0 = base[(long)i * stride], v1 = base[(long)(i + 1) * stride];
-        const float v2 = base[(long)(i + 2) * stride], v3 = base[(long)(i + 3) * stride];
-        s = (((s + v0) + v1) + v2) + v3;
-    }
-    for (; i < n; ++i) s += base[(long)i * stride];
-    return s;
-}
-
-// deterministic sum of one double pair per thread over the 256 threads of a workgroup; result valid in thread 0.
-// Inside a wavefront a fixed butterfly of lane exchanges, then the four wavefront sums in order through LDS
-// (two barriers; a tree over all 256 values through LDS took eight and ~0.9 us).
+// Sums of v[0] .. v[3] over the 256 threads of a workgroup in a fixed order; valid in thread 0.  Inside a wavefront lanes that
+// differ in bit 5, then bit 4, share out the four sums (seven exchanges of a double instead of twenty-four); red: 16 doubles.
 __device__ __forceinline__ double shfl_xor_double(double v, int mask)
 {
     int lo = __double2loint(v), hi = __double2hiint(v);
     lo = __shfl_xor(lo, mask); hi = __shfl_xor(hi, mask);
     return __hiloint2double(hi, lo);
 }
-__device__ __forceinline__ void block_sum2(double *red_r, double *red_i, double &r, double &i, int tid)
+__device__ __forceinline__ void block_sum4(double *red, double (&v)[4], int tid)
 {
+    const int lane = tid & 63;
+    const bool up5 = lane & 32, up4 = lane & 16;
+    const double a = (up5 ? v[2] : v[0]) + shfl_xor_double(up5 ? v[0] : v[2], 32);
+    const double b = (up5 ? v[3] : v[1]) + shfl_xor_double(up5 ? v[1] : v[3], 32);
+    double s = (up4 ? b : a) + shfl_xor_double(up4 ? a : b, 16);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        r += shfl_xor_double(r, o);
-        i += shfl_xor_double(i, o);
-    }
-    __syncthreads();                                   // (red_r, red_i may still be read from an earlier call)
-    if ((tid & 63) == 0) { red_r[tid >> 6] = r; red_i[tid >> 6] = i; }
+    for (int o = 8; o > 0; o >>= 1) s += shfl_xor_double(s, o);
+    if ((lane & 15) == 0) red[4 * (tid >> 6) + (lane >> 4)] = s;          // lane 0: v[0], 16: v[1], 32: v[2], 48: v[3]
     __syncthreads();
-    r = (red_r[0] + red_r[1]) + (red_r[2] + red_r[3]);
-    i = (red_i[0] + red_i[1]) + (red_i[2] + red_i[3]);
+    if (tid == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = (red[k] + red[4 + k]) + (red[8 + k] + red[12 + k]);
+    }
 }
 
+// Bound by the trips to memory of one workgroup: all are resident at once, and the slabs were written by the launch before.  A
+// thread takes four columns of every row it sums in one request; threads that the columns leave over share out the slabs (groups
+// of 2^lgB / 2^lgC threads, whose sums meet in LDS in the order of the groups).  First workgroup's start to last one's end, with a
+// column per thread and request and the discretisation in front of the sums, and now: 4096 tokens, H = P = 512: 8.3 and 5.3 us;
+// 4800 tokens, H = 1024, P = 512: 14.0 and 7.3; 32768 tokens, 512, 512: 11.2 and 7.3; 1024 tokens, 256, 256: 5.3 and 3.6.
 __global__ void __launch_bounds__(256) epilogue_kernel(EpilogueArgs a)
 {
-    __shared__ double red_r[256], red_i[256];
-    const int tid = threadIdx.x;
-    const int blk = blockIdx.x;
+    __shared__ float4 part[2][256];
+    __shared__ double red[16];
+    const int tid = threadIdx.x, blk = blockIdx.x;
     const long PH2 = 2L * a.P * a.H;
     if (blk < a.P) {
-        // The workgroups of this launch are all resident at once, so it lasts as long as the chain of dependent
-        // steps of one of them.  The loads that need nothing from the discretisation are requested first (the
-        // first partial row of dAbar, the slabs of the thread's first column), so that its double-precision
-        // transcendentals, and psi' behind them, run while those are under way.
         const int p = blk;
         const float2 apart0 = tid < a.npart ? a.dAbar_part[(long)tid * a.P + p] : make_float2(0.f, 0.f);
-        constexpr int EARLY = 8;                      // slabs of the first column requested ahead
-        const int hc = tid < a.H ? tid : 0;
-        const int nearly = a.nsplit_B < EARLY ? a.nsplit_B : EARLY;
-        float vr[EARLY], vi[EARLY];
+        const StateAdjoint z = a.adj[p];
+        const int units = (a.H + 3) / 4, lg = a.lgB, groups = 256 >> lg, group = tid >> lg, u0 = tid & ((1 << lg) - 1);
+        const float *B = reinterpret_cast<const float *>(a.B + (long)p * a.H), *rows = a.dBbar_part + 2L * p * a.H;
+        float *dB = reinterpret_cast<float *>(a.dB + (long)p * a.H);
+        double sum[4] = {0.0, 0.0, (double)apart0.x, (double)apart0.y};      // dg, dAbar
+        auto finish = [&](int u, const float4 (&b)[2], float4 r, float4 i) {
+            const int n = 2 * (a.H - 4 * u);                 // floats of B and dB from column 4 u on
+            // conj(g) dBbar
+            store4(dB + 8 * u, make_float4(z.gr * r.x + z.gi * i.x, z.gr * i.x - z.gi * r.x, z.gr * r.y + z.gi * i.y, z.gr * i.y - z.gi * r.y), n);
+            store4(dB + 8 * u + 4, make_float4(z.gr * r.z + z.gi * i.z, z.gr * i.z - z.gi * r.z, z.gr * r.w + z.gi * i.w, z.gr * i.w - z.gi * r.w), n - 4);
+            // conj(B) dBbar (columns past the end: zeros)
+            const float br[4] = {b[0].x, b[0].z, b[1].x, b[1].z}, bi[4] = {b[0].y, b[0].w, b[1].y, b[1].w};
+            const float sr[4] = {r.x, r.y, r.z, r.w}, si[4] = {i.x, i.y, i.z, i.w};
 #pragma unroll
-        for (int j = 0; j < EARLY; ++j) {
-            const long o = (long)(j < nearly ? j : 0) * PH2;
-            vr[j] = a.dBbar_part[o + (long)(2 * p) * a.H + hc];
-            vi[j] = a.dBbar_part[o + (long)(2 * p + 1) * a.H + hc];
+            for (int k = 0; k < 4; ++k) {
+                sum[0] += (double)br[k] * sr[k] + (double)bi[k] * si[k];
+                sum[1] += (double)br[k] * si[k] - (double)bi[k] * sr[k];
+            }
+        };
+        auto unit = [&](int u, float4 (&b)[2], float4 (&v)[2]) {
+            const int n = a.H - 4 * u;
+            b[0] = load4(B + 8 * u, 2 * n); b[1] = load4(B + 8 * u + 4, 2 * n - 4);
+            sum_slabs<2>(rows + 4 * u, PH2, a.H, group, groups, a.nsplit_B, n, v);
+        };
+        float4 b[2], v[2];
+        if (groups == 1) {
+            for (int u = u0; u < units; u += 256) { unit(u, b, v); finish(u, b, v[0], v[1]); }
+        } else {
+            if (u0 < units) { unit(u0, b, v); part[0][tid] = v[0]; part[1][tid] = v[1]; }
+            __syncthreads();
+            if (group == 0 && u0 < units) {
+                for (int g = 1; g < groups; ++g) { v[0] = add4(v[0], part[0][(g << lg) + u0]); v[1] = add4(v[1], part[1][(g << lg) + u0]); }
+                finish(u0, b, v[0], v[1]);
+            }
         }
-        const float2 bv0 = a.B[(long)p * a.H + hc];
-        const Zoh z = zoh_discretize(a.Lambda[p], a.log_delta[p]);
-        double pr, pi;
-        psi_prime(z.zr, z.zi, z.lr, z.li, pr, pi);
-        // (the barrier keeps the waits for the loads above behind the arithmetic above)
-        __builtin_amdgcn_sched_barrier(0);
-        float sr0 = 0.f, si0 = 0.f;
-#pragma unroll
-        for (int j = 0; j < EARLY; ++j)
-            if (j < nearly) { sr0 += vr[j]; si0 += vi[j]; }
-        sr0 = sum_slabs(a.dBbar_part + (long)(2 * p) * a.H + hc, PH2, a.nsplit_B, nearly, sr0);
-        si0 = sum_slabs(a.dBbar_part + (long)(2 * p + 1) * a.H + hc, PH2, a.nsplit_B, nearly, si0);
-        const float gr = (float)z.gr, gi = (float)z.gi;
-        double dgr = 0.0, dgi = 0.0;
-        for (int h = tid; h < a.H; h += 256) {
-            const bool first = h == tid;
-            const float sr = first ? sr0 : sum_slabs(a.dBbar_part + (long)(2 * p) * a.H + h, PH2, a.nsplit_B);
-            const float si = first ? si0 : sum_slabs(a.dBbar_part + (long)(2 * p + 1) * a.H + h, PH2, a.nsplit_B);
-            // conj(g) * dBbar
-            a.dB[(long)p * a.H + h] = make_float2(gr * sr + gi * si, gr * si - gi * sr);
-            const float2 bv = first ? bv0 : a.B[(long)p * a.H + h];
-            // conj(B) * dBbar
-            dgr += (double)bv.x * sr + (double)bv.y * si;
-            dgi += (double)bv.x * si - (double)bv.y * sr;
+        for (long i = tid + 256; i < a.npart; i += 256) {    // dAbar: further partial rows of the reverse scan
+            const float2 t = a.dAbar_part[i * a.P + p];
+            sum[2] += (double)t.x; sum[3] += (double)t.y;
         }
-        block_sum2(red_r, red_i, dgr, dgi, tid);
-        double ar = (double)apart0.x, ai = (double)apart0.y;     // dAbar: partial rows of the reverse scan
-        for (long i = tid + 256; i < a.npart; i += 256) {
-            ar += (double)a.dAbar_part[i * a.P + p].x;
-            ai += (double)a.dAbar_part[i * a.P + p].y;
-        }
-        block_sum2(red_r, red_i, ar, ai, tid);
+        block_sum4(red, sum, tid);
         if (tid == 0) {
-            const double Lr = a.Lambda[p].x, Li = a.Lambda[p].y, d = z.delta;
-            // conj(d * Abar) * dAbar + conj(d^2 psi') * dg
-            const double c1r = d * z.lr, c1i = d * z.li, c2r = d * d * pr, c2i = d * d * pi;
-            const double dLr = (c1r * ar + c1i * ai) + (c2r * dgr + c2i * dgi);
-            const double dLi = (c1r * ai - c1i * ar) + (c2r * dgi - c2i * dgr);
-            a.dLambda[p] = make_float2((float)dLr, (float)dLi);
-            // Re(conj(Lambda Abar) dAbar + conj(Abar) dg)
-            const double mr = Lr * z.lr - Li * z.li, mi = Lr * z.li + Li * z.lr;
-            const double dDelta = (mr * ar + mi * ai) + (z.lr * dgr + z.li * dgi);
-            a.dlog_delta[p] = (float)(d * dDelta);
+            const double dgr = sum[0], dgi = sum[1], ar = sum[2], ai = sum[3];
+            // conj(Delta Abar) dAbar + conj(Delta^2 psi') dg
+            a.dLambda[p] = make_float2((float)((z.ar * ar + z.ai * ai) + (z.pr * dgr + z.pi * dgi)),
+                                       (float)((z.ar * ai - z.ai * ar) + (z.pr * dgi - z.pi * dgr)));
+            // Delta Re(conj(Lambda Abar) dAbar + conj(Abar) dg)
+            a.dlog_delta[p] = (float)((z.mr * ar + z.mi * ai) + (z.ar * dgr + z.ai * dgi));
         }
     } else {
         const int h = blk - a.P;
-        for (int j = tid; j < 2 * a.P; j += 256) {
-            const float s = sum_slabs(a.dC_part + (long)h * 2 * a.P + j, PH2, a.nsplit_C);
-            reinterpret_cast<float *>(a.dC)[(long)h * 2 * a.P + j] = (j & 1) ? -s : s;
+        const int units = (2 * a.P + 3) / 4, lg = a.lgC, groups = 256 >> lg, group = tid >> lg, u0 = tid & ((1 << lg) - 1);
+        const float *row = a.dC_part + (long)h * 2 * a.P;
+        float *dC = reinterpret_cast<float *>(a.dC) + (long)h * 2 * a.P;
+        double sum[4] = {tid < a.nslab ? (double)a.dD_part[(long)tid * a.H + h] : 0.0, 0.0, 0.0, 0.0};
+        auto finish = [&](int u, float4 v) { store4(dC + 4 * u, make_float4(v.x, -v.y, v.z, -v.w), 2 * a.P - 4 * u); };
+        float4 v[1];
+        if (groups == 1) {
+            for (int u = u0; u < units; u += 256) { sum_slabs<1>(row + 4 * u, PH2, 0, 0, 1, a.nsplit_C, 2 * a.P - 4 * u, v); finish(u, v[0]); }
+        } else {
+            if (u0 < units) { sum_slabs<1>(row + 4 * u0, PH2, 0, group, groups, a.nsplit_C, 2 * a.P - 4 * u0, v); part[0][tid] = v[0]; }
+            __syncthreads();
+            if (group == 0 && u0 < units) {
+                for (int g = 1; g < groups; ++g) v[0] = add4(v[0], part[0][(g << lg) + u0]);
+                finish(u0, v[0]);
+            }
         }
-        double sd = 0.0, unused = 0.0;
-        for (int sl = tid; sl < a.nslab; sl += 256) sd += (double)a.dD_part[(long)sl * a.H + h];
-        block_sum2(red_r, red_i, sd, unused, tid);
-        if (tid == 0) a.dD[h] = (float)sd;
+        for (int sl = tid + 256; sl < a.nslab; sl += 256) sum[0] += (double)a.dD_part[(long)sl * a.H + h];
+        block_sum4(red, sum, tid);
+        if (tid == 0) a.dD[h] = (float)sum[0];
     }
 }
 
-hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s)
+// log2 of the threads that take a row of n columns, four each: 16 to 256
+static int column_threads_log2(int n)
 {
+    int lg = 4;
+    while (lg < 8 && (4 << lg) < n) ++lg;
+    return lg;
+}
+
+hipError_t launch_epilogue(const EpilogueArgs &a_in, hipStream_t s)
+{
+    EpilogueArgs a = a_in;
+    if (!a.adj) return hipErrorInvalidValue;
+    a.lgB = column_threads_log2(a.H); a.lgC = column_threads_log2(2 * a.P);
     hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)(a.P + a.H)), dim3(256), 0, s, a);
     return hipGetLastError();
 }

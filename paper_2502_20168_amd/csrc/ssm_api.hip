@@ -104,7 +104,7 @@ struct Layout {
     int planes;              // per operand of every product
     PackedLayout w_in, w_out;          // forward: Bbar and C
     PackedLayout w_gx, w_du;           // gradient pass: both transposed
-    size_t hdr, lam, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
+    size_t hdr, lam, adj, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
     // largest magnitudes of the operands of the products (shapes whose projections scan their own tiles):
     // amax_atomic: 2 x ABSMAX_SLOTS words gathered with atomics, directly before fdesc so that one range is
     // cleared; amax_slots: PREP_PASS_BLOCKS and 2 x amax_cd words of the passes
@@ -137,7 +137,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.lam = off; off += up((size_t)P * 8);
     o.ticket = off; off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
     o.desc = off; off += up(o.plan.desc_bytes);
-    o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
+    o.adj = o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
     size_t dA_elems = o.plan.partial_elems;
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
     // (forward + gradient pass with three planes instead, 20 shapes of H, P >= 512 at 3200 .. 16000 tokens: 17 % slower at
@@ -186,6 +186,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.dBpart = off; off += up((size_t)o.dB.slabs * 2 * P * H * 4);
         o.dApart = off; off += up(dA_elems * 8);
         o.dDpart = off; off += up((size_t)o.nslab * H * 4);
+        o.adj = off; off += up((size_t)P * sizeof(StateAdjoint));
     }
     o.total = off;
     return SSM_OK;
@@ -394,6 +395,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     pa.pack[1] = pack_job(ws, lo.w_gx, PACK_GX, lo.planes);
     pa.npack = 2;
     zero_ranges(pa, lo, ws, fused, (size_t)T);
+    pa.adj = reinterpret_cast<StateAdjoint *>(ws + lo.adj);
     // dD slabs: sum_t dy[t,h] u[t,h] over row slabs, in the same launch
     pa.cd.a = dy; pa.cd.b = u; pa.cd.T = T; pa.cd.H = (int)H; pa.cd.nslab = lo.nslab; pa.cd.partial = dDpart;
     // two scaled fp16 planes per operand: dy and u are measured where dD reads them, chi and the saved
@@ -482,8 +484,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     MARK();
 
     EpilogueArgs ea{};
-    ea.Lambda = reinterpret_cast<const float2 *>(Lambda); ea.B = reinterpret_cast<const float2 *>(B);
-    ea.log_delta = log_delta; ea.P = (int)P; ea.H = (int)H;
+    ea.B = reinterpret_cast<const float2 *>(B); ea.adj = pa.adj; ea.P = (int)P; ea.H = (int)H;
     ea.dBbar_part = dBpart; ea.nsplit_B = lo.dB.slabs;
     ea.dC_part = dCpart; ea.nsplit_C = lo.dC.slabs;
     ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : (int64_t)Bt * lo.plan.nTB;

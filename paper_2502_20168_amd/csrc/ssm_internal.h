@@ -198,6 +198,10 @@ enum PackKind { PACK_IN, PACK_OUT, PACK_GX, PACK_DU, PACK_WN, PACK_WT };
 struct PackJob { int kind, N, K, planes; void *frag; int *exp; int block0, nblocks, kparts; };   // the last three set by the launch
 void pack_place(PackJob &j, int block0);     // workgroups of 256 threads that a job takes, from block0 on; three planes: parts that K is shared out in
 
+// Factors of the adjoint of the discretisation of one state, all they need being the parameters: dLambda = conj(a) dAbar + conj(p) dg,
+// dlog_delta = Re(conj(m) dAbar + conj(a) dg), dB = conj(g) dBbar.
+struct alignas(16) StateAdjoint { double ar, ai, pr, pi, mr, mi; float gr, gi, pad[2]; };
+
 constexpr int PREP_MAX_PACKS = 4;
 struct PrepArgs {
     const float2 *Lambda; const float2 *B; const float2 *C; const float *log_delta; const float *W;
@@ -206,6 +210,7 @@ struct PrepArgs {
     WsHeader *hdr;           // cleared when non-null
     int pack_end[PREP_MAX_PACKS]; int npack;     // first workgroup behind every job (set by launch_prep); jobs: at least one
     PackJob pack[PREP_MAX_PACKS];
+    StateAdjoint *adj; int adj_blocks;           // [P] or null (gradient pass); its workgroups, the first of the grid (set by launch_prep)
     ColDotArgs cd;           // cd.partial non-null: the launch also computes the column-dot slabs
     int cd_block0, cd_colblocks;                 // set by launch_prep
     struct Zero { uint4 *p; size_t n16; int block0, nblocks; } zero[2];   // regions to clear in the same launch (block ranges set by it)
@@ -224,12 +229,13 @@ hipError_t launch_discretize(const float2 *Lambda, const float2 *B, const float 
                              hipStream_t s);
 
 struct EpilogueArgs {
-    const float2 *Lambda; const float2 *B; const float *log_delta; int P, H;
+    const float2 *B; const StateAdjoint *adj; int P, H;
     const float *dBbar_part; int nsplit_B;   // [nsplit_B][2P][H]
     const float *dC_part; int nsplit_C;      // [nsplit_C][H][2P]  (sum_t dy x_re, sum_t dy x_im)
     const float2 *dAbar_part; int64_t npart; // [npart][P]
     const float *dD_part; int nslab;         // [nslab][H]
     float2 *dLambda; float2 *dB; float2 *dC; float *dD; float *dlog_delta;
+    int lgB, lgC;                            // set by launch_epilogue
 };
 hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s);
 
