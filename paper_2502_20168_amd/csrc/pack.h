@@ -68,14 +68,15 @@ __device__ __attribute__((noinline)) ZohPair zoh_rounded_pair(float2 La, float d
 struct PackSrc { const float2 *Lambda, *B, *C; const float *log_delta, *W; int P, H; float2 *lam_bar; };
 
 constexpr int PACK_ZOH_BATCH = 1024;                 // states whose g a transposing job of Bbar keeps in LDS at a time
-constexpr size_t PACK_LDS_BYTES = PACK_ZOH_BATCH * 8 + 4 * 16 * 4;
+constexpr size_t pack_lds_bytes(int threads) { return PACK_ZOH_BATCH * 8 + threads / 64 * 16 * 4; }
+constexpr size_t PACK_LDS_BYTES = pack_lds_bytes(256);
 
 // lanes that share a row of chunks, values of n per lane, chunks per thread that stay in registers
 constexpr int pack_lanes(int kind) { return kind == PACK_IN ? 4 : (kind == PACK_WN ? 16 : 8); }
 constexpr int pack_per_lane(int kind) { return (kind == PACK_IN || kind == PACK_GX) ? 2 : 1; }
 constexpr int pack_kept(int kind, int planes) { return planes == 3 ? 1 : pack_per_lane(kind) == 2 ? 2 : 4; }
 
-// A workgroup of 256 threads packs pack_lanes * pack_per_lane consecutive n.  A thread owns one n (or the pair re, im of
+// A workgroup packs pack_lanes * pack_per_lane consecutive n.  A thread owns one n (or the pair re, im of
 // one state) and chunks of eight consecutive k: the 16 bytes per plane that one lane of a fragment holds, so stores are
 // whole 128-byte lines.  Up to H = P = 512 the jobs are bound by latency: an empty launch takes 2 us, the discretisation 1.2 us
 // and a thread's way through one chunk 0.5 us.
@@ -87,15 +88,15 @@ constexpr int pack_kept(int kind, int planes) { return planes == 3 ? 1 : pack_pe
 //     registers between the largest magnitude of every n (its scale) and the split, so that it is one trip to memory
 //     (measured at H = P = 512, two trips of dependent chunks instead: prep launches of 11.1 and 17.6 us).
 //     A K longer than that is read twice, round by round.
-template <int KIND, int PLANES>
+template <int KIND, int PLANES, int NT = 256>
 __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, int wg, unsigned char *lds)
 {
-    constexpr int G = pack_lanes(KIND), V = pack_per_lane(KIND), ROWS = 256 / G, KEPT = pack_kept(KIND, PLANES), RAW = 8 * V;
+    constexpr int G = pack_lanes(KIND), V = pack_per_lane(KIND), ROWS = NT / G, KEPT = pack_kept(KIND, PLANES), RAW = 8 * V;
     constexpr bool SHARED_K = PLANES == 3;
     const int blk = SHARED_K ? wg / j.kparts : wg;
     const int first = SHARED_K ? (wg - blk * j.kparts) * ROWS : 0;                   // the workgroup's first chunk
     float2 *gz = reinterpret_cast<float2 *>(lds);                                    // [PACK_ZOH_BATCH] g of the states (PACK_DU)
-    unsigned *red = reinterpret_cast<unsigned *>(lds + PACK_ZOH_BATCH * 8);          // [4][G * V]
+    unsigned *red = reinterpret_cast<unsigned *>(lds + PACK_ZOH_BATCH * 8);          // [wavefronts][G * V]
     const int tid = threadIdx.x, nl = tid % G, row = tid / G, lane = tid & 63, wave = tid >> 6;
     const int unit = blk * G + nl;                                                   // state, or n
     const int n0 = unit * V;
@@ -159,7 +160,7 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
             g = make_float2(z.z, z.w);
             if (row == 0 && first == 0 && s.lam_bar && unit < s.P) s.lam_bar[unit] = make_float2(z.x, z.y);
         } else if constexpr (KIND == PACK_DU && SHARED_K) {
-            static_assert(!SHARED_K || ROWS * 4 <= 256, "a state per thread");
+            static_assert(!SHARED_K || ROWS * 4 <= NT, "a state per thread");
             const int p = first * 4 + tid;
             if (tid < ROWS * 4) {
                 const float4 z = zoh_rounded<PLANES>(own_lambda, own_delta);
@@ -178,14 +179,14 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
             };
             const float2 *Lam = s.Lambda + b * PACK_ZOH_BATCH;
             const float *ld = s.log_delta + b * PACK_ZOH_BATCH;
-            if (nb <= 256) {
+            if (nb <= NT) {
                 if (tid < nb) keep(tid, zoh_rounded<PLANES>(Lam[tid], ld[tid]));
             } else {
-                for (int i = tid; i < nb; i += 512) {        // (two chains of double-precision arithmetic at a time)
-                    const int k = min(i + 256, nb - 1);
+                for (int i = tid; i < nb; i += 2 * NT) {        // (two chains of double-precision arithmetic at a time)
+                    const int k = min(i + NT, nb - 1);
                     const ZohPair z = zoh_rounded_pair(Lam[i], ld[i], Lam[k], ld[k]);
                     keep(i, z.a);
-                    if (i + 256 < nb) keep(i + 256, z.b);
+                    if (i + NT < nb) keep(i + NT, z.b);
                 }
             }
             __syncthreads();
@@ -242,7 +243,7 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
         for (int i = 0; i < V; ++i) {
             unsigned u = 0;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) u = max(u, red[w * (G * V) + nl * V + i]);
+            for (int w = 0; w < NT / 64; ++w) u = max(u, red[w * (G * V) + nl * V + i]);
             const int e = log2_scale_of(u);
             scale[i] = pow2f(e);
             if (row == 0 && n0 + i < npad) j.exp[n0 + i] = e;
@@ -268,7 +269,8 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
     float raw[KEPT][RAW];
     auto fetch_round = [&](int c0) {
 #pragma unroll
-        for (int t = 0; t < KEPT; ++t) fetch(min(c0 + t * ROWS + row, nch - 1), raw[t]);
+        for (int t = 0; t < KEPT; ++t)
+            if (t == 0 || c0 + t * ROWS < nch) fetch(min(c0 + t * ROWS + row, nch - 1), raw[t]);
     };
     auto put_round = [&](int c0) {
 #pragma unroll
@@ -295,6 +297,7 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
             discretize(c0 * 4 / PACK_ZOH_BATCH);
 #pragma unroll
             for (int t = 0; t < KEPT; ++t) {
+                if (t > 0 && c0 + t * ROWS >= nch) continue;
                 float v[V][8];
                 finish(min(c0 + t * ROWS + row, nch - 1), raw[t], v);
                 take_max(v);
@@ -309,16 +312,16 @@ __device__ __forceinline__ void pack_block(const PackSrc &s, const PackJob &j, i
     }
 }
 
-template <int PLANES>
+template <int PLANES, int NT>
 __device__ __forceinline__ void pack_dispatch(const PackSrc &s, const PackJob &j, int wg, unsigned char *lds)
 {
     switch (j.kind) {
-    case PACK_IN: pack_block<PACK_IN, PLANES>(s, j, wg, lds); break;
-    case PACK_OUT: pack_block<PACK_OUT, PLANES>(s, j, wg, lds); break;
-    case PACK_GX: pack_block<PACK_GX, PLANES>(s, j, wg, lds); break;
-    case PACK_DU: pack_block<PACK_DU, PLANES>(s, j, wg, lds); break;
-    case PACK_WN: pack_block<PACK_WN, PLANES>(s, j, wg, lds); break;
-    default: pack_block<PACK_WT, PLANES>(s, j, wg, lds); break;
+    case PACK_IN: pack_block<PACK_IN, PLANES, NT>(s, j, wg, lds); break;
+    case PACK_OUT: pack_block<PACK_OUT, PLANES, NT>(s, j, wg, lds); break;
+    case PACK_GX: pack_block<PACK_GX, PLANES, NT>(s, j, wg, lds); break;
+    case PACK_DU: pack_block<PACK_DU, PLANES, NT>(s, j, wg, lds); break;
+    case PACK_WN: pack_block<PACK_WN, PLANES, NT>(s, j, wg, lds); break;
+    default: pack_block<PACK_WT, PLANES, NT>(s, j, wg, lds); break;
     }
 }
 

@@ -5,11 +5,12 @@
 // small |Lambda Delta| that slowly decaying states have.
 #include "pack.h"
 
+#include <type_traits>
+
 namespace ssm {
 
 // ---------------------------------------------------------------------------------------------
-// partial[s][h] = sum_{t in slab s} a[t,h] * b[t,h]      (dD = sum_t dy_t (.) u_t)
-// workgroup = 64 columns x 4 row phases
+// partial[s][h] = sum_{t in slab s} a[t,h] * b[t,h]      (dD = sum_t dy_t (.) u_t), and largest magnitudes
 // ---------------------------------------------------------------------------------------------
 // maximum of v over the wavefront, valid in lane 63 (data-parallel-primitive moves only: inside quads,
 // inside rows of 16 lanes, then the last lane of a row broadcast to the following rows)
@@ -24,110 +25,109 @@ __device__ __forceinline__ unsigned wave_max_lane63(unsigned v)
     return v;
 }
 
-// Four values per lane -> lane l < 4 gets the maximum over the wavefront of value 2 (l & 1) + (l >> 1):
-// two halving steps inside the quads (lanes that differ in bit 0, then bit 1, swap the half the other
-// keeps), rotations inside the rows of 16 lanes, lane swaps across rows: seven moves for four reductions.
-__device__ __forceinline__ unsigned wave_max4(unsigned v0, unsigned v1, unsigned v2, unsigned v3, int lane)
+// Four values per lane -> lane l < 4 of every sixteen gets the maximum over the sixteen of value 2 (l & 1) + (l >> 1): two halving
+// steps inside the quads (lanes that differ in bit 0, then bit 1, swap the half the other keeps), two rotations.
+__device__ __forceinline__ unsigned row16_max4(unsigned v0, unsigned v1, unsigned v2, unsigned v3, int lane)
 {
     const bool up0 = lane & 1, up1 = (lane >> 1) & 1;
     const unsigned k0 = up0 ? v2 : v0, s0 = up0 ? v0 : v2, k1 = up0 ? v3 : v1, s1 = up0 ? v1 : v3;
-    const unsigned w0 = max(k0, (unsigned)__builtin_amdgcn_update_dpp((int)s0, (int)s0, 0xb1, 0xf, 0xf, false));
-    const unsigned w1 = max(k1, (unsigned)__builtin_amdgcn_update_dpp((int)s1, (int)s1, 0xb1, 0xf, 0xf, false));
+    const unsigned w0 = max(k0, dpp_move<0xb1>(s0)), w1 = max(k1, dpp_move<0xb1>(s1));      // quad_perm [1,0,3,2]
     const unsigned k = up1 ? w1 : w0, sd = up1 ? w0 : w1;
-    unsigned v = max(k, (unsigned)__builtin_amdgcn_update_dpp((int)sd, (int)sd, 0x4e, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xf, 0xf, false));   // row_ror:4
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xf, 0xf, false));   // row_ror:8
-    const auto r16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = max((unsigned)r16[0], (unsigned)r16[1]);
-    const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return max((unsigned)r32[0], (unsigned)r32[1]);
+    unsigned v = max(k, dpp_move<0x4e>(sd));                                                // quad_perm [2,3,0,1]
+    v = max(v, dpp_move<0x124>(v));                                                         // row_ror:4
+    return max(v, dpp_move<0x128>(v));                                                      // row_ror:8
 }
 
-// largest bit pattern of the non-negative floats v of a 256-thread workgroup, valid in thread 0
+// largest bit pattern of the non-negative floats v of a workgroup of NT threads, valid in every thread
+template <int NT>
 __device__ __forceinline__ unsigned block_absmax(float v)
 {
-    __shared__ unsigned wmax[4];
-    unsigned u = __float_as_uint(v);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) u = max(u, (unsigned)__shfl_xor((int)u, o));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = u;
+    __shared__ unsigned wmax[NT / 64];
+    unsigned u = wave_max_lane63(__float_as_uint(v));
+    __syncthreads();                                         // (wmax may still be read from an earlier call)
+    if ((threadIdx.x & 63) == 63) wmax[threadIdx.x >> 6] = u;
     __syncthreads();
-    return max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+    u = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) u = max(u, wmax[w]);
+    return u;
 }
 
-// arow (may be null): [colblocks][T], the largest magnitude of a[t, 64 columns of the block] per row t
+// partial[slab][64 columns of a block] and, where asked, the largest magnitudes of the pieces of a and b and arow (may be null):
+// [colblocks][T], the largest magnitude of a[t, 64 columns of the block] per row t.  Sixteen lanes take a row's 64 columns, 16 bytes
+// each, a wavefront four rows, and up to four such steps of both operands are in flight (rows past the slab re-read its last
+// one and count as zeros).
+template <int NT>
 __device__ __forceinline__ void coldot_block(const ColDotArgs &a, int colblock, int slab, unsigned *amax, unsigned *bmax, int slot,
-                                             unsigned *arow)
+                                             unsigned *arow, float *red)
 {
-    __shared__ float red[256];
-    const int tid = threadIdx.x;
-    const int col = colblock * 64 + (tid & 63), ph = tid >> 6;
+    constexpr int STEP = NT / 16;                            // rows of a step
+    const int tid = threadIdx.x, unit = tid & 15;
+    const int col = colblock * 64 + 4 * unit, n = a.H - col; // columns of this lane that exist: 4 or more, or none, unless cut
+    const bool cut = a.H % 4 != 0 && colblock * 64 + 64 > a.H;
+    const int cc = n > 0 ? col : 0;
     const long rows_per = (a.T + a.nslab - 1) / a.nslab;
     const long r0 = slab * rows_per, r1 = min((long)a.T, r0 + rows_per);
-    float s = 0.f, ma = 0.f, mb = 0.f;
-    // every lane walks the rows (a wavefront = 64 columns of the rows r0 + ph, + 4, ...); columns past H read
-    // column 0 and count as zero, so that the per-row maxima can be formed across the whole wavefront
-    const bool okc = col < a.H;
-    const int cc = okc ? col : 0;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    float ma = 0.f, mb = 0.f;
     unsigned *arow_cb = arow ? arow + (size_t)colblock * a.T : nullptr;
-    long t = r0 + ph;
-    for (; t + 60 < r1; t += 64) {           // sixteen independent row pairs in flight (one trip to memory for 64 rows of a slab)
-        float av[16], bv[16];
+    auto load = [&](const float *p) {
+        float4 v;
+        if (!cut) { const f32x4u w = *reinterpret_cast<const f32x4u *>(p + cc); v = make_float4(w.x, w.y, w.z, w.w); }
+        else v = make_float4(p[min(cc, a.H - 1)], p[min(cc + 1, a.H - 1)], p[min(cc + 2, a.H - 1)], p[min(cc + 3, a.H - 1)]);
+        return v;
+    };
+    auto take = [&](long t0, auto steps) {
+        constexpr int N = decltype(steps)::value;
+        const long t = t0 + tid / 16;
+        float4 av[N], bv[N];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            av[j] = a.a[(t + 4 * j) * a.H + cc];
-            bv[j] = a.b[(t + 4 * j) * a.H + cc];
+        for (int j = 0; j < N; ++j) {
+            const long r = min(t + j * STEP, r1 - 1) * a.H;
+            av[j] = load(a.a + r);
+            bv[j] = load(a.b + r);
         }
+        unsigned rm[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {        // the arithmetic in the order of the loop below
-            float a0 = av[4 * g], a1 = av[4 * g + 1], a2 = av[4 * g + 2], a3 = av[4 * g + 3];
-            float b0 = bv[4 * g], b1 = bv[4 * g + 1], b2 = bv[4 * g + 2], b3 = bv[4 * g + 3];
-            if (!okc) { a0 = a1 = a2 = a3 = 0.f; b0 = b1 = b2 = b3 = 0.f; }
-            s = fmaf(a0, b0, s); s = fmaf(a1, b1, s); s = fmaf(a2, b2, s); s = fmaf(a3, b3, s);
-            ma = fmaxf(fmaxf(ma, fmaxf(fabsf(a0), fabsf(a1))), fmaxf(fabsf(a2), fabsf(a3)));
-            mb = fmaxf(fmaxf(mb, fmaxf(fabsf(b0), fabsf(b1))), fmaxf(fabsf(b2), fabsf(b3)));
-            if (arow_cb) {
-                const int l = tid & 63;
-                const unsigned m = wave_max4(__float_as_uint(fabsf(a0)), __float_as_uint(fabsf(a1)), __float_as_uint(fabsf(a2)),
-                                             __float_as_uint(fabsf(a3)), l);
-                if (l < 4) arow_cb[t + 16 * g + 4 * (2 * (l & 1) + (l >> 1))] = m;
-            }
+        for (int j = 0; j < N; ++j) {
+            const bool in = t + j * STEP < r1;
+            const bool c0 = in && n > 0, c1 = in && n > 1, c2 = in && n > 2, c3 = in && n > 3;
+            const float4 x = make_float4(c0 ? av[j].x : 0.f, c1 ? av[j].y : 0.f, c2 ? av[j].z : 0.f, c3 ? av[j].w : 0.f);
+            const float4 y = make_float4(c0 ? bv[j].x : 0.f, c1 ? bv[j].y : 0.f, c2 ? bv[j].z : 0.f, c3 ? bv[j].w : 0.f);
+            s = make_float4(fmaf(x.x, y.x, s.x), fmaf(x.y, y.y, s.y), fmaf(x.z, y.z, s.z), fmaf(x.w, y.w, s.w));
+            const float mr = fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w)));
+            rm[j] = __float_as_uint(mr);
+            ma = fmaxf(ma, mr);
+            mb = fmaxf(mb, fmaxf(fmaxf(fabsf(y.x), fabsf(y.y)), fmaxf(fabsf(y.z), fabsf(y.w))));
         }
-    }
-    for (; t + 12 < r1; t += 16) {           // four independent row pairs in flight
-        float a0 = a.a[t * a.H + cc], b0 = a.b[t * a.H + cc];
-        float a1 = a.a[(t + 4) * a.H + cc], b1 = a.b[(t + 4) * a.H + cc];
-        float a2 = a.a[(t + 8) * a.H + cc], b2 = a.b[(t + 8) * a.H + cc];
-        float a3 = a.a[(t + 12) * a.H + cc], b3 = a.b[(t + 12) * a.H + cc];
-        if (!okc) { a0 = a1 = a2 = a3 = 0.f; b0 = b1 = b2 = b3 = 0.f; }
-        s = fmaf(a0, b0, s); s = fmaf(a1, b1, s); s = fmaf(a2, b2, s); s = fmaf(a3, b3, s);
-        ma = fmaxf(fmaxf(ma, fmaxf(fabsf(a0), fabsf(a1))), fmaxf(fabsf(a2), fabsf(a3)));
-        mb = fmaxf(fmaxf(mb, fmaxf(fabsf(b0), fabsf(b1))), fmaxf(fabsf(b2), fabsf(b3)));
         if (arow_cb) {
-            const int l = tid & 63;
-            const unsigned m = wave_max4(__float_as_uint(fabsf(a0)), __float_as_uint(fabsf(a1)), __float_as_uint(fabsf(a2)),
-                                         __float_as_uint(fabsf(a3)), l);
-            if (l < 4) arow_cb[t + 4 * (2 * (l & 1) + (l >> 1))] = m;
+            // lane l < 4 of the sixteen gets the row's maximum of step 2 (l & 1) + (l >> 1)
+            const unsigned m = row16_max4(rm[0], rm[1], rm[2], rm[3], unit);
+            const int j = 2 * (unit & 1) + (unit >> 1);
+            if (unit < 4 && j < N && t + j * STEP < r1) arow_cb[t + j * STEP] = m;
         }
+    };
+    for (long t0 = r0; t0 < r1;) {                           // (uniform)
+        if (r1 - t0 > 2 * STEP) { take(t0, std::integral_constant<int, 4>{}); t0 += 4 * STEP; }
+        else if (r1 - t0 > STEP) { take(t0, std::integral_constant<int, 2>{}); t0 += 2 * STEP; }
+        else { take(t0, std::integral_constant<int, 1>{}); t0 += STEP; }
     }
-    for (; t < r1; t += 4) {
-        float a0 = a.a[t * a.H + cc], b0 = a.b[t * a.H + cc];
-        if (!okc) { a0 = 0.f; b0 = 0.f; }
-        s = fmaf(a0, b0, s);
-        ma = fmaxf(ma, fabsf(a0)); mb = fmaxf(mb, fabsf(b0));
-        if (arow_cb) {
-            const unsigned u0 = wave_max_lane63(__float_as_uint(fabsf(a0)));
-            if ((tid & 63) == 63) arow_cb[t] = u0;
-        }
+    // over the four rows of a wavefront, then over the wavefronts in order
+#pragma unroll
+    for (int o = 16; o <= 32; o *= 2) {
+        s.x += __shfl_xor(s.x, o); s.y += __shfl_xor(s.y, o);
+        s.z += __shfl_xor(s.z, o); s.w += __shfl_xor(s.w, o);
     }
-    red[tid] = s;
+    if ((tid & 63) < 16) *reinterpret_cast<float4 *>(red + (tid >> 6) * 64 + 4 * unit) = s;
     __syncthreads();
-    if (ph == 0 && col < a.H)
-        a.partial[(long)slab * a.H + col] = (red[tid] + red[tid + 64]) + (red[tid + 128] + red[tid + 192]);
+    if (tid < 64 && colblock * 64 + tid < a.H) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) sum += red[w * 64 + tid];
+        a.partial[(long)slab * a.H + colblock * 64 + tid] = sum;
+    }
     if (amax) {
-        const unsigned ua = block_absmax(ma);
-        __syncthreads();
-        const unsigned ub = block_absmax(mb);
+        const unsigned ua = block_absmax<NT>(ma), ub = block_absmax<NT>(mb);
         if (tid == 0) { amax[slot] = ua; bmax[slot] = ub; }
     }
 }
@@ -187,11 +187,12 @@ __device__ __forceinline__ void absmax_rows_batch(const PrepArgs::Pass &q, size_
         if (lane == 63 && row0 + r < rows) q.slots[row0 + r] = u;
     }
 }
+template <int NT>
 __device__ __forceinline__ void absmax_rows_block(const PrepArgs::Pass &q, int piece)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t rows = q.n / (size_t)q.rowlen;
-    const size_t wid = (size_t)piece * 4 + wave, nw = (size_t)q.nblocks * 4;
+    const size_t wid = (size_t)piece * (NT / 64) + wave, nw = (size_t)q.nblocks * (NT / 64);
     if (rows <= nw) {
         if (wid < rows) absmax_rows_batch<1>(q, wid, rows, lane);
     } else {
@@ -200,16 +201,17 @@ __device__ __forceinline__ void absmax_rows_block(const PrepArgs::Pass &q, int p
 }
 
 // slots[piece] = largest magnitude of piece `piece` of x[n] (pieces of whole float4 units when vec)
+template <int NT>
 __device__ __forceinline__ void absmax_pass_block(const PrepArgs::Pass &q, int piece)
 {
-    if (q.rowlen > 0) { absmax_rows_block(q, piece); return; }
+    if (q.rowlen > 0) { absmax_rows_block<NT>(q, piece); return; }
     const int tid = threadIdx.x;
     float m = 0.f;
     if (q.vec) {
         const size_t n4 = q.n / 4;
         const float4 *x4 = reinterpret_cast<const float4 *>(q.x);
-        size_t i = (size_t)piece * 256 + tid;
-        const size_t stride = (size_t)q.nblocks * 256;
+        size_t i = (size_t)piece * NT + tid;
+        const size_t stride = (size_t)q.nblocks * NT;
         for (; i + 7 * stride < n4; i += 8 * stride) {          // eight loads in flight
             float4 v[8];
 #pragma unroll
@@ -230,9 +232,9 @@ __device__ __forceinline__ void absmax_pass_block(const PrepArgs::Pass &q, int p
             m = fmaxf(m, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
         }
     } else {
-        for (size_t i = (size_t)piece * 256 + tid; i < q.n; i += (size_t)q.nblocks * 256) m = fmaxf(m, fabsf(q.x[i]));
+        for (size_t i = (size_t)piece * NT + tid; i < q.n; i += (size_t)q.nblocks * NT) m = fmaxf(m, fabsf(q.x[i]));
     }
-    const unsigned u = block_absmax(m);
+    const unsigned u = block_absmax<NT>(m);
     if (tid == 0) q.slots[piece] = u;
 }
 
@@ -278,12 +280,15 @@ __device__ __forceinline__ void adjoint_block(const PackSrc &s, StateAdjoint *ou
     out[p] = o;
 }
 
+constexpr int PREP_ZERO_UNITS = 2048;        // 16-byte units that a workgroup clears
+
 // Everything that has to be done before the products of a pass, in one launch: the weights of its products in
 // fragment order, the column-dot slabs behind dD (gradient pass), the largest magnitudes that scale the planes of
 // the activations, and the words to be cleared.  The longest chains of dependent work come first in the grid.
-__global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
+template <int NT>
+__global__ void __launch_bounds__(NT, 4) prep_kernel(PrepArgs a)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[PACK_LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[pack_lds_bytes(NT)];
     const int blk = blockIdx.x, tid = threadIdx.x;
     const PackSrc src{a.Lambda, a.B, a.C, a.log_delta, a.W, a.P, a.H, a.lam_bar};
     static_assert(PREP_MAX_PACKS == 4, "one load for all");
@@ -300,26 +305,26 @@ __global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
     if (blk < e3) {
         const PackJob job = a.pack[(blk >= e0) + (blk >= e1) + (blk >= e2)];
         if (blk == a.adj_blocks && tid == 0 && hdr) { hdr->err = 0; hdr->magic = 0x53534d31u; }
-        if (job.planes == 3) pack_dispatch<3>(src, job, blk - job.block0, lds);
-        else pack_dispatch<2>(src, job, blk - job.block0, lds);
+        if (job.planes == 3) pack_dispatch<3, NT>(src, job, blk - job.block0, lds);
+        else pack_dispatch<2, NT>(src, job, blk - job.block0, lds);
         return;
     }
     if (a.cd.partial && blk < a.cd_block0 + a.cd_colblocks * a.cd.nslab) {
         const int cb = blk - a.cd_block0;
-        coldot_block(a.cd, cb % a.cd_colblocks, cb / a.cd_colblocks, a.cd_amax, a.cd_bmax, cb, a.cd_arow);
+        coldot_block<NT>(a.cd, cb % a.cd_colblocks, cb / a.cd_colblocks, a.cd_amax, a.cd_bmax, cb, a.cd_arow, reinterpret_cast<float *>(lds));
         return;
     }
     if (a.pass.nblocks > 0 && blk < a.pass.block0 + a.pass.nblocks) {
-        absmax_pass_block(a.pass, blk - a.pass.block0);
+        absmax_pass_block<NT>(a.pass, blk - a.pass.block0);
         return;
     }
 #pragma unroll
     for (int z = 0; z < 2; ++z) {
         if (a.zero[z].nblocks > 0 && blk < a.zero[z].block0 + a.zero[z].nblocks) {
-            const size_t i0 = (size_t)(blk - a.zero[z].block0) * (256 * 8) + tid;
+            const size_t i0 = (size_t)(blk - a.zero[z].block0) * PREP_ZERO_UNITS + tid;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const size_t i = i0 + (size_t)k * 256;
+            for (int k = 0; k < PREP_ZERO_UNITS / NT; ++k) {
+                const size_t i = i0 + (size_t)k * NT;
                 if (i < a.zero[z].n16) a.zero[z].p[i] = make_uint4(0, 0, 0, 0);
             }
             return;
@@ -327,10 +332,10 @@ __global__ void __launch_bounds__(256, 4) prep_kernel(PrepArgs a)
     }
 }
 
-void pack_place(PackJob &j, int block0)
+void pack_place(PackJob &j, int block0, int threads)
 {
     const int per = pack_lanes(j.kind) * pack_per_lane(j.kind), npad = (j.N + 31) / 32 * 32;
-    const int chunks = (j.K + 63) / 64 * 8, rows = 256 / pack_lanes(j.kind);
+    const int chunks = (j.K + 63) / 64 * 8, rows = threads / pack_lanes(j.kind);
     j.kparts = j.planes == 3 ? (chunks + rows - 1) / rows : 1;
     j.block0 = block0; j.nblocks = (npad + per - 1) / per * j.kparts;
 }
@@ -340,12 +345,17 @@ hipError_t launch_prep(const PrepArgs &a_in, hipStream_t s)
     PrepArgs a = a_in;
     long blocks = 0;
     if (a.npack < 1 || a.npack > PREP_MAX_PACKS) return hipErrorInvalidValue;
-    a.adj_blocks = a.adj ? (a.P + 255) / 256 : 0;
+    // The gradient pass with two planes: 512 threads, so that a packing workgroup has half as long a chain of chunks per thread
+    // (its launch as a whole with 256 and with 512 threads: 8.3 and 7.2 us at 4096 tokens, H = P = 512; 15.1 and 13.9 at 4800, H = 1024,
+    // P = 512).  The forward pass gains nothing by it (-3 .. +4 % of its time on twelve shapes): there a pass over the rows of u takes
+    // the registers that packing leaves, and starts later with two workgroups per CU than with four.
+    const int threads = a.cd.partial && a.pack[0].planes == 2 ? 512 : 256;
+    a.adj_blocks = a.adj ? (a.P + threads - 1) / threads : 0;
     blocks = a.adj_blocks;
     for (int i = 0; i < a.npack; ++i) {
         PackJob &j = a.pack[i];
         if (!j.frag || (j.planes != 3 && (j.planes != 2 || !j.exp))) return hipErrorInvalidValue;
-        pack_place(j, (int)blocks);
+        pack_place(j, (int)blocks, threads);
         blocks += j.nblocks;
     }
     for (int i = 0; i < PREP_MAX_PACKS; ++i) a.pack_end[i] = i < a.npack ? a.pack[i].block0 + a.pack[i].nblocks : (int)blocks;
@@ -364,11 +374,12 @@ hipError_t launch_prep(const PrepArgs &a_in, hipStream_t s)
     }
     for (PrepArgs::Zero &z : a.zero) {
         z.block0 = (int)blocks;
-        z.nblocks = (z.p && z.n16 > 0) ? (int)((z.n16 + 256 * 8 - 1) / (256 * 8)) : 0;
+        z.nblocks = (z.p && z.n16 > 0) ? (int)((z.n16 + PREP_ZERO_UNITS - 1) / PREP_ZERO_UNITS) : 0;
         blocks += z.nblocks;
     }
     if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    if (threads == 256) hipLaunchKernelGGL(prep_kernel<256>, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(prep_kernel<512>, dim3((unsigned)blocks), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 
@@ -395,9 +406,12 @@ hipError_t launch_discretize(const float2 *Lambda, const float2 *B, const float 
     return hipGetLastError();
 }
 
-int coldot_slabs(int64_t T)
+int coldot_slabs(int64_t T, int planes)
 {
-    int64_t n = (T + 63) / 64;
+    // rows of one slab: a round of a workgroup's loads with 256 threads, two with 512 (the prep launch of 4800 tokens, H = 1024, P = 512
+    // with 64, 128 and 256 rows: 16.7, 15.5 and 13.9 us; 4096 tokens, 512, 512: 8.4, 7.9 and 7.5)
+    const int64_t rows = planes == 2 ? 256 : 64;
+    int64_t n = (T + rows - 1) / rows;
     if (n > 64) n = 64;                     // (128 and 256 slabs at 16384 tokens: within 0.5 % either way)
     if (n < 1) n = 1;
     return (int)n;

@@ -129,9 +129,16 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     ssm_status st = check_dims(Bt, L, H, P);
     if (st != SSM_OK) return st;
     const size_t T = (size_t)Bt * L;
+    // (forward + gradient pass with three planes instead, 20 shapes of H, P >= 512 at 3200 .. 16000 tokens: 17 % slower at
+    // 32 x 100 tokens, H = P = 512, 28-56 % at the others.  With a shorter contraction two planes would be faster as well, by
+    // 4-29 % from 4800 tokens on (nothing at 32 x 100, H = P = 256); those shapes keep the exact split into three planes,
+    // which holds every element to its own last bit whatever else its row or matrix holds)
+    o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
+                        H >= 512 && P >= 512;
+    o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
+    o.nslab = coldot_slabs((int64_t)T, o.planes);
     o.plan = plan_scan(Bt, L, P);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
-    o.nslab = coldot_slabs((int64_t)T);
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));
     o.lam = off; off += up((size_t)P * 8);
@@ -140,12 +147,6 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.adj = o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
     size_t dA_elems = o.plan.partial_elems;
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
-    // (forward + gradient pass with three planes instead, 20 shapes of H, P >= 512 at 3200 .. 16000 tokens: 17 % slower at
-    // 32 x 100 tokens, H = P = 512, 28-56 % at the others.  With a shorter contraction two planes would be faster as well, by
-    // 4-29 % from 4800 tokens on (nothing at 32 x 100, H = P = 256); those shapes keep the exact split into three planes,
-    // which holds every element to its own last bit whatever else its row or matrix holds)
-    o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
-                        H >= 512 && P >= 512;
     if (o.planes2_unfused) {
         o.amax_atomic = off; off += 2 * ABSMAX_SLOTS * 4;            // chi / x (atomic slots of the scan kernels)
         o.row_parts = 1;
@@ -167,7 +168,6 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         const size_t per_tile = (size_t)(Bt * L / gemm_scan_rows(Bt * L, L, P, true)) * P;  // one dAbar row per scanning tile
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
-    o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
     if (gemm_scan_shape_ok(Bt, L, P)) {
         o.dC = o.dB = gemm_plan_slabs(2 * P, H, (int64_t)T, 2, REDUCTION_128x128, 2 * P);
     } else {
@@ -193,10 +193,10 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
 }
 
 // pieces of the pass that measures the largest magnitude of n floats (each workgroup takes whole
-// rounds of 256 float4 units)
+// rounds of 512 float4 units)
 inline int pass_pieces(size_t n)
 {
-    const size_t rounds = (n / 4 + 256 * 4 - 1) / (256 * 4);
+    const size_t rounds = (n / 4 + 512 * 4 - 1) / (512 * 4);
     return (int)(rounds < 1 ? 1 : (rounds > (size_t)PREP_PASS_BLOCKS ? (size_t)PREP_PASS_BLOCKS : rounds));
 }
 

@@ -185,7 +185,7 @@ hipError_t launch_reduce_partials(const float2 *partial, int64_t n, int64_t P, f
 struct ColDotArgs {          // partial[s][h] = sum over the rows of slab s of a[t,h] * b[t,h]
     const float *a; const float *b; int64_t T; int H; int nslab; float *partial;
 };
-int coldot_slabs(int64_t T);
+int coldot_slabs(int64_t T, int planes);
 
 // Weights of one product for the prep launch to split and put into fragment order (see gemm_packed.h):
 //   PACK_IN   n = 2p+c, k = h:  Bbar                     (input projection)
@@ -196,7 +196,7 @@ int coldot_slabs(int64_t T);
 //   PACK_WT   n = i, k = j:     W[i, j]                   (adjoint of the gate)
 enum PackKind { PACK_IN, PACK_OUT, PACK_GX, PACK_DU, PACK_WN, PACK_WT };
 struct PackJob { int kind, N, K, planes; void *frag; int *exp; int block0, nblocks, kparts; };   // the last three set by the launch
-void pack_place(PackJob &j, int block0);     // workgroups of 256 threads that a job takes, from block0 on; three planes: parts that K is shared out in
+void pack_place(PackJob &j, int block0, int threads = 256);     // workgroups that a job takes, from block0 on; three planes: parts that K is shared out in
 
 // Factors of the adjoint of the discretisation of one state, all they need being the parameters: dLambda = conj(a) dAbar + conj(p) dg,
 // dlog_delta = Re(conj(m) dAbar + conj(a) dg), dB = conj(g) dBbar.

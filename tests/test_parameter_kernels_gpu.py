@@ -23,6 +23,24 @@ EPILOGUE = [
     (300, 20, 8, 5),       # more partial rows of dAbar than threads
 ]
 
+PREP = [
+    # Bt, L, H, P: column dots and magnitudes of the gradient pass, rows of a slab and columns of a block
+    (1, 17, 62, 3),        # three planes: one step and a row, two columns left over
+    (5, 79, 67, 12),       # several slabs, the last one short
+    (24, 128, 3, 512),     # two planes: fewer than four columns
+    (8, 1024, 61, 512),    # one column left over
+    (24, 128, 66, 512),    # a second block of two columns
+    (40, 100, 515, 513),   # separate scans, ragged widths
+    (131, 128, 68, 512),   # slabs of 262 rows: a round of loads and six rows
+    (4, 256, 1100, 1040),  # K longer than a packing thread keeps in registers, more states than a batch
+]
+
+
+@pytest.mark.parametrize("shape", PREP, ids=["x".join(map(str, s)) for s in PREP])
+def test_launch_in_front_of_the_products(shape):
+    print(shape, flush=True)
+    check_workload(wl.custom("prep", *shape, p_reset=0.02, with_x0=True, seed=19), backward=True)
+
 
 @pytest.mark.parametrize("shape", EPILOGUE, ids=["x".join(map(str, s)) for s in EPILOGUE])
 def test_sums_behind_the_products(shape):
