@@ -31,22 +31,30 @@ struct Split4 { bf16x4 p[3]; };
 // four consecutive floats at an address that is only float-aligned (one 16-byte load: global loads need dword alignment)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
+// The four values from the sh-th on of a unit that was read sh values early: the rest zeros (sh <= 0: the unit; >= 4: zeros).
+// (selections one on top of the other, on lanes: nested ones become branches on lanes, and a loop that has such a branch anywhere is
+// rearranged so that its way out meets the way round, where the compiler then waits for loads that it could leave in flight)
+__device__ __forceinline__ float4 shift_unit(float4 v, int sh)
+{
+    const bool one = (sh & 1) != 0 && sh > 0, two = (sh & 2) != 0 && sh > 0, none = sh >= 4;
+    v = make_float4(one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? 0.f : v.w);
+    v = make_float4(two ? v.z : v.x, two ? v.w : v.y, two ? 0.f : v.z, two ? 0.f : v.w);
+    return make_float4(none ? 0.f : v.x, none ? 0.f : v.y, none ? 0.f : v.z, none ? 0.f : v.w);
+}
+
 // Exact three-way split of four floats by truncation: a1 = the upper 16 bits of a, a2 = the
 // upper 16 bits of a - a1, a3 = a - a1 - a2 (which has at most 8 significant bits left, so its
 // upper 16 bits hold it exactly).  Only full-rate integer/float VALU operations are used; two
 // bf16 values are packed with one byte permute.
-__device__ __forceinline__ Split4 split3(float4 v)
+__device__ __forceinline__ void split3_one(float x, unsigned &h, unsigned &m, unsigned &l)
 {
-    const unsigned x[4] = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-    unsigned h[4], m[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        h[i] = x[i] & 0xffff0000u;
-        const float r1 = __uint_as_float(x[i]) - __uint_as_float(h[i]);
-        m[i] = __float_as_uint(r1) & 0xffff0000u;
-        const float r2 = r1 - __uint_as_float(m[i]);
-        l[i] = __float_as_uint(r2);
-    }
+    h = __float_as_uint(x) & 0xffff0000u;
+    const float r1 = x - __uint_as_float(h);
+    m = __float_as_uint(r1) & 0xffff0000u;
+    l = __float_as_uint(r1 - __uint_as_float(m));
+}
+__device__ __forceinline__ Split4 split3_pack(const unsigned (&h)[4], const unsigned (&m)[4], const unsigned (&l)[4])
+{
     // bytes 2,3 of the first source become the low half, bytes 2,3 of the second the high half
     union { unsigned u[2]; bf16x4 b; } ph, pm, pl;
     ph.u[0] = __builtin_amdgcn_perm(h[1], h[0], 0x07060302u); ph.u[1] = __builtin_amdgcn_perm(h[3], h[2], 0x07060302u);
@@ -55,6 +63,13 @@ __device__ __forceinline__ Split4 split3(float4 v)
     Split4 o;
     o.p[0] = ph.b; o.p[1] = pm.b; o.p[2] = pl.b;
     return o;
+}
+__device__ __forceinline__ Split4 split3(float4 v)
+{
+    unsigned h[4], m[4], l[4];
+    split3_one(v.x, h[0], m[0], l[0]); split3_one(v.y, h[1], m[1], l[1]);
+    split3_one(v.z, h[2], m[2], l[2]); split3_one(v.w, h[3], m[3], l[3]);
+    return split3_pack(h, m, l);
 }
 
 // Two-plane split into fp16: with the operand (the whole matrix, or one row of it) scaled by a power

@@ -17,7 +17,7 @@
 // 104 us, 990 TFLOP/s of fp16 matrix work (a large fp16 library product reaches 1200 on this card).
 //
 // A workgroup is four consumer wavefronts (32 columns each) and four producer wavefronts (load, split, store to LDS);
-// BM = 64 rows by default, 32 where 64-row tiles would leave CUs idle.  At most 128 registers: two workgroups share a
+// BM = 64 rows by default, 32 (gemm_pk32_tile) where 64-row tiles would leave CUs idle.  At most 128 registers: two workgroups share a
 // CU, and the first loads, the stores and the scans of one overlap the K loop of the other.
 #pragma once
 
@@ -28,6 +28,8 @@ namespace ssm {
 
 constexpr int PK_BN = 128, PK_CONSUMERS = 4, PK_PRODUCERS = 4, PK_STAGES = 2;
 constexpr int PK_THREADS = 64 * (PK_CONSUMERS + PK_PRODUCERS);
+constexpr int PK32_WAVES = 8;                        // tiles of 32 rows: wavefronts that multiply
+constexpr int PK32_SHORT = 128, PK32_LONG = 256;     // and k per stage
 
 // Place of an element of the output tile staged in LDS: rows of BN floats, pieces of 32 (rows, at 32 columns) swapped in rows
 // 4 .. 7 of every eight, so that the two groups of rows that a wavefront stores at once meet different banks.
@@ -207,16 +209,15 @@ __device__ __forceinline__ ScanFlags<ROWS> scan_flags(const ScanEpilogue &a, con
     return f;
 }
 
-// the maximum over the 64 lanes, in all of them
-__device__ __forceinline__ unsigned wave_max(unsigned v)
+// the maximum over sixteen lanes, and over the 64, in all of them
+__device__ __forceinline__ unsigned row16_max(unsigned v)
 {
-    v = max(v, dpp_move<0xb1>(v));
-    v = max(v, dpp_move<0x4e>(v));
-    v = max(v, dpp_move<0x124>(v));
-    v = max(v, dpp_move<0x128>(v));
-    v = lane_xor_max<16>(v);
-    return lane_xor_max<32>(v);
+    v = max(v, dpp_move<0xb1>(v));                                    // quad_perm [1,0,3,2]
+    v = max(v, dpp_move<0x4e>(v));                                    // quad_perm [2,3,0,1]
+    v = max(v, dpp_move<0x124>(v));                                   // row_ror:4
+    return max(v, dpp_move<0x128>(v));                                // row_ror:8
 }
+__device__ __forceinline__ unsigned wave_max(unsigned v) { return lane_xor_max<32>(lane_xor_max<16>(row16_max(v))); }
 
 // The tile is staged in lds.tile on entry.  REV: chi_t = gx_t + [not is_first_{t+1}] conj(Abar) chi_{t+1}, which walks
 // time backwards (later chunks and later tiles are the predecessors) and also reduces
@@ -464,7 +465,7 @@ __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds
 // ---------------------------------------------------------------------------------------------
 template <int BM, int BN, int EPI>
 struct StoreInputs {
-    static constexpr int KW = 128 / BN, LANES = BN / 4;                  // partial tiles to add up, lanes that share a row
+    static constexpr int KW = BM == 32 ? PK32_WAVES * 32 / BN : 1, LANES = BN / 4;      // partial tiles to add up, lanes that share a row
     static constexpr int ALL = BM * BN / 4 < PK_THREADS ? 1 : BM * BN / 4 / PK_THREADS;      // units of four columns per thread,
     static constexpr int UNITS = ALL < 4 ? ALL : 4, BATCHES = ALL / UNITS;      // in batches of at most four
     static constexpr bool HAS_E = EPI >= 1 && EPI <= 6, HAS_E2 = EPI == 4, HAS_DIAG = EPI == 1 || EPI == 2 || EPI == 5 || EPI == 6;
@@ -480,6 +481,22 @@ struct StoreInputs {
     __device__ __forceinline__ void request(const PkDev &g, int tid, int batch, int m0, int n0)
     {
         const int col = n0 + 4 * (tid % LANES), n = g.N - col;
+        // a tile inside the result: the requests without a branch per unit and column (0.3 us of a launch of 9)
+        if (m0 + BM <= g.M && n0 + BN <= g.N) {
+#pragma unroll
+            for (int i = 0; i < UNITS; ++i) {
+                const int r = row_of(tid, batch, i);
+                const long row = m0 + (BM * BN / 4 < PK_THREADS ? min(r, BM - 1) : r);          // (threads past the tile: any row of it)
+                e[i] = e2[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                dropped[i] = false;
+                if (HAS_E && (EPI != 5 || g.E)) e[i] = load4(g.E + row * g.lde + col, 4);
+                if (HAS_E2) e2[i] = load4(g.E2 + row * g.lde + col, 4);
+                if ((EPI == 2 || EPI == 5) && g.rowflag) dropped[i] = g.rowflag[row] != 0;
+            }
+            d = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (HAS_DIAG && (EPI != 5 || g.C2)) d = load4(g.diag + col, 4);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < UNITS; ++i) {
             const long row = m0 + row_of(tid, batch, i);
@@ -571,20 +588,18 @@ struct StoreInputs {
 // so that 16 lanes reading the same piece of 16 rows, and 32 lanes writing two neighbouring rows, meet every bank once.
 __device__ __forceinline__ int pk_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-template <int BM, int BN, int NPL, int EPI>
+template <int BM, int NPL, int EPI>
 __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tile, int tid)
 {
     constexpr int NC = PK_CONSUMERS, NP = PK_PRODUCERS, BK = PK_BK, NS = PK_STAGES, PT = 64 * NP;
     constexpr int S = BK;                         // row stride of an LDS plane in halves; see pk_swizzle
     constexpr int PLANE = BM * S, STAGE = NPL * PLANE;
     constexpr int MI = BM / 32, KS = BK / 16;
-    // BN < 128: the consumers of the same 32 columns share out the k steps of a K tile
-    constexpr int CG = BN / 32, KW = NC / CG, KSW = KS / KW;
-    static_assert(BN == 128 || BM == 32, "narrow tiles have 32 rows");
+    static_assert(PK_BN == 32 * NC && (BM == 64 || BM == 128), "32 columns per consumer");
     constexpr bool SCANS = EPI == 7 || EPI == 8;
     constexpr int RC = SCANS ? BM / SCAN_WAVES : 8, FR = SCANS ? BM : 64;      // (scans)
     static_assert(!SCANS || BM >= 64, "scanning tiles have 64 or 128 rows");
-    // k steps of the weights in flight: what 128 registers hold (at 32 rows eight measured no better than four)
+    // k steps of the weights in flight: what 128 registers hold
     constexpr int PFB = (NPL == 3 && MI == 2) || MI == 4 ? 2 : 4;
     static_assert(MI <= 2 || NPL == 2, "128 rows of three planes do not fit the registers");
     __bf16 *stages = reinterpret_cast<__bf16 *>(smem_raw);
@@ -595,13 +610,13 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     ScanSaved<RC> saved;
     ScanFlagBytes<FR> flag_bytes;
     ScanFlags<FR> flags;
-    StoreInputs<BM, BN, EPI> in;
+    StoreInputs<BM, PK_BN, EPI> in;
     if constexpr (SCANS) flag_bytes = scan_request_flags<FR, EPI == 8>(g.scan, l, m0, g.M);
 
     if (wave >= NC) {
         // ------------------------------------------------------------------ producers
         // a thread stages NV units of 1 row x 4 k per K tile; PF K tiles of loads in flight
-        constexpr int NV = BM * BK / 4 / PT, PF = BM == 32 ? 4 : 2;
+        constexpr int NV = BM * BK / 4 / PT, PF = 2;
         static_assert(NV * PT * 4 == BM * BK, "tile must be a multiple of the producers' units");
         const int pt = tid - 64 * NC;
         const int kq = 4 * (pt % (BK / 4)), r0 = pt / (BK / 4);
@@ -709,20 +724,19 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     } else {
         // ------------------------------------------------------------------ consumers
         const int li = l & 31, hh = l >> 5;
-        const int cg = wave % CG, kw = wave / CG;
-        const bool work = n0 + cg * 32 < g.N;       // (a wavefront whose 32 columns lie past N only attends the barriers)
+        const bool work = n0 + wave * 32 < g.N;       // (a wavefront whose 32 columns lie past N only attends the barriers)
         v16f acc[MI];
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
         const int nks = nk * KS;
-        const uint4 *bp = g.frag + ((size_t)(work ? n0 / 32 + cg : 0) * nks + kw * KSW) * (NPL * 64) + l;
-        int frag_at[KSW];
+        const uint4 *bp = g.frag + (size_t)(work ? n0 / 32 + wave : 0) * nks * (NPL * 64) + l;
+        int frag_at[KS];
 #pragma unroll
-        for (int ks = 0; ks < KSW; ++ks) frag_at[ks] = li * S + 8 * pk_swizzle(li, 2 * (kw * KSW + ks) + hh);
+        for (int ks = 0; ks < KS; ++ks) frag_at[ks] = li * S + 8 * pk_swizzle(li, 2 * ks + hh);
         uint4 fb[PFB][NPL];
-        constexpr int MG = MI < 2 ? MI : 2, NG = MI / MG;         // row fragments per step of the loop below, steps per k step
+        constexpr int MG = 2, NG = MI / MG;         // row fragments per step of the loop below, steps per k step
         bf16x8 fa[2][MG][NPL];
         auto load_weights = [&](int set, int s) {
 #pragma unroll
@@ -756,46 +770,37 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
         int eb = 0;                                   // log2 of the scale of this lane's weight row
         if (work) {
 #pragma unroll
-            for (int s = 0; s < PFB; ++s) load_weights(s, min(s / KSW, nk - 1) * KS + s % KSW);
-            if constexpr (NPL == 2) eb = g.bexp[n0 + cg * 32 + li];
+            for (int s = 0; s < PFB; ++s) load_weights(s, s);
+            if constexpr (NPL == 2) eb = g.bexp[n0 + wave * 32 + li];
         }
         __syncthreads();
         if constexpr (SCANS) flags = scan_flags<FR, EPI == 8>(g.scan, flag_bytes, m0);
         if (work) {
             load_rows(0, 0, 0, 0);
-            constexpr int KU = PFB > KSW ? PFB / KSW : 1;           // K tiles per round of the fragments' registers
-            for (int kt0 = 0; kt0 < nk; kt0 += KU) {
+            for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll
-                for (int u = 0; u < KU; ++u) {
-                    const int kt = kt0 + u;
-                    if (KU > 1 && kt >= nk) break;
-#pragma unroll
-                    for (int st = 0; st < KSW * NG; ++st) {
-                        // the row fragments of the next step are requested before the matrix instructions of this one; at the
-                        // last step of a K tile the workgroup barrier comes first: it releases the stage just read and
-                        // guarantees that the next one is filled
-                        const int ks = st / NG, ig = st % NG, set = (u * KSW + ks) % PFB, rs = (u * KSW * NG + st) & 1;
-                        if (st + 1 < KSW * NG) load_rows(rs ^ 1, kt, (st + 1) / NG, (st + 1) % NG);
-                        else {
-                            __syncthreads();
-                            load_rows(rs ^ 1, kt + 1, 0, 0);   // past the last tile: a harmless read of a stale stage
-                        }
-                        multiply(rs, set, ig);
-                        if (ig == NG - 1) {
-                            const int tn = kt + (ks + PFB) / KSW;
-                            load_weights(set, min(tn, nk - 1) * KS + (ks + PFB) % KSW);
-                        }
-                        // issue order: an LDS read in the shadow of each of the first matrix instructions, the loads of the
-                        // weights behind the last
-                        constexpr int NREAD = NPL * MG, NMFMA = (NPL == 3 ? 6 : 3) * MG;
-#pragma unroll
-                        for (int z = 0; z < NREAD; ++z) {
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                        }
-                        __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NREAD, 0);
-                        if (ig == NG - 1) __builtin_amdgcn_sched_group_barrier(0x020, NPL, 0);
+                for (int st = 0; st < KS * NG; ++st) {
+                    // the row fragments of the next step are requested before the matrix instructions of this one; at the
+                    // last step of a K tile the workgroup barrier comes first: it releases the stage just read and
+                    // guarantees that the next one is filled
+                    const int ks = st / NG, ig = st % NG, set = ks % PFB, rs = st & 1;
+                    if (st + 1 < KS * NG) load_rows(rs ^ 1, kt, (st + 1) / NG, (st + 1) % NG);
+                    else {
+                        __syncthreads();
+                        load_rows(rs ^ 1, kt + 1, 0, 0);   // past the last tile: a harmless read of a stale stage
                     }
+                    multiply(rs, set, ig);
+                    if (ig == NG - 1) load_weights(set, min(kt + (ks + PFB) / KS, nk - 1) * KS + (ks + PFB) % KS);
+                    // issue order: an LDS read in the shadow of each of the first matrix instructions, the loads of the
+                    // weights behind the last
+                    constexpr int NREAD = NPL * MG, NMFMA = (NPL == 3 ? 6 : 3) * MG;
+#pragma unroll
+                    for (int z = 0; z < NREAD; ++z) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NREAD, 0);
+                    if (ig == NG - 1) __builtin_amdgcn_sched_group_barrier(0x020, NPL, 0);
                 }
             }
         } else {
@@ -819,7 +824,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[kw * BM * BN + tile_at<BN>(row_of(i, r), cg * 32 + li)] = acc[i][r];
+            for (int r = 0; r < 16; ++r) out[tile_at(row_of(i, r), wave * 32 + li)] = acc[i][r];
         if constexpr (!SCANS && MI == 4) in.request(g, tid, 0, m0, n0);
         __syncthreads();                                 // barrier 2: the tile is staged
     }
@@ -833,6 +838,243 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
             in.store(g, reinterpret_cast<const float *>(smem_raw), tid, batch, m0, n0);
         }
     }
+}
+
+// Tiles of 32 rows: launches that leave a workgroup a CU to itself, whose time is a chain of dependent steps rather than
+// throughput.  All eight wavefronts load, split and multiply.  A stage is 256 k of all rows, double-buffered in LDS, with one meeting of the
+// workgroup per stage; wavefronts that share 32 columns take every KW-th k step, and their partial tiles are added up as they are stored.
+//   The two wavefronts of a SIMD do the same thing at the same time, so what is not interleaved in each of them does not overlap: the
+// split of the next stage goes on in pieces of four instructions behind the matrix instructions, which wait for one another, and a unit's
+// registers are requested again (two stages ahead) as soon as it is stored.  The workgroup meets before the last k step of a stage, whose fragments
+// are in registers by then, so that the first fragments of the next stage come in its shadow.
+// Bound by what the L2 hands a CU (64 columns of three planes: 512 bytes per k, 125 bytes per ns) and by the matrix cores at the
+// clock that such a launch gets (1.7 - 1.9 GHz).  Launches, first start to last end, with four wavefronts that staged 64 k at a time for four that
+// multiplied, and now: 1024 x 512 x 1024: 9.4 and 8.5 us; 256 x 512 x 1024: 8.2 and 6.1; 64 x 512 x 1024: 7.2 and 4.9.
+//   A wait counts the requests made behind the one it is for.  So that the compiler finds the same order in every round of the loop, the
+// first stage stands in front of it, the loop has a single way out, and there is no branch on lanes in it.
+// AHEAD: k steps of the weights in flight: four; two beside a reduction, whose sixteen wavefronts leave each 128 registers
+template <int BN, int NPL, int EPI, int KC, int AHEAD>
+__device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tid)
+{
+    constexpr int BM = 32, S = KC, PLANE = BM * S, STAGE = NPL * PLANE, KS = KC / 16;
+    constexpr int CG = BN / 32, KW = PK32_WAVES / CG, KSW = KS / KW;         // column groups, wavefronts per group, k steps per wavefront and stage
+    constexpr int PFB = KSW < AHEAD ? KSW : AHEAD;
+    constexpr int RL = 32, NR = 2, NV = NR * (KC / 128);                     // lanes that share 128 k of a row, rows and units of a thread
+    static_assert(PK_THREADS / RL * NR == BM && (KC == 128 || KC == 256) && KSW % PFB == 0, "units, register sets");
+    __bf16 *stages = reinterpret_cast<__bf16 *>(smem_raw);
+    int *rowexp = reinterpret_cast<int *>(stages + 2 * STAGE);               // [BM] log2 of the scale of every row (two planes)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, li = l & 31, hh = l >> 5;
+    const int cg = wave % CG, kw = wave / CG;
+    const int nks = g.nkt * (PK_BK / 16), nst = (nks + KS - 1) / KS;         // k steps; stages
+    // piece c (16 bytes) of row r: permuted so that sixteen lanes that read the same piece of sixteen rows meet every bank once
+    auto place = [](int r, int c) { return r * S + 8 * (c ^ (r & 15)); };
+
+    // ---- the rows (a unit that hangs over the end of its row reads the row's last four values, see PkUnits)
+    const int kl = tid % RL, kq = 4 * kl, r0 = tid / RL;                     // units 0 and 1: rows r0 and r0 + 16; 2 and 3: 128 k on
+    const PkUnits units(g.K, g.lda);
+    const char *src = units.base(g.A + (long)m0 * g.lda, g.frag);
+    unsigned row_at[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) row_at[i] = units.row(r0 + 16 * i, g.M - m0);
+    float4 r[NV];
+    auto k_of = [&](int i, int t) { return t * KC + 128 * (i / NR) + kq; };
+    auto fetch = [&](int i, int t) {                                         // unit i of stage t
+        const f32x4u v = *reinterpret_cast<const f32x4u *>(src + (row_at[i % NR] + units.k(0, k_of(i, t))));
+        r[i] = make_float4(v.x, v.y, v.z, v.w);
+    };
+    const bool narrow = units.narrow;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) fetch(i, 0);
+    if (narrow) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const float *row = g.A + (long)(m0 + min(r0 + 16 * i, g.M - 1 - m0)) * g.lda;
+            float v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = kq + j < g.K ? row[kq + j] : 0.f;
+            r[i] = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    }
+    unsigned rw[NR];
+    if constexpr (NPL == 2) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const unsigned *w = g.rows + min(m0 + r0 + 16 * i, g.M - 1);
+            rw[i] = w[(long)min(kl, g.row_parts - 1) * g.row_stride];
+            for (int j = kl + RL; j < g.row_parts; j += RL) rw[i] = max(rw[i], w[(long)j * g.row_stride]);
+        }
+    }
+    // ---- the weights: k step j of this wavefront is step kw + KW j of the product
+    const bool work = n0 + cg * 32 < g.N;           // (a wavefront whose 32 columns lie past N multiplies the first ones and stores nothing)
+    const uint4 *bp = g.frag + (size_t)(work ? n0 / 32 + cg : 0) * nks * (NPL * 64);       // (a uniform address per step, the lane as its offset)
+    uint4 fb[PFB][NPL];
+    auto load_weights = [&](int set, int j) {
+        const uint4 *q = bp + (size_t)min(kw + KW * j, nks - 1) * (NPL * 64);
+#pragma unroll
+        for (int p = 0; p < NPL; ++p) fb[set][p] = q[p * 64 + l];
+    };
+    int eb = 0;                                     // log2 of the scale of this lane's weight row
+    if constexpr (NPL == 2) { if (work) eb = g.bexp[n0 + cg * 32 + li]; }
+#pragma unroll
+    for (int j = 0; j < PFB; ++j) load_weights(j, j);
+
+    float sc[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        sc[i] = 1.f;
+        if constexpr (NPL == 2) {
+            const int e = log2_scale_of(lane_xor_max<16>(row16_max(rw[i])));
+            sc[i] = pow2f(e);
+            if (kl == 0) rowexp[r0 + 16 * i] = e;
+        }
+    }
+    const bool cut = g.K % KC != 0 && !narrow;
+    // units of stage t that hang over: moved into place, zeros past the end of the row
+    auto shift = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) r[i] = shift_unit(r[i], k_of(i, t) - units.klast);
+    };
+    // The split of a thread's units in pieces: three planes: an element (four instructions), or a unit's six packed words and their
+    // stores; two planes: a unit.
+    constexpr int PER_UNIT = NPL == 3 ? 5 : 1, PIECES = NV * PER_UNIT;
+    unsigned h[4], m[4], lo[4];
+    auto piece = [&](__bf16 *st, int k) {
+        const int i = k / PER_UNIT, e = k % PER_UNIT;
+        if (NPL == 3 && e < 4) {
+            const float x = e == 0 ? r[i].x : e == 1 ? r[i].y : e == 2 ? r[i].z : r[i].w;
+            split3_one(x, h[e], m[e], lo[e]);
+        } else {
+            const Split4 sp = NPL == 3 ? split3_pack(h, m, lo) : split2_f16_mix(r[i], sc[i % NR]);
+            __bf16 *at = st + place(r0, kq / 8) + kq % 8 + 16 * (i % NR) * S + 128 * (i / NR);        // (16 rows or 128 k on: the same permutation)
+#pragma unroll
+            for (int p = 0; p < NPL; ++p) *reinterpret_cast<bf16x4 *>(at + p * PLANE) = sp.p[p];
+        }
+    };
+    v16f acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    // fragment of a k step of the stage in LDS: row li, k = 16 ks + 8 hh ..
+    int frag_at[KSW];
+#pragma unroll
+    for (int j = 0; j < KSW; ++j) frag_at[j] = place(li, 2 * (kw + KW * j) + hh);
+    bf16x8 fa[2][NPL];
+    auto load_rows = [&](int set, const __bf16 *st, int j) {
+#pragma unroll
+        for (int p = 0; p < NPL; ++p) fa[set][p] = *reinterpret_cast<const bf16x8 *>(st + p * PLANE + frag_at[j]);
+    };
+    // product q of a k step, smallest first (the order of gemm_pk_tile)
+    constexpr int NPROD = NPL == 3 ? 6 : 3;
+    auto multiply = [&](int sa, int sb, int q) {
+        constexpr int PA3[6] = {2, 1, 0, 1, 0, 0}, PB3[6] = {0, 1, 2, 0, 1, 0};
+        constexpr int PA2[3] = {1, 0, 0}, PB2[3] = {0, 1, 0};
+        if constexpr (NPL == 3)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[sa][PA3[q]], __builtin_bit_cast(bf16x8, fb[sb][PB3[q]]), acc, 0, 0, 0);
+        else
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[sa][PA2[q % 3]]),
+                                                         __builtin_bit_cast(f16x8, fb[sb][PB2[q % 3]]), acc, 0, 0, 0);
+    };
+    // pieces [k0, k1) of what goes to st, those behind matrix instruction n of m
+    auto pieces_behind = [&](__bf16 *st, int k0, int k1, int n, int m, int refill) {
+#pragma unroll
+        for (int k = 0; k < PIECES; ++k)
+            if (k >= k0 + (n * (k1 - k0) + m - 1) / m && k < k0 + ((n + 1) * (k1 - k0) + m - 1) / m) {
+                piece(st, k);
+                if (k % PER_UNIT == PER_UNIT - 1) fetch(k / PER_UNIT, refill);
+            }
+    };
+    // Multiplies stage t from k step JB on, whose fragments are in registers, and puts stage t + 1 into the other half of LDS.
+    auto stage = [&](int t, auto from) {
+        constexpr int JB = decltype(from)::value, NM = (KSW - 1 - JB) * NPROD;     // matrix instructions in front of the meeting
+        const __bf16 *cur = stages + (t & 1) * STAGE;
+        __bf16 *next = stages + ((t & 1) ^ 1) * STAGE;
+        if (cut && t + 2 == nst) shift(t + 1);
+        if constexpr (NM == 0) pieces_behind(next, 0, PIECES, 0, 1, t + 2);
+#pragma unroll
+        for (int j = JB; j < KSW; ++j) {
+            if (j + 1 < KSW) load_rows((j + 1) & 1, cur, j + 1);
+            else {
+                __syncthreads();
+                load_rows(0, next, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < NPROD; ++q) {
+                multiply(j & 1, j % PFB, q);
+                if (j + 1 < KSW) pieces_behind(next, 0, PIECES, (j - JB) * NPROD + q, NM > 0 ? NM : 1, t + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            load_weights(j % PFB, t * KSW + j + PFB);
+        }
+    };
+    // the last stage: no further one, and no k steps past the end
+    auto last = [&](auto from) {
+        constexpr int JB = decltype(from)::value;
+        const __bf16 *cur = stages + ((nst - 1) & 1) * STAGE;
+#pragma unroll
+        for (int j = JB; j < KSW; ++j) {
+            if (j + 1 < KSW) load_rows((j + 1) & 1, cur, j + 1);
+            if ((nst - 1) * KS + KW * j + kw < nks) {
+#pragma unroll
+                for (int q = 0; q < NPROD; ++q) multiply(j & 1, j % PFB, q);
+            }
+            if (j + PFB < KSW) load_weights(j % PFB, (nst - 1) * KSW + j + PFB);
+        }
+    };
+    // The first stage in halves, so that 128 k are multiplied while the other 128 are split (K is longer than 128 there); not beside a
+    // reduction, where the further copies of the code take more registers than a wavefront has.
+    constexpr bool HALVES = KC == 256 && AHEAD == 4;
+    constexpr int HALF_STAGE = HALVES ? PIECES / 2 : PIECES;
+    StoreInputs<BM, BN, EPI> in;
+    if (cut && nst == 1) shift(0);
+#pragma unroll
+    for (int k = 0; k < HALF_STAGE; ++k) pieces_behind(stages, k, k + 1, 0, 1, 1);
+    __syncthreads();
+    load_rows(0, stages, 0);
+    if constexpr (!HALVES) {
+        if constexpr (KSW % 2 == 0) {                     // (a single k step per wavefront and stage: only where one stage is all)
+            if (nst > 1) stage(0, std::integral_constant<int, 0>{});
+            for (int t = 1; t + 1 < nst; ++t) stage(t, std::integral_constant<int, 0>{});
+        }
+        in.request(g, tid, 0, m0, n0);
+        last(std::integral_constant<int, 0>{});
+    } else {
+        constexpr int JB = KSW / 2;
+#pragma unroll
+        for (int j = 0; j < JB; ++j) {
+            if (j + 1 < JB) load_rows((j + 1) & 1, stages, j + 1);
+#pragma unroll
+            for (int q = 0; q < NPROD; ++q) {
+                multiply(j & 1, j % PFB, q);
+                pieces_behind(stages, HALF_STAGE, PIECES, j * NPROD + q, JB * NPROD, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            load_weights(j % PFB, j + PFB);
+        }
+        __syncthreads();
+        load_rows(JB & 1, stages, JB);
+        if (nst == 1) {
+            in.request(g, tid, 0, m0, n0);
+            last(std::integral_constant<int, JB>{});
+        } else {
+            stage(0, std::integral_constant<int, JB>{});
+            for (int t = 1; t + 1 < nst; ++t) stage(t, std::integral_constant<int, 0>{});
+            in.request(g, tid, 0, m0, n0);
+            last(std::integral_constant<int, 0>{});
+        }
+    }
+    if constexpr (NPL == 2) {
+        // (see gemm_pk_tile)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = __builtin_ldexpf(acc[e], -(rowexp[8 * (e / 4) + 4 * hh + (e % 4)] + eb));
+    }
+    constexpr bool HALF = PK32_WAVES * 1024 * 4 <= STAGE * 2;                    // the parts fit the half of the stages that nobody reads any more
+    static_assert(HALF || PK32_WAVES * 1024 * 4 <= 2 * STAGE * 2, "or all of them");
+    if constexpr (!HALF) __syncthreads();
+    float *out = reinterpret_cast<float *>(stages + (HALF ? (nst & 1) * STAGE : 0));
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[kw * BM * BN + tile_at<BN>(8 * (e / 4) + 4 * hh + (e % 4), cg * 32 + li)] = acc[e];
+    __syncthreads();
+    static_assert(in.BATCHES == 1, "a unit or two per thread");
+    in.store(g, out, tid, 0, m0, n0);
 }
 
 // Tile of the workgroup in slot q of XCD x (workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2):
@@ -853,10 +1095,11 @@ __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
     return (uid < g.sc_units && tn < g.ntn) ? (b * g.sc_nt + tmL) * g.ntn + tn : g.ntm * g.ntn;
 }
 
-constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, bool scans)
+// kc: k per stage
+constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, bool scans, int kc)
 {
-    const size_t st = (size_t)PK_STAGES * NPL * BM * PK_BK * 2 + (size_t)BM * 4;       // stages and scales
-    const size_t ep = scans ? scan_lds_bytes(BM) : (size_t)BM * BN * 4 * (128 / BN);             // the staged tile
+    const size_t st = (size_t)PK_STAGES * NPL * BM * kc * 2 + (size_t)BM * 4;          // stages and scales
+    const size_t ep = scans ? scan_lds_bytes(BM) : (size_t)BM * BN * 4 * (BM == 32 ? PK32_WAVES * 32 / BN : 1);      // the staged tile (or its parts)
     return ep > st ? ep : st;
 }
 
@@ -874,7 +1117,11 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
         const int tile = pk_place(g, x, q - g.slot0);
         if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
         const int tm = tile / g.ntn, tn = tile - tm * g.ntn;
-        gemm_pk_tile<BM, BN, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid);
+        if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid);
+        else if constexpr (BM == 32) {
+            if (g.K <= PK32_SHORT) gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid);
+            else gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid);
+        } else gemm_pk_tile<BM, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid);
     } else if constexpr (TNB > 0) {
         if (q >= t0.slot0 && q < t0.slot0 + t0.nx) gemm_tn_problem<TNB, NPL>(t0, smem_raw, x, q - t0.slot0, tid);
         // (a branch of its own: choosing between the two argument structs at run time would put them on the stack)
@@ -928,11 +1175,14 @@ hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArg
         }
     }
     if (tn_first) { g.slot0 = (int)slots; slots += g.nx; }
-    constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI == 7 || EPI == 8), tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL) : 0;
-    constexpr size_t smem = pk > tnl ? pk : tnl;
+    constexpr size_t tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL) : 0;
+    constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI == 7 || EPI == 8, BM == 32 ? PK32_LONG : PK_BK);
+    constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, false, PK32_SHORT) : pk;
+    constexpr size_t most = pk > tnl ? pk : tnl;
+    const size_t smem = tnl > pk_short ? most : (BM == 32 && ((BN == 64 && WPE == 4 && TNB == 0) || a.K <= PK32_SHORT)) ? pk_short : most;
     auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE>;
     static std::atomic<bool> raised[KERNEL_MAXDEV];
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), smem, raised);
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), most, raised);
     if (e != hipSuccess) return e;
     if (slots <= 0 || slots > 0x7fffffffL / 8) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(pk_threads(TNB)), smem, s, g, t[0], t[1]);

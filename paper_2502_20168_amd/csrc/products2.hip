@@ -7,7 +7,7 @@ namespace ssm {
 hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s)
 {
     const PkTile t = product_tile(a, b, c);
-#define SSM_PK(rows, cols, epi, tnb) launch_pk_variant<rows, cols, 2, epi, tnb, 4>(a, b, c, tn_first, s)
+#define SSM_PK(rows, cols, epi, tnb) launch_pk_variant<rows, cols, 2, epi, tnb, (rows) == 32 ? 2 : 4>(a, b, c, tn_first, s)
 #define SSM_TALL(epi, tnb) return t.rows <= 64 ? SSM_PK(64, 128, epi, tnb) : SSM_PK(128, 128, epi, tnb)
 #define SSM_ALONE(epi) \
     case epi: \

@@ -12,9 +12,12 @@ hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const Gem
     if (t.rows == 32) return t.cols == 32 ? SSM_PK(32, 32, epi, tnb, wpe) : t.cols == 64 ? SSM_PK(32, 64, epi, tnb, wpe) : SSM_PK(32, 128, epi, tnb, wpe)
 #define SSM_ALONE(epi) \
     case epi: \
-        SSM_SMALL(epi, 0, 4); \
+        if (many) return SSM_PK(32, 64, epi, 0, 4); \
+        SSM_SMALL(epi, 0, 2); \
         return SSM_PK(64, 128, epi, 0, 4)
     if (!b) {
+        // more workgroups than CUs (at most 64 columns, many rows): short stages, two workgroups per CU
+        const bool many = t.rows == 32 && t.cols == 64 && (int64_t)((a.M + 31) / 32) * ((a.N + 63) / 64) > 256;
         switch (a.epilogue) {
         SSM_ALONE(0); SSM_ALONE(1); SSM_ALONE(2); SSM_ALONE(3); SSM_ALONE(5); SSM_ALONE(6);
         default: return hipErrorInvalidValue;

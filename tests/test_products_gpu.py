@@ -61,3 +61,34 @@ def test_states_do_not_depend_on_the_tile_of_the_launch():
     for k in ("x", "x_last"):
         assert torch.equal(big[k][:6], small[k]) and torch.equal(big[k][6:12], small[k]), k
     assert torch.equal(gb["dx0"][:6], gs["dx0"]) and torch.equal(gb["dx0"][6:12], gs["dx0"])
+
+
+# Tiles of 32 rows: K around the short stage of 128 k, the long one of 256 and their halves, in either of the two products of a
+# step (H, then 2 P), one to three groups of columns, rows that end inside a tile
+STEP_SHAPES = [(5, 127, 64), (33, 128, 65), (33, 129, 64), (64, 130, 96), (31, 191, 127), (40, 192, 128), (65, 256, 130), (1, 257, 129), (2, 260, 191),
+               (100, 383, 192), (96, 512, 257), (130, 515, 33), (520, 64, 60), (1024, 320, 160), (600, 1030, 40)]
+
+
+@pytest.mark.parametrize("shape", STEP_SHAPES, ids=["x".join(map(str, s)) for s in STEP_SHAPES])
+def test_steps_on_tiles_of_32_rows(shape):
+    """Two steps and the adjoint of one against float64: sums of K products of order one, each rounded by 2^-24 of the running sum, and the
+    dropped parts of the split below 2^-23 of the terms: 1e-6 of the norm leaves a factor of two or more at K = 1030."""
+    import torch
+    Bt, H, P = shape
+    print(shape, flush=True)
+    d = ssm.to_device(wl.gen_inputs(wl.custom("step", Bt, 2, H, P, p_reset=0.3, with_x0=True, seed=23)))
+    plan = ssm.ssm_step_prepare(d["Lambda"], d["B"], d["C"], d["log_delta"])
+    A, B = (t.to(torch.complex128) for t in ssm.ssm_discretize(d["Lambda"], d["B"], d["log_delta"]))
+    C, D = d["C"].to(torch.complex128), d["D"].double()
+    x, ref = d["x0"], d["x0"].to(torch.complex128)
+    close = lambda got, want: float((got.to(want.dtype) - want).norm() / want.norm()) < 1e-6
+    for t in range(2):
+        u, first = d["u"][:, t].contiguous(), d["is_first"][:, t].contiguous()
+        x, y = ssm.ssm_step(plan, d["D"], u, x, first, P=P)
+        ref = u.to(torch.complex128) @ B.T.contiguous() + torch.where(first[:, None] != 0, 0.0, A[None] * ref)
+        assert close(x, ref) and close(y, (ref @ C.T.contiguous()).real + D * u.double())
+    dy, dx = d["dy"][:, 0].contiguous(), d["x0"]
+    gx, du, dxp = ssm.ssm_step_bwd(plan, d["D"], dy, dx, first, P=P)
+    g = dy.to(torch.complex128) @ C.conj().contiguous() + dx.to(torch.complex128)
+    assert close(gx, g) and close(du, (g @ B.conj().contiguous()).real + D * dy.double())
+    assert close(dxp, torch.where(first[:, None] != 0, 0.0, A.conj()[None] * g))
