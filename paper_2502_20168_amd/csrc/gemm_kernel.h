@@ -222,9 +222,7 @@ struct SplitLoader {
         const int sh = row0 + 4 * (tid % (R / 4)) - (rows - 4);
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const float4 v = r[i];
-            r[i] = make_float4(sh <= 0 ? v.x : (sh == 1 ? v.y : (sh == 2 ? v.z : v.w)), sh <= 0 ? v.y : (sh == 1 ? v.z : v.w),
-                               sh <= 0 ? v.z : v.w, v.w);
+            r[i] = shift_unit(r[i], sh);
         }
     }
     // zeroes what lies past the end of the range in the tile at k0 (its last)
@@ -368,16 +366,21 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
         stash(0, 0);
         fetch(0, PF);
         __syncthreads();
-        // iteration kt stages tile kt + 1 from register set (kt + 1) % PF while the consumers work on tile kt
-        for (int kt = 0; kt + 1 < nk; kt += PF) {
+        // step kt stages tile kt + 1 from register set (kt + 1) % PF while the consumers work on tile kt (whole rounds, then
+        // what is left: see gemm_pk_tile)
+        auto step = [&](int kt, int j) {
+            stash((j + 1) % PF, kt + j + 1);
+            fetch((j + 1) % PF, kt + j + 1 + PF);
+            __syncthreads();
+        };
+        int kt = 0;
+        for (; kt + PF < nk; kt += PF) {
 #pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                if (kt + j + 1 >= nk) break;
-                stash((j + 1) % PF, kt + j + 1);
-                fetch((j + 1) % PF, kt + j + 1 + PF);
-                __syncthreads();
-            }
+            for (int j = 0; j < PF; ++j) step(kt, j);
         }
+#pragma unroll
+        for (int j = 0; j + 1 < PF; ++j)
+            if (kt + j + 1 < nk) step(kt, j);
         __syncthreads();
         if constexpr (KG > 1) __syncthreads();
         return;

@@ -588,6 +588,20 @@ struct StoreInputs {
 // so that 16 lanes reading the same piece of 16 rows, and 32 lanes writing two neighbouring rows, meet every bank once.
 __device__ __forceinline__ int pk_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
 
+// Four values from k on of a row of fewer than four.  (Waited for here: left outstanding, they would make the path without them wait for
+// everything it has requested since.)
+__device__ __forceinline__ float4 narrow_unit(const PkDev &g, int row, int k)
+{
+    const float *p = g.A + (long)row * g.lda;
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[j] = k + j < g.K ? p[k + j] : 0.f;
+        asm volatile("" : "+v"(v[j]));
+    }
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 template <int BM, int NPL, int EPI>
 __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tile, int tid)
 {
@@ -655,18 +669,11 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
             }
         }
         const bool narrow = units.narrow;
+#pragma unroll
+        for (int j = 0; j < PF; ++j) fetch(j, j);
         if (narrow) {
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const float *row = g.A + (long)(m0 + min(r0 + i * RSTEP, g.M - 1 - m0)) * g.lda;
-                float v[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = kq + j < g.K ? row[kq + j] : 0.f;
-                r[0][i] = make_float4(v[0], v[1], v[2], v[3]);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < PF; ++j) fetch(j, j);
+            for (int i = 0; i < NV; ++i) r[0][i] = narrow_unit(g, m0 + min(r0 + i * RSTEP, g.M - 1 - m0), kq);
         }
         if constexpr (NPL == 2) {
 #pragma unroll
@@ -686,12 +693,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
             if (t == ktail) {
                 const int sh = t * BK + kq - units.klast;              // > 0: the unit was read sh values early; >= 4: it lies past the row
 #pragma unroll
-                for (int i = 0; i < NV; ++i) {
-                    const float4 v = r[set][i];
-                    r[set][i] = make_float4(sh <= 0 ? v.x : (sh == 1 ? v.y : (sh == 2 ? v.z : (sh == 3 ? v.w : 0.f))),
-                                            sh <= 0 ? v.y : (sh == 1 ? v.z : (sh == 2 ? v.w : 0.f)),
-                                            sh <= 0 ? v.z : (sh == 1 ? v.w : 0.f), sh <= 0 ? v.w : 0.f);
-                }
+                for (int i = 0; i < NV; ++i) r[set][i] = shift_unit(r[set][i], sh);
             }
             __bf16 *st = stages + (t % NS) * STAGE + r0 * S + 8 * pk_swizzle(r0, kq / 8) + kq % 8;      // (RSTEP rows on: the same)
 #pragma unroll
@@ -706,16 +708,22 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
         fetch(0, PF);
         __syncthreads();
         if constexpr (SCANS) flags = scan_flags<FR, EPI == 8>(g.scan, flag_bytes, m0);
-        // iteration kt stages tile kt + 1 from register set (kt + 1) % PF while the consumers work on tile kt
-        for (int kt = 0; kt + 1 < nk; kt += PF) {
+        // step kt stages tile kt + 1 from register set (kt + 1) % PF while the consumers work on tile kt.  (Whole rounds, then what
+        // is left: a loop with a second way out is rearranged so that its ways out meet the way round, where the compiler then waits
+        // for loads that it could leave in flight.)
+        auto step = [&](int kt, int j) {
+            stash((j + 1) % PF, kt + j + 1);
+            fetch((j + 1) % PF, kt + j + 1 + PF);
+            __syncthreads();
+        };
+        int kt = 0;
+        for (; kt + PF < nk; kt += PF) {
 #pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                if (kt + j + 1 >= nk) break;
-                stash((j + 1) % PF, kt + j + 1);
-                fetch((j + 1) % PF, kt + j + 1 + PF);
-                __syncthreads();
-            }
+            for (int j = 0; j < PF; ++j) step(kt, j);
         }
+#pragma unroll
+        for (int j = 0; j + 1 < PF; ++j)
+            if (kt + j + 1 < nk) step(kt, j);
         __syncthreads();
         if constexpr (EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
         if constexpr (!SCANS) in.request(g, tid, 0, m0, n0);
@@ -887,13 +895,7 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
     for (int i = 0; i < NV; ++i) fetch(i, 0);
     if (narrow) {
 #pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            const float *row = g.A + (long)(m0 + min(r0 + 16 * i, g.M - 1 - m0)) * g.lda;
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = kq + j < g.K ? row[kq + j] : 0.f;
-            r[i] = make_float4(v[0], v[1], v[2], v[3]);
-        }
+        for (int i = 0; i < NR; ++i) r[i] = narrow_unit(g, m0 + min(r0 + 16 * i, g.M - 1 - m0), kq);
     }
     unsigned rw[NR];
     if constexpr (NPL == 2) {
