@@ -3,6 +3,8 @@
 #include "../../include/ssm.h"
 #include "pack.h"
 
+#include <type_traits>
+
 namespace ssm {
 namespace {
 
@@ -16,67 +18,96 @@ inline bool misaligned(const void *p, size_t a) { return (reinterpret_cast<uintp
 // Time-major arrays [T, N]; one thread per trajectory walks time backwards.  Neighbouring
 // threads read neighbouring trajectories of the same step, so every access is one coalesced
 // row segment; the only serial dependency is one fused multiply-add per step.
+// At 65536 trajectories a SIMD has a single wavefront, so a launch lasts as long as that one's trips to memory and its
+// instructions one behind the other: the loads of eight steps are in flight together (then of four, two, one), and an address is a
+// uniform row and the thread as its offset.  With a 64-bit address per value and four steps in flight (forward) or what the
+// compiler made of a plain loop (adjoint), and now: 16 steps of 65536 trajectories 3.96 and 3.74 us, adjoint 6.16 and 5.25; 64 of 2048: 5.8
+// and 4.8, 12.3 and 6.6.  (Sixteen steps in flight: 3.8 and 5.5 us at the first; workgroups of 256: the same within 2 %, slower at few trajectories.)
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) lambda_return_kernel(const float *__restrict__ r, const float *__restrict__ c,
-                                                            const float *__restrict__ v, float gamma, float lam,
-                                                            long T, long N, float *__restrict__ ret)
+constexpr int LAMBDA_STEPS = 8, LAMBDA_THREADS = 64;
+__global__ void __launch_bounds__(LAMBDA_THREADS) lambda_return_kernel(const float *__restrict__ r, const float *__restrict__ c,
+                                                                       const float *__restrict__ v, float gamma, float lam,
+                                                                       long T, long N, float *__restrict__ ret)
 {
-    const long n = (long)blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    float V = v[(T - 1) * N + n];
-    ret[(T - 1) * N + n] = V;
+    // (rows from the workgroup's first trajectory on: a uniform address and the thread as its offset)
+    const long n0 = (long)blockIdx.x * LAMBDA_THREADS;
+    const unsigned n = threadIdx.x;
+    if (n0 + n >= N) return;
+    r += n0; c += n0; v += n0; ret += n0;
     const float gl = gamma * lam, g1 = gamma * (1.f - lam);
+    float V = (v + (T - 1) * N)[n];
+    (ret + (T - 1) * N)[n] = V;
     long t = T - 2;
-    for (; t >= 3; t -= 4) {
-        // the loads of four steps do not depend on V: issue them together
-        float rr[4], cc[4], vv[4];
+    auto steps = [&](auto count) {
+        constexpr int S = decltype(count)::value;
+        for (; t >= S - 1; t -= S) {
+            float rr[S], cc[S], vv[S];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const long i = (t - j) * N + n;
-            rr[j] = r[i]; cc[j] = c[i]; vv[j] = v[i];
-        }
+            for (int j = 0; j < S; ++j) {
+                const long o = (t - j) * N;
+                rr[j] = (r + o)[n]; cc[j] = (c + o)[n]; vv[j] = (v + o)[n];
+            }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            // r + c (g1 v) + (c gl) V
-            V = fmaf(cc[j] * gl, V, fmaf(cc[j], g1 * vv[j], rr[j]));
-            ret[(t - j) * N + n] = V;
+            for (int j = 0; j < S; ++j) {
+                // r + c (g1 v) + (c gl) V
+                V = fmaf(cc[j] * gl, V, fmaf(cc[j], g1 * vv[j], rr[j]));
+                (ret + (t - j) * N)[n] = V;
+            }
         }
-    }
-    for (; t >= 0; --t) {
-        const long i = t * N + n;
-        const float cv = c[i];
-        V = fmaf(cv * gl, V, fmaf(cv, g1 * v[i], r[i]));
-        ret[i] = V;
-    }
+    };
+    steps(std::integral_constant<int, LAMBDA_STEPS>{});
+    if constexpr (LAMBDA_STEPS > 8) steps(std::integral_constant<int, 8>{});
+    if constexpr (LAMBDA_STEPS > 4) steps(std::integral_constant<int, 4>{});
+    steps(std::integral_constant<int, 2>{});
+    steps(std::integral_constant<int, 1>{});
 }
 
 // Adjoint: G_t = dret_t + gamma lambda c_{t-1} G_{t-1} walks time forwards;
 // dr_t = G_t, dc_t = G_t gamma ((1-lambda) v_t + lambda V_{t+1}), dv_t = G_t gamma c_t (1-lambda) for t < T-1;
 // the last step has dv = G and no reward / continue gradient.
-__global__ void __launch_bounds__(256) lambda_return_bwd_kernel(const float *__restrict__ c, const float *__restrict__ v,
-                                                                const float *__restrict__ ret, const float *__restrict__ dret,
-                                                                float gamma, float lam, long T, long N,
-                                                                float *__restrict__ dr, float *__restrict__ dc,
-                                                                float *__restrict__ dv)
+__global__ void __launch_bounds__(LAMBDA_THREADS) lambda_return_bwd_kernel(const float *__restrict__ c, const float *__restrict__ v,
+                                                                           const float *__restrict__ ret, const float *__restrict__ dret,
+                                                                           float gamma, float lam, long T, long N,
+                                                                           float *__restrict__ dr, float *__restrict__ dc,
+                                                                           float *__restrict__ dv)
 {
-    const long n = (long)blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
+    const long n0 = (long)blockIdx.x * LAMBDA_THREADS;
+    const unsigned n = threadIdx.x;
+    if (n0 + n >= N) return;
+    c += n0; v += n0; ret += n0; dret += n0; dr += n0; dc += n0; dv += n0;
     const float gl = gamma * lam, g1 = gamma * (1.f - lam);
     float G = 0.f, cprev = 0.f;
-    for (long t = 0; t < T - 1; ++t) {
-        const long i = t * N + n;
-        const float cv = c[i];
-        G = fmaf(gl * cprev, G, dret[i]);
-        dr[i] = G;
-        dc[i] = G * fmaf(gl, ret[i + N], g1 * v[i]);
-        dv[i] = G * (g1 * cv);
-        cprev = cv;
-    }
-    const long i = (T - 1) * N + n;
-    G = fmaf(gl * cprev, G, dret[i]);
-    dr[i] = 0.f;
-    dc[i] = 0.f;
-    dv[i] = G;
+    long t = 0;
+    auto steps = [&](auto count) {
+        constexpr int S = decltype(count)::value;
+        for (; t + S < T; t += S) {
+            float cc[S], vv[S], rt[S], dd[S];
+#pragma unroll
+            for (int j = 0; j < S; ++j) {
+                const long o = (t + j) * N;
+                cc[j] = (c + o)[n]; vv[j] = (v + o)[n]; rt[j] = (ret + o + N)[n]; dd[j] = (dret + o)[n];
+            }
+#pragma unroll
+            for (int j = 0; j < S; ++j) {
+                const long o = (t + j) * N;
+                G = fmaf(gl * cprev, G, dd[j]);
+                (dr + o)[n] = G;
+                (dc + o)[n] = G * fmaf(gl, rt[j], g1 * vv[j]);
+                (dv + o)[n] = G * (g1 * cc[j]);
+                cprev = cc[j];
+            }
+        }
+    };
+    steps(std::integral_constant<int, LAMBDA_STEPS>{});
+    if constexpr (LAMBDA_STEPS > 8) steps(std::integral_constant<int, 8>{});
+    if constexpr (LAMBDA_STEPS > 4) steps(std::integral_constant<int, 4>{});
+    steps(std::integral_constant<int, 2>{});
+    steps(std::integral_constant<int, 1>{});
+    const long o = (T - 1) * N;
+    G = fmaf(gl * cprev, G, (dret + o)[n]);
+    (dr + o)[n] = 0.f;
+    (dc + o)[n] = 0.f;
+    (dv + o)[n] = G;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -335,8 +366,8 @@ ssm_status ssm_lambda_return(const float *reward, const float *cont, const float
     if (T > SSM_MAX_TOKENS || N > SSM_MAX_TOKENS || T > SSM_MAX_ELEMS / N) return SSM_ERR_UNSUPPORTED;
     if (misaligned(reward, 4) || misaligned(cont, 4) || misaligned(value, 4) || misaligned(ret, 4))
         return SSM_ERR_INVALID_ARG;
-    const unsigned blocks = (unsigned)((N + 255) / 256);
-    hipLaunchKernelGGL(lambda_return_kernel, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(stream),
+    const unsigned blocks = (unsigned)((N + LAMBDA_THREADS - 1) / LAMBDA_THREADS);
+    hipLaunchKernelGGL(lambda_return_kernel, dim3(blocks), dim3(LAMBDA_THREADS), 0, static_cast<hipStream_t>(stream),
                        reward, cont, value, gamma, lambda, (long)T, (long)N, ret);
     HIP_TRY(hipGetLastError());
     return SSM_OK;
@@ -352,8 +383,8 @@ ssm_status ssm_lambda_return_bwd(const float *cont, const float *value, const fl
     if (misaligned(cont, 4) || misaligned(value, 4) || misaligned(ret, 4) || misaligned(dret, 4) ||
         misaligned(dreward, 4) || misaligned(dcont, 4) || misaligned(dvalue, 4))
         return SSM_ERR_INVALID_ARG;
-    const unsigned blocks = (unsigned)((N + 255) / 256);
-    hipLaunchKernelGGL(lambda_return_bwd_kernel, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(stream),
+    const unsigned blocks = (unsigned)((N + LAMBDA_THREADS - 1) / LAMBDA_THREADS);
+    hipLaunchKernelGGL(lambda_return_bwd_kernel, dim3(blocks), dim3(LAMBDA_THREADS), 0, static_cast<hipStream_t>(stream),
                        cont, value, ret, dret, gamma, lambda, (long)T, (long)N, dreward, dcont, dvalue);
     HIP_TRY(hipGetLastError());
     return SSM_OK;

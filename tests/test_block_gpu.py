@@ -42,6 +42,13 @@ def test_lambda_return_matches_oracle(T, N):
     assert not dr[-1].any().item() and not dc[-1].any().item()
 
 
+# horizons around batches of eight, four, two and one step; trajectories around a workgroup's 64
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 16, 17, 18, 25, 64])
+@pytest.mark.parametrize("N", [1, 63, 65, 200])
+def test_lambda_return_batches_of_steps(T, N):
+    test_lambda_return_matches_oracle(T, N)
+
+
 def test_lambda_return_extremes_of_lambda():
     import torch
     from paper_2502_20168_amd import binding as ssm
