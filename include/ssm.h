@@ -161,10 +161,11 @@ ssm_status ssm_scan_states_reverse(const ssm_c64 *A_bar, ssm_c64 *gx, const ssm_
 /* ssm_scan_states for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels
  * and bit-identical results; the scratch (status header, ticket counters and look-back descriptors of
- * sequences longer than 256 steps) lives in a device array that is part of the library image, one
- * copy per GPU, SSM_NOALLOC_SCRATCH_BYTES long.  The call allocates nothing and frees nothing.
- * A shape whose scratch (ssm_workspace_bytes(Bt, L, 1, P, 0), about Bt * L * P / 8 bytes for L > 256,
- * 256 bytes otherwise) exceeds that size is refused with SSM_ERR_SCRATCH_LIMIT before any launch.
+ * long sequences) lives in a device array that is part of the library image, one copy per GPU,
+ * SSM_NOALLOC_SCRATCH_BYTES long.  The call allocates nothing and frees nothing.
+ * A shape whose scratch would exceed that size with a look-back over 256 steps at a time (about
+ * Bt * L * P / 8 bytes for L > 256, 256 bytes otherwise; its plan may need less) is refused with
+ * SSM_ERR_SCRATCH_LIMIT before any launch.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams,
  * two host threads) race on it and must be serialised by the caller; consecutive calls on one stream
  * are fine (what must start at zero is cleared by the call itself, with a kernel).

@@ -40,7 +40,12 @@ ssm_status ssm_scan_states_noalloc(const ssm_c64 *A_bar, ssm_c64 *v, const uint8
     ssm::ScanOnlyLayout lo;
     const int st = ssm::make_scan_layout(Bt, L, P, false, lo);
     if (st != SSM_OK) return (ssm_status)st;
-    if (lo.total > SSM_NOALLOC_SCRATCH_BYTES) return SSM_ERR_SCRATCH_LIMIT;
+    // The limit of this entry point is that of a look-back over 256 steps of 16 states at a time for every sequence longer than that,
+    // whether the plan of the shape has one or not: which shapes it takes does not follow the plan.
+    const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t chains = L <= 256 ? 0 : (size_t)((P + 15) / 16 * Bt);
+    const size_t look_back = up(sizeof(ssm::WsHeader)) + up(chains * ssm::SCAN_TICKET_STRIDE * sizeof(uint32_t)) + up(chains * ((L + 255) / 256) * 16 * sizeof(ssm::ScanDesc));
+    if (lo.total > SSM_NOALLOC_SCRATCH_BYTES || look_back > SSM_NOALLOC_SCRATCH_BYTES) return SSM_ERR_SCRATCH_LIMIT;
     void *ptr = scratch_of_current_device();
     if (!ptr) return SSM_ERR_HIP;
     return (ssm_status)ssm::scan_states_forward(A_bar, v, is_first, x0, Bt, L, P, x_last, ptr, SSM_NOALLOC_SCRATCH_BYTES,

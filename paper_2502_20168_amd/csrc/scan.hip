@@ -2,19 +2,17 @@
 //
 // What is computed: the inclusive scan of Eq. 4 over the elements (Abar, Bbar u_k, reset flag)
 // of Eq. 9 under the operator of Eq. 10.  For a diagonal Abar the products are element-wise, so
-// every (sequence, state) pair is an independent lane.  Three nested levels combine partial
-// results with that operator:
+// every (sequence, state) pair is an independent lane.  Partial results are combined with that operator:
 //   1. a thread walks SCAN_E consecutive steps held in registers (loads are coalesced over the
 //      state index: neighbouring threads own neighbouring states of the same step);
-//   2. the cy chunks of a workgroup exchange their (product, state) aggregates through LDS;
-//   3. workgroups along time exchange aggregates through descriptors in global memory with a
-//      decoupled look-back: each publishes its own aggregate before it waits for anything, then
-//      fetches the aggregates of the earlier workgroups of its group (one per thread, all in
+//   2. the chunks of a wavefront exchange their (product, state) aggregates between lanes, the wavefronts of a
+//      workgroup through LDS;
+//   3. a workgroup holds whole sequences, or (plan_scan) 1024, 512 or 256 steps of one: several workgroups along time
+//      exchange aggregates through descriptors in global memory with a decoupled look-back: each publishes its own aggregate
+//      before it waits for anything, then fetches the aggregates of the earlier workgroups of its group (one per thread, all in
 //      flight at once) plus the inclusive state that closes the previous group.
-// Logical time-block ids come from an atomic ticket per chain, so a workgroup only ever waits
+// With a look-back, logical time-block ids come from an atomic ticket per chain, so a workgroup only ever waits
 // for workgroups that started before it, and every wait is bounded by spin_limit.
-// Workgroups whose steps carry no flag at all take a guard-free path (plain recurrence, pointer
-// stepping, Abar^16 by squaring): the kernel is issue bound otherwise, not memory bound.
 //
 // The reverse scan runs the same operator over reversed time with conj(Abar):
 //   chi_t = gx_t + [not is_first_{t+1}] conj(Abar) chi_{t+1}
@@ -55,17 +53,19 @@ __device__ __forceinline__ unsigned group16_max(unsigned (&v)[16], int lane)
     return v[0];
 }
 __device__ __forceinline__ int group16_index(int lane) { return 8 * (lane & 1) + 4 * ((lane >> 1) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 3) & 1); }
+__device__ __forceinline__ float2 shfl_up2(float2 v, int d) { return make_float2(__shfl_up(v.x, d), __shfl_up(v.y, d)); }
 
 // MAXOUT: the kernel also records the largest magnitude of every token row of its output (atomic maxima
 // into a.rowmax_out, zero on entry: the product that consumes the output stages every token under its own
 // scale) and of the whole output (a.amax_out, ABSMAX_SLOTS slots, zero on entry).
 template <bool REV, bool MAXOUT>
-__global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
+__global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(ScanArgs a)
 {
     constexpr int E = SCAN_E;
-    __shared__ float2 sA[SCAN_THREADS];
-    __shared__ float2 sS[SCAN_THREADS];
-    __shared__ float2 sX[SCAN_THREADS];
+    constexpr int THREADS = MAXOUT ? 256 : SCAN_MAX_THREADS;
+    __shared__ float2 sA[THREADS];                   // (level 2: one per wavefront and lane; level 3: one per thread)
+    __shared__ float2 sS[THREADS];
+    __shared__ float2 sX[MAXOUT ? 256 : 16];
     __shared__ unsigned s_id;
 
     const int tid = threadIdx.x;
@@ -96,12 +96,15 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     const int s0 = (tb * a.cy + chunk) * E;          // first logical step of this thread
     const int len = max(0, min(E, L - s0));
     const long rowbase = (long)b * L;
-    // every thread of the workgroup owns E steps of a valid state: no guards needed
-    const bool full = ((tb + 1) * a.cy * E <= L) && ((px + 1) * a.pxb <= a.P);
+    // every thread of the wavefront (MAXOUT: of the workgroup) owns E steps of a valid state: no guards needed
+    const bool full = MAXOUT ? ((tb + 1) * a.cy * E <= L) && ((px + 1) * a.pxb <= a.P) : __builtin_amdgcn_ballot_w64(len == E && active) == ~0ull;
     const int stride = REV ? -a.P : a.P;                         // elements between consecutive logical steps
     const int pc = min(p, a.P - 1), sc = min(s0, L - 1);         // a valid state and step for every thread
     const long first = (rowbase + (REV ? (L - 1 - sc) : sc)) * a.P + pc;      // element of logical step s0
     const bool ends = len > 0 && s0 + len == L;                  // the thread owns the last logical step
+    // state that flows into the sequence (with a look-back, into its first workgroup: level 3)
+    float2 Xin = make_float2(0.f, 0.f);
+    if (!MAXOUT && a.nTB == 1 && !REV && a.x0 && active) Xin = a.x0[(long)b * a.P + p];
 
     float2 lam = active ? a.lam[p] : make_float2(0.f, 0.f);
     if (REV) lam.y = -lam.y;
@@ -198,16 +201,59 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     float2 l2 = cmul(lam, lam);
     l2 = cmul(l2, l2); l2 = cmul(l2, l2); l2 = cmul(l2, l2);
     A = (rmask & 0xffffu) ? make_float2(0.f, 0.f) : l2;
-    sA[tid] = A;
-    sS[tid] = S;
-    __syncthreads();
 
-    // ---- level 2: exclusive combine over the earlier chunks of this workgroup
+    // ---- level 2: exclusive combine over the earlier chunks of this workgroup: between the lanes of a wavefront that hold the
+    // same state (in log2 steps), then over the earlier groups of chunks (wavefronts; chunks, where one fills a wavefront) in LDS
+    const bool several = a.pxb < 64;                 // chunks of a state in one wavefront
+    const int wl = tid & 63, group = several ? tid >> 6 : chunk, ngroup = several ? (a.cy * a.pxb + 63) >> 6 : a.cy;
+    // (MAXOUT: chunk by chunk in LDS, the incoming state by way of sX, and the sum of dAbar over the chunks as well.  Its registers hold the
+    // maxima too: with the exchanges the reverse one needs 134 of them where it needs 118, one wavefront of a SIMD fewer, and takes 34.0 us
+    // where it takes 28.6: 30 x 300 x 512)
     float2 Aex = make_float2(1.f, 0.f), Sex = make_float2(0.f, 0.f);
-    for (int j = 0; j < chunk; ++j) {
-        const float2 Aj = sA[j * a.pxb + lane], Sj = sS[j * a.pxb + lane];
-        Sex = cfma(Aj, Sex, Sj);
-        Aex = cmul(Aj, Aex);
+    if constexpr (MAXOUT) {
+        sA[tid] = A;
+        sS[tid] = S;
+        __syncthreads();
+        for (int j = 0; j < chunk; ++j) {
+            const float2 Aj = sA[j * a.pxb + lane], Sj = sS[j * a.pxb + lane];
+            Sex = cfma(Aj, Sex, Sj);
+            Aex = cmul(Aj, Aex);
+        }
+    } else {
+        float2 Ai = A, Si = S;
+        for (int d = a.pxb; d < 64; d *= 2) {
+            const float2 Au = shfl_up2(Ai, d), Su = shfl_up2(Si, d);
+            const float2 nS = cfma(Ai, Su, Si), nA = cmul(Ai, Au);
+            Si = make_float2(wl >= d ? nS.x : Si.x, wl >= d ? nS.y : Si.y);
+            Ai = make_float2(wl >= d ? nA.x : Ai.x, wl >= d ? nA.y : Ai.y);
+        }
+        if (several) {
+            const float2 Au = shfl_up2(Ai, a.pxb), Su = shfl_up2(Si, a.pxb);
+            Aex = make_float2(wl >= a.pxb ? Au.x : 1.f, wl >= a.pxb ? Au.y : 0.f);
+            Sex = make_float2(wl >= a.pxb ? Su.x : 0.f, wl >= a.pxb ? Su.y : 0.f);
+        }
+        if (!several || wl >= 64 - a.pxb) { sA[group * a.pxb + lane] = Ai; sS[group * a.pxb + lane] = Si; }
+        __syncthreads();
+        float2 Ap = make_float2(1.f, 0.f), Sp = make_float2(0.f, 0.f);
+        // (three aggregates are read at a time: one by one, every step of the chain waits for LDS)
+        for (int g0 = 0; g0 < group; g0 += 3) {
+            float2 Ac[3], Sc[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int i = min(g0 + c, group - 1) * a.pxb + lane;
+                Ac[c] = sA[i]; Sc[c] = sS[i];
+                asm volatile("" : "+v"(Ac[c].x), "+v"(Ac[c].y), "+v"(Sc[c].x), "+v"(Sc[c].y));
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const bool use = g0 + c < group;
+                const float2 nS = cfma(Ac[c], Sp, Sc[c]), nA = cmul(Ac[c], Ap);
+                Sp = make_float2(use ? nS.x : Sp.x, use ? nS.y : Sp.y);
+                Ap = make_float2(use ? nA.x : Ap.x, use ? nA.y : Ap.y);
+            }
+        }
+        Sex = cfma(Aex, Sp, Sex);
+        Aex = cmul(Aex, Ap);
     }
 
     // ---- level 3: incoming state of the workgroup.
@@ -223,7 +269,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     const bool lastchunk = (chunk == a.cy - 1);
     const size_t desc_stride = (size_t)nchains * a.pxb;          // descriptors per time block
     ScanDesc *mine = a.desc + ((size_t)id * a.pxb + lane);
-    float2 Ablk = make_float2(0.f, 0.f), Sblk = make_float2(0.f, 0.f), Xin = make_float2(0.f, 0.f);
+    float2 Ablk = make_float2(0.f, 0.f), Sblk = make_float2(0.f, 0.f);
     if (lastchunk) {
         Ablk = cmul(A, Aex);
         Sblk = cfma(A, Sex, S);
@@ -232,7 +278,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
             publish_word(&mine->agg[0], Sblk.x, tag);
             publish_word(&mine->agg[1], Sblk.y, tag);
         }
-        if (sg0 == 0 && !REV && a.x0 && active) Xin = a.x0[(long)b * a.P + p];
+        if ((MAXOUT || a.nTB > 1) && sg0 == 0 && !REV && a.x0 && active) Xin = a.x0[(long)b * a.P + p];
     }
     if (tb > 0) {                                    // uniform over the workgroup
         __syncthreads();                             // level 2 has finished reading sA / sS
@@ -292,12 +338,15 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
             publish_word(&mine->incl[0], incl.x, 3u);
             publish_word(&mine->incl[1], incl.y, 3u);
         }
-        sX[lane] = Xin;
+        if (MAXOUT || a.nTB > 1) sX[lane] = Xin;
     }
-    __syncthreads();
+    if (MAXOUT || a.nTB > 1) {                                 // uniform
+        __syncthreads();
+        Xin = sX[lane];
+    }
 
     // ---- level 1, second pass: the states themselves
-    float2 xs = cfma(Aex, sX[lane], Sex);
+    float2 xs = cfma(Aex, Xin, Sex);
     float2 acc = make_float2(0.f, 0.f);
     unsigned rm[MAXOUT ? E : 1];                     // MAXOUT: magnitude of the value stored at step e
     float2 xend = make_float2(0.f, 0.f);             // state of the last logical step
@@ -350,11 +399,21 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     }
     if (REV) {
         // sum the chunks' contributions to dAbar; one partial row per (sequence, workgroup in time)
-        sA[tid] = acc;
+        const int parts = MAXOUT ? a.cy : ngroup;
+        if constexpr (MAXOUT) {
+            sA[tid] = acc;
+        } else {
+            for (int d = a.pxb; d < 64; d *= 2) {
+                acc.x += __shfl_xor(acc.x, d);
+                acc.y += __shfl_xor(acc.y, d);
+            }
+            __syncthreads();                         // level 2 has finished reading sA
+            if (!several || wl < a.pxb) sA[group * a.pxb + lane] = acc;
+        }
         __syncthreads();
-        if (chunk == 0 && active) {
+        if (tid < a.pxb && active) {
             float2 sum = make_float2(0.f, 0.f);
-            for (int j = 0; j < a.cy; ++j) {
+            for (int j = 0; j < parts; ++j) {
                 sum.x += sA[j * a.pxb + lane].x;
                 sum.y += sA[j * a.pxb + lane].y;
             }
@@ -363,17 +422,43 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_kernel(ScanArgs a)
     }
 }
 
-ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P)
+// Chunks and states of a workgroup.  16 states are one 128-byte line of a step.
+//   up to 256 steps: about 256 threads, as many states as that leaves for whole sequences;
+//   up to 512 steps, and up to 1024 where there are 64 such workgroups: whole sequences of 16 states;
+//   else a look-back, over blocks of 256 steps; of 1024 or 512 where that makes 192 to 384 of them, about one per CU (with more of
+//   them, small workgroups that overlap are better: 5 x 3000 x 700: 47.8 us with 256 steps, 53.1 with 1024) and the last one
+//   does not leave more than a tenth of all idle (16 x 2100 x 64: 13.4 and 14.9).
+//   Scans that record magnitudes (records): 256 steps at most, since the maxima and the saved states together do not fit the registers of
+//   1024 threads (gradient pass with larger workgroups: 8 x 700, H = 512, P = 640 166.9 -> 173.6 us).
+// Bytes and trips to memory bound all of them.  With 256 steps to a workgroup at every length, and a look-back above (us, scan-level entry points,
+// forward and reverse, now behind the arrow):  20 x 300 x 250: 17.8 -> 14.1, 22.7 -> 19.5    10 x 500 x 300: 16.5 -> 12.9, 21.2 -> 17.7
+//   1 x 300 x 64: 9.2 -> 6.3, 12.2 -> 9.4    16 x 1000 x 512: 26.8 -> 25.9, 39.9 -> 40.1    32 x 1000 x 1024: 101 -> 86, 188 -> 183
+//   4 x 4096 x 256: 17.0 -> 16.2, 26.1 -> 26.3    2 x 20000 x 64: 21.4 -> 17.6, 28.8 -> 24.4    1 x 60000 x 64: 39.0 -> 18.8, 49.4 -> 28.4
+// (whole sequences of 4096 steps, four states to a workgroup of 1024 threads: 4 x 4096 x 256 16.5 and 28.0, 1 x 4096 x 64 14.7 and 20.8)
+ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P, bool records)
 {
     ScanPlan pl;
-    // as many chunks per workgroup as the sequence can use, at most 16 (16 lanes = one 128-byte
-    // line of complex64 per step)
-    int cy = 1;
-    while (cy < 16 && (int64_t)cy * SCAN_E < L) cy *= 2;
-    pl.cy = cy;
-    pl.pxb = SCAN_THREADS / cy;
+    const int64_t chunks = (L + SCAN_E - 1) / SCAN_E, chains = (P + 15) / 16 * Bt;
+    pl.pxb = 16;
+    if (records) {
+        pl.cy = 1;
+        while (pl.cy < 16 && pl.cy < chunks) pl.cy *= 2;
+        pl.pxb = 256 / pl.cy;
+    } else if (chunks <= 16) {
+        pl.pxb = 256;
+        while (pl.pxb > 16 && (pl.pxb * chunks > 256 || pl.pxb / 2 >= P)) pl.pxb /= 2;
+        pl.cy = (int)chunks;
+    } else if (chunks <= 32 || (chunks <= 64 && chains >= 64)) {
+        pl.cy = (int)chunks;
+    } else {
+        pl.cy = 16;
+        for (int cy : {32, 64}) {
+            const int64_t blocks = (chunks + cy - 1) / cy;
+            if (chains * blocks >= 192 && chains * blocks <= 384 && blocks * cy * 10 <= chunks * 11) pl.cy = cy;
+        }
+    }
     pl.nPX = (int)((P + pl.pxb - 1) / pl.pxb);
-    pl.nTB = (int)((L + (int64_t)cy * SCAN_E - 1) / ((int64_t)cy * SCAN_E));
+    pl.nTB = (int)((chunks + pl.cy - 1) / pl.cy);
     pl.nblocks = (int64_t)pl.nPX * Bt * pl.nTB;
     // look-back scratch: ticket counters (one per chain, 64 bytes apart) followed by descriptors
     pl.ticket_bytes = pl.nTB > 1 ? (size_t)pl.nPX * Bt * SCAN_TICKET_STRIDE * sizeof(uint32_t) : 0;
@@ -385,13 +470,17 @@ ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P)
 hipError_t launch_scan(const ScanArgs &a, bool reverse, hipStream_t s)
 {
     const int64_t nblocks = (int64_t)a.nPX * a.Bt * a.nTB;
-    if (nblocks <= 0 || nblocks > 0x7fffffffLL || a.pxb * a.cy != SCAN_THREADS) return hipErrorInvalidValue;
+    if (nblocks <= 0 || nblocks > 0x7fffffffLL || a.pxb < 16 || a.pxb > 256 || (a.pxb & (a.pxb - 1)) || a.cy < 1) return hipErrorInvalidValue;
+    // a look-back: a thread per (state, workgroup of a group), blocks of a power of two of chunks
+    if (a.nTB > 1 ? a.pxb != 16 || (a.cy != 16 && a.cy != 32 && a.cy != 64) : (int64_t)a.cy * SCAN_E < a.L) return hipErrorInvalidValue;
+    const int64_t threads = ((int64_t)a.pxb * a.cy + 63) / 64 * 64;
     const bool maxout = a.rowmax_out != nullptr;
-    if (maxout && !a.amax_out) return hipErrorInvalidValue;
-    if (reverse && maxout) hipLaunchKernelGGL((scan_kernel<true, true>), dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s, a);
-    else if (reverse) hipLaunchKernelGGL((scan_kernel<true, false>), dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s, a);
-    else if (maxout) hipLaunchKernelGGL((scan_kernel<false, true>), dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s, a);
-    else hipLaunchKernelGGL((scan_kernel<false, false>), dim3((unsigned)nblocks), dim3(SCAN_THREADS), 0, s, a);
+    if (threads > (maxout ? 256 : SCAN_MAX_THREADS) || (maxout && !a.amax_out)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nblocks), block((unsigned)threads);
+    if (reverse && maxout) hipLaunchKernelGGL((scan_kernel<true, true>), grid, block, 0, s, a);
+    else if (reverse) hipLaunchKernelGGL((scan_kernel<true, false>), grid, block, 0, s, a);
+    else if (maxout) hipLaunchKernelGGL((scan_kernel<false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((scan_kernel<false, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

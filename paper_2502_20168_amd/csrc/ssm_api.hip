@@ -23,7 +23,7 @@ int make_scan_layout(int64_t Bt, int64_t L, int64_t P, bool rev, ScanOnlyLayout 
     if (P > SSM_MAX_WIDTH) return SSM_ERR_UNSUPPORTED;
     if (Bt > SSM_MAX_TOKENS || L > SSM_MAX_TOKENS || Bt > SSM_MAX_TOKENS / L) return SSM_ERR_UNSUPPORTED;
     if (Bt * L > SSM_MAX_ELEMS / (2 * P)) return SSM_ERR_UNSUPPORTED;
-    o.plan = plan_scan(Bt, L, P);
+    o.plan = plan_scan(Bt, L, P, false);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
     size_t off = 0;
     o.hdr = off; off += up256(sizeof(WsHeader));
@@ -137,7 +137,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
                         H >= 512 && P >= 512;
     o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
     o.nslab = coldot_slabs((int64_t)T, o.planes);
-    o.plan = plan_scan(Bt, L, P);
+    o.plan = plan_scan(Bt, L, P, o.planes2_unfused);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));

@@ -118,13 +118,12 @@ SlabPlan gemm_plan_slabs(int64_t M, int64_t N, int64_t K, int count, ReductionTi
 
 // ---------------------------------------------------------------------------------------------
 // Resettable scan over the sequence dimension (forward and reverse time).
-// One thread owns SCAN_E consecutive steps of one (sequence, state) lane; a workgroup of 256
-// threads is laid out as cy chunks x pxb lanes and so covers cy*SCAN_E steps of pxb states;
-// longer sequences use several workgroups along time that hand their running state forward
-// through descriptors in global memory (decoupled look-back).
+// One thread owns SCAN_E consecutive steps of one (sequence, state) lane; a workgroup is laid out as cy chunks x pxb lanes and so
+// covers cy*SCAN_E steps of pxb states: whole sequences, or a part of longer ones, whose workgroups along time hand their
+// running state forward through descriptors in global memory (decoupled look-back).
 // ---------------------------------------------------------------------------------------------
 constexpr int SCAN_E = 16;
-constexpr int SCAN_THREADS = 256;
+constexpr int SCAN_MAX_THREADS = 1024;
 constexpr int SCAN_TICKET_STRIDE = 16;   // uint32 slots between the ticket counters of two chains
 
 struct ScanDesc {            // one per (workgroup, lane); 32 bytes; every word = (float << 32) | tag
@@ -134,14 +133,15 @@ struct ScanDesc {            // one per (workgroup, lane); 32 bytes; every word 
 };
 
 struct ScanPlan {
-    int pxb, cy;             // lanes and chunks per workgroup (pxb * cy == SCAN_THREADS)
+    int pxb, cy;             // lanes and chunks per workgroup
     int nPX, nTB;            // workgroups along the state and the time dimension
     int64_t nblocks;         // nPX * Bt * nTB
     size_t ticket_bytes;     // per-chain ticket counters, 0 when nTB == 1
     size_t desc_bytes;       // 0 when nTB == 1
     size_t partial_elems;    // Bt * nTB * P complex partial sums of the reverse scan
 };
-ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P);
+// records: the scans also record the magnitudes of their output (ScanArgs::rowmax_out)
+ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P, bool records);
 
 struct WsHeader {            // first 256 bytes of every workspace
     uint32_t err, magic;
