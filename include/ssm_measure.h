@@ -44,7 +44,8 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
 
 /* What ssm_scan_fwd / ssm_scan_bwd would launch for a shape: host logic only, no GPU call.  Writes
  * SSM_PLAN_FIELDS int32 values to the HOST array out:
- *   [0] 1 when the input projection and C^H dy scan their own output tiles (no scan kernel)
+ *   [0] 1 when the input projection and C^H dy scan their own output tiles of 64 or 128 tokens (no scan kernel); 0 otherwise,
+ *       also where small products scan the rows of their 32-row tiles (T tokens, 2 P columns: at most 64 tiles of 128 x 128, L <= 2048)
  *   [1] planes per operand of the layer's products: 2 (scaled fp16) or 3 (bf16)
  *   [2] K slabs of dC, [3] K slabs of dBbar
  *   [4] gradient pass: 3 = du, dBbar slabs and dC slabs in one launch; 2 = two launches of two products
@@ -52,7 +53,7 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
  *   [6], [7] the same for the launches of C^H dy with dC and of du with dBbar when [4] == 2
  *   [8], [9], [10] tile of the launch of the input projection, of the output projection and of du, as
  *       1024 x rows + columns
- *   [11] workgroups along time of the scan kernels (1: no look-back; unused when [0] == 1)
+ *   [11] workgroups along time of the scan kernels (1: no look-back; unused where products scan their tiles)
  * Returns SSM_ERR_INVALID_ARG / SSM_ERR_UNSUPPORTED for shapes the library does not take.           */
 #define SSM_PLAN_FIELDS 12
 ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_t *out /* host */);

@@ -89,6 +89,19 @@ size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
     return (size_t)tiles * 64 * 2 * sizeof(unsigned long long);
 }
 
+// Small layers: the input projection and C^H dy take tiles of 32 rows there anyway (every small pair does), and those scan their rows, whatever the
+// sequences' length (up to 64 tiles: a thread for every eight of them).
+bool gemm_row_scan_ok(int64_t Bt, int64_t L, int64_t P)
+{
+    return !gemm_scan_shape_ok(Bt, L, P) && gemm_small_pair(Bt * L, 2 * P) && L <= ROW_SCAN_MAX_STEPS;
+}
+
+size_t gemm_row_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
+{
+    if (ROW_SCAN_TOKENS % L == 0) return 0;          // a tile holds whole sequences: nothing is handed over
+    return (size_t)((Bt * L + ROW_SCAN_TOKENS - 1) / ROW_SCAN_TOKENS) * P * 2 * sizeof(unsigned long long);
+}
+
 // The tile of a product.
 //   32 rows where 64-row tiles would occupy at most half of the CUs (1024 x 1024 x 512, 128 tiles of 64 x 128: 6.2 us
 //     against 7.7; 4096 x 512 x 1024, 256 tiles: 16.7 against 14.5).  What a workgroup then waits for is its chain of
@@ -102,7 +115,7 @@ size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
 //     116 us; the gate's, 4096 tokens, H = 1024: 92 against 97, but H = 768, 564 workgroups: 67 against 62).
 PkTile product_tile(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c)
 {
-    if (a.epilogue == 7 || a.epilogue == 8) return {a.scan.rows, 128};
+    if ((a.epilogue == 7 || a.epilogue == 8) && a.planes == 2) return {a.scan.rows, 128};
     const auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     int64_t items = 0;
     for (const GemmArgs *t : {b, c})
@@ -124,10 +137,12 @@ bool reduction_ok(const GemmArgs &t, int planes)
 bool scan_args_ok(const GemmArgs &a)
 {
     const ScanEpilogue &c = a.scan;
-    if (a.planes != 2 || !c.lam || !c.err || c.L <= 0 || a.N != 2 * c.P || a.M % c.L != 0 || (c.rows != 64 && c.rows != 128) || a.M % c.rows != 0) return false;
+    if (!c.lam || !c.err || c.L <= 0 || a.N != 2 * c.P || a.M % c.L != 0 || (a.epilogue == 8 && (!c.xsaved || !c.partial))) return false;
+    if (a.planes == 3) return c.rows == ROW_SCAN_TOKENS && gemm_row_scan_ok(a.M / c.L, c.L, c.P) && (c.desc || ROW_SCAN_TOKENS % c.L == 0);
+    if ((c.rows != 64 && c.rows != 128) || a.M % c.rows != 0) return false;
     const bool chain = c.L % c.rows == 0 && c.L <= SCAN_MAX_STEPS && (c.desc || c.L == 64);
     const bool whole = c.L < c.rows && 64 % c.L == 0 && c.L % (c.rows / 8) == 0;
-    return (chain || whole) && (a.epilogue == 7 || (c.xsaved && c.partial));
+    return chain || whole;
 }
 }  // namespace
 

@@ -102,6 +102,7 @@ struct Layout {
     // record the largest magnitude of every token row of x and chi with atomics, the prep launch measures the rest)
     bool planes2_unfused;
     int planes;              // per operand of every product
+    bool row_scan;           // three planes: the input projection and C^H dy scan their tiles of 32 rows; the scan kernels are not launched
     PackedLayout w_in, w_out;          // forward: Bbar and C
     PackedLayout w_gx, w_du;           // gradient pass: both transposed
     size_t hdr, lam, adj, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
@@ -136,14 +137,15 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
                         H >= 512 && P >= 512;
     o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
+    o.row_scan = gemm_row_scan_ok(Bt, L, P);
     o.nslab = coldot_slabs((int64_t)T, o.planes);
     o.plan = plan_scan(Bt, L, P, o.planes2_unfused);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));
     o.lam = off; off += up((size_t)P * 8);
-    o.ticket = off; off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
-    o.desc = off; off += up(o.plan.desc_bytes);
+    o.ticket = off; if (!o.row_scan) off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
+    o.desc = off; if (!o.row_scan) off += up(o.plan.desc_bytes);
     o.adj = o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
     size_t dA_elems = o.plan.partial_elems;
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
@@ -167,6 +169,11 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.rowpart = off; off += up(T * (size_t)o.row_parts * 4);
         const size_t per_tile = (size_t)(Bt * L / gemm_scan_rows(Bt * L, L, P, true)) * P;  // one dAbar row per scanning tile
         if (per_tile > dA_elems) dA_elems = per_tile;
+    }
+    if (o.row_scan) {
+        o.fdesc_bytes = gemm_row_scan_desc_bytes(Bt, L, P);
+        o.fdesc = off; off += up(o.fdesc_bytes);
+        dA_elems = (T + ROW_SCAN_TOKENS - 1) / ROW_SCAN_TOKENS * P;
     }
     if (gemm_scan_shape_ok(Bt, L, P)) {
         o.dC = o.dB = gemm_plan_slabs(2 * P, H, (int64_t)T, 2, REDUCTION_128x128, 2 * P);
@@ -249,7 +256,11 @@ void zero_ranges(PrepArgs &pa, const Layout &lo, char *ws, bool fused, size_t T)
         pa.zero[0].p = reinterpret_cast<uint4 *>(ws + lo.amax_atomic);
         pa.zero[0].n16 = (2 * ABSMAX_SLOTS * 4 + (fused ? lo.fdesc_bytes : up(T * 4))) / 16;
     }
-    if (!fused && lo.plan.nTB > 1) {
+    if (lo.row_scan) {
+        pa.zero[0].p = reinterpret_cast<uint4 *>(ws + lo.fdesc);
+        pa.zero[0].n16 = lo.fdesc_bytes / 16;
+    }
+    if (!fused && !lo.row_scan && lo.plan.nTB > 1) {
         pa.zero[1].p = reinterpret_cast<uint4 *>(ws + lo.ticket);
         pa.zero[1].n16 = (lo.desc + up(lo.plan.desc_bytes) - lo.ticket) / 16;
     }
@@ -312,18 +323,18 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     g1.C = reinterpret_cast<float *>(xs); g1.ldc = 2 * P;
     g1.M = T; g1.N = (int)(2 * P); g1.K = (int)H;
     if (two_planes) g1.amaxA = AbsMax{nullptr, 0, rowmax, 1, T};
-    if (fused) {
+    if (fused || lo.row_scan) {
         g1.epilogue = 7;
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
-        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = gemm_scan_rows(T, L, P, false); g1.scan.spin_limit = spin_limit();
-        g1.scan.rowmax_out = rowpart;                        // of the states, for the output projection
+        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : ROW_SCAN_TOKENS; g1.scan.spin_limit = spin_limit();
+        if (two_planes) g1.scan.rowmax_out = rowpart;        // of the states, for the output projection
     }
     HIP_TRY(launch_product(g1, s));
     MARK();
 
-    if (!fused) {
+    if (!fused && !lo.row_scan) {
         ScanArgs sa{};
         sa.in = xs; sa.out = xs; sa.lam = lam; sa.is_first = is_first;
         sa.x0 = reinterpret_cast<const float2 *>(x0); sa.x_last = reinterpret_cast<float2 *>(x_last);
@@ -433,8 +444,8 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     g4.C = dCpart; g4.ldc = 2 * P;
     g4.M = (int)H; g4.N = (int)(2 * P); g4.K = T; g4.splits = lo.dC.slabs;
     if (two_planes) { g3.amaxA = mx_dy_rows; g4.amaxA = mx_dy; g4.amaxB = mx_x; }
-    if (fused) {
-        // the product scans its own tiles; the dC slabs wait for the next launch, where the largest
+    if (fused || lo.row_scan) {
+        // the product scans its own tiles; with two planes the dC slabs wait for the next launch, where the largest
         // magnitude of the saved states (recorded here, as the scan reads them) is known
         g3.epilogue = 8;
         g3.scan.lam = lam; g3.scan.is_first = is_first;
@@ -442,16 +453,14 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
-        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = gemm_scan_rows(T, L, P, true); g3.scan.spin_limit = spin_limit();
-        g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart;
-        HIP_TRY(launch_product(g3, s));
-    } else {
-        // dC needs only dy and the saved states: it shares the launch
-        HIP_TRY(launch_products(g3, &g4, nullptr, lo.dC.first, s));
+        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : ROW_SCAN_TOKENS; g3.scan.spin_limit = spin_limit();
+        if (two_planes) { g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart; }
     }
+    // (otherwise dC needs only dy and the saved states: it shares the launch)
+    HIP_TRY(fused ? launch_product(g3, s) : launch_products(g3, &g4, nullptr, lo.dC.first, s));
     MARK();
 
-    if (!fused) {
+    if (!fused && !lo.row_scan) {
         ScanArgs sa{};
         sa.in = chi; sa.out = chi; sa.lam = lam; sa.is_first = is_first;
         sa.x0 = reinterpret_cast<const float2 *>(x0);
@@ -487,7 +496,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     ea.B = reinterpret_cast<const float2 *>(B); ea.adj = pa.adj; ea.P = (int)P; ea.H = (int)H;
     ea.dBbar_part = dBpart; ea.nsplit_B = lo.dB.slabs;
     ea.dC_part = dCpart; ea.nsplit_C = lo.dC.slabs;
-    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : (int64_t)Bt * lo.plan.nTB;
+    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : lo.row_scan ? (Bt * L + ROW_SCAN_TOKENS - 1) / ROW_SCAN_TOKENS : (int64_t)Bt * lo.plan.nTB;
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
     ea.dC = reinterpret_cast<float2 *>(dC); ea.dD = dD; ea.dlog_delta = dlog_delta;

@@ -92,3 +92,37 @@ def test_steps_on_tiles_of_32_rows(shape):
     g = dy.to(torch.complex128) @ C.conj().contiguous() + dx.to(torch.complex128)
     assert close(gx, g) and close(du, (g @ B.conj().contiguous()).real + D * dy.double())
     assert close(dxp, torch.where(first[:, None] != 0, 0.0, A.conj()[None] * g))
+
+
+# Small layers scan the rows of their 32-row tiles: sequences that start and end anywhere in a tile, rows past the last token, one tile and 64
+# tiles per sequence (and one step more: a scan kernel), one to many column groups, several workgroups along the columns
+ROW_SCANS = [(40, 1, 16, 8), (3, 5, 8, 3), (2, 31, 40, 33), (33, 33, 20, 16), (7, 61, 130, 17), (2, 64, 32, 32), (21, 97, 64, 70), (5, 512, 96, 65),
+             (3, 1000, 33, 129), (1, 2047, 24, 40), (3, 2048, 20, 36), (1, 2049, 24, 40), (2, 32, 64, 1040), (64, 16, 300, 200), (13, 40, 512, 512)]
+
+
+@pytest.mark.parametrize("shape", ROW_SCANS, ids=["x".join(map(str, s)) for s in ROW_SCANS])
+@pytest.mark.parametrize("resets", [0.0, 0.02, 1.0])
+def test_scans_on_tiles_of_32_rows(shape, resets):
+    Bt, L, H, P = shape
+    print(shape, resets, flush=True)
+    check_workload(wl.custom("row scans", Bt, L, H, P, p_reset=resets, with_x0=resets < 1.0, lam_re_lo=0.001, seed=31), backward=True)
+
+
+def test_what_one_sequence_holds_does_not_reach_the_next_in_its_tile():
+    """Two of five sequences of 13 steps (three tiles, the last one short) hold values beyond every float: the others come out as
+    without them, to the last bit."""
+    import torch
+    d = ssm.to_device(wl.gen_inputs(wl.custom("inf", 5, 13, 24, 20, p_reset=0.05, with_x0=True, seed=37)))
+    par = [d[k] for k in ("Lambda", "B", "C", "D", "log_delta")]
+    bad = {k: d[k].clone() for k in ("u", "dy")}
+    for k in bad:
+        bad[k][1], bad[k][3] = float("inf"), 3e38
+    out = []
+    for e in (d, bad):
+        f = ssm.ssm_scan_fwd(*par, e["u"], d["is_first"], d["x0"])
+        b = ssm.ssm_scan_bwd(*par, e["u"], d["is_first"], d["x0"], f["x"], e["dy"])
+        out.append([f["y"], f["x"], f["x_last"], b["du"], b["dx0"]])
+    assert not bool(torch.isfinite(out[1][0][1]).any())
+    for good, got in zip(*out):
+        for i in (0, 2, 4):
+            assert torch.equal(good[i], got[i])
