@@ -89,17 +89,22 @@ size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
     return (size_t)tiles * 64 * 2 * sizeof(unsigned long long);
 }
 
-// Small layers: the input projection and C^H dy take tiles of 32 rows there anyway (every small pair does), and those scan their rows, whatever the
-// sequences' length (up to 64 tiles: a thread for every eight of them).
-bool gemm_row_scan_ok(int64_t Bt, int64_t L, int64_t P)
+// Three planes: the input projection and C^H dy scan the rows of the tiles that they take anyway, whatever the sequences' length (up to 64 tiles
+// before another one: eight for each of a state's threads): 32 rows in small pairs, else 64.  The launches on tiles of other widths or
+// heights keep the scan kernels: at most 32 states and many rows, and the few tokens of layers so wide that the product alone takes 32 rows but not beside reductions.
+int gemm_row_scan_rows(int64_t T, int64_t L, int64_t P)
 {
-    return !gemm_scan_shape_ok(Bt, L, P) && gemm_small_pair(Bt * L, 2 * P) && L <= ROW_SCAN_MAX_STEPS;
+    const bool small = gemm_small_pair(T, 2 * P);
+    const int rows = small ? 32 : 64;
+    if (L > (int64_t)ROW_SCAN_MAX_TILES * rows) return 0;
+    return small || (P > 32 && ((T + 63) / 64) * ((2 * P + 127) / 128) > 128) ? rows : 0;
 }
 
-size_t gemm_row_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P)
+size_t gemm_row_scan_desc_bytes(int64_t T, int64_t L, int64_t P)
 {
-    if (ROW_SCAN_TOKENS % L == 0) return 0;          // a tile holds whole sequences: nothing is handed over
-    return (size_t)((Bt * L + ROW_SCAN_TOKENS - 1) / ROW_SCAN_TOKENS) * P * 2 * sizeof(unsigned long long);
+    const int rows = gemm_row_scan_rows(T, L, P);
+    if (rows == 0 || rows % L == 0) return 0;        // a tile holds whole sequences: nothing is handed over
+    return (size_t)((T + rows - 1) / rows) * P * 2 * sizeof(unsigned long long);
 }
 
 // The tile of a product.
@@ -138,7 +143,7 @@ bool scan_args_ok(const GemmArgs &a)
 {
     const ScanEpilogue &c = a.scan;
     if (!c.lam || !c.err || c.L <= 0 || a.N != 2 * c.P || a.M % c.L != 0 || (a.epilogue == 8 && (!c.xsaved || !c.partial))) return false;
-    if (a.planes == 3) return c.rows == ROW_SCAN_TOKENS && gemm_row_scan_ok(a.M / c.L, c.L, c.P) && (c.desc || ROW_SCAN_TOKENS % c.L == 0);
+    if (a.planes == 3) return c.rows > 0 && c.rows == gemm_row_scan_rows(a.M, c.L, c.P) && (c.desc || c.rows % c.L == 0);
     if ((c.rows != 64 && c.rows != 128) || a.M % c.rows != 0) return false;
     const bool chain = c.L % c.rows == 0 && c.L <= SCAN_MAX_STEPS && (c.desc || c.L == 64);
     const bool whole = c.L < c.rows && 64 % c.L == 0 && c.L % (c.rows / 8) == 0;

@@ -584,6 +584,324 @@ struct StoreInputs {
     }
 };
 
+// ---------------------------------------------------------------------------------------------
+// Epilogues 7 and 8 with three planes: the resettable scan over the 32 or 64 consecutive tokens of a tile and its BN / 2 states.  The tokens are
+// those of any sequences: where one starts inside the tile nothing flows in (its x0 is put into the element itself), so the length
+// of a sequence need not fit the tile.  Thread (q, c), q < 8, owns the q-th run of 4 or 8 tokens in scan order of state c:
+//   1. pass for zero incoming state; the runs are combined through LDS;
+//   2. the tile's aggregate (state for zero incoming state, tag) is published as two tagged words per state before any wait;
+//   3. the tiles that come earlier in the same sequence are shared out over the eight threads of a state, each requests all its words at once and
+//      folds them, and every thread folds the eight;
+//   4. second pass from the registers: states, x_last; reverse: dAbar (a row per tile) and dx0.
+// The powers of Abar that the folds take are computed in double precision and rounded once.  A reset selects instead of multiplying by zero: what
+// one sequence holds cannot reach the next, infinities and NaN included.  Tiles are placed in the order of their tokens (mode 6), so that
+// a tile only waits for tiles with smaller workgroup ids, which publish without waiting for anything; every wait is bounded.
+// Bound by its chain of dependent steps (the tile through LDS 0.3 us, either pass and the fold between them 0.4 to 0.5 each, a trip to
+// memory and back where tiles wait).  As a kernel of its own the scan paid its start, the way to memory and back, and the gap in front of it.  With scan
+// kernels and now: input projection of 16 x 64 tokens, H = P = 256 (32 rows): 5.8 + 4.8 us and 8.6; of 20 x 300, 500, 250 (64 rows): 23.1 + 14.1 and 30.6, C^H dy
+// 42.8 + 16.6 and 56.8.  Forward and gradient pass, 19 layers of 128 .. 4000 tokens on 32 rows: 13 % faster on geometric mean (16 x 64, 256, 256: 53.7 -> 47.5 us;
+// 32 x 60, 200, 100: 55.0 -> 45.9; 1 x 2048, 128, 64: 46.6 -> 39.4); 14 on 64 rows: 7 % (20 x 300, 500, 250: 182 -> 172; 9 x 997, 128, 140: 97.0 -> 82.7; 100 x 100,
+// 1000, 128: 259 -> 255).
+// ---------------------------------------------------------------------------------------------
+constexpr int ROW_SCAN_CHUNKS = 8, ROW_SCAN_RUN = 8;          // runs of a tile; tiles that a thread folds at most
+constexpr size_t row_scan_lds_bytes(int BN) { return (size_t)4 * ROW_SCAN_CHUNKS * (BN / 2) * 8; }
+
+// What is requested ahead: Abar, the flags, and for the thread's tokens x_{t-1} (reverse) and x0 where they start a sequence (both directions).
+struct RowScanStart { float2 lam; unsigned flag, next; };
+template <int ROWS> struct RowScanSaved { float2 x[ROWS / ROW_SCAN_CHUNKS]; };
+// bit r: row r of the tile; sequence of row 0
+template <int ROWS> struct RowScanMasks {
+    using Bits = std::conditional_t<ROWS == 32, unsigned, unsigned long long>;
+    Bits first, start, end, drop; int b0;
+    static_assert(ROWS == 32 || ROWS == 64, "a bit for every row");
+};
+__device__ __forceinline__ int popcount(unsigned v) { return __popc(v); }
+__device__ __forceinline__ int popcount(unsigned long long v) { return __popcll(v); }
+__device__ __forceinline__ unsigned reversed(unsigned v) { return __brev(v); }
+__device__ __forceinline__ unsigned long long reversed(unsigned long long v) { return __brevll(v); }
+
+// row of the tile that a lane looks at; 32 rows: lane 32 and those above it at the one behind the tile
+template <int ROWS> __device__ __forceinline__ int row_scan_lane(int tid) { return ROWS == 32 ? min(tid & 63, ROWS) : tid & 63; }
+template <int ROWS, int BN>
+__device__ __forceinline__ RowScanStart row_scan_start(const PkDev &g, int tid, int m0, int n0)
+{
+    const ScanEpilogue &a = g.scan;
+    RowScanStart s;
+    s.lam = a.lam[min(n0 / 2 + tid % (BN / 2), a.P - 1)];
+    s.flag = s.next = 0;
+    if (a.is_first) {
+        s.flag = a.is_first[min(m0 + row_scan_lane<ROWS>(tid), g.M - 1)];
+        if (ROWS == 64) s.next = a.is_first[min(m0 + ROWS, g.M - 1)];
+    }
+    return s;
+}
+// the rows at which a sequence starts and ends (whole wavefronts; the last token ends one, so that in reverse nothing comes in from rows past it)
+template <int ROWS>
+__device__ __forceinline__ RowScanMasks<ROWS> row_scan_ends(const PkDev &g, int tid, int m0)
+{
+    using Bits = typename RowScanMasks<ROWS>::Bits;
+    const unsigned row = (unsigned)(m0 + row_scan_lane<ROWS>(tid)), L = (unsigned)g.scan.L, b = row / L;
+    return {0, (Bits)__ballot(row == b * L), (Bits)__ballot(row + 1 == (b + 1) * L), 0, __builtin_amdgcn_readfirstlane((int)b)};
+}
+// drop: nothing flows into the row -- forward: a flag, or the start of a sequence; reverse: a flag of the token behind it, or a sequence end
+template <int ROWS, bool REV>
+__device__ __forceinline__ void row_scan_flags(RowScanMasks<ROWS> &k, const RowScanStart &s)
+{
+    using Bits = typename RowScanMasks<ROWS>::Bits;
+    const unsigned long long f = __ballot(s.flag != 0);
+    k.first = (Bits)f;
+    unsigned long long behind = f >> 1;
+    if (ROWS == 64) behind |= (unsigned long long)(__builtin_amdgcn_readfirstlane(s.next) != 0) << 63;
+    k.drop = REV ? (Bits)behind | k.end : k.first | k.start;
+}
+// Powers of Abar (its conjugate in reverse) over a run of tokens, the runs before the thread's, and a tile: in double precision, rounded once.
+struct RowScanPowers { float2 run, before, tile; };
+template <int ROWS, int BN, bool REV>
+__device__ __forceinline__ RowScanPowers row_scan_powers(float2 lam, int tid)
+{
+    const int q = tid / (BN / 2);
+    double re = lam.x, im = REV ? -lam.y : lam.y, br = 1.0, bi = 0.0;
+    auto square = [&] {
+        const double t = re * re - im * im;
+        im *= 2.0 * re; re = t;
+    };
+    auto take = [&](bool bit) {
+        const double r = br * re - bi * im, i = br * im + bi * re;
+        br = bit ? r : br; bi = bit ? i : bi;
+    };
+    RowScanPowers w;
+    square(); square();
+    if (ROWS == 64) square();
+    w.run = make_float2((float)re, (float)im);
+    take(q & 1); square(); take(q & 2); square(); take(q & 4); square();
+    w.before = make_float2((float)br, (float)bi);
+    w.tile = make_float2((float)re, (float)im);
+    return w;
+}
+// sequence of a row
+template <int ROWS>
+__device__ __forceinline__ int row_scan_sequence(const RowScanMasks<ROWS> &k, int r)
+{
+    return k.b0 + popcount((typename RowScanMasks<ROWS>::Bits)(k.start & (((typename RowScanMasks<ROWS>::Bits)2 << r) - 2)));
+}
+
+template <int ROWS, int BN, bool REV>
+__device__ __forceinline__ RowScanSaved<ROWS> row_scan_request(const PkDev &g, const RowScanMasks<ROWS> &k, int tid, int m0, int n0)
+{
+    constexpr int CH = ROWS / ROW_SCAN_CHUNKS;
+    const ScanEpilogue &a = g.scan;
+    const int c = tid % (BN / 2), q = tid / (BN / 2), p = n0 / 2 + c;
+    const auto row_of = [&](int i) { return REV ? ROWS - 1 - (CH * q + i) : CH * q + i; };
+    RowScanSaved<ROWS> s;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) s.x[i] = make_float2(0.f, 0.f);
+    if (q >= ROW_SCAN_CHUNKS) return s;                      // (whole wavefronts)
+    if (REV) {
+        // (rows and states past the end: any)
+        const float2 *x = a.xsaved + min(p, a.P - 1);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) s.x[i] = x[(long)min(max(m0 + row_of(i) - 1, 0), g.M - 1) * a.P];
+    }
+    if (k.start != 0) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = row_of(i);
+            if (!((k.start >> r) & 1u)) continue;
+            s.x[i] = make_float2(0.f, 0.f);
+            if (a.x0 && p < a.P && m0 + r < g.M) s.x[i] = a.x0[(long)row_scan_sequence(k, r) * a.P + p];
+        }
+    }
+    return s;
+}
+
+// tile: KW partial tiles of ROWS x BN, as tile_at places them; mem: row_scan_lds_bytes of LDS that nobody else uses
+template <int ROWS, int BN, int KW, bool REV>
+__device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile, float2 *mem, int tid, int m0, int n0, float2 lam, const RowScanPowers &power,
+                                              const RowScanMasks<ROWS> &k, const RowScanSaved<ROWS> &saved)
+{
+    using Bits = typename RowScanMasks<ROWS>::Bits;
+    constexpr int NL = BN / 2, NC = ROW_SCAN_CHUNKS, CH = ROWS / NC;
+    const ScanEpilogue &a = g.scan;
+    float2 *cS = mem, *pS = mem + NC * NL, *pA = mem + 2 * NC * NL, *cD = mem + 3 * NC * NL;
+    const int c = tid % NL, q = tid / NL, p = n0 / 2 + c;
+    const bool on = q < NC, active = on && p < a.P;          // (on: whole wavefronts)
+    auto row_of = [&](int i) { return REV ? ROWS - 1 - (CH * q + i) : CH * q + i; };
+    // the drop bits in scan order: bit e: the e-th row of the scan
+    const Bits cut = REV ? reversed(k.drop) : k.drop;
+    // earlier tiles of the sequence that flows in, none where it is cut at the first row of the scan; whether another tile follows in the sequence
+    const int here = m0 / ROWS;
+    int npred = 0;
+    bool has_succ;
+    if (REV) {
+        const long end = (long)(k.b0 + popcount((Bits)(k.start & ~(Bits)1)) + 1) * a.L - 1;        // of the sequence of the last row
+        if (!(cut & 1u) && m0 + ROWS < g.M) npred = (int)(end / ROWS) - here;       // (behind the last row nothing follows)
+        has_succ = !(k.start & 1u);
+    } else {
+        if (!(cut & 1u)) npred = here - (int)((long)k.b0 * a.L / ROWS);
+        has_succ = !(k.end >> (ROWS - 1));
+    }
+    const int run = (npred + NC - 1) / NC;                   // tiles that a thread folds
+    if (REV) lam.y = -lam.y;
+    float2 val[CH], S = make_float2(0.f, 0.f);
+    if (on) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const float *at = tile + tile_at<BN>(row_of(i), 2 * c);
+            val[i] = *reinterpret_cast<const float2 *>(at);
+#pragma unroll
+            for (int w = 1; w < KW; ++w) {
+                const float2 v = *reinterpret_cast<const float2 *>(at + w * ROWS * BN);
+                val[i].x += v.x; val[i].y += v.y;
+            }
+        }
+        if (m0 + ROWS > g.M) {                               // (rows past the last token: zeros)
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+                if (m0 + row_of(i) >= g.M) val[i] = make_float2(0.f, 0.f);
+        }
+        if (!REV && (k.start & ~k.first) != 0) {
+            // the state that flows into a sequence, unless its first step drops it
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+                if ((k.start & ~k.first) >> row_of(i) & 1u) val[i] = cfma(lam, saved.x[i], val[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const float2 n = cfma(lam, S, val[i]);
+            const bool r = (cut >> (CH * q + i)) & 1u;
+            S = make_float2(r ? val[i].x : n.x, r ? val[i].y : n.y);
+        }
+        cS[q * NL + c] = S;
+    }
+    __syncthreads();                                         // the states of the runs are in LDS
+    float2 Sex = make_float2(0.f, 0.f);
+    const bool cut_before = on && (cut & (((Bits)1 << (CH * (q & 7))) - 1)) != 0;       // a reset in an earlier run of the tile
+    if (on) {
+        float2 Sc[NC - 1];
+#pragma unroll
+        for (int j = 0; j < NC - 1; ++j) Sc[j] = cS[j * NL + c];
+#pragma unroll
+        for (int j = 0; j < NC - 1; ++j) {
+            const bool any = ((cut >> (CH * j)) & ((1u << CH) - 1u)) != 0;
+            const float2 n = cfma(power.run, Sex, Sc[j]);
+            const float2 m = make_float2(any ? Sc[j].x : n.x, any ? Sc[j].y : n.y);
+            Sex = make_float2(j < q ? m.x : Sex.x, j < q ? m.y : Sex.y);
+        }
+        if (q == NC - 1 && active && has_succ) {
+            const bool any = (cut >> (CH * (NC - 1))) != 0;
+            const float2 n = cfma(power.run, Sex, S);
+            unsigned long long *word = a.desc + (size_t)here * 2 * a.P + p;
+            const unsigned tag = cut != 0 ? 2u : 1u;
+            publish_word(word, any ? S.x : n.x, tag);
+            publish_word(word + a.P, any ? S.y : n.y, tag);
+        }
+        const int kn = min(run, npred - q * run);
+        if (kn > 0) {
+            // the earliest tile of the run first; all words are requested in every round until all are there
+            const int first = (REV ? here + npred : here - npred) + (REV ? -1 : 1) * q * run;
+            const long step = (REV ? -1 : 1) * (long)a.P * 2;
+            const unsigned long long *w = a.desc + (size_t)first * 2 * a.P + min(p, a.P - 1);
+            float2 Ar = make_float2(1.f, 0.f), Sr = make_float2(0.f, 0.f);
+            auto fold = [&](auto count, int j0) {            // tiles j0 .. j0 + N - 1 of the run
+                constexpr int N = decltype(count)::value;
+                unsigned long long w0[N], w1[N];
+                bool all = false;
+                for (unsigned spins = 0;; ++spins) {
+                    all = true;
+#pragma unroll
+                    for (int j = 0; j < N; ++j) {
+                        const unsigned long long *wj = w + step * min(j0 + j, kn - 1);
+                        w0[j] = poll_word(wj); w1[j] = poll_word(wj + a.P);
+                    }
+#pragma unroll
+                    for (int j = 0; j < N; ++j) all = all & (word_tag(w0[j]) != 0) & (word_tag(w1[j]) != 0);
+                    if (__ballot(active && !all) == 0 || spins >= a.spin_limit) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (active && !all) atomicOr(a.err, 1u);     // gave up: flagged, and finished anyway
+#pragma unroll
+                for (int j = 0; j < N; ++j) {
+                    if (j0 + j >= kn) continue;
+                    // a missing aggregate hands on NaN: every state that depends on it becomes NaN, so the failure cannot pass as data
+                    const bool missing = (word_tag(w0[j]) == 0) | (word_tag(w1[j]) == 0), stop = missing | (word_tag(w0[j]) == 2u);
+                    const float2 Sj = missing ? make_float2(__builtin_nanf(""), __builtin_nanf("")) : make_float2(word_value(w0[j]), word_value(w1[j]));
+                    const float2 n = cfma(power.tile, Sr, Sj), An = cmul(power.tile, Ar);
+                    Sr = make_float2(stop ? Sj.x : n.x, stop ? Sj.y : n.y);
+                    Ar = make_float2(stop ? 0.f : An.x, stop ? 0.f : An.y);
+                }
+            };
+            // (four at a time: eight take more registers than there are)
+            if (run == 1) fold(std::integral_constant<int, 1>{}, 0);
+            else for (int j = 0; j < run; j += 4) fold(std::integral_constant<int, 4>{}, j);
+            pS[q * NL + c] = Sr;
+            pA[q * NL + c] = Ar;
+        }
+    }
+    if (npred > 0) __syncthreads();                          // the folded runs are in LDS
+    if (on) {
+        float2 X = make_float2(0.f, 0.f);
+        for (int j0 = 0; j0 * run < npred; j0 += 4) {        // (four reads at a time; those behind the last run are not used)
+            float2 Al[4], Sl[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { Al[j] = pA[(j0 + j) * NL + c]; Sl[j] = pS[(j0 + j) * NL + c]; }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if ((j0 + j) * run >= npred) break;
+                const float2 n = cfma(Al[j], X, Sl[j]);
+                const bool stop = Al[j].x == 0.f && Al[j].y == 0.f;
+                X = make_float2(stop ? Sl[j].x : n.x, stop ? Sl[j].y : n.y);
+            }
+        }
+        const float2 in = cfma(power.before, X, Sex);
+        float2 xs = make_float2(cut_before ? Sex.x : in.x, cut_before ? Sex.y : in.y), acc = make_float2(0.f, 0.f);
+        float2 *dst = reinterpret_cast<float2 *>(g.C) + (long)m0 * a.P + p;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = row_of(i);
+            const float2 n = cfma(lam, xs, val[i]);
+            const bool rs = (cut >> (CH * q + i)) & 1u;
+            xs = make_float2(rs ? val[i].x : n.x, rs ? val[i].y : n.y);
+            if (REV) {
+                const bool first = (k.first >> r) & 1u;
+                const float2 v = make_float2(first ? 0.f : saved.x[i].x, first ? 0.f : saved.x[i].y);
+                acc.x = fmaf(v.x, xs.x, fmaf(v.y, xs.y, acc.x));
+                acc.y = fmaf(v.x, xs.y, fmaf(-v.y, xs.x, acc.y));
+            }
+            val[i] = xs;
+        }
+        if (active) {
+            if (m0 + ROWS <= g.M) {
+#pragma unroll
+                for (int i = 0; i < CH; ++i) dst[row_of(i) * a.P] = val[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (m0 + row_of(i) < g.M) dst[row_of(i) * a.P] = val[i];
+            }
+            const Bits edge = REV ? k.start : k.end;
+            float2 *at_edge = REV ? a.dx0 : a.x_last;
+            if (edge != 0 && at_edge) {
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    const int r = row_of(i);                 // (lam holds conj(Abar) in reverse)
+                    if (((edge >> r) & 1u) && m0 + r < g.M)
+                        at_edge[(long)row_scan_sequence(k, r) * a.P + p] = !REV ? val[i] : (k.first >> r) & 1u ? make_float2(0.f, 0.f) : cmul(lam, val[i]);
+                }
+            }
+        }
+        if (REV) cD[q * NL + c] = acc;
+    }
+    if (REV) {
+        __syncthreads();                                     // the runs' contributions to dAbar are in LDS
+        if (q == 0 && active) {
+            float2 sum = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) { const float2 v = cD[j * NL + c]; sum.x += v.x; sum.y += v.y; }
+            a.partial[(size_t)here * a.P + p] = sum;
+        }
+    }
+}
+
 // Place of the c-th 16-byte piece of row r of an LDS plane (rows of 128 bytes, no padding): the pieces of a row are permuted
 // so that 16 lanes reading the same piece of 16 rows, and 32 lanes writing two neighbouring rows, meet every bank once.
 __device__ __forceinline__ int pk_swizzle(int r, int c) { return c ^ ((r >> 1) & 7); }
@@ -610,7 +928,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     constexpr int PLANE = BM * S, STAGE = NPL * PLANE;
     constexpr int MI = BM / 32, KS = BK / 16;
     static_assert(PK_BN == 32 * NC && (BM == 64 || BM == 128), "32 columns per consumer");
-    constexpr bool SCANS = EPI == 7 || EPI == 8;
+    constexpr bool SCANS = (EPI == 7 || EPI == 8) && NPL == 2, ROW_SCANS = (EPI == 7 || EPI == 8) && NPL == 3;
     constexpr int RC = SCANS ? BM / SCAN_WAVES : 8, FR = SCANS ? BM : 64;      // (scans)
     static_assert(!SCANS || BM >= 64, "scanning tiles have 64 or 128 rows");
     // k steps of the weights in flight: what 128 registers hold
@@ -626,6 +944,14 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     ScanFlags<FR> flags;
     StoreInputs<BM, PK_BN, EPI> in;
     if constexpr (SCANS) flag_bytes = scan_request_flags<FR, EPI == 8>(g.scan, l, m0, g.M);
+    RowScanStart row_scan;
+    RowScanMasks<64> row_masks;
+    RowScanSaved<64> row_saved;
+    static_assert(!ROW_SCANS || BM == 64, "rows of the masks");
+    if constexpr (ROW_SCANS) {
+        row_scan = row_scan_start<64, PK_BN>(g, tid, m0, n0);
+        row_masks = row_scan_ends<64>(g, tid, m0);
+    }
 
     if (wave >= NC) {
         // ------------------------------------------------------------------ producers
@@ -725,8 +1051,9 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
         for (int j = 0; j + 1 < PF; ++j)
             if (kt + j + 1 < nk) step(kt, j);
         __syncthreads();
-        if constexpr (EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
-        if constexpr (!SCANS) in.request(g, tid, 0, m0, n0);
+        if constexpr (SCANS && EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
+        if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, EPI == 8>(g, row_masks, tid, m0, n0);
+        else if constexpr (!SCANS) in.request(g, tid, 0, m0, n0);
         __syncthreads();                             // barriers 1 and 2, see below
         __syncthreads();
     } else {
@@ -825,8 +1152,9 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
                 for (int r = 0; r < 16; ++r) acc[i][r] = __builtin_ldexpf(acc[i][r], -(rowexp[row_of(i, r)] + eb));
         }
         // (at 128 rows the accumulators leave no registers for the inputs before they are staged)
-        if constexpr (EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
-        if constexpr (!SCANS && MI < 4) in.request(g, tid, 0, m0, n0);
+        if constexpr (SCANS && EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
+        if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, EPI == 8>(g, row_masks, tid, m0, n0);
+        else if constexpr (!SCANS && MI < 4) in.request(g, tid, 0, m0, n0);
         __syncthreads();                                 // barrier 1: every wavefront has left the K loop, LDS is free
         float *out = reinterpret_cast<float *>(smem_raw);
 #pragma unroll
@@ -839,295 +1167,17 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
 
     // (producers and consumers together: one copy of the code)
     if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags);
-    else {
+    else if constexpr (ROW_SCANS) {
+        static_assert(BM * PK_BN * 4 + row_scan_lds_bytes(PK_BN) <= NS * STAGE * 2, "what the scan keeps behind the staged tile");
+        row_scan_flags<64, EPI == 8>(row_masks, row_scan);
+        const RowScanPowers power = row_scan_powers<64, PK_BN, EPI == 8>(row_scan.lam, tid);
+        row_scan_body<64, PK_BN, 1, EPI == 8>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid, m0, n0,
+                                              row_scan.lam, power, row_masks, row_saved);
+    } else {
 #pragma unroll
         for (int batch = 0; batch < in.BATCHES; ++batch) {
             if (batch > 0) in.request(g, tid, batch, m0, n0);
             in.store(g, reinterpret_cast<const float *>(smem_raw), tid, batch, m0, n0);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Epilogues 7 and 8 on tiles of 32 rows (three planes): the resettable scan over 32 consecutive tokens of BN / 2 states.  The tokens are
-// those of any sequences: where one starts inside the tile nothing flows in (its x0 is put into the element itself), so the length
-// of a sequence need not fit the tile.  Thread (q, c), q < 8, owns the q-th run of 4 tokens in scan order of state c:
-//   1. pass for zero incoming state; the runs are combined through LDS;
-//   2. the tile's aggregate (state for zero incoming state, tag) is published as two tagged words per state before any wait;
-//   3. the tiles that come earlier in the same sequence are shared out over the eight threads of a state, each requests all its words at once and
-//      folds them, and every thread folds the eight;
-//   4. second pass from the registers: states, x_last; reverse: dAbar (a row per tile) and dx0.
-// The powers of Abar that the folds take are computed in double precision and rounded once.  A reset selects instead of multiplying by zero: what
-// one sequence holds cannot reach the next, infinities and NaN included.  Tiles are placed in the order of their tokens (mode 6), so that
-// a tile only waits for tiles with smaller workgroup ids, which publish without waiting for anything; every wait is bounded.
-// Bound by its chain of dependent steps (partial tiles through LDS 0.3 us, either pass and the fold between them 0.4 to 0.5 each, a trip to
-// memory and back where tiles wait).  As a kernel of its own the scan paid its start, the way to memory and back, and the gap in front of it: input
-// projection and scan of 16 x 64 tokens, H = P = 256: 5.8 + 4.8 us and a gap, now 8.6; 4 x 256: 9.1.  Twenty layers of 128 .. 4000 tokens, forward and
-// gradient pass: 13 % faster on geometric mean (16 x 64, 256, 256: 53.7 -> 47.5 us; 32 x 60, 200, 100: 55.0 -> 45.9; 1 x 2048, 128, 64: 46.6 -> 39.4).
-// ---------------------------------------------------------------------------------------------
-constexpr int ROW_SCAN_CHUNK = 4, ROW_SCAN_CHUNKS = 8, ROW_SCAN_RUN = 8;
-static_assert(ROW_SCAN_CHUNK * ROW_SCAN_CHUNKS == ROW_SCAN_TOKENS && ROW_SCAN_MAX_STEPS <= ROW_SCAN_RUN * ROW_SCAN_CHUNKS * ROW_SCAN_TOKENS,
-              "a thread's runs of tokens and of tiles");
-
-// What is requested ahead: Abar, the flags, and for the thread's tokens x_{t-1} (reverse) and x0 where they start a sequence (both directions).
-struct RowScanStart { float2 lam; unsigned flag; };
-struct RowScanSaved { float2 x[ROW_SCAN_CHUNK]; };
-struct RowScanMasks { unsigned first, start, end, drop; int b0; };       // bit r: row r of the tile; sequence of row 0
-
-template <int BN>
-__device__ __forceinline__ RowScanStart row_scan_start(const PkDev &g, int tid, int m0, int n0)
-{
-    const ScanEpilogue &a = g.scan;
-    RowScanStart s;
-    s.lam = a.lam[min(n0 / 2 + tid % (BN / 2), a.P - 1)];
-    s.flag = a.is_first ? a.is_first[min(m0 + min(tid & 63, ROW_SCAN_TOKENS), g.M - 1)] : 0u;
-    return s;
-}
-// The rows at which a sequence starts and ends (whole wavefronts; lanes above 32 repeat lane 32.  Row M counts as the start of a sequence, so
-// that in reverse nothing comes in from the rows past M).
-__device__ __forceinline__ RowScanMasks row_scan_ends(const PkDev &g, int tid, int m0)
-{
-    const unsigned row = (unsigned)(m0 + min(tid & 63, ROW_SCAN_TOKENS)), L = (unsigned)g.scan.L, b = row / L;
-    const unsigned long long s = __ballot(row == b * L);
-    return {0u, (unsigned)s, (unsigned)(s >> 1), 0u, __builtin_amdgcn_readfirstlane((int)b)};
-}
-// drop: nothing flows into the row -- forward: a flag, or the start of a sequence; reverse: a flag of the token behind it, or a sequence end
-template <bool REV>
-__device__ __forceinline__ void row_scan_flags(RowScanMasks &k, unsigned flag)
-{
-    const unsigned long long f = __ballot(flag != 0);
-    k.first = (unsigned)f;
-    k.drop = REV ? (unsigned)(f >> 1) | k.end : k.first | k.start;
-}
-// Powers of Abar (its conjugate in reverse) over a run of tokens, the runs before the thread's, and a tile: in double precision, rounded once.
-struct RowScanPowers { float2 run, before, tile; };
-template <int BN, bool REV>
-__device__ __forceinline__ RowScanPowers row_scan_powers(float2 lam, int tid)
-{
-    const int q = tid / (BN / 2);
-    double re = lam.x, im = REV ? -lam.y : lam.y, br = 1.0, bi = 0.0;
-    auto square = [&] {
-        const double t = re * re - im * im;
-        im *= 2.0 * re; re = t;
-    };
-    auto take = [&](bool bit) {
-        const double r = br * re - bi * im, i = br * im + bi * re;
-        br = bit ? r : br; bi = bit ? i : bi;
-    };
-    RowScanPowers w;
-    square(); square();
-    w.run = make_float2((float)re, (float)im);
-    take(q & 1); square(); take(q & 2); square(); take(q & 4); square();
-    w.before = make_float2((float)br, (float)bi);
-    w.tile = make_float2((float)re, (float)im);
-    return w;
-}
-// sequence of a row
-__device__ __forceinline__ int row_scan_sequence(const RowScanMasks &k, int r) { return k.b0 + __popc(k.start & ((2u << r) - 2u)); }
-
-template <int BN, bool REV>
-__device__ __forceinline__ RowScanSaved row_scan_request(const PkDev &g, const RowScanMasks &k, int tid, int m0, int n0)
-{
-    const ScanEpilogue &a = g.scan;
-    const int c = tid % (BN / 2), q = tid / (BN / 2), p = n0 / 2 + c;
-    const auto row_of = [&](int i) { return REV ? ROW_SCAN_TOKENS - 1 - (ROW_SCAN_CHUNK * q + i) : ROW_SCAN_CHUNK * q + i; };
-    RowScanSaved s;
-#pragma unroll
-    for (int i = 0; i < ROW_SCAN_CHUNK; ++i) s.x[i] = make_float2(0.f, 0.f);
-    if (q >= ROW_SCAN_CHUNKS) return s;                      // (whole wavefronts)
-    if (REV) {
-        // (rows and states past the end: any)
-        const float2 *x = a.xsaved + min(p, a.P - 1);
-#pragma unroll
-        for (int i = 0; i < ROW_SCAN_CHUNK; ++i) s.x[i] = x[(long)min(max(m0 + row_of(i) - 1, 0), g.M - 1) * a.P];
-    }
-    if (k.start != 0) {
-#pragma unroll
-        for (int i = 0; i < ROW_SCAN_CHUNK; ++i) {
-            const int r = row_of(i);
-            if (!((k.start >> r) & 1u)) continue;
-            s.x[i] = make_float2(0.f, 0.f);
-            if (a.x0 && p < a.P && m0 + r < g.M) s.x[i] = a.x0[(long)row_scan_sequence(k, r) * a.P + p];
-        }
-    }
-    return s;
-}
-
-// tile: KW partial tiles of 32 x BN, as tile_at places them; mem: 4 x 8 x BN / 2 values of LDS that nobody else uses
-template <int BN, int KW, bool REV>
-__device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile, float2 *mem, int tid, int m0, int n0, float2 lam, const RowScanPowers &power,
-                                              const RowScanMasks &k, const RowScanSaved &saved)
-{
-    constexpr int NL = BN / 2, CH = ROW_SCAN_CHUNK, NC = ROW_SCAN_CHUNKS, ROWS = ROW_SCAN_TOKENS;
-    const ScanEpilogue &a = g.scan;
-    float2 *cS = mem, *pS = mem + NC * NL, *pA = mem + 2 * NC * NL, *cD = mem + 3 * NC * NL;
-    const int c = tid % NL, q = tid / NL, p = n0 / 2 + c;
-    const bool on = q < NC, active = on && p < a.P;          // (on: whole wavefronts)
-    auto row_of = [&](int i) { return REV ? ROWS - 1 - (CH * q + i) : CH * q + i; };
-    // the drop bits in scan order: bit e: the e-th row of the scan
-    const unsigned cut = REV ? __brev(k.drop) : k.drop;
-    // earlier tiles of the sequence that flows in, none where it is cut at the first row of the scan; whether another tile follows in the sequence
-    const int here = m0 / ROWS;
-    int npred = 0;
-    bool has_succ;
-    if (REV) {
-        const long end = (long)(k.b0 + __popc(k.start & ~1u) + 1) * a.L - 1;        // of the sequence of the last row
-        if (!(cut & 1u) && m0 + ROWS < g.M) npred = (int)(end / ROWS) - here;       // (behind the last row nothing follows)
-        has_succ = !(k.start & 1u);
-    } else {
-        if (!(cut & 1u)) npred = here - (int)((long)k.b0 * a.L / ROWS);
-        has_succ = !(k.end >> 31);
-    }
-    const int run = (npred + NC - 1) / NC;                   // tiles that a thread folds
-    if (REV) lam.y = -lam.y;
-    float2 val[CH], S = make_float2(0.f, 0.f);
-    if (on) {
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const float *at = tile + tile_at<BN>(row_of(i), 2 * c);
-            val[i] = *reinterpret_cast<const float2 *>(at);
-#pragma unroll
-            for (int w = 1; w < KW; ++w) {
-                const float2 v = *reinterpret_cast<const float2 *>(at + w * ROWS * BN);
-                val[i].x += v.x; val[i].y += v.y;
-            }
-        }
-        if (m0 + ROWS > g.M) {                               // (rows past the last token: zeros)
-#pragma unroll
-            for (int i = 0; i < CH; ++i)
-                if (m0 + row_of(i) >= g.M) val[i] = make_float2(0.f, 0.f);
-        }
-        if (!REV && (k.start & ~k.first) != 0) {
-            // the state that flows into a sequence, unless its first step drops it
-#pragma unroll
-            for (int i = 0; i < CH; ++i)
-                if ((k.start & ~k.first) >> row_of(i) & 1u) val[i] = cfma(lam, saved.x[i], val[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const float2 n = cfma(lam, S, val[i]);
-            const bool r = (cut >> (CH * q + i)) & 1u;
-            S = make_float2(r ? val[i].x : n.x, r ? val[i].y : n.y);
-        }
-        cS[q * NL + c] = S;
-    }
-    __syncthreads();                                         // the states of the runs are in LDS
-    float2 Sex = make_float2(0.f, 0.f);
-    const bool cut_before = on && (cut & ((1u << (CH * (q & 7))) - 1u)) != 0;       // a reset in an earlier run of the tile
-    if (on) {
-        float2 Sc[NC - 1];
-#pragma unroll
-        for (int j = 0; j < NC - 1; ++j) Sc[j] = cS[j * NL + c];
-#pragma unroll
-        for (int j = 0; j < NC - 1; ++j) {
-            const bool any = (cut >> (CH * j)) & ((1u << CH) - 1u);
-            const float2 n = cfma(power.run, Sex, Sc[j]);
-            const float2 m = make_float2(any ? Sc[j].x : n.x, any ? Sc[j].y : n.y);
-            Sex = make_float2(j < q ? m.x : Sex.x, j < q ? m.y : Sex.y);
-        }
-        if (q == NC - 1 && active && has_succ) {
-            const bool any = (cut >> (CH * (NC - 1))) != 0;
-            const float2 n = cfma(power.run, Sex, S);
-            unsigned long long *word = a.desc + (size_t)here * 2 * a.P + p;
-            const unsigned tag = cut != 0 ? 2u : 1u;
-            publish_word(word, any ? S.x : n.x, tag);
-            publish_word(word + a.P, any ? S.y : n.y, tag);
-        }
-        const int kn = min(run, npred - q * run);
-        if (kn > 0) {
-            // the earliest tile of the run first; all words are requested in every round until all are there
-            const int first = (REV ? here + npred : here - npred) + (REV ? -1 : 1) * q * run;
-            const long step = (REV ? -1 : 1) * (long)a.P * 2;
-            const unsigned long long *w = a.desc + (size_t)first * 2 * a.P + min(p, a.P - 1);
-            float2 Ar = make_float2(1.f, 0.f), Sr = make_float2(0.f, 0.f);
-            auto fold = [&](auto count) {
-                constexpr int N = decltype(count)::value;    // requests per round, at least kn
-                unsigned long long w0[N], w1[N];
-                bool all = false;
-                for (unsigned spins = 0;; ++spins) {
-                    all = true;
-#pragma unroll
-                    for (int j = 0; j < N; ++j) {
-                        const unsigned long long *wj = w + step * min(j, kn - 1);
-                        w0[j] = poll_word(wj); w1[j] = poll_word(wj + a.P);
-                    }
-#pragma unroll
-                    for (int j = 0; j < N; ++j) all = all & (word_tag(w0[j]) != 0) & (word_tag(w1[j]) != 0);
-                    if (__ballot(active && !all) == 0 || spins >= a.spin_limit) break;
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                if (active && !all) atomicOr(a.err, 1u);     // gave up: flagged, and finished anyway
-#pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    if (j >= kn) continue;
-                    // a missing aggregate hands on NaN: every state that depends on it becomes NaN, so the failure cannot pass as data
-                    const bool missing = (word_tag(w0[j]) == 0) | (word_tag(w1[j]) == 0), stop = missing | (word_tag(w0[j]) == 2u);
-                    const float2 Sj = missing ? make_float2(__builtin_nanf(""), __builtin_nanf("")) : make_float2(word_value(w0[j]), word_value(w1[j]));
-                    const float2 n = cfma(power.tile, Sr, Sj), An = cmul(power.tile, Ar);
-                    Sr = make_float2(stop ? Sj.x : n.x, stop ? Sj.y : n.y);
-                    Ar = make_float2(stop ? 0.f : An.x, stop ? 0.f : An.y);
-                }
-            };
-            if (run == 1) fold(std::integral_constant<int, 1>{});
-            else fold(std::integral_constant<int, ROW_SCAN_RUN>{});
-            pS[q * NL + c] = Sr;
-            pA[q * NL + c] = Ar;
-        }
-    }
-    if (npred > 0) __syncthreads();                          // the folded runs are in LDS
-    if (on) {
-        float2 X = make_float2(0.f, 0.f);
-        for (int j = 0; j * run < npred; ++j) {
-            const float2 Al = pA[j * NL + c], Sl = pS[j * NL + c], n = cfma(Al, X, Sl);
-            const bool stop = Al.x == 0.f && Al.y == 0.f;
-            X = make_float2(stop ? Sl.x : n.x, stop ? Sl.y : n.y);
-        }
-        const float2 in = cfma(power.before, X, Sex);
-        float2 xs = make_float2(cut_before ? Sex.x : in.x, cut_before ? Sex.y : in.y), acc = make_float2(0.f, 0.f);
-        float2 *dst = reinterpret_cast<float2 *>(g.C) + (long)m0 * a.P + p;
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int r = row_of(i);
-            const float2 n = cfma(lam, xs, val[i]);
-            const bool rs = (cut >> (CH * q + i)) & 1u;
-            xs = make_float2(rs ? val[i].x : n.x, rs ? val[i].y : n.y);
-            if (REV) {
-                const bool first = (k.first >> r) & 1u;
-                const float2 v = make_float2(first ? 0.f : saved.x[i].x, first ? 0.f : saved.x[i].y);
-                acc.x = fmaf(v.x, xs.x, fmaf(v.y, xs.y, acc.x));
-                acc.y = fmaf(v.x, xs.y, fmaf(-v.y, xs.x, acc.y));
-            }
-            val[i] = xs;
-        }
-        if (active) {
-            if (m0 + ROWS <= g.M) {
-#pragma unroll
-                for (int i = 0; i < CH; ++i) dst[row_of(i) * a.P] = val[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < CH; ++i)
-                    if (m0 + row_of(i) < g.M) dst[row_of(i) * a.P] = val[i];
-            }
-            const unsigned edge = REV ? k.start : k.end;
-            float2 *at_edge = REV ? a.dx0 : a.x_last;
-            if (edge != 0 && at_edge) {
-#pragma unroll
-                for (int i = 0; i < CH; ++i) {
-                    const int r = row_of(i);                 // (lam holds conj(Abar) in reverse)
-                    if (((edge >> r) & 1u) && m0 + r < g.M)
-                        at_edge[(long)row_scan_sequence(k, r) * a.P + p] = !REV ? val[i] : (k.first >> r) & 1u ? make_float2(0.f, 0.f) : cmul(lam, val[i]);
-                }
-            }
-        }
-        if (REV) cD[q * NL + c] = acc;
-    }
-    if (REV) {
-        __syncthreads();                                     // the runs' contributions to dAbar are in LDS
-        if (q == 0 && active) {
-            float2 sum = make_float2(0.f, 0.f);
-#pragma unroll
-            for (int j = 0; j < NC; ++j) { const float2 v = cD[j * NL + c]; sum.x += v.x; sum.y += v.y; }
-            a.partial[(size_t)here * a.P + p] = sum;
         }
     }
 }
@@ -1162,15 +1212,15 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
     auto place = [](int r, int c) { return r * S + 8 * (c ^ (r & 15)); };
     constexpr bool SCANS = EPI == 7 || EPI == 8;
     RowScanStart scan;
-    RowScanMasks masks;
-    RowScanSaved saved;
+    RowScanMasks<BM> masks;
+    RowScanSaved<BM> saved;
     RowScanPowers power;
     // (beside a reduction, whose wavefronts have 128 registers, the states before the last stage)
     constexpr bool EARLY = AHEAD == 4;
     if constexpr (SCANS) {
-        scan = row_scan_start<BN>(g, tid, m0, n0);
-        masks = row_scan_ends(g, tid, m0);
-        if constexpr (EARLY) saved = row_scan_request<BN, EPI == 8>(g, masks, tid, m0, n0);
+        scan = row_scan_start<BM, BN>(g, tid, m0, n0);
+        masks = row_scan_ends<BM>(g, tid, m0);
+        if constexpr (EARLY) saved = row_scan_request<BM, BN, EPI == 8>(g, masks, tid, m0, n0);
     }
 
     // ---- the rows (a unit that hangs over the end of its row reads the row's last four values, see PkUnits)
@@ -1324,9 +1374,9 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
     StoreInputs<BM, BN, EPI> in;
     auto request = [&] {
         if constexpr (SCANS) {
-            row_scan_flags<EPI == 8>(masks, scan.flag);
-            if constexpr (EARLY) power = row_scan_powers<BN, EPI == 8>(scan.lam, tid);
-            else saved = row_scan_request<BN, EPI == 8>(g, masks, tid, m0, n0);
+            row_scan_flags<BM, EPI == 8>(masks, scan);
+            if constexpr (EARLY) power = row_scan_powers<BM, BN, EPI == 8>(scan.lam, tid);
+            else saved = row_scan_request<BM, BN, EPI == 8>(g, masks, tid, m0, n0);
         } else in.request(g, tid, 0, m0, n0);
     };
     if (cut && nst == 1) shift(0);
@@ -1380,9 +1430,9 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
     __syncthreads();
     if constexpr (SCANS) {
         constexpr int FREE = (HALF ? STAGE : 2 * STAGE) * 2 - PK32_WAVES * 1024 * 4;        // bytes of LDS behind the parts
-        static_assert(FREE >= 4 * ROW_SCAN_CHUNKS * (BN / 2) * 8, "what the scan keeps there");
-        if constexpr (!EARLY) power = row_scan_powers<BN, EPI == 8>(scan.lam, tid);
-        row_scan_body<BN, KW, EPI == 8>(g, out, reinterpret_cast<float2 *>(out + PK32_WAVES * 1024), tid, m0, n0, scan.lam, power, masks, saved);
+        static_assert(FREE >= (int)row_scan_lds_bytes(BN), "what the scan keeps there");
+        if constexpr (!EARLY) power = row_scan_powers<BM, BN, EPI == 8>(scan.lam, tid);
+        row_scan_body<BM, BN, KW, EPI == 8>(g, out, reinterpret_cast<float2 *>(out + PK32_WAVES * 1024), tid, m0, n0, scan.lam, power, masks, saved);
     } else {
         static_assert(in.BATCHES == 1, "a unit or two per thread");
         in.store(g, out, tid, 0, m0, n0);
@@ -1395,7 +1445,7 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
 //   mode 5 (scan epilogues): a unit = the tiles of one sequence and one group of column tiles, time-major; units are dealt
 //           to the XCDs, so a tile only ever waits for tiles in earlier slots of its own XCD, which were dispatched
 //           before it;
-//   mode 6 (scan epilogues on tiles of 32 rows): row tiles in the order of the scan, whose predecessors have smaller ids.
+//   mode 6 (scan epilogues with three planes): row tiles in the order of the scan, whose predecessors have smaller ids.
 __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
 {
     if (g.mode == 0) return x * g.nx + q;
@@ -1460,7 +1510,7 @@ inline PkDev make_pk_dev(const GemmArgs &a)
     g.scan = a.scan;
     g.rows = a.amaxA.rows; g.row_parts = a.amaxA.row_parts; g.row_stride = a.amaxA.row_stride;
     g.c2_rowmax = a.c2_rowmax;
-    if (BM == 32 && (a.epilogue == 7 || a.epilogue == 8)) {
+    if (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8)) {
         g.sc_rev = a.epilogue == 8;
         g.mode = 6;
     } else if ((a.epilogue == 7 || a.epilogue == 8) && a.scan.L >= BM) {

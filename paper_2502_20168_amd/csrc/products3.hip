@@ -20,7 +20,8 @@ hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const Gem
         const bool many = t.rows == 32 && t.cols == 64 && (int64_t)((a.M + 31) / 32) * ((a.N + 63) / 64) > 256;
         switch (a.epilogue) {
         SSM_ALONE(0); SSM_ALONE(1); SSM_ALONE(2); SSM_ALONE(3); SSM_ALONE(5); SSM_ALONE(6);
-        case 7:                                          // (small pairs only, as the reverse scan below)
+        case 7:
+            if (a.scan.rows == 64) return SSM_PK(64, 128, 7, 0, 4);
             SSM_SMALL(7, 0, 2);
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
@@ -32,11 +33,7 @@ hipError_t products_three_planes(const GemmArgs &a, const GemmArgs *b, const Gem
         SSM_SMALL(epi, 64, 4); \
         return hipErrorInvalidValue            /* (a small pair has at most 128 tiles of 64 x 128: 32 rows) */
     switch (a.epilogue) {
-    SSM_PAIR(0); SSM_PAIR(1); SSM_PAIR(4);
-    case 8:
-        if (!gemm_small_pair(a.M, a.N)) return hipErrorInvalidValue;
-        SSM_SMALL(8, 64, 4);
-        return hipErrorInvalidValue;
+    SSM_PAIR(0); SSM_PAIR(1); SSM_PAIR(4); SSM_PAIR(8);
     default: return hipErrorInvalidValue;
     }
 #undef SSM_PAIR

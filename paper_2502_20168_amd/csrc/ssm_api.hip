@@ -102,7 +102,7 @@ struct Layout {
     // record the largest magnitude of every token row of x and chi with atomics, the prep launch measures the rest)
     bool planes2_unfused;
     int planes;              // per operand of every product
-    bool row_scan;           // three planes: the input projection and C^H dy scan their tiles of 32 rows; the scan kernels are not launched
+    int row_scan;            // three planes: tokens per tile of the input projection and of C^H dy, which scan them (no scan kernels), or 0
     PackedLayout w_in, w_out;          // forward: Bbar and C
     PackedLayout w_gx, w_du;           // gradient pass: both transposed
     size_t hdr, lam, adj, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
@@ -137,7 +137,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
                         H >= 512 && P >= 512;
     o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
-    o.row_scan = gemm_row_scan_ok(Bt, L, P);
+    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : 0;
     o.nslab = coldot_slabs((int64_t)T, o.planes);
     o.plan = plan_scan(Bt, L, P, o.planes2_unfused);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
@@ -171,9 +171,9 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
     if (o.row_scan) {
-        o.fdesc_bytes = gemm_row_scan_desc_bytes(Bt, L, P);
+        o.fdesc_bytes = gemm_row_scan_desc_bytes((int64_t)T, L, P);
         o.fdesc = off; off += up(o.fdesc_bytes);
-        dA_elems = (T + ROW_SCAN_TOKENS - 1) / ROW_SCAN_TOKENS * P;
+        dA_elems = (T + o.row_scan - 1) / o.row_scan * P;
     }
     if (gemm_scan_shape_ok(Bt, L, P)) {
         o.dC = o.dB = gemm_plan_slabs(2 * P, H, (int64_t)T, 2, REDUCTION_128x128, 2 * P);
@@ -293,7 +293,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     float2 *xs = x ? reinterpret_cast<float2 *>(x) : reinterpret_cast<float2 *>(ws + lo.xbuf);
     const int T = (int)(Bt * L);
 
-    // Shapes whose sequences are whole numbers of 128-step pieces: the input projection scans its own
+    // Two planes, sequences of whole 128-step pieces (fused), and three planes (lo.row_scan): the input projection scans its own
     // output tile and stores the states directly (no scan kernel, Bbar u never goes to memory).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
@@ -328,7 +328,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
-        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : ROW_SCAN_TOKENS; g1.scan.spin_limit = spin_limit();
+        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : lo.row_scan; g1.scan.spin_limit = spin_limit();
         if (two_planes) g1.scan.rowmax_out = rowpart;        // of the states, for the output projection
     }
     HIP_TRY(launch_product(g1, s));
@@ -394,8 +394,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     const int T = (int)(Bt * L);
     const float *xf = reinterpret_cast<const float *>(x);
 
-    // Shapes whose sequences are whole numbers of 128-step pieces: C^H dy runs the reverse scan on its
-    // own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
+    // The same shapes: C^H dy runs the reverse scan on its own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
     PrepArgs pa{};
@@ -453,7 +452,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
-        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : ROW_SCAN_TOKENS; g3.scan.spin_limit = spin_limit();
+        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : lo.row_scan; g3.scan.spin_limit = spin_limit();
         if (two_planes) { g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart; }
     }
     // (otherwise dC needs only dy and the saved states: it shares the launch)
@@ -496,7 +495,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     ea.B = reinterpret_cast<const float2 *>(B); ea.adj = pa.adj; ea.P = (int)P; ea.H = (int)H;
     ea.dBbar_part = dBpart; ea.nsplit_B = lo.dB.slabs;
     ea.dC_part = dCpart; ea.nsplit_C = lo.dC.slabs;
-    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : lo.row_scan ? (Bt * L + ROW_SCAN_TOKENS - 1) / ROW_SCAN_TOKENS : (int64_t)Bt * lo.plan.nTB;
+    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : lo.row_scan ? (Bt * L + lo.row_scan - 1) / lo.row_scan : (int64_t)Bt * lo.plan.nTB;
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
     ea.dC = reinterpret_cast<float2 *>(dC); ea.dD = dD; ea.dlog_delta = dlog_delta;

@@ -40,7 +40,7 @@ struct AbsMax {
 // directly and Bbar u never goes to memory.  Rows are tokens (Bt sequences of L steps), columns (re, im) pairs of P
 // states.
 constexpr int SCAN_MAX_STEPS = 4096;         // longest sequence
-constexpr int ROW_SCAN_TOKENS = 32, ROW_SCAN_MAX_STEPS = 2048;       // on tiles of 32 rows (three planes)
+constexpr int ROW_SCAN_MAX_TILES = 64;       // with three planes: tiles of a sequence that come before another one
 struct ScanEpilogue {
     const float2 *lam;            // [P] Abar
     const uint8_t *is_first;      // [Bt*L] or null
@@ -49,13 +49,13 @@ struct ScanEpilogue {
     const float2 *xsaved;         // [Bt, L, P] states of the forward pass (reverse, epilogue 8)
     float2 *partial;              // [ceil(Bt * L / rows), P] per-tile rows of dAbar (reverse)
     float2 *dx0;                  // [Bt, P] or null (reverse)
-    unsigned long long *desc;     // [M / 64 * ceil(N/128) * 64][2] tagged aggregate words, rows == 32: [ceil(M / 32)][2][P]; zero on entry
+    unsigned long long *desc;     // [M / 64 * ceil(N/128) * 64][2] tagged aggregate words, three planes: [ceil(M / rows)][2][P]; zero on entry
     unsigned *err;                // set when a bounded wait gives up
     unsigned *amax_out;           // [ABSMAX_SLOTS] or null: atomic maximum of the magnitudes stored to C, zero on entry
     unsigned *xmax_out;           // [ABSMAX_SLOTS] or null (reverse, with amax_out): atomic maximum of the magnitudes of xsaved
     unsigned *rowmax_out;         // [ceil(N/128), M] or null: per column tile and row, the largest magnitude stored to C
     int L, P;
-    int rows;                     // tokens per tile: gemm_scan_rows, or ROW_SCAN_TOKENS
+    int rows;                     // tokens per tile: gemm_scan_rows, three planes: gemm_row_scan_rows
     unsigned spin_limit;
 };
 
@@ -91,9 +91,10 @@ bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P);
 int gemm_scan_rows(int64_t T, int64_t L, int64_t P, bool reverse);
 // bytes of tagged words epilogues 7 and 8 need (zeroed before the launch)
 size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P);
-// the same products on tiles of 32 rows and three planes scan their rows: whether, and the bytes of tagged words
-bool gemm_row_scan_ok(int64_t Bt, int64_t L, int64_t P);
-size_t gemm_row_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P);
+// the same products with three planes scan the rows of their tiles, sequences of any length: tokens per tile, 32 or 64, 0 where
+// they do not; and the bytes of tagged words
+int gemm_row_scan_rows(int64_t T, int64_t L, int64_t P);
+size_t gemm_row_scan_desc_bytes(int64_t T, int64_t L, int64_t P);
 // One launch: a product with packed weights and up to two reductions over tokens whose inputs are ready at the same
 // time (b, c: null when absent; c only with b).  tn_first: the reductions' work items take the first slots.
 hipError_t launch_products(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);

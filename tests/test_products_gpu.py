@@ -94,15 +94,18 @@ def test_steps_on_tiles_of_32_rows(shape):
     assert close(dxp, torch.where(first[:, None] != 0, 0.0, A.conj()[None] * g))
 
 
-# Small layers scan the rows of their 32-row tiles: sequences that start and end anywhere in a tile, rows past the last token, one tile and 64
-# tiles per sequence (and one step more: a scan kernel), one to many column groups, several workgroups along the columns
+# Three planes: the projections scan the rows of their tiles: sequences that start and end anywhere in a tile, rows past the last token, one tile and
+# 64 tiles per sequence (and one step more: a scan kernel), one to many column groups, several workgroups along the columns; 32-row tiles
 ROW_SCANS = [(40, 1, 16, 8), (3, 5, 8, 3), (2, 31, 40, 33), (33, 33, 20, 16), (7, 61, 130, 17), (2, 64, 32, 32), (21, 97, 64, 70), (5, 512, 96, 65),
-             (3, 1000, 33, 129), (1, 2047, 24, 40), (3, 2048, 20, 36), (1, 2049, 24, 40), (2, 32, 64, 1040), (64, 16, 300, 200), (13, 40, 512, 512)]
+             (3, 1000, 33, 129), (1, 2047, 24, 40), (3, 2048, 20, 36), (1, 2049, 24, 40), (2, 32, 64, 1040), (64, 16, 300, 200), (13, 40, 512, 512),
+             # and of 64-row ones
+             (30, 100, 256, 256), (9, 997, 70, 140), (3, 4095, 36, 70), (1, 4097, 40, 100), (500, 13, 40, 100), (190, 33, 24, 300), (2001, 3, 16, 129),
+             (97, 64, 40, 257), (60, 65, 33, 200), (5, 2049, 40, 33)]
 
 
 @pytest.mark.parametrize("shape", ROW_SCANS, ids=["x".join(map(str, s)) for s in ROW_SCANS])
 @pytest.mark.parametrize("resets", [0.0, 0.02, 1.0])
-def test_scans_on_tiles_of_32_rows(shape, resets):
+def test_scans_on_the_rows_of_tiles(shape, resets):
     Bt, L, H, P = shape
     print(shape, resets, flush=True)
     check_workload(wl.custom("row scans", Bt, L, H, P, p_reset=resets, with_x0=resets < 1.0, lam_re_lo=0.001, seed=31), backward=True)
