@@ -594,7 +594,7 @@ struct StoreInputs {
 //      folds them, and every thread folds the eight;
 //   4. second pass from the registers: states, x_last; reverse: dAbar (a row per tile) and dx0.
 // The powers of Abar that the folds take are computed in double precision and rounded once.  A reset selects instead of multiplying by zero: what
-// one sequence holds cannot reach the next, infinities and NaN included.  Tiles are placed in the order of their tokens (mode 6), so that
+// one sequence holds cannot reach the next, infinities and NaN included.  Tiles are placed in the order of their tokens (modes 6 and 7), so that
 // a tile only waits for tiles with smaller workgroup ids, which publish without waiting for anything; every wait is bounded.
 // Bound by its chain of dependent steps (the tile through LDS 0.3 us, either pass and the fold between them 0.4 to 0.5 each, a trip to
 // memory and back where tiles wait).  As a kernel of its own the scan paid its start, the way to memory and back, and the gap in front of it.  With scan
@@ -1445,14 +1445,16 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
 //   mode 5 (scan epilogues): a unit = the tiles of one sequence and one group of column tiles, time-major; units are dealt
 //           to the XCDs, so a tile only ever waits for tiles in earlier slots of its own XCD, which were dispatched
 //           before it;
-//   mode 6 (scan epilogues with three planes): row tiles in the order of the scan, whose predecessors have smaller ids.
+//   modes 6 and 7 (scan epilogues with three planes): row tiles in the order of the scan, whose predecessors have smaller workgroup ids.  6: the
+//           column tiles of a row tile go to different XCDs, so that few row tiles occupy all of them; 7: to one, which then reads the rows once (the
+//           row tile before it belongs to the XCD before that, or to the last one in an earlier round of slots).
 __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
 {
     if (g.mode == 0) return x * g.nx + q;
-    if (g.mode == 6) {
-        const int n = 8 * q + x, tiles = g.ntm * g.ntn;
-        if (n >= tiles || !g.sc_rev) return n;
-        return (g.ntm - 1 - n / g.ntn) * g.ntn + n % g.ntn;
+    if (g.mode == 6 || g.mode == 7) {
+        const int n = 8 * q + x;
+        const int r = g.mode == 6 ? n / g.ntn : 8 * (q / g.ntn) + x, tn = g.mode == 6 ? n % g.ntn : q % g.ntn;       // row tile in scan order
+        return r < g.ntm ? (g.sc_rev ? g.ntm - 1 - r : r) * g.ntn + tn : g.ntm * g.ntn;
     }
     const int per_unit = g.sc_nt * g.sc_cpu;
     const int uid = x + 8 * (q / per_unit), r = q % per_unit;
@@ -1512,7 +1514,10 @@ inline PkDev make_pk_dev(const GemmArgs &a)
     g.c2_rowmax = a.c2_rowmax;
     if (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8)) {
         g.sc_rev = a.epilogue == 8;
-        g.mode = 6;
+        // (mode 7 from 64 row tiles on, where the XCDs get as many within 1/8: 14 shapes of 3000 .. 30000 tokens, gradient pass: 1.6 % faster on geometric
+        // mean, 16 x 1000, 256, 256: 201.4 -> 194.9 us, 20 x 300, 500, 250: 171.2 -> 169.1, none slower by more than runs of one side differ)
+        g.mode = BM == 64 && g.ntm >= 64 ? 7 : 6;
+        if (g.mode == 7) g.nx = (g.ntm + 7) / 8 * g.ntn;
     } else if ((a.epilogue == 7 || a.epilogue == 8) && a.scan.L >= BM) {
         g.sc_rev = a.epilogue == 8;
         const int nseq = a.M / a.scan.L;
