@@ -45,7 +45,7 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
 /* What ssm_scan_fwd / ssm_scan_bwd would launch for a shape: host logic only, no GPU call.  Writes
  * SSM_PLAN_FIELDS int32 values to the HOST array out:
  *   [0] 1 when the input projection and C^H dy scan their own output tiles on two planes (no scan kernel); 0 otherwise, also where
- *       such products scan the rows of their tiles on three planes
+ *       such products scan the rows of their tiles, sequences of any length (three planes; forward also two)
  *   [1] planes per operand of the layer's products: 2 (scaled fp16) or 3 (bf16)
  *   [2] K slabs of dC, [3] K slabs of dBbar
  *   [4] gradient pass: 3 = du, dBbar slabs and dC slabs in one launch; 2 = two launches of two products

@@ -585,7 +585,7 @@ struct StoreInputs {
 };
 
 // ---------------------------------------------------------------------------------------------
-// Epilogues 7 and 8 with three planes: the resettable scan over the 32 or 64 consecutive tokens of a tile and its BN / 2 states.  The tokens are
+// Epilogues 7 and 8 with three planes, 9 with two (forward): the resettable scan over the 32 or 64 consecutive tokens of a tile and its BN / 2 states.  The tokens are
 // those of any sequences: where one starts inside the tile nothing flows in (its x0 is put into the element itself), so the length
 // of a sequence need not fit the tile.  Thread (q, c), q < 8, owns the q-th run of 4 or 8 tokens in scan order of state c:
 //   1. pass for zero incoming state; the runs are combined through LDS;
@@ -601,7 +601,8 @@ struct StoreInputs {
 // kernels and now: input projection of 16 x 64 tokens, H = P = 256 (32 rows): 5.8 + 4.8 us and 8.6; of 20 x 300, 500, 250 (64 rows): 23.1 + 14.1 and 30.6, C^H dy
 // 42.8 + 16.6 and 56.8.  Forward and gradient pass, 19 layers of 128 .. 4000 tokens on 32 rows: 13 % faster on geometric mean (16 x 64, 256, 256: 53.7 -> 47.5 us;
 // 32 x 60, 200, 100: 55.0 -> 45.9; 1 x 2048, 128, 64: 46.6 -> 39.4); 14 on 64 rows: 7 % (20 x 300, 500, 250: 182 -> 172; 9 x 997, 128, 140: 97.0 -> 82.7; 100 x 100,
-// 1000, 128: 259 -> 255).
+// 1000, 128: 259 -> 255).  Forward on two planes (64 rows; there the states' row maxima are recorded as well): 24 x 200, 1024, 512: 95.5 -> 90.4; 100 x 100, 512, 512:
+// 106.6 -> 90.2; 300 x 100: 264 -> 240, although products of many tiles alone are a little faster with 128 rows.
 // ---------------------------------------------------------------------------------------------
 constexpr int ROW_SCAN_CHUNKS = 8, ROW_SCAN_RUN = 8;          // runs of a tile; tiles that a thread folds at most
 constexpr size_t row_scan_lds_bytes(int BN) { return (size_t)4 * ROW_SCAN_CHUNKS * (BN / 2) * 8; }
@@ -715,7 +716,8 @@ __device__ __forceinline__ RowScanSaved<ROWS> row_scan_request(const PkDev &g, c
 }
 
 // tile: KW partial tiles of ROWS x BN, as tile_at places them; mem: row_scan_lds_bytes of LDS that nobody else uses
-template <int ROWS, int BN, int KW, bool REV>
+// (MAXIMA: 64 rows, whose eight tokens of a thread make a wavefront one run of all states)
+template <int ROWS, int BN, int KW, bool REV, bool MAXIMA = false>
 __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile, float2 *mem, int tid, int m0, int n0, float2 lam, const RowScanPowers &power,
                                               const RowScanMasks<ROWS> &k, const RowScanSaved<ROWS> &saved)
 {
@@ -878,6 +880,7 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
                 for (int i = 0; i < CH; ++i)
                     if (m0 + row_of(i) < g.M) dst[row_of(i) * a.P] = val[i];
             }
+            if constexpr (MAXIMA) static_assert(ROWS == 64 && BN == 128 && !REV, "rows8_wave_max");
             const Bits edge = REV ? k.start : k.end;
             float2 *at_edge = REV ? a.dx0 : a.x_last;
             if (edge != 0 && at_edge) {
@@ -890,6 +893,15 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
             }
         }
         if (REV) cD[q * NL + c] = acc;
+        if constexpr (MAXIMA) {
+            // largest magnitude of every row within the tile's states, for the product that stages the states under a scale each
+            unsigned top[CH];
+#pragma unroll
+            for (int i = 0; i < CH; ++i) top[i] = active ? __float_as_uint(fmaxf(fabsf(val[i].x), fabsf(val[i].y))) : 0u;
+            const unsigned r = rows8_wave_max(top, c);
+            const int row = m0 + CH * q + rows8_index(c);
+            if (c < 8 && row < g.M) a.rowmax_out[(size_t)(n0 / BN) * g.M + row] = r;
+        }
     }
     if (REV) {
         __syncthreads();                                     // the runs' contributions to dAbar are in LDS
@@ -928,7 +940,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     constexpr int PLANE = BM * S, STAGE = NPL * PLANE;
     constexpr int MI = BM / 32, KS = BK / 16;
     static_assert(PK_BN == 32 * NC && (BM == 64 || BM == 128), "32 columns per consumer");
-    constexpr bool SCANS = (EPI == 7 || EPI == 8) && NPL == 2, ROW_SCANS = (EPI == 7 || EPI == 8) && NPL == 3;
+    constexpr bool SCANS = (EPI == 7 || EPI == 8) && NPL == 2, ROW_SCANS = ((EPI == 7 || EPI == 8) && NPL == 3) || EPI == 9;
     constexpr int RC = SCANS ? BM / SCAN_WAVES : 8, FR = SCANS ? BM : 64;      // (scans)
     static_assert(!SCANS || BM >= 64, "scanning tiles have 64 or 128 rows");
     // k steps of the weights in flight: what 128 registers hold
@@ -1168,10 +1180,9 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     // (producers and consumers together: one copy of the code)
     if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags);
     else if constexpr (ROW_SCANS) {
-        static_assert(BM * PK_BN * 4 + row_scan_lds_bytes(PK_BN) <= NS * STAGE * 2, "what the scan keeps behind the staged tile");
         row_scan_flags<64, EPI == 8>(row_masks, row_scan);
         const RowScanPowers power = row_scan_powers<64, PK_BN, EPI == 8>(row_scan.lam, tid);
-        row_scan_body<64, PK_BN, 1, EPI == 8>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid, m0, n0,
+        row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid, m0, n0,
                                               row_scan.lam, power, row_masks, row_saved);
     } else {
 #pragma unroll
@@ -1445,7 +1456,7 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
 //   mode 5 (scan epilogues): a unit = the tiles of one sequence and one group of column tiles, time-major; units are dealt
 //           to the XCDs, so a tile only ever waits for tiles in earlier slots of its own XCD, which were dispatched
 //           before it;
-//   modes 6 and 7 (scan epilogues with three planes): row tiles in the order of the scan, whose predecessors have smaller workgroup ids.  6: the
+//   modes 6 and 7 (scans of rows): row tiles in the order of the scan, whose predecessors have smaller workgroup ids.  6: the
 //           column tiles of a row tile go to different XCDs, so that few row tiles occupy all of them; 7: to one, which then reads the rows once (the
 //           row tile before it belongs to the XCD before that, or to the last one in an earlier round of slots).
 __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
@@ -1466,10 +1477,11 @@ __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
 }
 
 // kc: k per stage
-constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, bool scans, int kc)
+constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, int epi, int kc)
 {
+    const bool scans = (epi == 7 || epi == 8) && NPL == 2, row_scans = BM == 64 && (epi >= 7) && !scans;
     const size_t st = (size_t)PK_STAGES * NPL * BM * kc * 2 + (size_t)BM * 4;          // stages and scales
-    const size_t ep = scans ? scan_lds_bytes(BM) : (size_t)BM * BN * 4 * (BM == 32 ? PK32_WAVES * 32 / BN : 1);      // the staged tile (or its parts)
+    const size_t ep = scans ? scan_lds_bytes(BM) : row_scans ? (size_t)BM * BN * 4 + row_scan_lds_bytes(BN) : (size_t)BM * BN * 4 * (BM == 32 ? PK32_WAVES * 32 / BN : 1);      // the staged tile (or its parts)
     return ep > st ? ep : st;
 }
 
@@ -1512,7 +1524,7 @@ inline PkDev make_pk_dev(const GemmArgs &a)
     g.scan = a.scan;
     g.rows = a.amaxA.rows; g.row_parts = a.amaxA.row_parts; g.row_stride = a.amaxA.row_stride;
     g.c2_rowmax = a.c2_rowmax;
-    if (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8)) {
+    if (a.epilogue == 9 || (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8))) {
         g.sc_rev = a.epilogue == 8;
         // (mode 7 from 64 row tiles on, where the XCDs get as many within 1/8: 14 shapes of 3000 .. 30000 tokens, gradient pass: 1.6 % faster on geometric
         // mean, 16 x 1000, 256, 256: 201.4 -> 194.9 us, 20 x 300, 500, 250: 171.2 -> 169.1, none slower by more than runs of one side differ)
@@ -1552,8 +1564,8 @@ hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArg
     }
     if (tn_first) { g.slot0 = (int)slots; slots += g.nx; }
     constexpr size_t tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL) : 0;
-    constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI == 7 || EPI == 8, BM == 32 ? PK32_LONG : PK_BK);
-    constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, false, PK32_SHORT) : pk;
+    constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI, BM == 32 ? PK32_LONG : PK_BK);
+    constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, EPI, PK32_SHORT) : pk;
     constexpr size_t most = pk > tnl ? pk : tnl;
     const size_t smem = tnl > pk_short ? most : (BM == 32 && ((BN == 64 && WPE == 4 && TNB == 0) || a.K <= PK32_SHORT)) ? pk_short : most;
     auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE>;

@@ -19,6 +19,7 @@ hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmA
         case 0: SSM_TALL(0, 0);
         case 3: SSM_TALL(3, 0);
         case 7: SSM_TALL(7, 0);
+        case 9: return SSM_PK(64, 128, 9, 0);
         case 8: SSM_TALL(8, 0);
         default: return hipErrorInvalidValue;
         }

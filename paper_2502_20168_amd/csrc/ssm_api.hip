@@ -98,11 +98,12 @@ struct Layout {
     // the largest magnitude of the saved states, which the reverse scan records on its way); otherwise dC shares the
     // launch of C^H dy.
     SlabPlan dC, dB;
-    // separate scan kernels, products of more than 64 tiles: two scaled fp16 planes there too (the scan kernels
+    // sequences of no whole 128-step pieces, products of more than 64 tiles: two scaled fp16 planes there too, the reverse scan (and the forward one
+    // of sequences of more than 64 tiles) in a kernel of its own (the scan kernels
     // record the largest magnitude of every token row of x and chi with atomics, the prep launch measures the rest)
     bool planes2_unfused;
     int planes;              // per operand of every product
-    int row_scan;            // three planes: tokens per tile of the input projection and of C^H dy, which scan them (no scan kernels), or 0
+    int row_scan;            // tokens per tile of the input projection (and, three planes, of C^H dy), which scans them (no scan kernel), or 0
     PackedLayout w_in, w_out;          // forward: Bbar and C
     PackedLayout w_gx, w_du;           // gradient pass: both transposed
     size_t hdr, lam, adj, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
@@ -137,7 +138,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
                         H >= 512 && P >= 512;
     o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
-    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : 0;
+    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : o.planes2_unfused && !bwd && L <= 64 * ROW_SCAN_MAX_TILES ? 64 : 0;
     o.nslab = coldot_slabs((int64_t)T, o.planes);
     o.plan = plan_scan(Bt, L, P, o.planes2_unfused);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
@@ -151,8 +152,8 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
     if (o.planes2_unfused) {
         o.amax_atomic = off; off += 2 * ABSMAX_SLOTS * 4;            // chi / x (atomic slots of the scan kernels)
-        o.row_parts = 1;
-        o.rowpart = off; off += up(T * 4);                           // rows of x / chi, directly behind: one range is cleared
+        o.row_parts = o.row_scan ? (int)((2 * P + 127) / 128) : 1;
+        o.rowpart = off; off += up(T * (size_t)o.row_parts * 4);     // rows of x / chi, directly behind: one range is cleared (scan kernels)
         o.amax_cd = o.nslab * (int)((H + 63) / 64);
         o.amax_slots = off; off += up((size_t)(PREP_PASS_BLOCKS + 2 * o.amax_cd) * 4);
         o.rowmax = off; off += up(T * (size_t)((H + 63) / 64) * 4);
@@ -171,7 +172,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
     if (o.row_scan) {
-        o.fdesc_bytes = gemm_row_scan_desc_bytes((int64_t)T, L, P);
+        o.fdesc_bytes = gemm_row_scan_desc_bytes((int64_t)T, L, P, o.row_scan);
         o.fdesc = off; off += up(o.fdesc_bytes);
         dA_elems = (T + o.row_scan - 1) / o.row_scan * P;
     }
@@ -252,7 +253,7 @@ struct StageTimer {
 // descriptors of scan kernels with several workgroups along time.
 void zero_ranges(PrepArgs &pa, const Layout &lo, char *ws, bool fused, size_t T)
 {
-    if (lo.planes == 2) {
+    if (lo.planes == 2 && !lo.row_scan) {
         pa.zero[0].p = reinterpret_cast<uint4 *>(ws + lo.amax_atomic);
         pa.zero[0].n16 = (2 * ABSMAX_SLOTS * 4 + (fused ? lo.fdesc_bytes : up(T * 4))) / 16;
     }
@@ -293,7 +294,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     float2 *xs = x ? reinterpret_cast<float2 *>(x) : reinterpret_cast<float2 *>(ws + lo.xbuf);
     const int T = (int)(Bt * L);
 
-    // Two planes, sequences of whole 128-step pieces (fused), and three planes (lo.row_scan): the input projection scans its own
+    // Two planes, sequences of whole 128-step pieces (fused), and sequences of other lengths (lo.row_scan): the input projection scans its own
     // output tile and stores the states directly (no scan kernel, Bbar u never goes to memory).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
@@ -324,7 +325,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     g1.M = T; g1.N = (int)(2 * P); g1.K = (int)H;
     if (two_planes) g1.amaxA = AbsMax{nullptr, 0, rowmax, 1, T};
     if (fused || lo.row_scan) {
-        g1.epilogue = 7;
+        g1.epilogue = fused || !two_planes ? 7 : 9;
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
@@ -394,7 +395,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     const int T = (int)(Bt * L);
     const float *xf = reinterpret_cast<const float *>(x);
 
-    // The same shapes: C^H dy runs the reverse scan on its own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
+    // The same shapes (other lengths: three planes): C^H dy runs the reverse scan on its own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
     PrepArgs pa{};
@@ -623,7 +624,10 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     GemmArgs in{}, o{}, du{}, dC{}, dB{};
     in.planes = o.planes = du.planes = lo.planes;
     in.M = o.M = du.M = (int)T; in.N = (int)(2 * P); o.N = du.N = (int)H;
-    in.epilogue = fused ? 7 : 0; in.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : 0; o.epilogue = du.epilogue = 1;
+    Layout fwd;
+    st = make_layout(Bt, L, H, P, false, fwd);
+    if (st != SSM_OK) return st;
+    in.epilogue = fused ? 7 : fwd.row_scan ? (lo.planes == 2 ? 9 : 7) : 0; in.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : fwd.row_scan; o.epilogue = du.epilogue = 1;
     dC.M = (int)H; dC.N = (int)(2 * P); dC.splits = lo.dC.slabs;
     dB.M = (int)(2 * P); dB.N = (int)H; dB.splits = lo.dB.slabs;
     const auto tile = [](PkTile t) { return t.rows * 1024 + t.cols; };

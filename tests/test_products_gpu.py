@@ -100,7 +100,9 @@ ROW_SCANS = [(40, 1, 16, 8), (3, 5, 8, 3), (2, 31, 40, 33), (33, 33, 20, 16), (7
              (3, 1000, 33, 129), (1, 2047, 24, 40), (3, 2048, 20, 36), (1, 2049, 24, 40), (2, 32, 64, 1040), (64, 16, 300, 200), (13, 40, 512, 512),
              # and of 64-row ones
              (30, 100, 256, 256), (9, 997, 70, 140), (3, 4095, 36, 70), (1, 4097, 40, 100), (500, 13, 40, 100), (190, 33, 24, 300), (2001, 3, 16, 129),
-             (97, 64, 40, 257), (60, 65, 33, 200), (5, 2049, 40, 33)]
+             (97, 64, 40, 257), (60, 65, 33, 200), (5, 2049, 40, 33),
+             # and, forward, on two planes: rows past the last token, states past the last one, many short sequences, 64 tiles and a step more
+             (14, 300, 512, 512), (33, 97, 520, 577), (300, 13, 512, 530), (1, 4095, 512, 512), (1, 4097, 513, 512)]
 
 
 @pytest.mark.parametrize("shape", ROW_SCANS, ids=["x".join(map(str, s)) for s in ROW_SCANS])
