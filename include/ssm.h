@@ -87,7 +87,9 @@ int ssm_version(void);
 /* Bound on the polls of one cross-workgroup wait (default 2^20, each poll sleeps about 128 clocks);
  * returns the previous value.  Process-wide and meant for tests: a bound of 0 makes every wait whose
  * predecessor is not ready yet give up at once, so the give-up path can be exercised while every
- * kernel still terminates.                                                                      */
+ * kernel still terminates.  (Projections that scan the rows of their tiles, see ssm_plan_describe,
+ * never give up: a workgroup that has waited for that many polls, or for 256, computes itself what
+ * is missing, with the same result to the last bit.)                                            */
 uint32_t ssm_set_spin_limit(uint32_t polls);
 
 /* Scratch bytes the forward (want_bwd = 0) or the gradient pass (want_bwd != 0) needs for the

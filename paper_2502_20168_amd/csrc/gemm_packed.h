@@ -39,6 +39,9 @@ __device__ __forceinline__ int tile_at(int row, int col)
     return BN == 32 ? (row ^ ((row >> 2) & 1)) * BN + col : row * BN + (col ^ ((row & 4) << 3));
 }
 
+// the resettable scan over the rows of a tile (sequences of any length): row_scan_body
+constexpr bool scans_rows(int planes, int epilogue) { return epilogue == 9 || (planes == 3 && (epilogue == 7 || epilogue == 8)); }
+
 struct PkDev {
     const float *A; long lda;
     const uint4 *frag; const int *bexp;     // packed weights; log2 of the scale of every row n (two planes)
@@ -594,8 +597,12 @@ struct StoreInputs {
 //      folds them, and every thread folds the eight;
 //   4. second pass from the registers: states, x_last; reverse: dAbar (a row per tile) and dx0.
 // The powers of Abar that the folds take are computed in double precision and rounded once.  A reset selects instead of multiplying by zero: what
-// one sequence holds cannot reach the next, infinities and NaN included.  Tiles are placed in the order of their tokens (modes 6 and 7), so that
-// a tile only waits for tiles with smaller workgroup ids, which publish without waiting for anything; every wait is bounded.
+// one sequence holds cannot reach the next, infinities and NaN included.
+// A tile waits for tiles on other XCDs.  They have smaller workgroup ids (modes 6 and 7) and publish without waiting for anything, but they need not have been
+// started: every XCD starts its share of a launch on its own, and one can be full of tiles of another launch, on another stream, that wait for theirs behind tiles
+// of this one.  So no tile relies on it: after ROW_SCAN_POLLS polls it computes the aggregate that is missing itself, to the last bit as
+// its own tile would, publishes it and starts again (gemm_pk_kernel).  Nothing else on the way: as placement in chains of one XCD (mode 5) the passes of 18 layers
+// took up to 8 % longer (the rows are read by several XCDs, or the XCDs have unequal shares), with row tiles drawn from counters 4 %, with this 0.7 %.
 // Bound by its chain of dependent steps (the tile through LDS 0.3 us, either pass and the fold between them 0.4 to 0.5 each, a trip to
 // memory and back where tiles wait).  As a kernel of its own the scan paid its start, the way to memory and back, and the gap in front of it.  With scan
 // kernels and now: input projection of 16 x 64 tokens, H = P = 256 (32 rows): 5.8 + 4.8 us and 8.6; of 20 x 300, 500, 250 (64 rows): 23.1 + 14.1 and 30.6, C^H dy
@@ -717,14 +724,16 @@ __device__ __forceinline__ RowScanSaved<ROWS> row_scan_request(const PkDev &g, c
 
 // tile: KW partial tiles of ROWS x BN, as tile_at places them; mem: row_scan_lds_bytes of LDS that nobody else uses
 // (MAXIMA: 64 rows, whose eight tokens of a thread make a wavefront one run of all states)
+// ahead: only the aggregate is published, for another tile's sake.  Returns -1, or the row tile whose aggregate is missing (nothing is stored then).
 template <int ROWS, int BN, int KW, bool REV, bool MAXIMA = false>
-__device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile, float2 *mem, int tid, int m0, int n0, float2 lam, const RowScanPowers &power,
-                                              const RowScanMasks<ROWS> &k, const RowScanSaved<ROWS> &saved)
+__device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, float2 *mem, int tid, int m0, int n0, float2 lam, const RowScanPowers &power,
+                                             const RowScanMasks<ROWS> &k, const RowScanSaved<ROWS> &saved, bool ahead)
 {
     using Bits = typename RowScanMasks<ROWS>::Bits;
     constexpr int NL = BN / 2, NC = ROW_SCAN_CHUNKS, CH = ROWS / NC;
     const ScanEpilogue &a = g.scan;
     float2 *cS = mem, *pS = mem + NC * NL, *pA = mem + 2 * NC * NL, *cD = mem + 3 * NC * NL;
+    int *missing = reinterpret_cast<int *>(cS + (NC - 1) * NL);      // (the last run's state is nobody's input) row tile that is waited for in vain, or -1
     const int c = tid % NL, q = tid / NL, p = n0 / 2 + c;
     const bool on = q < NC, active = on && p < a.P;          // (on: whole wavefronts)
     auto row_of = [&](int i) { return REV ? ROWS - 1 - (CH * q + i) : CH * q + i; };
@@ -773,8 +782,9 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
             const bool r = (cut >> (CH * q + i)) & 1u;
             S = make_float2(r ? val[i].x : n.x, r ? val[i].y : n.y);
         }
-        cS[q * NL + c] = S;
+        if (q < NC - 1) cS[q * NL + c] = S;
     }
+    if (tid == 0) *missing = -1;
     __syncthreads();                                         // the states of the runs are in LDS
     float2 Sex = make_float2(0.f, 0.f);
     const bool cut_before = on && (cut & (((Bits)1 << (CH * (q & 7))) - 1)) != 0;       // a reset in an earlier run of the tile
@@ -789,7 +799,7 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
             const float2 m = make_float2(any ? Sc[j].x : n.x, any ? Sc[j].y : n.y);
             Sex = make_float2(j < q ? m.x : Sex.x, j < q ? m.y : Sex.y);
         }
-        if (q == NC - 1 && active && has_succ) {
+        if (q == NC - 1 && active && (has_succ || ahead)) {
             const bool any = (cut >> (CH * (NC - 1))) != 0;
             const float2 n = cfma(power.run, Sex, S);
             unsigned long long *word = a.desc + (size_t)here * 2 * a.P + p;
@@ -797,7 +807,7 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
             publish_word(word, any ? S.x : n.x, tag);
             publish_word(word + a.P, any ? S.y : n.y, tag);
         }
-        const int kn = min(run, npred - q * run);
+        const int kn = ahead ? 0 : min(run, npred - q * run);
         if (kn > 0) {
             // the earliest tile of the run first; all words are requested in every round until all are there
             const int first = (REV ? here + npred : here - npred) + (REV ? -1 : 1) * q * run;
@@ -820,13 +830,12 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
                     if (__ballot(active && !all) == 0 || spins >= a.spin_limit) break;
                     __builtin_amdgcn_s_sleep(1);
                 }
-                if (active && !all) atomicOr(a.err, 1u);     // gave up: flagged, and finished anyway
 #pragma unroll
                 for (int j = 0; j < N; ++j) {
                     if (j0 + j >= kn) continue;
-                    // a missing aggregate hands on NaN: every state that depends on it becomes NaN, so the failure cannot pass as data
-                    const bool missing = (word_tag(w0[j]) == 0) | (word_tag(w1[j]) == 0), stop = missing | (word_tag(w0[j]) == 2u);
-                    const float2 Sj = missing ? make_float2(__builtin_nanf(""), __builtin_nanf("")) : make_float2(word_value(w0[j]), word_value(w1[j]));
+                    if (active && (word_tag(w0[j]) == 0 || word_tag(w1[j]) == 0)) *missing = first + (REV ? -1 : 1) * (j0 + j);       // (any of them)
+                    const bool stop = word_tag(w0[j]) == 2u;
+                    const float2 Sj = make_float2(word_value(w0[j]), word_value(w1[j]));
                     const float2 n = cfma(power.tile, Sr, Sj), An = cmul(power.tile, Ar);
                     Sr = make_float2(stop ? Sj.x : n.x, stop ? Sj.y : n.y);
                     Ar = make_float2(stop ? 0.f : An.x, stop ? 0.f : An.y);
@@ -839,7 +848,12 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
             pA[q * NL + c] = Ar;
         }
     }
-    if (npred > 0) __syncthreads();                          // the folded runs are in LDS
+    if (ahead) return -1;
+    if (npred > 0) {
+        __syncthreads();                                     // the folded runs are in LDS
+        const int m = __builtin_amdgcn_readfirstlane(*missing);
+        if (m >= 0) return m;
+    }
     if (on) {
         float2 X = make_float2(0.f, 0.f);
         for (int j0 = 0; j0 * run < npred; j0 += 4) {        // (four reads at a time; those behind the last run are not used)
@@ -912,6 +926,7 @@ __device__ __forceinline__ void row_scan_body(const PkDev &g, const float *tile,
             a.partial[(size_t)here * a.P + p] = sum;
         }
     }
+    return -1;
 }
 
 // Place of the c-th 16-byte piece of row r of an LDS plane (rows of 128 bytes, no padding): the pieces of a row are permuted
@@ -932,8 +947,9 @@ __device__ __forceinline__ float4 narrow_unit(const PkDev &g, int row, int k)
     return make_float4(v[0], v[1], v[2], v[3]);
 }
 
+// ahead and result: see row_scan_body (other epilogues: false and -1)
 template <int BM, int NPL, int EPI>
-__device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tile, int tid)
+__device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tile, int tid, bool ahead)
 {
     constexpr int NC = PK_CONSUMERS, NP = PK_PRODUCERS, BK = PK_BK, NS = PK_STAGES, PT = 64 * NP;
     constexpr int S = BK;                         // row stride of an LDS plane in halves; see pk_swizzle
@@ -1182,8 +1198,8 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
     else if constexpr (ROW_SCANS) {
         row_scan_flags<64, EPI == 8>(row_masks, row_scan);
         const RowScanPowers power = row_scan_powers<64, PK_BN, EPI == 8>(row_scan.lam, tid);
-        row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid, m0, n0,
-                                              row_scan.lam, power, row_masks, row_saved);
+        return row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid,
+                                                               m0, n0, row_scan.lam, power, row_masks, row_saved, ahead);
     } else {
 #pragma unroll
         for (int batch = 0; batch < in.BATCHES; ++batch) {
@@ -1191,6 +1207,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
             in.store(g, reinterpret_cast<const float *>(smem_raw), tid, batch, m0, n0);
         }
     }
+    return -1;
 }
 
 // Tiles of 32 rows: launches that leave a workgroup a CU to itself, whose time is a chain of dependent steps rather than
@@ -1207,7 +1224,7 @@ __device__ __forceinline__ void gemm_pk_tile(const PkDev &g, unsigned char *smem
 // first stage stands in front of it, the loop has a single way out, and there is no branch on lanes in it.
 // AHEAD: k steps of the weights in flight: four; two beside a reduction, whose sixteen wavefronts leave each 128 registers
 template <int BN, int NPL, int EPI, int KC, int AHEAD>
-__device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tid)
+__device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tid, bool ahead)
 {
     constexpr int BM = 32, S = KC, PLANE = BM * S, STAGE = NPL * PLANE, KS = KC / 16;
     constexpr int CG = BN / 32, KW = PK32_WAVES / CG, KSW = KS / KW;         // column groups, wavefronts per group, k steps per wavefront and stage
@@ -1443,11 +1460,12 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
         constexpr int FREE = (HALF ? STAGE : 2 * STAGE) * 2 - PK32_WAVES * 1024 * 4;        // bytes of LDS behind the parts
         static_assert(FREE >= (int)row_scan_lds_bytes(BN), "what the scan keeps there");
         if constexpr (!EARLY) power = row_scan_powers<BM, BN, EPI == 8>(scan.lam, tid);
-        row_scan_body<BM, BN, KW, EPI == 8>(g, out, reinterpret_cast<float2 *>(out + PK32_WAVES * 1024), tid, m0, n0, scan.lam, power, masks, saved);
+        return row_scan_body<BM, BN, KW, EPI == 8>(g, out, reinterpret_cast<float2 *>(out + PK32_WAVES * 1024), tid, m0, n0, scan.lam, power, masks, saved, ahead);
     } else {
         static_assert(in.BATCHES == 1, "a unit or two per thread");
         in.store(g, out, tid, 0, m0, n0);
     }
+    return -1;
 }
 
 // Tile of the workgroup in slot q of XCD x (workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2):
@@ -1456,7 +1474,7 @@ __device__ __forceinline__ void gemm_pk32_tile(const PkDev &g, unsigned char *sm
 //   mode 5 (scan epilogues): a unit = the tiles of one sequence and one group of column tiles, time-major; units are dealt
 //           to the XCDs, so a tile only ever waits for tiles in earlier slots of its own XCD, which were dispatched
 //           before it;
-//   modes 6 and 7 (scans of rows): row tiles in the order of the scan, whose predecessors have smaller workgroup ids.  6: the
+//   modes 6 and 7 (scans of rows): row tiles in the order of the scan, so that predecessors have smaller workgroup ids.  6: the
 //           column tiles of a row tile go to different XCDs, so that few row tiles occupy all of them; 7: to one, which then reads the rows once (the
 //           row tile before it belongs to the XCD before that, or to the last one in an earlier round of slots).
 __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
@@ -1490,6 +1508,22 @@ constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, int epi, int kc)
 // (a reduction may have more wavefronts than a product; the surplus leaves a product's workgroup at once)
 constexpr int pk_threads(int TNB) { return TNB > 0 ? 64 * (tn_consumers(TNB) + tn_producers(TNB)) : PK_THREADS; }
 
+// A pointer that was read as a word: to global memory.  (The compiler knows that of the kernel's arguments themselves.  A load from an address that it does not
+// know it of counts against LDS as well as memory, and every wait for one is a wait for all.)
+template <class T> __device__ __forceinline__ void in_global(T *&p)
+{
+    auto q = (T __attribute__((address_space(1))) *)p;
+    asm("" : "+s"(q));
+    p = (T *)q;
+}
+__device__ __forceinline__ void in_global(PkDev &g)
+{
+    in_global(g.A); in_global(g.frag); in_global(g.bexp); in_global(g.C); in_global(g.rows);
+    ScanEpilogue &a = g.scan;
+    in_global(a.lam); in_global(a.is_first); in_global(a.x0); in_global(a.x_last); in_global(a.xsaved); in_global(a.partial);
+    in_global(a.dx0); in_global(a.desc); in_global(a.err); in_global(a.rowmax_out);
+}
+
 template <int BM, int BN, int NPL, int EPI, int TNB, int WPE>
 __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
 {
@@ -1499,11 +1533,33 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
         const int tile = pk_place(g, x, q - g.slot0);
         if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
         const int tm = tile / g.ntn, tn = tile - tm * g.ntn;
-        if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid);
-        else if constexpr (BM == 32) {
-            if (g.K <= PK32_SHORT) gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid);
-            else gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid);
-        } else gemm_pk_tile<BM, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid);
+        auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
+            if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+            else if constexpr (BM == 32) {
+                if (g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+            } else return gemm_pk_tile<BM, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
+        };
+        if constexpr (!scans_rows(NPL, EPI)) run(g, tm, tid, false);
+        else {
+            // Row tile m: this workgroup's, or one whose aggregate it misses.  (At most two rounds per tile of the sequence; the bound on them only keeps a mistake
+            // from hanging.)  Nothing of a round stays in registers for another one, the arguments included: that would take more than there are.
+            auto args = (const unsigned long long __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+            for (int m = tm, rounds = 0;; ++rounds) {
+                int id = tid;
+                asm volatile("" : "+v"(id), "+s"(m), "+s"(args));
+                static_assert(sizeof(PkDev) % 8 == 0, "whole words, the first of the arguments");
+                union { unsigned long long w[sizeof(PkDev) / 8]; PkDev g; } own;
+#pragma unroll
+                for (size_t i = 0; i < sizeof(PkDev) / 8; ++i) own.w[i] = args[i];
+                in_global(own.g);
+                const int missing = __builtin_amdgcn_readfirstlane(run(own.g, m, id, m != tm));
+                if (missing < 0 && m == tm) break;
+                if (rounds > 4 * ROW_SCAN_MAX_TILES) { atomicOr(own.g.scan.err, 1u); break; }
+                m = missing < 0 ? tm : missing;
+                __syncthreads();                             // LDS is free
+            }
+        }
     } else if constexpr (TNB > 0) {
         if (q >= t0.slot0 && q < t0.slot0 + t0.nx) gemm_tn_problem<TNB, NPL>(t0, smem_raw, x, q - t0.slot0, tid);
         // (a branch of its own: choosing between the two argument structs at run time would put them on the stack)

@@ -4,6 +4,7 @@
 #include "../../include/ssm_measure.h"
 #include "ssm_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <vector>
 
@@ -329,7 +330,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
-        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : lo.row_scan; g1.scan.spin_limit = spin_limit();
+        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : lo.row_scan; g1.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
         if (two_planes) g1.scan.rowmax_out = rowpart;        // of the states, for the output projection
     }
     HIP_TRY(launch_product(g1, s));
@@ -453,7 +454,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
-        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : lo.row_scan; g3.scan.spin_limit = spin_limit();
+        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : lo.row_scan; g3.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
         if (two_planes) { g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart; }
     }
     // (otherwise dC needs only dy and the saved states: it shares the launch)

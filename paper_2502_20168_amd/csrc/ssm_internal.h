@@ -41,7 +41,8 @@ struct AbsMax {
 // directly and Bbar u never goes to memory.  Rows are tokens (Bt sequences of L steps), columns (re, im) pairs of P
 // states.
 constexpr int SCAN_MAX_STEPS = 4096;         // longest sequence
-constexpr int ROW_SCAN_MAX_TILES = 64;       // with three planes: tiles of a sequence that come before another one
+constexpr int ROW_SCAN_MAX_TILES = 64;       // scans of rows: tiles of a sequence that come before another one
+constexpr uint32_t ROW_SCAN_POLLS = 256;     // polls after which a tile computes the aggregate that it waits for itself: a few times as long as a launch takes
 struct ScanEpilogue {
     const float2 *lam;            // [P] Abar
     const uint8_t *is_first;      // [Bt*L] or null

@@ -131,3 +131,68 @@ def test_what_one_sequence_holds_does_not_reach_the_next_in_its_tile():
     for good, got in zip(*out):
         for i in (0, 2, 4):
             assert torch.equal(good[i], got[i])
+
+
+@pytest.mark.parametrize("shape", [(8, 100, 256, 256), (1, 2047, 24, 40), (2, 64, 32, 32), (20, 300, 500, 250), (9, 997, 70, 140), (3, 4095, 36, 70),
+                                   (5, 1500, 512, 512), (24, 200, 1024, 512)], ids=lambda s: "x".join(map(str, s)))
+def test_tiles_that_wait_for_nobody(shape):
+    """With no polls a tile whose predecessors have not published yet computes their aggregates itself: the same results to the last bit,
+    no give-up and no NaN, on 32 and 64 rows, three planes (either direction) and two (forward; the other way a scan kernel may give up)."""
+    import torch
+    Bt, L, H, P = shape
+    print(shape, flush=True)
+    d = ssm.to_device(wl.gen_inputs(wl.custom("alone", Bt, L, H, P, p_reset=0.005, with_x0=True, lam_re_lo=0.001, seed=41)))
+    par = [d[k] for k in ("Lambda", "B", "C", "D", "log_delta")]
+    ws_f, ws_b = ssm.alloc_workspace(Bt, L, H, P, False), ssm.alloc_workspace(Bt, L, H, P, True)
+    two_planes = ssm.ssm_plan_describe(Bt, L, H, P)["planes"] == 2
+
+    def run():
+        f = ssm.ssm_scan_fwd(*par, d["u"], d["is_first"], d["x0"], workspace=ws_f)
+        out = dict(f)
+        if not two_planes:
+            out.update(ssm.ssm_scan_bwd(*par, d["u"], d["is_first"], d["x0"], f["x"], d["dy"], workspace=ws_b))
+            assert ssm.ssm_workspace_status(ws_b) == ssm.SSM_OK
+        assert ssm.ssm_workspace_status(ws_f) == ssm.SSM_OK
+        return out
+
+    want = run()
+    old = ssm.ssm_set_spin_limit(0)
+    try:
+        got = run()
+    finally:
+        ssm.ssm_set_spin_limit(old)
+    for k in want:
+        assert torch.equal(got[k], want[k]), k
+    again = run()
+    for k in want:
+        assert torch.equal(again[k], want[k]), k
+
+
+def test_row_scans_of_more_workgroups_than_fit_on_four_streams():
+    """The header's promise for launches whose tiles wait for one another and are not all resident at once: forward and gradient passes on four
+    streams with workspaces of their own, queued together, come out as those alone, to the last bit."""
+    import torch
+    work = []
+    for i, shp in enumerate([(16, 1000, 256, 256), (30, 1000, 512, 512), (100, 100, 256, 200), (3, 2048, 64, 128)]):
+        d = ssm.to_device(wl.gen_inputs(wl.custom("streams%d" % i, *shp, p_reset=0.002, with_x0=True, seed=50 + i)))
+        work.append((d, ssm.alloc_workspace(*shp, False), ssm.alloc_workspace(*shp, True), torch.cuda.Stream()))
+
+    def run(d, ws_f, ws_b, stream=None):
+        par = [d[k] for k in ("Lambda", "B", "C", "D", "log_delta")]
+        f = ssm.ssm_scan_fwd(*par, d["u"], d["is_first"], d["x0"], workspace=ws_f, stream=stream)
+        b = ssm.ssm_scan_bwd(*par, d["u"], d["is_first"], d["x0"], f["x"], d["dy"], workspace=ws_b, stream=stream)
+        return {**f, **b}
+
+    want = [run(*w[:3]) for w in work]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(6):
+        for w in work:
+            with torch.cuda.stream(w[3]):
+                got.append(run(*w))
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        w = work[i % 4]
+        assert ssm.ssm_workspace_status(w[1]) == ssm.SSM_OK and ssm.ssm_workspace_status(w[2]) == ssm.SSM_OK
+        for k in g:
+            assert torch.equal(g[k], want[i % 4][k]), (i, k)
