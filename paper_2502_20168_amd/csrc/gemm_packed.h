@@ -871,6 +871,8 @@ __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, 
         const float2 in = cfma(power.before, X, Sex);
         float2 xs = make_float2(cut_before ? Sex.x : in.x, cut_before ? Sex.y : in.y), acc = make_float2(0.f, 0.f);
         float2 *dst = reinterpret_cast<float2 *>(g.C) + (long)m0 * a.P + p;
+        // rows whose x_{t-1} is no factor of dAbar: where the state is dropped, and those past the last token
+        const Bits no_factor = k.first | (m0 + ROWS > g.M ? ~(Bits)0 << (g.M - m0) : (Bits)0);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int r = row_of(i);
@@ -878,8 +880,8 @@ __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, 
             const bool rs = (cut >> (CH * q + i)) & 1u;
             xs = make_float2(rs ? val[i].x : n.x, rs ? val[i].y : n.y);
             if (REV) {
-                const bool first = (k.first >> r) & 1u;
-                const float2 v = make_float2(first ? 0.f : saved.x[i].x, first ? 0.f : saved.x[i].y);
+                const bool none = (no_factor >> r) & 1u;
+                const float2 v = make_float2(none ? 0.f : saved.x[i].x, none ? 0.f : saved.x[i].y);
                 acc.x = fmaf(v.x, xs.x, fmaf(v.y, xs.y, acc.x));
                 acc.y = fmaf(v.x, xs.y, fmaf(-v.y, xs.x, acc.y));
             }

@@ -196,3 +196,20 @@ def test_row_scans_of_more_workgroups_than_fit_on_four_streams():
         assert ssm.ssm_workspace_status(w[1]) == ssm.SSM_OK and ssm.ssm_workspace_status(w[2]) == ssm.SSM_OK
         for k in g:
             assert torch.equal(g[k], want[i % 4][k]), (i, k)
+
+
+@pytest.mark.parametrize("shape", [(3, 50, 32, 24), (8, 100, 256, 256), (30, 101, 64, 300)], ids=lambda s: "x".join(map(str, s)))
+def test_the_last_saved_state_is_no_factor_of_the_transitions_gradient(shape):
+    """x_{t-1} chi_t over the steps there are: what follows the last state does not count, also where the last tile has rows past it."""
+    import torch
+    Bt, L, H, P = shape
+    d = ssm.to_device(wl.gen_inputs(wl.custom("last", Bt, L, H, P, p_reset=0.02, with_x0=True, seed=43)))
+    par = [d[k] for k in ("Lambda", "B", "C", "D", "log_delta")]
+    x = ssm.ssm_scan_fwd(*par, d["u"], d["is_first"], d["x0"])["x"]
+    out = []
+    for value in (1.0, float("inf"), float("nan")):
+        x[-1, -1] = value
+        out.append(ssm.ssm_scan_bwd(*par, d["u"], d["is_first"], d["x0"], x, d["dy"]))
+    for o in out[1:]:
+        for k in ("du", "dLambda", "dB", "dlog_delta", "dx0"):
+            assert torch.equal(o[k], out[0][k]), k
