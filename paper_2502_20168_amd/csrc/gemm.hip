@@ -100,9 +100,8 @@ int gemm_row_scan_rows(int64_t T, int64_t L, int64_t P)
     return small || (P > 32 && ((T + 63) / 64) * ((2 * P + 127) / 128) > 128) ? rows : 0;
 }
 
-size_t gemm_row_scan_desc_bytes(int64_t T, int64_t L, int64_t P, int rows)
+size_t gemm_row_scan_desc_bytes(int64_t T, int64_t P, int rows)
 {
-    if (rows % L == 0) return 0;                     // a tile holds whole sequences: nothing is handed over
     return (size_t)((T + rows - 1) / rows) * P * 2 * sizeof(unsigned long long);
 }
 

@@ -173,8 +173,10 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
     if (o.row_scan) {
-        o.fdesc_bytes = gemm_row_scan_desc_bytes((int64_t)T, L, P, o.row_scan);
-        o.fdesc = off; off += up(o.fdesc_bytes);
+        // (reserved also where a tile holds whole sequences and nothing is handed over, so that a workspace holds shorter sequences as well)
+        const size_t words = gemm_row_scan_desc_bytes((int64_t)T, P, o.row_scan);
+        o.fdesc = off; off += up(words);
+        o.fdesc_bytes = o.row_scan % L == 0 ? 0 : words;
         dA_elems = (T + o.row_scan - 1) / o.row_scan * P;
     }
     if (gemm_scan_shape_ok(Bt, L, P)) {
@@ -198,6 +200,13 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.adj = off; off += up((size_t)P * sizeof(StateAdjoint));
     }
     o.total = off;
+    if (bwd && o.planes2_unfused) {
+        // a workspace of the gradient pass holds the forward pass as well, whose row maxima can be more (a word per column tile)
+        Layout fwd;
+        st = make_layout(Bt, L, H, P, false, fwd);
+        if (st != SSM_OK) return st;
+        o.total = std::max(o.total, fwd.total);
+    }
     return SSM_OK;
 }
 

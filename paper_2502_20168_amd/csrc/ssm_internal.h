@@ -96,7 +96,7 @@ size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P);
 // the same products with three planes scan the rows of their tiles, sequences of any length: tokens per tile, 32 or 64, 0 where
 // they do not; and the bytes of tagged words
 int gemm_row_scan_rows(int64_t T, int64_t L, int64_t P);
-size_t gemm_row_scan_desc_bytes(int64_t T, int64_t L, int64_t P, int rows);
+size_t gemm_row_scan_desc_bytes(int64_t T, int64_t P, int rows);
 // One launch: a product with packed weights and up to two reductions over tokens whose inputs are ready at the same
 // time (b, c: null when absent; c only with b).  tn_first: the reductions' work items take the first slots.
 hipError_t launch_products(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c, bool tn_first, hipStream_t s);

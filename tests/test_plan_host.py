@@ -144,3 +144,17 @@ def test_the_binding_loads_torch_before_the_library():
     out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0, out.stderr
     assert out.stdout.strip().splitlines()[-1] == "2"
+
+
+@pytest.mark.parametrize("Bt,L,H,P", [(238, 1371, 1080, 970), (101, 4072, 662, 736), (207, 3228, 648, 1018), (24, 200, 1024, 512), (20, 300, 500, 250)])
+def test_a_workspace_of_the_gradient_pass_holds_the_forward_pass(Bt, L, H, P):
+    assert ssm.ssm_workspace_bytes(Bt, L, H, P, False) <= ssm.ssm_workspace_bytes(Bt, L, H, P, True)
+
+
+@pytest.mark.parametrize("long,short", [((1, 4, 6, 124), (1, 3, 6, 124)), ((3, 4, 286, 5), (3, 3, 286, 5)), ((2, 32, 64, 64), (2, 31, 64, 64)),
+                                        ((4, 64, 40, 300), (4, 63, 40, 300)), ((500, 16, 200, 200), (500, 13, 200, 200))])
+def test_a_workspace_holds_shorter_sequences_as_well(long, short):
+    """Also where the longer ones fill whole tiles, whose rows hand nothing over."""
+    for bwd in (False, True):
+        assert ssm.ssm_workspace_bytes(*short, bwd) <= ssm.ssm_workspace_bytes(*long, bwd)
+        assert ssm.ssm_block_workspace_bytes(*short, bwd) <= ssm.ssm_block_workspace_bytes(*long, bwd)
