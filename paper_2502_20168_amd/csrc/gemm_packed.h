@@ -1224,7 +1224,9 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
 // multiplied, and now: 1024 x 512 x 1024: 9.4 and 8.5 us; 256 x 512 x 1024: 8.2 and 6.1; 64 x 512 x 1024: 7.2 and 4.9.
 //   A wait counts the requests made behind the one it is for.  So that the compiler finds the same order in every round of the loop, the
 // first stage stands in front of it, the loop has a single way out, and there is no branch on lanes in it.
-// AHEAD: k steps of the weights in flight: four; two beside a reduction, whose sixteen wavefronts leave each 128 registers
+// AHEAD: k steps of the weights in flight: four; two beside a reduction, whose sixteen wavefronts leave each 128 registers (short stages
+// of at most 64 columns: four there too).  No variant spills.  With four on short stages of 128 columns and the places of all eight steps of a stage kept, those beside a
+// reduction spilled up to 14: forward and gradient pass of 32 x 60 tokens, H = 100, P = 200: 55.0 -> 51.4 us; 16 x 64, 128, 256: 42.0 -> 39.8; 16 x 64, 256, 256: 47.2 -> 46.8.
 template <int BN, int NPL, int EPI, int KC, int AHEAD>
 __device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tid, bool ahead)
 {
@@ -1331,14 +1333,18 @@ __device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *sme
     v16f acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    // fragment of a k step of the stage in LDS: row li, k = 16 ks + 8 hh ..
+    // Fragment of a k step of the stage in LDS: row li, k = 16 ks + 8 hh ..  Its piece is 2 (kw + KW j) + hh, and 2 kw + hh < 2 KW, a power of two: step j's place is step
+    // 0's with bits of j flipped.  (Beside a reduction, where there are no registers to keep the places of eight steps in, they are flipped at every step.)
+    const int frag0 = place(li, 2 * kw + hh);
     int frag_at[KSW];
 #pragma unroll
-    for (int j = 0; j < KSW; ++j) frag_at[j] = place(li, 2 * (kw + KW * j) + hh);
+    for (int j = 0; j < KSW; ++j) frag_at[j] = frag0 ^ 16 * KW * j;
     bf16x8 fa[2][NPL];
     auto load_rows = [&](int set, const __bf16 *st, int j) {
+        int at = frag_at[j];
+        if constexpr (AHEAD == 2 && KSW == 8) asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "i"(16 * KW * j), "v"(frag0));
 #pragma unroll
-        for (int p = 0; p < NPL; ++p) fa[set][p] = *reinterpret_cast<const bf16x8 *>(st + p * PLANE + frag_at[j]);
+        for (int p = 0; p < NPL; ++p) fa[set][p] = *reinterpret_cast<const bf16x8 *>(st + p * PLANE + at);
     };
     // product q of a k step, smallest first (the order of gemm_pk_tile)
     constexpr int NPROD = NPL == 3 ? 6 : 3;
@@ -1538,7 +1544,7 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
         auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
             if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             else if constexpr (BM == 32) {
-                if (g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                if (g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, TNB == 0 || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
                 return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             } else return gemm_pk_tile<BM, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
         };

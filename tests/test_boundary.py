@@ -194,3 +194,15 @@ def test_binding_refuses_cpu_tensors(lib):
     with pytest.raises(ValueError):
         ssm.ssm_scan_fwd(z, torch.zeros(4, 3, dtype=torch.complex64), torch.zeros(3, 4, dtype=torch.complex64),
                          torch.zeros(3), torch.zeros(4), torch.zeros(1, 5, 3))
+
+
+def test_no_kernel_keeps_registers_in_memory(lib):
+    """The metadata of the built kernels: a private segment would mean registers that did not fit, spilled inside the loops of the products."""
+    data, key = open(ssm.LIB_PATH, "rb").read(), b".private_segment_fixed_size"
+    sizes, at = [], data.find(key)
+    while at >= 0:
+        at += len(key)                                    # a msgpack integer follows
+        wide = {0xcc: 1, 0xcd: 2, 0xce: 4}.get(data[at], 0)
+        sizes.append(int.from_bytes(data[at + 1:at + 1 + wide], "big") if wide else data[at])
+        at = data.find(key, at)
+    assert len(sizes) > 60 and not any(sizes), sizes
