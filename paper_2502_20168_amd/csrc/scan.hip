@@ -431,7 +431,10 @@ __global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(S
 
 // Chunks and states of a workgroup.  16 states are one 128-byte line of a step.
 //   up to 256 steps: about 256 threads, as many states as that leaves for whole sequences;
-//   up to 512 steps, and up to 1024 where there are 64 such workgroups: whole sequences of 16 states;
+//   up to 512 steps: whole sequences of 16 states; up to 1024 as well where there are 64 such workgroups, and either one per CU at most, or up to three rounds of them
+//   that leave no more than three tenths of the chip's threads idle (one of 1024 threads has a CU to itself, so nothing overlaps its loads and stores: what is saved is
+//   the clearing launch).  Forward and reverse call with a look-back and with whole sequences: 10 x 520 x 400: 44.3 and 36.5;
+//   12 x 1024 x 1024: 171 and 165; 8 x 700 x 640: 61.1 and 64.2; 100 x 600 x 200: 193 and 199; 28 x 1024 x 768: 322 and 330;
 //   else a look-back, over blocks of 256 steps; of 1024 or 512 where that makes 192 to 384 of them, about one per CU (with more of
 //   them, small workgroups that overlap are better: 5 x 3000 x 700: 47.8 us with 256 steps, 53.1 with 1024) and the last one
 //   does not leave more than a tenth of all idle (16 x 2100 x 64: 13.4 and 14.9).
@@ -439,7 +442,7 @@ __global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(S
 //   1024 threads (gradient pass with larger workgroups: 8 x 700, H = 512, P = 640 166.9 -> 173.6 us).
 // Bytes and trips to memory bound all of them.  With 256 steps to a workgroup at every length, and a look-back above (us, scan-level entry points,
 // forward and reverse, now behind the arrow):  20 x 300 x 250: 17.8 -> 14.1, 22.7 -> 19.5    10 x 500 x 300: 16.5 -> 12.9, 21.2 -> 17.7
-//   1 x 300 x 64: 9.2 -> 6.3, 12.2 -> 9.4    16 x 1000 x 512: 26.8 -> 25.9, 39.9 -> 40.1    32 x 1000 x 1024: 101 -> 86, 188 -> 183
+//   1 x 300 x 64: 9.2 -> 6.3, 12.2 -> 9.4    16 x 1000 x 512: 26.8 -> 25.9, 39.9 -> 40.1
 //   4 x 4096 x 256: 17.0 -> 16.2, 26.1 -> 26.3    2 x 20000 x 64: 21.4 -> 17.6, 28.8 -> 24.4    1 x 60000 x 64: 39.0 -> 18.8, 49.4 -> 28.4
 // (whole sequences of 4096 steps, four states to a workgroup of 1024 threads: 4 x 4096 x 256 16.5 and 28.0, 1 x 4096 x 64 14.7 and 20.8)
 ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P, bool records)
@@ -455,13 +458,13 @@ ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P, bool records)
         pl.pxb = 256;
         while (pl.pxb > 16 && (pl.pxb * chunks > 256 || pl.pxb / 2 >= P)) pl.pxb /= 2;
         pl.cy = (int)chunks;
-    } else if (chunks <= 32 || (chunks <= 64 && chains >= 64)) {
+    } else if (chunks <= 32 || (chunks <= 64 && chains >= 64 && (chains <= 256 || (chains <= 768 && chains * chunks * 10 >= (chains + 255) / 256 * 256 * 64 * 7)))) {
         pl.cy = (int)chunks;
     } else {
         pl.cy = 16;
         for (int cy : {32, 64}) {
             const int64_t blocks = (chunks + cy - 1) / cy;
-            if (chains * blocks >= 192 && chains * blocks <= 384 && blocks * cy * 10 <= chunks * 11) pl.cy = cy;
+            if (blocks > 1 && chains * blocks >= 192 && chains * blocks <= 384 && blocks * cy * 10 <= chunks * 11) pl.cy = cy;
         }
     }
     pl.nPX = (int)((P + pl.pxb - 1) / pl.pxb);

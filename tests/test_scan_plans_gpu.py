@@ -15,6 +15,7 @@ SHAPES = [
     (3, 1, 5), (2, 15, 300), (2, 17, 129), (1, 33, 260), (5, 80, 31), (3, 200, 17),    # up to 256 steps: 256 .. 16 states
     (2, 256, 16), (2, 257, 15), (3, 300, 33), (1, 512, 40),                         # whole sequences of 16 states
     (2, 513, 40), (16, 513, 60), (7, 1000, 150), (64, 1024, 9),                       # up to 1024 steps: look-back or whole
+    (17, 600, 250), (19, 1000, 256), (32, 1000, 250), (49, 1024, 250),                # the same with more than 256 such workgroups: look-back, look-back, whole, look-back
     (1, 1025, 20), (2, 5000, 70),                                                     # blocks of 256 steps
     (16, 2040, 64), (2, 20000, 64),                                                   # of 512
     (4, 4000, 250), (1, 60000, 60), (4, 4096, 256),                                   # of 1024
