@@ -24,7 +24,7 @@ inline bool misaligned(const void *p, size_t a) { return (reinterpret_cast<uintp
 // compiler made of a plain loop (adjoint), and now: 16 steps of 65536 trajectories 3.96 and 3.74 us, adjoint 6.16 and 5.25; 64 of 2048: 5.8
 // and 4.8, 12.3 and 6.6.  (Sixteen steps in flight: 3.8 and 5.5 us at the first; workgroups of 256: the same within 2 %, slower at few trajectories.)
 // ---------------------------------------------------------------------------------------------
-constexpr int LAMBDA_STEPS = 8, LAMBDA_THREADS = 64;
+constexpr int LAMBDA_STEPS = 8, LAMBDA_THREADS = 64;      // (and what is left of the steps in batches of four, two, one)
 __global__ void __launch_bounds__(LAMBDA_THREADS) lambda_return_kernel(const float *__restrict__ r, const float *__restrict__ c,
                                                                        const float *__restrict__ v, float gamma, float lam,
                                                                        long T, long N, float *__restrict__ ret)
@@ -56,8 +56,7 @@ __global__ void __launch_bounds__(LAMBDA_THREADS) lambda_return_kernel(const flo
         }
     };
     steps(std::integral_constant<int, LAMBDA_STEPS>{});
-    if constexpr (LAMBDA_STEPS > 8) steps(std::integral_constant<int, 8>{});
-    if constexpr (LAMBDA_STEPS > 4) steps(std::integral_constant<int, 4>{});
+    steps(std::integral_constant<int, 4>{});
     steps(std::integral_constant<int, 2>{});
     steps(std::integral_constant<int, 1>{});
 }
@@ -99,8 +98,7 @@ __global__ void __launch_bounds__(LAMBDA_THREADS) lambda_return_bwd_kernel(const
         }
     };
     steps(std::integral_constant<int, LAMBDA_STEPS>{});
-    if constexpr (LAMBDA_STEPS > 8) steps(std::integral_constant<int, 8>{});
-    if constexpr (LAMBDA_STEPS > 4) steps(std::integral_constant<int, 4>{});
+    steps(std::integral_constant<int, 4>{});
     steps(std::integral_constant<int, 2>{});
     steps(std::integral_constant<int, 1>{});
     const long o = (T - 1) * N;

@@ -30,6 +30,19 @@ struct Split4 { bf16x4 p[3]; };
 
 // four consecutive floats at an address that is only float-aligned (one 16-byte load: global loads need dword alignment)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+// Four consecutive values of a row from p, n of which exist (an address that is only float-aligned).
+__device__ __forceinline__ float4 load4(const float *p, int n)
+{
+    if (n >= 4) { const f32x4u v = *reinterpret_cast<const f32x4u *>(p); return make_float4(v.x, v.y, v.z, v.w); }
+    return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
+}
+__device__ __forceinline__ void store4(float *p, float4 v, int n)
+{
+    if (n >= 4) { const f32x4u w = {v.x, v.y, v.z, v.w}; *reinterpret_cast<f32x4u *>(p) = w; return; }
+    if (n > 0) p[0] = v.x;
+    if (n > 1) p[1] = v.y;
+    if (n > 2) p[2] = v.z;
+}
 
 // The four values from the sh-th on of a unit that was read sh values early: the rest zeros (sh <= 0: the unit; >= 4: zeros).
 // (selections one on top of the other, on lanes: nested ones become branches on lanes, and a loop that has such a branch anywhere is
@@ -306,7 +319,8 @@ constexpr int tn_consumers(int TB) { return TB == 64 ? 8 : 4; }
 constexpr int tn_rows(int TB) { return TB == 64 ? 64 : 128; }
 constexpr int tn_cols(int TB) { return TB == 128 ? 128 : 64; }
 constexpr int tn_bk(int TB) { return TB == 64 ? 64 : 32; }
-constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * NPL * tn_bk(TB) * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }     // stages, two scales
+// (stages, two scales)
+constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * NPL * tn_bk(TB) * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }
 
 template <int TB, int NPL, int EDGE>
 __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, int m0, int n0, int z, int kbeg, int kend, int tid)

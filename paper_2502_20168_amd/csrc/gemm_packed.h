@@ -476,11 +476,6 @@ struct StoreInputs {
     bool dropped[UNITS];
 
     static __device__ __forceinline__ int row_of(int tid, int batch, int i) { return tid / LANES + (batch * UNITS + i) * (PK_THREADS / LANES); }
-    static __device__ __forceinline__ float4 load4(const float *p, int n)          // n valid values from p
-    {
-        if (n >= 4) { const f32x4u v = *reinterpret_cast<const f32x4u *>(p); return make_float4(v.x, v.y, v.z, v.w); }
-        return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
-    }
     __device__ __forceinline__ void request(const PkDev &g, int tid, int batch, int m0, int n0)
     {
         const int col = n0 + 4 * (tid % LANES), n = g.N - col;
@@ -512,13 +507,6 @@ struct StoreInputs {
         }
         d = make_float4(0.f, 0.f, 0.f, 0.f);
         if (HAS_DIAG && n > 0 && (EPI != 5 || g.C2)) d = load4(g.diag + col, n);
-    }
-    static __device__ __forceinline__ void put4(float *p, float4 v, int n)
-    {
-        if (n >= 4) { f32x4u w = {v.x, v.y, v.z, v.w}; *reinterpret_cast<f32x4u *>(p) = w; return; }
-        if (n > 0) p[0] = v.x;
-        if (n > 1) p[1] = v.y;
-        if (n > 2) p[2] = v.z;
     }
     __device__ __forceinline__ void store(const PkDev &g, const float *tile, int tid, int batch, int m0, int n0)
     {
@@ -566,8 +554,8 @@ struct StoreInputs {
                 o = make_float4(fmaf(v.x, e2[i].x, e[i].x), fmaf(v.y, e2[i].y, e[i].y), fmaf(v.z, e2[i].z, e[i].z), fmaf(v.w, e2[i].w, e[i].w));
             }
             if (in) {
-                put4(g.C + row * g.ldc + col, o, n);
-                if (second) put4(g.C2 + row * g.ldc + col, o2, n);
+                store4(g.C + row * g.ldc + col, o, n);
+                if (second) store4(g.C2 + row * g.ldc + col, o2, n);
             }
             if constexpr (EPI == 6 && BN == 128) {
                 // the product that consumes C2 stages its rows under a scale each: the largest magnitude of every row within
@@ -598,11 +586,12 @@ struct StoreInputs {
 //   4. second pass from the registers: states, x_last; reverse: dAbar (a row per tile) and dx0.
 // The powers of Abar that the folds take are computed in double precision and rounded once.  A reset selects instead of multiplying by zero: what
 // one sequence holds cannot reach the next, infinities and NaN included.
-// A tile waits for tiles on other XCDs.  They have smaller workgroup ids (modes 6 and 7) and publish without waiting for anything, but they need not have been
-// started: every XCD starts its share of a launch on its own, and one can be full of tiles of another launch, on another stream, that wait for theirs behind tiles
-// of this one.  So no tile relies on it: after ROW_SCAN_POLLS polls it computes the aggregate that is missing itself, to the last bit as
-// its own tile would, publishes it and starts again (gemm_pk_kernel).  Nothing else on the way: as placement in chains of one XCD (mode 5) the passes of 18 layers
-// took up to 8 % longer (the rows are read by several XCDs, or the XCDs have unequal shares), with row tiles drawn from counters 4 %, with this 0.7 %.
+//   A tile waits for tiles on other XCDs.  They have smaller workgroup ids (modes 6 and 7) and publish without waiting for anything, but
+// they need not have been started: every XCD starts its share of a launch on its own, and one can be full of tiles of another launch, on
+// another stream, that wait for theirs behind tiles of this one.  So no tile relies on it: after ROW_SCAN_POLLS polls it computes the
+// aggregate that is missing itself, to the last bit as its own tile would, publishes it and starts again (gemm_pk_kernel).  On 18 layers
+// this takes the passes 0.7 % longer than tiles that rely on the order; row tiles drawn from counters up to 4 %, chains of one XCD
+// (mode 5) up to 8 %, where several XCDs read the same rows or get unequal shares.
 // Bound by its chain of dependent steps (the tile through LDS 0.3 us, either pass and the fold between them 0.4 to 0.5 each, a trip to
 // memory and back where tiles wait).  As a kernel of its own the scan paid its start, the way to memory and back, and the gap in front of it.  With scan
 // kernels and now: input projection of 16 x 64 tokens, H = P = 256 (32 rows): 5.8 + 4.8 us and 8.6; of 20 x 300, 500, 250 (64 rows): 23.1 + 14.1 and 30.6, C^H dy
@@ -611,7 +600,8 @@ struct StoreInputs {
 // 1000, 128: 259 -> 255).  Forward on two planes (64 rows; there the states' row maxima are recorded as well): 24 x 200, 1024, 512: 95.5 -> 90.4; 100 x 100, 512, 512:
 // 106.6 -> 90.2; 300 x 100: 264 -> 240, although products of many tiles alone are a little faster with 128 rows.
 // ---------------------------------------------------------------------------------------------
-constexpr int ROW_SCAN_CHUNKS = 8, ROW_SCAN_RUN = 8;          // runs of a tile; tiles that a thread folds at most
+constexpr int ROW_SCAN_CHUNKS = 8;                            // runs of a tile, threads that share out the tiles before it
+static_assert(ROW_SCAN_MAX_TILES <= ROW_SCAN_CHUNKS * 8, "a thread folds at most eight tiles");
 constexpr size_t row_scan_lds_bytes(int BN) { return (size_t)4 * ROW_SCAN_CHUNKS * (BN / 2) * 8; }
 
 // What is requested ahead: Abar, the flags, and for the thread's tokens x_{t-1} (reverse) and x0 where they start a sequence (both directions).
@@ -1225,8 +1215,9 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
 //   A wait counts the requests made behind the one it is for.  So that the compiler finds the same order in every round of the loop, the
 // first stage stands in front of it, the loop has a single way out, and there is no branch on lanes in it.
 // AHEAD: k steps of the weights in flight: four; two beside a reduction, whose sixteen wavefronts leave each 128 registers (short stages
-// of at most 64 columns: four there too).  No variant spills.  With four on short stages of 128 columns and the places of all eight steps of a stage kept, those beside a
-// reduction spilled up to 14: forward and gradient pass of 32 x 60 tokens, H = 100, P = 200: 55.0 -> 51.4 us; 16 x 64, 128, 256: 42.0 -> 39.8; 16 x 64, 256, 256: 47.2 -> 46.8.
+// of at most 64 columns: four there too).  No variant spills.  With four on short stages of 128 columns, and the places of all eight
+// steps of a stage kept, those beside a reduction spilled up to 14: forward and gradient pass of 32 x 60 tokens, H = 100, P = 200:
+// 55.0 -> 51.4 us; 16 x 64, 128, 256: 42.0 -> 39.8; 16 x 64, 256, 256: 47.2 -> 46.8.
 template <int BN, int NPL, int EPI, int KC, int AHEAD>
 __device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tid, bool ahead)
 {
@@ -1333,8 +1324,9 @@ __device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *sme
     v16f acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    // Fragment of a k step of the stage in LDS: row li, k = 16 ks + 8 hh ..  Its piece is 2 (kw + KW j) + hh, and 2 kw + hh < 2 KW, a power of two: step j's place is step
-    // 0's with bits of j flipped.  (Beside a reduction, where there are no registers to keep the places of eight steps in, they are flipped at every step.)
+    // Fragment of a k step of the stage in LDS: row li, k = 16 ks + 8 hh ..  Its piece is 2 (kw + KW j) + hh, and 2 kw + hh < 2 KW, a
+    // power of two: step j's place is step 0's with bits of j flipped.  (Beside a reduction, where there are no registers to keep the
+    // places of eight steps in, they are flipped at every step.)
     const int frag0 = place(li, 2 * kw + hh);
     int frag_at[KSW];
 #pragma unroll
@@ -1507,7 +1499,8 @@ constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, int epi, int kc)
 {
     const bool scans = (epi == 7 || epi == 8) && NPL == 2, row_scans = BM == 64 && (epi >= 7) && !scans;
     const size_t st = (size_t)PK_STAGES * NPL * BM * kc * 2 + (size_t)BM * 4;          // stages and scales
-    const size_t ep = scans ? scan_lds_bytes(BM) : row_scans ? (size_t)BM * BN * 4 + row_scan_lds_bytes(BN) : (size_t)BM * BN * 4 * (BM == 32 ? PK32_WAVES * 32 / BN : 1);      // the staged tile (or its parts)
+    const size_t tile = (size_t)BM * BN * 4 * (BM == 32 ? PK32_WAVES * 32 / BN : 1);           // the staged tile (or its parts)
+    const size_t ep = scans ? scan_lds_bytes(BM) : row_scans ? tile + row_scan_lds_bytes(BN) : tile;
     return ep > st ? ep : st;
 }
 

@@ -44,7 +44,8 @@ ssm_status ssm_scan_states_noalloc(const ssm_c64 *A_bar, ssm_c64 *v, const uint8
     // whether the plan of the shape has one or not: which shapes it takes does not follow the plan.
     const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t chains = L <= 256 ? 0 : (size_t)((P + 15) / 16 * Bt);
-    const size_t look_back = up(sizeof(ssm::WsHeader)) + up(chains * ssm::SCAN_TICKET_STRIDE * sizeof(uint32_t)) + up(chains * ((L + 255) / 256) * 16 * sizeof(ssm::ScanDesc));
+    const size_t tickets = chains * ssm::SCAN_TICKET_STRIDE * sizeof(uint32_t), descs = chains * ((L + 255) / 256) * 16 * sizeof(ssm::ScanDesc);
+    const size_t look_back = up(sizeof(ssm::WsHeader)) + up(tickets) + up(descs);
     if (lo.total > SSM_NOALLOC_SCRATCH_BYTES || look_back > SSM_NOALLOC_SCRATCH_BYTES) return SSM_ERR_SCRATCH_LIMIT;
     void *ptr = scratch_of_current_device();
     if (!ptr) return SSM_ERR_HIP;

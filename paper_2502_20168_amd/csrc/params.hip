@@ -435,19 +435,6 @@ int coldot_slabs(int64_t T, int planes)
 // a thread per state beside everything else it does.  Here, in every workgroup of a state, their double-precision
 // transcendentals were 2 to 3.4 us in front of sums of 1 to 3 us.
 // ---------------------------------------------------------------------------------------------
-// Four consecutive values of a row from p, n of which exist (an address that is only float-aligned).
-__device__ __forceinline__ float4 load4(const float *p, int n)
-{
-    if (n >= 4) { const f32x4u v = *reinterpret_cast<const f32x4u *>(p); return make_float4(v.x, v.y, v.z, v.w); }
-    return make_float4(n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, 0.f);
-}
-__device__ __forceinline__ void store4(float *p, float4 v, int n)
-{
-    if (n >= 4) { const f32x4u w = {v.x, v.y, v.z, v.w}; *reinterpret_cast<f32x4u *>(p) = w; return; }
-    if (n > 0) p[0] = v.x;
-    if (n > 1) p[1] = v.y;
-    if (n > 2) p[2] = v.z;
-}
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
 // s[r] = sum over the slabs i, i + step, ... < n of the four values at base + i stride + r pitch, r < R: in the order of the

@@ -339,7 +339,8 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g1.scan.lam = lam; g1.scan.is_first = is_first;
         g1.scan.x0 = reinterpret_cast<const float2 *>(x0); g1.scan.x_last = reinterpret_cast<float2 *>(x_last);
         g1.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g1.scan.err = &hdr->err;
-        g1.scan.L = (int)L; g1.scan.P = (int)P; g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : lo.row_scan; g1.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
+        g1.scan.L = (int)L; g1.scan.P = (int)P;
+        g1.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : lo.row_scan; g1.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
         if (two_planes) g1.scan.rowmax_out = rowpart;        // of the states, for the output projection
     }
     HIP_TRY(launch_product(g1, s));
@@ -463,7 +464,8 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
         g3.scan.dx0 = reinterpret_cast<float2 *>(dx0);
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
-        g3.scan.L = (int)L; g3.scan.P = (int)P; g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : lo.row_scan; g3.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
+        g3.scan.L = (int)L; g3.scan.P = (int)P;
+        g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : lo.row_scan; g3.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
         if (two_planes) { g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart; }
     }
     // (otherwise dC needs only dy and the saved states: it shares the launch)
@@ -506,7 +508,8 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     ea.B = reinterpret_cast<const float2 *>(B); ea.adj = pa.adj; ea.P = (int)P; ea.H = (int)H;
     ea.dBbar_part = dBpart; ea.nsplit_B = lo.dB.slabs;
     ea.dC_part = dCpart; ea.nsplit_C = lo.dC.slabs;
-    ea.dAbar_part = dApart; ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : lo.row_scan ? (Bt * L + lo.row_scan - 1) / lo.row_scan : (int64_t)Bt * lo.plan.nTB;
+    ea.dAbar_part = dApart;
+    ea.npart = fused ? Bt * L / gemm_scan_rows(T, L, P, true) : lo.row_scan ? (Bt * L + lo.row_scan - 1) / lo.row_scan : (int64_t)Bt * lo.plan.nTB;
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
     ea.dC = reinterpret_cast<float2 *>(dC); ea.dD = dD; ea.dlog_delta = dlog_delta;
@@ -637,7 +640,9 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     Layout fwd;
     st = make_layout(Bt, L, H, P, false, fwd);
     if (st != SSM_OK) return st;
-    in.epilogue = fused ? 7 : fwd.row_scan ? (lo.planes == 2 ? 9 : 7) : 0; in.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : fwd.row_scan; o.epilogue = du.epilogue = 1;
+    in.epilogue = fused ? 7 : fwd.row_scan ? (lo.planes == 2 ? 9 : 7) : 0;
+    in.scan.rows = fused ? gemm_scan_rows(T, L, P, false) : fwd.row_scan;
+    o.epilogue = du.epilogue = 1;
     dC.M = (int)H; dC.N = (int)(2 * P); dC.splits = lo.dC.slabs;
     dB.M = (int)(2 * P); dB.N = (int)H; dB.splits = lo.dB.slabs;
     const auto tile = [](PkTile t) { return t.rows * 1024 + t.cols; };

@@ -15,7 +15,7 @@ SHAPES = [
     (3, 1, 5), (2, 15, 300), (2, 17, 129), (1, 33, 260), (5, 80, 31), (3, 200, 17),    # up to 256 steps: 256 .. 16 states
     (2, 256, 16), (2, 257, 15), (3, 300, 33), (1, 512, 40),                         # whole sequences of 16 states
     (2, 513, 40), (16, 513, 60), (7, 1000, 150), (64, 1024, 9),                       # up to 1024 steps: look-back or whole
-    (17, 600, 250), (19, 1000, 256), (32, 1000, 250), (49, 1024, 250),                # the same with more than 256 such workgroups: look-back, look-back, whole, look-back
+    (17, 600, 250), (19, 1000, 256), (49, 1024, 250), (32, 1000, 250),                # more than 256 such workgroups: look-back, the last one whole
     (1, 1025, 20), (2, 5000, 70),                                                     # blocks of 256 steps
     (16, 2040, 64), (2, 20000, 64),                                                   # of 512
     (4, 4000, 250), (1, 60000, 60), (4, 4096, 256),                                   # of 1024
@@ -55,9 +55,10 @@ def test_scan_plans(shape, pr):
     assert_close(dx.cpu().numpy(), (1 - fl[:, 0])[:, None] * np.conj(Abar.astype(np.complex128)) * chi_ref[:, 0], TOL_GRAD, "dx0")
 
 
-@pytest.mark.parametrize("shape", [(14, 300, 512, 512), (9, 515, 520, 512), (5, 1500, 512, 512), (5, 1030, 512, 530)], ids=str)
+# (the forward scan runs in the input projection, up to 4096 steps; longer ones: a scan kernel of several workgroups along time either way)
+@pytest.mark.parametrize("shape", [(14, 300, 512, 512), (9, 515, 520, 512), (5, 1500, 512, 512), (5, 1030, 512, 530), (2, 4100, 512, 520), (1, 5003, 530, 512)], ids=str)
 def test_scans_that_record_magnitudes(shape):
-    """Two planes: the row maxima that the scan kernels record scale the products behind them."""
+    """Two planes: the row maxima that the scan kernels (and the forward scan in its product) record scale the products behind them."""
     Bt, L, H, P = shape
     p = ssm.ssm_plan_describe(Bt, L, H, P)
     assert p["planes"] == 2 and p["scans_in_projections"] == 0
