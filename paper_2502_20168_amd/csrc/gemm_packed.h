@@ -590,7 +590,7 @@ struct StoreInputs {
 // they need not have been started: every XCD starts its share of a launch on its own, and one can be full of tiles of another launch, on
 // another stream, that wait for theirs behind tiles of this one.  So no tile relies on it: after ROW_SCAN_POLLS polls it computes the
 // aggregate that is missing itself, to the last bit as its own tile would, publishes it and starts again (gemm_pk_kernel).  On 18 layers
-// this takes the passes 0.7 % longer than tiles that rely on the order; row tiles drawn from counters up to 4 %, chains of one XCD
+// the passes take 0.6 % longer than with tiles that rely on the order (2 % at most); with row tiles drawn from counters up to 4 %, chains of one XCD
 // (mode 5) up to 8 %, where several XCDs read the same rows or get unequal shares.
 // Bound by its chain of dependent steps (the tile through LDS 0.3 us, either pass and the fold between them 0.4 to 0.5 each, a trip to
 // memory and back where tiles wait).  As a kernel of its own the scan paid its start, the way to memory and back, and the gap in front of it.  With scan
@@ -1541,24 +1541,27 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
                 return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             } else return gemm_pk_tile<BM, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
         };
-        if constexpr (!scans_rows(NPL, EPI)) run(g, tm, tid, false);
-        else {
-            // Row tile m: this workgroup's, or one whose aggregate it misses.  (At most two rounds per tile of the sequence; the bound on them only keeps a mistake
-            // from hanging.)  Nothing of a round stays in registers for another one, the arguments included: that would take more than there are.
-            auto args = (const unsigned long long __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
-            for (int m = tm, rounds = 0;; ++rounds) {
-                int id = tid;
-                asm volatile("" : "+v"(id), "+s"(m), "+s"(args));
-                static_assert(sizeof(PkDev) % 8 == 0, "whole words, the first of the arguments");
-                union { unsigned long long w[sizeof(PkDev) / 8]; PkDev g; } own;
+        const int missing = __builtin_amdgcn_readfirstlane(run(g, tm, tid, false));
+        if constexpr (scans_rows(NPL, EPI)) {
+            if (__builtin_expect(missing >= 0, 0)) {
+                // The aggregate of row tile `missing`, then this tile again, until none is missing.  (At most two rounds per tile of the
+                // sequence; the bound on them only keeps a mistake from hanging.)  A copy of the code for itself: in a loop nothing may stay
+                // in registers from one round to the next, the arguments included, which every tile would pay for (16 layers: 0.2 %).
+                auto args = (const unsigned long long __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+                for (int m = missing, rounds = 0;; ++rounds) {
+                    __syncthreads();                         // LDS is free
+                    int id = tid;
+                    asm volatile("" : "+v"(id), "+s"(m), "+s"(args));
+                    static_assert(sizeof(PkDev) % 8 == 0, "whole words, the first of the arguments");
+                    union { unsigned long long w[sizeof(PkDev) / 8]; PkDev g; } own;
 #pragma unroll
-                for (size_t i = 0; i < sizeof(PkDev) / 8; ++i) own.w[i] = args[i];
-                in_global(own.g);
-                const int missing = __builtin_amdgcn_readfirstlane(run(own.g, m, id, m != tm));
-                if (missing < 0 && m == tm) break;
-                if (rounds > 4 * ROW_SCAN_MAX_TILES) { atomicOr(own.g.scan.err, 1u); break; }
-                m = missing < 0 ? tm : missing;
-                __syncthreads();                             // LDS is free
+                    for (size_t i = 0; i < sizeof(PkDev) / 8; ++i) own.w[i] = args[i];
+                    in_global(own.g);
+                    const int next = __builtin_amdgcn_readfirstlane(run(own.g, m, id, m != tm));
+                    if (next < 0 && m == tm) break;
+                    if (rounds > 4 * ROW_SCAN_MAX_TILES) { atomicOr(own.g.scan.err, 1u); break; }
+                    m = next < 0 ? tm : next;
+                }
             }
         }
     } else if constexpr (TNB > 0) {
