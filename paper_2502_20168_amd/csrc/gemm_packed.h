@@ -413,7 +413,7 @@ __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds
             const bool r = (rmask >> e) & 1u;
             const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
             xs = cfma(le, xs, val[i]);
-            if (active) (dst + (long)e * a.P)[c] = xs;
+            if (active) store_through(dst + (long)e * a.P + c, xs);
             const float me = fmaxf(fabsf(xs.x), fabsf(xs.y));
             rm[e % SCAN_CHUNK] = active ? __float_as_uint(me) : 0u;
             amax = fmaxf(amax, me);
@@ -554,8 +554,15 @@ struct StoreInputs {
                 o = make_float4(fmaf(v.x, e2[i].x, e[i].x), fmaf(v.y, e2[i].y, e[i].y), fmaf(v.z, e2[i].z, e[i].z), fmaf(v.w, e2[i].w, e[i].w));
             }
             if (in) {
-                store4(g.C + row * g.ldc + col, o, n);
-                if (second) store4(g.C2 + row * g.ldc + col, o2, n);
+                if constexpr (BM == 128) {
+                    // (launches of several rounds: of little use, and 1024 x 16 tokens, 512, 512, forward, take 0.5 % longer with it)
+                    store4(g.C + row * g.ldc + col, o, n);
+                    if (second) store4(g.C2 + row * g.ldc + col, o2, n);
+                } else {
+                    const int at = r * (int)g.ldc + c;
+                    store4_through(g.C + m0 * g.ldc + n0, at, o, n);
+                    if (second) store4_through(g.C2 + m0 * g.ldc + n0, at, o2, n);
+                }
             }
             if constexpr (EPI == 6 && BN == 128) {
                 // the product that consumes C2 stages its rows under a scale each: the largest magnitude of every row within
@@ -880,11 +887,11 @@ __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, 
         if (active) {
             if (m0 + ROWS <= g.M) {
 #pragma unroll
-                for (int i = 0; i < CH; ++i) dst[row_of(i) * a.P] = val[i];
+                for (int i = 0; i < CH; ++i) store_through(dst + row_of(i) * a.P, val[i]);
             } else {
 #pragma unroll
                 for (int i = 0; i < CH; ++i)
-                    if (m0 + row_of(i) < g.M) dst[row_of(i) * a.P] = val[i];
+                    if (m0 + row_of(i) < g.M) store_through(dst + row_of(i) * a.P, val[i]);
             }
             if constexpr (MAXIMA) static_assert(ROWS == 64 && BN == 128 && !REV, "rows8_wave_max");
             const Bits edge = REV ? k.start : k.end;
