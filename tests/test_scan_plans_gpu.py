@@ -20,6 +20,7 @@ SHAPES = [
     (16, 2040, 64), (2, 20000, 64),                                                   # of 512
     (4, 4000, 250), (1, 60000, 60), (4, 4096, 256),                                   # of 1024
     (12, 2050, 250), (20, 1300, 350),                                                 # of 256 again: many of them
+    (3, 3000, 935), (40, 230, 930),                                                   # more than 64 MiB in rows of no whole lines: stores left in the L2
 ]
 
 
