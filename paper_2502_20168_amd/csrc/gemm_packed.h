@@ -52,6 +52,7 @@ struct PkDev {
     int M, N, K, nkt;                       // nkt: K tiles of 64
     int ntm, ntn, nx, mode, slot0;          // tiles; slots per XCD, placement mode, first slot
     int sc_nt, sc_cpu, sc_ncg, sc_units, sc_rev;
+    FastDiv by_ntn, by_unit, by_ncg, by_cpu;     // ntn, sc_nt * sc_cpu, sc_ncg, sc_cpu
     ScanEpilogue scan;
     const unsigned *rows; int row_parts; long row_stride;    // largest magnitudes of the rows of A (two planes), see AbsMax
     unsigned *c2_rowmax;                    // epilogue 6: [ceil(N/128)][M] or null
@@ -143,7 +144,7 @@ __device__ __forceinline__ ScanSaved<RC> scan_request_saved(const ScanEpilogue &
     const int p = n0 / 2 + c;
     const bool active = p < a.P;
     const int row0 = m0 + q * RC;
-    const int b = row0 / a.L, t0 = row0 % a.L;
+    const int b = (int)a.by_L(row0), t0 = row0 - b * a.L;
     // (row addresses are uniform: one lane offset for all of them)
     const float2 *xprev = a.xsaved + ((long)row0 - 1) * a.P + n0 / 2;                // x_{t0-1}; valid for e >= 1 or t0 > 0
     ScanSaved<RC> s;
@@ -177,18 +178,17 @@ template <int ROWS> struct ScanFlags {                       // bit r of first[h
         return (unsigned)(word(w, r / 64) >> (r & 63)) & ((1u << n) - 1u);
     }
 };
+// (Without flags the bytes come from the packed weights and are not used.  With the requests in a branch the compiler moves the comparison of
+// the bytes into it as well, and the workgroup waits for them before it requests anything else.)
 template <int ROWS, bool REV>
-__device__ __forceinline__ ScanFlagBytes<ROWS> scan_request_flags(const ScanEpilogue &a, int l, int m0, int M)
+__device__ __forceinline__ ScanFlagBytes<ROWS> scan_request_flags(const PkDev &g, int l, int m0)
 {
     ScanFlagBytes<ROWS> v;
+    const uint8_t *f = g.scan.is_first ? g.scan.is_first + m0 : reinterpret_cast<const uint8_t *>(g.frag);
     v.next = 0;
 #pragma unroll
-    for (int h = 0; h < ROWS / 64; ++h) v.own[h] = 0;
-    if (a.is_first) {
-#pragma unroll
-        for (int h = 0; h < ROWS / 64; ++h) v.own[h] = a.is_first[m0 + 64 * h + l];
-        if (REV) v.next = a.is_first[min(m0 + ROWS, M - 1)];
-    }
+    for (int h = 0; h < ROWS / 64; ++h) v.own[h] = f[64 * h + l];
+    if (REV) v.next = f[min(ROWS, g.M - 1 - m0)];
     return v;
 }
 // first: is_first.  drop: the state that flows into the step is dropped -- forward: the step's own flag; reverse: the flag
@@ -199,7 +199,7 @@ __device__ __forceinline__ ScanFlags<ROWS> scan_flags(const ScanEpilogue &a, con
     constexpr int H = ROWS / 64;
     ScanFlags<ROWS> f;
 #pragma unroll
-    for (int h = 0; h < H; ++h) f.first[h] = f.drop[h] = __ballot(v.own[h] != 0);
+    for (int h = 0; h < H; ++h) f.first[h] = f.drop[h] = a.is_first ? __ballot(v.own[h] != 0) : 0ull;
     if (REV) {
 #pragma unroll
         for (int h = 0; h < H; ++h) f.drop[h] = (f.first[h] >> 1) | (h + 1 < H ? f.first[h + 1 < H ? h + 1 : h] << 63 : 0ull);
@@ -207,7 +207,7 @@ __device__ __forceinline__ ScanFlags<ROWS> scan_flags(const ScanEpilogue &a, con
 #pragma unroll
             for (int h = 0; h < H; ++h)
                 for (int r = a.L - 1; r < 64; r += a.L) f.drop[h] |= 1ull << r;          // (L divides 64)
-        } else if ((m0 + ROWS) % a.L == 0 || __builtin_amdgcn_readfirstlane(v.next) != 0) f.drop[H - 1] |= 1ull << 63;
+        } else if ((int)a.by_L(m0 + ROWS) * a.L == m0 + ROWS || (a.is_first && __builtin_amdgcn_readfirstlane(v.next) != 0)) f.drop[H - 1] |= 1ull << 63;
     }
     return f;
 }
@@ -227,7 +227,7 @@ __device__ __forceinline__ unsigned wave_max(unsigned v) { return lane_xor_max<3
 // dAbar += [not is_first_t] conj(x_{t-1}) chi_t per tile and writes dx0.
 template <int ROWS, bool REV>
 __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds &lds, int q, int c, int m0, int n0, int tile,
-                                                   ScanSaved<ROWS / SCAN_WAVES> &saved, const ScanFlags<ROWS> &flags)
+                                                   ScanSaved<ROWS / SCAN_WAVES> &saved, const ScanFlags<ROWS> &flags, float2 lam)
 {
     constexpr int RC = ROWS / SCAN_WAVES, H = ROWS / SCAN_UNIT, NC = RC / SCAN_CHUNK, WH = SCAN_WAVES / H, UC = SCAN_UNIT / SCAN_CHUNK;
     static_assert(SCAN_CHUNK == 8 && UC == 8 && (H == 1 || H == 2), "the powers of Abar below");
@@ -241,8 +241,8 @@ __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds
     // sequence starts at a chunk boundary inside the tile and its incoming state is x0 (forward) or zero (reverse).
     const bool whole_seqs = a.L < ROWS;
     const int row0 = m0 + q * RC;                            // token index of this thread's first step
-    const int b = row0 / a.L, t0 = row0 - b * a.L;           // its sequence and its lowest time index
-    const int tmL = whole_seqs ? 0 : t0 / ROWS, nt = whole_seqs ? 1 : a.L / ROWS;
+    const int b = (int)a.by_L(row0), t0 = row0 - b * a.L;    // its sequence and its lowest time index
+    const int tmL = whole_seqs ? 0 : t0 / ROWS, nt = whole_seqs ? 1 : a.L / ROWS;      // (ROWS: a power of two)
     const int tn = n0 / PK_BN;
     const int npred = H * (REV ? nt - 1 - tmL : tmL);        // units of the chain before the tile in scan order
     const unsigned fmask = flags.bits(flags.first, q * RC, RC), rmask = flags.bits(flags.drop, q * RC, RC);
@@ -250,7 +250,6 @@ __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds
     auto chunk_resets = [&](int h, int j) { return flags.bits(flags.drop, REV ? ROWS - SCAN_UNIT * h - 8 * (j + 1) : SCAN_UNIT * h + 8 * j, 8) != 0; };
     auto unit_resets = [&](int h) { return flags.word(flags.drop, REV ? H - 1 - h : h) != 0; };
 
-    float2 lam = active ? a.lam[p] : make_float2(0.f, 0.f);
     if (REV) lam.y = -lam.y;
     float2 X = make_float2(0.f, 0.f);                        // state that flows into the sequence
     if (!REV && a.x0 && active) X = a.x0[(long)b * a.P + p];
@@ -627,17 +626,21 @@ __device__ __forceinline__ unsigned long long reversed(unsigned long long v) { r
 
 // row of the tile that a lane looks at; 32 rows: lane 32 and those above it at the one behind the tile
 template <int ROWS> __device__ __forceinline__ int row_scan_lane(int tid) { return ROWS == 32 ? min(tid & 63, ROWS) : tid & 63; }
-template <int ROWS, int BN>
+template <int ROWS, int BN, bool TIGHT>
 __device__ __forceinline__ RowScanStart row_scan_start(const PkDev &g, int tid, int m0, int n0)
 {
     const ScanEpilogue &a = g.scan;
     RowScanStart s;
     s.lam = a.lam[min(n0 / 2 + tid % (BN / 2), a.P - 1)];
-    s.flag = s.next = 0;
-    if (a.is_first) {
-        s.flag = a.is_first[min(m0 + row_scan_lane<ROWS>(tid), g.M - 1)];
-        if (ROWS == 64) s.next = a.is_first[min(m0 + ROWS, g.M - 1)];
+    // (requested without a branch: see scan_request_flags.  TIGHT: beside a reduction 128 columns leave no registers to do without one)
+    if constexpr (TIGHT) {
+        s.flag = s.next = 0;
+        if (a.is_first) s.flag = a.is_first[min(m0 + row_scan_lane<ROWS>(tid), g.M - 1)];
+        return s;
     }
+    const uint8_t *f = a.is_first ? a.is_first + m0 : reinterpret_cast<const uint8_t *>(g.frag);
+    s.flag = f[min(row_scan_lane<ROWS>(tid), g.M - 1 - m0)];
+    s.next = ROWS == 64 ? f[min(ROWS, g.M - 1 - m0)] : 0u;
     return s;
 }
 // the rows at which a sequence starts and ends (whole wavefronts; the last token ends one, so that in reverse nothing comes in from rows past it)
@@ -645,18 +648,18 @@ template <int ROWS>
 __device__ __forceinline__ RowScanMasks<ROWS> row_scan_ends(const PkDev &g, int tid, int m0)
 {
     using Bits = typename RowScanMasks<ROWS>::Bits;
-    const unsigned row = (unsigned)(m0 + row_scan_lane<ROWS>(tid)), L = (unsigned)g.scan.L, b = row / L;
+    const unsigned row = (unsigned)(m0 + row_scan_lane<ROWS>(tid)), L = (unsigned)g.scan.L, b = g.scan.by_L(row);
     return {0, (Bits)__ballot(row == b * L), (Bits)__ballot(row + 1 == (b + 1) * L), 0, __builtin_amdgcn_readfirstlane((int)b)};
 }
 // drop: nothing flows into the row -- forward: a flag, or the start of a sequence; reverse: a flag of the token behind it, or a sequence end
 template <int ROWS, bool REV>
-__device__ __forceinline__ void row_scan_flags(RowScanMasks<ROWS> &k, const RowScanStart &s)
+__device__ __forceinline__ void row_scan_flags(RowScanMasks<ROWS> &k, const RowScanStart &s, bool flags)
 {
     using Bits = typename RowScanMasks<ROWS>::Bits;
-    const unsigned long long f = __ballot(s.flag != 0);
+    const unsigned long long f = flags ? __ballot(s.flag != 0) : 0ull;
     k.first = (Bits)f;
     unsigned long long behind = f >> 1;
-    if (ROWS == 64) behind |= (unsigned long long)(__builtin_amdgcn_readfirstlane(s.next) != 0) << 63;
+    if (ROWS == 64) behind |= (unsigned long long)(flags && __builtin_amdgcn_readfirstlane(s.next) != 0) << 63;
     k.drop = REV ? (Bits)behind | k.end : k.first | k.start;
 }
 // Powers of Abar (its conjugate in reverse) over a run of tokens, the runs before the thread's, and a tile: in double precision, rounded once.
@@ -969,14 +972,15 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     ScanSaved<RC> saved;
     ScanFlagBytes<FR> flag_bytes;
     ScanFlags<FR> flags;
+    float2 lam;                                              // Abar of the lane's state
     StoreInputs<BM, PK_BN, EPI> in;
-    if constexpr (SCANS) flag_bytes = scan_request_flags<FR, EPI == 8>(g.scan, l, m0, g.M);
+    if constexpr (SCANS) flag_bytes = scan_request_flags<FR, EPI == 8>(g, l, m0);
     RowScanStart row_scan;
     RowScanMasks<64> row_masks;
     RowScanSaved<64> row_saved;
     static_assert(!ROW_SCANS || BM == 64, "rows of the masks");
     if constexpr (ROW_SCANS) {
-        row_scan = row_scan_start<64, PK_BN>(g, tid, m0, n0);
+        row_scan = row_scan_start<64, PK_BN, false>(g, tid, m0, n0);
         row_masks = row_scan_ends<64>(g, tid, m0);
     }
 
@@ -1014,12 +1018,14 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
         // hands log2 of the scale to the consumers (which read it behind the K loop).
         unsigned rw[NV];
         if constexpr (NPL == 2) {
+            // (the words of all rows together; a loop over further ones only where there are some)
+            const auto words = [&](int j, auto take) {
+                const unsigned *w = g.rows + m0 + (long)min(j, g.row_parts - 1) * g.row_stride;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const unsigned *w = g.rows + min(m0 + r0 + i * RSTEP, g.M - 1);
-                rw[i] = w[(long)min(kq / 4, g.row_parts - 1) * g.row_stride];
-                for (int j = kq / 4 + 16; j < g.row_parts; j += 16) rw[i] = max(rw[i], w[(long)j * g.row_stride]);
-            }
+                for (int i = 0; i < NV; ++i) take(i, w[min(r0 + i * RSTEP, g.M - 1 - m0)]);
+            };
+            words(kq / 4, [&](int i, unsigned v) { rw[i] = v; });
+            for (int j = 16; j < g.row_parts; j += 16) words(j + kq / 4, [&](int i, unsigned v) { rw[i] = max(rw[i], v); });
         }
         const bool narrow = units.narrow;
 #pragma unroll
@@ -1078,6 +1084,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
         for (int j = 0; j + 1 < PF; ++j)
             if (kt + j + 1 < nk) step(kt, j);
         __syncthreads();
+        if constexpr (SCANS) lam = g.scan.lam[min(n0 / 2 + l, g.scan.P - 1)];
         if constexpr (SCANS && EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
         if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, EPI == 8>(g, row_masks, tid, m0, n0);
         else if constexpr (!SCANS) in.request(g, tid, 0, m0, n0);
@@ -1178,6 +1185,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][r] = __builtin_ldexpf(acc[i][r], -(rowexp[row_of(i, r)] + eb));
         }
+        if constexpr (SCANS) lam = g.scan.lam[min(n0 / 2 + l, g.scan.P - 1)];
         // (at 128 rows the accumulators leave no registers for the inputs before they are staged)
         if constexpr (SCANS && EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
         if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, EPI == 8>(g, row_masks, tid, m0, n0);
@@ -1193,9 +1201,9 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     }
 
     // (producers and consumers together: one copy of the code)
-    if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags);
+    if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags, lam);
     else if constexpr (ROW_SCANS) {
-        row_scan_flags<64, EPI == 8>(row_masks, row_scan);
+        row_scan_flags<64, EPI == 8>(row_masks, row_scan, g.scan.is_first != nullptr);
         const RowScanPowers power = row_scan_powers<64, PK_BN, EPI == 8>(row_scan.lam, tid);
         return row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid,
                                                                m0, n0, row_scan.lam, power, row_masks, row_saved, ahead);
@@ -1246,9 +1254,9 @@ __device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *sme
     RowScanSaved<BM> saved;
     RowScanPowers power;
     // (beside a reduction, whose wavefronts have 128 registers, the states before the last stage)
-    constexpr bool EARLY = AHEAD == 4;
+    constexpr bool EARLY = AHEAD == 4, TIGHT = !EARLY && BN == 128;
     if constexpr (SCANS) {
-        scan = row_scan_start<BM, BN>(g, tid, m0, n0);
+        scan = row_scan_start<BM, BN, TIGHT>(g, tid, m0, n0);
         masks = row_scan_ends<BM>(g, tid, m0);
         if constexpr (EARLY) saved = row_scan_request<BM, BN, EPI == 8>(g, masks, tid, m0, n0);
     }
@@ -1409,7 +1417,7 @@ __device__ __forceinline__ int gemm_pk32_tile(const PkDev &g, unsigned char *sme
     StoreInputs<BM, BN, EPI> in;
     auto request = [&] {
         if constexpr (SCANS) {
-            row_scan_flags<BM, EPI == 8>(masks, scan);
+            row_scan_flags<BM, EPI == 8>(masks, scan, TIGHT || g.scan.is_first != nullptr);
             if constexpr (EARLY) power = row_scan_powers<BM, BN, EPI == 8>(scan.lam, tid);
             else saved = row_scan_request<BM, BN, EPI == 8>(g, masks, tid, m0, n0);
         } else in.request(g, tid, 0, m0, n0);
@@ -1489,14 +1497,13 @@ __device__ __forceinline__ int pk_place(const PkDev &g, int x, int q)
     if (g.mode == 0) return x * g.nx + q;
     if (g.mode == 6 || g.mode == 7) {
         const int n = 8 * q + x;
-        const int r = g.mode == 6 ? n / g.ntn : 8 * (q / g.ntn) + x, tn = g.mode == 6 ? n % g.ntn : q % g.ntn;       // row tile in scan order
+        const int m = g.mode == 6 ? n : q, d = (int)g.by_ntn(m), tn = m - d * g.ntn, r = g.mode == 6 ? d : 8 * d + x;       // row tile in scan order
         return r < g.ntm ? (g.sc_rev ? g.ntm - 1 - r : r) * g.ntn + tn : g.ntm * g.ntn;
     }
     const int per_unit = g.sc_nt * g.sc_cpu;
-    const int uid = x + 8 * (q / per_unit), r = q % per_unit;
-    const int b = uid / g.sc_ncg, cg = uid % g.sc_ncg;
-    const int tn = cg * g.sc_cpu + r % g.sc_cpu;
-    const int tslot = r / g.sc_cpu;                 // time-ordered slot; the reverse scan starts at the sequence end
+    const int u = (int)g.by_unit(q), uid = x + 8 * u, r = q - u * per_unit;
+    const int b = (int)g.by_ncg(uid), cg = uid - b * g.sc_ncg;
+    const int tslot = (int)g.by_cpu(r), tn = cg * g.sc_cpu + r - tslot * g.sc_cpu;      // time-ordered slot; the reverse scan starts at the sequence end
     const int tmL = g.sc_rev ? g.sc_nt - 1 - tslot : tslot;
     return (uid < g.sc_units && tn < g.ntn) ? (b * g.sc_nt + tmL) * g.ntn + tn : g.ntm * g.ntn;
 }
@@ -1538,9 +1545,18 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int x = blockIdx.x % 8, q = blockIdx.x / 8, tid = threadIdx.x;
     if (TNB == 0 || (q >= g.slot0 && q < g.slot0 + g.nx)) {
+        // (what the way to the first loads needs is requested together: left to where they are used, the arguments come in four or five trips)
+        // (a scan beside a reduction has no registers to keep them in)
+        if constexpr (EPI < 7 || TNB == 0)
+            asm volatile("" ::"s"(g.A), "s"(g.lda), "s"(g.frag), "s"(g.bexp), "s"(g.rows), "s"(g.row_parts), "s"(g.row_stride), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.nkt),
+                         "s"(g.ntm), "s"(g.ntn), "s"(g.nx), "s"(g.mode), "s"(g.slot0), "s"(g.by_ntn.mul), "s"(g.by_ntn.shift));
+        if constexpr (EPI >= 7 && TNB == 0)
+            asm volatile("" ::"s"(g.scan.is_first), "s"(g.scan.lam), "s"(g.scan.L), "s"(g.scan.P), "s"(g.scan.by_L.mul), "s"(g.scan.by_L.shift), "s"(g.sc_rev), "s"(g.sc_nt),
+                         "s"(g.sc_cpu), "s"(g.sc_ncg), "s"(g.sc_units), "s"(g.by_unit.mul), "s"(g.by_unit.shift), "s"(g.by_ncg.mul), "s"(g.by_ncg.shift),
+                         "s"(g.by_cpu.mul), "s"(g.by_cpu.shift));
         const int tile = pk_place(g, x, q - g.slot0);
         if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
-        const int tm = tile / g.ntn, tn = tile - tm * g.ntn;
+        const int tm = (int)g.by_ntn(tile), tn = tile - tm * g.ntn;
         auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
             if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             else if constexpr (BM == 32) {
@@ -1588,7 +1604,9 @@ inline PkDev make_pk_dev(const GemmArgs &a)
     g.ntm = (a.M + BM - 1) / BM; g.ntn = (a.N + BN - 1) / BN;
     const long ntiles = (long)g.ntm * g.ntn;
     g.nx = (int)((ntiles + 7) / 8); g.mode = 0; g.slot0 = 0;
+    g.by_ntn = FastDiv::by(g.ntn);
     g.scan = a.scan;
+    if (a.scan.L > 0) g.scan.by_L = FastDiv::by(a.scan.L);
     g.rows = a.amaxA.rows; g.row_parts = a.amaxA.row_parts; g.row_stride = a.amaxA.row_stride;
     g.c2_rowmax = a.c2_rowmax;
     if (a.epilogue == 9 || (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8))) {
@@ -1608,6 +1626,7 @@ inline PkDev make_pk_dev(const GemmArgs &a)
         g.sc_units = nseq * ncg;
         g.mode = 5;
         g.nx = ((g.sc_units + 7) / 8) * g.sc_nt * g.sc_cpu;
+        g.by_unit = FastDiv::by(g.sc_nt * g.sc_cpu); g.by_ncg = FastDiv::by(g.sc_ncg); g.by_cpu = FastDiv::by(g.sc_cpu);
     }
     return g;
 }

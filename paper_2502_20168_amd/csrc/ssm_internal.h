@@ -36,6 +36,19 @@ struct AbsMax {
     const unsigned *rows; int row_parts; long row_stride;
 };
 
+// Division of integers below 2^31 by a number that the host knows: floor(n / d) = n mul >> shift with mul = ceil(2^(31 + l) / d), 2^l >= d.
+// (Three scalar instructions; the compiler's own division by an argument is over twenty, one behind the other, and placing a tile takes five.)
+struct FastDiv {
+    unsigned mul, shift;
+    static FastDiv by(unsigned d)
+    {
+        unsigned l = 0;
+        while ((1ull << l) < d) ++l;
+        return {(unsigned)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
+    }
+    __host__ __device__ __forceinline__ unsigned operator()(unsigned n) const { return (unsigned)(((unsigned long long)n * mul) >> shift); }
+};
+
 // Epilogue 7 of a product with packed weights: the resettable scan (Eq. 4 with the elements of Eq. 9 and the
 // operator of Eq. 10) over the rows of the output tile itself, so that the input projection stores the states x
 // directly and Bbar u never goes to memory.  Rows are tokens (Bt sequences of L steps), columns (re, im) pairs of P
@@ -57,6 +70,7 @@ struct ScanEpilogue {
     unsigned *xmax_out;           // [ABSMAX_SLOTS] or null (reverse, with amax_out): atomic maximum of the magnitudes of xsaved
     unsigned *rowmax_out;         // [ceil(N/128), M] or null: per column tile and row, the largest magnitude stored to C
     int L, P;
+    FastDiv by_L;                 // set by the launch
     int rows;                     // tokens per tile: gemm_scan_rows, three planes: gemm_row_scan_rows
     unsigned spin_limit;
 };
