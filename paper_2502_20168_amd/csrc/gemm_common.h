@@ -15,7 +15,8 @@ struct GemmDev {
     int ntm, ntn;
     // placement of the (tile, split) work items on the 8 XCDs: slots per XCD, mapping mode and its
     // parameter, first slot of this problem in its launch
-    int splits, nx, mode, mpar, slot0;
+    int splits, nx, mode, par, slot0;
+    FastDiv by_ntn, by_par;
     AbsMax amaxA, amaxB;    // two-plane fp16 staging only
 };
 

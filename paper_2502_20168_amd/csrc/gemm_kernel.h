@@ -535,10 +535,11 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 // instead of once per tile band.
 __device__ __forceinline__ void tn_place(const GemmDev &g, int x, int q, int &z, int &tile)
 {
-    if (g.mode == 0) { z = 0; tile = x * g.nx + q; }
-    else if (g.mode == 1) { z = x + 8 * (q % g.mpar); tile = q / g.mpar; }        // splits = 8 * mpar
-    else if (g.mode == 2) { z = x % g.splits; tile = (x / g.splits) * g.nx + q; } // 8 = splits * mpar: bands of nx tiles
-    else { const int item = x * g.nx + q; z = item / (g.ntm * g.ntn); tile = item % (g.ntm * g.ntn); }
+    if (g.mode == 0) { z = 0; tile = x * g.nx + q; return; }
+    const int n = g.mode == 1 ? q : g.mode == 2 ? x : x * g.nx + q, d = (int)g.by_par(n), rest = n - d * g.par;
+    if (g.mode == 1) { z = x + 8 * rest; tile = d; }                              // splits = 8 * par
+    else if (g.mode == 2) { z = rest; tile = d * g.nx + q; }                      // 8 = splits * bands of nx tiles, par = splits
+    else { z = d; tile = rest; }                                                  // par = tiles
 }
 
 template <int TB, int NPL>
@@ -548,7 +549,7 @@ __device__ __forceinline__ void gemm_tn_problem(const GemmDev &g, unsigned char 
     tn_place(g, x, q, z, tile);
     if (q >= g.nx || z >= g.splits || tile >= g.ntm * g.ntn) return;
     constexpr int TM = tn_rows(TB), TN = tn_cols(TB);
-    const int m0 = (tile / g.ntn) * TM, n0 = (tile % g.ntn) * TN;
+    const int tm = (int)g.by_ntn(tile), m0 = tm * TM, n0 = (tile - tm * g.ntn) * TN;
     const int kbeg = z * g.kper, kend = min(g.K, kbeg + g.kper);
     __bf16 *stages = reinterpret_cast<__bf16 *>(smem);
     if (kbeg >= kend) {
@@ -582,10 +583,11 @@ inline GemmDev make_tn_dev(const GemmArgs &a)
     g.ntn = (a.N + tn_cols(TB) - 1) / tn_cols(TB);
     const long ntiles = (long)g.ntm * g.ntn;
     g.splits = splits;
-    if (splits == 1) { g.mode = 0; g.mpar = 0; g.nx = (int)((ntiles + 7) / 8); }
-    else if (splits % 8 == 0) { g.mode = 1; g.mpar = splits / 8; g.nx = (int)(ntiles * g.mpar); }
-    else if (8 % splits == 0) { g.mode = 2; g.mpar = 8 / splits; g.nx = (int)((ntiles + g.mpar - 1) / g.mpar); }
-    else { g.mode = 3; g.mpar = 0; g.nx = (int)((ntiles * splits + 7) / 8); }
+    if (splits == 1) { g.mode = 0; g.par = 1; g.nx = (int)((ntiles + 7) / 8); }
+    else if (splits % 8 == 0) { g.mode = 1; g.par = splits / 8; g.nx = (int)(ntiles * g.par); }
+    else if (8 % splits == 0) { g.mode = 2; g.par = splits; g.nx = (int)((ntiles * splits + 7) / 8); }
+    else { g.mode = 3; g.par = (int)ntiles; g.nx = (int)((ntiles * splits + 7) / 8); }
+    g.by_ntn = FastDiv::by(g.ntn); g.by_par = FastDiv::by(g.par);
     g.amaxA = a.amaxA; g.amaxB = a.amaxB;
     return g;
 }

@@ -1539,6 +1539,11 @@ __device__ __forceinline__ void in_global(PkDev &g)
     in_global(a.dx0); in_global(a.desc); in_global(a.err); in_global(a.rowmax_out);
 }
 
+__device__ __forceinline__ void in_global(GemmDev &g)
+{
+    in_global(g.A); in_global(g.B); in_global(g.C); in_global(g.amaxA.slots); in_global(g.amaxB.slots);
+}
+
 template <int BM, int BN, int NPL, int EPI, int TNB, int WPE>
 __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
 {
@@ -1588,9 +1593,16 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
             }
         }
     } else if constexpr (TNB > 0) {
-        if (q >= t0.slot0 && q < t0.slot0 + t0.nx) gemm_tn_problem<TNB, NPL>(t0, smem_raw, x, q - t0.slot0, tid);
-        // (a branch of its own: choosing between the two argument structs at run time would put them on the stack)
-        else gemm_tn_problem<TNB, NPL>(t1, smem_raw, x, q - t1.slot0, tid);
+        // (one copy of the code for both, whose arguments are read as words: with a copy each, whose loops do not fit the instruction cache together,
+        // and choosing between the two structs would put them on the stack)
+        const bool second = q < t0.slot0 || q >= t0.slot0 + t0.nx;
+        static_assert(sizeof(PkDev) % 8 == 0 && sizeof(GemmDev) % 8 == 0, "whole words, one behind the other");
+        auto args = (const unsigned long long __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() + (sizeof(PkDev) + (second ? sizeof(GemmDev) : 0)) / 8;
+        union { unsigned long long w[sizeof(GemmDev) / 8]; GemmDev t; } own;
+#pragma unroll
+        for (size_t i = 0; i < sizeof(GemmDev) / 8; ++i) own.w[i] = args[i];
+        in_global(own.t);
+        gemm_tn_problem<TNB, NPL>(own.t, smem_raw, x, q - own.t.slot0, tid);
     }
 }
 
