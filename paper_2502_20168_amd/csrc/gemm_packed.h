@@ -1559,7 +1559,8 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
             asm volatile("" ::"s"(g.scan.is_first), "s"(g.scan.lam), "s"(g.scan.L), "s"(g.scan.P), "s"(g.scan.by_L.mul), "s"(g.scan.by_L.shift), "s"(g.sc_rev), "s"(g.sc_nt),
                          "s"(g.sc_cpu), "s"(g.sc_ncg), "s"(g.sc_units), "s"(g.by_unit.mul), "s"(g.by_unit.shift), "s"(g.by_ncg.mul), "s"(g.by_ncg.shift),
                          "s"(g.by_cpu.mul), "s"(g.by_cpu.shift));
-        const int tile = pk_place(g, x, q - g.slot0);
+        // (only scans are placed otherwise than in mode 0: left to run time, every product has the code of all modes on its way to the first loads)
+        const int tile = EPI < 7 ? x * g.nx + q - g.slot0 : pk_place(g, x, q - g.slot0);
         if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
         const int tm = (int)g.by_ntn(tile), tn = tile - tm * g.ntn;
         auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
