@@ -67,31 +67,27 @@ __global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(S
     __shared__ float2 sA[THREADS];                   // (level 2: one per wavefront and lane; level 3: one per thread)
     __shared__ float2 sS[THREADS];
     __shared__ float2 sX[MAXOUT ? 256 : 16];
-    __shared__ unsigned s_id;
+    __shared__ unsigned s_tb;
 
     const int tid = threadIdx.x;
+    // A chain = the workgroups along time of one sequence and group of states.  (Scalar values all of them, by multiplications: as divisions by lanes they
+    // were 0.2 us in front of the first loads.)  Time index slowest: all first-in-time workgroups start before any second-in-time one.
     const int nchains = a.nPX * a.Bt;
-    unsigned id;
+    int tb = (int)a.by_chains(blockIdx.x);
+    const int chain = (int)blockIdx.x - tb * nchains, b = (int)a.by_nPX(chain), px = chain - b * a.nPX;
+    const int lane = tid & (a.pxb - 1), chunk = tid >> a.lg_pxb;
+    const int p = px * a.pxb + lane, pc = min(p, a.P - 1);       // pc, sc below: a valid state and step for every thread
+    float2 lam = a.lam[pc];
     if (a.nTB > 1) {
-        // One ticket counter per (sequence, state block) chain: the i-th workgroup of a chain to
-        // start takes time block i, so its predecessors along time have started before it.
-        if (tid == 0) {
-            const unsigned chain = blockIdx.x % nchains;
-            s_id = atomicAdd(a.ticket + (size_t)chain * SCAN_TICKET_STRIDE, 1u) * nchains + chain;
-        }
+        // One ticket counter per chain: the i-th workgroup of a chain to start takes time block i, so its predecessors along
+        // time have started before it.
+        if (tid == 0) s_tb = atomicAdd(a.ticket + (size_t)chain * SCAN_TICKET_STRIDE, 1u);
         __syncthreads();
-        id = s_id;
+        tb = __builtin_amdgcn_readfirstlane((int)s_tb);
     } else {
-        id = blockIdx.x;
         // no cross-workgroup wait can happen: mark the workspace header as clean
-        if (id == 0 && tid == 0) { a.err[0] = 0; a.err[1] = 0x53534d31u; }
+        if (blockIdx.x == 0 && tid == 0) { a.err[0] = 0; a.err[1] = 0x53534d31u; }
     }
-    // time index slowest: all first-in-time workgroups start before any second-in-time one
-    const int px = id % a.nPX;
-    const int b = (id / a.nPX) % a.Bt;
-    const int tb = id / nchains;
-    const int lane = tid % a.pxb, chunk = tid / a.pxb;
-    const int p = px * a.pxb + lane;
     const bool active = p < a.P;
     const int L = a.L;
     const int s0 = (tb * a.cy + chunk) * E;          // first logical step of this thread
@@ -100,14 +96,13 @@ __global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(S
     // every thread of the wavefront (MAXOUT: of the workgroup) owns E steps of a valid state: no guards needed
     const bool full = MAXOUT ? ((tb + 1) * a.cy * E <= L) && ((px + 1) * a.pxb <= a.P) : __builtin_amdgcn_ballot_w64(len == E && active) == ~0ull;
     const int stride = REV ? -a.P : a.P;                         // elements between consecutive logical steps
-    const int pc = min(p, a.P - 1), sc = min(s0, L - 1);         // a valid state and step for every thread
+    const int sc = min(s0, L - 1);
     const long first = (rowbase + (REV ? (L - 1 - sc) : sc)) * a.P + pc;      // element of logical step s0
     const bool ends = len > 0 && s0 + len == L;                  // the thread owns the last logical step
     // state that flows into the sequence (with a look-back, into its first workgroup: level 3)
     float2 Xin = make_float2(0.f, 0.f);
     if (!MAXOUT && a.nTB == 1 && !REV && a.x0 && active) Xin = a.x0[(long)b * a.P + p];
 
-    float2 lam = active ? a.lam[p] : make_float2(0.f, 0.f);
     if (REV) lam.y = -lam.y;
 
     // logical step s <-> time t: forward t = s, reverse t = L-1-s.
@@ -276,7 +271,7 @@ __global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(S
     const int sg0 = (tb / G) * G;
     const bool lastchunk = (chunk == a.cy - 1);
     const size_t desc_stride = (size_t)nchains * a.pxb;          // descriptors per time block
-    ScanDesc *mine = a.desc + ((size_t)id * a.pxb + lane);
+    ScanDesc *mine = a.desc + (((size_t)tb * nchains + chain) * a.pxb + lane);
     float2 Ablk = make_float2(0.f, 0.f), Sblk = make_float2(0.f, 0.f);
     if (lastchunk) {
         Ablk = cmul(A, Aex);
@@ -481,13 +476,16 @@ ScanPlan plan_scan(int64_t Bt, int64_t L, int64_t P, bool records)
     return pl;
 }
 
-hipError_t launch_scan(const ScanArgs &a, bool reverse, hipStream_t s)
+hipError_t launch_scan(const ScanArgs &a_in, bool reverse, hipStream_t s)
 {
+    ScanArgs a = a_in;
     const int64_t nblocks = (int64_t)a.nPX * a.Bt * a.nTB;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL || a.pxb < 16 || a.pxb > 256 || (a.pxb & (a.pxb - 1)) || a.cy < 1) return hipErrorInvalidValue;
     // a look-back: a thread per (state, workgroup of a group), blocks of a power of two of chunks
     if (a.nTB > 1 ? a.pxb != 16 || (a.cy != 16 && a.cy != 32 && a.cy != 64) : (int64_t)a.cy * SCAN_E < a.L) return hipErrorInvalidValue;
     const int64_t threads = ((int64_t)a.pxb * a.cy + 63) / 64 * 64;
+    a.by_chains = FastDiv::by((unsigned)((int64_t)a.nPX * a.Bt)); a.by_nPX = FastDiv::by((unsigned)a.nPX);
+    a.lg_pxb = __builtin_ctz((unsigned)a.pxb);
     const bool maxout = a.rowmax_out != nullptr;
     if (threads > (maxout ? 256 : SCAN_MAX_THREADS) || (maxout && !a.amax_out)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblocks), block((unsigned)threads);

@@ -182,6 +182,7 @@ struct ScanArgs {
     uint32_t *ticket;        // per-chain counters, SCAN_TICKET_STRIDE apart (nTB > 1 only)
     uint32_t *err;           // &WsHeader::err (the magic word follows it)
     int Bt, L, P, pxb, cy, nPX, nTB;
+    FastDiv by_chains, by_nPX; int lg_pxb;       // nPX * Bt, nPX; log2 of pxb (set by the launch)
     uint32_t spin_limit;
     unsigned *rowmax_out;    // [Bt*L] or null: atomic maximum of the magnitudes of every token row of `out`, zero on entry
     unsigned *amax_out;      // [ABSMAX_SLOTS] (with rowmax_out): atomic maximum of the magnitudes of `out`, zero on entry
