@@ -350,6 +350,59 @@ PackSrc glu_source(const float *W, int64_t H)
 }
 
 }  // namespace
+
+int half_glu_backward(const float *u, const float *W, const float *gate, const float *dy, int64_t T, int64_t H, float *du, float *dW,
+                      void *workspace, size_t ws_bytes, hipStream_t s, SlabSum *dW_slabs)
+{
+    if (!u || !W || !gate || !dy || !du || !dW) return SSM_ERR_INVALID_ARG;
+    if (T <= 0 || H <= 0) return SSM_ERR_INVALID_ARG;
+    GluLayout lo;
+    if (!make_glu_layout(T, H, true, lo)) return SSM_ERR_UNSUPPORTED;
+    if (misaligned(u, 16) || misaligned(W, 4) || misaligned(gate, 16) || misaligned(dy, 16) || misaligned(du, 4) ||
+        misaligned(dW, 4))
+        return SSM_ERR_INVALID_ARG;
+    if (!workspace || misaligned(workspace, ALIGN) || ws_bytes < lo.total) return SSM_ERR_WORKSPACE;
+    char *ws = static_cast<char *>(workspace);
+    float *x1 = reinterpret_cast<float *>(ws + lo.x1);
+    float *dz = reinterpret_cast<float *>(ws + lo.dz);
+    float *ds = reinterpret_cast<float *>(ws + lo.ds), *gd = reinterpret_cast<float *>(ws + lo.gd);
+    float *dWpart = reinterpret_cast<float *>(ws + lo.dWpart);
+    const long n = (long)T * H;
+    unsigned *rowmax = reinterpret_cast<unsigned *>(ws + lo.rowmax);
+    unsigned *x1_slots = reinterpret_cast<unsigned *>(ws + lo.slots), *dz_slots = x1_slots + GLU_MAX_SLOTS;
+    const PackJob w = glu_pack(ws, lo, H, PACK_WT);
+    if (lo.two_planes) {
+        hipLaunchKernelGGL(gate_bwd_prep_max_kernel, dim3((unsigned)(lo.main_blocks + w.nblocks)), dim3(256), 0, s, u, gate, dy,
+                           x1, dz, ds, gd, n, (int)H, (long)T, rowmax, x1_slots, dz_slots, glu_source(W, H), w);
+    } else {
+        hipLaunchKernelGGL(gate_bwd_prep_kernel, dim3((unsigned)(((n + 3) / 4 + 255) / 256 + w.nblocks)), dim3(256), 0, s, u, gate, dy, x1,
+                           dz, ds, gd, n, glu_source(W, H), w);
+    }
+    HIP_TRY(hipGetLastError());
+    // du[t, i] = ds[t, i] + gd[t, i] sum_j dz[t, j] W[i, j]
+    GemmArgs g{};
+    g.A = dz; g.lda = H; g.w = PackedW{w.frag, w.exp}; g.planes = lo.planes;
+    g.C = du; g.ldc = H; g.E = ds; g.E2 = gd; g.lde = H; g.epilogue = 4;
+    g.M = (int)T; g.N = (int)H; g.K = (int)H;
+    if (lo.two_planes) g.amaxA = AbsMax{nullptr, 0, rowmax, lo.row_parts, (long)T};
+    // dW[i, j] = sum_t x1[t, i] dz[t, j]: reduction over tokens in K slabs (same launch), then a fixed-order sum
+    GemmArgs h{};
+    h.A = x1; h.lda = H;
+    h.B = dz; h.ldb = H;
+    h.C = dWpart; h.ldc = H;
+    h.M = (int)H; h.N = (int)H; h.K = (int)T; h.splits = lo.splits;
+    if (lo.two_planes) { h.amaxA = AbsMax{x1_slots, lo.main_blocks, nullptr, 0, 0}; h.amaxB = AbsMax{dz_slots, lo.main_blocks, nullptr, 0, 0}; }
+    HIP_TRY(launch_products(g, &h, nullptr, lo.dw_first, s));
+    const long nw = (long)H * H;
+    if (dW_slabs) {
+        *dW_slabs = SlabSum{dWpart, dW, nw, lo.splits};
+        return SSM_OK;
+    }
+    hipLaunchKernelGGL(sum_slabs_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, dWpart, nw, lo.splits, dW);
+    HIP_TRY(hipGetLastError());
+    return SSM_OK;
+}
+
 }  // namespace ssm
 
 using namespace ssm;
@@ -433,50 +486,7 @@ ssm_status ssm_half_glu_bwd(const float *u, const float *W, const float *gate, c
                             int64_t T, int64_t H, float *du, float *dW,
                             void *workspace, size_t ws_bytes, void *stream)
 {
-    if (!u || !W || !gate || !dy || !du || !dW) return SSM_ERR_INVALID_ARG;
-    if (T <= 0 || H <= 0) return SSM_ERR_INVALID_ARG;
-    GluLayout lo;
-    if (!make_glu_layout(T, H, true, lo)) return SSM_ERR_UNSUPPORTED;
-    if (misaligned(u, 16) || misaligned(W, 4) || misaligned(gate, 16) || misaligned(dy, 16) || misaligned(du, 4) ||
-        misaligned(dW, 4))
-        return SSM_ERR_INVALID_ARG;
-    if (!workspace || misaligned(workspace, ALIGN) || ws_bytes < lo.total) return SSM_ERR_WORKSPACE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    char *ws = static_cast<char *>(workspace);
-    float *x1 = reinterpret_cast<float *>(ws + lo.x1);
-    float *dz = reinterpret_cast<float *>(ws + lo.dz);
-    float *ds = reinterpret_cast<float *>(ws + lo.ds), *gd = reinterpret_cast<float *>(ws + lo.gd);
-    float *dWpart = reinterpret_cast<float *>(ws + lo.dWpart);
-    const long n = (long)T * H;
-    unsigned *rowmax = reinterpret_cast<unsigned *>(ws + lo.rowmax);
-    unsigned *x1_slots = reinterpret_cast<unsigned *>(ws + lo.slots), *dz_slots = x1_slots + GLU_MAX_SLOTS;
-    const PackJob w = glu_pack(ws, lo, H, PACK_WT);
-    if (lo.two_planes) {
-        hipLaunchKernelGGL(gate_bwd_prep_max_kernel, dim3((unsigned)(lo.main_blocks + w.nblocks)), dim3(256), 0, s, u, gate, dy,
-                           x1, dz, ds, gd, n, (int)H, (long)T, rowmax, x1_slots, dz_slots, glu_source(W, H), w);
-    } else {
-        hipLaunchKernelGGL(gate_bwd_prep_kernel, dim3((unsigned)(((n + 3) / 4 + 255) / 256 + w.nblocks)), dim3(256), 0, s, u, gate, dy, x1,
-                           dz, ds, gd, n, glu_source(W, H), w);
-    }
-    HIP_TRY(hipGetLastError());
-    // du[t, i] = ds[t, i] + gd[t, i] sum_j dz[t, j] W[i, j]
-    GemmArgs g{};
-    g.A = dz; g.lda = H; g.w = PackedW{w.frag, w.exp}; g.planes = lo.planes;
-    g.C = du; g.ldc = H; g.E = ds; g.E2 = gd; g.lde = H; g.epilogue = 4;
-    g.M = (int)T; g.N = (int)H; g.K = (int)H;
-    if (lo.two_planes) g.amaxA = AbsMax{nullptr, 0, rowmax, lo.row_parts, (long)T};
-    // dW[i, j] = sum_t x1[t, i] dz[t, j]: reduction over tokens in K slabs (same launch), then a fixed-order sum
-    GemmArgs h{};
-    h.A = x1; h.lda = H;
-    h.B = dz; h.ldb = H;
-    h.C = dWpart; h.ldc = H;
-    h.M = (int)H; h.N = (int)H; h.K = (int)T; h.splits = lo.splits;
-    if (lo.two_planes) { h.amaxA = AbsMax{x1_slots, lo.main_blocks, nullptr, 0, 0}; h.amaxB = AbsMax{dz_slots, lo.main_blocks, nullptr, 0, 0}; }
-    HIP_TRY(launch_products(g, &h, nullptr, lo.dw_first, s));
-    const long nw = (long)H * H;
-    hipLaunchKernelGGL(sum_slabs_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, dWpart, nw, lo.splits, dW);
-    HIP_TRY(hipGetLastError());
-    return SSM_OK;
+    return static_cast<ssm_status>(half_glu_backward(u, W, gate, dy, T, H, du, dW, workspace, ws_bytes, static_cast<hipStream_t>(stream), nullptr));
 }
 
 }  // extern "C"

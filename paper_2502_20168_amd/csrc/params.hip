@@ -429,6 +429,7 @@ int coldot_slabs(int64_t T, int planes)
 //       dAbar_p = sum of the reverse scan's partial rows;
 //       dLambda_p = conj(Delta Abar) dAbar + conj(Delta^2 psi'(z)) dg,   psi(z) = (e^z - 1)/z
 //       dlog_delta_p = Delta * Re(conj(Lambda Abar) dAbar + conj(Abar) dg)
+//   workgroups from P+H on: the slabs of another reduction, where there is one
 //   workgroups [P, P+H): row h of dC = sum of its slabs with the imaginary part negated
 //       (dC[h,p] = sum_t dy[t,h] conj(x[t,p])), and dD[h] = sum of the column-dot slabs.
 // The factors of dAbar and dg depend on the parameters alone: the prep launch of the pass computes them (adjoint_block),
@@ -494,6 +495,16 @@ __global__ void __launch_bounds__(256) epilogue_kernel(EpilogueArgs a)
     __shared__ double red[16];
     const int tid = threadIdx.x, blk = blockIdx.x;
     const long PH2 = 2L * a.P * a.H;
+    if (blk >= a.P + a.H) {
+        // (four values per thread, the gate's dW: as a launch of its own 5.6 us and a boundary, block of 32 x 128, 1024, 512)
+        const long i = 4 * ((long)(blk - a.P - a.H) * 256 + tid);
+        if (i >= a.also.n) return;
+        const int n = (int)min(a.also.n - i, 4L);
+        float4 v[1];
+        sum_slabs<1>(a.also.part + i, a.also.n, 0, 0, 1, a.also.slabs, n, v);
+        store4(a.also.out + i, v[0], n);
+        return;
+    }
     if (blk < a.P) {
         const int p = blk;
         const float2 apart0 = tid < a.npart ? a.dAbar_part[(long)tid * a.P + p] : make_float2(0.f, 0.f);
@@ -582,7 +593,9 @@ hipError_t launch_epilogue(const EpilogueArgs &a_in, hipStream_t s)
     EpilogueArgs a = a_in;
     if (!a.adj) return hipErrorInvalidValue;
     a.lgB = column_threads_log2(a.H); a.lgC = column_threads_log2(2 * a.P);
-    hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)(a.P + a.H)), dim3(256), 0, s, a);
+    const int64_t further = a.also.out ? (a.also.n + 1023) / 1024 : 0;
+    if (a.P + a.H + further > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)(a.P + a.H + further)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

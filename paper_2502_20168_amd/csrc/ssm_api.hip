@@ -379,7 +379,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
                    const float *log_delta, const float *u, const uint8_t *is_first, const ssm_c64 *x0,
                    int64_t Bt, int64_t L, int64_t H, int64_t P, const ssm_c64 *x, const float *dy,
                    float *du, ssm_c64 *dLambda, ssm_c64 *dB, ssm_c64 *dC, float *dD, float *dlog_delta,
-                   ssm_c64 *dx0, void *workspace, size_t ws_bytes, hipStream_t s, StageTimer *timer)
+                   ssm_c64 *dx0, void *workspace, size_t ws_bytes, hipStream_t s, StageTimer *timer, const SlabSum &also = {})
 {
     if (!Lambda || !B || !C || !D || !log_delta || !u || !x || !dy || !du || !dLambda || !dB || !dC ||
         !dD || !dlog_delta)
@@ -513,6 +513,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     ea.dD_part = dDpart; ea.nslab = lo.nslab;
     ea.dLambda = reinterpret_cast<float2 *>(dLambda); ea.dB = reinterpret_cast<float2 *>(dB);
     ea.dC = reinterpret_cast<float2 *>(dC); ea.dD = dD; ea.dlog_delta = dlog_delta;
+    ea.also = also;
     HIP_TRY(launch_epilogue(ea, s));
     MARK();
     return SSM_OK;
@@ -898,10 +899,13 @@ ssm_status ssm_block_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 
     char *ws = static_cast<char *>(workspace);
     float *dypre = reinterpret_cast<float *>(ws + bl.dypre);
     // the gate's adjoint turns dout into the gradient of the layer's output, then the layer's own pass
-    st = ssm_half_glu_bwd(y, W, gate, dout, Bt * L, H, dypre, dW, ws + bl.glu, bl.dypre - bl.glu, stream);
+    // (whose last launch also sums up the slabs of dW)
+    SlabSum dW_slabs{};
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    st = static_cast<ssm_status>(half_glu_backward(y, W, gate, dout, Bt * L, H, dypre, dW, ws + bl.glu, bl.dypre - bl.glu, s, &dW_slabs));
     if (st != SSM_OK) return st;
     return run_bwd(Lambda, B, C, D, log_delta, u, is_first, x0, Bt, L, H, P, x, dypre, du, dLambda, dB, dC, dD,
-                   dlog_delta, dx0, ws + bl.ssm, bl.glu - bl.ssm, static_cast<hipStream_t>(stream), nullptr);
+                   dlog_delta, dx0, ws + bl.ssm, bl.glu - bl.ssm, s, nullptr, dW_slabs);
 }
 
 ssm_status ssm_workspace_status(const void *workspace, void *stream)

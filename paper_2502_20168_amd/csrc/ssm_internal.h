@@ -250,6 +250,9 @@ hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
 hipError_t launch_discretize(const float2 *Lambda, const float2 *B, const float *log_delta, int P, int H, float2 *lam_bar, float2 *Bbar,
                              hipStream_t s);
 
+// out[i] = sum of slabs of n values each, in their order; out == nullptr: nothing to sum
+struct SlabSum { const float *part; float *out; int64_t n; int slabs; };
+
 struct EpilogueArgs {
     const float2 *B; const StateAdjoint *adj; int P, H;
     const float *dBbar_part; int nsplit_B;   // [nsplit_B][2P][H]
@@ -257,8 +260,12 @@ struct EpilogueArgs {
     const float2 *dAbar_part; int64_t npart; // [npart][P]
     const float *dD_part; int nslab;         // [nslab][H]
     float2 *dLambda; float2 *dB; float2 *dC; float *dD; float *dlog_delta;
+    SlabSum also;                            // of another reduction, in the same launch
     int lgB, lgC;                            // set by launch_epilogue
 };
 hipError_t launch_epilogue(const EpilogueArgs &a, hipStream_t s);
+// body of ssm_half_glu_bwd (returns an ssm_status); dW_slabs non-null: the slabs of dW are left to a later launch, which is handed over
+int half_glu_backward(const float *u, const float *W, const float *gate, const float *dy, int64_t T, int64_t H, float *du, float *dW,
+                      void *workspace, size_t ws_bytes, hipStream_t s, SlabSum *dW_slabs);
 
 }  // namespace ssm

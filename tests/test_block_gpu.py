@@ -152,6 +152,22 @@ def test_s5_block_matches_oracle_composition(Bt, L, H, P):
     assert torch.equal(f2["y"], f["y"]) and torch.equal(out2.reshape(Bt, L, H), f["out"])
 
 
+# widths whose H * H is no multiple of the 1024 values of a workgroup, or of the four of a thread; one slab and many
+@pytest.mark.parametrize("Bt,L,H,P", [(1, 3, 1, 2), (1, 5, 3, 2), (4, 100, 33, 9), (6, 600, 67, 30), (3, 64, 65, 64), (16, 256, 512, 64)])
+def test_slabs_summed_in_the_layers_last_launch(Bt, L, H, P):
+    """dW of the block, whose slabs the layer's parameter epilogue sums up, is that of the gate's own call to the last bit."""
+    import torch
+    from paper_2502_20168_amd import binding as ssm
+    w = wl.custom("block", Bt, L, H, P, backward=True, p_reset=0.02, force_first=True, with_x0=False, seed=5)
+    d = ssm.to_device(wl.gen_inputs(w))
+    Wd = torch.from_numpy(wl.gen_half_glu(4, H, seed=6)["W"]).cuda()
+    par = (d["Lambda"], d["B"], d["C"], d["D"], d["log_delta"], Wd, d["u"], d["is_first"], None)
+    f = ssm.ssm_block_fwd(*par)
+    b = ssm.ssm_block_bwd(*par, f["x"], f["y"], f["gate"], d["dy"])
+    _, dW = ssm.ssm_half_glu_bwd(f["y"].reshape(Bt * L, H), Wd, f["gate"].reshape(Bt * L, H), d["dy"].reshape(Bt * L, H))
+    assert torch.equal(b["dW"], dW)
+
+
 def _block_random_shapes(n, seed):
     rng = np.random.Generator(np.random.PCG64(seed))
     return [(int(rng.integers(1, 3000)), int(rng.choice([rng.integers(1, 40), rng.integers(40, 400), 4 * rng.integers(8, 130)])))
