@@ -510,6 +510,9 @@ struct StoreInputs {
     __device__ __forceinline__ void store(const PkDev &g, const float *tile, int tid, int batch, int m0, int n0)
     {
         const int c = 4 * (tid % LANES), col = n0 + c, n = g.N - col;
+        // Through the L2 where every unit is 16 aligned bytes.  Others are written in pieces that only the L2 puts together: forward pass of 208 x 64 tokens, H = 35,
+        // P = 72: 21.4 us, with all stores through the L2 24.0; forward and gradient pass of 200 x 64, 99, 33: 61.6 and 66.5, of 208 x 64, 64, 72: 65.1 and 62.5.
+        const bool through = BM < 128 && ((reinterpret_cast<uintptr_t>(g.C) | reinterpret_cast<uintptr_t>(g.C2) | 4 * g.ldc) & 15) == 0;
 #pragma unroll
         for (int i = 0; i < UNITS; ++i) {
             const int r = row_of(tid, batch, i);
@@ -553,8 +556,8 @@ struct StoreInputs {
                 o = make_float4(fmaf(v.x, e2[i].x, e[i].x), fmaf(v.y, e2[i].y, e[i].y), fmaf(v.z, e2[i].z, e[i].z), fmaf(v.w, e2[i].w, e[i].w));
             }
             if (in) {
-                if constexpr (BM == 128) {
-                    // (launches of several rounds: of little use, and 1024 x 16 tokens, 512, 512, forward, take 0.5 % longer with it)
+                if (!through) {
+                    // (128 rows: launches of several rounds: of little use, and 1024 x 16 tokens, 512, 512, forward, take 0.5 % longer with it)
                     store4(g.C + row * g.ldc + col, o, n);
                     if (second) store4(g.C2 + row * g.ldc + col, o2, n);
                 } else {
