@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "fast_div.h"
+
 namespace ssm {
 
 // ---------------------------------------------------------------------------------------------
@@ -34,19 +36,6 @@ constexpr int ABSMAX_SLOTS = 512;            // slots of a maximum that is gathe
 struct AbsMax {
     const unsigned *slots; int n;            // slots == nullptr and rows == nullptr: not known
     const unsigned *rows; int row_parts; long row_stride;
-};
-
-// Division of integers below 2^31 by a number that the host knows: floor(n / d) = n mul >> shift with mul = ceil(2^(31 + l) / d), 2^l >= d.
-// (Three scalar instructions; the compiler's own division by an argument is over twenty, one behind the other, and placing a tile takes five.)
-struct FastDiv {
-    unsigned mul, shift;
-    static FastDiv by(unsigned d)
-    {
-        unsigned l = 0;
-        while ((1ull << l) < d) ++l;
-        return {(unsigned)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
-    }
-    __host__ __device__ __forceinline__ unsigned operator()(unsigned n) const { return (unsigned)(((unsigned long long)n * mul) >> shift); }
 };
 
 // Epilogue 7 of a product with packed weights: the resettable scan (Eq. 4 with the elements of Eq. 9 and the

@@ -1,5 +1,6 @@
 """Every 16-byte request that the producers of a product make for its activations, walked on the host with the functions
-that the kernel takes its addresses from: all of them lie inside the activations, or inside the packed weights."""
+that the kernel takes its addresses from: all of them lie inside the activations, or inside the packed weights.  And the
+divisions that place a tile, against the processor's."""
 import os
 import subprocess
 
@@ -56,11 +57,43 @@ int main()
 }
 """
 
+DIVIDE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <initializer_list>
+#include "fast_div.h"
+int main()
+{
+    const unsigned top = 0x7fffffffu;
+    long bad = 0;
+    auto check = [&](unsigned n, unsigned d) { if (n <= top && ssm::FastDiv::by(d)(n) != n / d) { if (!bad++) printf("%u / %u\n", n, d); } };
+    srand(1);
+    auto any = [&] { return ((unsigned)rand() << 16 ^ (unsigned)rand()) & top; };
+    for (int k = 0; k < 200000; ++k) {
+        // divisors of any length, and those next to a power of two
+        unsigned d = k < 4096 ? k + 1 : any() >> rand() % 31;
+        if (k % 3 == 0) d = (1u << k % 31) + (unsigned)(k / 31 % 3) - 1;
+        if (d == 0 || d > top) continue;
+        const unsigned q = top / d * d, m = any() / d * d;               // multiples and their neighbours
+        for (unsigned n : {0u, 1u, d - 1, d, d + 1, m - 1, m, m + d - 1, q - 1, q, top, any()}) check(n, d);
+    }
+    return bad != 0;
+}
+"""
 
-def test_no_request_leaves_the_activations_or_the_weights(tmp_path):
+
+def _run(tmp_path, text):
     src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
-    src.write_text(WALK)
+    src.write_text(text)
     subprocess.check_call([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2502_20168_amd", "csrc"), str(src),
                            "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+def test_no_request_leaves_the_activations_or_the_weights(tmp_path):
+    _run(tmp_path, WALK)
+
+
+def test_divisions_by_multiplication_are_exact(tmp_path):
+    _run(tmp_path, DIVIDE)
