@@ -17,8 +17,7 @@ struct FastDiv {
     unsigned mul, shift;
     static FastDiv by(unsigned d)
     {
-        unsigned l = 0;
-        while ((1ull << l) < d) ++l;
+        const unsigned l = d > 1 ? 32 - (unsigned)__builtin_clz(d - 1) : 0;
         return {(unsigned)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
     }
     SSM_DIV unsigned operator()(unsigned n) const { return (unsigned)(((unsigned long long)n * mul) >> shift); }
