@@ -24,6 +24,8 @@
 #include "gemm_kernel.h"
 #include "pk_units.h"
 
+#include <type_traits>
+
 namespace ssm {
 
 constexpr int PK_BN = 128, PK_CONSUMERS = 4, PK_PRODUCERS = 4, PK_STAGES = 2;
@@ -54,9 +56,21 @@ struct PkDev {
     int sc_nt, sc_cpu, sc_ncg, sc_units, sc_rev;
     FastDiv by_ntn, by_unit, by_ncg, by_cpu;     // ntn, sc_nt * sc_cpu, sc_ncg, sc_cpu
     ScanEpilogue scan;
-    const unsigned *rows; int row_parts; long row_stride;    // largest magnitudes of the rows of A (two planes), see AbsMax
+    const unsigned *rows; int row_parts;    // largest magnitudes of the rows of A (two planes), see AbsMax
+    // C and C2 are stored through the L2 (store_rule.h).  (Here: the four bytes in front of row_stride were empty.  In front of `scan` it moved the
+    // arguments of the scans by eight, some into another cache line: an input projection on 32 x 64 tiles, 8000 tokens, H = 100, P = 30: 7.5 -> 8.0 us)
+    int through;
+    long row_stride;
     unsigned *c2_rowmax;                    // epilogue 6: [ceil(N/128)][M] or null
 };
+
+// LEFT: the states stay in the L2 until the launch ends (store_rule.h).  A kernel of its own: chosen between at run time, the stores of 64-row row scans took
+// 0.5 to 1 % of forward and gradient pass (6000 to 12000 tokens, H from 64 to 128, P from 250 to 512), through the L2 as before.
+template <bool LEFT> __device__ __forceinline__ void store_state(float2 *p, float2 v)
+{
+    if constexpr (LEFT) *p = v;
+    else store_through(p, v);
+}
 
 // ---------------------------------------------------------------------------------------------
 // Epilogues 7 and 8: the resettable scan (forward, or the reverse one of the gradient pass) over the rows of a
@@ -224,8 +238,8 @@ __device__ __forceinline__ unsigned wave_max(unsigned v) { return lane_xor_max<3
 
 // The tile is staged in lds.tile on entry.  REV: chi_t = gx_t + [not is_first_{t+1}] conj(Abar) chi_{t+1}, which walks
 // time backwards (later chunks and later tiles are the predecessors) and also reduces
-// dAbar += [not is_first_t] conj(x_{t-1}) chi_t per tile and writes dx0.
-template <int ROWS, bool REV>
+// dAbar += [not is_first_t] conj(x_{t-1}) chi_t per tile and writes dx0.  LEFT: see store_state.
+template <int ROWS, bool REV, bool LEFT>
 __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds &lds, int q, int c, int m0, int n0, int tile,
                                                    ScanSaved<ROWS / SCAN_WAVES> &saved, const ScanFlags<ROWS> &flags, float2 lam)
 {
@@ -412,7 +426,7 @@ __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds
             const bool r = (rmask >> e) & 1u;
             const float2 le = make_float2(r ? 0.f : lam.x, r ? 0.f : lam.y);
             xs = cfma(le, xs, val[i]);
-            if (active) store_through(dst + (long)e * a.P + c, xs);
+            val[i] = xs;
             const float me = fmaxf(fabsf(xs.x), fabsf(xs.y));
             rm[e % SCAN_CHUNK] = active ? __float_as_uint(me) : 0u;
             amax = fmaxf(amax, me);
@@ -423,6 +437,10 @@ __device__ __forceinline__ void scan_epilogue_body(const PkDev &g, const ScanLds
                 acc.x = fmaf(qv.x, xs.x, fmaf(qv.y, xs.y, acc.x));
                 acc.y = fmaf(qv.x, xs.y, fmaf(-qv.y, xs.x, acc.y));
             }
+        }
+        if (active) {
+#pragma unroll
+            for (int i = 0; i < SCAN_CHUNK; ++i) store_state<LEFT>(dst + (long)(REV ? RC - 1 - (8 * k + i) : 8 * k + i) * a.P + c, val[i]);
         }
         if (a.rowmax_out) {
             // largest magnitude of every row within this column tile, stored as [column tile][row] (the consumer of C
@@ -510,9 +528,6 @@ struct StoreInputs {
     __device__ __forceinline__ void store(const PkDev &g, const float *tile, int tid, int batch, int m0, int n0)
     {
         const int c = 4 * (tid % LANES), col = n0 + c, n = g.N - col;
-        // Through the L2 where every unit is 16 aligned bytes.  Others are written in pieces that only the L2 puts together: forward pass of 208 x 64 tokens, H = 35,
-        // P = 72: 21.4 us, with all stores through the L2 24.0; forward and gradient pass of 200 x 64, 99, 33: 61.6 and 66.5, of 208 x 64, 64, 72: 65.1 and 62.5.
-        const bool through = BM < 128 && ((reinterpret_cast<uintptr_t>(g.C) | reinterpret_cast<uintptr_t>(g.C2) | 4 * g.ldc) & 15) == 0;
 #pragma unroll
         for (int i = 0; i < UNITS; ++i) {
             const int r = row_of(tid, batch, i);
@@ -556,7 +571,7 @@ struct StoreInputs {
                 o = make_float4(fmaf(v.x, e2[i].x, e[i].x), fmaf(v.y, e2[i].y, e[i].y), fmaf(v.z, e2[i].z, e[i].z), fmaf(v.w, e2[i].w, e[i].w));
             }
             if (in) {
-                if (!through) {
+                if (BM == 128 || !g.through) {
                     // (128 rows: launches of several rounds: of little use, and 1024 x 16 tokens, 512, 512, forward, take 0.5 % longer with it)
                     store4(g.C + row * g.ldc + col, o, n);
                     if (second) store4(g.C2 + row * g.ldc + col, o2, n);
@@ -728,7 +743,7 @@ __device__ __forceinline__ RowScanSaved<ROWS> row_scan_request(const PkDev &g, c
 // tile: KW partial tiles of ROWS x BN, as tile_at places them; mem: row_scan_lds_bytes of LDS that nobody else uses
 // (MAXIMA: 64 rows, whose eight tokens of a thread make a wavefront one run of all states)
 // ahead: only the aggregate is published, for another tile's sake.  Returns -1, or the row tile whose aggregate is missing (nothing is stored then).
-template <int ROWS, int BN, int KW, bool REV, bool MAXIMA = false>
+template <int ROWS, int BN, int KW, bool REV, bool MAXIMA = false, bool LEFT = false>
 __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, float2 *mem, int tid, int m0, int n0, float2 lam, const RowScanPowers &power,
                                              const RowScanMasks<ROWS> &k, const RowScanSaved<ROWS> &saved, bool ahead)
 {
@@ -893,11 +908,11 @@ __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, 
         if (active) {
             if (m0 + ROWS <= g.M) {
 #pragma unroll
-                for (int i = 0; i < CH; ++i) store_through(dst + row_of(i) * a.P, val[i]);
+                for (int i = 0; i < CH; ++i) store_state<LEFT>(dst + row_of(i) * a.P, val[i]);
             } else {
 #pragma unroll
                 for (int i = 0; i < CH; ++i)
-                    if (m0 + row_of(i) < g.M) store_through(dst + row_of(i) * a.P, val[i]);
+                    if (m0 + row_of(i) < g.M) store_state<LEFT>(dst + row_of(i) * a.P, val[i]);
             }
             if constexpr (MAXIMA) static_assert(ROWS == 64 && BN == 128 && !REV, "rows8_wave_max");
             const Bits edge = REV ? k.start : k.end;
@@ -953,7 +968,7 @@ __device__ __forceinline__ float4 narrow_unit(const PkDev &g, int row, int k)
 }
 
 // ahead and result: see row_scan_body (other epilogues: false and -1)
-template <int BM, int NPL, int EPI>
+template <int BM, int NPL, int EPI, bool LEFT>
 __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_raw, int m0, int n0, int tile, int tid, bool ahead)
 {
     constexpr int NC = PK_CONSUMERS, NP = PK_PRODUCERS, BK = PK_BK, NS = PK_STAGES, PT = 64 * NP;
@@ -1204,11 +1219,11 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     }
 
     // (producers and consumers together: one copy of the code)
-    if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags, lam);
+    if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8, LEFT>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags, lam);
     else if constexpr (ROW_SCANS) {
         row_scan_flags<64, EPI == 8>(row_masks, row_scan, g.scan.is_first != nullptr);
         const RowScanPowers power = row_scan_powers<64, PK_BN, EPI == 8>(row_scan.lam, tid);
-        return row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid,
+        return row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9, LEFT>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid,
                                                                m0, n0, row_scan.lam, power, row_masks, row_saved, ahead);
     } else {
 #pragma unroll
@@ -1547,7 +1562,7 @@ __device__ __forceinline__ void in_global(GemmDev &g)
     in_global(g.A); in_global(g.B); in_global(g.C); in_global(g.amaxA.slots); in_global(g.amaxB.slots);
 }
 
-template <int BM, int BN, int NPL, int EPI, int TNB, int WPE>
+template <int BM, int BN, int NPL, int EPI, int TNB, int WPE, bool LEFT>
 __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -1571,7 +1586,7 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
             else if constexpr (BM == 32) {
                 if (g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, TNB == 0 || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
                 return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
-            } else return gemm_pk_tile<BM, NPL, EPI>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
+            } else return gemm_pk_tile<BM, NPL, EPI, LEFT>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
         };
         const int missing = __builtin_amdgcn_readfirstlane(run(g, tm, tid, false));
         if constexpr (scans_rows(NPL, EPI)) {
@@ -1625,6 +1640,8 @@ inline PkDev make_pk_dev(const GemmArgs &a)
     if (a.scan.L > 0) g.scan.by_L = FastDiv::by(a.scan.L);
     g.rows = a.amaxA.rows; g.row_parts = a.amaxA.row_parts; g.row_stride = a.amaxA.row_stride;
     g.c2_rowmax = a.c2_rowmax;
+    const auto address = [](const void *p) { return reinterpret_cast<uintptr_t>(p); };
+    g.through = a.epilogue >= 7 ? states_through(address(a.C), a.M, a.scan.P) : output_through(address(a.C), address(a.C2), a.M, 4 * a.ldc);
     if (a.epilogue == 9 || (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8))) {
         g.sc_rev = a.epilogue == 8;
         // (mode 7 from 64 row tiles on, where the XCDs get as many within 1/8: 14 shapes of 3000 .. 30000 tokens, gradient pass: 1.6 % faster on geometric
@@ -1670,13 +1687,19 @@ hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArg
     constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, EPI, PK32_SHORT) : pk;
     constexpr size_t most = pk > tnl ? pk : tnl;
     const size_t smem = tnl > pk_short ? most : (BM == 32 && ((BN == 64 && WPE == 4 && TNB == 0) || a.K <= PK32_SHORT)) ? pk_short : most;
-    auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE>;
-    static std::atomic<bool> raised[KERNEL_MAXDEV];
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), most, raised);
-    if (e != hipSuccess) return e;
     if (slots <= 0 || slots > 0x7fffffffL / 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(pk_threads(TNB)), smem, s, g, t[0], t[1]);
-    return hipGetLastError();
+    const auto launch = [&](auto left) -> hipError_t {
+        auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE, decltype(left)::value>;
+        static std::atomic<bool> raised[KERNEL_MAXDEV];
+        const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), most, raised);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(pk_threads(TNB)), smem, s, g, t[0], t[1]);
+        return hipGetLastError();
+    };
+    // (scans on smaller tiles: launches of at most 4 MiB of states on 32 rows, 32 MiB in the chains of 64)
+    if constexpr (EPI >= 7 && (BM == 128 || (BM == 64 && scans_rows(NPL, EPI))))
+        if (!g.through) return launch(std::true_type{});
+    return launch(std::false_type{});
 }
 
 }  // namespace ssm

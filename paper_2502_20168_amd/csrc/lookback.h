@@ -60,7 +60,8 @@ __device__ __forceinline__ bool wait_pair(const unsigned long long *w, unsigned 
 // be written back (boundaries between launches: 2.0 us behind a kernel that writes little, 3.2 to 4 behind one that writes 16 MB).
 // What the products and their scans write is not read again in the launch.  Forward and gradient pass of 16 x 256 tokens, H = P = 512: 131.4 ->
 // 128.4 us; 16 x 64, 256, 256: 46.6 -> 45.3; 4 x 4096, 256, 256: 158.9 -> 156.8; the 64 launches of a roll-out of 1024 x 16: 625 -> 617; launches of
-// several rounds within 0.3 % either way.  (Where a kernel's lanes write whole aligned units: see StoreInputs::store and launch_scan for where they do not.)
+// several rounds within 0.5 % either way.  Outputs and states take it by the rule of store_rule.h; the slabs of the reductions always, at any width (a few MB, written
+// once and read by the next launch; limited to widths of whole lines: 1 to 2.5 % slower on twelve of eighteen layers).
 __device__ __forceinline__ void store_through(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_through(float2 *p, float2 v)
 {

@@ -58,7 +58,7 @@ __device__ __forceinline__ float2 shfl_up2(float2 v, int d) { return make_float2
 // MAXOUT: the kernel also records the largest magnitude of every token row of its output (atomic maxima
 // into a.rowmax_out, zero on entry: the product that consumes the output stages every token under its own
 // scale) and of the whole output (a.amax_out, ABSMAX_SLOTS slots, zero on entry).
-// THROUGH: the states are stored through the L2 (store_through); see launch_scan.
+// THROUGH: the states are stored through the L2 (store_through); see store_rule.h.
 template <bool REV, bool MAXOUT, bool THROUGH>
 __global__ void __launch_bounds__(MAXOUT ? 256 : SCAN_MAX_THREADS) scan_kernel(ScanArgs a)
 {
@@ -489,11 +489,7 @@ hipError_t launch_scan(const ScanArgs &a_in, bool reverse, hipStream_t s)
     const bool maxout = a.rowmax_out != nullptr;
     if (threads > (maxout ? 256 : SCAN_MAX_THREADS) || (maxout && !a.amax_out)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblocks), block((unsigned)threads);
-    // States of up to 64 MiB, or in rows of whole cache lines, go through the L2 to memory at once: the L2 then holds little that the next launch
-    // has to wait for.  Scan and its reverse, stores left in the L2 and through it (us): 20 x 300 steps of 250 states 33.6 and 30.8,
-    // 16 x 256, 512: 25.0 and 23.3, 8 x 1024, 1024: 63.7 and 61.1, 4 x 4096, 256: 47.5 and 46.1, 128 x 256, 512 (134 MB of states) 131.7 and 130.8;
-    // more states than that in lines that two workgroups write half of, which only the L2 puts together: 7 x 4000, 900: 257.0 and 260.1.
-    const bool through = a.P % 16 == 0 || (int64_t)a.Bt * a.L * a.P * 8 <= 64 << 20;
+    const bool through = states_through(reinterpret_cast<uintptr_t>(a.out), (int64_t)a.Bt * a.L, a.P);
     const auto launch = [&](auto rev, auto max) {
         constexpr bool R = decltype(rev)::value, M = decltype(max)::value;
         if (through) hipLaunchKernelGGL((scan_kernel<R, M, true>), grid, block, 0, s, a);

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "fast_div.h"
+#include "store_rule.h"
 
 namespace ssm {
 

@@ -57,7 +57,8 @@ def test_scan_plans(shape, pr):
 
 
 # (the forward scan runs in the input projection, up to 4096 steps; longer ones: a scan kernel of several workgroups along time either way)
-@pytest.mark.parametrize("shape", [(14, 300, 512, 512), (9, 515, 520, 512), (5, 1500, 512, 512), (5, 1030, 512, 530), (2, 4100, 512, 520), (1, 5003, 530, 512)], ids=str)
+@pytest.mark.parametrize("shape", [(14, 300, 512, 512), (9, 515, 520, 512), (5, 1500, 512, 512), (5, 1030, 512, 530), (2, 4100, 512, 520), (1, 5003, 530, 512),
+                                   (17, 1000, 512, 530), (4, 4200, 512, 530)], ids=str)      # (states past 64 MiB: left in the L2)
 def test_scans_that_record_magnitudes(shape):
     """Two planes: the row maxima that the scan kernels (and the forward scan in its product) record scale the products behind them."""
     Bt, L, H, P = shape
