@@ -429,9 +429,9 @@ int coldot_slabs(int64_t T, int planes)
 //       dAbar_p = sum of the reverse scan's partial rows;
 //       dLambda_p = conj(Delta Abar) dAbar + conj(Delta^2 psi'(z)) dg,   psi(z) = (e^z - 1)/z
 //       dlog_delta_p = Delta * Re(conj(Lambda Abar) dAbar + conj(Abar) dg)
-//   workgroups from P+H on: the slabs of another reduction, where there is one
 //   workgroups [P, P+H): row h of dC = sum of its slabs with the imaginary part negated
-//       (dC[h,p] = sum_t dy[t,h] conj(x[t,p])), and dD[h] = sum of the column-dot slabs.
+//       (dC[h,p] = sum_t dy[t,h] conj(x[t,p])), and dD[h] = sum of the column-dot slabs;
+//   workgroups from P+H on: the slabs of another reduction, where there is one.
 // The factors of dAbar and dg depend on the parameters alone: the prep launch of the pass computes them (adjoint_block),
 // a thread per state beside everything else it does.  Here, in every workgroup of a state, their double-precision
 // transcendentals were 2 to 3.4 us in front of sums of 1 to 3 us.
@@ -439,20 +439,20 @@ int coldot_slabs(int64_t T, int planes)
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
 // s[r] = sum over the slabs i, i + step, ... < n of the four values at base + i stride + r pitch, r < R: in the order of the
-// slabs, four of them (4 R loads) in flight at a time.  A slab past the end re-reads the last one and is not added.
-template <int R>
+// slabs, D of them (D R loads) in flight at a time.  A slab past the end re-reads the last one and is not added.
+template <int R, int D = 4>
 __device__ __forceinline__ void sum_slabs(const float *base, long stride, long pitch, int i, int step, int n, int valid, float4 (&s)[R])
 {
 #pragma unroll
     for (int r = 0; r < R; ++r) s[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (; i < n; i += 4 * step) {
-        float4 v[4][R];
+    for (; i < n; i += D * step) {
+        float4 v[D][R];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < D; ++j)
 #pragma unroll
             for (int r = 0; r < R; ++r) v[j][r] = load4(base + (long)min(i + j * step, n - 1) * stride + r * pitch, valid);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < D; ++j)
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if (i + j * step < n) s[r] = add4(s[r], v[j][r]);
@@ -484,11 +484,18 @@ __device__ __forceinline__ void block_sum4(double *red, double (&v)[4], int tid)
     }
 }
 
-// Bound by the trips to memory of one workgroup: all are resident at once, and the slabs were written by the launch before.  A
+// Bound by the trips to memory of one workgroup: up to P + H = 1280 (96 registers: five per CU) a layer's are all resident at once, and the slabs were written by the launch before.  A
 // thread takes four columns of every row it sums in one request; threads that the columns leave over share out the slabs (groups
 // of 2^lgB / 2^lgC threads, whose sums meet in LDS in the order of the groups).  First workgroup's start to last one's end, with a
 // column per thread and request and the discretisation in front of the sums, and now: 4096 tokens, H = P = 512: 8.3 and 5.3 us;
 // 4800 tokens, H = 1024, P = 512: 14.0 and 7.3; 32768 tokens, 512, 512: 11.2 and 7.3; 1024 tokens, 256, 256: 5.3 and 3.6.
+// Behind them, started as those end, the gate's dW (a launch of its own: 5.6 us and a boundary, block of 32 x 128, 1024, 512), slab by slab in the
+// order of its own call, so nobody shares out slabs: up to 64 of them are as many trips to memory as there are batches in flight, and narrow layers have few
+// workgroups.  Eight at a time, and one value per thread up to 128 x 128, instead of four and four: blocks of 4096 tokens, H = P = 64: 57.0 -> 52.3 us, 128:
+// 72.1 -> 69.7; 16384, 64: 96.4 -> 92.2, 128: 122.5 -> 117.0.  From H = 200 on four values (16384, 200, 100: 163.9, single ones 166.0); up to four slabs four at a
+// time, since a batch reads the last slab again.
+constexpr int64_t SINGLE_VALUES = 128 * 128;
+__host__ __device__ __forceinline__ bool single_values(int64_t n) { return n <= SINGLE_VALUES; }
 __global__ void __launch_bounds__(256) epilogue_kernel(EpilogueArgs a)
 {
     __shared__ float4 part[2][256];
@@ -496,12 +503,16 @@ __global__ void __launch_bounds__(256) epilogue_kernel(EpilogueArgs a)
     const int tid = threadIdx.x, blk = blockIdx.x;
     const long PH2 = 2L * a.P * a.H;
     if (blk >= a.P + a.H) {
-        // (four values per thread, the gate's dW: as a launch of its own 5.6 us and a boundary, block of 32 x 128, 1024, 512)
-        const long i = 4 * ((long)(blk - a.P - a.H) * 256 + tid);
+        const long at = (long)(blk - a.P - a.H) * 256 + tid;
+        const bool single = single_values(a.also.n);
+        const long i = single ? at : 4 * at;
         if (i >= a.also.n) return;
-        const int n = (int)min(a.also.n - i, 4L);
+        const int n = single ? 1 : (int)min(a.also.n - i, 4L);
+        const float *part = a.also.part + i;
         float4 v[1];
-        sum_slabs<1>(a.also.part + i, a.also.n, 0, 0, 1, a.also.slabs, n, v);
+        if (single) sum_slabs<1, 8>(part, a.also.n, 0, 0, 1, a.also.slabs, 1, v);
+        else if (a.also.slabs <= 4) sum_slabs<1>(part, a.also.n, 0, 0, 1, a.also.slabs, n, v);
+        else sum_slabs<1, 8>(part, a.also.n, 0, 0, 1, a.also.slabs, n, v);
         store4(a.also.out + i, v[0], n);
         return;
     }
@@ -593,7 +604,7 @@ hipError_t launch_epilogue(const EpilogueArgs &a_in, hipStream_t s)
     EpilogueArgs a = a_in;
     if (!a.adj) return hipErrorInvalidValue;
     a.lgB = column_threads_log2(a.H); a.lgC = column_threads_log2(2 * a.P);
-    const int64_t further = a.also.out ? (a.also.n + 1023) / 1024 : 0;
+    const int64_t further = !a.also.out ? 0 : single_values(a.also.n) ? (a.also.n + 255) / 256 : (a.also.n + 1023) / 1024;
     if (a.P + a.H + further > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)(a.P + a.H + further)), dim3(256), 0, s, a);
     return hipGetLastError();

@@ -153,8 +153,10 @@ def test_s5_block_matches_oracle_composition(Bt, L, H, P):
     assert torch.equal(f2["y"], f["y"]) and torch.equal(out2.reshape(Bt, L, H), f["out"])
 
 
-# widths whose H * H is no multiple of the 1024 values of a workgroup, or of the four of a thread; one slab and many
-@pytest.mark.parametrize("Bt,L,H,P", [(1, 3, 1, 2), (1, 5, 3, 2), (4, 100, 33, 9), (6, 600, 67, 30), (3, 64, 65, 64), (16, 256, 512, 64)])
+# widths whose H * H is no multiple of the 256 or 1024 values of a workgroup, or of the four of a thread; one slab and many; the widest
+# with a value per thread and the next
+@pytest.mark.parametrize("Bt,L,H,P", [(1, 3, 1, 2), (1, 5, 3, 2), (4, 100, 33, 9), (6, 600, 67, 30), (3, 64, 65, 64), (16, 256, 512, 64),
+                                      (32, 128, 128, 8), (32, 128, 129, 16), (2, 64, 129, 16)])
 def test_slabs_summed_in_the_layers_last_launch(Bt, L, H, P):
     """dW of the block, whose slabs the layer's parameter epilogue sums up, is that of the gate's own call to the last bit."""
     import torch
