@@ -40,14 +40,14 @@ PEAK_F16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 / bf16 matrix
 # commit it was taken at).  Counters cannot be read from inside this process: these are constants of that
 # profile, not measurements of this run.
 PROFILE_TRAFFIC = {
-    "source": "profiles/gemm_scan_cfg2_fwd_bwd.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE at commit 281c0b1, counters scaled by "
+    "source": "profiles/gemm_scan_cfg2_fwd_bwd.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE at commit 4fc0876, counters scaled by "
               "a 64 MiB element-wise kernel of the same run); constants of that profile, not measured by this run",
-    "read_bytes": 274.6 * 2 ** 20, "write_bytes": 79.2 * 2 ** 20, "total_bytes": 353.8 * 2 ** 20,
+    "read_bytes": 274.4 * 2 ** 20, "write_bytes": 79.2 * 2 ** 20, "total_bytes": 353.6 * 2 ** 20,
     "algorithmic_bytes": 88.1e6, "total_over_algorithmic": 4.2,
-    "dominant_launch_bytes": (110.9 + 24.0) * 2 ** 20,
+    "dominant_launch_bytes": (110.6 + 24.0) * 2 ** 20,
     # reads chi 16, Bbar 2, dy 8; chi 16, u 8; dy 8, x 16; writes du 8, four slabs of dBbar and of dC 2 each (MiB)
     "dominant_launch_algorithmic_bytes": (74 + 24) * 2 ** 20,
-    "dominant_launch_mfma_busy": 0.546,
+    "dominant_launch_mfma_busy": 0.524,
 }
 
 

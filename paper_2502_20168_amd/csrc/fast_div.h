@@ -10,9 +10,9 @@
 
 namespace ssm {
 
-// floor(n / d), n and d below 2^31, d > 0: n mul >> shift with mul = ceil(2^(31 + l) / d), 2^l >= d.  (Three scalar instructions; the compiler's own
+// floor(n / d), n and d below 2^31, d > 0: n mul >> shift with mul = ceil(2^(31 + l) / d), 2^l >= d (Granlund and Montgomery, 1994).  (Three scalar instructions; the compiler's own
 // division by an argument is over twenty, one behind the other, and placing a tile takes five.  No number of rows reaches 2^31, those past the
-// last token of a tile included: a state of more than 32 values each would not fit any memory.)
+// last token of a tile included: rows are divided in scans of more than 32 states or of few tokens, and 2^31 rows of 33 states would not fit any memory.)
 struct FastDiv {
     unsigned mul, shift;
     static FastDiv by(unsigned d)
