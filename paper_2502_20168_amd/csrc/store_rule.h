@@ -14,6 +14,10 @@
 // 300 x 200 tokens, H = 500, P = 64 took 144 us instead of 131, of 160 x 200, 900, 30 118 instead of 95.
 //   Scan kernels (scan and its reverse), rows of no whole lines: 11 MiB 1.10, 23 1.05, 46 to 62 0.997 to 1.016, 64 to 192 with P = 900, 935 or 100 0.97 to 1.00,
 // with 250, 300 or 530 0.998 to 1.03.  Rows of whole lines, 128 to 384 MiB: 0.997 to 1.016.
+//   All of the above repeats a pass on the same arrays.  Over four sets of arrays in turn, what the rule leaves in the L2 would take 1.025 (states, forward), 1.014
+// (forward and gradient pass) and 1.039, 1.015 (outputs) times as long through it, 0.995 at the least (120 passes).  Not kept: left in the L2 as well where a row
+// scan of at most 128 input columns has more than one round of workgroups (513 tiles of 64 x 128 and more).  Repeated on the same arrays the forward pass alone gains 2 to 5 %
+// (6981 tokens, H = 38, P = 553: 49.5 -> 46.1 us) and forward and gradient pass lose 0.7 %; over four sets in turn the forward pass loses 1 to 3 % up to 1500 tiles.
 #pragma once
 
 #include <stdint.h>
