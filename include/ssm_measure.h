@@ -19,6 +19,7 @@ extern "C" {
 /* The same code path as ssm_scan_fwd / ssm_scan_bwd.  They wait for the stream before returning and
  * write the milliseconds of each stage to the HOST array stage_ms:
  *   forward : [0] discretise+pack, [1] input projection, [2] scan, [3] output projection
+ *             (a forward pass in one launch: [0])
  *   backward: [0] discretise+pack and dD partials, [1] gx = C^H dy (with the reverse scan in its tiles
  *             where the shape allows), [2] reverse scan kernel, [3] du with the dBbar and dC partials
  *             (one launch), [4] empty,
@@ -52,7 +53,8 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
  *   [5] 1 when the slab work items take the first slots of the launch of [4] == 3
  *   [6], [7] the same for the launches of C^H dy with dC and of du with dBbar when [4] == 2
  *   [8], [9], [10] tile of the launch of the input projection, of the output projection and of du, as
- *       1024 x rows + columns
+ *       1024 x rows + columns (the forward pass of at most 64 columns, 64 states and 64 steps per sequence on three planes is
+ *       one launch of its own up to 512 workgroups of 64 tokens; [8] and [9] are the tiles it would have otherwise)
  *   [11] workgroups along time of the scan kernels (1: no look-back; unused where products scan their tiles)
  * Returns SSM_ERR_INVALID_ARG / SSM_ERR_UNSUPPORTED for shapes the library does not take.           */
 #define SSM_PLAN_FIELDS 12

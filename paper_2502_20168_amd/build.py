@@ -15,7 +15,7 @@ OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssmscan.so")
 BIND = os.path.join(HERE, "_ssmbind.so")
 BIND_SOURCE = os.path.join(CSRC, "pybind.cpp")
-SOURCES = ["products2.hip", "products3.hip", "params.hip", "block.hip", "scan.hip", "ssm_api.hip", "gemm.hip", "noalloc.hip"]
+SOURCES = ["products2.hip", "products3.hip", "params.hip", "block.hip", "narrow.hip", "scan.hip", "ssm_api.hip", "gemm.hip", "noalloc.hip"]
 HEADERS = [os.path.join(CSRC, h) for h in ("ssm_internal.h", "fast_div.h", "store_rule.h", "gemm_common.h", "gemm_kernel.h", "gemm_packed.h", "pk_units.h", "pack.h", "lookback.h")] + \
           [os.path.join(os.path.dirname(HERE), "include", h) for h in ("ssm.h", "ssm_measure.h")]
 # packed-fp32 instructions are switched off on purpose (target feature removed for device code)

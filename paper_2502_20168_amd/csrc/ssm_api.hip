@@ -304,6 +304,20 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     float2 *xs = x ? reinterpret_cast<float2 *>(x) : reinterpret_cast<float2 *>(ws + lo.xbuf);
     const int T = (int)(Bt * L);
 
+    if (lo.planes == 3 && narrow_fwd_shape(Bt, L, H, P)) {
+        // a narrow layer over short sequences: one launch
+        MARK();
+        NarrowFwd n{};
+        n.Lambda = reinterpret_cast<const float2 *>(Lambda); n.B = reinterpret_cast<const float2 *>(B); n.C = reinterpret_cast<const float2 *>(C);
+        n.D = D; n.log_delta = log_delta; n.u = u; n.is_first = is_first; n.x0 = reinterpret_cast<const float2 *>(x0);
+        n.y = y; n.x = reinterpret_cast<float2 *>(x); n.x_last = reinterpret_cast<float2 *>(x_last); n.gelu_y = gelu_y; n.hdr = hdr;
+        n.Bt = (int)Bt; n.L = (int)L; n.H = (int)H; n.P = (int)P;
+        if (gate) { n.W = gate->W; n.pack = gate->w; }
+        HIP_TRY(launch_narrow_fwd(n, s));
+        for (int i = 0; i < SSM_FWD_STAGES; ++i) MARK();
+        return SSM_OK;
+    }
+
     // Two planes, sequences of whole 128-step pieces (fused), and sequences of other lengths (lo.row_scan): the input projection scans its own
     // output tile and stores the states directly (no scan kernel, Bbar u never goes to memory).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);

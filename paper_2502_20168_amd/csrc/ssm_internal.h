@@ -240,6 +240,25 @@ hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
 hipError_t launch_discretize(const float2 *Lambda, const float2 *B, const float *log_delta, int P, int H, float2 *lam_bar, float2 *Bbar,
                              hipStream_t s);
 
+// The forward pass of a narrow layer in one launch (narrow.hip).
+constexpr int NARROW_MAX = 64;               // columns, states, and steps
+struct NarrowFwd {
+    const float2 *Lambda, *B, *C; const float *D, *log_delta, *u; const uint8_t *is_first; const float2 *x0;
+    float *y; float2 *x, *x_last;            // x, x_last: or null
+    float *gelu_y;                           // GELU(y), or null
+    WsHeader *hdr;
+    int Bt, L, H, P;
+    const float *W; PackJob pack;            // the gate's weights, put into fragment order beside it, or null
+    int seqs, layer_blocks; FastDiv by_L;    // sequences of a workgroup; workgroups of the layer (set by the launch)
+};
+// (Its requests take units of four values.  Up to 512 workgroups, two rounds with more than 32 columns or states: 1.2 to 2.7 times as fast as the three
+// launches; 600 x 50 tokens, 64, 64, 600 workgroups with 50 of 64 rows each: 22.5 us and 22.8.)
+inline bool narrow_fwd_shape(int64_t Bt, int64_t L, int64_t H, int64_t P)
+{
+    return H >= 4 && P >= 2 && H <= NARROW_MAX && P <= NARROW_MAX && L <= NARROW_MAX && (Bt + NARROW_MAX / L - 1) / (NARROW_MAX / L) <= 512;
+}
+hipError_t launch_narrow_fwd(const NarrowFwd &a, hipStream_t s);
+
 // out[i] = sum of slabs of n values each, in their order; out == nullptr: nothing to sum
 struct SlabSum { const float *part; float *out; int64_t n; int slabs; };
 
