@@ -6,7 +6,7 @@
 namespace ssm {
 
 // A product over T tokens with N columns that has few 128x128 tiles shares its launch with a K = T
-// reduction on 64x64x64 tiles: a quarter of the multiply-adds per workgroup, so that the chain of K
+// reduction on 64x64 tiles: a quarter of the multiply-adds per workgroup, so that the chain of K
 // steps a small shape waits for is short.
 // (forward + gradient pass with 32 instead of 64, 36 shapes of 1000 .. 4000 tokens, H and P 128 .. 512: 3 % faster to 3 %
 // slower, 0.1 % slower on the mean; above 64 the product itself has a workgroup per CU)
@@ -23,8 +23,8 @@ static bool takes_tall_tiles(int64_t tall, int64_t low, int64_t items) { return 
 // Reductions of M x N over K rows (`count` of them, with the same number of tiles) that share a launch with a product.
 // What a launch of several rounds wants is one work item of the reductions per CU, a few less rather than more, and all of
 // them in the first slots: every CU then works on one item from beginning to end while the product's tiles pass through its
-// second place.  Beside a small product, whose workgroups have a CU to themselves (64 x 64 tiles, eight wavefronts of
-// either kind), half as many, and in front only where an item is the longer chain (more rows than the product's K loop).
+// second place.  Beside a small product (64 x 64 tiles)
+// half as many, and in front only where an item is the longer chain (more rows than the product's K loop).
 // The counts are those that divide 8 or that 8 divides, because then an XCD owns whole slabs or one band of one
 // (tn_place), and a few between; the one whose number of items is nearest in ratio; an item keeps at least 192 (64) rows.
 // One reduction, two planes: fewer, down to 160 items, where the launch with tiles of 128 rows then fits (4800 tokens, H 1024, P 512:

@@ -314,30 +314,28 @@ __device__ __forceinline__ unsigned lane_xor_max(unsigned v)
 // LDS and issue MFMAs, and four producer wavefronts that only stage tiles (global load -> split -> LDS).  A producer
 // and a consumer share each SIMD, so the VALU work of the split co-executes with the matrix instructions of the other
 // wavefront.  Two LDS stages: in iteration kt the producers fill the stage of tile kt+1 while the consumers work
-// on tile kt, with one workgroup barrier per K tile.  128 x 128 x 32 tiles, or 64 x 64 x 64 where the products of
-// the launch are small; with two planes two workgroups share a CU, so
-// that one's first loads and stores overlap the other's K loop.
+// on tile kt, with one workgroup barrier per K tile.  128 x 128 tiles (three planes 128 x 64), or 64 x 64 where the products of
+// the launch are small; two workgroups share a CU, so that one's first loads and stores overlap the other's K loop.
+//   Beside small products too: with eight wavefronts of either kind and 64 k per K tile an item of 64 x 64 took half as long, but every workgroup of the launch
+// then had a CU to itself, products of eight wavefronts included, and launches of 257 to 512 workgroups took two rounds.  Forward and gradient pass, with
+// that and now: 8 x 250 tokens, H = P = 180: 60.1 -> 52.9 us; 20 x 64, 300, 300: 73.0 -> 62.2; 16 x 33, 64, 64: 32.2 -> 26.3; block of 8 x 250, 180, 180:
+// 83.3 -> 72.6; 18 shapes 5.5 % faster on geometric mean; 16 x 64, 256, 256 (256 workgroups) the same, 8 x 1000, 128, 256 (items of 1000 tokens) 1.7 % slower.
 // ---------------------------------------------------------------------------------------------
 constexpr int TN_STAGES = 2;
-// Wavefronts: eight of either kind beside small products, whose workgroups have a CU to themselves and wait for the split
-// of every K tile and for chains of dependent matrix instructions (two consumers share out the k steps of a 32 x 32 block
-// and add up their results).
-constexpr int tn_producers(int TB) { return TB == 64 ? 8 : 4; }
-constexpr int tn_consumers(int TB) { return TB == 64 ? 8 : 4; }
+constexpr int TN_PRODUCERS = 4, TN_CONSUMERS = 4, TN_BK = 32;
 // Tiles by name: 128 = 128 x 128, 96 = 128 x 64 (three planes: half the registers and three quarters of the LDS of a square
 // tile, so that two workgroups share a CU here too), 64 = 64 x 64.
 constexpr int tn_rows(int TB) { return TB == 64 ? 64 : 128; }
 constexpr int tn_cols(int TB) { return TB == 128 ? 128 : 64; }
-constexpr int tn_bk(int TB) { return TB == 64 ? 64 : 32; }
 // (stages, two scales)
-constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * NPL * tn_bk(TB) * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }
+constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * NPL * TN_BK * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }
 
 template <int TB, int NPL, int EDGE>
 __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, int m0, int n0, int z, int kbeg, int kend, int tid)
 {
-    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), BK = tn_bk(TB), NS = TN_STAGES, NC = tn_consumers(TB), KG = NC / 4, NP = tn_producers(TB), PT = 64 * NP;
+    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), BK = TN_BK, NS = TN_STAGES, NC = TN_CONSUMERS, NP = TN_PRODUCERS, PT = 64 * NP;
     // K tiles of global loads in flight per producer (128 x 128 tiles: 3, 4 and 6 measured 1-5 % slower)
-    constexpr int PF = TB == 64 ? 4 : 2;
+    constexpr int PF = TB == 64 ? 3 : 2;
     using LA = SplitLoader<TM, BK, PT, NPL>;
     using LB = SplitLoader<TN, BK, PT, NPL>;
     static_assert(NPL == 2 || NPL == 3, "three bf16 planes or two scaled fp16 planes per operand");
@@ -409,13 +407,12 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
         for (int j = 0; j + 1 < PF; ++j)
             if (kt + j + 1 < nk) step(kt, j);
         __syncthreads();
-        if constexpr (KG > 1) __syncthreads();
         return;
     }
 
     // ---------------------------------------------------------------------- consumers
     const int l = tid & 63;
-    const int kg = wave / 4, wm = wave % 4 / 2, wn = wave % 2;
+    const int wm = wave / 2, wn = wave % 2;
     const int li = l & 31, hh = l >> 5;
     v16f acc[MI][NI];
 #pragma unroll
@@ -424,12 +421,19 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    // A single block per wavefront: the five small products of a k step go into two accumulators of their own.  The large one is then rounded once per
+    // step instead of six times (errors of dB and dC against 64 bits over 18 layers: 0.95 of what they were with two wavefronts that shared out the steps, of dW 0.80;
+    // 1.05 and 1.19 in one accumulator), and the chain of dependent matrix instructions is half as long.
+    constexpr bool APART = MI == 1 && NI == 1 && NPL == 3;
+    v16f small[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) small[0][r] = small[1][r] = 0.f;
 
     // Software pipeline over the 16-wide k steps: the fragments of step s+1 are requested from LDS before the matrix
     // instructions of step s are issued.  At the last step of a K tile the workgroup barrier comes first: it both
     // releases the stage just read (all its reads have completed, they feed the instructions about to be
     // issued) and guarantees that the next stage is filled.
-    constexpr int KS = BK / 16 / KG;              // k steps of a tile per wavefront
+    constexpr int KS = BK / 16;                   // k steps of a tile
     static_assert(KS % 2 == 0, "k steps per tile: even");
     bf16x8 fa[2][MI][NPL], fb[2][NI][NPL];
     auto fetch_frags = [&](int set, int kt, int ks) {
@@ -437,11 +441,11 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) fa[set][i][s] = LA::fragment(st + s * LA::PLANE, wm * WM + i * 32, (kg * KS + ks) * 16, l);
+            for (int s = 0; s < NPL; ++s) fa[set][i][s] = LA::fragment(st + s * LA::PLANE, wm * WM + i * 32, ks * 16, l);
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) fb[set][j][s] = LB::fragment(st + STAGE_A + s * LB::PLANE, wn * WN + j * 32, (kg * KS + ks) * 16, l);
+            for (int s = 0; s < NPL; ++s) fb[set][j][s] = LB::fragment(st + STAGE_A + s * LB::PLANE, wn * WN + j * 32, ks * 16, l);
     };
     // the products of one accumulator keep their order (smallest first); the MI*NI accumulators alternate so that
     // consecutive matrix instructions are independent
@@ -457,8 +461,10 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
                     const int pa = NPL == 3 ? PA3[p] : PA2[p % 3], pb = NPL == 3 ? PB3[p] : PB2[p % 3];
-                    if constexpr (NPL == 3)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i][pa], fb[set][j][pb], acc[i][j], 0, 0, 0);
+                    if constexpr (NPL == 3) {
+                        v16f &c = APART && p + 1 < NPROD ? small[p & 1] : acc[i][j];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i][pa], fb[set][j][pb], c, 0, 0, 0);
+                    }
                     else
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[set][i][pa]),
                                                                            __builtin_bit_cast(f16x8, fb[set][j][pb]), acc[i][j], 0, 0, 0);
@@ -492,17 +498,9 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
             interleave();
         }
     }
-    if constexpr (KG > 1) {
-        static_assert(MI == 1 && NI == 1 && NPL == 3, "one block per wavefront");
-        float *part = reinterpret_cast<float *>(stages) + wave % 4 * 1024 + l;
-        if (kg == 1) {
+    if constexpr (APART) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) part[r * 64] = acc[0][0][r];
-        }
-        __syncthreads();
-        if (kg == 1) return;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][0][r] += part[r * 64];
+        for (int r = 0; r < 16; ++r) acc[0][0][r] += small[0][r] + small[1][r];
     }
     if constexpr (NPL == 2) {
         // one exponent adjustment per element takes both scales off (exact; their sum can leave the exponent range of
@@ -571,7 +569,7 @@ __device__ __forceinline__ void gemm_tn_problem(const GemmDev &g, unsigned char 
 template <int TB>
 inline GemmDev make_tn_dev(const GemmArgs &a)
 {
-    constexpr int BK = tn_bk(TB);
+    constexpr int BK = TN_BK;
     GemmDev g{};
     g.A = a.A; g.lda = a.lda; g.B = a.B; g.ldb = a.ldb; g.C = a.C; g.ldc = a.ldc;
     g.M = a.M; g.N = a.N; g.K = a.K;

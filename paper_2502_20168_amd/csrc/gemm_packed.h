@@ -1235,7 +1235,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     return -1;
 }
 
-// Tiles of 32 rows: launches that leave a workgroup a CU to itself, whose time is a chain of dependent steps rather than
+// Tiles of 32 rows: launches that leave a workgroup a CU to itself (beside reductions: two to a CU, on short stages), whose time is a chain of dependent steps rather than
 // throughput.  All eight wavefronts load, split and multiply.  A stage is 256 k of all rows, double-buffered in LDS, with one meeting of the
 // workgroup per stage; wavefronts that share 32 columns take every KW-th k step, and their partial tiles are added up as they are stored.
 //   The two wavefronts of a SIMD do the same thing at the same time, so what is not interleaved in each of them does not overlap: the
@@ -1247,7 +1247,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
 // multiplied, and now: 1024 x 512 x 1024: 9.4 and 8.5 us; 256 x 512 x 1024: 8.2 and 6.1; 64 x 512 x 1024: 7.2 and 4.9.
 //   A wait counts the requests made behind the one it is for.  So that the compiler finds the same order in every round of the loop, the
 // first stage stands in front of it, the loop has a single way out, and there is no branch on lanes in it.
-// AHEAD: k steps of the weights in flight: four; two beside a reduction, whose sixteen wavefronts leave each 128 registers (short stages
+// AHEAD: k steps of the weights in flight: four; two beside a reduction, where wavefronts have 128 registers (short stages
 // of at most 64 columns: four there too).  No variant spills.  With four on short stages of 128 columns, and the places of all eight
 // steps of a stage kept, those beside a reduction spilled up to 14: forward and gradient pass of 32 x 60 tokens, H = 100, P = 200:
 // 55.0 -> 51.4 us; 16 x 64, 128, 256: 42.0 -> 39.8; 16 x 64, 256, 256: 47.2 -> 46.8.
@@ -1538,8 +1538,7 @@ constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, int epi, int kc)
 
 // One launch carries a product with packed weights and up to two K = T reductions (TNB > 0: their tile is
 // TNB x TNB; absent ones have no slots).  Every problem owns a contiguous range of the slots of every XCD.
-// (a reduction may have more wavefronts than a product; the surplus leaves a product's workgroup at once)
-constexpr int pk_threads(int TNB) { return TNB > 0 ? 64 * (tn_consumers(TNB) + tn_producers(TNB)) : PK_THREADS; }
+static_assert(TN_PRODUCERS + TN_CONSUMERS == PK_PRODUCERS + PK_CONSUMERS, "a launch's workgroups have one size");
 
 // A pointer that was read as a word: to global memory.  (The compiler knows that of the kernel's arguments themselves.  A load from an address that it does not
 // know it of counts against LDS as well as memory, and every wait for one is a wait for all.)
@@ -1563,7 +1562,7 @@ __device__ __forceinline__ void in_global(GemmDev &g)
 }
 
 template <int BM, int BN, int NPL, int EPI, int TNB, int WPE, bool LEFT>
-__global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
+__global__ void __launch_bounds__(PK_THREADS, WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int x = blockIdx.x % 8, q = blockIdx.x / 8, tid = threadIdx.x;
@@ -1579,13 +1578,14 @@ __global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, 
                          "s"(g.by_cpu.mul), "s"(g.by_cpu.shift));
         // (only scans are placed otherwise than in mode 0: left to run time, every product has the code of all modes on its way to the first loads)
         const int tile = EPI < 7 ? x * g.nx + q - g.slot0 : pk_place(g, x, q - g.slot0);
-        if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
+        if (tile >= g.ntm * g.ntn) return;
         const int tm = (int)g.by_ntn(tile), tn = tile - tm * g.ntn;
         auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
             if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             else if constexpr (BM == 32) {
-                if (g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, TNB == 0 || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
-                return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                // (beside reductions long stages only where 32 columns have a single k step per wavefront and short stage)
+                if ((TNB > 0 && BN >= 64) || g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, TNB == 0 || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                if constexpr (TNB == 0 || BN == 32) return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             } else return gemm_pk_tile<BM, NPL, EPI, LEFT>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
         };
         const int missing = __builtin_amdgcn_readfirstlane(run(g, tm, tid, false));
@@ -1686,14 +1686,14 @@ hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArg
     constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI, BM == 32 ? PK32_LONG : PK_BK);
     constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, EPI, PK32_SHORT) : pk;
     constexpr size_t most = pk > tnl ? pk : tnl;
-    const size_t smem = tnl > pk_short ? most : (BM == 32 && ((BN == 64 && WPE == 4 && TNB == 0) || a.K <= PK32_SHORT)) ? pk_short : most;
+    const size_t smem = BM == 32 && ((BN >= 64 && WPE == 4) || a.K <= PK32_SHORT) ? (pk_short > tnl ? pk_short : tnl) : most;
     if (slots <= 0 || slots > 0x7fffffffL / 8) return hipErrorInvalidValue;
     const auto launch = [&](auto left) -> hipError_t {
         auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE, decltype(left)::value>;
         static std::atomic<bool> raised[KERNEL_MAXDEV];
         const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), most, raised);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(pk_threads(TNB)), smem, s, g, t[0], t[1]);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(PK_THREADS), smem, s, g, t[0], t[1]);
         return hipGetLastError();
     };
     // (scans on smaller tiles: launches of at most 4 MiB of states on 32 rows, 32 MiB in the chains of 64)

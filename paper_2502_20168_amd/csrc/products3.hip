@@ -1,5 +1,5 @@
 // Products with packed weights on three bf16 planes per operand, and the reductions over tokens that share their
-// launches (on 64x64x64 tiles where the product is small).
+// launches (on 64x64 tiles where the product is small).
 #include "gemm_packed.h"
 
 namespace ssm {
