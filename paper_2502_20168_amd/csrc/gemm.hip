@@ -121,7 +121,7 @@ size_t gemm_row_scan_desc_bytes(int64_t T, int64_t P, int rows)
 //     116 us; the gate's, 4096 tokens, H = 1024: 92 against 97, but H = 768, 564 workgroups: 67 against 62).
 PkTile product_tile(const GemmArgs &a, const GemmArgs *b, const GemmArgs *c)
 {
-    if ((a.epilogue >= 7 && a.epilogue <= 9) && a.planes == 2) return {a.scan.rows, 128};
+    if ((a.epilogue >= 7) && a.planes == 2) return {a.scan.rows, 128};
     const auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     int64_t items = 0;
     for (const GemmArgs *t : {b, c})
@@ -143,8 +143,8 @@ bool reduction_ok(const GemmArgs &t, int planes)
 bool scan_args_ok(const GemmArgs &a)
 {
     const ScanEpilogue &c = a.scan;
-    if (!c.lam || !c.err || c.L <= 0 || a.N != 2 * c.P || a.M % c.L != 0 || (a.epilogue == 8 && (!c.xsaved || !c.partial))) return false;
-    if (a.epilogue == 9) return a.planes == 2 && c.rows == 64 && c.L <= ROW_SCAN_MAX_TILES * 64 && c.rowmax_out && (c.desc || 64 % c.L == 0);
+    if (!c.lam || !c.err || c.L <= 0 || a.N != 2 * c.P || a.M % c.L != 0 || ((a.epilogue == 8 || a.epilogue == 10) && (!c.xsaved || !c.partial))) return false;
+    if (a.epilogue >= 9) return a.planes == 2 && (a.epilogue == 9 || c.amax_out) && c.rows == 64 && c.L <= ROW_SCAN_MAX_TILES * 64 && c.rowmax_out && (c.desc || 64 % c.L == 0);
     if (a.planes == 3) return c.rows > 0 && c.rows == gemm_row_scan_rows(a.M, c.L, c.P) && (c.desc || c.rows % c.L == 0);
     if ((c.rows != 64 && c.rows != 128) || a.M % c.rows != 0) return false;
     const bool chain = c.L % c.rows == 0 && c.L <= SCAN_MAX_STEPS && (c.desc || c.L == 64);
@@ -166,7 +166,7 @@ hipError_t launch_products(const GemmArgs &a, const GemmArgs *b, const GemmArgs 
     case 4: if (!a.E || !a.E2) return hipErrorInvalidValue; break;
     case 5: if ((a.C2 && !a.diag) || a.N % 2) return hipErrorInvalidValue; break;
     case 6: if (!a.diag || !a.E || !a.C2) return hipErrorInvalidValue; break;
-    case 7: case 8: case 9: if (!scan_args_ok(a)) return hipErrorInvalidValue; break;
+    case 7: case 8: case 9: case 10: if (!scan_args_ok(a)) return hipErrorInvalidValue; break;
     default: return hipErrorInvalidValue;
     }
     return a.planes == 2 ? products_two_planes(a, b, c, tn_first, s) : products_three_planes(a, b, c, tn_first, s);

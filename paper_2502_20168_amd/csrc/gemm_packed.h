@@ -42,7 +42,7 @@ __device__ __forceinline__ int tile_at(int row, int col)
 }
 
 // the resettable scan over the rows of a tile (sequences of any length): row_scan_body
-constexpr bool scans_rows(int planes, int epilogue) { return epilogue == 9 || (planes == 3 && (epilogue == 7 || epilogue == 8)); }
+constexpr bool scans_rows(int planes, int epilogue) { return epilogue >= 9 || (planes == 3 && epilogue >= 7); }
 
 struct PkDev {
     const float *A; long lda;
@@ -600,7 +600,7 @@ struct StoreInputs {
 };
 
 // ---------------------------------------------------------------------------------------------
-// Epilogues 7 and 8 with three planes, 9 with two (forward): the resettable scan over the 32 or 64 consecutive tokens of a tile and its BN / 2 states.  The tokens are
+// Epilogues 7 and 8 with three planes, 9 and 10 (forward, reverse) with two: the resettable scan over the 32 or 64 consecutive tokens of a tile and its BN / 2 states.  The tokens are
 // those of any sequences: where one starts inside the tile nothing flows in (its x0 is put into the element itself), so the length
 // of a sequence need not fit the tile.  Thread (q, c), q < 8, owns the q-th run of 4 or 8 tokens in scan order of state c:
 //   1. pass for zero incoming state; the runs are combined through LDS;
@@ -623,6 +623,10 @@ struct StoreInputs {
 // 32 x 60, 200, 100: 55.0 -> 45.9; 1 x 2048, 128, 64: 46.6 -> 39.4); 14 on 64 rows: 7 % (20 x 300, 500, 250: 182 -> 172; 9 x 997, 128, 140: 97.0 -> 82.7; 100 x 100,
 // 1000, 128: 259 -> 255).  Forward on two planes (64 rows; there the states' row maxima are recorded as well): 24 x 200, 1024, 512: 95.5 -> 90.4; 100 x 100, 512, 512:
 // 106.6 -> 90.2; 300 x 100: 264 -> 240, although products of many tiles alone are a little faster with 128 rows.
+// Reverse on two planes, beside the dC slabs (64 rows; chi's row maxima and its largest magnitude are recorded): chi is written once instead of written, read and written again, and the
+// chain along time is hidden behind the reductions.  Forward and gradient pass with a scan kernel and now: 60 x 100, 512, 512: 198.6 -> 185.9; 9 x 515, 700, 530: 235.7 ->
+// 217.8; 300 x 100, 512, 512: 787 -> 750; 2000 x 5, 512, 512: 345.6 -> 290.6; 24 x 200, 1024, 512: 261.4 -> 261.9 (as much as the scan cost is lost where the product
+// took 128-row tiles); 21 layers: 4 % faster on geometric mean, 0.4 % slower at worst.  The dC slabs beside du instead: 1.2 % slower; their items behind the tiles: 2.8 %.
 // ---------------------------------------------------------------------------------------------
 constexpr int ROW_SCAN_CHUNKS = 8;                            // runs of a tile, threads that share out the tiles before it
 static_assert(ROW_SCAN_MAX_TILES <= ROW_SCAN_CHUNKS * 8, "a thread folds at most eight tiles");
@@ -914,7 +918,7 @@ __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, 
                 for (int i = 0; i < CH; ++i)
                     if (m0 + row_of(i) < g.M) store_state<LEFT>(dst + row_of(i) * a.P, val[i]);
             }
-            if constexpr (MAXIMA) static_assert(ROWS == 64 && BN == 128 && !REV, "rows8_wave_max");
+            if constexpr (MAXIMA) static_assert(ROWS == 64 && BN == 128, "rows8_wave_max");
             const Bits edge = REV ? k.start : k.end;
             float2 *at_edge = REV ? a.dx0 : a.x_last;
             if (edge != 0 && at_edge) {
@@ -933,8 +937,13 @@ __device__ __forceinline__ int row_scan_body(const PkDev &g, const float *tile, 
 #pragma unroll
             for (int i = 0; i < CH; ++i) top[i] = active ? __float_as_uint(fmaxf(fabsf(val[i].x), fabsf(val[i].y))) : 0u;
             const unsigned r = rows8_wave_max(top, c);
-            const int row = m0 + CH * q + rows8_index(c);
+            const int row = m0 + row_of(rows8_index(c));
             if (c < 8 && row < g.M) a.rowmax_out[(size_t)(n0 / BN) * g.M + row] = r;
+            if constexpr (REV) {
+                // and of chi as a whole, for the sums over tokens
+                const unsigned v = wave_max(r);
+                if (c == 0) atomicMax(a.amax_out + (unsigned)(here * NC + q) % ABSMAX_SLOTS, v);
+            }
         }
     }
     if (REV) {
@@ -976,7 +985,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     constexpr int PLANE = BM * S, STAGE = NPL * PLANE;
     constexpr int MI = BM / 32, KS = BK / 16;
     static_assert(PK_BN == 32 * NC && (BM == 64 || BM == 128), "32 columns per consumer");
-    constexpr bool SCANS = (EPI == 7 || EPI == 8) && NPL == 2, ROW_SCANS = ((EPI == 7 || EPI == 8) && NPL == 3) || EPI == 9;
+    constexpr bool SCANS = (EPI == 7 || EPI == 8) && NPL == 2, ROW_SCANS = scans_rows(NPL, EPI), REVERSE = EPI == 8 || EPI == 10;
     constexpr int RC = SCANS ? BM / SCAN_WAVES : 8, FR = SCANS ? BM : 64;      // (scans)
     static_assert(!SCANS || BM >= 64, "scanning tiles have 64 or 128 rows");
     // k steps of the weights in flight: what 128 registers hold
@@ -1104,7 +1113,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
         __syncthreads();
         if constexpr (SCANS) lam = g.scan.lam[min(n0 / 2 + l, g.scan.P - 1)];
         if constexpr (SCANS && EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
-        if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, EPI == 8>(g, row_masks, tid, m0, n0);
+        if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, REVERSE>(g, row_masks, tid, m0, n0);
         else if constexpr (!SCANS) in.request(g, tid, 0, m0, n0);
         __syncthreads();                             // barriers 1 and 2, see below
         __syncthreads();
@@ -1206,7 +1215,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
         if constexpr (SCANS) lam = g.scan.lam[min(n0 / 2 + l, g.scan.P - 1)];
         // (at 128 rows the accumulators leave no registers for the inputs before they are staged)
         if constexpr (SCANS && EPI == 8 && MI < 4) saved = scan_request_saved<RC>(g.scan, wave, l, m0, n0);
-        if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, EPI == 8>(g, row_masks, tid, m0, n0);
+        if constexpr (ROW_SCANS) row_saved = row_scan_request<64, PK_BN, REVERSE>(g, row_masks, tid, m0, n0);
         else if constexpr (!SCANS && MI < 4) in.request(g, tid, 0, m0, n0);
         __syncthreads();                                 // barrier 1: every wavefront has left the K loop, LDS is free
         float *out = reinterpret_cast<float *>(smem_raw);
@@ -1221,9 +1230,9 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     // (producers and consumers together: one copy of the code)
     if constexpr (SCANS) scan_epilogue_body<FR, EPI == 8, LEFT>(g, ScanLds(smem_raw, FR), wave, l, m0, n0, tile, saved, flags, lam);
     else if constexpr (ROW_SCANS) {
-        row_scan_flags<64, EPI == 8>(row_masks, row_scan, g.scan.is_first != nullptr);
-        const RowScanPowers power = row_scan_powers<64, PK_BN, EPI == 8>(row_scan.lam, tid);
-        return row_scan_body<64, PK_BN, 1, EPI == 8, EPI == 9, LEFT>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid,
+        row_scan_flags<64, REVERSE>(row_masks, row_scan, g.scan.is_first != nullptr);
+        const RowScanPowers power = row_scan_powers<64, PK_BN, REVERSE>(row_scan.lam, tid);
+        return row_scan_body<64, PK_BN, 1, REVERSE, EPI >= 9, LEFT>(g, reinterpret_cast<const float *>(smem_raw), reinterpret_cast<float2 *>(smem_raw + BM * PK_BN * 4), tid,
                                                                m0, n0, row_scan.lam, power, row_masks, row_saved, ahead);
     } else {
 #pragma unroll
@@ -1553,7 +1562,7 @@ __device__ __forceinline__ void in_global(PkDev &g)
     in_global(g.A); in_global(g.frag); in_global(g.bexp); in_global(g.C); in_global(g.rows);
     ScanEpilogue &a = g.scan;
     in_global(a.lam); in_global(a.is_first); in_global(a.x0); in_global(a.x_last); in_global(a.xsaved); in_global(a.partial);
-    in_global(a.dx0); in_global(a.desc); in_global(a.err); in_global(a.rowmax_out);
+    in_global(a.dx0); in_global(a.desc); in_global(a.err); in_global(a.rowmax_out); in_global(a.amax_out);
 }
 
 __device__ __forceinline__ void in_global(GemmDev &g)
@@ -1642,8 +1651,8 @@ inline PkDev make_pk_dev(const GemmArgs &a)
     g.c2_rowmax = a.c2_rowmax;
     const auto address = [](const void *p) { return reinterpret_cast<uintptr_t>(p); };
     g.through = a.epilogue >= 7 ? states_through(address(a.C), a.M, a.scan.P) : output_through(address(a.C), address(a.C2), a.M, 4 * a.ldc);
-    if (a.epilogue == 9 || (a.planes == 3 && (a.epilogue == 7 || a.epilogue == 8))) {
-        g.sc_rev = a.epilogue == 8;
+    if (scans_rows(a.planes, a.epilogue)) {
+        g.sc_rev = a.epilogue == 8 || a.epilogue == 10;
         // (mode 7 from 64 row tiles on, where the XCDs get as many within 1/8: 14 shapes of 3000 .. 30000 tokens, gradient pass: 1.6 % faster on geometric
         // mean, 16 x 1000, 256, 256: 201.4 -> 194.9 us, 20 x 300, 500, 250: 171.2 -> 169.1, none slower by more than runs of one side differ)
         g.mode = BM == 64 && g.ntm >= 64 ? 7 : 6;

@@ -25,7 +25,8 @@ hipError_t products_two_planes(const GemmArgs &a, const GemmArgs *b, const GemmA
         }
     }
     switch (a.epilogue) {
-    case 0: SSM_TALL(0, 128);                             // C^H dy with the dC slabs (separate scan kernels)
+    case 0: SSM_TALL(0, 128);                             // C^H dy with the dC slabs (a separate scan kernel)
+    case 10: return SSM_PK(64, 128, 10, 128);             // and its scan
     case 1: SSM_TALL(1, 128);                             // du with the dBbar slabs, and the dC slabs
     case 4: SSM_TALL(4, 128);                             // adjoint of the gate with the dW slabs
     default: return hipErrorInvalidValue;

@@ -99,12 +99,12 @@ struct Layout {
     // the largest magnitude of the saved states, which the reverse scan records on its way); otherwise dC shares the
     // launch of C^H dy.
     SlabPlan dC, dB;
-    // sequences of no whole 128-step pieces, products of more than 64 tiles: two scaled fp16 planes there too, the reverse scan (and the forward one
-    // of sequences of more than 64 tiles) in a kernel of its own (the scan kernels
-    // record the largest magnitude of every token row of x and chi with atomics, the prep launch measures the rest)
+    // sequences of no whole 128-step pieces, products of more than 64 tiles: two scaled fp16 planes there too, the projections scan the rows of their tiles and
+    // record the largest magnitude of every row of x and chi; the scans of sequences of more than 64 tiles in a kernel of their own (which records
+    // them with atomics).  The prep launch measures the rest
     bool planes2_unfused;
     int planes;              // per operand of every product
-    int row_scan;            // tokens per tile of the input projection (and, three planes, of C^H dy), which scans them (no scan kernel), or 0
+    int row_scan;            // tokens per tile of the input projection and of C^H dy, which scan them (no scan kernel), or 0
     PackedLayout w_in, w_out;          // forward: Bbar and C
     PackedLayout w_gx, w_du;           // gradient pass: both transposed
     size_t hdr, lam, adj, xbuf, chi, ticket, desc, dCpart, dBpart, dApart, dDpart, fdesc, fdesc_bytes, total;
@@ -136,18 +136,19 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     // 32 x 100 tokens, H = P = 512, 28-56 % at the others.  With a shorter contraction two planes would be faster as well, by
     // 4-29 % from 4800 tokens on (nothing at 32 x 100, H = P = 256); those shapes keep the exact split into three planes,
     // which holds every element to its own last bit whatever else its row or matrix holds)
-    o.planes2_unfused = !gemm_scan_shape_ok(Bt, L, P) && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) &&
-                        H >= 512 && P >= 512;
-    o.planes = (gemm_scan_shape_ok(Bt, L, P) || o.planes2_unfused) ? 2 : 3;
-    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : o.planes2_unfused && !bwd && L <= 64 * ROW_SCAN_MAX_TILES ? 64 : 0;
+    const bool fused = gemm_scan_shape_ok(Bt, L, P), unfused2 = !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) && H >= 512 && P >= 512;
+    o.planes2_unfused = !fused && unfused2;
+    o.planes = fused || o.planes2_unfused ? 2 : 3;
+    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : o.planes2_unfused && L <= 64 * ROW_SCAN_MAX_TILES ? 64 : 0;
     o.nslab = coldot_slabs((int64_t)T, o.planes);
     o.plan = plan_scan(Bt, L, P, o.planes2_unfused);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));
     o.lam = off; off += up((size_t)P * 8);
-    o.ticket = off; if (!o.row_scan) off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
-    o.desc = off; if (!o.row_scan) off += up(o.plan.desc_bytes);
+    const bool look_back = !o.row_scan || (bwd && o.planes2_unfused);       // (the latter: room only, see below)
+    o.ticket = off; if (look_back) off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
+    o.desc = off; if (look_back) off += up(o.plan.desc_bytes);
     o.adj = o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
     size_t dA_elems = o.plan.partial_elems;
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
@@ -159,7 +160,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.amax_slots = off; off += up((size_t)(PREP_PASS_BLOCKS + 2 * o.amax_cd) * 4);
         o.rowmax = off; off += up(T * (size_t)((H + 63) / 64) * 4);
     }
-    if (gemm_scan_shape_ok(Bt, L, P)) {              // tagged words of a projection that scans its own output
+    if (fused) {                                     // tagged words of a projection that scans its own output
         static_assert(ABSMAX_SLOTS * 4 % ALIGN == 0, "the atomic slots and the tagged words are cleared as one range");
         o.amax_atomic = off; off += 2 * ABSMAX_SLOTS * 4;            // chi, then the saved states (gradient pass)
         o.fdesc_bytes = gemm_scan_desc_bytes(Bt, L, P);
@@ -179,7 +180,7 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.fdesc_bytes = o.row_scan % L == 0 ? 0 : words;
         dA_elems = (T + o.row_scan - 1) / o.row_scan * P;
     }
-    if (gemm_scan_shape_ok(Bt, L, P)) {
+    if (fused) {
         o.dC = o.dB = gemm_plan_slabs(2 * P, H, (int64_t)T, 2, REDUCTION_128x128, 2 * P);
     } else {
         o.dC = gemm_plan_slabs(H, 2 * P, (int64_t)T, 1, reduction_tile(o.planes, gemm_small_pair((int64_t)T, 2 * P)), H);
@@ -198,6 +199,12 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         o.dApart = off; off += up(dA_elems * 8);
         o.dDpart = off; off += up((size_t)o.nslab * H * 4);
         o.adj = off; off += up((size_t)P * sizeof(StateAdjoint));
+    }
+    if (bwd && unfused2) {
+        // What the scan of rows takes (tagged words, row maxima, rows of dAbar) goes on top of what a scan kernel would take, and is added at every length: so a
+        // workspace that holds as many shorter sequences (1024 steps, or 4097, and then 1000) with scan kernels does so with either.  (3 to 5 % more)
+        off += o.row_scan ? up(T * 4) + up(o.plan.partial_elems * 8)
+                          : up(gemm_row_scan_desc_bytes((int64_t)T, P, 64)) + up(T * (size_t)((2 * P + 127) / 128) * 4) + up((T + 63) / 64 * P * 8);
     }
     o.total = off;
     if (bwd && o.planes2_unfused) {
@@ -270,6 +277,10 @@ void zero_ranges(PrepArgs &pa, const Layout &lo, char *ws, bool fused, size_t T)
     if (lo.row_scan) {
         pa.zero[0].p = reinterpret_cast<uint4 *>(ws + lo.fdesc);
         pa.zero[0].n16 = lo.fdesc_bytes / 16;
+        if (lo.planes == 2 && lo.chi) {                  // the gradient pass: the largest magnitude of chi
+            pa.zero[1].p = reinterpret_cast<uint4 *>(ws + lo.amax_atomic);
+            pa.zero[1].n16 = ABSMAX_SLOTS * 4 / 16;
+        }
     }
     if (!fused && !lo.row_scan && lo.plan.nTB > 1) {
         pa.zero[1].p = reinterpret_cast<uint4 *>(ws + lo.ticket);
@@ -420,7 +431,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     const int T = (int)(Bt * L);
     const float *xf = reinterpret_cast<const float *>(x);
 
-    // The same shapes (other lengths: three planes): C^H dy runs the reverse scan on its own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
+    // The same shapes, and other lengths (lo.row_scan): C^H dy runs the reverse scan on its own output tile (chi stored directly, dAbar rows per tile, no scan kernel).
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
     MARK();
     PrepArgs pa{};
@@ -470,9 +481,9 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     g4.M = (int)H; g4.N = (int)(2 * P); g4.K = T; g4.splits = lo.dC.slabs;
     if (two_planes) { g3.amaxA = mx_dy_rows; g4.amaxA = mx_dy; g4.amaxB = mx_x; }
     if (fused || lo.row_scan) {
-        // the product scans its own tiles; with two planes the dC slabs wait for the next launch, where the largest
+        // the product scans its own tiles; with two planes and fused the dC slabs wait for the next launch, where the largest
         // magnitude of the saved states (recorded here, as the scan reads them) is known
-        g3.epilogue = 8;
+        g3.epilogue = two_planes && !fused ? 10 : 8;
         g3.scan.lam = lam; g3.scan.is_first = is_first;
         g3.scan.x0 = reinterpret_cast<const float2 *>(x0);
         g3.scan.xsaved = reinterpret_cast<const float2 *>(x); g3.scan.partial = dApart;
@@ -480,7 +491,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         g3.scan.desc = reinterpret_cast<unsigned long long *>(ws + lo.fdesc); g3.scan.err = &hdr->err;
         g3.scan.L = (int)L; g3.scan.P = (int)P;
         g3.scan.rows = fused ? gemm_scan_rows(T, L, P, true) : lo.row_scan; g3.scan.spin_limit = fused ? spin_limit() : std::min(spin_limit(), ROW_SCAN_POLLS);
-        if (two_planes) { g3.scan.amax_out = am_atomic; g3.scan.xmax_out = am_xsaved; g3.scan.rowmax_out = rowpart; }
+        if (two_planes) { g3.scan.amax_out = am_atomic; g3.scan.xmax_out = fused ? am_xsaved : nullptr; g3.scan.rowmax_out = rowpart; }
     }
     // (otherwise dC needs only dy and the saved states: it shares the launch)
     HIP_TRY(fused ? launch_product(g3, s) : launch_products(g3, &g4, nullptr, lo.dC.first, s));

@@ -23,7 +23,7 @@ namespace ssm {
 //     6: as 1, and C2 = GELU(C) (output projection that feeds the half-GLU gate);
 //     7: the resettable scan over the rows of the output tile (see ScanEpilogue): C = states;
 //     8: the reverse-time scan of the gradient pass over the rows of the output tile: C = chi;
-//     9: as 7 with two planes and sequences of any length;
+//     9, 10: as 7 and 8 with two planes and sequences of any length;
 //   a reduction over tokens, C[m,n] = sum_k A[k,m] B[k,n]  (gemm_kernel.h).  splits > 1: split z covers a
 //     contiguous K range and writes its own slab C + z*M*ldc; the caller reduces the slabs.
 // ---------------------------------------------------------------------------------------------
@@ -51,13 +51,13 @@ struct ScanEpilogue {
     const uint8_t *is_first;      // [Bt*L] or null
     const float2 *x0;             // [Bt, P] or null
     float2 *x_last;               // [Bt, P] or null (forward)
-    const float2 *xsaved;         // [Bt, L, P] states of the forward pass (reverse, epilogue 8)
+    const float2 *xsaved;         // [Bt, L, P] states of the forward pass (reverse, epilogues 8 and 10)
     float2 *partial;              // [ceil(Bt * L / rows), P] per-tile rows of dAbar (reverse)
     float2 *dx0;                  // [Bt, P] or null (reverse)
-    unsigned long long *desc;     // [M / 64 * ceil(N/128) * 64][2] tagged aggregate words, three planes: [ceil(M / rows)][2][P]; zero on entry
+    unsigned long long *desc;     // [M / 64 * ceil(N/128) * 64][2] tagged aggregate words, scans of rows: [ceil(M / rows)][2][P]; zero on entry
     unsigned *err;                // set when a bounded wait gives up
-    unsigned *amax_out;           // [ABSMAX_SLOTS] or null: atomic maximum of the magnitudes stored to C, zero on entry
-    unsigned *xmax_out;           // [ABSMAX_SLOTS] or null (reverse, with amax_out): atomic maximum of the magnitudes of xsaved
+    unsigned *amax_out;           // [ABSMAX_SLOTS] or null (epilogue 10: not): atomic maximum of the magnitudes stored to C, zero on entry
+    unsigned *xmax_out;           // [ABSMAX_SLOTS] or null (epilogue 8, with amax_out): atomic maximum of the magnitudes of xsaved
     unsigned *rowmax_out;         // [ceil(N/128), M] or null: per column tile and row, the largest magnitude stored to C
     int L, P;
     FastDiv by_L;                 // set by the launch
@@ -79,7 +79,7 @@ struct GemmArgs {
     int epilogue; const uint8_t *rowflag;
     const float *E2; float *C2;                      // epilogues 3, 4, 6 (gate), pitch lde / ldc; 5
     int M, N, K, splits;
-    ScanEpilogue scan;                               // epilogues 7 and 8
+    ScanEpilogue scan;                               // epilogues 7 to 10
     AbsMax amaxA, amaxB;                             // largest magnitudes of A (products: of its rows) and B when known
     unsigned *c2_rowmax;                             // epilogue 6: [ceil(N/128)][M] words, the largest magnitude of every
                                                      // row of C2 per piece of 128 columns; or null
@@ -97,8 +97,8 @@ bool gemm_scan_shape_ok(int64_t Bt, int64_t L, int64_t P);
 int gemm_scan_rows(int64_t T, int64_t L, int64_t P, bool reverse);
 // bytes of tagged words epilogues 7 and 8 need (zeroed before the launch)
 size_t gemm_scan_desc_bytes(int64_t Bt, int64_t L, int64_t P);
-// the same products with three planes scan the rows of their tiles, sequences of any length: tokens per tile, 32 or 64, 0 where
-// they do not; and the bytes of tagged words
+// the same products scan the rows of their tiles, sequences of any length (epilogues 7 and 8 with three planes, 9 and 10 on 64 rows with two): tokens per tile with
+// three planes, 32 or 64, 0 where they do not; and the bytes of tagged words
 int gemm_row_scan_rows(int64_t T, int64_t L, int64_t P);
 size_t gemm_row_scan_desc_bytes(int64_t T, int64_t P, int rows);
 // One launch: a product with packed weights and up to two reductions over tokens whose inputs are ready at the same
