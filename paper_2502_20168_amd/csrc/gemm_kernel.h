@@ -319,7 +319,8 @@ __device__ __forceinline__ unsigned lane_xor_max(unsigned v)
 //   Beside small products too: with eight wavefronts of either kind and 64 k per K tile an item of 64 x 64 took half as long, but every workgroup of the launch
 // then had a CU to itself, products of eight wavefronts included, and launches of 257 to 512 workgroups took two rounds.  Forward and gradient pass, with
 // that and now: 8 x 250 tokens, H = P = 180: 60.1 -> 52.9 us; 20 x 64, 300, 300: 73.0 -> 62.2; 16 x 33, 64, 64: 32.2 -> 26.3; block of 8 x 250, 180, 180:
-// 83.3 -> 72.6; 18 shapes 5.5 % faster on geometric mean; 16 x 64, 256, 256 (256 workgroups) the same, 8 x 1000, 128, 256 (items of 1000 tokens) 1.7 % slower.
+// 83.3 -> 72.6; 18 shapes 5.5 % faster on geometric mean; 16 x 64, 256, 256 (256 workgroups) the same.  Launches that fit one round all the same (products3.hip) keep 64 k per K
+// tile, a CU to a workgroup and two register sets: with 32 they were 2 to 7 % slower than that (8 x 1000, 128, 256: 84.3 us with sixteen wavefronts, 87.2 and now 85.4).
 // ---------------------------------------------------------------------------------------------
 constexpr int TN_STAGES = 2;
 constexpr int TN_PRODUCERS = 4, TN_CONSUMERS = 4, TN_BK = 32;
@@ -328,14 +329,14 @@ constexpr int TN_PRODUCERS = 4, TN_CONSUMERS = 4, TN_BK = 32;
 constexpr int tn_rows(int TB) { return TB == 64 ? 64 : 128; }
 constexpr int tn_cols(int TB) { return TB == 128 ? 128 : 64; }
 // (stages, two scales)
-constexpr size_t tn_lds_bytes(int TB, int NPL) { return (size_t)TN_STAGES * NPL * TN_BK * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }
+constexpr size_t tn_lds_bytes(int TB, int NPL, int BK) { return (size_t)TN_STAGES * NPL * BK * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }
 
-template <int TB, int NPL, int EDGE>
+template <int TB, int NPL, int EDGE, int BK>
 __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, int m0, int n0, int z, int kbeg, int kend, int tid)
 {
-    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), BK = TN_BK, NS = TN_STAGES, NC = TN_CONSUMERS, NP = TN_PRODUCERS, PT = 64 * NP;
+    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), NS = TN_STAGES, NC = TN_CONSUMERS, NP = TN_PRODUCERS, PT = 64 * NP;
     // K tiles of global loads in flight per producer (128 x 128 tiles: 3, 4 and 6 measured 1-5 % slower)
-    constexpr int PF = TB == 64 ? 3 : 2;
+    constexpr int PF = TB == 64 && BK == TN_BK ? 3 : 2;
     using LA = SplitLoader<TM, BK, PT, NPL>;
     using LB = SplitLoader<TN, BK, PT, NPL>;
     static_assert(NPL == 2 || NPL == 3, "three bf16 planes or two scaled fp16 planes per operand");
@@ -540,7 +541,7 @@ __device__ __forceinline__ void tn_place(const GemmDev &g, int x, int q, int &z,
     else { z = d; tile = rest; }                                                  // par = tiles
 }
 
-template <int TB, int NPL>
+template <int TB, int NPL, int BK>
 __device__ __forceinline__ void gemm_tn_problem(const GemmDev &g, unsigned char *smem, int x, int q, int tid)
 {
     int z, tile;
@@ -558,11 +559,11 @@ __device__ __forceinline__ void gemm_tn_problem(const GemmDev &g, unsigned char 
             if (row < g.M && col < g.N) Cz[(long)row * g.ldc + col] = 0.f;
         }
     } else if (m0 + TM <= g.M && n0 + TN <= g.N) {
-        gemm_tn_tile<TB, NPL, 0>(g, stages, m0, n0, z, kbeg, kend, tid);
+        gemm_tn_tile<TB, NPL, 0, BK>(g, stages, m0, n0, z, kbeg, kend, tid);
     } else if (g.M >= 4 && g.N >= 4) {
-        gemm_tn_tile<TB, NPL, 1>(g, stages, m0, n0, z, kbeg, kend, tid);
+        gemm_tn_tile<TB, NPL, 1, BK>(g, stages, m0, n0, z, kbeg, kend, tid);
     } else {
-        gemm_tn_tile<TB, NPL, 2>(g, stages, m0, n0, z, kbeg, kend, tid);
+        gemm_tn_tile<TB, NPL, 2, BK>(g, stages, m0, n0, z, kbeg, kend, tid);
     }
 }
 

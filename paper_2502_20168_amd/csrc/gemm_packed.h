@@ -1244,7 +1244,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     return -1;
 }
 
-// Tiles of 32 rows: launches that leave a workgroup a CU to itself (beside reductions: two to a CU, on short stages), whose time is a chain of dependent steps rather than
+// Tiles of 32 rows: launches that leave a workgroup a CU to itself (beside reductions: two to a CU, on short stages, where one would be slower: products3.hip), whose time is a chain of dependent steps rather than
 // throughput.  All eight wavefronts load, split and multiply.  A stage is 256 k of all rows, double-buffered in LDS, with one meeting of the
 // workgroup per stage; wavefronts that share 32 columns take every KW-th k step, and their partial tiles are added up as they are stored.
 //   The two wavefronts of a SIMD do the same thing at the same time, so what is not interleaved in each of them does not overlap: the
@@ -1592,9 +1592,10 @@ __global__ void __launch_bounds__(PK_THREADS, WPE) gemm_pk_kernel(PkDev g, GemmD
         auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
             if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             else if constexpr (BM == 32) {
-                // (beside reductions long stages only where 32 columns have a single k step per wavefront and short stage)
-                if ((TNB > 0 && BN >= 64) || g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, TNB == 0 || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
-                if constexpr (TNB == 0 || BN == 32) return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, TNB == 0 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                // (two to a CU beside reductions: long stages only where 32 columns have a single k step per wavefront and short stage)
+                constexpr bool ALONE = TNB == 0 || WPE == 2;
+                if ((!ALONE && BN >= 64) || g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, ALONE || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                if constexpr (ALONE || BN == 32) return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, ALONE ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             } else return gemm_pk_tile<BM, NPL, EPI, LEFT>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
         };
         const int missing = __builtin_amdgcn_readfirstlane(run(g, tm, tid, false));
@@ -1630,7 +1631,7 @@ __global__ void __launch_bounds__(PK_THREADS, WPE) gemm_pk_kernel(PkDev g, GemmD
 #pragma unroll
         for (size_t i = 0; i < sizeof(GemmDev) / 8; ++i) own.w[i] = args[i];
         in_global(own.t);
-        gemm_tn_problem<TNB, NPL>(own.t, smem_raw, x, q - own.t.slot0, tid);
+        gemm_tn_problem<TNB, NPL, WPE == 2 ? 2 * TN_BK : TN_BK>(own.t, smem_raw, x, q - own.t.slot0, tid);
     }
 }
 
@@ -1691,7 +1692,7 @@ hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArg
         }
     }
     if (tn_first) { g.slot0 = (int)slots; slots += g.nx; }
-    constexpr size_t tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL) : 0;
+    constexpr size_t tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL, WPE == 2 ? 2 * TN_BK : TN_BK) : 0;
     constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI, BM == 32 ? PK32_LONG : PK_BK);
     constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, EPI, PK32_SHORT) : pk;
     constexpr size_t most = pk > tnl ? pk : tnl;

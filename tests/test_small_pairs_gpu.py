@@ -15,6 +15,8 @@ SHAPES = [
     (1, 31, 70, 40), (1, 32, 64, 64), (1, 33, 66, 34),       # fewer tokens than a K tile, one, one more
     (8, 1000, 128, 256),                                   # items of 1000 tokens
     (3, 100, 1000, 1000),                                  # tiles in three columns and more, one slab
+    # one workgroup per compute unit, K tiles of 64 tokens: fewer, one more and a half, contractions at the line and beside it, a round of items and one of tiles
+    (1, 31, 460, 256), (1, 65, 448, 224), (3, 32, 447, 223), (5, 97, 513, 30), (2, 100, 1024, 512), (32, 250, 128, 225),
 ]
 
 
