@@ -2,7 +2,7 @@
 // step.  A pass at the small shapes is a handful of kernels of 2-5 us each, and marshalling it in Python (attribute
 // checks of a dozen tensors, an allocation per output, the current stream, ctypes conversions) took 12-15 us per call, as
 // long as the kernels ran.  Measured per call, host time: lambda-return and its gradient 24.7 -> 8.7 us, one ssm_step
-// 17.3 -> 7.8 us, forward of a 2 x 64 x 32 x 32 layer 29.3 -> 14.3 us; about 3 us of it per kernel launch either way.
+// 17.3 -> 7.8 us, forward of a 2 x 64 x 32 x 32 layer (three launches then) 29.3 -> 14.3 us; about 3 us of it per kernel launch either way.
 //
 // Contract with binding.py: every function takes positional arguments only and returns
 //   the outputs (a tensor, a tuple or a dict) when the call was made and succeeded,
