@@ -46,19 +46,25 @@ ssm_status ssm_scan_bwd_profiled(const ssm_c64 *Lambda, const ssm_c64 *B, const 
 /* What ssm_scan_fwd / ssm_scan_bwd would launch for a shape: host logic only, no GPU call.  Writes
  * SSM_PLAN_FIELDS int32 values to the HOST array out:
  *   [0] 1 when the input projection and C^H dy scan their own output tiles on two planes (no scan kernel); 0 otherwise, also where
- *       such products scan the rows of their tiles, sequences of any length (three planes; forward also two)
+ *       such products scan the rows of their tiles, sequences of any length
  *   [1] planes per operand of the layer's products: 2 (scaled fp16) or 3 (bf16)
  *   [2] K slabs of dC, [3] K slabs of dBbar
  *   [4] gradient pass: 3 = du, dBbar slabs and dC slabs in one launch; 2 = two launches of two products
  *   [5] 1 when the slab work items take the first slots of the launch of [4] == 3
  *   [6], [7] the same for the launches of C^H dy with dC and of du with dBbar when [4] == 2
  *   [8], [9], [10] tile of the launch of the input projection, of the output projection and of du, as
- *       1024 x rows + columns (the forward pass of at most 64 columns, 64 states and 64 steps per sequence on three planes is
- *       one launch of its own up to 512 workgroups of 64 tokens; [8] and [9] are the tiles it would have otherwise)
+ *       1024 x rows + columns (a forward pass in one launch, see ssm_plan_launches, has neither of the first two: [8] and [9] are
+ *       the tiles of the three launches in its place)
  *   [11] workgroups along time of the scan kernels (1: no look-back; unused where products scan their tiles)
  * Returns SSM_ERR_INVALID_ARG / SSM_ERR_UNSUPPORTED for shapes the library does not take.           */
 #define SSM_PLAN_FIELDS 12
 ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_t *out /* host */);
+
+/* How many kernels ssm_scan_fwd and ssm_scan_bwd launch for a shape, written to the HOST array out: host logic only.
+ *   [0] forward: 1 (a narrow layer over short sequences), 3 (the input projection scans its tiles) or 4 (a scan kernel)
+ *   [1] gradient pass: 4 (C^H dy scans its tiles) or 5 (a scan kernel)
+ * Errors as for ssm_plan_describe.                                                                   */
+ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_t *out /* host, [2] */);
 
 #ifdef __cplusplus
 }

@@ -13,7 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Dict, Optional
+from typing import Dict, Optional, Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libssmscan.so")
@@ -37,7 +37,8 @@ EXPORTS = ("ssm_strerror", "ssm_version", "ssm_workspace_bytes", "ssm_discretize
            "ssm_scan_bwd_profiled", "ssm_workspace_status", "ssm_step_plan_bytes", "ssm_step_prepare", "ssm_step",
            "ssm_step_bwd", "ssm_lambda_return", "ssm_lambda_return_bwd", "ssm_half_glu_workspace_bytes", "ssm_half_glu_fwd",
            "ssm_half_glu_bwd", "ssm_block_workspace_bytes", "ssm_block_fwd", "ssm_block_bwd", "ssm_set_spin_limit",
-           "ssm_scan_states_noalloc", "ssm_scan_states_noalloc_status", "ssm_plan_describe")
+           "ssm_scan_states_noalloc", "ssm_scan_states_noalloc_status", "ssm_plan_describe",
+           "ssm_plan_launches")
 
 _lib = None
 _native = None
@@ -619,6 +620,18 @@ def ssm_plan_describe(Bt: int, L: int, H: int, P: int) -> Dict[str, int]:
     if rc != SSM_OK:
         raise SsmError(rc, "ssm_plan_describe")
     return dict(zip(PLAN_FIELD_NAMES, [int(v) for v in out]))
+
+
+def ssm_plan_launches(Bt: int, L: int, H: int, P: int) -> Tuple[int, int]:
+    """How many kernels ssm_scan_fwd and ssm_scan_bwd launch for a shape (host logic only, needs no GPU)."""
+    out = (ctypes.c_int32 * 2)()
+    fn = lib().ssm_plan_launches
+    fn.restype = ctypes.c_int
+    fn.argtypes = [_i64, _i64, _i64, _i64, ctypes.POINTER(ctypes.c_int32)]
+    rc = fn(Bt, L, H, P, out)
+    if rc != SSM_OK:
+        raise SsmError(rc, "ssm_plan_launches")
+    return out[0], out[1]
 
 
 def ssm_workspace_status(workspace, stream=None) -> int:

@@ -288,6 +288,9 @@ void zero_ranges(PrepArgs &pa, const Layout &lo, char *ws, bool fused, size_t T)
     }
 }
 
+// a narrow layer over short sequences
+inline bool fwd_is_one_launch(const Layout &lo, int64_t Bt, int64_t L, int64_t H, int64_t P) { return lo.planes == 3 && narrow_fwd_shape(Bt, L, H, P); }
+
 // The S5 block: the layer's forward pass prepares the gate's product on its way -- W goes into fragment order in the
 // prep launch, and with two planes the rows of GELU(y) are measured where the output projection stores it.
 struct GatePrep { unsigned *x1_rowmax; const float *W; PackJob w; };
@@ -315,8 +318,7 @@ ssm_status run_fwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
     float2 *xs = x ? reinterpret_cast<float2 *>(x) : reinterpret_cast<float2 *>(ws + lo.xbuf);
     const int T = (int)(Bt * L);
 
-    if (lo.planes == 3 && narrow_fwd_shape(Bt, L, H, P)) {
-        // a narrow layer over short sequences: one launch
+    if (fwd_is_one_launch(lo, Bt, L, H, P)) {
         MARK();
         NarrowFwd n{};
         n.Lambda = reinterpret_cast<const float2 *>(Lambda); n.B = reinterpret_cast<const float2 *>(B); n.C = reinterpret_cast<const float2 *>(C);
@@ -676,6 +678,20 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     out[9] = tile(product_tile(o, nullptr, nullptr));
     out[10] = tile(product_tile(du, &dB, fused ? &dC : nullptr));
     out[11] = lo.plan.nTB;
+    return SSM_OK;
+}
+
+ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_t *out)
+{
+    if (!out) return SSM_ERR_INVALID_ARG;
+    const bool fused = gemm_scan_shape_ok(Bt, L, P);
+    Layout lo;
+    ssm_status st = make_layout(Bt, L, H, P, false, lo);
+    if (st != SSM_OK) return st;
+    out[0] = fwd_is_one_launch(lo, Bt, L, H, P) ? 1 : fused || lo.row_scan ? 3 : 4;
+    st = make_layout(Bt, L, H, P, true, lo);
+    if (st != SSM_OK) return st;
+    out[1] = fused || lo.row_scan ? 4 : 5;
     return SSM_OK;
 }
 
