@@ -62,9 +62,9 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
 
 /* How many kernels ssm_scan_fwd and ssm_scan_bwd launch for a shape, written to the HOST array out: host logic only.
  *   [0] forward: 1 (a narrow layer over short sequences), 3 (the input projection scans its tiles) or 4 (a scan kernel)
- *   [1] gradient pass: 4 (C^H dy scans its tiles) or 5 (a scan kernel)
+ *   [1] gradient pass in a workspace of ws_bytes: 4 (C^H dy scans its tiles), 5 (a scan kernel) or 0 (refused: too small)
  * Errors as for ssm_plan_describe.                                                                   */
-ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_t *out /* host, [2] */);
+ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, size_t ws_bytes, int32_t *out /* host, [2] */);
 
 #ifdef __cplusplus
 }

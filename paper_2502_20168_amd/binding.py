@@ -622,13 +622,16 @@ def ssm_plan_describe(Bt: int, L: int, H: int, P: int) -> Dict[str, int]:
     return dict(zip(PLAN_FIELD_NAMES, [int(v) for v in out]))
 
 
-def ssm_plan_launches(Bt: int, L: int, H: int, P: int) -> Tuple[int, int]:
-    """How many kernels ssm_scan_fwd and ssm_scan_bwd launch for a shape (host logic only, needs no GPU)."""
+def ssm_plan_launches(Bt: int, L: int, H: int, P: int, ws_bytes: Optional[int] = None) -> Tuple[int, int]:
+    """How many kernels ssm_scan_fwd and ssm_scan_bwd launch for a shape, the gradient pass in a workspace of ws_bytes (0: it refuses;
+    default: of ssm_workspace_bytes).  Host logic only, needs no GPU."""
+    if ws_bytes is None:
+        ws_bytes = ssm_workspace_bytes(Bt, L, H, P, True)
     out = (ctypes.c_int32 * 2)()
     fn = lib().ssm_plan_launches
     fn.restype = ctypes.c_int
-    fn.argtypes = [_i64, _i64, _i64, _i64, ctypes.POINTER(ctypes.c_int32)]
-    rc = fn(Bt, L, H, P, out)
+    fn.argtypes = [_i64, _i64, _i64, _i64, _sz, ctypes.POINTER(ctypes.c_int32)]
+    rc = fn(Bt, L, H, P, ws_bytes, out)
     if rc != SSM_OK:
         raise SsmError(rc, "ssm_plan_launches")
     return out[0], out[1]

@@ -127,7 +127,8 @@ ssm_status check_dims(int64_t Bt, int64_t L, int64_t H, int64_t P)
     return SSM_OK;
 }
 
-ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, Layout &o)
+// rows = false: a scan kernel in the gradient pass on two planes also where C^H dy could scan the rows of its tiles
+ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, Layout &o, bool rows = true)
 {
     ssm_status st = check_dims(Bt, L, H, P);
     if (st != SSM_OK) return st;
@@ -136,19 +137,18 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
     // 32 x 100 tokens, H = P = 512, 28-56 % at the others.  With a shorter contraction two planes would be faster as well, by
     // 4-29 % from 4800 tokens on (nothing at 32 x 100, H = P = 256); those shapes keep the exact split into three planes,
     // which holds every element to its own last bit whatever else its row or matrix holds)
-    const bool fused = gemm_scan_shape_ok(Bt, L, P), unfused2 = !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) && H >= 512 && P >= 512;
-    o.planes2_unfused = !fused && unfused2;
+    const bool fused = gemm_scan_shape_ok(Bt, L, P);
+    o.planes2_unfused = !fused && !gemm_small_pair((int64_t)T, 2 * P) && !gemm_small_pair((int64_t)T, H) && H >= 512 && P >= 512;
     o.planes = fused || o.planes2_unfused ? 2 : 3;
-    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : o.planes2_unfused && L <= 64 * ROW_SCAN_MAX_TILES ? 64 : 0;
+    o.row_scan = o.planes == 3 ? gemm_row_scan_rows((int64_t)T, L, P) : o.planes2_unfused && (rows || !bwd) && L <= 64 * ROW_SCAN_MAX_TILES ? 64 : 0;
     o.nslab = coldot_slabs((int64_t)T, o.planes);
     o.plan = plan_scan(Bt, L, P, o.planes2_unfused);
     if (o.plan.nblocks > 0x7fffffffLL) return SSM_ERR_UNSUPPORTED;
     size_t off = 0;
     o.hdr = off; off += up(sizeof(WsHeader));
     o.lam = off; off += up((size_t)P * 8);
-    const bool look_back = !o.row_scan || (bwd && o.planes2_unfused);       // (the latter: room only, see below)
-    o.ticket = off; if (look_back) off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
-    o.desc = off; if (look_back) off += up(o.plan.desc_bytes);
+    o.ticket = off; if (!o.row_scan) off += up(o.plan.ticket_bytes);       // tickets and descriptors are contiguous
+    o.desc = off; if (!o.row_scan) off += up(o.plan.desc_bytes);
     o.adj = o.xbuf = o.chi = o.dCpart = o.dBpart = o.dApart = o.dDpart = o.fdesc = o.fdesc_bytes = 0;
     size_t dA_elems = o.plan.partial_elems;
     o.amax_atomic = o.amax_slots = o.rowmax = o.rowpart = 0; o.amax_cd = o.row_parts = 0;
@@ -173,10 +173,12 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         const size_t per_tile = (size_t)(Bt * L / gemm_scan_rows(Bt * L, L, P, true)) * P;  // one dAbar row per scanning tile
         if (per_tile > dA_elems) dA_elems = per_tile;
     }
+    size_t shared_words = 0;         // in the place of the dBbar slabs, which are written in the launch after the scan
     if (o.row_scan) {
         // (reserved also where a tile holds whole sequences and nothing is handed over, so that a workspace holds shorter sequences as well)
         const size_t words = gemm_row_scan_desc_bytes((int64_t)T, P, o.row_scan);
-        o.fdesc = off; off += up(words);
+        if (bwd && o.planes == 2) shared_words = words;
+        else { o.fdesc = off; off += up(words); }
         o.fdesc_bytes = o.row_scan % L == 0 ? 0 : words;
         dA_elems = (T + o.row_scan - 1) / o.row_scan * P;
     }
@@ -195,16 +197,11 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         add_packed(off, o.w_du, H, 2 * P, o.planes);
         o.chi = off; off += up(T * P * 8);
         o.dCpart = off; off += up((size_t)o.dC.slabs * 2 * P * H * 4);
-        o.dBpart = off; off += up((size_t)o.dB.slabs * 2 * P * H * 4);
+        o.dBpart = off; off += up(std::max((size_t)o.dB.slabs * 2 * P * H * 4, shared_words));
+        if (shared_words) o.fdesc = o.dBpart;
         o.dApart = off; off += up(dA_elems * 8);
         o.dDpart = off; off += up((size_t)o.nslab * H * 4);
         o.adj = off; off += up((size_t)P * sizeof(StateAdjoint));
-    }
-    if (bwd && unfused2) {
-        // What the scan of rows takes (tagged words, row maxima, rows of dAbar) goes on top of what a scan kernel would take, and is added at every length: so a
-        // workspace that holds as many shorter sequences (1024 steps, or 4097, and then 1000) with scan kernels does so with either.  (3 to 5 % more)
-        off += o.row_scan ? up(T * 4) + up(o.plan.partial_elems * 8)
-                          : up(gemm_row_scan_desc_bytes((int64_t)T, P, 64)) + up(T * (size_t)((2 * P + 127) / 128) * 4) + up((T + 63) / 64 * P * 8);
     }
     o.total = off;
     if (bwd && o.planes2_unfused) {
@@ -214,7 +211,23 @@ ssm_status make_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, La
         if (st != SSM_OK) return st;
         o.total = std::max(o.total, fwd.total);
     }
+    if (bwd && o.planes2_unfused && o.row_scan) {
+        // (never less than with a scan kernel, so that a workspace holds as many shorter sequences: see gradient_layout)
+        Layout kernel;
+        st = make_layout(Bt, L, H, P, true, kernel, false);
+        if (st != SSM_OK) return st;
+        o.total = std::max(o.total, kernel.total);
+    }
     return SSM_OK;
+}
+
+// The gradient pass in a workspace of ws_bytes.  On two planes the scan of rows takes up to 2.4 % more than a scan kernel, 0.2 % at the median of 1300 shapes (16
+// bytes per state and 64 tokens that find no room among the dBbar slabs, 8 of dAbar, a row maximum per 128 columns).  A workspace that holds the scan kernel's form only, say
+// one of 24 x 4096 steps, 512, 512, whose caller goes on with 24 x 4095, runs that: 60 x 100 tokens, 512, 512: 136 us instead of 121.
+ssm_status gradient_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, size_t ws_bytes, Layout &o)
+{
+    const ssm_status st = make_layout(Bt, L, H, P, true, o);
+    return st == SSM_OK && ws_bytes < o.total && o.planes2_unfused && o.row_scan ? make_layout(Bt, L, H, P, true, o, false) : st;
 }
 
 // pieces of the pass that measures the largest magnitude of n floats (each workgroup takes whole
@@ -412,7 +425,7 @@ ssm_status run_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 *C, co
         !dD || !dlog_delta)
         return SSM_ERR_INVALID_ARG;
     Layout lo;
-    ssm_status st = make_layout(Bt, L, H, P, true, lo);
+    ssm_status st = gradient_layout(Bt, L, H, P, ws_bytes, lo);
     if (st != SSM_OK) return st;
     if (misaligned(Lambda, 8) || misaligned(B, 8) || misaligned(C, 8) || misaligned(D, 4) ||
         misaligned(log_delta, 4) || misaligned(u, 4) || misaligned(x, 8) || misaligned(dy, 4) ||
@@ -681,7 +694,7 @@ ssm_status ssm_plan_describe(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     return SSM_OK;
 }
 
-ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_t *out)
+ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, size_t ws_bytes, int32_t *out)
 {
     if (!out) return SSM_ERR_INVALID_ARG;
     const bool fused = gemm_scan_shape_ok(Bt, L, P);
@@ -689,9 +702,9 @@ ssm_status ssm_plan_launches(int64_t Bt, int64_t L, int64_t H, int64_t P, int32_
     ssm_status st = make_layout(Bt, L, H, P, false, lo);
     if (st != SSM_OK) return st;
     out[0] = fwd_is_one_launch(lo, Bt, L, H, P) ? 1 : fused || lo.row_scan ? 3 : 4;
-    st = make_layout(Bt, L, H, P, true, lo);
+    st = gradient_layout(Bt, L, H, P, ws_bytes, lo);
     if (st != SSM_OK) return st;
-    out[1] = fused || lo.row_scan ? 4 : 5;
+    out[1] = ws_bytes < lo.total ? 0 : fused || lo.row_scan ? 4 : 5;
     return SSM_OK;
 }
 
@@ -863,10 +876,10 @@ struct BlockLayout {
     // forward: the gate's W in fragment order; with two planes the rows of GELU(y) in pieces of 128 columns
     int gate_planes, row_parts; PackedLayout w; size_t x1_rowmax;
 };
-bool make_block_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, BlockLayout &o)
+bool make_block_layout(int64_t Bt, int64_t L, int64_t H, int64_t P, bool bwd, BlockLayout &o, bool rows = true)
 {
     Layout lo;
-    if (make_layout(Bt, L, H, P, bwd, lo) != SSM_OK) return false;
+    if (make_layout(Bt, L, H, P, bwd, lo, rows) != SSM_OK) return false;
     const size_t TH = up((size_t)Bt * L * H * 4);
     size_t off = 0;
     o.ssm = off; off += up(lo.total);
@@ -936,6 +949,8 @@ ssm_status ssm_block_bwd(const ssm_c64 *Lambda, const ssm_c64 *B, const ssm_c64 
     if (st != SSM_OK) return st;
     BlockLayout bl;
     if (!make_block_layout(Bt, L, H, P, true, bl)) return SSM_ERR_UNSUPPORTED;
+    // (the layer's part may be what its form with a scan kernel takes: see gradient_layout)
+    if (ws_bytes < bl.total && !make_block_layout(Bt, L, H, P, true, bl, false)) return SSM_ERR_UNSUPPORTED;
     if (!workspace || misaligned(workspace, ALIGN) || ws_bytes < bl.total) return SSM_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace);
     float *dypre = reinterpret_cast<float *>(ws + bl.dypre);
