@@ -316,27 +316,26 @@ __device__ __forceinline__ unsigned lane_xor_max(unsigned v)
 // wavefront.  Two LDS stages: in iteration kt the producers fill the stage of tile kt+1 while the consumers work
 // on tile kt, with one workgroup barrier per K tile.  128 x 128 tiles (three planes 128 x 64), or 64 x 64 where the products of
 // the launch are small; two workgroups share a CU, so that one's first loads and stores overlap the other's K loop.
-//   Beside small products too: with eight wavefronts of either kind and 64 k per K tile an item of 64 x 64 took half as long, but every workgroup of the launch
-// then had a CU to itself, products of eight wavefronts included, and launches of 257 to 512 workgroups took two rounds.  Forward and gradient pass, with
-// that and now: 8 x 250 tokens, H = P = 180: 60.1 -> 52.9 us; 20 x 64, 300, 300: 73.0 -> 62.2; 16 x 33, 64, 64: 32.2 -> 26.3; block of 8 x 250, 180, 180:
-// 83.3 -> 72.6; 18 shapes 5.5 % faster on geometric mean; 16 x 64, 256, 256 (256 workgroups) the same.  Launches that fit one round all the same (products3.hip) keep 64 k per K
-// tile, a CU to a workgroup and two register sets: with 32 they were 2 to 7 % slower than that (8 x 1000, 128, 256: 84.3 us with sixteen wavefronts, 87.2 and now 85.4).
+//   Beside small products eight wavefronts of either kind and 64 k per K tile take half as long for an item of 64 x 64, but every workgroup of the launch then has a CU to
+// itself, products of eight wavefronts included, and launches of more workgroups than CUs take two rounds.  Gradient pass in that form and with four of either kind, 32 k and two
+// workgroups per CU: 20 x 64, 300, 300: 48.0 and 39.4 us; 30 x 60, 256, 200: 40.9 and 33.9; 6 x 100, 600, 600: 64.5 and 55.3.  The lines between the forms: products3.hip.
 // ---------------------------------------------------------------------------------------------
 constexpr int TN_STAGES = 2;
-constexpr int TN_PRODUCERS = 4, TN_CONSUMERS = 4, TN_BK = 32;
+constexpr int TN_BK = 32;
 // Tiles by name: 128 = 128 x 128, 96 = 128 x 64 (three planes: half the registers and three quarters of the LDS of a square
-// tile, so that two workgroups share a CU here too), 64 = 64 x 64.
-constexpr int tn_rows(int TB) { return TB == 64 ? 64 : 128; }
+// tile, so that two workgroups share a CU here too), 64 = 64 x 64, 65 = 64 x 64 by eight wavefronts of either kind.
+constexpr int tn_rows(int TB) { return TB < 96 ? 64 : 128; }
 constexpr int tn_cols(int TB) { return TB == 128 ? 128 : 64; }
+constexpr int tn_wavefronts(int TB) { return TB == 65 ? 8 : 4; }
 // (stages, two scales)
 constexpr size_t tn_lds_bytes(int TB, int NPL, int BK) { return (size_t)TN_STAGES * NPL * BK * (tn_rows(TB) + tn_cols(TB)) * 2 + (NPL == 2 ? 16 : 0); }
 
 template <int TB, int NPL, int EDGE, int BK>
 __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, int m0, int n0, int z, int kbeg, int kend, int tid)
 {
-    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), NS = TN_STAGES, NC = TN_CONSUMERS, NP = TN_PRODUCERS, PT = 64 * NP;
+    constexpr int TM = tn_rows(TB), TN = tn_cols(TB), NS = TN_STAGES, NC = tn_wavefronts(TB), KG = NC / 4, NP = NC, PT = 64 * NP;
     // K tiles of global loads in flight per producer (128 x 128 tiles: 3, 4 and 6 measured 1-5 % slower)
-    constexpr int PF = TB == 64 && BK == TN_BK ? 3 : 2;
+    constexpr int PF = TB == 65 ? 4 : TB == 64 && BK == TN_BK ? 3 : 2;
     using LA = SplitLoader<TM, BK, PT, NPL>;
     using LB = SplitLoader<TN, BK, PT, NPL>;
     static_assert(NPL == 2 || NPL == 3, "three bf16 planes or two scaled fp16 planes per operand");
@@ -408,12 +407,13 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
         for (int j = 0; j + 1 < PF; ++j)
             if (kt + j + 1 < nk) step(kt, j);
         __syncthreads();
+        if constexpr (KG > 1) __syncthreads();
         return;
     }
 
     // ---------------------------------------------------------------------- consumers
     const int l = tid & 63;
-    const int wm = wave / 2, wn = wave % 2;
+    const int kg = wave / 4, wm = wave % 4 / 2, wn = wave % 2;
     const int li = l & 31, hh = l >> 5;
     v16f acc[MI][NI];
 #pragma unroll
@@ -423,8 +423,8 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     // A single block per wavefront: the five small products of a k step go into two accumulators of their own.  The large one is then rounded once per
-    // step instead of six times (errors of dB and dC against 64 bits over 18 layers: 0.95 of what they were with two wavefronts that shared out the steps, of dW 0.80;
-    // 1.05 and 1.19 in one accumulator), and the chain of dependent matrix instructions is half as long.
+    // step instead of six times (errors of sums of exact operands against 64 bits: 0.39 to 0.47 of those in one accumulator, 0.37 to 0.46 where two wavefronts share out the
+    // steps), and the chain of dependent matrix instructions is half as long.
     constexpr bool APART = MI == 1 && NI == 1 && NPL == 3;
     v16f small[2];
 #pragma unroll
@@ -434,7 +434,7 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
     // instructions of step s are issued.  At the last step of a K tile the workgroup barrier comes first: it both
     // releases the stage just read (all its reads have completed, they feed the instructions about to be
     // issued) and guarantees that the next stage is filled.
-    constexpr int KS = BK / 16;                   // k steps of a tile
+    constexpr int KS = BK / 16 / KG;              // k steps of a tile per wavefront
     static_assert(KS % 2 == 0, "k steps per tile: even");
     bf16x8 fa[2][MI][NPL], fb[2][NI][NPL];
     auto fetch_frags = [&](int set, int kt, int ks) {
@@ -442,11 +442,11 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) fa[set][i][s] = LA::fragment(st + s * LA::PLANE, wm * WM + i * 32, ks * 16, l);
+            for (int s = 0; s < NPL; ++s) fa[set][i][s] = LA::fragment(st + s * LA::PLANE, wm * WM + i * 32, (kg * KS + ks) * 16, l);
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) fb[set][j][s] = LB::fragment(st + STAGE_A + s * LB::PLANE, wn * WN + j * 32, ks * 16, l);
+            for (int s = 0; s < NPL; ++s) fb[set][j][s] = LB::fragment(st + STAGE_A + s * LB::PLANE, wn * WN + j * 32, (kg * KS + ks) * 16, l);
     };
     // the products of one accumulator keep their order (smallest first); the MI*NI accumulators alternate so that
     // consecutive matrix instructions are independent
@@ -502,6 +502,18 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
     if constexpr (APART) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[0][0][r] += small[0][r] + small[1][r];
+    }
+    if constexpr (KG > 1) {
+        static_assert(MI == 1 && NI == 1 && NPL == 3, "one block per wavefront");
+        float *part = reinterpret_cast<float *>(stages) + wave % 4 * 1024 + l;
+        if (kg == 1) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[r * 64] = acc[0][0][r];
+        }
+        __syncthreads();
+        if (kg == 1) return;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][0][r] += part[r * 64];
     }
     if constexpr (NPL == 2) {
         // one exponent adjustment per element takes both scales off (exact; their sum can leave the exponent range of

@@ -1244,7 +1244,7 @@ __device__ __forceinline__ int gemm_pk_tile(const PkDev &g, unsigned char *smem_
     return -1;
 }
 
-// Tiles of 32 rows: launches that leave a workgroup a CU to itself (beside reductions: two to a CU, on short stages, where one would be slower: products3.hip), whose time is a chain of dependent steps rather than
+// Tiles of 32 rows: launches that leave a workgroup a CU to itself (beside reductions also two to a CU, on short stages: products3.hip), whose time is a chain of dependent steps rather than
 // throughput.  All eight wavefronts load, split and multiply.  A stage is 256 k of all rows, double-buffered in LDS, with one meeting of the
 // workgroup per stage; wavefronts that share 32 columns take every KW-th k step, and their partial tiles are added up as they are stored.
 //   The two wavefronts of a SIMD do the same thing at the same time, so what is not interleaved in each of them does not overlap: the
@@ -1546,8 +1546,10 @@ constexpr size_t pk_lds_bytes(int BM, int BN, int NPL, int epi, int kc)
 }
 
 // One launch carries a product with packed weights and up to two K = T reductions (TNB > 0: their tile is
-// TNB x TNB; absent ones have no slots).  Every problem owns a contiguous range of the slots of every XCD.
-static_assert(TN_PRODUCERS + TN_CONSUMERS == PK_PRODUCERS + PK_CONSUMERS, "a launch's workgroups have one size");
+// that of this name; absent ones have no slots).  Every problem owns a contiguous range of the slots of every XCD.
+// (a reduction may have more wavefronts than a product; the surplus leaves a product's workgroup at once)
+constexpr int pk_threads(int TNB) { return TNB > 0 ? 128 * tn_wavefronts(TNB) : PK_THREADS; }
+constexpr int pk_tn_bk(int TNB, int WPE) { return TNB == 65 || WPE == 2 ? 2 * TN_BK : TN_BK; }
 
 // A pointer that was read as a word: to global memory.  (The compiler knows that of the kernel's arguments themselves.  A load from an address that it does not
 // know it of counts against LDS as well as memory, and every wait for one is a wait for all.)
@@ -1571,7 +1573,7 @@ __device__ __forceinline__ void in_global(GemmDev &g)
 }
 
 template <int BM, int BN, int NPL, int EPI, int TNB, int WPE, bool LEFT>
-__global__ void __launch_bounds__(PK_THREADS, WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
+__global__ void __launch_bounds__(pk_threads(TNB), WPE) gemm_pk_kernel(PkDev g, GemmDev t0, GemmDev t1)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int x = blockIdx.x % 8, q = blockIdx.x / 8, tid = threadIdx.x;
@@ -1587,15 +1589,16 @@ __global__ void __launch_bounds__(PK_THREADS, WPE) gemm_pk_kernel(PkDev g, GemmD
                          "s"(g.by_cpu.mul), "s"(g.by_cpu.shift));
         // (only scans are placed otherwise than in mode 0: left to run time, every product has the code of all modes on its way to the first loads)
         const int tile = EPI < 7 ? x * g.nx + q - g.slot0 : pk_place(g, x, q - g.slot0);
-        if (tile >= g.ntm * g.ntn) return;
+        if (tile >= g.ntm * g.ntn || tid >= PK_THREADS) return;
         const int tm = (int)g.by_ntn(tile), tn = tile - tm * g.ntn;
         auto run = [&](const PkDev &g, int tm, int tid, bool ahead) {
             if constexpr (BM == 32 && BN == 64 && WPE == 4 && TNB == 0) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, 4>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             else if constexpr (BM == 32) {
-                // (two to a CU beside reductions: long stages only where 32 columns have a single k step per wavefront and short stage)
-                constexpr bool ALONE = TNB == 0 || WPE == 2;
-                if ((!ALONE && BN >= 64) || g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, ALONE || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
-                if constexpr (ALONE || BN == 32) return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, ALONE ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                // (two to a CU beside reductions: long stages only where 32 columns have a single k step per wavefront and short stage; beside items of sixteen wavefronts, whose
+                // launches leave a workgroup a CU too, long ones with the registers of two)
+                constexpr bool ALONE = TNB == 0 || WPE == 2, LONG = ALONE || TNB == 65 || BN == 32;
+                if (!LONG || g.K <= PK32_SHORT) return gemm_pk32_tile<BN, NPL, EPI, PK32_SHORT, ALONE || BN < 128 ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
+                if constexpr (LONG) return gemm_pk32_tile<BN, NPL, EPI, PK32_LONG, ALONE ? 4 : 2>(g, smem_raw, tm * BM, tn * BN, tid, ahead);
             } else return gemm_pk_tile<BM, NPL, EPI, LEFT>(g, smem_raw, tm * BM, tn * BN, tile, tid, ahead);
         };
         const int missing = __builtin_amdgcn_readfirstlane(run(g, tm, tid, false));
@@ -1631,7 +1634,7 @@ __global__ void __launch_bounds__(PK_THREADS, WPE) gemm_pk_kernel(PkDev g, GemmD
 #pragma unroll
         for (size_t i = 0; i < sizeof(GemmDev) / 8; ++i) own.w[i] = args[i];
         in_global(own.t);
-        gemm_tn_problem<TNB, NPL, WPE == 2 ? 2 * TN_BK : TN_BK>(own.t, smem_raw, x, q - own.t.slot0, tid);
+        gemm_tn_problem<TNB, NPL, pk_tn_bk(TNB, WPE)>(own.t, smem_raw, x, q - own.t.slot0, tid);
     }
 }
 
@@ -1692,18 +1695,18 @@ hipError_t launch_pk_variant(const GemmArgs &a, const GemmArgs *b, const GemmArg
         }
     }
     if (tn_first) { g.slot0 = (int)slots; slots += g.nx; }
-    constexpr size_t tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL, WPE == 2 ? 2 * TN_BK : TN_BK) : 0;
+    constexpr size_t tnl = TNB > 0 ? tn_lds_bytes(TNB, NPL, pk_tn_bk(TNB, WPE)) : 0;
     constexpr size_t pk = pk_lds_bytes(BM, BN, NPL, EPI, BM == 32 ? PK32_LONG : PK_BK);
     constexpr size_t pk_short = BM == 32 ? pk_lds_bytes(BM, BN, NPL, EPI, PK32_SHORT) : pk;
     constexpr size_t most = pk > tnl ? pk : tnl;
-    const size_t smem = BM == 32 && ((BN >= 64 && WPE == 4) || a.K <= PK32_SHORT) ? (pk_short > tnl ? pk_short : tnl) : most;
+    const size_t smem = BM == 32 && ((BN >= 64 && WPE == 4 && TNB != 65) || a.K <= PK32_SHORT) ? (pk_short > tnl ? pk_short : tnl) : most;
     if (slots <= 0 || slots > 0x7fffffffL / 8) return hipErrorInvalidValue;
     const auto launch = [&](auto left) -> hipError_t {
         auto kern = gemm_pk_kernel<BM, BN, NPL, EPI, TNB, WPE, decltype(left)::value>;
         static std::atomic<bool> raised[KERNEL_MAXDEV];
         const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), most, raised);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(PK_THREADS), smem, s, g, t[0], t[1]);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(8 * slots)), dim3(pk_threads(TNB)), smem, s, g, t[0], t[1]);
         return hipGetLastError();
     };
     // (scans on smaller tiles: launches of at most 4 MiB of states on 32 rows, 32 MiB in the chains of 64)
