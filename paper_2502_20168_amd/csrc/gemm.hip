@@ -27,10 +27,11 @@ static bool takes_tall_tiles(int64_t tall, int64_t low, int64_t items) { return 
 // half as many, and in front only where an item is the longer chain (more rows than the product's K loop).
 // The counts are those that divide 8 or that 8 divides, because then an XCD owns whole slabs or one band of one
 // (tn_place), and a few between; the one whose number of items is nearest in ratio; an item keeps at least 192 (64) rows.
-// One reduction, two planes: fewer, down to 160 items, where the launch with tiles of 128 rows then fits (4800 tokens, H 1024, P 512:
-// 304 + 192 workgroups instead of 600 + 256, each of the two launches 68.5 us against 71; gradient pass, 62 shapes of 2400 ..
-// 11000 tokens: -5 .. +1.5 %, -1.1 % on the mean; the gate's 8448 tokens, H 512: 66.6 against 74.5.  With 144 items and fewer
-// +3 .. +30 %; two reductions beside one product -5 .. +9 %, +2 % on the mean).
+// One reduction, two planes: fewer, down to 160 items, where the launch with tiles of 128 rows then fits (4800 tokens, H 1024, P 512: 304 + 192
+// workgroups instead of 600 + 256, du beside dBbar 68.5 us against 71; gradient pass, 62 shapes of 2400 .. 11000 tokens: -5 .. +1.5 %, -1.1 % on the mean; the
+// gate's 8448 tokens, H 512: 66.6 against 74.5.  With 144 items and fewer +3 .. +30 %; two reductions beside one product -5 .. +9 %, +2 % on the mean).
+// dC beside C^H dy that scans its rows: the product keeps its tiles of 64 rows, and the same fewer slabs are still the faster (17 layers for which the counts
+// differ, gradient pass: -4.0 .. +0.2 %, -2.1 % on the mean; 24 x 200, 1024, 512 with 2, 3, 4, 5, 8 slabs: 172.1, 168.2, 170.5, 167.8, 173.8 us).
 // Measured on 251 launches (every product's reductions at 1000 .. 32768 tokens, H and P from 64 to 1024) against 18 counts in either order:
 // the gradient pass is 0.7 % slower than with the best of them on geometric mean, 8 % at worst.  Some (us; this rule, best, same
 // count with the product first):

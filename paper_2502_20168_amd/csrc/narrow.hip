@@ -5,10 +5,10 @@
 // input projection (32 x 32 blocks of u Bbar^T, a wavefront each), the resettable scan (eight threads per state, eight tokens each), output
 // projection (K = 2P in two halves), D (.) u.
 //   Such a layer is bound by latency: as prep, input projection with its scan and output projection it was three launches of 3.5 to 6.6 us, each a
-// trip to memory and back, and the host took as long to submit them (2.4 us each) as they took to run.  2 x 64 tokens, H = P = 32: 12.2 -> 5.6 us
+// trip to memory and back, and the host took as long to submit them (2.4 us each) as they took to run.  Time per C call, one behind the other: 2 x 64 tokens, H = P = 32: 13.1 -> 5.6 us
 // (by the clock inside: arguments and requests 0.6, discretisation 0.7 while the values come, planes 0.6, products 0.4 and 0.6, scan 1.5, stores 0.4 and the start
-// and end of a launch); 16 x 64, 64, 64: 12.5 -> 7.9; 128 x 33, 64, 64: 14.1 -> 7.9; 1500 x 7, 64, 64: 17.5 -> 8.5.  With every operand requested by the lanes of its
-// fragment instead of in whole lines: 6.6 and 12.5 us.  Errors against 64 bits: 0.87 to 1.03 of what they were.
+// and end of a launch); 16 x 64, 64, 64: 13.0 -> 8.0; 128 x 33, 64, 64: 14.5 -> 8.1; 1500 x 7, 64, 64: 17.7 -> 8.8; 500 x 60, 64, 64: 29.3 -> 16.6.  With every operand
+// requested by the lanes of its fragment instead of in whole lines the first two took 6.6 and 12.5.  Errors against 64 bits: 0.87 to 1.03 of what they were.
 #include "pack.h"
 
 namespace ssm {

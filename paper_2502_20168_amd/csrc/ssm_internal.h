@@ -251,8 +251,9 @@ struct NarrowFwd {
     const float *W; PackJob pack;            // the gate's weights, put into fragment order beside it, or null
     int seqs, layer_blocks; FastDiv by_L;    // sequences of a workgroup; workgroups of the layer (set by the launch)
 };
-// (Its requests take units of four values.  Up to 512 workgroups, two rounds with more than 32 columns or states: 1.2 to 2.7 times as fast as the three
-// launches; 600 x 50 tokens, 64, 64, 600 workgroups with 50 of 64 rows each: 22.5 us and 22.8.)
+// (Its requests take units of four values: rows of at least that many.  Against the other launches of the forward pass 1.2 to 2.8 times as fast.  Up to 512 workgroups, and on
+// three planes only: the range in which the errors were compared, not where it stops paying.  Beyond: 128 x 64 tokens, 64, 64 (two planes) 16.0 us and 8.4; 256 x 32: 14.7, 8.5;
+// 512 x 64, 32, 32: 22.2, 8.0; 600 x 50, 64, 64 (600 workgroups): 29.3, 22.8; 2000 x 50, 32, 32: 47.4, 25.8.)
 inline bool narrow_fwd_shape(int64_t Bt, int64_t L, int64_t H, int64_t P)
 {
     return H >= 4 && P >= 2 && H <= NARROW_MAX && P <= NARROW_MAX && L <= NARROW_MAX && (Bt + NARROW_MAX / L - 1) / (NARROW_MAX / L) <= 512;
