@@ -413,7 +413,7 @@ __device__ __forceinline__ void gemm_tn_tile(const GemmDev &g, __bf16 *stages, i
 
     // ---------------------------------------------------------------------- consumers
     const int l = tid & 63;
-    const int kg = wave / 4, wm = wave % 4 / 2, wn = wave % 2;
+    const int kg = KG > 1 ? wave / 4 : 0, wm = (KG > 1 ? wave % 4 : wave) / 2, wn = wave % 2;
     const int li = l & 31, hh = l >> 5;
     v16f acc[MI][NI];
 #pragma unroll
